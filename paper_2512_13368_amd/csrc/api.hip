@@ -319,10 +319,7 @@ int blossom_attn_bwd_positions(const blossom_params *p, int32_t kv_groups, const
   a.lse_lt = lse_lt; a.lse_st = lse_st; a.dO = dO; a.dQ = dQ; a.dK = dK; a.dV = dV;
   a.d_gate_w = d_gate_w; a.d_gate_b = d_gate_b; a.ws = ws;
   clear_stale_error();
-  // the per-row pass (gate gradient, the constants of each row) reads neither the selection nor K and V
-  launch_bwd(kp, p->dtype, a, kBwdStageGate, (hipStream_t)hip_stream);
-  if (launch_failed()) return launch_status();
-  launch_bwd_positions(kp, p->dtype, a, bwd_carve(kp, p->dtype, ws), kv_groups, (hipStream_t)hip_stream);
+  launch_bwd_positions(kp, p->dtype, a, kv_groups, (hipStream_t)hip_stream);
   return launch_status();
 }
 

@@ -484,48 +484,43 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(const float *__restrict__
   }
 }
 
-// Fixed-order reduction of the partial gate gradients over batch rows and chunks, two levels:
-// level 1 sums kGateSlices contiguous slices of a head's partials, level 2 sums the slices.
-constexpr int kGateSlices = 32;
+// Reduction of the partial gate gradients over batch rows and chunks, in a fixed order: a workgroup owns
+// kGateCols of the 2d+1 columns of one head, 64 threads per column take every 64th partial row in four running
+// sums, and a tree over the 64 closes the column.  One launch: at these sizes (a few MB at most) a second
+// level costs more in launching (4-5 us) than it saves in reading.
+constexpr int kGateCols = 16;
 
-__global__ __launch_bounds__(256) void bwd_gate_reduce1_kernel(const float *__restrict__ partial,
-                                                               float *__restrict__ stage2, int nchunk, KParams p)
+__global__ __launch_bounds__(1024) void bwd_gate_reduce_kernel(const float *__restrict__ partial,
+                                                               float *__restrict__ d_gate_w,
+                                                               float *__restrict__ d_gate_b, int nchunk, KParams p)
 {
+  __shared__ float red[64][kGateCols + 1];
   const int h = blockIdx.x;
-  const int sl = blockIdx.y;
   const int G = 2 * p.d + 1;
   const int N = p.B * nchunk;  // partial rows of this head, ordered by (batch row, chunk)
-  const int per = (N + kGateSlices - 1) / kGateSlices;
-  const int lo = sl * per, hi = min(N, lo + per);
-  // one thread per output column; four independent running sums keep four loads in flight, and
-  // are added in a fixed order at the end
-  for (int c = threadIdx.x; c < G; c += blockDim.x) {
-    float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  const int x = threadIdx.x % kGateCols, y = threadIdx.x / kGateCols;
+  const int c = blockIdx.y * kGateCols + x;
+  float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  if (c < G) {
     auto at = [&](int nn) -> float {
-      const int r = nn / nchunk, ch = nn % nchunk;
+      const int r = nn / nchunk, ch = nn - r * nchunk;
       return partial[(((size_t)r * p.H + h) * nchunk + ch) * G + c];
     };
-    int nn = lo;
-    for (; nn + 4 <= hi; nn += 4) {
-      const float v0 = at(nn), v1 = at(nn + 1), v2 = at(nn + 2), v3 = at(nn + 3);
+    int nn = y;
+    for (; nn + 192 < N; nn += 256) {
+      const float v0 = at(nn), v1 = at(nn + 64), v2 = at(nn + 128), v3 = at(nn + 192);
       acc[0] += v0; acc[1] += v1; acc[2] += v2; acc[3] += v3;
     }
-    for (; nn < hi; ++nn) acc[0] += at(nn);
-    stage2[((size_t)h * kGateSlices + sl) * G + c] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+    for (; nn < N; nn += 64) acc[0] += at(nn);
   }
-}
-
-__global__ __launch_bounds__(256) void bwd_gate_reduce2_kernel(const float *__restrict__ stage2,
-                                                               float *__restrict__ d_gate_w,
-                                                               float *__restrict__ d_gate_b, KParams p)
-{
-  const int h = blockIdx.x;
-  const int G = 2 * p.d + 1;
-  for (int c = threadIdx.x; c < G; c += blockDim.x) {
-    float acc = 0.0f;
-    for (int sl = 0; sl < kGateSlices; ++sl) acc += stage2[((size_t)h * kGateSlices + sl) * G + c];
-    if (c < 2 * p.d) d_gate_w[(size_t)h * 2 * p.d + c] = acc;
-    else if (d_gate_b) d_gate_b[h] = acc;
+  red[y][x] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  for (int half = 32; half >= 1; half >>= 1) {
+    __syncthreads();
+    if (y < half) red[y][x] += red[y + half][x];
+  }
+  if (y == 0 && c < G) {
+    if (c < 2 * p.d) d_gate_w[(size_t)h * 2 * p.d + c] = red[0][x];
+    else if (d_gate_b) d_gate_b[h] = red[0][x];
   }
 }
 
@@ -1024,8 +1019,6 @@ BwdWorkspace bwd_carve(const KParams &p, int dtype, void *ws)
   off = align256(off + BH * p.NB * p.k * sizeof(int));
   w.partial = reinterpret_cast<float *>(base + off);
   off = align256(off + BH * w.nchunk * (2 * p.d + 1) * sizeof(float));
-  w.stage2 = reinterpret_cast<float *>(base + off);
-  off = align256(off + (size_t)p.H * kGateSlices * (2 * p.d + 1) * sizeof(float));
   if (bwd_mfma_supported(p, dtype)) {
     w.g_lt = reinterpret_cast<uint16_t *>(base + off);
     off = align256(off + BH * p.L * p.d * sizeof(uint16_t));
@@ -1042,6 +1035,26 @@ BwdWorkspace bwd_carve(const KParams &p, int dtype, void *ws)
 
 size_t bwd_workspace_bytes(const KParams &p, int dtype) { return bwd_carve(p, dtype, nullptr).total; }
 
+static void launch_gate_reduce(const KParams &p, const BwdArgs &a, const BwdWorkspace &w, int nchunk, hipStream_t st)
+{
+  hipLaunchKernelGGL(bwd_gate_reduce_kernel, dim3((unsigned)p.H, (unsigned)((2 * p.d + kGateCols) / kGateCols)), dim3(1024), 0,
+                     st, w.partial, a.d_gate_w, a.d_gate_b, nchunk, p);
+}
+
+// the resident kernels do the whole backward in one launch; only the sum of the gate gradients over the batch follows
+static void launch_bwd_resident(const KParams &p, int dtype, const BwdArgs &a, unsigned stages, int kv_groups, hipStream_t st)
+{
+  const BwdWorkspace w = bwd_carve(p, dtype, a.ws);
+  launch_bwd_res(p, dtype, a, w, stages, kv_groups, st);
+  if (launch_failed()) return;
+  if (stages & kBwdStageGate) launch_gate_reduce(p, a, w, 1, st);
+}
+
+void launch_bwd_positions(const KParams &p, int dtype, const BwdArgs &a, int kv_groups, hipStream_t st)
+{
+  launch_bwd_resident(p, dtype, a, kBwdStageAll, kv_groups, st);
+}
+
 template <typename T, int D>
 static void launch_bwd_t(const KParams &p, int dtype, const BwdArgs &a, unsigned stages, hipStream_t st)
 {
@@ -1053,10 +1066,8 @@ static void launch_bwd_t(const KParams &p, int dtype, const BwdArgs &a, unsigned
     BLOSSOM_LAUNCH((bwd_prep_kernel<T, D>), dim3(BH * w.nchunk), dim3(256), 0, st,
                        (const float *)a.o_lt, (const float *)a.o_st, (const T *)a.dO, a.valid_len, a.gate_w,
                        a.gate_b, w.rowstat, w.partial, a.lse_lt, a.lse_st, w.g_lt, w.g_st, w.rowI_lt, w.rowI_st, p);
-    BLOSSOM_LAUNCH(bwd_gate_reduce1_kernel, dim3((unsigned)p.H, kGateSlices), dim3(256), 0, st, w.partial,
-                       w.stage2, w.nchunk, p);
-    BLOSSOM_LAUNCH(bwd_gate_reduce2_kernel, dim3((unsigned)p.H), dim3(256), 0, st, w.stage2, a.d_gate_w,
-                       a.d_gate_b, p);
+    launch_gate_reduce(p, a, w, w.nchunk, st);
+    if (launch_failed()) return;
   }
   if (stages & kBwdStageInverse) {
     const int W = p.NB <= kInvWavesMaxNB ? kInvWaves : 1;
@@ -1067,11 +1078,6 @@ static void launch_bwd_t(const KParams &p, int dtype, const BwdArgs &a, unsigned
   if (mfma) {
     if (launch_failed()) return;
     launch_bwd_mfma(p, a, w, stages, st);
-    return;
-  }
-  if (bwd_res_supported(p, dtype)) {
-    if (launch_failed()) return;
-    launch_bwd_res(p, dtype, a, w, stages, st);
     return;
   }
   const size_t lds = 2 * (size_t)p.b * (D + 1) * sizeof(float);  // two tiles of b rows
@@ -1111,6 +1117,10 @@ static void launch_bwd_t(const KParams &p, int dtype, const BwdArgs &a, unsigned
 
 void launch_bwd(const KParams &p, int dtype, const BwdArgs &a, unsigned stages, hipStream_t st)
 {
+  if (bwd_res_supported(p, dtype)) {
+    launch_bwd_resident(p, dtype, a, stages, 0, st);
+    return;
+  }
   with_head_dim(p.d, [&](auto dim) {
     constexpr int D = decltype(dim)::value;
     if (dtype == 0) launch_bwd_t<float, D>(p, dtype, a, stages, st);

@@ -61,8 +61,7 @@ struct BwdWorkspace {
   int *offs;         // [B*H,(NB+1)] inverse selection list: offsets
   int *items;        // [B*H,NB*k]   inverse selection list: query blocks per key block, in a fixed order;
                      //              bit kInvFewShift marks a query block whose long-term rows may see few keys
-  float *partial;    // [B*H*nchunk,(2d+1)] partial gate-weight gradients
-  float *stage2;     // [H,slices,(2d+1)] second reduction level
+  float *partial;    // [B*H*nchunk,(2d+1)] partial gate-weight gradients (resident kernels: one row per (row, head))
   // matrix-core path only: per-branch upstream gradient dO_x = a_x*dO + dz*Wg_x in bf16, and per
   // row the three-term bf16 splits of (-lse_x*log2(e), -dO_x.o_x) as (hi|mid<<16, lo) pairs
   uint16_t *g_lt, *g_st;      // [B*H*L,d]
@@ -95,6 +94,8 @@ constexpr int kInvFewShift = 30;
 constexpr int kInvBlockMask = (1 << kInvFewShift) - 1;
 enum : unsigned { kBwdStageGate = 1u, kBwdStageInverse = 2u, kBwdStageDQ = 4u, kBwdStageDKV = 8u, kBwdStageAll = 15u };
 void launch_bwd(const KParams &p, int dtype, const BwdArgs &a, unsigned stages, hipStream_t st);
+// the backward under a per-position selection (resident kernels only): a.sel = sel_pos [B,G,L,k]
+void launch_bwd_positions(const KParams &p, int dtype, const BwdArgs &a, int kv_groups, hipStream_t st);
 
 // mfma_fwd.hip: matrix-core forward for bf16, d = 64, b in {32, 64}
 bool fwd_mfma_supported(const KParams &p, int dtype);
@@ -102,15 +103,15 @@ void launch_fwd_mfma(const KParams &p, const FwdArgs &a, hipStream_t st);
 // mfma_fwd4.hip: the four-wavefront forward for block size 64 (launch_fwd_mfma dispatches to it)
 void launch_fwd_mfma4(const KParams &p, const FwdArgs &a, hipStream_t st);
 
-// mfma_f32.hip: forward, dQ and dK/dV on the fp32 matrix instructions for short sequences (fp32 or bf16
+// mfma_f32.hip: forward and backward on the fp32 matrix instructions for short sequences (fp32 or bf16
 // storage, d in {8, 16, 32}, b in {8, 16}, the streamed tensors of a head resident in LDS)
 bool fwd_res_supported(const KParams &p, int dtype);
 void launch_fwd_res(const KParams &p, int dtype, const FwdArgs &a, hipStream_t st);
 bool fwd_positions_supported(const KParams &p, int dtype);
 bool bwd_res_supported(const KParams &p, int dtype);
 bool bwd_positions_supported(const KParams &p, int dtype);
-void launch_bwd_positions(const KParams &p, int dtype, const BwdArgs &a, const BwdWorkspace &w, int kv_groups, hipStream_t st);
-void launch_bwd_res(const KParams &p, int dtype, const BwdArgs &a, const BwdWorkspace &w, unsigned stages, hipStream_t st);
+void launch_bwd_res(const KParams &p, int dtype, const BwdArgs &a, const BwdWorkspace &w, unsigned stages, int kv_groups,
+                    hipStream_t st);
 
 // mfma_bwd.hip: matrix-core dQ and dK/dV for bf16, d = 64, b in {32, 64}
 bool bwd_mfma_supported(const KParams &p, int dtype);
