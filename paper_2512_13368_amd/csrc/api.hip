@@ -59,6 +59,7 @@ int check_params(const blossom_params *p, KParams *kp)
   kp->scale = p->softmax_scale > 0.0f ? p->softmax_scale : 1.0f / std::sqrt((float)p->d);
   kp->sblk = p->stis_mode >= 1 ? (p->stis_block > 0 ? p->stis_block : p->block) : 0;
   kp->bidir = p->stis_mode == 2;
+  kp->sblk_inv = kp->sblk > 0 ? 1.0f / (float)kp->sblk : 0.0f;
   kp->last_lo = kp->sblk > 0 ? p->L - kp->sblk : 0x3FFFFFFF;
   kp->nq = p->last_block_only ? 1 : (int)NB;
   kp->rope_cos = nullptr;
@@ -199,7 +200,7 @@ int blossom_attn_fwd(const blossom_params *p, const void *Q, const void *K, cons
   a.dense = 0;
   clear_stale_error();
   if (fwd_mfma_supported(kp, p->dtype)) launch_fwd_mfma(kp, a, (hipStream_t)hip_stream);
-  else if (fwd_res_supported(kp, p->dtype)) launch_fwd_res(kp, p->dtype, a, (hipStream_t)hip_stream);
+  else if (small_supported(kp)) launch_fwd_small(kp, p->dtype, a, (hipStream_t)hip_stream);
   else launch_fwd_generic(kp, p->dtype, a, (hipStream_t)hip_stream);
   return launch_status();
 }
@@ -282,7 +283,7 @@ int blossom_attn_fwd_positions(const blossom_params *p, int32_t kv_groups, const
   if (!Q || !K || !V || !valid_len || !sel_pos || !gate_w || !O) return BLOSSOM_ERR_NULL;
   if (!aligned16(Q) || !aligned16(K) || !aligned16(V) || !aligned16(O)) return BLOSSOM_ERR_ALIGN;
   if ((o_lt && !aligned16(o_lt)) || (o_st && !aligned16(o_st))) return BLOSSOM_ERR_ALIGN;
-  if (!fwd_positions_supported(kp, p->dtype)) return BLOSSOM_ERR_UNSUPPORTED;
+  if (!fwd_positions_supported(kp)) return BLOSSOM_ERR_UNSUPPORTED;
   FwdArgs a{};
   a.Q = Q; a.K = K; a.V = V; a.valid_len = valid_len; a.sel = sel_pos;
   a.gate_w = gate_w; a.gate_b = gate_b; a.O = O;
@@ -290,7 +291,7 @@ int blossom_attn_fwd_positions(const blossom_params *p, int32_t kv_groups, const
   a.dense = 0;
   a.kv_groups = kv_groups;
   clear_stale_error();
-  launch_fwd_res(kp, p->dtype, a, (hipStream_t)hip_stream);
+  launch_fwd_small(kp, p->dtype, a, (hipStream_t)hip_stream);
   return launch_status();
 }
 
@@ -310,7 +311,7 @@ int blossom_attn_bwd_positions(const blossom_params *p, int32_t kv_groups, const
   if (!aligned16(Q) || !aligned16(K) || !aligned16(V) || !aligned16(o_lt) || !aligned16(o_st) || !aligned16(dO) ||
       !aligned16(dQ) || !aligned16(dK) || !aligned16(dV))
     return BLOSSOM_ERR_ALIGN;
-  if (!bwd_positions_supported(kp, p->dtype)) return BLOSSOM_ERR_UNSUPPORTED;
+  if (!bwd_positions_supported(kp)) return BLOSSOM_ERR_UNSUPPORTED;
   rc = check_ws(kp, p->dtype, BLOSSOM_WS_BWD, ws, ws_bytes);
   if (rc) return rc;
   BwdArgs a{};
@@ -367,7 +368,7 @@ int blossom_dense_causal_fwd(const blossom_params *p, const void *Q, const void 
   a.dense = 1;
   clear_stale_error();
   if (fwd_mfma_supported(kp, p->dtype)) launch_fwd_mfma(kp, a, (hipStream_t)hip_stream);
-  else if (fwd_res_supported(kp, p->dtype)) launch_fwd_res(kp, p->dtype, a, (hipStream_t)hip_stream);
+  else if (small_supported(kp)) launch_fwd_small(kp, p->dtype, a, (hipStream_t)hip_stream);
   else launch_fwd_generic(kp, p->dtype, a, (hipStream_t)hip_stream);
   return launch_status();
 }

@@ -15,6 +15,7 @@ struct KParams {
   int NB;       // ceil(L / b)
   float scale;  // softmax scale (already resolved, > 0)
   int sblk;     // mask block size of the full short-term mask (Eq. 15); 0 = local window only
+  float sblk_inv;  // 1 / sblk (0 without Eq. 15): mask block of a position = (int)((position + 0.5) * sblk_inv)
   int last_lo;  // first of the last sblk positions (L - sblk); INT_MAX/2 when sblk == 0
   int nq;       // query blocks walked by select and forward: NB, or 1 (the last one) in serving mode
   int bidir;    // 1: bidirectional form (Eq. 15 as printed, no causal mask in either branch); sblk > 0 then
@@ -29,9 +30,7 @@ __host__ __device__ __forceinline__ bool is_pow2(int x) { return x >= 1 && (x & 
 __host__ __device__ __forceinline__ bool holds_pow2(int lo, int hi)
 {
   if (hi < 1) return false;
-  int top = 1;
-  while (top <= hi / 2) top *= 2;  // largest power of two <= hi
-  return top >= lo;
+  return (1 << (31 - __builtin_clz((unsigned)hi))) >= lo;  // the largest power of two <= hi
 }
 // (symmetric in i - j: the causal callers only ever ask about j <= i)
 __device__ __forceinline__ bool st_visible(const KParams &p, int i, int j)

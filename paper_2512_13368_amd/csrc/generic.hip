@@ -1033,26 +1033,30 @@ BwdWorkspace bwd_carve(const KParams &p, int dtype, void *ws)
   return w;
 }
 
-size_t bwd_workspace_bytes(const KParams &p, int dtype) { return bwd_carve(p, dtype, nullptr).total; }
-
-static void launch_gate_reduce(const KParams &p, const BwdArgs &a, const BwdWorkspace &w, int nchunk, hipStream_t st)
+size_t bwd_workspace_bytes(const KParams &p, int dtype)
 {
-  hipLaunchKernelGGL(bwd_gate_reduce_kernel, dim3((unsigned)p.H, (unsigned)((2 * p.d + kGateCols) / kGateCols)), dim3(1024), 0,
-                     st, w.partial, a.d_gate_w, a.d_gate_b, nchunk, p);
+  SmallWs w;
+  return small_supported(p) ? small_ws_bytes(p, &w, nullptr) : bwd_carve(p, dtype, nullptr).total;
 }
 
-// the resident kernels do the whole backward in one launch; only the sum of the gate gradients over the batch follows
-static void launch_bwd_resident(const KParams &p, int dtype, const BwdArgs &a, unsigned stages, int kv_groups, hipStream_t st)
+static void launch_gate_reduce(const KParams &p, const BwdArgs &a, const float *partial, int nchunk, hipStream_t st)
 {
-  const BwdWorkspace w = bwd_carve(p, dtype, a.ws);
-  launch_bwd_res(p, dtype, a, w, stages, kv_groups, st);
+  hipLaunchKernelGGL(bwd_gate_reduce_kernel, dim3((unsigned)p.H, (unsigned)((2 * p.d + kGateCols) / kGateCols)), dim3(1024), 0,
+                     st, partial, a.d_gate_w, a.d_gate_b, nchunk, p);
+}
+
+static void launch_bwd_small_all(const KParams &p, int dtype, const BwdArgs &a, unsigned stages, int kv_groups, hipStream_t st)
+{
+  SmallWs w;
+  small_ws_bytes(p, &w, reinterpret_cast<char *>(a.ws));
+  launch_bwd_small(p, dtype, a, w, stages, kv_groups, st);
   if (launch_failed()) return;
-  if (stages & kBwdStageGate) launch_gate_reduce(p, a, w, 1, st);
+  if (stages & kBwdStageGate) launch_gate_reduce(p, a, w.partial, small_partial_rows(p, kv_groups), st);
 }
 
 void launch_bwd_positions(const KParams &p, int dtype, const BwdArgs &a, int kv_groups, hipStream_t st)
 {
-  launch_bwd_resident(p, dtype, a, kBwdStageAll, kv_groups, st);
+  launch_bwd_small_all(p, dtype, a, kBwdStageAll, kv_groups, st);
 }
 
 template <typename T, int D>
@@ -1066,7 +1070,7 @@ static void launch_bwd_t(const KParams &p, int dtype, const BwdArgs &a, unsigned
     BLOSSOM_LAUNCH((bwd_prep_kernel<T, D>), dim3(BH * w.nchunk), dim3(256), 0, st,
                        (const float *)a.o_lt, (const float *)a.o_st, (const T *)a.dO, a.valid_len, a.gate_w,
                        a.gate_b, w.rowstat, w.partial, a.lse_lt, a.lse_st, w.g_lt, w.g_st, w.rowI_lt, w.rowI_st, p);
-    launch_gate_reduce(p, a, w, w.nchunk, st);
+    launch_gate_reduce(p, a, w.partial, w.nchunk, st);
     if (launch_failed()) return;
   }
   if (stages & kBwdStageInverse) {
@@ -1117,8 +1121,8 @@ static void launch_bwd_t(const KParams &p, int dtype, const BwdArgs &a, unsigned
 
 void launch_bwd(const KParams &p, int dtype, const BwdArgs &a, unsigned stages, hipStream_t st)
 {
-  if (bwd_res_supported(p, dtype)) {
-    launch_bwd_resident(p, dtype, a, stages, 0, st);
+  if (small_supported(p)) {
+    launch_bwd_small_all(p, dtype, a, stages, 0, st);
     return;
   }
   with_head_dim(p.d, [&](auto dim) {

@@ -61,7 +61,7 @@ struct BwdWorkspace {
   int *offs;         // [B*H,(NB+1)] inverse selection list: offsets
   int *items;        // [B*H,NB*k]   inverse selection list: query blocks per key block, in a fixed order;
                      //              bit kInvFewShift marks a query block whose long-term rows may see few keys
-  float *partial;    // [B*H*nchunk,(2d+1)] partial gate-weight gradients (resident kernels: one row per (row, head))
+  float *partial;    // [B*H*nchunk,(2d+1)] partial gate-weight gradients
   // matrix-core path only: per-branch upstream gradient dO_x = a_x*dO + dz*Wg_x in bf16, and per
   // row the three-term bf16 splits of (-lse_x*log2(e), -dO_x.o_x) as (hi|mid<<16, lo) pairs
   uint16_t *g_lt, *g_st;      // [B*H*L,d]
@@ -103,15 +103,22 @@ void launch_fwd_mfma(const KParams &p, const FwdArgs &a, hipStream_t st);
 // mfma_fwd4.hip: the four-wavefront forward for block size 64 (launch_fwd_mfma dispatches to it)
 void launch_fwd_mfma4(const KParams &p, const FwdArgs &a, hipStream_t st);
 
-// mfma_f32.hip: forward and backward on the fp32 matrix instructions for short sequences (fp32 or bf16
-// storage, d in {8, 16, 32}, b in {8, 16}, the streamed tensors of a head resident in LDS)
-bool fwd_res_supported(const KParams &p, int dtype);
-void launch_fwd_res(const KParams &p, int dtype, const FwdArgs &a, hipStream_t st);
-bool fwd_positions_supported(const KParams &p, int dtype);
-bool bwd_res_supported(const KParams &p, int dtype);
-bool bwd_positions_supported(const KParams &p, int dtype);
-void launch_bwd_res(const KParams &p, int dtype, const BwdArgs &a, const BwdWorkspace &w, unsigned stages, int kv_groups,
-                    hipStream_t st);
+// mfma_f32.hip: forward and backward on the fp32 matrix instructions for small heads (fp32 or bf16 storage,
+// d in {8, 16, 32}, b in {8, 16}, L <= 16384)
+struct SmallWs {
+  float *rowc;           // [B*H,NT,6,16]  per query tile of 16 rows: alpha, dz, D_lt, D_st, lse_lt and lse_st in log2 units
+  unsigned *tile_words;  // [B*G,NT,words] long-term key tiles of each query tile
+  unsigned *sel_bits;    // selection bits per query block (block size 8) or per position
+  float *partial;        // [B*H,small_partial_rows,(2d+1)] partial gate-weight gradients
+};
+bool small_supported(const KParams &p);
+void launch_fwd_small(const KParams &p, int dtype, const FwdArgs &a, hipStream_t st);
+bool fwd_positions_supported(const KParams &p);
+bool bwd_positions_supported(const KParams &p);
+size_t small_ws_bytes(const KParams &p, SmallWs *w, char *base);  // carves w from base, returns the total
+int small_partial_rows(const KParams &p, int kv_groups);
+void launch_bwd_small(const KParams &p, int dtype, const BwdArgs &a, const SmallWs &w, unsigned stages, int kv_groups,
+                      hipStream_t st);
 
 // mfma_bwd.hip: matrix-core dQ and dK/dV for bf16, d = 64, b in {32, 64}
 bool bwd_mfma_supported(const KParams &p, int dtype);

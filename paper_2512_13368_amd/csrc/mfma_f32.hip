@@ -1,46 +1,48 @@
-// Forward and backward on the fp32 matrix instructions for short sequences (Eq. 1 under the two branch
-// masks, Eq. 16-19 and their chain rule, and the same-style dense causal comparison): fp32 or bf16
-// storage, d in {8, 16, 32}, block size 8 or 16, sequences whose streamed tensors fit the LDS of a
-// workgroup.  That is the paper's own regime (Sec. 4.1, Appendix E: histories of at most 200 items,
-// hidden size 64 over 2 to 8 heads, selection block 16); the 64 x 64 bf16 tiles of the long-sequence
-// kernels would be mostly padding there.
+// Forward and backward on the fp32 matrix instructions for small heads (Eq. 1 under the two branch masks,
+// Eq. 16-19 and their chain rule, and the same-style dense causal comparison): fp32 or bf16 storage,
+// d in {8, 16, 32}, block size 8 or 16.  That is the paper's own regime (Sec. 4.1, Appendix E: hidden size 64
+// or 128 over 2 to 8 heads, selection block 16, histories of 200 items, up to 2000 in the efficiency study);
+// the 64 x 64 bf16 tiles of the other matrix-core kernels would be mostly padding there.
 //
-// One workgroup per (row, head), or per (row, key/value group) in the per-position form.  Positions are
-// cut into 16-row tiles of v_mfma_f32_16x16x4_f32 (true fp32 products accumulated in fp32) whatever the
-// block size; a selection block of 8 is half a tile and the selection is tested per element.  The tensors
-// that a walk streams are staged once, as fp32, from the first valid tile on, into LDS rows of d + 4 floats
-// (both operand read patterns below are then bank-conflict free); each wavefront walks whole tiles of its
-// own with no barrier and no staging inside the walks.
+// Positions are cut into 16-row tiles of v_mfma_f32_16x16x4_f32 (true fp32 products accumulated in fp32)
+// whatever the block size; a selection block of 8 is half a tile and the selection is tested per element.
+// A wavefront takes one query tile (forward, dQ) or one key tile (dK/dV) at a time.  Heads that fit a workgroup's LDS
+// (rows of d + 4 floats, two workgroups per CU: L up to about 200 at d = 32, 450 at d = 16, 750 at d = 8) are staged
+// there, and the backward of such a head is one kernel that reads every tensor once; longer ones stream the tiles
+// they walk from memory (L1 and L2) into operand registers, with neither barriers nor a limit on the length.
 //
 // BOTH BRANCHES IN ONE WALK.  The branches share the logits, so a walk visits the union of the two tile
 // sets once and applies two masks to one product: forward forms S once and adds P_lt V and P_st V;
-// backward needs S, dO V^T, and, because dS = dS_lt + dS_st multiplies the same K and Q, one product each
-// for dQ, dK and dV (dV: the coefficient of dO is a_lt P_lt + a_st P_st, the gate part is a rank-one term
-// per key).  Which tiles a walk visits comes from bit masks over tiles (one pair of 64-bit words per query
-// tile and per key tile), built once per workgroup from the selection rows and the mask geometry.
+// backward needs one product each for dQ, dK and dV, because dS = dS_lt + dS_st multiplies the same K and Q (dV:
+// the coefficient of dO is a_lt P_lt + a_st P_st, the gate part is a rank-one term per key).  The tiles of a walk
+// come from bit words over tiles: the short-term ones by a ballot of the mask geometry, the long-term ones
+// from the selection rows.
 //   forward: S^T = K Q^T, keys as the M dimension: lane (q = lane % 16, g = lane / 16) owns query column
 //            q and the logits of keys 4g .. 4g+3 of the tile; O^T += V^T P^T with P^T = the accumulator of
 //            S^T as it stands (step r contracts key 4g + r of every lane group).
 //   dQ:      same orientation: S^T and G_x^T = V dO_x^T leave the matrix cores in the layout in which
 //            dS^T is the B operand of dQ^T += K^T dS^T.
-//   dK/dV:   queries as the M dimension (lane (key, g): key column, query rows 4g .. 4g+3); the per-row
-//            constants are 16-byte broadcast reads from LDS, the lane's own K and V rows are registers.
+//   dK/dV:   queries as the M dimension (lane (key, g): key column, query rows 4g .. 4g+3).
 // A contraction over channels takes channel (d/4)*g + s in step s, so that a lane's operands are d/4
-// consecutive floats: one or two 16-byte LDS reads per tile instead of d/4 reads.
+// consecutive elements: one or two 16-byte loads per tile.
 //
-// EXPONENTIALS WITHOUT A RUNNING MAXIMUM.  |logit| <= |q| |k|: where the largest such bound of a query tile is
-// at most 60 (in log2 units) exp2 of the logits themselves neither overflows nor loses accuracy in fp32, so
-// neither a maximum nor a rescale is needed and the branches share one exponential.  Otherwise the walk runs
-// once more beforehand for the two row maxima.
+// EXPONENTIALS WITHOUT A RUNNING MAXIMUM.  A walk takes exp2 of the logits themselves, one exponential for both
+// branches, and keeps the largest |logit| it met: up to 60 (log2 units) nothing overflows or loses accuracy
+// in fp32.  Beyond that (or if an output left fp32's range) the walk is repeated with the two row maxima,
+// found by a walk of their own, as references.
 //
-// Backward is one kernel: per-row gate pass (alpha, dz, D_x and the gate-weight gradients of its (row, head)),
-// dK/dV, then dQ; K, V, Q, dO, o_lt and o_st come from memory once.  With dO_x = a_x*dO + dz*Wg_x the upstream
-// gradient of branch x (a_lt = alpha, a_st = 1 - alpha) and D_x = dO_x.o_x:
+// The dQ kernel also does the per-row gate pass (alpha, dz, D_x and the gate-weight gradients): a wavefront has
+// its query rows' dO at hand.  It leaves the row constants and the long-term tile words of every query tile for the
+// dK/dV kernel, which finds the query tiles of a key tile by a ballot over those words (no inverse lists).
+// With dO_x = a_x*dO + dz*Wg_x the upstream gradient of branch x (a_lt = alpha, a_st = 1 - alpha) and D_x = dO_x.o_x:
 //   P_ij = exp(scale*q_i.k_j - lse_x,i),  dS_ij = P_ij * (dO_x,i.v_j - D_x,i),
 //   dQ_i = scale * sum_j dS_ij k_j,  dK_j = scale * sum_i dS_ij q_i,  dV_j = sum_i P_ij dO_x,i.
 // Masks (the causal window, or all of Eq. 15 in its causal or its bidirectional form), gate, outputs and padding
 // rules are those of the scalar kernels of generic.hip; shapes outside this range stay there.
+#include <algorithm>
+
 #include "launch.h"
+#include "mfma_common.h"
 
 namespace blossom {
 
@@ -52,16 +54,14 @@ constexpr float kLog2eF = 1.4426950408889634f;
 constexpr float kLn2F = 0.6931471805599453f;
 constexpr float kNegInfF = -__builtin_huge_valf();
 constexpr float kHugeF = 1.0e30f;
-constexpr size_t kResLdsMax = 160 * 1024;
 constexpr int kTile = 16;
-constexpr int kMaxTiles = 64;        // tile masks are 64-bit words
+constexpr int kMaxWaves = 8;          // wavefronts per workgroup at most
 constexpr float kSmallLogit = 60.0f;  // log2 units: exp2 of such a logit, and sums over a row, stay far inside fp32
 
 template <int D>
 struct Geo {
   static constexpr int CPL = D / 4;            // channels per lane of a channel contraction: CPL*g .. CPL*g + CPL-1
   static constexpr int NMB = (D + 15) / 16;    // 16-channel output blocks (d = 8 fills half of one)
-  static constexpr int LDR = D + 4;            // floats per staged row (12, 20 or 36: conflict free, 16-byte rows)
 };
 
 // CPL consecutive elements as floats
@@ -80,35 +80,6 @@ __device__ __forceinline__ void load_n(const float *p, float (&o)[N])
   }
 }
 template <int N>
-__device__ __forceinline__ void load_n(const bf16_t *p, float (&o)[N])
-{
-  if constexpr (N == 2) {
-    const uint32_t v = *reinterpret_cast<const uint32_t *>(p);
-    o[0] = __uint_as_float(v << 16);
-    o[1] = __uint_as_float(v & 0xFFFF0000u);
-  } else if constexpr (N == 4) {
-    load4(p, o);
-  } else {
-    const uint4 v = *reinterpret_cast<const uint4 *>(p);
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      o[2 * i] = __uint_as_float(w[i] << 16);
-      o[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
-    }
-  }
-}
-template <int N>
-__device__ __forceinline__ void store_n(float *p, const float (&o)[N])
-{
-  if constexpr (N == 2) {
-    *reinterpret_cast<float2 *>(p) = make_float2(o[0], o[1]);
-  } else {
-#pragma unroll
-    for (int i = 0; i < N; i += 4) *reinterpret_cast<float4 *>(p + i) = make_float4(o[i], o[i + 1], o[i + 2], o[i + 3]);
-  }
-}
-template <int N>
 __device__ __forceinline__ void zero_n(float (&o)[N])
 {
 #pragma unroll
@@ -121,21 +92,56 @@ __device__ __forceinline__ float dot_n(const float (&a)[N], const float (&b)[N],
   for (int i = 0; i < N; ++i) c = fmaf(a[i], b[i], c);
   return c;
 }
-// sum over the four lane groups of a column
-__device__ __forceinline__ float sum_g(float x)
+// reciprocal to fp32 accuracy: the hardware estimate (1 ulp) and one Newton step; x is a normal number
+__device__ __forceinline__ float recip(float x)
 {
-  x += __shfl_xor(x, 16);
-  return x + __shfl_xor(x, 32);
+  const float r = __builtin_amdgcn_rcpf(x);
+  return fmaf(r, fmaf(-x, r, 1.0f), r);
+}
+__device__ __forceinline__ float sigmoid(float z)
+{
+  const float e = __builtin_amdgcn_exp2f(fminf(-z * kLog2eF, 126.0f));
+  return recip(1.0f + e);
 }
 
-// A operand of a product whose contraction runs over the 16 rows of a staged tile: element r is row 4g + r,
-// column `col` (d = 8: columns 8..15 hold anything, their output rows are never stored)
-template <int LDR>
-__device__ __forceinline__ void col_frag(const float *tile, int g, int col, float (&o)[4])
+// sum and maximum over the four lane groups of a column (rows 0/1, 2/3 then halves of the wavefront swapped in
+// registers), sum over the 16 columns of a lane group (rotations inside a row of 16 lanes)
+typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
+template <typename F>
+__device__ __forceinline__ float fold_g(float x, F &&f)
 {
-  const float *p = tile + 4 * g * LDR + col;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) o[r] = p[r * LDR];
+  const unsigned u = __float_as_uint(x);
+  const u32x2_t a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const unsigned v = __float_as_uint(f(__uint_as_float(a[0]), __uint_as_float(a[1])));
+  const u32x2_t b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return f(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float sum_g(float x)
+{
+  return fold_g(x, [](float a, float b) { return a + b; });
+}
+__device__ __forceinline__ float max_g(float x)
+{
+  return fold_g(x, [](float a, float b) { return fmaxf(a, b); });
+}
+template <int N>
+__device__ __forceinline__ float row_ror(float x)
+{
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + N, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float sum_row(float x)
+{
+  x += row_ror<8>(x);
+  x += row_ror<4>(x);
+  x += row_ror<2>(x);
+  return x + row_ror<1>(x);
+}
+__device__ __forceinline__ float max_row(float x)
+{
+  x = fmaxf(x, row_ror<8>(x));
+  x = fmaxf(x, row_ror<4>(x));
+  x = fmaxf(x, row_ror<2>(x));
+  return fmaxf(x, row_ror<1>(x));
 }
 
 // lane (col, g) holds channels 16*mb + 4g + r of one row in a[mb][r]: stores those below D
@@ -171,112 +177,329 @@ __device__ __forceinline__ void store_grad_row(T *dst_row, const f32x4 (&a)[Geo<
     }
 }
 
-// zeros for the `count` elements from dst on (whole rows: a multiple of 8 elements, 16-byte aligned)
+// zeros for the `count` elements from dst on, by one wavefront (whole rows: a multiple of 8 elements, 16-byte aligned)
 template <typename T>
-__device__ __forceinline__ void zero_fill(T *dst, int count, int tid, int nthr)
+__device__ __forceinline__ void zero_fill(T *dst, int count, int lane)
 {
   uint4 *q = reinterpret_cast<uint4 *>(dst);
   const int pieces = count * (int)sizeof(T) / 16;
-  for (int i = tid; i < pieces; i += nthr) q[i] = make_uint4(0u, 0u, 0u, 0u);
+  for (int i = lane; i < pieces; i += 64) q[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
-// ---- what a workgroup knows about its masks -----------------------------------------------------------------
-// In LDS, as 32-bit words:
-//   tm_lt, tm_st [NT][2]   bit T: query tile I walks key tile T in the branch
-//   cm_lt, cm_st [NT][2]   bit I: key tile T is walked by query tile I            (backward)
-//   selw [NW][SR]          selection bits: word w of row x, bit e: key block 32*w + e is selected; x is a query block,
-//                          or a position in the per-position form
-//   kid [16*NT]            mask block of each position (Eq. 15)
-struct MaskLayout {
-  int NT, NW, SR;
-  int tm_lt, tm_st, cm_lt, cm_st, selw, kid, words;
+
+__device__ __forceinline__ unsigned abs_diff(int a, int b)  // both non-negative
+{
+  unsigned d;
+  asm("v_sad_u32 %0, %1, %2, 0" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
+
+// mask block of position pos + r (Eq. 15): (pos + r + 1/2) / sblk, exact in fp32 while positions stay below 2^22 (the
+// quotient is at least 1/(2 sblk) away from a whole number); all zero without Eq. 15, where no two blocks are then
+// a power of two apart
+__device__ __forceinline__ int mask_block(const KParams &p, int pos, int r = 0)
+{
+  return (int)fmaf((float)pos, p.sblk_inv, ((float)r + 0.5f) * p.sblk_inv);
+}
+
+// short-term visibility of (query i, key j + r) that the causal and validity tests let through (those make the difference
+// non-negative in the causal form, so its absolute value serves both forms); plain bit operations, no branches.
+// UNIT: no mask block of Eq. 15, or one of a single position.
+template <bool UNIT>
+__device__ __forceinline__ bool st_sees(const KParams &p, int i, int j, int kid_i, int kid_j, bool last)
+{
+  const unsigned d = abs_diff(i, j);
+  const bool pow2 = UNIT ? (__popc(d) == 1) & (p.sblk != 0) : __popc(abs_diff(kid_i, kid_j)) == 1;
+  return (d < (unsigned)p.w) | pow2 | last;
+}
+
+// may any query of tile I see any key of tile J in the short-term branch (J <= I in the causal form)?
+__device__ __forceinline__ bool st_reaches(const KParams &p, int I, int J)
+{
+  const int hi = max(I, J) * kTile, lo = min(I, J) * kTile;
+  const bool window = hi - lo - (kTile - 1) < p.w;
+  if (p.sblk == 0) return window;
+  // largest mask-block distance of the two tiles' positions, and the largest power of two in it, against the smallest
+  const int top = mask_block(p, hi, kTile - 1) - mask_block(p, lo);
+  const int bottom = mask_block(p, hi) - mask_block(p, lo, kTile - 1);
+  const int pow2 = 1 << (31 - __clz(top | 1));
+  return window | ((top >= 1) & (pow2 >= bottom)) | (J * kTile + kTile - 1 >= p.last_lo);
+}
+
+// A tensor slice behind a buffer descriptor: loads take 32-bit byte offsets (no address arithmetic in vector registers)
+// and return zeros past the end of the slice, which is how the rows of the last, partial tile read.
+constexpr unsigned kNowhere = 0xFFFFF000u;  // a byte offset past every slice
+struct Slice {
+  __amdgpu_buffer_rsrc_t d;
+  __device__ __forceinline__ Slice(const void *base, size_t bytes)
+      : d(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)bytes, 0x00027000)) {}
 };
-__host__ __device__ inline MaskLayout mask_layout(const KParams &p, bool perpos, bool bwd)
+typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
+template <typename T, int N>
+__device__ __forceinline__ void load_n(const Slice &s, unsigned off, float (&o)[N])
 {
-  MaskLayout m;
-  m.NT = (p.L + kTile - 1) / kTile;
-  m.NW = (p.NB + 31) / 32;
-  m.SR = perpos ? kTile * m.NT : 2 * m.NT;
-  int o = 0;
-  m.tm_lt = o; o += 2 * m.NT;
-  m.tm_st = o; o += 2 * m.NT;
-  m.cm_lt = o; o += bwd ? 2 * m.NT : 0;
-  m.cm_st = o; o += bwd ? 2 * m.NT : 0;
-  m.selw = o; o += m.NW * m.SR;
-  o = (o + 3) / 4 * 4;
-  m.kid = o; o += p.sblk > 0 ? kTile * m.NT : 0;
-  m.words = (o + 3) / 4 * 4;
-  return m;
-}
-
-__device__ __forceinline__ unsigned long long tile_mask(const unsigned *m, int off, int I)
-{
-  const unsigned lo = __builtin_amdgcn_readfirstlane(m[off + 2 * I]);
-  const unsigned hi = __builtin_amdgcn_readfirstlane(m[off + 2 * I + 1]);
-  return ((unsigned long long)hi << 32) | lo;
-}
-
-// Fills the mask words (the caller synchronises afterwards).  bh_sel: the (row, head) or (row, group) index of the
-// selection rows; sel == nullptr: dense causal attention, every tile up to the own one in the long-term masks.
-template <int BK, bool PERPOS, bool BWD>
-__device__ __forceinline__ void build_masks(unsigned *m, const MaskLayout &ml, const KParams &p, const int *sel, int bh_sel,
-                                            int p0, int tid, int nthr)
-{
-  const int NT = ml.NT;
-  for (int i = tid; i < ml.kid; i += nthr) m[i] = 0u;
-  if (p.sblk > 0)
-    for (int i = tid; i < kTile * NT; i += nthr) reinterpret_cast<int *>(m)[ml.kid + i] = i / p.sblk;
-  __syncthreads();
-  const int T0 = p0 / kTile;
-  auto set_tile = [&](int tm, int cm, int I, int J) {
-    atomicOr(&m[tm + 2 * I + (J >> 5)], 1u << (J & 31));
-    if (BWD) atomicOr(&m[cm + 2 * J + (I >> 5)], 1u << (I & 31));
-  };
-  // short-term reach of every pair of tiles
-  const int *kid = reinterpret_cast<const int *>(m) + ml.kid;
-  for (int idx = tid; idx < NT * NT; idx += nthr) {
-    const int I = idx / NT, J = idx - I * NT;
-    if (J < T0 || I < T0 || (J > I && !p.bidir)) continue;
-    if (!sel) {
-      set_tile(ml.tm_lt, ml.cm_lt, I, J);
-      continue;
+  if constexpr (sizeof(T) == 4) {
+    if constexpr (N == 2) {
+      const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(s.d, off, 0, 0);
+      o[0] = __uint_as_float(v[0]); o[1] = __uint_as_float(v[1]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < N; i += 4) {
+        const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(s.d, off + 4 * i, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[i + e] = __uint_as_float(v[e]);
+      }
     }
-    const int dist = (I > J ? I - J : J - I) * kTile - (kTile - 1);  // smallest distance of the two tiles' positions
-    bool reach = dist < p.w;
-    if (!reach && p.sblk > 0) {
-      const int q_lo = kid[I * kTile], q_hi = kid[min(I * kTile + kTile - 1, p.L - 1)];
-      const int k_lo = kid[J * kTile], k_hi = kid[min(J * kTile + kTile - 1, p.L - 1)];
-      reach = min(J * kTile + kTile - 1, p.L - 1) >= p.last_lo ||
-              (J <= I ? holds_pow2(q_lo - k_hi, q_hi - k_lo) : holds_pow2(k_lo - q_hi, k_hi - q_lo));
+  } else {
+    unsigned w[N / 2];
+    if constexpr (N == 2) {
+      w[0] = __builtin_amdgcn_raw_buffer_load_b32(s.d, off, 0, 0);
+    } else if constexpr (N == 4) {
+      const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(s.d, off, 0, 0);
+      w[0] = v[0]; w[1] = v[1];
+    } else {
+      const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(s.d, off, 0, 0);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[e] = v[e];
     }
-    if (reach) set_tile(ml.tm_st, ml.cm_st, I, J);
-  }
-  if (!sel) return;
-  // selection rows (entries outside [0, NB), blocks after the query and blocks without a valid key drop out)
-  const int rows = PERPOS ? p.L : p.NB;
-  const int *s = sel + (size_t)bh_sel * rows * p.k;
-  for (int idx = tid; idx < rows * p.k; idx += nthr) {
-    const int x = idx / p.k;
-    const int J = s[idx];
-    const int I = PERPOS ? x / kTile : x * BK / kTile;
-    const int q_hi = PERPOS ? x : x * BK + BK - 1;  // last position of the row or block
-    if (J < 0 || J >= p.NB || q_hi < p0 || (J * BK > q_hi && !p.bidir) || (J + 1) * BK <= p0) continue;
-    atomicOr(&m[ml.selw + (J >> 5) * ml.SR + x], 1u << (J & 31));
-    set_tile(ml.tm_lt, ml.cm_lt, I, J * BK / kTile);
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) {
+      o[2 * i] = __uint_as_float(w[i] << 16);
+      o[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
+    }
   }
 }
 
-// short-term visibility of a (query, key) pair that the causal and validity tests have let through
-__device__ __forceinline__ bool st_sees(const KParams &p, int diff, int kid_diff, int key)
+// The lane id, rebuilt where it stands: addresses formed from it are not computed ahead of a walk and kept in registers
+// through it.
+__device__ __forceinline__ int fresh_lane()
 {
-  if (p.bidir) {
-    diff = abs(diff);
-    kid_diff = abs(kid_diff);
-  }
-  bool v = diff < p.w;
-  if (p.sblk > 0) v = v || (kid_diff > 0 && (kid_diff & (kid_diff - 1)) == 0) || key >= p.last_lo;
-  return v;
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
 }
+
+// one head's [L,D] rows as matrix operands
+template <typename T, int D>
+struct Rows {
+  static constexpr bool kNear = false;  // far: operands are requested a tile ahead
+  static constexpr unsigned TB = kTile * D * sizeof(T);  // bytes of a tile
+  Slice s;
+  unsigned row_off, col_off;  // this lane's place in a tile
+  __device__ __forceinline__ Rows(const T *head, int L, int q, int g) : s(head, (size_t)L * D * sizeof(T))
+  {
+    row_off = (unsigned)(q * D + Geo<D>::CPL * g) * (unsigned)sizeof(T);
+    col_off = (unsigned)(4 * g * D + (D < 16 ? (q & (D - 1)) : q)) * (unsigned)sizeof(T);
+  }
+  // contraction over channels: channels CPL*g .. of row q of tile t
+  __device__ __forceinline__ void row(int t, float (&o)[Geo<D>::CPL]) const { load_n<T>(s, row_off + (unsigned)t * TB, o); }
+  // contraction over the tile's rows: element r is row 4g + r, channel 16*mb + q (d = 8: the upper eight output rows
+  // repeat the lower ones and are never stored)
+  __device__ __forceinline__ void col(int t, float (&o)[Geo<D>::NMB][4]) const
+  {
+    const unsigned off = col_off + (unsigned)t * TB;
+#pragma unroll
+    for (int mb = 0; mb < Geo<D>::NMB; ++mb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const unsigned at = off + (unsigned)((r * D + 16 * mb) * sizeof(T));
+        if constexpr (sizeof(T) == 4) o[mb][r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(s.d, at, 0, 0));
+        else o[mb][r] = __uint_as_float((unsigned)__builtin_amdgcn_raw_buffer_load_b16(s.d, at, 0, 0) << 16);
+      }
+  }
+};
+
+// the same from LDS, where a workgroup staged the head as fp32 rows of D + 4 floats (12, 20 or 36: both read patterns are
+// conflict free and rows stay 16-byte aligned)
+template <int D>
+constexpr int kLdsRow = D + 4;
+template <int D>
+struct LdsRows {
+  static constexpr bool kNear = true;  // near: operands are read where they are used and take no registers before
+  const float *row_at, *col_at;  // this lane's place in tile 0
+  __device__ __forceinline__ LdsRows(const float *base, int q, int g)
+      : row_at(base + q * kLdsRow<D> + Geo<D>::CPL * g), col_at(base + 4 * g * kLdsRow<D> + (D < 16 ? (q & (D - 1)) : q))
+  {
+  }
+  __device__ __forceinline__ void row(int t, float (&o)[Geo<D>::CPL]) const { load_n<Geo<D>::CPL>(row_at + t * (kTile * kLdsRow<D>), o); }
+  __device__ __forceinline__ void col(int t, float (&o)[Geo<D>::NMB][4]) const
+  {
+    const float *at = col_at + t * (kTile * kLdsRow<D>);
+#pragma unroll
+    for (int mb = 0; mb < Geo<D>::NMB; ++mb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o[mb][r] = at[r * kLdsRow<D> + 16 * mb];
+  }
+};
+template <int N>
+__device__ __forceinline__ void store_lds(float *p, const float (&o)[N])
+{
+  if constexpr (N == 2) {
+    *reinterpret_cast<float2 *>(p) = make_float2(o[0], o[1]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < N; i += 4) *reinterpret_cast<float4 *>(p + i) = make_float4(o[i], o[i + 1], o[i + 2], o[i + 3]);
+  }
+}
+// two heads' rows from tile T0 on into LDS (rows past the end are zeros)
+template <typename T, int D>
+__device__ __forceinline__ void stage_pair(const T *A, const T *B, float *a_lds, float *b_lds, int L, int T0, int NT, int lane, int wv, int W)
+{
+  constexpr int CPL = Geo<D>::CPL;
+  const int q = lane & 15, g = lane >> 4;
+  const Rows<T, D> Ar(A, L, q, g), Br(B, L, q, g);
+  for (int t = T0 + wv; t < NT; t += W) {
+    float x[CPL], y[CPL];
+    Ar.row(t, x);
+    Br.row(t, y);
+    const int at = (t * kTile + q) * kLdsRow<D> + CPL * g;
+    store_lds<CPL>(a_lds + at, x);
+    store_lds<CPL>(b_lds + at, y);
+  }
+}
+
+// pairs of bits (blocks of 8) -> one bit per tile
+__device__ __forceinline__ unsigned pair_bits(unsigned long long b)
+{
+  b = (b | (b >> 1)) & 0x5555555555555555ull;
+  b = (b | (b >> 1)) & 0x3333333333333333ull;
+  b = (b | (b >> 2)) & 0x0F0F0F0F0F0F0F0Full;
+  b = (b | (b >> 4)) & 0x00FF00FF00FF00FFull;
+  b = (b | (b >> 8)) & 0x0000FFFF0000FFFFull;
+  return (unsigned)(b | (b >> 16));
+}
+
+// THE WALK.  Tiles are grouped by kind, 32 tiles (a word) at a time, as four bit masks in scalar registers, and each kind
+// has a loop of its own whose body is one straight line: no branches, so the accumulators stay in place and the loads of the
+// next tile (of whatever kind) are waited for where they are used.
+//   0 general   both branches, every mask test: tiles of both branches, the diagonal, the first and the last valid tile, and
+//               tiles with last-block keys of Eq. 15
+//   1 lt        long-term only: no mask (per-element selection tests where blocks are smaller than tiles or per position)
+//   2 st        short-term only: window and power-of-two tests
+//   3 diagonal  short-term only, mask block 1: a tile 2, 4, 8 ... tiles away, where each row sees the one key at its own offset
+struct Walk {
+  unsigned m0 = 0, m1 = 0, m2 = 0, m3 = 0;  // tiles of the word still to come
+  unsigned lt = 0;                          // long-term tiles of the word
+  int base = 0;                             // first tile of the word
+  // lt_bits, st, edge: tiles of the word in either branch, and those that need every test; dia: candidates of kind 3
+  __device__ __forceinline__ void start(int w, unsigned lt_bits, unsigned st, unsigned edge, unsigned dia)
+  {
+    base = w * 32;
+    lt = lt_bits;
+    m0 = (lt & st) | (edge & (lt | st));
+    m1 = lt & ~m0;
+    m3 = st & ~lt & ~m0 & dia;
+    m2 = st & ~lt & ~m0 & ~m3;
+  }
+  __device__ __forceinline__ bool any() const { return (m0 | m1 | m2 | m3) != 0u; }
+  // the first tile still to come (some tile when there is none: a harmless read-ahead)
+  __device__ __forceinline__ int peek() const
+  {
+    const unsigned m = m0 ? m0 : m1 ? m1 : m2 ? m2 : m3;
+    return base + (m ? __builtin_ctz(m) : 0);
+  }
+};
+// bits of word w for the tiles lo .. hi
+__device__ __forceinline__ unsigned word_range(int w, int lo, int hi)
+{
+  const int a = max(lo - w * 32, 0), z = min(hi - w * 32, 31);
+  return a > z ? 0u : (0xFFFFFFFFu >> (31 - z)) & (0xFFFFFFFFu << a);
+}
+// Short-term tiles of word w for tile X (a query tile when key_side is false, else a key tile), tiles lo .. hi in question
+// (causal: keys up to X, or queries from X on).  dia: those of kind 3.
+template <bool KEY_SIDE>
+__device__ __forceinline__ unsigned st_word(const KParams &p, int X, int w, int lo, int hi, int lane, unsigned &dia)
+{
+  dia = 0u;
+  const unsigned range = word_range(w, lo, hi);
+  if (p.sblk > 1) {  // any mask block: one tile per lane
+    const int t = w * 32 + (lane & 31);
+    const bool r = KEY_SIDE ? st_reaches(p, t, X) : st_reaches(p, X, t);
+    return (unsigned)__ballot((lane < 32) & r) & range;
+  }
+  const int reach = (p.w + kTile - 2) / kTile;  // tiles up to this far away hold a key of the window
+  unsigned st = word_range(w, X - reach, X + reach);
+  if (p.sblk == 1) {
+    for (int d = 1; d <= max(X - lo, hi - X); d <<= 1) {
+      const int u = X - d - w * 32, v = X + d - w * 32;
+      const unsigned bits = ((unsigned)u < 32u ? 1u << u : 0u) | ((unsigned)v < 32u ? 1u << v : 0u);
+      st |= bits;
+      if (d > max(reach, 1)) dia |= bits;
+    }
+    // the last position: its tile is walked by every query tile (that reaches it)
+    if (!KEY_SIDE) st |= word_range(w, p.last_lo / kTile, p.last_lo / kTile);
+    else if (X >= p.last_lo / kTile) st = 0xFFFFFFFFu;
+  }
+  return st & range;
+}
+
+// What a query tile's wavefront knows about its long-term selection.  In LDS (this wavefront's words): sel rows of
+// its query blocks as bits over key blocks [kTile/BK][NWb], then the tile words [NWt].  Per-position form: `row` is the
+// lane's own row (at most 64 key blocks).
+template <int BK, bool PERPOS>
+struct LtSel {
+  static constexpr int NROW = PERPOS ? 0 : kTile / BK;
+  unsigned *bits, *tiles;
+  int NWb;
+  unsigned long long row;
+
+  // sel rows: of query block x0 on (or, per position, of this lane's position: nullptr where it takes no part).  p0: the
+  // first valid position.  Entries outside [0, NB), later blocks (causal form) and blocks without a valid key drop out.
+  __device__ __forceinline__ void build(const KParams &p, unsigned *lds, const int *sel_rows, const int *sel_pos, int I, int iq,
+                                        int p0, int lane)
+  {
+    NWb = (p.NB + 31) / 32;
+    const int NWt = ((p.L + kTile - 1) / kTile + 31) / 32;
+    bits = lds;
+    tiles = lds + NROW * NWb;
+    row = 0ull;
+    if constexpr (PERPOS) {
+      if (sel_pos)
+        for (int e = 0; e < p.k; ++e) {
+          const int J = sel_pos[e];
+          if (J >= 0 && J < p.NB && J * BK <= iq && (J + 1) * BK > p0) row |= 1ull << J;
+        }
+      unsigned lo = (unsigned)row, hi = (unsigned)(row >> 32);
+      lo = or_row(lo);
+      hi = or_row(hi);
+      const unsigned long long all = ((unsigned long long)__builtin_amdgcn_readfirstlane(hi) << 32) | __builtin_amdgcn_readfirstlane(lo);
+      if (lane < NWt) tiles[lane] = BK == kTile ? (lane == 0 ? (unsigned)all : (unsigned)(all >> 32)) : pair_bits(all);
+    } else {
+      for (int i = lane; i < NROW * NWb + NWt; i += 64) bits[i] = 0u;
+      for (int i = lane; i < NROW * p.k; i += 64) {
+        const int xr = NROW == 1 ? 0 : (i >= p.k ? 1 : 0);
+        const int x = I * NROW + xr;
+        if (x >= p.NB) continue;
+        const int J = sel_rows[i];  // (consecutive rows are contiguous)
+        if (J < 0 || J >= p.NB || (J > x && !p.bidir) || (J + 1) * BK <= p0) continue;
+        atomicOr(&bits[xr * NWb + (J >> 5)], 1u << (J & 31));
+        const int t = J * BK / kTile;
+        atomicOr(&tiles[t >> 5], 1u << (t & 31));
+      }
+    }
+  }
+  static __device__ __forceinline__ unsigned or_row(unsigned x)
+  {
+    x |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xf, 0xf, false);
+    x |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x124, 0xf, 0xf, false);
+    x |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x122, 0xf, 0xf, false);
+    return x | (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x121, 0xf, 0xf, false);
+  }
+  __device__ __forceinline__ unsigned word(int w) const { return __builtin_amdgcn_readfirstlane(tiles[w]); }
+  // did the lane's row select the block of its keys (four keys from key0 on share one)?  Only asked about tiles in `tiles`.
+  __device__ __forceinline__ bool sees(int q, int key0) const
+  {
+    const int Jb = key0 / BK;
+    if constexpr (PERPOS) return (row >> Jb) & 1ull;
+    else if constexpr (BK < kTile) return (bits[(q / BK) * NWb + (Jb >> 5)] >> (Jb & 31)) & 1u;
+    else return true;
+  }
+};
+__host__ __device__ inline int lt_words(const KParams &p, bool perpos)
+{
+  return (perpos ? 0 : kTile / p.b) * ((p.NB + 31) / 32) + ((p.L + kTile - 1) / kTile + 31) / 32;
+}
+
 
 }  // namespace
 
@@ -285,268 +508,294 @@ __device__ __forceinline__ bool st_sees(const KParams &p, int diff, int kid_diff
 // =============================================================================================
 // PERPOS: the long-term branch takes one selection row per query POSITION and key/value group (the
 // selection rule as printed, Eq. 8-13 with Eq. 4-5): K and V are [B,G,L,d], `sel` is [B,G,L,k] with
-// selection blocks of BK positions.  A workgroup serves the hpg query heads of its group, which share its
-// staged keys and values (hpg = 1 otherwise).
-template <typename T, int D, int BK, bool PERPOS>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void fwd_res_kernel(
+// selection blocks of BK positions; head h reads the keys and values of group h / (H/G).
+// `parts` workgroups share the query tiles of a head.  sel == nullptr: dense causal attention.
+// RES: the workgroup stages the keys and values in LDS first, and serves all hpg query heads that read them.
+template <typename T, int D, int BK, bool PERPOS, bool RES>
+__global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(D == 32 ? 5 : 6))) void fwd_small_kernel(
     const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V, const int *__restrict__ valid_len,
     const int *__restrict__ sel, const float *__restrict__ gate_w, const float *__restrict__ gate_b,
     T *__restrict__ O, float *__restrict__ o_lt_out, float *__restrict__ o_st_out, float *__restrict__ lse_lt_out,
-    float *__restrict__ lse_st_out, int hpg, KParams p)
+    float *__restrict__ lse_st_out, int hpg, int parts, KParams p)
 {
-  constexpr int CPL = Geo<D>::CPL, NMB = Geo<D>::NMB, LDR = Geo<D>::LDR;
-  extern __shared__ __attribute__((aligned(16))) float lds_res[];
-  __shared__ float red_s[16];
-  const MaskLayout ml = mask_layout(p, PERPOS, false);
-  const int NT = ml.NT;
-  float *Ks = lds_res;
-  float *Vs = Ks + NT * kTile * LDR;
-  unsigned *mw = reinterpret_cast<unsigned *>(Vs + NT * kTile * LDR + 16);
-
-  const int tid = threadIdx.x, nthr = blockDim.x;
-  const int lane = tid & 63;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), W = nthr >> 6;
-  const int bg = blockIdx.x;  // (row, key/value head)
-  const int G = p.H / hpg;
-  const int b = bg / G;
-  const int n = clamp_len(valid_len[b], p.L);
-  const int p0 = p.L - n;
-  const int T0 = p0 / kTile;
+  constexpr int CPL = Geo<D>::CPL, NMB = Geo<D>::NMB;
+  extern __shared__ __attribute__((aligned(16))) float small_lds[];  // RES: K and V rows; then the wavefronts' selection words
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = blockDim.x >> 6;
+  const unsigned vid = mfma::xcd_remap(blockIdx.x, gridDim.x);
+  const int heads = RES ? hpg : 1;  // query heads of this workgroup
+  const int bh0 = (int)(vid / parts) * heads, part = (int)(vid % parts);
+  const int b = bh0 / p.H;
+  const int NT = (p.L + kTile - 1) / kTile;
+  const int p0 = p.L - clamp_len(valid_len[b], p.L);
+  const int T0 = p0 / kTile;  // (beyond the last tile of a row without a valid position)
   const int q = lane & 15, g = lane >> 4;
-  const size_t head_kv = (size_t)bg * p.L * D;
+  const int kvh = PERPOS ? bh0 / hpg : bh0;
   const bool dense = sel == nullptr;
   const int row_lo = (p.NB - p.nq) * BK;  // first row that is written (serving mode: the last block's)
-
-  if (n == 0 || T0 * kTile > row_lo) {  // rows before the first valid tile: outputs are zero
-    for (int hh = 0; hh < hpg; ++hh) {
-      const size_t r0 = (size_t)(bg * hpg + hh) * p.L + row_lo;
-      const int rows = (n == 0 ? p.L : T0 * kTile) - row_lo;
-      zero_fill(O + r0 * D, rows * D, tid, nthr);
-      if (o_lt_out) zero_fill(o_lt_out + r0 * D, rows * D, tid, nthr);
-      if (o_st_out) zero_fill(o_st_out + r0 * D, rows * D, tid, nthr);
-      for (int i = tid; i < rows; i += nthr) {
-        if (lse_lt_out) lse_lt_out[r0 + i] = 0.0f;
-        if (lse_st_out) lse_st_out[r0 + i] = 0.0f;
-      }
-    }
-    if (n == 0) return;
+  const T *Kh = K + (size_t)kvh * p.L * D, *Vh = V + (size_t)kvh * p.L * D;
+  const int pitch = RES ? NT * kTile * kLdsRow<D> : 0;  // floats of a staged tensor
+  if constexpr (RES) {
+    stage_pair<T, D>(Kh, Vh, small_lds, small_lds + pitch, p.L, T0, NT, lane, wv, W);
+    __syncthreads();
   }
-
-  // ---- staging, and the largest key norm and value magnitude ----
-  float k2 = 0.0f, vm = 0.0f;
-  for (int t = T0 + wv; t < NT; t += W) {
-    const int r = t * kTile + q;
-    float kx[CPL], vx[CPL];
-    zero_n(kx);
-    zero_n(vx);
-    if (r < p.L && r >= p0) {
-      load_n<CPL>(K + head_kv + (size_t)r * D + CPL * g, kx);
-      load_n<CPL>(V + head_kv + (size_t)r * D + CPL * g, vx);
-    }
-    store_n<CPL>(Ks + r * LDR + CPL * g, kx);
-    store_n<CPL>(Vs + r * LDR + CPL * g, vx);
-    k2 = fmaxf(k2, sum_g(dot_n(kx, kx, 0.0f)));
-#pragma unroll
-    for (int i = 0; i < CPL; ++i) vm = fmaxf(vm, fabsf(vx[i]));
-  }
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    k2 = fmaxf(k2, __shfl_xor(k2, off));
-    vm = fmaxf(vm, __shfl_xor(vm, off));
-  }
-  if (lane == 0) {
-    red_s[wv] = k2;
-    red_s[8 + wv] = vm;
-  }
-  build_masks<BK, PERPOS, false>(mw, ml, p, sel, bg, p0, tid, nthr);
-  __syncthreads();
-  k2 = 0.0f;
-  vm = 0.0f;
-  for (int w = 0; w < W; ++w) {
-    k2 = fmaxf(k2, red_s[w]);
-    vm = fmaxf(vm, red_s[8 + w]);
-  }
-
+  using TileRows = std::conditional_t<RES, LdsRows<D>, Rows<T, D>>;
+  const TileRows Kr = [&] {
+    if constexpr (RES) return LdsRows<D>(small_lds, q, g);
+    else return Rows<T, D>(Kh, p.L, q, g);
+  }();
+  const TileRows Vr = [&] {
+    if constexpr (RES) return LdsRows<D>(small_lds + pitch, q, g);
+    else return Rows<T, D>(Vh, p.L, q, g);
+  }();
   const float c2 = p.scale * kLog2eF;
-  const int *kid = reinterpret_cast<const int *>(mw) + ml.kid;
-  const int I_lo = max(T0, row_lo / kTile);
-  const int n_task = (NT - I_lo) * hpg;
+  unsigned *my_lds = reinterpret_cast<unsigned *>(small_lds + 2 * pitch) + wv * lt_words(p, PERPOS);
 
-  // query tiles of this wavefront, longest walks first, dealt forth and back over the wavefronts
-  for (int rnd = 0; rnd * W < n_task; ++rnd) {
-    const int u = rnd * W + ((rnd & 1) ? W - 1 - wv : wv);
-    if (u >= n_task) continue;
-    const int I = NT - 1 - u / hpg;
-    const int bh = bg * hpg + u % hpg;
-    const int h = bh % p.H;
+  for (int hh = 0; hh < heads; ++hh)
+  for (int u = part * W + wv; NT - 1 - u >= row_lo / kTile; u += parts * W) {
+    const int bh = bh0 + hh, h = bh % p.H;
+    const Slice Qs(Q + (size_t)bh * p.L * D, (size_t)p.L * D * sizeof(T));
+    const int I = NT - 1 - u;
     const int iq = I * kTile + q;
-    const bool in_range = iq < p.L && iq >= row_lo;
     const bool active = iq < p.L && iq >= p0;
-    const size_t rowoff = ((size_t)bh * p.L + min(iq, p.L - 1)) * D;
-    const size_t lrow = (size_t)bh * p.L + min(iq, p.L - 1);
-
+    if (I < T0 || p0 >= p.L) {  // no valid query: outputs are zero
+      const int r_lo = max(I * kTile, row_lo), rows = min(I * kTile + kTile, p.L) - r_lo;
+      const size_t r0 = (size_t)bh * p.L + r_lo;
+      const int el = fresh_lane();
+      zero_fill(O + r0 * D, rows * D, el);
+      if (o_lt_out) zero_fill(o_lt_out + r0 * D, rows * D, el);
+      if (o_st_out) zero_fill(o_st_out + r0 * D, rows * D, el);
+      if (el < rows) {
+        if (lse_lt_out) lse_lt_out[r0 + el] = 0.0f;
+        if (lse_st_out) lse_st_out[r0 + el] = 0.0f;
+      }
+      continue;
+    }
     float qf[CPL];
-    zero_n(qf);
-    if (active) load_n<CPL>(Q + rowoff + CPL * g, qf);
+    load_n<T>(Qs, active ? (unsigned)(iq * D + CPL * g) * (unsigned)sizeof(T) : kNowhere, qf);
+    LtSel<BK, PERPOS> ls;
+    if (!dense)
+      ls.build(p, my_lds, PERPOS ? nullptr : sel + ((size_t)bh * p.NB + I * (kTile / BK)) * p.k,
+               PERPOS && active ? sel + ((size_t)kvh * p.L + iq) * p.k : nullptr, I, iq, p0, lane);
 #pragma unroll
     for (int i = 0; i < CPL; ++i) qf[i] *= c2;
-    const float q2 = sum_g(dot_n(qf, qf, 0.0f));
-    const bool small = __all(q2 * k2 <= kSmallLogit * kSmallLogit) && vm <= 1.0e18f;
-
-    const unsigned long long m_lt = tile_mask(mw, ml.tm_lt, I), m_st = tile_mask(mw, ml.tm_st, I);
-    const int kid_q = p.sblk > 0 ? kid[iq] : 0;
-
-    auto logits = [&](int J) -> f32x4 {
-      float kf[CPL];
-      load_n<CPL>(Ks + (J * kTile + q) * LDR + CPL * g, kf);
-      f32x4 s = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int c = 0; c < CPL; ++c) s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c], qf[c], s, 0, 0, 0);
-      return s;
+    const int kid_q = mask_block(p, iq);
+    const int J_hi = p.bidir ? NT - 1 : I;
+    // the walk of word w
+    Walk wk;
+    auto word = [&](int w) __attribute__((always_inline)) {
+      unsigned dia = 0u;
+      const unsigned lt = dense ? word_range(w, T0, I) : ls.word(w);
+      const unsigned st = dense ? 0u : st_word<false>(p, I, w, T0, J_hi, lane, dia);
+      unsigned edge = word_range(w, T0, T0) | word_range(w, I, I) | word_range(w, NT - 1, NT - 1) | word_range(w, p.last_lo / kTile, NT - 1);
+      // (two query blocks per tile: a row's sums must not depend on what the other block selected, which the serving mode does
+      // not know, so every short-term tile is general there and the order of the walk follows from the geometry)
+      if (BK < kTile && !PERPOS) edge |= st;
+      wk.start(w, lt, st, edge, dia);
     };
-    // visibility of this lane's four keys of tile J, one bit each, for the branches that walk the tile
-    auto see = [&](int J, bool lt, bool st, unsigned &v_lt, unsigned &v_st) {
-      const int key0 = J * kTile + 4 * g;
-      unsigned ok = 15u;
-      if (J == T0 || J == I || J == NT - 1) {
-        ok = 0u;
-        const int hi = p.bidir ? p.L - 1 : iq;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) ok |= (key0 + r >= p0 && key0 + r <= hi) ? 1u << r : 0u;
-      }
-      v_lt = v_st = 0u;
-      if (lt) {
-        v_lt = ok;
-        if ((PERPOS || BK < kTile) && !dense) {  // the lane's four keys share a block
-          const int Jb = key0 / BK;
-          const int x = PERPOS ? iq : iq / BK;
-          if (((mw[ml.selw + (Jb >> 5) * ml.SR + x] >> (Jb & 31)) & 1u) == 0u) v_lt = 0u;
-        }
-      }
-      if (st) {
-        int4 kd = make_int4(0, 0, 0, 0);
-        if (p.sblk > 0) kd = *reinterpret_cast<const int4 *>(kid + key0);
-        const int kdv[4] = {kd.x, kd.y, kd.z, kd.w};
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v_st |= st_sees(p, iq - key0 - r, kid_q - kdv[r], key0 + r) ? 1u << r : 0u;
-        v_st &= ok;
-      }
-    };
-
-    float ml_lt = 0.0f, ml_st = 0.0f;  // the references the exponentials are taken against
-    if (!small) {
-      float a = kNegInfF, c = kNegInfF;
-      for (unsigned long long mm = m_lt | m_st; mm; mm &= mm - 1) {
-        const int J = __builtin_ctzll(mm);
-        const f32x4 s = logits(J);
-        unsigned v_lt, v_st;
-        see(J, (m_lt >> J) & 1ull, (m_st >> J) & 1ull, v_lt, v_st);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          a = (v_lt >> r) & 1u ? fmaxf(a, s[r]) : a;
-          c = (v_st >> r) & 1u ? fmaxf(c, s[r]) : c;
-        }
-      }
-      a = fmaxf(a, __shfl_xor(a, 16));
-      a = fmaxf(a, __shfl_xor(a, 32));
-      c = fmaxf(c, __shfl_xor(c, 16));
-      c = fmaxf(c, __shfl_xor(c, 32));
-      ml_lt = a == kNegInfF ? 0.0f : a;
-      ml_st = c == kNegInfF ? 0.0f : c;
-    }
-
     f32x4 a_lt[NMB], a_st[NMB];
 #pragma unroll
     for (int mb = 0; mb < NMB; ++mb) {
       a_lt[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
       a_st[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    float l_lt = 0.0f, l_st = 0.0f;
-    for (unsigned long long mm = m_lt | m_st; mm; mm &= mm - 1) {
-      const int J = __builtin_ctzll(mm);
-      const bool lt = (m_lt >> J) & 1ull, st = (m_st >> J) & 1ull;
-      const f32x4 s = logits(J);
-      unsigned v_lt, v_st;
-      see(J, lt, st, v_lt, v_st);
-      float vf[NMB][4];
+    float l_lt = 0.0f, l_st = 0.0f, ref_lt = 0.0f, ref_st = 0.0f, s_max = 0.0f;
+    float kf[CPL], vf[NMB][4];
+    auto logits = [&]() -> f32x4 {
+      f32x4 s = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int mb = 0; mb < NMB; ++mb) col_frag<LDR>(Vs + J * kTile * LDR, g, 16 * mb + q, vf[mb]);
-      float e_lt[4], e_st[4];
-      if (small) {
+      for (int c = 0; c < CPL; ++c) s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c], qf[c], s, 0, 0, 0);
+      return s;
+    };
+    auto add_lt = [&](const float (&e)[4]) __attribute__((always_inline)) {
+      l_lt += (e[0] + e[1]) + (e[2] + e[3]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int mb = 0; mb < NMB; ++mb) a_lt[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[mb][r], e[r], a_lt[mb], 0, 0, 0);
+    };
+    auto add_st = [&](const float (&e)[4]) __attribute__((always_inline)) {
+      l_st += (e[0] + e[1]) + (e[2] + e[3]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int mb = 0; mb < NMB; ++mb) a_st[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[mb][r], e[r], a_st[mb], 0, 0, 0);
+    };
+    // visibility of this lane's four keys of a general tile
+    auto see = [&](auto unit, int t, bool (&v_lt)[4], bool (&v_st)[4]) __attribute__((always_inline)) {
+      const int key0 = t * kTile + 4 * g;
+      const unsigned span = (unsigned)((p.bidir ? p.L - 1 : iq) - p0);
+      bool s_lt = (wk.lt >> (t & 31)) & 1u;
+      if ((PERPOS || BK < kTile) && !dense) s_lt &= ls.sees(q, key0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const bool ok = (unsigned)(key0 + r - p0) <= span;
+        v_lt[r] = ok & s_lt;
+        v_st[r] = ok & st_sees<decltype(unit)::value>(p, iq, key0 + r, kid_q, mask_block(p, key0, r), key0 + r >= p.last_lo);
+      }
+    };
+    const int dr = (q >> 2) == g ? (q & 3) : 4;  // which of the lane's four keys of a diagonal tile its row sees (4: none)
+    // one tile: the next one's keys are requested as soon as this one's are in the matrix cores, its values at the end
+    auto body = [&](auto kind, auto unit, unsigned &mask) __attribute__((always_inline)) {
+      constexpr int KIND = decltype(kind)::value;
+      const int t = wk.base + __builtin_ctz(mask);
+      mask &= mask - 1;
+      const int t_next = wk.peek();
+      const f32x4 s = logits();
+      Kr.row(t_next, kf);
+      if constexpr (TileRows::kNear) Vr.col(t, vf);
+      s_max = fmaxf(fmaxf(s_max, fabsf(s[0])), fabsf(s[1]));
+      s_max = fmaxf(fmaxf(s_max, fabsf(s[2])), fabsf(s[3]));
+      float e[4];
+      if constexpr (KIND != 3) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) e[r] = __builtin_amdgcn_exp2f(s[r]);
+      }
+      if constexpr (KIND == 0) {
+        bool v_lt[4], v_st[4];
+        see(unit, t, v_lt, v_st);
+        float el[4], es[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const float e = __builtin_amdgcn_exp2f(s[r]);
-          e_lt[r] = (v_lt >> r) & 1u ? e : 0.0f;
-          e_st[r] = (v_st >> r) & 1u ? e : 0.0f;
+          el[r] = v_lt[r] ? e[r] : 0.0f;
+          es[r] = v_st[r] ? e[r] : 0.0f;
         }
+        add_lt(el);
+        add_st(es);
+      } else if constexpr (KIND == 1) {
+        if constexpr (PERPOS || BK < kTile) {
+          const bool v = dense || ls.sees(q, t * kTile + 4 * g);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) e[r] = v ? e[r] : 0.0f;
+        }
+        add_lt(e);
+      } else if constexpr (KIND == 2) {
+        const int key0 = t * kTile + 4 * g;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          e[r] = st_sees<decltype(unit)::value>(p, iq, key0 + r, kid_q, mask_block(p, key0, r), false) ? e[r] : 0.0f;
+        add_st(e);
       } else {
+        const float sd = dr == 0 ? s[0] : dr == 1 ? s[1] : dr == 2 ? s[2] : s[3];
+        const float ed = __builtin_amdgcn_exp2f(sd);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) e[r] = dr == r ? ed : 0.0f;
+        add_st(e);
+      }
+      if constexpr (!TileRows::kNear) Vr.col(t_next, vf);
+    };
+    auto walk = [&](auto unit) __attribute__((always_inline)) {
+      for (int w = T0 >> 5; w <= J_hi >> 5; ++w) {
+        word(w);
+        if (!wk.any()) continue;
+        const int t = wk.peek();
+        Kr.row(t, kf);
+        if constexpr (!TileRows::kNear) Vr.col(t, vf);
+        while (wk.m0) body(std::integral_constant<int, 0>{}, unit, wk.m0);
+        while (wk.m1) body(std::integral_constant<int, 1>{}, unit, wk.m1);
+        while (wk.m2) body(std::integral_constant<int, 2>{}, unit, wk.m2);
+        while (wk.m3) body(std::integral_constant<int, 3>{}, unit, wk.m3);
+      }
+    };
+    if (p.sblk <= 1) walk(std::true_type{});
+    else walk(std::false_type{});
+    float size = 0.0f;
+#pragma unroll
+    for (int mb = 0; mb < NMB; ++mb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) size += fabsf(a_lt[mb][r]) + fabsf(a_st[mb][r]);
+    if (!__all(s_max <= kSmallLogit && size < 1.0e37f)) {
+      // large logits, or values near the end of fp32's range: the row maxima of both branches, then the walk against them
+      float x_lt = kNegInfF, x_st = kNegInfF;
+      auto each = [&](auto f) __attribute__((always_inline)) {
+        for (int w = T0 >> 5; w <= J_hi >> 5; ++w) {
+          word(w);
+          for (unsigned m = wk.m0 | wk.m1 | wk.m2 | wk.m3; m; m &= m - 1) f(wk.base + __builtin_ctz(m));
+        }
+      };
+      each([&](int J) {
+        Kr.row(J, kf);
+        const f32x4 s = logits();
+        bool v_lt[4], v_st[4];
+        see(std::false_type{}, J, v_lt, v_st);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          e_lt[r] = (v_lt >> r) & 1u ? __builtin_amdgcn_exp2f(s[r] - ml_lt) : 0.0f;
-          e_st[r] = (v_st >> r) & 1u ? __builtin_amdgcn_exp2f(s[r] - ml_st) : 0.0f;
+          x_lt = fmaxf(x_lt, v_lt[r] ? s[r] : kNegInfF);
+          x_st = fmaxf(x_st, v_st[r] ? s[r] : kNegInfF);
         }
+      });
+      x_lt = max_g(x_lt);
+      x_st = max_g(x_st);
+      ref_lt = x_lt == kNegInfF ? 0.0f : x_lt;
+      ref_st = x_st == kNegInfF ? 0.0f : x_st;
+      l_lt = l_st = 0.0f;
+#pragma unroll
+      for (int mb = 0; mb < NMB; ++mb) {
+        a_lt[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        a_st[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
-      if (lt) {
-        l_lt += (e_lt[0] + e_lt[1]) + (e_lt[2] + e_lt[3]);
+      each([&](int J) {
+        Kr.row(J, kf);
+        Vr.col(J, vf);
+        const f32x4 s = logits();
+        bool v_lt[4], v_st[4];
+        see(std::false_type{}, J, v_lt, v_st);
+        float el[4], es[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int mb = 0; mb < NMB; ++mb)
-            a_lt[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[mb][r], e_lt[r], a_lt[mb], 0, 0, 0);
-      }
-      if (st) {
-        l_st += (e_st[0] + e_st[1]) + (e_st[2] + e_st[3]);
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int mb = 0; mb < NMB; ++mb)
-            a_st[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[mb][r], e_st[r], a_st[mb], 0, 0, 0);
-      }
+        for (int r = 0; r < 4; ++r) {
+          el[r] = v_lt[r] ? __builtin_amdgcn_exp2f(s[r] - ref_lt) : 0.0f;
+          es[r] = v_st[r] ? __builtin_amdgcn_exp2f(s[r] - ref_st) : 0.0f;
+        }
+        add_lt(el);
+        add_st(es);
+      });
     }
     // closes a branch: normalised output (zero for rows that take no part), returns the lse
     auto finish = [&](f32x4 (&acc)[NMB], float l, float m) -> float {
       const float lt = sum_g(l);
       const bool ok = active && lt > 0.0f;
-      const float inv = ok ? 1.0f / lt : 0.0f;
+      const float inv = ok ? recip(lt) : 0.0f;
 #pragma unroll
       for (int mb = 0; mb < NMB; ++mb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[mb][r] *= inv;
-      return ok ? (m + __log2f(lt)) * kLn2F : 0.0f;
+      return ok ? (m + __builtin_amdgcn_logf(lt)) * kLn2F : 0.0f;
     };
-    const float lse_lt = finish(a_lt, l_lt, ml_lt);
+    const int el = fresh_lane(), eg = el >> 4, ei = I * kTile + (el & 15);
+    const bool in_range = ei < p.L && ei >= row_lo;
+    const size_t lrow = (size_t)bh * p.L + ei, rowoff = lrow * D;
+    const float lse_lt = finish(a_lt, l_lt, ref_lt);
     if (dense) {
-      if (in_range) store_row4<T, D>(O + rowoff, a_lt, g);
-      if (in_range && g == 0 && lse_lt_out) lse_lt_out[lrow] = lse_lt;
+      if (in_range) store_row4<T, D>(O + rowoff, a_lt, eg);
+      if (in_range && eg == 0 && lse_lt_out) lse_lt_out[lrow] = lse_lt;
       continue;
     }
-    const float lse_st = finish(a_st, l_st, ml_st);
+    const float lse_st = finish(a_st, l_st, ref_st);
 
     // ---- gate and blend (Eq. 18-19) ----
     const float *wl = gate_w + (size_t)h * 2 * D;
     float z = 0.0f;
 #pragma unroll
     for (int mb = 0; mb < NMB; ++mb)
+      if (16 * mb + 4 * eg < D) {
+        float x[4], y[4];
+        load_n<4>(wl + 16 * mb + 4 * eg, x);
+        load_n<4>(wl + D + 16 * mb + 4 * eg, y);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int c = 16 * mb + 4 * g + r;
-        if (c < D) {
-          z = fmaf(wl[c], a_lt[mb][r], z);
-          z = fmaf(wl[D + c], a_st[mb][r], z);
-        }
+        for (int r = 0; r < 4; ++r) z = fmaf(y[r], a_st[mb][r], fmaf(x[r], a_lt[mb][r], z));
       }
     z = sum_g(z) + (gate_b ? gate_b[h] : 0.0f);
-    const float alpha = active ? 1.0f / (1.0f + __expf(-z)) : 0.0f;
+    const float alpha = sigmoid(z);
     if (in_range) {
-      if (o_lt_out) store_row4<float, D>(o_lt_out + rowoff, a_lt, g);
-      if (o_st_out) store_row4<float, D>(o_st_out + rowoff, a_st, g);
+      if (o_lt_out) store_row4<float, D>(o_lt_out + rowoff, a_lt, eg);
+      if (o_st_out) store_row4<float, D>(o_st_out + rowoff, a_st, eg);
       f32x4 o[NMB];
 #pragma unroll
       for (int mb = 0; mb < NMB; ++mb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) o[mb][r] = alpha * a_lt[mb][r] + (1.0f - alpha) * a_st[mb][r];
-      store_row4<T, D>(O + rowoff, o, g);
-      if (g == 0) {
+      store_row4<T, D>(O + rowoff, o, eg);
+      if (eg == 0) {
         if (lse_lt_out) lse_lt_out[lrow] = lse_lt;
         if (lse_st_out) lse_st_out[lrow] = lse_st;
       }
@@ -555,439 +804,622 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void f
 }
 
 // =============================================================================================
-// backward: gate pass, dK/dV and dQ of a (row, head), or of the hpg query heads of a (row, group)
+// backward of one query tile (gate pass, dQ) and of one key tile (dK, dV)
 // =============================================================================================
-// stages: kBwdStage* bits (a subset for callers that run the passes one at a time; the gate pass is redone
-// in the workgroup whenever a later pass needs its row constants, and only writes with kBwdStageGate).
-// hc: query heads whose Q, dO and row constants are in LDS at a time (hpg whenever that fits).  With hc < hpg
-// the key tiles go in rounds of one per wavefront and every round stages the heads chunk by chunk, the
-// accumulators staying in registers.
-template <typename T, int D, int BK, bool PERPOS>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void bwd_res_kernel(
-    const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V, const int *__restrict__ valid_len,
-    const int *__restrict__ sel, const float *__restrict__ gate_w, const float *__restrict__ gate_b,
-    const float *__restrict__ o_lt, const float *__restrict__ o_st, const float *__restrict__ lse_lt,
-    const float *__restrict__ lse_st, const T *__restrict__ dO, T *__restrict__ dQ, T *__restrict__ dK,
-    T *__restrict__ dV, float *__restrict__ partial, int hpg, int hc, unsigned stages, KParams p)
-{
-  constexpr int CPL = Geo<D>::CPL, NMB = Geo<D>::NMB, LDR = Geo<D>::LDR, GW = 2 * D + 1;
-  extern __shared__ __attribute__((aligned(16))) float lds_res[];
-  const MaskLayout ml = mask_layout(p, PERPOS, true);
-  const int NT = ml.NT, rows = NT * kTile;
-  float *A0 = lds_res;                                   // [hc][2][rows][LDR]: Q and dO per head; later K and V
-  float *rc = A0 + 2 * hc * rows * LDR + 16;             // [hc][6][rows]: alpha, dz, D_lt, D_st, lse2_lt, lse2_st
-  unsigned *mw = reinterpret_cast<unsigned *>(rc + 6 * hc * rows);
-  float *red = reinterpret_cast<float *>(mw + ml.words);  // [hc][W][GW]
+namespace {
 
-  const int tid = threadIdx.x, nthr = blockDim.x;
-  const int lane = tid & 63;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), W = nthr >> 6;
-  const int bg = blockIdx.x;  // (row, key/value head)
-  const int G = p.H / hpg;
-  const int b = bg / G;
-  const int n = clamp_len(valid_len[b], p.L);
-  const int p0 = p.L - n;
-  const int T0 = n == 0 ? NT : p0 / kTile;
-  const int q = lane & 15, g = lane >> 4;
-  const size_t head_kv = (size_t)bg * p.L * D;
-  const bool do_gate = stages & kBwdStageGate, do_dq = stages & kBwdStageDQ, do_dkv = stages & kBwdStageDKV;
-  const float c2 = p.scale * kLog2eF;
-
-  {  // rows before the first valid tile: zero gradients
-    const int zr = min(T0 * kTile, p.L);
-    if (do_dkv) {
-      zero_fill(dK + head_kv, zr * D, tid, nthr);
-      zero_fill(dV + head_kv, zr * D, tid, nthr);
-    }
-    if (do_dq)
-      for (int hh = 0; hh < hpg; ++hh) zero_fill(dQ + (size_t)(bg * hpg + hh) * p.L * D, zr * D, tid, nthr);
-    if (n == 0) {
-      if (do_gate)
-        for (int i = tid; i < hpg * GW; i += nthr) partial[(size_t)bg * hpg * GW + i] = 0.0f;
-      return;
-    }
+// LDS of bwd_res_kernel, in floats: K and V, per head Q and dO (overlay: in the place of K and V), row constants, tile words and
+// selection bits, the wavefronts' selection words
+struct ResLayout {
+  int pitch, qg, rowc, words, waves, total;
+  __host__ __device__ ResLayout(const KParams &p, bool perpos, int hpg, int overlay, int W)
+  {
+    const int NT = (p.L + kTile - 1) / kTile, rows = NT * kTile;
+    pitch = rows * (p.d + 4);
+    qg = overlay ? 0 : 2 * pitch;
+    rowc = overlay ? 2 * hpg * pitch : 2 * pitch + 2 * hpg * pitch;
+    words = rowc + hpg * 6 * rows;
+    waves = words + NT * ((NT + 31) / 32) + (perpos ? 2 * rows : p.b < kTile ? 2 * NT * ((p.NB + 31) / 32) : 0);
+    waves = (waves + 3) / 4 * 4;
+    total = waves + W * lt_words(p, perpos);
   }
-  build_masks<BK, PERPOS, true>(mw, ml, p, sel, bg, p0, tid, nthr);
-  const int *kid = reinterpret_cast<const int *>(mw) + ml.kid;
+};
 
-  // gate pass of this lane's row of one head: the row constants from its slices of dO, o_lt and o_st
-  struct RowConst {
-    float al, dz, D_lt, D_st;
-  };
-  auto row_const = [&](const float (&gr)[CPL], const float (&ol)[CPL], const float (&os)[CPL], const float (&wl)[CPL],
-                       const float (&ws)[CPL], float bias, bool valid) -> RowConst {
-    const float a_ll = sum_g(dot_n(gr, ol, 0.0f)), a_ss = sum_g(dot_n(gr, os, 0.0f));
-    const float w_l = sum_g(dot_n(wl, ol, 0.0f)), w_s = sum_g(dot_n(ws, os, 0.0f));
-    RowConst c{0.f, 0.f, 0.f, 0.f};
-    if (valid) {
-      c.al = 1.0f / (1.0f + __expf(-(bias + w_l + w_s)));
-      c.dz = (a_ll - a_ss) * c.al * (1.0f - c.al);
-      c.D_lt = c.al * a_ll + c.dz * w_l;
-      c.D_st = (1.0f - c.al) * a_ss + c.dz * w_s;
-    }
-    return c;
-  };
-
-  // ---- Q, dO and the row constants of heads h0 .. h0+nh-1 of the group into LDS ----
-  auto stage_heads = [&](int h0, int nh, bool gate) {
-    for (int hl = 0; hl < nh; ++hl) {
-      const int bh = bg * hpg + h0 + hl;
-      const int h = bh % p.H;
-      float *Qs = A0 + 2 * hl * rows * LDR, *Gs = Qs + rows * LDR, *rch = rc + 6 * hl * rows;
-      float wl[CPL], ws[CPL], gl[CPL], gs[CPL], gb = 0.0f;
-      load_n<CPL>(gate_w + (size_t)h * 2 * D + CPL * g, wl);
-      load_n<CPL>(gate_w + (size_t)h * 2 * D + D + CPL * g, ws);
-      const float bias = gate_b ? gate_b[h] : 0.0f;
-      zero_n(gl);
-      zero_n(gs);
-      for (int t = T0 + wv; t < NT; t += W) {
-        const int r = t * kTile + q;
-        const bool valid = r < p.L && r >= p0;
-        const size_t lrow = (size_t)bh * p.L + r, ro = lrow * D + CPL * g;
-        float qx[CPL], gr[CPL], ol[CPL], os[CPL];
-        zero_n(qx);
-        zero_n(gr);
-        zero_n(ol);
-        zero_n(os);
-        float la = kHugeF, lb = kHugeF;  // rows that take no part: every probability zero
-        if (valid) {
-          load_n<CPL>(Q + ro, qx);
-          load_n<CPL>(dO + ro, gr);
-          load_n<CPL>(o_lt + ro, ol);
-          load_n<CPL>(o_st + ro, os);
-          la = lse_lt[lrow] * kLog2eF;
-          lb = lse_st[lrow] * kLog2eF;
-        }
-        store_n<CPL>(Qs + r * LDR + CPL * g, qx);
-        store_n<CPL>(Gs + r * LDR + CPL * g, gr);
-        const RowConst c = row_const(gr, ol, os, wl, ws, bias, valid);
-        if (g == 0) {
-          rch[r] = c.al;
-          rch[rows + r] = c.dz;
-          rch[2 * rows + r] = c.D_lt;
-          rch[3 * rows + r] = c.D_st;
-          rch[4 * rows + r] = la;
-          rch[5 * rows + r] = lb;
-        }
-        if (gate) {
-#pragma unroll
-          for (int i = 0; i < CPL; ++i) {
-            gl[i] = fmaf(c.dz, ol[i], gl[i]);
-            gs[i] = fmaf(c.dz, os[i], gs[i]);
-          }
-          gb += c.dz;
-        }
-      }
-      if (gate) {  // sums over the 16 rows of the lanes, one slot per wavefront
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) {
-#pragma unroll
-          for (int i = 0; i < CPL; ++i) {
-            gl[i] += __shfl_xor(gl[i], off);
-            gs[i] += __shfl_xor(gs[i], off);
-          }
-          gb += __shfl_xor(gb, off);
-        }
-        float *rw = red + (hl * W + wv) * GW;
-        if (q == 0) {
-#pragma unroll
-          for (int i = 0; i < CPL; ++i) {
-            rw[CPL * g + i] = gl[i];
-            rw[D + CPL * g + i] = gs[i];
-          }
-          if (g == 0) rw[2 * D] = gb;
-        }
-      }
-    }
-  };
-
-  // ---- dK, dV: key tiles ----
-  if (do_gate || do_dkv) {
-    const int chunks = (hpg + hc - 1) / hc;
-    int staged = -1;
-    for (int rnd = 0; rnd == 0 || (do_dkv && rnd * W < NT - T0); ++rnd) {
-      const int u = rnd * W + ((rnd & 1) ? W - 1 - wv : wv);
-      const int J = T0 + u;  // early key tiles have the longest walks: they start first
-      const bool have = do_dkv && J < NT;
-      const int j = min(J, NT - 1) * kTile + q;
-      const bool in_range = have && j < p.L;
-      const bool key_ok = in_range && j >= p0;
-      const int row = min(j, p.L - 1);
-      f32x4 dk[NMB], dv[NMB];
-#pragma unroll
-      for (int mb = 0; mb < NMB; ++mb) {
-        dk[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        dv[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-      }
-      float kf[CPL], vf[CPL];
-      zero_n(kf);
-      zero_n(vf);
-      if (key_ok) {
-        load_n<CPL>(K + head_kv + (size_t)row * D + CPL * g, kf);
-        load_n<CPL>(V + head_kv + (size_t)row * D + CPL * g, vf);
-      }
-#pragma unroll
-      for (int i = 0; i < CPL; ++i) kf[i] *= c2;
-
-      for (int ch = 0; ch < chunks; ++ch) {
-        const int h0 = ch * hc, nh = min(hc, hpg - h0);
-        if (staged != ch) {
-          if (staged >= 0) __syncthreads();
-          stage_heads(h0, nh, do_gate && rnd == 0);
-          staged = ch;
-          __syncthreads();  // (covers the masks as well)
-          if (do_gate && rnd == 0)
-            for (int i = tid; i < nh * GW; i += nthr) {
-              const int hl = i / GW, c = i - hl * GW;
-              float a = 0.0f;
-              for (int w = 0; w < W; ++w) a += red[(hl * W + w) * GW + c];
-              partial[(size_t)(bg * hpg + h0 + hl) * GW + c] = a;
-            }
-        }
-        if (!have) continue;
-        const unsigned long long m_lt = tile_mask(mw, ml.cm_lt, J), m_st = tile_mask(mw, ml.cm_st, J);
-        const int kid_k = p.sblk > 0 ? kid[j] : 0;
-        for (int hl = 0; hl < nh; ++hl) {
-          const int h = (bg * hpg + h0 + hl) % p.H;
-          const float *Qs = A0 + 2 * hl * rows * LDR, *Gs = Qs + rows * LDR, *rch = rc + 6 * hl * rows;
-          const float *wrow = gate_w + (size_t)h * 2 * D;
-          float wl[CPL], ws[CPL];
-          load_n<CPL>(wrow + CPL * g, wl);
-          load_n<CPL>(wrow + D + CPL * g, ws);
-          const float wv_lt = sum_g(dot_n(wl, vf, 0.0f)), wv_st = sum_g(dot_n(ws, vf, 0.0f));  // Wg_x . v_j
-          float t_lt = 0.0f, t_st = 0.0f;  // sum_i dz_i P_ij per branch
-          for (unsigned long long mm = m_lt | m_st; mm; mm &= mm - 1) {
-            const int I = __builtin_ctzll(mm);
-            const bool lt = (m_lt >> I) & 1ull, st = (m_st >> I) & 1ull;
-            const int r0 = I * kTile;
-            float qa[CPL], ga[CPL];
-            load_n<CPL>(Qs + (r0 + q) * LDR + CPL * g, qa);
-            load_n<CPL>(Gs + (r0 + q) * LDR + CPL * g, ga);
-            f32x4 s = {0.f, 0.f, 0.f, 0.f}, gv = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int c = 0; c < CPL; ++c) {
-              s = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[c], kf[c], s, 0, 0, 0);
-              gv = __builtin_amdgcn_mfma_f32_16x16x4f32(ga[c], vf[c], gv, 0, 0, 0);
-            }
-            const int i0 = r0 + 4 * g;  // this lane's rows i0 .. i0+3
-            unsigned ok = 15u;
-            if (I == J && !p.bidir) {
-              ok = 0u;
-#pragma unroll
-              for (int r = 0; r < 4; ++r) ok |= i0 + r >= j ? 1u << r : 0u;
-            }
-            float al[4], dz[4], pc[4], ds[4];
-            load_n<4>(rch + i0, al);
-            load_n<4>(rch + rows + i0, dz);
-            zero_n(pc);
-            zero_n(ds);
-            if (lt) {
-              float Dx[4], l2[4];
-              load_n<4>(rch + 2 * rows + i0, Dx);
-              load_n<4>(rch + 4 * rows + i0, l2);
-              unsigned v = ok;
-              const int Jb = j / BK;
-              if (PERPOS) {
-                const uint4 w4 = *reinterpret_cast<const uint4 *>(mw + ml.selw + (Jb >> 5) * ml.SR + i0);
-                const unsigned wr[4] = {w4.x, w4.y, w4.z, w4.w};
-                unsigned sb = 0u;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) sb |= ((wr[r] >> (Jb & 31)) & 1u) << r;
-                v &= sb;
-              } else if (BK < kTile) {
-                if (((mw[ml.selw + (Jb >> 5) * ml.SR + i0 / BK] >> (Jb & 31)) & 1u) == 0u) v = 0u;
-              }
-#pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                const float pr = (v >> r) & 1u ? __builtin_amdgcn_exp2f(s[r] - l2[r]) : 0.0f;
-                pc[r] = al[r] * pr;
-                ds[r] = pr * fmaf(al[r], gv[r], fmaf(dz[r], wv_lt, -Dx[r]));
-                t_lt = fmaf(dz[r], pr, t_lt);
-              }
-            }
-            if (st) {
-              float Dx[4], l2[4];
-              load_n<4>(rch + 3 * rows + i0, Dx);
-              load_n<4>(rch + 5 * rows + i0, l2);
-              int4 kd = make_int4(0, 0, 0, 0);
-              if (p.sblk > 0) kd = *reinterpret_cast<const int4 *>(kid + i0);
-              const int kdv[4] = {kd.x, kd.y, kd.z, kd.w};
-#pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                const bool v = ((ok >> r) & 1u) && st_sees(p, i0 + r - j, kdv[r] - kid_k, j);
-                const float pr = v ? __builtin_amdgcn_exp2f(s[r] - l2[r]) : 0.0f;
-                const float as = 1.0f - al[r];
-                pc[r] = fmaf(as, pr, pc[r]);
-                ds[r] = fmaf(pr, fmaf(as, gv[r], fmaf(dz[r], wv_st, -Dx[r])), ds[r]);
-                t_st = fmaf(dz[r], pr, t_st);
-              }
-            }
-            // dV^T += dO^T (a P), dK^T += Q^T dS: row = query 4g + r, column = channel 16*mb + q
-            float gc[NMB][4], qc[NMB][4];
-#pragma unroll
-            for (int mb = 0; mb < NMB; ++mb) {
-              col_frag<LDR>(Gs + r0 * LDR, g, 16 * mb + q, gc[mb]);
-              col_frag<LDR>(Qs + r0 * LDR, g, 16 * mb + q, qc[mb]);
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-              for (int mb = 0; mb < NMB; ++mb) {
-                dv[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(gc[mb][r], pc[r], dv[mb], 0, 0, 0);
-                dk[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(qc[mb][r], ds[r], dk[mb], 0, 0, 0);
-              }
-          }
-          // the gate part of dV: sum_i dz_i P_ij times the gate row of the branch
-          t_lt = sum_g(t_lt);
-          t_st = sum_g(t_st);
-#pragma unroll
-          for (int mb = 0; mb < NMB; ++mb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const int c = 16 * mb + 4 * g + r;
-              if (c < D) dv[mb][r] += fmaf(t_lt, wrow[c], t_st * wrow[D + c]);
-            }
-        }
-      }
-      if (in_range) {
-        store_grad_row<T, D>(dK + head_kv + (size_t)row * D, dk, p.scale, key_ok, p, true, row, g);
-        store_grad_row<T, D>(dV + head_kv + (size_t)row * D, dv, 1.0f, key_ok, p, false, row, g);
-      }
-    }
+// one query head as the gate pass and dQ read it
+struct QueryHead {
+  Slice Q, dO, o_lt, o_st, lse_lt, lse_st;
+  template <typename T>
+  __device__ __forceinline__ QueryHead(const T *q, const T *g, const float *ol, const float *os, const float *ll, const float *lst, int bh,
+                                       int L, int D)
+      : Q(q + (size_t)bh * L * D, (size_t)L * D * sizeof(T)), dO(g + (size_t)bh * L * D, (size_t)L * D * sizeof(T)),
+        o_lt(ol + (size_t)bh * L * D, (size_t)L * D * 4), o_st(os + (size_t)bh * L * D, (size_t)L * D * 4),
+        lse_lt(ll + (size_t)bh * L, (size_t)L * 4), lse_st(lst + (size_t)bh * L, (size_t)L * 4)
+  {
   }
-
-  // ---- dQ: query tiles ----
-  if (!do_dq) return;
-  const bool have_rc = (do_gate || do_dkv) && hc >= hpg;  // the row constants of every head are in LDS
-  float *Ks = A0, *Vs = A0 + rows * LDR;
-  __syncthreads();
-  for (int t = T0 + wv; t < NT; t += W) {
-    const int r = t * kTile + q;
-    float kx[CPL], vx[CPL];
-    zero_n(kx);
-    zero_n(vx);
-    if (r < p.L && r >= p0) {
-      load_n<CPL>(K + head_kv + (size_t)r * D + CPL * g, kx);
-      load_n<CPL>(V + head_kv + (size_t)r * D + CPL * g, vx);
-    }
-    store_n<CPL>(Ks + r * LDR + CPL * g, kx);
-    store_n<CPL>(Vs + r * LDR + CPL * g, vx);
+};
+// the gate of one head, this lane's channels of its row, and the running gradient sums of the rows this wavefront took
+template <int D>
+struct GateSums {
+  float wl[Geo<D>::CPL], ws[Geo<D>::CPL], bias, gl[Geo<D>::CPL], gs[Geo<D>::CPL], gb;
+  __device__ __forceinline__ GateSums(const float *gate_w, const float *gate_b, int h, int g)
+  {
+    load_n<Geo<D>::CPL>(gate_w + (size_t)h * 2 * D + Geo<D>::CPL * g, wl);
+    load_n<Geo<D>::CPL>(gate_w + (size_t)h * 2 * D + D + Geo<D>::CPL * g, ws);
+    bias = gate_b ? gate_b[h] : 0.0f;
+    zero_n(gl);
+    zero_n(gs);
+    gb = 0.0f;
   }
-  __syncthreads();
-  const int n_task = (NT - T0) * hpg;
-  for (int rnd = 0; rnd * W < n_task; ++rnd) {
-    const int u = rnd * W + ((rnd & 1) ? W - 1 - wv : wv);
-    if (u >= n_task) continue;
-    const int I = NT - 1 - u / hpg;
-    const int hh = u % hpg;
-    const int bh = bg * hpg + hh;
-    const int h = bh % p.H;
-    const int iq = I * kTile + q;
-    const bool in_range = iq < p.L;
-    const bool active = in_range && iq >= p0;
-    const int row = min(iq, p.L - 1);
-    const size_t lrow = (size_t)bh * p.L + row, rowoff = lrow * D;
-    float qf[CPL], gr[CPL], wl[CPL], ws[CPL];
-    zero_n(qf);
-    zero_n(gr);
-    load_n<CPL>(gate_w + (size_t)h * 2 * D + CPL * g, wl);
-    load_n<CPL>(gate_w + (size_t)h * 2 * D + D + CPL * g, ws);
-    if (active) {
-      load_n<CPL>(Q + rowoff + CPL * g, qf);
-      load_n<CPL>(dO + rowoff + CPL * g, gr);
-    }
-#pragma unroll
-    for (int i = 0; i < CPL; ++i) qf[i] *= c2;
-    RowConst c;
-    float l2_lt, l2_st;
-    if (have_rc) {
-      const float *rch = rc + 6 * hh * rows;
-      c.al = rch[iq];
-      c.dz = rch[rows + iq];
-      c.D_lt = rch[2 * rows + iq];
-      c.D_st = rch[3 * rows + iq];
-      l2_lt = rch[4 * rows + iq];
-      l2_st = rch[5 * rows + iq];
-    } else {
-      float ol[CPL], os[CPL];
-      zero_n(ol);
-      zero_n(os);
-      if (active) {
-        load_n<CPL>(o_lt + rowoff + CPL * g, ol);
-        load_n<CPL>(o_st + rowoff + CPL * g, os);
-      }
-      c = row_const(gr, ol, os, wl, ws, gate_b ? gate_b[h] : 0.0f, active);
-      l2_lt = active ? lse_lt[lrow] * kLog2eF : kHugeF;
-      l2_st = active ? lse_st[lrow] * kLog2eF : kHugeF;
-    }
-    float gx_lt[CPL], gx_st[CPL];  // dO_x of this lane's row
+  // sums over the 16 rows of the lanes, then over the workgroup's W wavefronts in order, to out[2D+1]; red: [kMaxWaves][2D+1] in LDS
+  __device__ __forceinline__ void finish(float (*red)[2 * D + 1], float *out, int lane, int wv, int W)
+  {
+    constexpr int CPL = Geo<D>::CPL, GW = 2 * D + 1;
+    const int q = lane & 15, g = lane >> 4;
 #pragma unroll
     for (int i = 0; i < CPL; ++i) {
-      gx_lt[i] = fmaf(c.al, gr[i], c.dz * wl[i]);
-      gx_st[i] = fmaf(1.0f - c.al, gr[i], c.dz * ws[i]);
+      gl[i] = sum_row(gl[i]);
+      gs[i] = sum_row(gs[i]);
     }
-    f32x4 dq[NMB];
+    gb = sum_row(gb);
+    if (q == 0) {
 #pragma unroll
-    for (int mb = 0; mb < NMB; ++mb) dq[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const unsigned long long m_lt = tile_mask(mw, ml.tm_lt, I), m_st = tile_mask(mw, ml.tm_st, I);
-    const int kid_q = p.sblk > 0 ? kid[iq] : 0;
-    for (unsigned long long mm = m_lt | m_st; mm; mm &= mm - 1) {
-      const int J = __builtin_ctzll(mm);
-      const bool lt = (m_lt >> J) & 1ull, st = (m_st >> J) & 1ull;
-      float kf[CPL], vf[CPL];
-      load_n<CPL>(Ks + (J * kTile + q) * LDR + CPL * g, kf);
-      load_n<CPL>(Vs + (J * kTile + q) * LDR + CPL * g, vf);
-      f32x4 s = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int i = 0; i < CPL; ++i) s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i], qf[i], s, 0, 0, 0);
-      const int key0 = J * kTile + 4 * g;
-      unsigned ok = 15u;
-      if (J == T0 || J == I || J == NT - 1) {
-        ok = 0u;
-        const int hi = p.bidir ? p.L - 1 : iq;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) ok |= (key0 + r >= p0 && key0 + r <= hi) ? 1u << r : 0u;
+      for (int i = 0; i < CPL; ++i) {
+        red[wv][CPL * g + i] = gl[i];
+        red[wv][D + CPL * g + i] = gs[i];
       }
-      float ds[4];
-      zero_n(ds);
-      if (lt) {
-        f32x4 gv = {0.f, 0.f, 0.f, 0.f};
+      if (g == 0) red[wv][2 * D] = gb;
+    }
+    __syncthreads();
+    for (int c = threadIdx.x; c < GW; c += blockDim.x) {
+      float a = 0.0f;
+      for (int w = 0; w < W; ++w) a += red[w][c];
+      out[c] = a;
+    }
+  }
+};
+
+// Query tile I.  sel_head: the head's selection rows (per query block, or per position of its group).  sink() takes the row
+// constants, the selection and the row's Q and dO when do_rows asks for them.
+template <typename T, int D, int BK, bool PERPOS, typename TileRows, typename Sink>
+__device__ __forceinline__ void query_tile(const KParams &p, int I, int T0, int NT, int p0, int lane, const QueryHead &in,
+                                           const TileRows &Kr, const TileRows &Vr, const int *sel_head, unsigned *my_lds,
+                                           GateSums<D> &gate, bool do_rows, bool do_dq, T *dQ_head, Sink &&sink)
+{
+  constexpr int CPL = Geo<D>::CPL, NMB = Geo<D>::NMB;
+  const int q = lane & 15, g = lane >> 4;
+  const float c2 = p.scale * kLog2eF;
+  const int iq = I * kTile + q;
+  const bool active = iq < p.L && iq >= p0;
+  float qf[CPL], gr[CPL], ol[CPL], os[CPL];
+  const unsigned e_at = active ? (unsigned)(iq * D + CPL * g) : kNowhere / 4;  // rows that take no part read zeros
+  load_n<T>(in.dO, e_at * (unsigned)sizeof(T), gr);
+  load_n<float>(in.o_lt, e_at * 4u, ol);
+  load_n<float>(in.o_st, e_at * 4u, os);
+  load_n<T>(in.Q, e_at * (unsigned)sizeof(T), qf);
+  const unsigned l_at = active ? 4u * (unsigned)iq : kNowhere;
+  float l2_lt = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(in.lse_lt.d, l_at, 0, 0)) * kLog2eF;
+  float l2_st = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(in.lse_st.d, l_at, 0, 0)) * kLog2eF;
+  if (!active) l2_lt = l2_st = kHugeF;
+  LtSel<BK, PERPOS> ls;
+  ls.build(p, my_lds, PERPOS ? nullptr : sel_head + (size_t)I * (kTile / BK) * p.k,
+           PERPOS && active ? sel_head + (size_t)iq * p.k : nullptr, I, iq, p0, lane);
+
+  // ---- gate pass of the tile's rows ----
+  const float a_ll = sum_g(dot_n(gr, ol, 0.0f)), a_ss = sum_g(dot_n(gr, os, 0.0f));
+  const float w_l = sum_g(dot_n(gate.wl, ol, 0.0f)), w_s = sum_g(dot_n(gate.ws, os, 0.0f));
+  float al = sigmoid(gate.bias + w_l + w_s);
+  float dz = (a_ll - a_ss) * al * (1.0f - al);
+  float D_lt = al * a_ll + dz * w_l, D_st = (1.0f - al) * a_ss + dz * w_s;
+  if (!active) al = dz = D_lt = D_st = 0.0f;
+  if (do_rows) {
+    sink(I, al, dz, D_lt, D_st, l2_lt, l2_st, ls, qf, gr);
 #pragma unroll
-        for (int i = 0; i < CPL; ++i) gv = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i], gx_lt[i], gv, 0, 0, 0);
-        unsigned v = ok;
-        if (PERPOS || BK < kTile) {
-          const int Jb = key0 / BK;
-          const int x = PERPOS ? iq : iq / BK;
-          if (((mw[ml.selw + (Jb >> 5) * ml.SR + x] >> (Jb & 31)) & 1u) == 0u) v = 0u;
-        }
+    for (int i = 0; i < CPL; ++i) {
+      gate.gl[i] = fmaf(dz, ol[i], gate.gl[i]);
+      gate.gs[i] = fmaf(dz, os[i], gate.gs[i]);
+    }
+    gate.gb += dz;
+  }
+  if (!do_dq) return;
+
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          ds[r] = (v >> r) & 1u ? __builtin_amdgcn_exp2f(s[r] - l2_lt) * (gv[r] - c.D_lt) : 0.0f;
+  for (int i = 0; i < CPL; ++i) {
+    qf[i] *= c2;
+    ol[i] = fmaf(al, gr[i], dz * gate.wl[i]);         // dO_lt of this lane's row
+    os[i] = fmaf(1.0f - al, gr[i], dz * gate.ws[i]);  // dO_st
+  }
+  f32x4 dq[NMB];
+#pragma unroll
+  for (int mb = 0; mb < NMB; ++mb) dq[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int kid_q = mask_block(p, iq);
+  const int J_hi = p.bidir ? NT - 1 : I;
+  Walk wk;
+  const int dr = (q >> 2) == g ? (q & 3) : 4;
+  float kf[CPL], vf[CPL], kc[NMB][4];
+  auto body = [&](auto kind, auto unit, unsigned &mask) __attribute__((always_inline)) {
+    constexpr int KIND = decltype(kind)::value;
+    constexpr bool LT = KIND <= 1, ST = KIND != 1;
+    const int t = wk.base + __builtin_ctz(mask);
+    mask &= mask - 1;
+    const int t_next = wk.peek();
+    f32x4 s = {0.f, 0.f, 0.f, 0.f}, g_lt = s, g_st = s;
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) {
+      s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c], qf[c], s, 0, 0, 0);
+      if constexpr (LT) g_lt = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[c], ol[c], g_lt, 0, 0, 0);
+      if constexpr (ST) g_st = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[c], os[c], g_st, 0, 0, 0);
+    }
+    Kr.row(t_next, kf);
+    Vr.row(t_next, vf);
+    const int key0 = t * kTile + 4 * g;
+    float ds[4];
+    if constexpr (KIND == 0) {
+      const unsigned span = (unsigned)((p.bidir ? p.L - 1 : iq) - p0);
+      bool s_lt = (wk.lt >> (t & 31)) & 1u;
+      if (PERPOS || BK < kTile) s_lt &= ls.sees(q, key0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const bool ok = (unsigned)(key0 + r - p0) <= span;
+        const bool v_st = ok & st_sees<decltype(unit)::value>(p, iq, key0 + r, kid_q, mask_block(p, key0, r), key0 + r >= p.last_lo);
+        const float e = __builtin_amdgcn_exp2f(s[r] - l2_lt), f = __builtin_amdgcn_exp2f(s[r] - l2_st);
+        ds[r] = (ok & s_lt ? e : 0.0f) * (g_lt[r] - D_lt);
+        ds[r] = fmaf(v_st ? f : 0.0f, g_st[r] - D_st, ds[r]);
       }
-      if (st) {
-        f32x4 gv = {0.f, 0.f, 0.f, 0.f};
+    } else if constexpr (KIND == 1) {
+      const bool v = (PERPOS || BK < kTile) ? ls.sees(q, key0) : true;
 #pragma unroll
-        for (int i = 0; i < CPL; ++i) gv = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i], gx_st[i], gv, 0, 0, 0);
-        int4 kd = make_int4(0, 0, 0, 0);
-        if (p.sblk > 0) kd = *reinterpret_cast<const int4 *>(kid + key0);
-        const int kdv[4] = {kd.x, kd.y, kd.z, kd.w};
+      for (int r = 0; r < 4; ++r) {
+        const float e = __builtin_amdgcn_exp2f(s[r] - l2_lt);
+        ds[r] = ((PERPOS || BK < kTile) ? (v ? e : 0.0f) : e) * (g_lt[r] - D_lt);
+      }
+    } else if constexpr (KIND == 2) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float e = __builtin_amdgcn_exp2f(s[r] - l2_st);
+        ds[r] = (st_sees<decltype(unit)::value>(p, iq, key0 + r, kid_q, mask_block(p, key0, r), false) ? e : 0.0f) * (g_st[r] - D_st);
+      }
+    } else {
+      const float sd = dr == 0 ? s[0] : dr == 1 ? s[1] : dr == 2 ? s[2] : s[3];
+      const float gd = dr == 0 ? g_st[0] : dr == 1 ? g_st[1] : dr == 2 ? g_st[2] : g_st[3];
+      const float x = __builtin_amdgcn_exp2f(sd - l2_st) * (gd - D_st);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) ds[r] = dr == r ? x : 0.0f;
+    }
+    if constexpr (TileRows::kNear) Kr.col(t, kc);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int mb = 0; mb < NMB; ++mb) dq[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kc[mb][r], ds[r], dq[mb], 0, 0, 0);
+    if constexpr (!TileRows::kNear) Kr.col(t_next, kc);
+  };
+  auto walk = [&](auto unit) __attribute__((always_inline)) {
+    for (int w = T0 >> 5; w <= J_hi >> 5; ++w) {
+      unsigned dia;
+      const unsigned st = st_word<false>(p, I, w, T0, J_hi, lane, dia);
+      const unsigned edge =
+          word_range(w, T0, T0) | word_range(w, I, I) | word_range(w, NT - 1, NT - 1) | word_range(w, p.last_lo / kTile, NT - 1);
+      wk.start(w, ls.word(w), st, edge, dia);
+      if (!wk.any()) continue;
+      const int t = wk.peek();
+      Kr.row(t, kf);
+      Vr.row(t, vf);
+      if constexpr (!TileRows::kNear) Kr.col(t, kc);
+      while (wk.m0) body(std::integral_constant<int, 0>{}, unit, wk.m0);
+      while (wk.m1) body(std::integral_constant<int, 1>{}, unit, wk.m1);
+      while (wk.m2) body(std::integral_constant<int, 2>{}, unit, wk.m2);
+      while (wk.m3) body(std::integral_constant<int, 3>{}, unit, wk.m3);
+    }
+  };
+  if (p.sblk <= 1) walk(std::true_type{});
+  else walk(std::false_type{});
+  const int el = fresh_lane(), ei = I * kTile + (el & 15);
+  if (ei < p.L) store_grad_row<T, D>(dQ_head + (size_t)ei * D, dq, p.scale, ei >= p0, p, true, ei, el >> 4);
+}
+
+// Key tile J; kf, vf: this lane's channels of its key and value row (zeros where the row takes no part).  The hpg query heads that
+// read the rows add into the same gradients.  src gives their Q and dO rows, row constants, tile words and selection bits.
+template <typename T, int D, int BK, bool PERPOS, typename Src>
+__device__ __forceinline__ void key_tile(const KParams &p, int J, int T0, int NT, int p0, int lane, float (&kf)[Geo<D>::CPL],
+                                         const float (&vf)[Geo<D>::CPL], int hpg, const Src &src, T *dK_head, T *dV_head)
+{
+  constexpr int CPL = Geo<D>::CPL, NMB = Geo<D>::NMB;
+  const int q = lane & 15, g = lane >> 4;
+  const int NWb = (p.NB + 31) / 32;
+  const float c2 = p.scale * kLog2eF;
+  const int j = J * kTile + q;
+  f32x4 dk[NMB], dv[NMB];
+#pragma unroll
+  for (int mb = 0; mb < NMB; ++mb) {
+    dk[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    dv[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+#pragma unroll
+  for (int i = 0; i < CPL; ++i) kf[i] *= c2;
+  const int kid_k = mask_block(p, j);
+  const bool last_k = j >= p.last_lo;
+  const int I_lo = p.bidir ? T0 : J;
+  const int Jb = j / BK;  // this lane's key block
+  const bool last_tile = J * kTile + kTile - 1 >= p.last_lo;  // holds last-block keys
+  const int dr = (q >> 2) == g ? (q & 3) : 4;
+
+  for (int hl = 0; hl < hpg; ++hl) {
+    const auto Qr = src.q_rows(hl);
+    const auto Gr = src.g_rows(hl);
+    constexpr bool near = decltype(src.q_rows(0))::kNear;
+    const float *wrow = src.gate_row(hl);
+    float t_lt = 0.0f, t_st = 0.0f;  // sum_i dz_i P_ij per branch
+    float wv_lt, wv_st;              // Wg_x . v_j
+    {
+      float wl[CPL], ws[CPL];
+      load_n<CPL>(wrow + CPL * g, wl);
+      load_n<CPL>(wrow + D + CPL * g, ws);
+      wv_lt = sum_g(dot_n(wl, vf, 0.0f));
+      wv_st = sum_g(dot_n(ws, vf, 0.0f));
+    }
+    Walk wk;
+    float qa[CPL], ga[CPL], qc[NMB][4], gc[NMB][4];
+    float al[4], dz[4], D_lt[4], D_st[4], l_lt[4], l_st[4];  // row constants of this lane's four query rows
+    auto consts = [&](int I) __attribute__((always_inline)) {
+      auto get = [&](int k, float (&x)[4]) { src.constant(hl, I, k, x); };
+      get(0, al);
+      get(1, dz);
+      get(2, D_lt);
+      get(3, D_st);
+      get(4, l_lt);
+      get(5, l_st);
+    };
+    auto body = [&](auto kind, auto unit, unsigned &mask) __attribute__((always_inline)) {
+      constexpr int KIND = decltype(kind)::value;
+      constexpr bool LT = KIND <= 1, ST = KIND != 1;
+      const int t = wk.base + __builtin_ctz(mask);
+      mask &= mask - 1;
+      const int t_next = wk.peek();
+      if constexpr (near) consts(t);
+      f32x4 s = {0.f, 0.f, 0.f, 0.f}, gv = s;
+#pragma unroll
+      for (int c = 0; c < CPL; ++c) {
+        s = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[c], kf[c], s, 0, 0, 0);
+        gv = __builtin_amdgcn_mfma_f32_16x16x4f32(ga[c], vf[c], gv, 0, 0, 0);
+      }
+      Qr.row(t_next, qa);
+      Gr.row(t_next, ga);
+      const int i0 = t * kTile + 4 * g;  // this lane's rows i0 .. i0+3
+      float pc[4], ds[4];
+      unsigned w4[4] = {1u, 1u, 1u, 1u};  // bit 0: the row selected this lane's key block
+      if constexpr (LT && PERPOS) {
+        const unsigned *sb = src.bits + i0 * 2 + (Jb >> 5);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) w4[r] = sb[2 * r] >> (Jb & 31);
+      } else if constexpr (LT && BK < kTile) {
+        const unsigned x = src.bits[(t * 2 + (g >> 1)) * NWb + min(Jb >> 5, NWb - 1)] >> (Jb & 31);
+        w4[0] = w4[1] = w4[2] = w4[3] = x;
+      }
+      if constexpr (KIND != 3) {
+        const bool in_lt = KIND != 0 || ((wk.lt >> (t & 31)) & 1u) != 0u;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const bool v = ((ok >> r) & 1u) && st_sees(p, iq - key0 - r, kid_q - kdv[r], key0 + r);
-          const float e = v ? __builtin_amdgcn_exp2f(s[r] - l2_st) : 0.0f;
-          ds[r] = fmaf(e, gv[r] - c.D_st, ds[r]);
+          bool ok = true;
+          if constexpr (KIND == 0) ok = (i0 + r >= j) | (p.bidir != 0);
+          pc[r] = ds[r] = 0.0f;
+          if constexpr (LT) {
+            const float e = __builtin_amdgcn_exp2f(s[r] - l_lt[r]);
+            const float pr = (KIND == 0 || PERPOS || BK < kTile) ? (ok & in_lt & ((w4[r] & 1u) != 0u) ? e : 0.0f) : e;
+            pc[r] = al[r] * pr;
+            ds[r] = pr * fmaf(al[r], gv[r], fmaf(dz[r], wv_lt, -D_lt[r]));
+            t_lt = fmaf(dz[r], pr, t_lt);
+          }
+          if constexpr (ST) {
+            const float e = __builtin_amdgcn_exp2f(s[r] - l_st[r]);
+            const float pr = ok & st_sees<decltype(unit)::value>(p, i0 + r, j, mask_block(p, i0, r), kid_k, KIND == 0 ? last_k : false) ? e : 0.0f;
+            const float as = 1.0f - al[r];
+            pc[r] = fmaf(as, pr, pc[r]);
+            ds[r] = fmaf(pr, fmaf(as, gv[r], fmaf(dz[r], wv_st, -D_st[r])), ds[r]);
+            t_st = fmaf(dz[r], pr, t_st);
+          }
+        }
+      } else {
+        auto pick = [&](const float (&x)[4]) { return dr == 0 ? x[0] : dr == 1 ? x[1] : dr == 2 ? x[2] : x[3]; };
+        const float sd = dr == 0 ? s[0] : dr == 1 ? s[1] : dr == 2 ? s[2] : s[3];
+        const float gd = dr == 0 ? gv[0] : dr == 1 ? gv[1] : dr == 2 ? gv[2] : gv[3];
+        const float zd = pick(dz), as = 1.0f - pick(al);
+        const float e = __builtin_amdgcn_exp2f(sd - pick(l_st));
+        const float pr = dr < 4 ? e : 0.0f;
+        const float xp = as * pr, xs = pr * fmaf(as, gd, fmaf(zd, wv_st, -pick(D_st)));
+        t_st = fmaf(zd, pr, t_st);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          pc[r] = dr == r ? xp : 0.0f;
+          ds[r] = dr == r ? xs : 0.0f;
         }
       }
-      float kc[NMB][4];
-#pragma unroll
-      for (int mb = 0; mb < NMB; ++mb) col_frag<LDR>(Ks + J * kTile * LDR, g, 16 * mb + q, kc[mb]);
+      if constexpr (!near) {
+        consts(t_next);
+      } else {
+        Qr.col(t, qc);
+        Gr.col(t, gc);
+      }
+      // dV^T += dO^T (a P), dK^T += Q^T dS
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int mb = 0; mb < NMB; ++mb)
-          dq[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kc[mb][r], ds[r], dq[mb], 0, 0, 0);
+        for (int mb = 0; mb < NMB; ++mb) {
+          dv[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(gc[mb][r], pc[r], dv[mb], 0, 0, 0);
+          dk[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(qc[mb][r], ds[r], dk[mb], 0, 0, 0);
+        }
+      if constexpr (!near) {
+        Qr.col(t_next, qc);
+        Gr.col(t_next, gc);
+      }
+    };
+    auto walk = [&](auto unit) __attribute__((always_inline)) {
+      for (int w = I_lo >> 5; w <= (NT - 1) >> 5; ++w) {
+        const int I = w * 32 + (lane & 31);
+        const unsigned tw = src.tile_word(min(max(I, T0), NT - 1), J >> 5);
+        const unsigned lt = (unsigned)__ballot((lane < 32) & ((tw >> (J & 31)) & 1u)) & word_range(w, I_lo, NT - 1);
+        unsigned dia;
+        const unsigned st = st_word<true>(p, J, w, I_lo, NT - 1, lane, dia);
+        wk.start(w, lt, st, last_tile ? 0xFFFFFFFFu : word_range(w, J, J), dia);
+        if (!wk.any()) continue;
+        const int t = wk.peek();
+        Qr.row(t, qa);
+        Gr.row(t, ga);
+        if constexpr (!near) {
+          consts(t);
+          Qr.col(t, qc);
+          Gr.col(t, gc);
+        }
+        while (wk.m0) body(std::integral_constant<int, 0>{}, unit, wk.m0);
+        while (wk.m1) body(std::integral_constant<int, 1>{}, unit, wk.m1);
+        while (wk.m2) body(std::integral_constant<int, 2>{}, unit, wk.m2);
+        while (wk.m3) body(std::integral_constant<int, 3>{}, unit, wk.m3);
+      }
+    };
+    if (p.sblk <= 1) walk(std::true_type{});
+    else walk(std::false_type{});
+    // the gate part of dV: sum_i dz_i P_ij times the gate row of the branch
+    t_lt = sum_g(t_lt);
+    t_st = sum_g(t_st);
+#pragma unroll
+    for (int mb = 0; mb < NMB; ++mb)
+      if (16 * mb + 4 * g < D) {
+        float x[4], y[4];
+        load_n<4>(wrow + 16 * mb + 4 * g, x);
+        load_n<4>(wrow + D + 16 * mb + 4 * g, y);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dv[mb][r] += fmaf(t_lt, x[r], t_st * y[r]);
+      }
+  }
+  const int el = fresh_lane(), ej = J * kTile + (el & 15);
+  if (ej < p.L) {
+    store_grad_row<T, D>(dK_head + (size_t)ej * D, dk, p.scale, ej >= p0, p, true, ej, el >> 4);
+    store_grad_row<T, D>(dV_head + (size_t)ej * D, dv, 1.0f, ej >= p0, p, false, ej, el >> 4);
+  }
+}
+
+}  // namespace
+
+// =============================================================================================
+// backward, heads streamed from memory: gate pass and dQ, then dK/dV
+// =============================================================================================
+// What the dK/dV kernel reads (SmallWs): per query tile the row constants [6][16] (alpha, dz, D_lt, D_st and the two lse
+// in log2 units; rows that take no part have lse 1e30: every probability zero), its long-term tile words [NWt], and the
+// selection bits per query block (block size 8) or per position.
+// stages: kBwdStageGate writes those and the partial gate gradients, kBwdStageDQ writes dQ (the row constants are
+// formed in either case).
+template <typename T, int D, int BK, bool PERPOS>
+__global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(D == 32 ? 4 : 5))) void bwd_dq_small_kernel(
+    const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V, const int *__restrict__ valid_len,
+    const int *__restrict__ sel, const float *__restrict__ gate_w, const float *__restrict__ gate_b,
+    const float *__restrict__ o_lt, const float *__restrict__ o_st, const float *__restrict__ lse_lt,
+    const float *__restrict__ lse_st, const T *__restrict__ dO, T *__restrict__ dQ, SmallWs ws, int hpg, int parts,
+    unsigned stages, KParams p)
+{
+  constexpr int GW = 2 * D + 1;
+  extern __shared__ __attribute__((aligned(16))) float small_lds[];  // the wavefronts' selection words
+  __shared__ float red[kMaxWaves][GW];
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = blockDim.x >> 6;
+  const unsigned vid = mfma::xcd_remap(blockIdx.x, gridDim.x);
+  const int bh = (int)(vid / parts), part = (int)(vid % parts);
+  const int NT = (p.L + kTile - 1) / kTile, NWt = (NT + 31) / 32;
+  const int p0 = p.L - clamp_len(valid_len[bh / p.H], p.L);
+  const int T0 = p0 / kTile;
+  const int q = lane & 15, g = lane >> 4;
+  const int kvh = PERPOS ? bh / hpg : bh;
+  const Rows<T, D> Kr(K + (size_t)kvh * p.L * D, p.L, q, g), Vr(V + (size_t)kvh * p.L * D, p.L, q, g);
+  const QueryHead in(Q, dO, o_lt, o_st, lse_lt, lse_st, bh, p.L, D);
+  GateSums<D> gate(gate_w, gate_b, bh % p.H, g);
+  unsigned *my_lds = reinterpret_cast<unsigned *>(small_lds) + wv * lt_words(p, PERPOS);
+  T *dQ_head = dQ + (size_t)bh * p.L * D;
+  const bool do_rows = stages & kBwdStageGate, do_dq = stages & kBwdStageDQ;
+  auto sink = [&](int I, float al, float dz, float D_lt, float D_st, float l2_lt, float l2_st, const LtSel<BK, PERPOS> &ls, const auto &,
+                  const auto &) __attribute__((always_inline)) {
+    const int el = fresh_lane(), eq = el & 15, eg = el >> 4;
+    float *rc = ws.rowc + ((size_t)bh * NT + I) * (6 * kTile);
+    // lane group 0 writes alpha, group 1 dz, 2 D_lt, 3 D_st; groups 0 and 1 then the two lse
+    rc[el] = eg == 0 ? al : eg == 1 ? dz : eg == 2 ? D_lt : D_st;
+    if (eg < 2) rc[64 + el] = eg == 0 ? l2_lt : l2_st;
+    if (PERPOS && bh % hpg != 0) return;
+    for (int i = el; i < NWt; i += 64) ws.tile_words[((size_t)kvh * NT + I) * NWt + i] = ls.tiles[i];
+    if constexpr (PERPOS) {
+      if (eg == 0) *reinterpret_cast<unsigned long long *>(ws.sel_bits + ((size_t)kvh * NT * kTile + I * kTile + eq) * 2) = ls.row;
+    } else if constexpr (BK < kTile) {
+      for (int i = el; i < 2 * ls.NWb; i += 64) ws.sel_bits[((size_t)kvh * NT + I) * 2 * ls.NWb + i] = ls.bits[i];
     }
-    if (in_range) store_grad_row<T, D>(dQ + rowoff, dq, p.scale, active, p, true, row, g);
+  };
+  for (int u = part * W + wv; u < NT; u += parts * W) {
+    const int I = NT - 1 - u;
+    if (I < T0 || p0 >= p.L) {  // no valid query
+      if (do_dq) zero_fill(dQ_head + I * kTile * D, min(kTile, p.L - I * kTile) * D, fresh_lane());
+      continue;
+    }
+    query_tile<T, D, BK, PERPOS>(p, I, T0, NT, p0, lane, in, Kr, Vr, sel + (size_t)kvh * (PERPOS ? p.L : p.NB) * p.k, my_lds, gate,
+                                 do_rows, do_dq, dQ_head, sink);
+  }
+  if (do_rows) gate.finish(red, ws.partial + ((size_t)bh * parts + part) * GW, lane, wv, W);
+}
+
+template <typename T, int D, int BK, bool PERPOS>
+__global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(D == 32 ? 3 : 4))) void bwd_dkv_small_kernel(
+    const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V, const int *__restrict__ valid_len,
+    const float *__restrict__ gate_w, const T *__restrict__ dO, SmallWs ws, T *__restrict__ dK, T *__restrict__ dV, int hpg, int parts,
+    KParams p)
+{
+  constexpr int CPL = Geo<D>::CPL;
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = blockDim.x >> 6;
+  const unsigned vid = mfma::xcd_remap(blockIdx.x, gridDim.x);
+  const int bg = (int)(vid / parts), part = (int)(vid % parts);
+  const int NT = (p.L + kTile - 1) / kTile, NWt = (NT + 31) / 32, NWb = (p.NB + 31) / 32;
+  const int p0 = p.L - clamp_len(valid_len[bg / (p.H / hpg)], p.L);
+  const int T0 = p0 / kTile;
+  const int q = lane & 15, g = lane >> 4;
+  const size_t head_kv = (size_t)bg * p.L * D;
+  const Rows<T, D> Kr(K + head_kv, p.L, q, g), Vr(V + head_kv, p.L, q, g);
+  struct {
+    const T *Q, *dO;
+    const float *rowc, *gate_w;
+    const unsigned *bits;
+    Slice words;
+    int bh0, H, L, NT, NWt, q, g;
+    __device__ __forceinline__ Rows<T, D> q_rows(int hl) const { return Rows<T, D>(Q + (size_t)(bh0 + hl) * L * D, L, q, g); }
+    __device__ __forceinline__ Rows<T, D> g_rows(int hl) const { return Rows<T, D>(dO + (size_t)(bh0 + hl) * L * D, L, q, g); }
+    __device__ __forceinline__ const float *gate_row(int hl) const { return gate_w + (size_t)((bh0 + hl) % H) * 2 * D; }
+    __device__ __forceinline__ void constant(int hl, int I, int k, float (&x)[4]) const
+    {
+      const Slice rc(rowc + (size_t)(bh0 + hl) * NT * (6 * kTile), (size_t)NT * (6 * kTile) * 4);
+      load_n<float>(rc, (unsigned)(I * (6 * kTile) + 16 * k + 4 * g) * 4u, x);
+    }
+    __device__ __forceinline__ unsigned tile_word(int I, int w) const
+    {
+      return __builtin_amdgcn_raw_buffer_load_b32(words.d, 4u * (unsigned)(I * NWt + w), 0, 0);
+    }
+  } src = {Q, dO, ws.rowc, gate_w, ws.sel_bits + (size_t)bg * (PERPOS ? NT * kTile * 2 : NT * 2 * NWb),
+           Slice(ws.tile_words + (size_t)bg * NT * NWt, (size_t)NT * NWt * 4), bg * hpg, p.H, p.L, NT, NWt, q, g};
+  for (int J = part * W + wv; J < NT; J += parts * W) {
+    if (J < T0 || p0 >= p.L) {  // no valid key
+      const int cnt = min(kTile, p.L - J * kTile) * D, el = fresh_lane();
+      zero_fill(dK + head_kv + (size_t)J * kTile * D, cnt, el);
+      zero_fill(dV + head_kv + (size_t)J * kTile * D, cnt, el);
+      continue;
+    }
+    float kf[CPL], vf[CPL];
+    Kr.row(J, kf);
+    Vr.row(J, vf);
+    key_tile<T, D, BK, PERPOS>(p, J, T0, NT, p0, lane, kf, vf, hpg, src, dK + head_kv, dV + head_kv);
+  }
+}
+
+// =============================================================================================
+// backward, whole heads in LDS: gate pass, dQ and dK/dV of a (row, head), or of a (row, group), in one workgroup
+// =============================================================================================
+// K and V are staged, the query tiles run (each leaving its Q and dO rows, row constants and selection in LDS), then the key
+// tiles.  Every tensor comes from memory once, in two round trips.  overlay: Q and dO do not fit beside K and V; they take
+// their place after the query tiles, read a second time (from L2).
+template <typename T, int D, int BK, bool PERPOS>
+__global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(4))) void bwd_res_kernel(
+    const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V, const int *__restrict__ valid_len,
+    const int *__restrict__ sel, const float *__restrict__ gate_w, const float *__restrict__ gate_b,
+    const float *__restrict__ o_lt, const float *__restrict__ o_st, const float *__restrict__ lse_lt,
+    const float *__restrict__ lse_st, const T *__restrict__ dO, T *__restrict__ dQ, T *__restrict__ dK, T *__restrict__ dV,
+    float *__restrict__ partial, int hpg, int overlay, unsigned stages, KParams p)
+{
+  constexpr int CPL = Geo<D>::CPL, GW = 2 * D + 1;
+  extern __shared__ __attribute__((aligned(16))) float small_lds[];
+  __shared__ float red[kMaxWaves][GW];
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = blockDim.x >> 6;
+  const int bg = blockIdx.x;  // (row, key/value head)
+  const int NT = (p.L + kTile - 1) / kTile, NWt = (NT + 31) / 32, NWb = (p.NB + 31) / 32;
+  const int p0 = p.L - clamp_len(valid_len[bg / (p.H / hpg)], p.L);
+  const int T0 = p0 / kTile;
+  const int q = lane & 15, g = lane >> 4;
+  const size_t head_kv = (size_t)bg * p.L * D;
+  const bool do_gate = stages & kBwdStageGate, do_dq = stages & kBwdStageDQ, do_dkv = stages & kBwdStageDKV;
+  const ResLayout lay(p, PERPOS, hpg, overlay, W);
+  float *Ks = small_lds, *Vs = Ks + lay.pitch, *QG = small_lds + lay.qg, *rc = small_lds + lay.rowc;
+  unsigned *words = reinterpret_cast<unsigned *>(small_lds + lay.words), *bits = words + NT * NWt;
+  unsigned *my_lds = reinterpret_cast<unsigned *>(small_lds + lay.waves) + wv * lt_words(p, PERPOS);
+
+  stage_pair<T, D>(K + head_kv, V + head_kv, Ks, Vs, p.L, T0, NT, lane, wv, W);
+  __syncthreads();
+  const LdsRows<D> Kr(Ks, q, g), Vr(Vs, q, g);
+  const int *sel_head = sel + (size_t)bg * (PERPOS ? p.L : p.NB) * p.k;
+  for (int hl = 0; hl < hpg; ++hl) {
+    const int bh = bg * hpg + hl;
+    const QueryHead in(Q, dO, o_lt, o_st, lse_lt, lse_st, bh, p.L, D);
+    GateSums<D> gate(gate_w, gate_b, bh % p.H, g);
+    T *dQ_head = dQ + (size_t)bh * p.L * D;
+    auto sink = [&](int I, float al, float dz, float D_lt, float D_st, float l2_lt, float l2_st, const LtSel<BK, PERPOS> &ls,
+                    const float (&qf)[CPL], const float (&gr)[CPL]) __attribute__((always_inline)) {
+      float *c = rc + (hl * NT + I) * (6 * kTile);
+      c[lane] = g == 0 ? al : g == 1 ? dz : g == 2 ? D_lt : D_st;
+      if (g < 2) c[64 + lane] = g == 0 ? l2_lt : l2_st;
+      if (!overlay) {
+        const int at = 2 * hl * lay.pitch + (I * kTile + q) * kLdsRow<D> + CPL * g;
+        store_lds<CPL>(QG + at, qf);
+        store_lds<CPL>(QG + lay.pitch + at, gr);
+      }
+      if (hl > 0) return;
+      for (int i = lane; i < NWt; i += 64) words[I * NWt + i] = ls.tiles[i];
+      if constexpr (PERPOS) {
+        if (g == 0) *reinterpret_cast<unsigned long long *>(bits + (I * kTile + q) * 2) = ls.row;
+      } else if constexpr (BK < kTile) {
+        for (int i = lane; i < 2 * NWb; i += 64) bits[I * 2 * NWb + i] = ls.bits[i];
+      }
+    };
+    for (int u = wv; u < NT; u += W) {
+      const int I = NT - 1 - u;
+      if (I < T0 || p0 >= p.L) {  // no valid query
+        if (do_dq) zero_fill(dQ_head + I * kTile * D, min(kTile, p.L - I * kTile) * D, fresh_lane());
+        continue;
+      }
+      query_tile<T, D, BK, PERPOS>(p, I, T0, NT, p0, lane, in, Kr, Vr, sel_head, my_lds, gate, true, do_dq, dQ_head, sink);
+    }
+    if (hl > 0) __syncthreads();
+    gate.finish(red, partial + (size_t)bh * GW, lane, wv, W);  // (its barrier also closes the query tiles of the head)
+  }
+  if (!do_dkv) return;
+  (void)do_gate;
+  float kf[CPL], vf[CPL];
+  if (overlay) {
+    __syncthreads();
+    for (int hl = 0; hl < hpg; ++hl) {
+      const size_t at = (size_t)(bg * hpg + hl) * p.L * D;
+      stage_pair<T, D>(Q + at, dO + at, QG + 2 * hl * lay.pitch, QG + (2 * hl + 1) * lay.pitch, p.L, T0, NT, lane, wv, W);
+    }
+    __syncthreads();
+  }
+  struct {
+    const float *qg, *rc, *gate_w;
+    const unsigned *bits, *words;
+    int bh0, H, NT, NWt, q, g, pitch;
+    __device__ __forceinline__ LdsRows<D> q_rows(int hl) const { return LdsRows<D>(qg + 2 * hl * pitch, q, g); }
+    __device__ __forceinline__ LdsRows<D> g_rows(int hl) const { return LdsRows<D>(qg + (2 * hl + 1) * pitch, q, g); }
+    __device__ __forceinline__ const float *gate_row(int hl) const { return gate_w + (size_t)((bh0 + hl) % H) * 2 * D; }
+    __device__ __forceinline__ void constant(int hl, int I, int k, float (&x)[4]) const
+    {
+      load_n<4>(rc + (hl * NT + I) * (6 * kTile) + 16 * k + 4 * g, x);
+    }
+    __device__ __forceinline__ unsigned tile_word(int I, int w) const { return words[I * NWt + w]; }
+  } src = {QG, rc, gate_w, bits, words, bg * hpg, p.H, NT, NWt, q, g, lay.pitch};
+  const Rows<T, D> Kg(K + head_kv, p.L, q, g), Vg(V + head_kv, p.L, q, g);
+  for (int u = wv; u < NT; u += W) {
+    const int J = (T0 + u) % NT;  // the tiles without a valid key come last
+    if (J < T0 || p0 >= p.L) {
+      const int cnt = min(kTile, p.L - J * kTile) * D, el = fresh_lane();
+      zero_fill(dK + head_kv + (size_t)J * kTile * D, cnt, el);
+      zero_fill(dV + head_kv + (size_t)J * kTile * D, cnt, el);
+      continue;
+    }
+    if (overlay) {
+      Kg.row(J, kf);
+      Vg.row(J, vf);
+    } else {
+      Kr.row(J, kf);
+      Vr.row(J, vf);
+    }
+    key_tile<T, D, BK, PERPOS>(p, J, T0, NT, p0, lane, kf, vf, hpg, src, dK + head_kv, dV + head_kv);
   }
 }
 
@@ -996,27 +1428,57 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void b
 // =============================================================================================
 namespace {
 
-int res_rows(const KParams &p) { return (p.L + kTile - 1) / kTile * kTile; }
-size_t res_fwd_lds_bytes(const KParams &p, bool perpos)
+bool small_shape(const KParams &p)
 {
-  return ((size_t)2 * res_rows(p) * (p.d + 4) + 16 + mask_layout(p, perpos, false).words) * sizeof(float);
-}
-size_t res_bwd_lds_bytes(const KParams &p, bool perpos, int hc, int waves)
-{
-  return ((size_t)2 * hc * res_rows(p) * (p.d + 4) + 16 + (size_t)6 * hc * res_rows(p) + mask_layout(p, perpos, true).words +
-          (size_t)hc * waves * (2 * p.d + 1)) * sizeof(float);
+  return (p.d == 8 || p.d == 16 || p.d == 32) && (p.b == 8 || p.b == 16) && p.L <= 16384;
 }
 
-bool res_shape(const KParams &p)
+// How a launch is laid out: whether workgroups hold whole heads in LDS (then one workgroup per unit), wavefronts per workgroup,
+// workgroups per unit.  units: query heads, or key/value heads where a workgroup serves a whole group.
+struct SmallPlan {
+  bool res, overlay;
+  int waves, parts;
+  size_t lds;
+};
+constexpr size_t kSmallLds = 80 * 1024 - 4096;  // two workgroups per CU
+// Few heads: eight wavefronts each, a head's latency counts.  Many: four, whose shares are longer and better balanced (always a
+// multiple of the four SIMDs: with five or six wavefronts the backward took 1.4 times as long).
+bool many_heads(int units) { return units >= 2048; }
+int res_waves(int units) { return many_heads(units) ? 4 : 8; }
+SmallPlan stream_plan(const KParams &p, int units, size_t words_per_wave)
 {
-  // One workgroup per (row, head): enough of them to fill the chip, or so little work that it does not matter.
-  return (p.d == 8 || p.d == 16 || p.d == 32) && (p.b == 8 || p.b == 16) && p.L <= kMaxTiles * kTile &&
-         ((long)p.B * p.H >= 64 || p.L <= 256);
+  const int NT = (p.L + kTile - 1) / kTile;
+  SmallPlan s{false, false, 4, 1, 4 * words_per_wave * sizeof(float)};
+  // enough workgroups for about two rounds of the chip's wavefronts (256 CUs x 20), at most one tile per wavefront
+  const int want = (2 * 256 * 20 + units * s.waves - 1) / (units * s.waves);
+  s.parts = std::max(1, std::min((NT + s.waves - 1) / s.waves, want));
+  return s;
+}
+SmallPlan fwd_plan(const KParams &p, bool perpos, int hpg)
+{
+  const size_t rows = (size_t)(p.L + kTile - 1) / kTile * kTile;
+  const int units = p.B * p.H / hpg;
+  SmallPlan s{true, false, res_waves(units), 1, 0};
+  s.lds = (2 * rows * (p.d + 4) + (size_t)s.waves * lt_words(p, perpos)) * sizeof(float);
+  if (p.nq == p.NB && s.lds <= kSmallLds) return s;
+  s = stream_plan(p, p.B * p.H, lt_words(p, perpos));
+  if (p.nq != p.NB) s = SmallPlan{false, false, 1, 1, lt_words(p, perpos) * sizeof(float)};  // serving mode: one query tile per head
+  return s;
+}
+SmallPlan bwd_plan(const KParams &p, bool perpos, int hpg)
+{
+  const int units = p.B * p.H / hpg;
+  // with many heads four small workgroups per CU beat two that hold everything (B=2048 H=8 L=200 d=16: 672 against 917 us)
+  for (int overlay = many_heads(units) ? 1 : 0; overlay < 2; ++overlay) {
+    SmallPlan s{true, overlay != 0, res_waves(units), 1, 0};
+    s.lds = (size_t)ResLayout(p, perpos, hpg, overlay, s.waves).total * sizeof(float);
+    if (s.lds <= kSmallLds) return s;
+  }
+  return stream_plan(p, p.B * p.H, lt_words(p, perpos));
 }
 
-constexpr int kResWaves = 8;
 // The per-position form has limits that its callers know (144 KB of fp32 rows of 20 or 36 floats, see the header).
-constexpr size_t kPosLdsLimit = 144 * 1024;
+constexpr size_t kPosLimit = 144 * 1024;
 size_t pos_fwd_limit_bytes(const KParams &p) { return 2 * (size_t)(p.NB * p.b + 16) * ((p.d < 16 ? 16 : p.d) + 4) * sizeof(float); }
 size_t pos_bwd_limit_bytes(const KParams &p)
 {
@@ -1034,7 +1496,7 @@ void want_lds(Kern kernel, size_t lds)
 }
 
 template <typename F>
-void with_res_dims(const KParams &p, F &&f)
+void with_small_dims(const KParams &p, F &&f)
 {
   auto with_bk = [&](auto dim) {
     if (p.b == 8) f(dim, std::integral_constant<int, 8>{});
@@ -1047,87 +1509,113 @@ void with_res_dims(const KParams &p, F &&f)
 
 }  // namespace
 
-bool fwd_res_supported(const KParams &p, int dtype)
-{
-  (void)dtype;
-  return res_shape(p) && res_fwd_lds_bytes(p, false) <= kResLdsMax - 256;
-}
+bool small_supported(const KParams &p) { return small_shape(p); }
 
-// the per-position form exists in this kernel family only: what the shape has to satisfy, whatever the batch
-bool fwd_positions_supported(const KParams &p, int dtype)
+bool fwd_positions_supported(const KParams &p)
 {
-  (void)dtype;
-  return (p.d == 8 || p.d == 16 || p.d == 32) && (p.b == 8 || p.b == 16) && !p.bidir && p.NB <= 64 && p.nq == p.NB &&
-         pos_fwd_limit_bytes(p) <= kPosLdsLimit;
+  return small_shape(p) && !p.bidir && p.NB <= 64 && p.nq == p.NB && pos_fwd_limit_bytes(p) <= kPosLimit;
 }
+bool bwd_positions_supported(const KParams &p) { return fwd_positions_supported(p) && pos_bwd_limit_bytes(p) <= kPosLimit; }
 
-bool bwd_res_supported(const KParams &p, int dtype)
+size_t small_ws_bytes(const KParams &p, SmallWs *w, char *base)
 {
-  (void)dtype;
-  return res_shape(p) && res_bwd_lds_bytes(p, false, 1, kResWaves) <= kResLdsMax - 256;
+  if (!small_shape(p)) return 0;
+  const size_t BH = (size_t)p.B * p.H, NT = (size_t)(p.L + kTile - 1) / kTile;
+  const size_t NWt = (NT + 31) / 32, NWb = ((size_t)p.NB + 31) / 32;
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    char *at = base + off;
+    off += (bytes + 255) & ~(size_t)255;
+    return at;
+  };
+  w->rowc = reinterpret_cast<float *>(take(BH * NT * 6 * kTile * sizeof(float)));
+  w->tile_words = reinterpret_cast<unsigned *>(take(BH * NT * NWt * sizeof(unsigned)));
+  const size_t per_tile = std::max(p.b < kTile ? 2 * NWb : (size_t)1, bwd_positions_supported(p) ? (size_t)2 * kTile : (size_t)0);
+  w->sel_bits = reinterpret_cast<unsigned *>(take(BH * NT * per_tile * sizeof(unsigned)));
+  w->partial = reinterpret_cast<float *>(take(BH * NT * (2 * p.d + 1) * sizeof(float)));  // (at most one row per tile)
+  return off;
 }
-
-bool bwd_positions_supported(const KParams &p, int dtype)
+int small_partial_rows(const KParams &p, int kv_groups)
 {
-  return fwd_positions_supported(p, dtype) && pos_bwd_limit_bytes(p) <= kPosLdsLimit;
+  return bwd_plan(p, kv_groups > 0, kv_groups > 0 ? p.H / kv_groups : 1).parts;
 }
 
 template <typename T>
-static void launch_fwd_res_t(const KParams &p, const FwdArgs &a, hipStream_t st)
+static void launch_fwd_small_t(const KParams &p, const FwdArgs &a, hipStream_t st)
 {
   const bool perpos = a.kv_groups > 0;
-  const size_t lds = res_fwd_lds_bytes(p, perpos);
   const int hpg = perpos ? p.H / a.kv_groups : 1;
-  with_res_dims(p, [&](auto dim, auto bk) {
+  const SmallPlan pl = fwd_plan(p, perpos, hpg);
+  const int grid = p.B * p.H / (pl.res ? hpg : 1) * pl.parts;
+  with_small_dims(p, [&](auto dim, auto bk) {
     constexpr int D = decltype(dim)::value, BK = decltype(bk)::value;
     auto go = [&](auto kernel) {
-      want_lds(kernel, lds);
-      hipLaunchKernelGGL(kernel, dim3((unsigned)(p.B * p.H / hpg)), dim3(64 * kResWaves), lds, st, (const T *)a.Q,
-                         (const T *)a.K, (const T *)a.V, a.valid_len, a.dense ? nullptr : a.sel, a.gate_w, a.gate_b, (T *)a.O,
-                         (float *)a.o_lt, (float *)a.o_st, a.lse_lt, a.lse_st, hpg, p);
+      want_lds(kernel, pl.lds);
+      hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * pl.waves), pl.lds, st, (const T *)a.Q, (const T *)a.K,
+                         (const T *)a.V, a.valid_len, a.dense ? nullptr : a.sel, a.gate_w, a.gate_b, (T *)a.O,
+                         (float *)a.o_lt, (float *)a.o_st, a.lse_lt, a.lse_st, hpg, pl.parts, p);
     };
-    if (perpos) go(fwd_res_kernel<T, D, BK, true>);
-    else go(fwd_res_kernel<T, D, BK, false>);
+    if (perpos) pl.res ? go(fwd_small_kernel<T, D, BK, true, true>) : go(fwd_small_kernel<T, D, BK, true, false>);
+    else pl.res ? go(fwd_small_kernel<T, D, BK, false, true>) : go(fwd_small_kernel<T, D, BK, false, false>);
   });
 }
 
-void launch_fwd_res(const KParams &p, int dtype, const FwdArgs &a, hipStream_t st)
+void launch_fwd_small(const KParams &p, int dtype, const FwdArgs &a, hipStream_t st)
 {
-  if (dtype == 0) launch_fwd_res_t<float>(p, a, st);
-  else launch_fwd_res_t<bf16_t>(p, a, st);
+  if (dtype == 0) launch_fwd_small_t<float>(p, a, st);
+  else launch_fwd_small_t<bf16_t>(p, a, st);
 }
 
 template <typename T>
-static void launch_bwd_res_t(const KParams &p, const BwdArgs &a, const BwdWorkspace &w, unsigned stages, int kv_groups,
-                             hipStream_t st)
+static void launch_bwd_small_t(const KParams &p, const BwdArgs &a, const SmallWs &w, unsigned stages, int kv_groups, hipStream_t st)
 {
   const bool perpos = kv_groups > 0;
   const int hpg = perpos ? p.H / kv_groups : 1;
-  int hc = hpg;  // as many heads of the group at a time as fit
-  while (hc > 1 && res_bwd_lds_bytes(p, perpos, hc, kResWaves) > kResLdsMax - 256) --hc;
-  const size_t lds = res_bwd_lds_bytes(p, perpos, hc, kResWaves);
-  with_res_dims(p, [&](auto dim, auto bk) {
+  if ((stages & (kBwdStageGate | kBwdStageDQ | kBwdStageDKV)) == 0) return;
+  const SmallPlan pl = bwd_plan(p, perpos, hpg);
+  with_small_dims(p, [&](auto dim, auto bk) {
     constexpr int D = decltype(dim)::value, BK = decltype(bk)::value;
-    auto go = [&](auto kernel) {
-      want_lds(kernel, lds);
-      hipLaunchKernelGGL(kernel, dim3((unsigned)(p.B * p.H / hpg)), dim3(64 * kResWaves), lds, st, (const T *)a.Q,
-                         (const T *)a.K, (const T *)a.V, a.valid_len, a.sel, a.gate_w, a.gate_b, (const float *)a.o_lt,
-                         (const float *)a.o_st, a.lse_lt, a.lse_st, (const T *)a.dO, (T *)a.dQ, (T *)a.dK, (T *)a.dV,
-                         w.partial, hpg, hc, stages, p);
-    };
-    if (perpos) go(bwd_res_kernel<T, D, BK, true>);
-    else go(bwd_res_kernel<T, D, BK, false>);
+    if (pl.res) {
+      auto go = [&](auto kernel) {
+        want_lds(kernel, pl.lds);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(p.B * p.H / hpg)), dim3(64 * pl.waves), pl.lds, st, (const T *)a.Q,
+                           (const T *)a.K, (const T *)a.V, a.valid_len, a.sel, a.gate_w, a.gate_b, (const float *)a.o_lt,
+                           (const float *)a.o_st, a.lse_lt, a.lse_st, (const T *)a.dO, (T *)a.dQ, (T *)a.dK, (T *)a.dV, w.partial,
+                           hpg, (int)pl.overlay, stages, p);
+      };
+      if (perpos) go(bwd_res_kernel<T, D, BK, true>);
+      else go(bwd_res_kernel<T, D, BK, false>);
+      return;
+    }
+    if (stages & (kBwdStageGate | kBwdStageDQ)) {
+      auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(p.B * p.H * pl.parts)), dim3(64 * pl.waves), pl.lds, st, (const T *)a.Q,
+                           (const T *)a.K, (const T *)a.V, a.valid_len, a.sel, a.gate_w, a.gate_b, (const float *)a.o_lt,
+                           (const float *)a.o_st, a.lse_lt, a.lse_st, (const T *)a.dO, (T *)a.dQ, w, hpg, pl.parts, stages, p);
+      };
+      if (perpos) go(bwd_dq_small_kernel<T, D, BK, true>);
+      else go(bwd_dq_small_kernel<T, D, BK, false>);
+      if (launch_failed()) return;
+    }
+    if (stages & kBwdStageDKV) {
+      const SmallPlan pk = stream_plan(p, p.B * p.H / hpg, 0);
+      auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(p.B * p.H / hpg * pk.parts)), dim3(64 * pk.waves), 0, st, (const T *)a.Q,
+                           (const T *)a.K, (const T *)a.V, a.valid_len, a.gate_w, (const T *)a.dO, w, (T *)a.dK, (T *)a.dV, hpg,
+                           pk.parts, p);
+      };
+      if (perpos) go(bwd_dkv_small_kernel<T, D, BK, true>);
+      else go(bwd_dkv_small_kernel<T, D, BK, false>);
+    }
   });
 }
 
-// gate pass (partial gate gradients, one row of 2d+1 per (row, head), in w.partial), dK/dV and dQ as asked for;
-// kv_groups > 0: a.sel holds one row per position and group
-void launch_bwd_res(const KParams &p, int dtype, const BwdArgs &a, const BwdWorkspace &w, unsigned stages, int kv_groups,
-                    hipStream_t st)
+// gate pass and dQ, then dK/dV; kv_groups > 0: a.sel holds one row per position and group
+void launch_bwd_small(const KParams &p, int dtype, const BwdArgs &a, const SmallWs &w, unsigned stages, int kv_groups,
+                      hipStream_t st)
 {
-  if ((stages & (kBwdStageGate | kBwdStageDQ | kBwdStageDKV)) == 0) return;
-  if (dtype == 0) launch_bwd_res_t<float>(p, a, w, stages, kv_groups, st);
-  else launch_bwd_res_t<bf16_t>(p, a, w, stages, kv_groups, st);
+  if (dtype == 0) launch_bwd_small_t<float>(p, a, w, stages, kv_groups, st);
+  else launch_bwd_small_t<bf16_t>(p, a, w, stages, kv_groups, st);
 }
 
 }  // namespace blossom

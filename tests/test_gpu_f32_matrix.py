@@ -135,3 +135,24 @@ def test_seeded_random_shapes_in_the_resident_range():
         x.valid_len[:] = [L, int(rng.integers(0, L + 1)), int(rng.integers(0, L + 1)), min(L, 1 + int(rng.integers(0, b)))]
         same = w.topk >= w.NB and (w.window >= L or sblk >= L)
         run_case(w, x=x, backward=True, check_dense=(case % 4 == 0 and not bidir), gate_scale=0.4, branches_coincide=same)
+
+
+@pytest.mark.parametrize("dtype,d,b,B_,H,L,sblk,bidir,amp", [
+    ("fp32", 8, 8, 260, 8, 17, 1, False, 1),     # 2080 heads: four wavefronts and shared buffers per workgroup
+    ("bf16", 32, 16, 257, 8, 31, 2, True, 1),    # the same in bf16, bidirectional, ragged in the second tile
+    ("fp32", 32, 16, 3, 2, 225, 0, False, 1),    # past the resident backward at d = 32: its tiles are streamed
+    ("fp32", 16, 8, 3, 2, 513, 1, False, 1),     # one item past 32 tiles: second word of a tile list
+    ("fp32", 8, 16, 2, 2, 1043, 5, True, 1),     # past 64 tiles, bidirectional
+    ("bf16", 16, 16, 2, 2, 1024, 16, False, 1),
+    ("fp32", 16, 16, 5, 2, 150, 1, False, 30),   # logits beyond 60: the walk with row maxima, resident ...
+    ("fp32", 32, 8, 2, 2, 530, 0, False, 30),    # ... and streamed
+])
+def test_many_heads_streamed_tiles_and_large_logits(dtype, d, b, B_, H, L, sblk, bidir, amp):
+    w = with_shape(WORKLOADS["cfg2"], name=f"small-{dtype}-d{d}-b{b}-L{L}-x{amp}", B=B_, H=H, L=L, d=d, block=b,
+                   topk=3, window=b + 3, dtype=dtype, qkv_scaled=(dtype == "bf16"), len_lo=1, len_hi=L,
+                   stis_block=sblk, bidir=bidir, seed=1700 + d + b + L)
+    x = make_inputs(w, want_dO=True)
+    x.valid_len[:2] = [L, max(1, L - b - 3)]
+    x.Q *= np.float32(amp)
+    pairs = None if B_ * H < 64 else [0, 1, H, B_ * H // 2 + 1, B_ * H - 1]
+    run_case(with_shape(w, backward=False), x=x, pairs=pairs, backward=True, gate_scale=0.4)
