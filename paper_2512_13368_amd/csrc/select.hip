@@ -6,66 +6,114 @@
 // This file is compiled with -ffp-contract=off; the only fused operations are the explicit
 // __fmaf_rn calls.  Plain ALUs only: the work is O(NB^2 d) per head and HBM-bound on the
 // pooling pass.
+#include <algorithm>
+
 #include "common.h"
 #include "launch.h"
 
 namespace blossom {
 
+// 16 bytes as floats.
+__device__ __forceinline__ void unpack(const uint4 &v, float (&o)[4])
+{
+  o[0] = __uint_as_float(v.x); o[1] = __uint_as_float(v.y); o[2] = __uint_as_float(v.z); o[3] = __uint_as_float(v.w);
+}
+__device__ __forceinline__ void unpack(const uint4 &v, float (&o)[8])
+{
+  const unsigned w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    o[2 * i] = __uint_as_float(w[i] << 16);
+    o[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
+  }
+}
+
+__device__ __forceinline__ void unpack(const uint2 &v, float (&o)[4])
+{
+  o[0] = __uint_as_float(v.x << 16); o[1] = __uint_as_float(v.x & 0xFFFF0000u);
+  o[2] = __uint_as_float(v.y << 16); o[3] = __uint_as_float(v.y & 0xFFFF0000u);
+}
+
+// Sum of a block's valid positions, in ascending order, for 16 bytes of channels of one tensor: kPoolBatch rows are in
+// flight at a time (a rolled loop, which the compiler unrolled without hoisting a load, waited for each row in turn:
+// the one-workgroup selection of B=128 H=4 L=1024 d=64 bf16 took 32 us, 24 now).  Rows past the end are read as the last one and add +0, which
+// changes nothing: a sum that starts from +0 is never -0.
+template <typename T, int D, int kPoolBatch, int EPT>
+__device__ __forceinline__ void pool_batches(const T *__restrict__ src, int lo, int hi, float (&a)[EPT])
+{
+  for (int t = lo; t < hi; t += kPoolBatch) {
+    using V = std::conditional_t<EPT * sizeof(T) == 16, uint4, uint2>;
+    V v[kPoolBatch];
+#pragma unroll
+    for (int i = 0; i < kPoolBatch; ++i) v[i] = *reinterpret_cast<const V *>(src + (size_t)min(t + i, hi - 1) * D);
+#pragma unroll
+    for (int i = 0; i < kPoolBatch; ++i) {
+      float x[EPT];
+      unpack(v[i], x);
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) a[e] = a[e] + (t + i < hi ? x[e] : 0.0f);
+    }
+  }
+}
+
+template <typename T, int D, int EPT>
+__device__ __forceinline__ void pool_block(const T *__restrict__ src, int lo, int hi, float (&a)[EPT])
+{
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) a[e] = 0.0f;
+  if (hi - lo > 8) pool_batches<T, D, 16>(src, lo, hi, a);
+  else pool_batches<T, D, 8>(src, lo, hi, a);
+}
+
+// Where the mean of channel c of key block J of head bh goes: rows of d channels, or (more than kRowBlocks blocks) transposed.
+constexpr int kRowBlocks = 128;
+template <int D>
+__device__ __forceinline__ size_t kmean_at(int bh, int J, int c, int NB)
+{
+  return NB <= kRowBlocks ? ((size_t)bh * NB + J) * D + c : ((size_t)bh * D + c) * NB + J;
+}
+
 // ---- pooling ------------------------------------------------------------------------------
-// One lane owns 4 channels of one block of one tensor and walks the block's valid positions
-// in ascending order.  qsum  [B,H,NB,d]   (unnormalised sums of Q)
-//                     kmeanT[B,H,d,NB]   (means of K, transposed so that the scoring pass
-//                                         reads consecutive blocks with consecutive lanes)
+// One lane owns 16 bytes of channels of one block of one tensor.  qsum [B,H,NB,d] (unnormalised sums of Q), kmean: above.
 // KCMP: K holds compressed keys [B,H,NB,d] supplied by the caller (Eq. 9 with the caller's phi);
-// they are copied as they are into the transposed fp32 layout instead of being pooled.
+// they are copied as they are instead of being pooled.
 template <typename T, int D, bool KCMP>
 __global__ __launch_bounds__(256) void pool_kernel(const T *__restrict__ Q, const T *__restrict__ K,
                                                    const int *__restrict__ valid_len,
-                                                   float *__restrict__ qsum, float *__restrict__ kmeanT,
+                                                   float *__restrict__ qsum, float *__restrict__ kmean,
                                                    KParams p)
 {
-  constexpr int LPT = D / 4;  // lanes per (tensor, row-head, block) task
+  constexpr int EPT = 4;
+  constexpr int LPT = D / EPT;  // lanes per (tensor, row-head, block) task
   const long n_bhj = (long)p.B * p.H * p.NB;
   const long task = (long)blockIdx.x * (256 / LPT) + threadIdx.x / LPT;
   if (task >= 2 * n_bhj) return;
-  const int c4 = (threadIdx.x % LPT) * 4;
+  const int c0 = (threadIdx.x % LPT) * EPT;
   const int which = task >= n_bhj;
   const long rem = which ? task - n_bhj : task;
   const int bh = (int)(rem / p.NB);
   const int J = (int)(rem % p.NB);
   if (!which && J < p.NB - p.nq) return;  // serving mode: only the last query block is pooled
+  float a[EPT];
   if (KCMP && which) {
-    float x[4];
-    load4(K + ((size_t)bh * p.NB + J) * D + c4, x);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) kmeanT[((size_t)bh * D + c4 + e) * p.NB + J] = x[e];
+    for (int e = 0; e < EPT; e += 4) load4(K + ((size_t)bh * p.NB + J) * D + c0 + e, reinterpret_cast<float(&)[4]>(a[e]));
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) kmean[kmean_at<D>(bh, J, c0 + e, p.NB)] = a[e];
     return;
   }
-  const int n = clamp_len(valid_len[bh / p.H], p.L);
-  const int p0 = p.L - n;
-  const int lo = max(J * p.b, p0);
-  const int hi = min((J + 1) * p.b, p.L);
-  const T *src = (which ? K : Q) + (size_t)bh * p.L * D + c4;
-  float a[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 8
-  for (int t = lo; t < hi; ++t) {
-    float x[4];
-    load4(src + (size_t)t * D, x);
-    a[0] = a[0] + x[0];
-    a[1] = a[1] + x[1];
-    a[2] = a[2] + x[2];
-    a[3] = a[3] + x[3];
-  }
+  const int p0 = p.L - clamp_len(valid_len[bh / p.H], p.L);
+  const int lo = max(J * p.b, p0), hi = min((J + 1) * p.b, p.L);
+  pool_block<T, D, EPT>((which ? K : Q) + (size_t)bh * p.L * D + c0, lo, hi, a);
   if (!which) {
-    store4(qsum + ((size_t)bh * p.NB + J) * D + c4, a);
-  } else {
-    const int cnt = hi - lo;
-    const float fc = (float)cnt;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float m = cnt > 0 ? __fdiv_rn(a[e], fc) : 0.0f;
-      kmeanT[((size_t)bh * D + c4 + e) * p.NB + J] = m;
-    }
+    for (int e = 0; e < EPT; e += 4)
+      store4(qsum + ((size_t)bh * p.NB + J) * D + c0 + e, reinterpret_cast<float(&)[4]>(a[e]));
+  } else {
+    const float fc = (float)(hi - lo);
+#pragma unroll
+    for (int e = 0; e < EPT; ++e)
+      kmean[kmean_at<D>(bh, J, c0 + e, p.NB)] = hi > lo ? __fdiv_rn(a[e], fc) : 0.0f;
   }
 }
 
@@ -84,7 +132,7 @@ constexpr int kRopeRows = 64;
 template <typename T, int D>
 __global__ __launch_bounds__(256) void rope_pool_kernel(const T *__restrict__ Q, const T *__restrict__ K,
                                                         const int *__restrict__ valid_len,
-                                                        float *__restrict__ qsum, float *__restrict__ kmeanT,
+                                                        float *__restrict__ qsum, float *__restrict__ kmean,
                                                         T *__restrict__ Q_rot, T *__restrict__ K_rot, KParams p)
 {
   constexpr int EPT = 16 / (int)sizeof(T);  // elements of a 16-byte piece: 8 bf16 or 4 fp32
@@ -146,126 +194,353 @@ __global__ __launch_bounds__(256) void rope_pool_kernel(const T *__restrict__ Q,
       qsum[((size_t)bh * p.NB + J) * D + c] = a;
     } else {
       const int cnt = hi - lo;
-      kmeanT[((size_t)bh * D + c) * p.NB + J] = cnt > 0 ? __fdiv_rn(a, (float)cnt) : 0.0f;
+      kmean[kmean_at<D>(bh, J, c, p.NB)] = cnt > 0 ? __fdiv_rn(a, (float)cnt) : 0.0f;
     }
   }
 }
 
 // ---- scoring + top-k ----------------------------------------------------------------------
-// One wavefront per (row, head, query block I).  Lane-strided candidates J_first <= J < I.
-// Each score becomes one 64-bit key in LDS: an order-preserving integer image of the fp32 score
-// (with -0 folded onto +0, so that equal scores give equal images) above NB-1-J, so that
-// "beats" under (score descending, index ascending) is a single unsigned comparison of unique
-// keys.  A candidate is selected iff fewer than `take` candidates beat it; ballots and prefix
-// popcounts emit the list in ascending order.
-__device__ __forceinline__ unsigned long long rank_key(float score, int J, int NB)
+// Each score becomes an order-preserving integer image of the fp32 value (with -0 folded onto +0, so that equal
+// scores give equal images); "beats" under (score descending, index ascending) compares the images, then the indexes.
+// In the bidirectional form the query's own block is a candidate with the largest possible image: it is always taken
+// and comes out at its place in the ascending list.  In the causal form it closes the list.
+__device__ __forceinline__ unsigned score_image(float score)
 {
   unsigned u = __float_as_uint(score);
-  if (u == 0x80000000u) u = 0u;                       // -0 ties with +0
-  u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);     // monotone in the score
-  return ((unsigned long long)u << 32) | (unsigned)(NB - 1 - J);
+  if (u == 0x80000000u) u = 0u;                    // -0 ties with +0
+  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);  // monotone in the score
 }
 
+// The candidates of query block I of a row whose valid positions start at p0: [J_first, J_end), and how many are taken.
+struct Candidates {
+  int J_first, J_end, take;
+  bool any;  // the block holds a valid query
+};
+__device__ __forceinline__ Candidates candidates(const KParams &p, int p0, int I)
+{
+  Candidates c;
+  c.any = min((I + 1) * p.b, p.L) > p0;
+  c.J_first = p0 / p.b;
+  c.J_end = p.bidir ? p.NB : I;
+  const int n_cand = p.bidir ? p.NB - c.J_first - 1 : I - c.J_first;
+  c.take = min(p.k - 1, n_cand) + (p.bidir ? 1 : 0);
+  if (!c.any) c.take = 0;
+  return c;
+}
+
+// One fused-multiply-add chain over the channels, in ascending order; rows of d floats in LDS.
 template <int D>
-__global__ __launch_bounds__(64) void score_topk_kernel(const float *__restrict__ qsum,
-                                                        const float *__restrict__ kmeanT,
-                                                        const int *__restrict__ valid_len,
-                                                        int *__restrict__ sel, KParams p)
+__device__ __forceinline__ float score_dot(const float *q, const float *k)
+{
+  float acc = 0.0f;
+#pragma unroll
+  for (int c = 0; c < D; c += 4) {
+    const float4 a = *reinterpret_cast<const float4 *>(q + c), b = *reinterpret_cast<const float4 *>(k + c);
+    acc = __fmaf_rn(a.x, b.x, acc);
+    acc = __fmaf_rn(a.y, b.y, acc);
+    acc = __fmaf_rn(a.z, b.z, acc);
+    acc = __fmaf_rn(a.w, b.w, acc);
+  }
+  return acc;
+}
+
+// Up to 32 blocks: one thread per (query block, candidate) pair.  A candidate is selected iff fewer than `take` beat it;
+// a query block's choices are the bits of one word, written out with consecutive threads on consecutive entries.
+// scratch: NB*NB images, then NB words.  Every thread of the workgroup calls it, after a barrier.
+constexpr int kPairBlocks = 32;
+template <int D>
+__device__ void pick_by_pairs(const float *q_s, const float *k_s, unsigned *scratch, int *__restrict__ out, int p0,
+                              const KParams &p)
+{
+  const int tid = threadIdx.x, nt = blockDim.x, NB = p.NB, I0 = NB - p.nq;
+  unsigned *img = scratch, *chosen = scratch + NB * NB;
+  // causal: rows I and NB-1-I together hold NB-1 candidates
+  const int pairs = p.bidir ? NB * NB : (NB + 1) / 2 * (NB - 1);
+  auto pair = [&](int e, int &I, int &J) {
+    const int w = p.bidir ? NB : NB - 1, r = e / w, c = e - r * w;
+    I = r;
+    J = c;
+    if (!p.bidir) {
+      const int big = NB - 1 - r;
+      I = c < big ? big : r;
+      J = c < big ? c : c - big;
+      if (c >= big && big == r) return false;  // the middle row of an odd count stands alone
+    }
+    return I >= I0 && J >= p0 / p.b;
+  };
+  for (int I = tid; I < NB; I += nt) {
+    const Candidates c = candidates(p, p0, I);
+    chosen[I] = c.any && !p.bidir ? 1u << I : 0u;
+  }
+  for (int e = tid; e < pairs; e += nt) {
+    int I, J;
+    if (!pair(e, I, J)) continue;
+    img[I * NB + J] = p.bidir && I == J ? ~0u : score_image(score_dot<D>(q_s + (I - I0) * (D + 4), k_s + J * (D + 4)));
+  }
+  __syncthreads();
+  for (int e = tid; e < pairs; e += nt) {
+    int I, J;
+    if (!pair(e, I, J)) continue;
+    const Candidates c = candidates(p, p0, I);
+    const unsigned mine = img[I * NB + J];
+    int rank = 0;
+    for (int Jo = c.J_first; Jo < c.J_end; ++Jo) {
+      const unsigned other = img[I * NB + Jo];
+      rank += other > mine || (other == mine && Jo < J) ? 1 : 0;
+    }
+    if (rank < c.take) atomicOr(&chosen[I], 1u << J);
+  }
+  __syncthreads();
+  for (int e = tid; e < p.nq * p.k; e += nt) {
+    const int r = e / p.k;
+    unsigned m = chosen[I0 + r];
+    for (int slot = e - r * p.k; slot > 0 && m; --slot) m &= m - 1;
+    out[(size_t)I0 * p.k + e] = m ? __builtin_ctz(m) : -1;
+  }
+}
+
+// Up to 128 blocks: a wavefront takes kRowsPerWave query blocks at a time, one or two candidates per lane.  The query rows
+// lie across the lanes too and are read channel by channel into scalar registers.  The take-th largest image of a row is
+// found bit by bit from the top (a compare and a population count per bit and slot: the scalar unit does most of it, and
+// a vector instruction costs four cycles), the rows' searches independent of each other and given up as soon as exactly
+// `take` images are left above the line.  (Ranks by counting the larger images, as for the pairs: 17 against 15 us at
+// B=32 H=8 L=1997 d=64, 63 blocks.)
+// q(r): the row r's channel `lane` (any value from lane d on).
+constexpr int kRowsPerWave = 4;
+__device__ __forceinline__ float lane_value(float v, int lane)
+{
+  return __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(v), lane));
+}
+template <int D, int SLOTS, int R, typename QRow>
+__device__ __forceinline__ void pick_rows(QRow &&q, const float *k_s, int *__restrict__ out, int I0, int I1, int p0,
+                                          const KParams &p)
+{
+  const int lane = threadIdx.x & 63;
+  const int J_first = p0 / p.b;
+  int J[SLOTS];
+  const float *k[SLOTS];
+#pragma unroll
+  for (int s = 0; s < SLOTS; ++s) {
+    J[s] = J_first + lane + 64 * s;
+    k[s] = k_s + min(J[s], p.NB - 1) * (D + 4);
+  }
+  float acc[R][SLOTS], qv[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    qv[r] = q(min(r, I1 - 1 - I0));
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) acc[r][s] = 0.0f;
+  }
+#pragma unroll 4
+  for (int c0 = 0; c0 < D; c0 += 4) {
+    float kv[SLOTS][4];
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) load4(k[s] + c0, kv[s]);
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const float qc = lane_value(qv[r], c0 + c);
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) acc[r][s] = __fmaf_rn(qc, kv[s][c], acc[r][s]);
+      }
+  }
+  unsigned u[R][SLOTS], line[R];  // images: 0, below every other, where there is no candidate
+  int take[R], above[R];          // above: images at or above the line
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const Candidates c = candidates(p, p0, I0 + r);
+    take[r] = c.take;
+    above[r] = -1;
+    line[r] = 0u;
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s)
+      u[r][s] = J[s] >= c.J_end ? 0u : p.bidir && J[s] == I0 + r ? ~0u : score_image(acc[r][s]);
+  }
+  for (int bit = 31; bit >= 0; --bit) {
+    bool done = true;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const unsigned test = line[r] | (1u << bit);
+      int cnt = 0;
+#pragma unroll
+      for (int s = 0; s < SLOTS; ++s) cnt += __popcll(__ballot(u[r][s] >= test));
+      line[r] = cnt >= take[r] ? test : line[r];
+      above[r] = cnt >= take[r] ? cnt : above[r];
+      done = done && above[r] == take[r];
+    }
+    if (done) break;
+  }
+  const unsigned long long below = (1ull << lane) - 1ull;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int I = I0 + r;
+    if (I >= I1) break;
+    unsigned long long ch[SLOTS], eq[SLOTS];
+    int left = take[r];
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {
+      ch[s] = take[r] > 0 ? __ballot(u[r][s] > line[r]) : 0ull;
+      eq[s] = __ballot(u[r][s] == line[r]);
+      left -= __popcll(ch[s]);
+    }
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {  // of the images on the line, the first `left` in ascending block order
+      ch[s] |= __ballot(((eq[s] >> lane) & 1ull) && (int)__popcll(eq[s] & below) < left);
+      left -= __popcll(eq[s]);
+    }
+    int *row = out + (size_t)I * p.k;
+    int base = 0;
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {
+      if ((ch[s] >> lane) & 1ull) row[base + __popcll(ch[s] & below)] = J[s];
+      base += __popcll(ch[s]);
+    }
+    if (!p.bidir && candidates(p, p0, I).any) {
+      if (lane == 0) row[base] = I;
+      ++base;
+    }
+    for (int e = base + lane; e < p.k; e += 64) row[e] = -1;
+  }
+}
+template <int D>
+__device__ __forceinline__ void pick_by_rows(const float *q_s, const float *k_s, int *__restrict__ out, int I0, int I1, int p0,
+                                             const KParams &p)
+{
+  const int waves = blockDim.x >> 6, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  auto go = [&](auto rows) {
+    constexpr int R = decltype(rows)::value;
+    for (int I = I0 + R * wave; I < I1; I += R * waves) {
+      const int last = min(I + R, I1);
+      auto q = [&](int r) { return q_s[(I - I0 + r) * (D + 4) + (threadIdx.x & (D - 1))]; };
+      if ((p.bidir ? p.NB : last - 1) - p0 / p.b > 64) pick_rows<D, 2, R>(q, k_s, out, I, last, p0, p);
+      else pick_rows<D, 1, R>(q, k_s, out, I, last, p0, p);
+    }
+  };
+  if (I1 - I0 <= waves) go(std::integral_constant<int, 1>{});  // (serving mode: one row)
+  else go(std::integral_constant<int, kRowsPerWave>{});
+}
+
+// LDS of a workgroup that scores `rows` query blocks of a head: padded rows of d + 4 floats, and the pairs' images.
+static size_t pick_lds(const KParams &p, int rows)
+{
+  const size_t pairs = p.NB <= kPairBlocks ? (size_t)p.NB * p.NB + p.NB : 0;
+  return ((size_t)(rows + p.NB) * (p.d + 4) + pairs) * sizeof(float);
+}
+
+// Pooling, scoring and top-k of one head in one workgroup: the pooled rows stay in LDS.  As two kernels the
+// pooled rows went through memory, and the second, a wavefront per query block, was all latency: at
+// B=2048 H=8 L=200 d=16 fp32 it took 55 us after 58 us of pooling, at B=128 H=4 L=1024 d=64 bf16 15 after 25.
+template <typename T, int D>
+__global__ __launch_bounds__(1024) void select_head_kernel(const T *__restrict__ Q, const T *__restrict__ K,
+                                                           const int *__restrict__ valid_len, int *__restrict__ sel, KParams p)
+{
+  constexpr int EPT = 16 / (int)sizeof(T);
+  constexpr int LPT = D / EPT;
+  extern __shared__ __attribute__((aligned(16))) float sel_lds[];
+  float *q_s = sel_lds, *k_s = q_s + p.nq * (D + 4);
+  const int bh = blockIdx.x;
+  const int p0 = p.L - clamp_len(valid_len[bh / p.H], p.L);
+  for (int e = threadIdx.x; e < (p.nq + p.NB) * LPT; e += blockDim.x) {
+    const int row = e / LPT, c0 = (e % LPT) * EPT;
+    const bool key = row >= p.nq;
+    const int J = key ? row - p.nq : p.NB - p.nq + row;
+    const int lo = max(J * p.b, p0), hi = min((J + 1) * p.b, p.L);
+    float a[EPT];
+    pool_block<T, D, EPT>((key ? K : Q) + (size_t)bh * p.L * D + c0, lo, hi, a);
+    if (key) {
+      const float fc = (float)(hi - lo);
+#pragma unroll
+      for (int i = 0; i < EPT; ++i) a[i] = hi > lo ? __fdiv_rn(a[i], fc) : 0.0f;
+    }
+#pragma unroll
+    for (int i = 0; i < EPT; i += 4) store4(q_s + row * (D + 4) + c0 + i, reinterpret_cast<float(&)[4]>(a[i]));
+  }
+  __syncthreads();
+  int *out = sel + (size_t)bh * p.NB * p.k;
+  if (p.NB <= kPairBlocks)
+    pick_by_pairs<D>(q_s, k_s, reinterpret_cast<unsigned *>(k_s + p.NB * (D + 4)), out, p0, p);
+  else
+    pick_by_rows<D>(q_s, k_s, out, p.NB - p.nq, p.NB, p0, p);
+}
+
+// Scoring and top-k of pooled rows, up to 128 blocks: a workgroup per kScoreRows query blocks of a head (or per head,
+// where the pairs do it), which holds the head's key means in LDS.
+constexpr int kScoreRows = 16;
+template <int D>
+__global__ __launch_bounds__(256) void score_topk_kernel(const float *__restrict__ qsum, const float *__restrict__ kmean,
+                                                         const int *__restrict__ valid_len, int *__restrict__ sel, int rows,
+                                                         KParams p)
+{
+  extern __shared__ __attribute__((aligned(16))) float sel_lds[];
+  const int chunks = (p.nq + rows - 1) / rows;
+  const int bh = blockIdx.x / chunks;
+  const int I0 = p.NB - p.nq + (int)(blockIdx.x % chunks) * rows, I1 = min(I0 + rows, p.NB);
+  float *q_s = sel_lds, *k_s = q_s + rows * (D + 4);
+  const int p0 = p.L - clamp_len(valid_len[bh / p.H], p.L);
+  auto stage = [&](float *to, const float *from, int lo, int hi) {  // eight loads in flight per thread
+    const int end = hi * (D / 4);
+    for (int e0 = lo * (D / 4) + (int)threadIdx.x; e0 < end; e0 += 8 * 256) {
+      float4 v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = reinterpret_cast<const float4 *>(from)[min(e0 + i * 256, end - 1)];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int e = e0 + i * 256;
+        if (e < end) *reinterpret_cast<float4 *>(to + e / (D / 4) * (D + 4) + e % (D / 4) * 4) = v[i];
+      }
+    }
+  };
+  stage(q_s, qsum + ((size_t)bh * p.NB + I0) * D, 0, I1 - I0);
+  stage(k_s, kmean + (size_t)bh * p.NB * D, p0 / p.b, p.bidir ? p.NB : I1);  // (I1 <= NB)
+  __syncthreads();
+  int *out = sel + (size_t)bh * p.NB * p.k;
+  if (p.NB <= kPairBlocks)
+    pick_by_pairs<D>(q_s, k_s, reinterpret_cast<unsigned *>(k_s + p.NB * (D + 4)), out, p0, p);
+  else
+    pick_by_rows<D>(q_s, k_s, out, I0, I1, p0, p);
+}
+
+// More than 128 blocks: one wavefront per (row, head, query block), lane-strided candidates, keys (the image above
+// NB-1-J: unique, one unsigned comparison) in LDS.  A candidate is selected iff fewer than `take` candidates beat it;
+// ballots and prefix popcounts emit the list in ascending order.
+template <int D>
+__global__ __launch_bounds__(64) void score_topk_many_kernel(const float *__restrict__ qsum,
+                                                             const float *__restrict__ kmeanT,
+                                                             const int *__restrict__ valid_len,
+                                                             int *__restrict__ sel, KParams p)
 {
   __shared__ float qs[D];
   extern __shared__ unsigned long long key_s[];  // NB keys (sized at launch: a static worst-case array would cap the occupancy)
   const int lane = threadIdx.x;
   const int I = p.NB - p.nq + (int)(blockIdx.x % p.nq);
   const int bh = blockIdx.x / p.nq;
-  const int n = clamp_len(valid_len[bh / p.H], p.L);
-  const int p0 = p.L - n;
+  const int p0 = p.L - clamp_len(valid_len[bh / p.H], p.L);
   int *out = sel + ((size_t)bh * p.NB + I) * p.k;
-  const int hi = min((I + 1) * p.b, p.L);
-  if (hi <= p0) {  // no valid query in this block
+  const Candidates cd = candidates(p, p0, I);
+  if (!cd.any) {
     for (int e = lane; e < p.k; e += 64) out[e] = -1;
     return;
   }
-  const int J_first = p0 / p.b;
-  // candidates: the earlier blocks that hold a valid key; in the bidirectional form the later ones too.
-  // There the query's own block sits among them with the largest possible key, so it is always taken
-  // and comes out at its place in the ascending list.
-  const int J_end = p.bidir ? p.NB : I;
-  const int n_cand = p.bidir ? p.NB - J_first - 1 : I - J_first;
-  const int take = min(p.k - 1, n_cand) + (p.bidir ? 1 : 0);
   for (int c = lane; c < D; c += 64) qs[c] = qsum[((size_t)bh * p.NB + I) * D + c];
   __syncthreads();
   const float *km = kmeanT + (size_t)bh * D * p.NB;
-  if (J_end - J_first <= 128 && J_end - J_first > 40) {  // (fewer candidates: the rank loop below is cheaper)
-    // Up to two candidates per lane, kept in registers.  Their scores are two independent chains over
-    // the channels; the k-th largest score image is found by a radix search from the top bit down
-    // (one ballot and one population count per bit and candidate slot: scalar work), and equal
-    // images are taken in ascending block order, which is the lower-index-wins rule.
-    const int Ja = J_first + lane, Jb = Ja + 64;
-    const bool has_a = Ja < J_end, has_b = Jb < J_end;
-    float acc_a = 0.0f, acc_b = 0.0f;
-    const float *ka = km + min(Ja, p.NB - 1), *kb = km + min(Jb, p.NB - 1);
-    if (J_end - J_first > 64) {
-#pragma unroll 16
-      for (int c = 0; c < D; ++c) {
-        acc_a = __fmaf_rn(qs[c], ka[(size_t)c * p.NB], acc_a);
-        acc_b = __fmaf_rn(qs[c], kb[(size_t)c * p.NB], acc_b);
-      }
-    } else {
-#pragma unroll 16
-      for (int c = 0; c < D; ++c) acc_a = __fmaf_rn(qs[c], ka[(size_t)c * p.NB], acc_a);
-    }
-    // 32-bit image of rank_key's upper word; the own block (bidirectional form) gets the largest value
-    auto image = [&](float sc, int J) -> unsigned {
-      if (J == I) return 0xFFFFFFFFu;
-      return (unsigned)(rank_key(sc, 0, 1) >> 32);
-    };
-    const unsigned ua = image(acc_a, Ja), ub = image(acc_b, Jb);
-    unsigned prefix = 0;
-    int remaining = take;
-    if (take > 0) {
-      for (int bit = 31; bit >= 0; --bit) {
-        const unsigned test = prefix | (1u << bit);
-        const unsigned himask = ~((1u << bit) - 1u);
-        const int cnt = __popcll(__ballot(has_a && (ua & himask) == test)) +
-                        __popcll(__ballot(has_b && (ub & himask) == test));
-        if (cnt >= remaining) prefix = test;  // the k-th largest has this bit set
-        else remaining -= cnt;                // everything with this bit set lies above it
-      }
-    }
-    // prefix: the take-th largest image; `remaining` of the candidates equal to it are still to be taken
-    const unsigned long long eq_a = __ballot(has_a && ua == prefix), eq_b = __ballot(has_b && ub == prefix);
-    const unsigned long long lt_mask = (1ull << lane) - 1ull;
-    const bool ch_a = take > 0 && has_a && (ua > prefix || (ua == prefix && __popcll(eq_a & lt_mask) < remaining));
-    const bool ch_b = take > 0 && has_b &&
-                      (ub > prefix || (ub == prefix && __popcll(eq_a) + __popcll(eq_b & lt_mask) < remaining));
-    const unsigned long long ma = __ballot(ch_a), mb = __ballot(ch_b);
-    if (ch_a) out[__popcll(ma & lt_mask)] = Ja;
-    const int na = __popcll(ma);
-    if (ch_b) out[na + __popcll(mb & lt_mask)] = Jb;
-    int base = na + __popcll(mb);
-    if (!p.bidir) {
-      if (lane == 0) out[base] = I;
-      ++base;
-    }
-    for (int e = base + lane; e < p.k; e += 64) out[e] = -1;
-    return;
-  }
-  for (int J = J_first + lane; J < J_end; J += 64) {
+  for (int J = cd.J_first + lane; J < cd.J_end; J += 64) {
     float acc = 0.0f;
 #pragma unroll 8
     for (int c = 0; c < D; ++c) acc = __fmaf_rn(qs[c], km[(size_t)c * p.NB + J], acc);
-    key_s[J] = J == I ? ~0ull : rank_key(acc, J, p.NB);
+    key_s[J] = J == I ? ~0ull : ((unsigned long long)score_image(acc) << 32) | (unsigned)(p.NB - 1 - J);
   }
   __syncthreads();
   int base = 0;
-  for (int J0 = J_first; J0 < J_end; J0 += 64) {
+  for (int J0 = cd.J_first; J0 < cd.J_end; J0 += 64) {
     const int J = J0 + lane;
     bool chosen = false;
-    if (J < J_end) {
+    if (J < cd.J_end) {
       const unsigned long long mine = key_s[J];
       int rank = 0;
-      for (int Jo = J_first; Jo < J_end; ++Jo) rank += key_s[Jo] > mine ? 1 : 0;
-      chosen = rank < take;
+      for (int Jo = cd.J_first; Jo < cd.J_end; ++Jo) rank += key_s[Jo] > mine ? 1 : 0;
+      chosen = rank < cd.take;
     }
     const unsigned long long mask = __ballot(chosen);
     if (chosen) {
@@ -283,29 +558,55 @@ __global__ __launch_bounds__(64) void score_topk_kernel(const float *__restrict_
 }
 
 // ---- launchers ----------------------------------------------------------------------------
+// One workgroup per head pools the whole of it, up to kHeadBytes of Q and K (beyond, the longest row of a batch sets the
+// time, not the memory).  With more than 32 blocks the scoring is no longer short, and fewer than kHeads heads leave CUs
+// idle through it: at B=30 H=8 L=2000 d=64 b=32 one workgroup per head takes 23 us and two kernels 29, at B=8 18 and 14.
+constexpr size_t kHeadBytes = 512 * 1024;
+constexpr long kHeads = 192;
+static bool one_workgroup_per_head(const KParams &p, size_t elem)
+{
+  if ((size_t)(p.L + std::min(p.L, p.nq * p.b)) * p.d * elem > kHeadBytes) return false;
+  if (p.NB > kRowBlocks || pick_lds(p, p.nq) > 64 * 1024) return false;
+  return p.NB <= kPairBlocks || (long)p.B * p.H >= kHeads;
+}
+
 template <typename T, int D>
 static void launch_select_t(const KParams &p, const void *Q, const void *K, bool kcmp, const int *valid_len,
                             int *sel, void *ws, void *Q_rot, void *K_rot, hipStream_t st)
 {
+  constexpr int LPT = D * (int)sizeof(T) / 16;  // (select_head_kernel's lanes per block)
+  if (!kcmp && !p.rope_cos && one_workgroup_per_head(p, sizeof(T))) {
+    const int lanes = std::max((p.nq + p.NB) * LPT, p.NB > kPairBlocks ? 64 * p.nq / kRowsPerWave : 0);
+    const int threads = std::min(1024, (lanes + 63) / 64 * 64);
+    hipLaunchKernelGGL((select_head_kernel<T, D>), dim3((unsigned)(p.B * p.H)), dim3((unsigned)threads), pick_lds(p, p.nq), st,
+                       (const T *)Q, (const T *)K, valid_len, sel, p);
+    return;
+  }
   float *qsum = reinterpret_cast<float *>(ws);
-  float *kmeanT = qsum + (size_t)p.B * p.H * p.NB * D;
+  float *kmean = qsum + (size_t)p.B * p.H * p.NB * D;
   const long tasks = 2L * p.B * p.H * p.NB;
   const int per_wg = 256 / (D / 4);
   const unsigned grid = (unsigned)((tasks + per_wg - 1) / per_wg);
   if (kcmp) {
     BLOSSOM_LAUNCH((pool_kernel<T, D, true>), dim3(grid), dim3(256), 0, st, (const T *)Q, (const T *)K,
-                   valid_len, qsum, kmeanT, p);
+                   valid_len, qsum, kmean, p);
   } else if (p.rope_cos) {
     const long rgrid = 2L * p.B * p.H * ((p.L + kRopeRows - 1) / kRopeRows);
     BLOSSOM_LAUNCH((rope_pool_kernel<T, D>), dim3((unsigned)rgrid), dim3(256), 0, st,
-                   (const T *)Q, (const T *)K, valid_len, qsum, kmeanT, (T *)Q_rot, (T *)K_rot, p);
+                   (const T *)Q, (const T *)K, valid_len, qsum, kmean, (T *)Q_rot, (T *)K_rot, p);
   } else {
     BLOSSOM_LAUNCH((pool_kernel<T, D, false>), dim3(grid), dim3(256), 0, st, (const T *)Q, (const T *)K,
-                   valid_len, qsum, kmeanT, p);
+                   valid_len, qsum, kmean, p);
   }
-  hipLaunchKernelGGL((score_topk_kernel<D>), dim3((unsigned)(p.B * p.H * p.nq)), dim3(64),
-                     (size_t)p.NB * sizeof(unsigned long long), st,
-                     qsum, kmeanT, valid_len, sel, p);
+  if (p.NB > kRowBlocks) {
+    hipLaunchKernelGGL((score_topk_many_kernel<D>), dim3((unsigned)(p.B * p.H * p.nq)), dim3(64),
+                       (size_t)p.NB * sizeof(unsigned long long), st, qsum, kmean, valid_len, sel, p);
+    return;
+  }
+  const int few = (long)p.B * p.H * p.nq < 1024L * kScoreRows ? 4 : kScoreRows;  // (1024 workgroups: four per CU)
+  const int rows = p.NB <= kPairBlocks ? p.nq : std::min(p.nq, few);
+  hipLaunchKernelGGL((score_topk_kernel<D>), dim3((unsigned)(p.B * p.H * ((p.nq + rows - 1) / rows))), dim3(256),
+                     pick_lds(p, rows), st, qsum, kmean, valid_len, sel, rows, p);
 }
 
 size_t select_workspace_bytes(const KParams &p) { return 2 * (size_t)p.B * p.H * p.NB * p.d * sizeof(float); }

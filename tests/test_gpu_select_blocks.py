@@ -1,0 +1,41 @@
+"""Block selection on the GPU against the CPU oracle where its kernels change hands: pairs up to 32 blocks, rows with one
+or two candidates per lane up to 128, more than 128; one workgroup per head or pooling and scoring apart, with few
+and many heads.  Inputs of small whole numbers make many scores equal, so that the order of equal scores counts too."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2512_13368_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rows,H,L,d,b,k,dtype,stis,last", [
+    (3, 2, 9, 8, 8, 2, "fp32", 0, False),         # two blocks, the second of one item
+    (3, 2, 512, 16, 16, 5, "fp32", 0, False),     # 32 blocks: the most that pairs take
+    (3, 2, 513, 16, 16, 5, "bf16", 0, False),     # 33, few heads: pooling apart, four rows per workgroup
+    (50, 4, 513, 8, 16, 4, "fp32", 0, False),     # 33, many heads: one workgroup per head
+    (50, 4, 1037, 16, 16, 6, "bf16", 2, False),   # 65 in the bidirectional form: two candidates per lane
+    (50, 4, 1024, 8, 8, 7, "fp32", 0, False),     # 128
+    (3, 2, 1024, 32, 8, 130, "bf16", 2, False),   # 128, everything selected, padding behind
+    (2, 2, 1025, 8, 8, 4, "fp32", 0, False),      # 129
+    (70, 4, 4100, 64, 64, 8, "bf16", 0, False),   # pooling apart, sixteen rows per workgroup, ragged last block
+    (4, 2, 2040, 64, 32, 8, "bf16", 0, True),     # the last block alone
+])
+def test_selection_at_the_limits_of_its_kernels(rows, H, L, d, b, k, dtype, stis, last):
+    rng = np.random.default_rng(L + k)
+    Q, K = (rng.integers(-1, 2, size=(rows, H, L, d)).astype(np.float32) for _ in range(2))
+    vl = rng.integers(0, L + 1, size=rows).astype(np.int32)
+    vl[:2] = [L, max(1, L - b - 3)]
+    vl[-1] = 0 if rows > 2 else 1
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    p = B.Params(rows, H, L, d, b, k, 8, B.BF16 if dtype == "bf16" else B.F32, stis_mode=stis, stis_block=b if stis else 0,
+                 last_block_only=int(last))
+    print(f"select B{rows} H{H} L{L} d{d} b{b} k{k} {dtype} stis{stis} last{last}", flush=True)
+    dev = [torch.from_numpy(t).cuda() for t in (Q, K, vl)]
+    sel = B.select_blocks(p, dev[0].to(dt), dev[1].to(dt), dev[2]).cpu().numpy()
+    want = oracle.select_blocks(Q, K, vl, b, k, bidir=stis == 2)
+    if last:
+        sel, want = sel[:, :, -1], want[:, :, -1]
+    np.testing.assert_array_equal(sel, want)
