@@ -1,4 +1,4 @@
-"""Python binding of libblossom.so: argument marshalling only.
+"""Python binding of libblossom.so: argument marshalling only (that of the hot calls in native code, ``_fastcall.so``).
 
 Every step of the path runs in the HIP kernels behind the C ABI of
 ``include/blossom.h``; this module turns torch device tensors into pointers,
@@ -135,6 +135,21 @@ class Params:
                              self.last_block_only)
 
 
+_fast = None
+
+
+def fastcall():
+    """The native marshalling of the hot calls (csrc/fastcall.cpp).  Each returns the C ABI's error code, or None where an
+    argument is missing or not as expected: then the Python path below allocates, or names what is wrong."""
+    global _fast
+    if _fast is None:
+        import torch  # noqa: F401  (the module is linked against its libraries)
+        lib()
+        from . import _fastcall
+        _fast = _fastcall
+    return _fast
+
+
 def workspace_bytes(p: Params, which: int) -> int:
     cp = p.c()
     return int(lib().blossom_workspace_bytes(ctypes.byref(cp), which))
@@ -173,6 +188,11 @@ def _workspace(p: Params, which: int, ws, device):
 
 
 def select_blocks(p: Params, Q, K, valid_len, sel=None, ws=None, stream=None):
+    rc = (_fast or fastcall()).select_blocks(p, Q, K, valid_len, sel, ws, stream)
+    if rc is not None:
+        if rc:
+            raise BlossomError(rc, "blossom_select_blocks")
+        return sel
     import torch
     shp = (p.B, p.H, p.L, p.d)
     _check_tensor(Q, shp, _torch_dtype(p), "Q")
@@ -211,6 +231,11 @@ def select_blocks_static(p: Params, Q, K, valid_len, sel, stream=None):
 def rope_select_blocks(p: Params, Q, K, rope_cos, rope_sin, valid_len, Q_rot=None, K_rot=None, sel=None, ws=None,
                        stream=None):
     """blossom_rope_select_blocks: returns (Q_rot, K_rot, sel)."""
+    rc = (_fast or fastcall()).rope_select_blocks(p, Q, K, rope_cos, rope_sin, valid_len, Q_rot, K_rot, sel, ws, stream)
+    if rc is not None:
+        if rc:
+            raise BlossomError(rc, "blossom_rope_select_blocks")
+        return Q_rot, K_rot, sel
     import torch
     shp = (p.B, p.H, p.L, p.d)
     dt = _torch_dtype(p)
@@ -267,6 +292,13 @@ class FwdOut:
 
 def attn_fwd(p: Params, Q, K, V, valid_len, sel, gate_w, gate_b=None, out: FwdOut | None = None,
              ws=None, stream=None) -> FwdOut:
+    if out is not None:
+        rc = (_fast or fastcall()).attn_fwd(p, Q, K, V, valid_len, sel, gate_w, gate_b, out.O, out.o_lt, out.o_st, out.lse_lt,
+                                            out.lse_st, ws, stream)
+        if rc is not None:
+            if rc:
+                raise BlossomError(rc, "blossom_attn_fwd")
+            return out
     import torch
     shp = (p.B, p.H, p.L, p.d)
     dt = _torch_dtype(p)
@@ -310,6 +342,14 @@ class BwdOut:
 def attn_bwd(p: Params, Q, K, V, valid_len, sel, gate_w, gate_b, fwd: FwdOut, dO,
              out: BwdOut | None = None, ws=None, stream=None, stages: int = BWD_ALL, rope=None) -> BwdOut:
     """blossom_attn_bwd (or _stages); rope=(cos, sin) calls blossom_attn_bwd_rope instead."""
+    if out is not None and stages == BWD_ALL:
+        rc = (_fast or fastcall()).attn_bwd(p, Q, K, V, valid_len, sel, gate_w, gate_b, fwd.o_lt, fwd.o_st, fwd.lse_lt,
+                                            fwd.lse_st, dO, out.dQ, out.dK, out.dV, out.d_gate_w, out.d_gate_b, ws,
+                                            *(rope or (None, None)), stream)
+        if rc is not None:
+            if rc:
+                raise BlossomError(rc, "blossom_attn_bwd")
+            return out
     import torch
     shp = (p.B, p.H, p.L, p.d)
     dt = _torch_dtype(p)
@@ -398,6 +438,12 @@ def select_positions(p: Params, kv_groups: int, cmp_block: int, cmp_stride: int,
                      sel_pos=None, ws=None, stream=None):
     """blossom_select_positions: the printed selection rule, one row per position and key/value group.
     p.block is the selection block size, p.topk is k.  Returns sel_pos int32 [B,G,L,topk]."""
+    rc = (_fast or fastcall()).select_positions(p, kv_groups, cmp_block, cmp_stride, Q, K, valid_len, score_scale, sel_pos, ws,
+                                                stream)
+    if rc is not None:
+        if rc:
+            raise BlossomError(rc, "blossom_select_positions")
+        return sel_pos
     import torch
     dt = _torch_dtype(p)
     _check_tensor(Q, (p.B, p.H, p.L, p.d), dt, "Q")
@@ -421,6 +467,13 @@ def attn_fwd_positions(p: Params, kv_groups: int, Q, K, V, valid_len, sel_pos, g
                        want_branches: bool = False, stream=None) -> FwdOut:
     """blossom_attn_fwd_positions: forward under one selection row per query position and key/value group
     (K, V [B,G,L,d], sel_pos [B,G,L,topk]).  `want_branches` also returns o_lt, o_st, lse_lt, lse_st."""
+    if out is not None:
+        rc = (_fast or fastcall()).attn_fwd_positions(p, kv_groups, Q, K, V, valid_len, sel_pos, gate_w, gate_b, out.O, out.o_lt,
+                                                      out.o_st, out.lse_lt, out.lse_st, stream)
+        if rc is not None:
+            if rc:
+                raise BlossomError(rc, "blossom_attn_fwd_positions")
+            return out
     import torch
     shp = (p.B, p.H, p.L, p.d)
     dt = _torch_dtype(p)
@@ -451,6 +504,14 @@ def attn_bwd_positions(p: Params, kv_groups: int, Q, K, V, valid_len, sel_pos, g
                        out: BwdOut | None = None, ws=None, stream=None) -> BwdOut:
     """blossom_attn_bwd_positions: backward of attn_fwd_positions (dQ [B,H,L,d]; dK, dV [B,G,L,d]: the
     gradients of the query heads of a group added up)."""
+    if out is not None:
+        rc = (_fast or fastcall()).attn_bwd_positions(p, kv_groups, Q, K, V, valid_len, sel_pos, gate_w, gate_b, fwd.o_lt,
+                                                      fwd.o_st, fwd.lse_lt, fwd.lse_st, dO, out.dQ, out.dK, out.dV,
+                                                      out.d_gate_w, out.d_gate_b, ws, stream)
+        if rc is not None:
+            if rc:
+                raise BlossomError(rc, "blossom_attn_bwd_positions")
+            return out
     import torch
     shp = (p.B, p.H, p.L, p.d)
     kv_shp = (p.B, kv_groups, p.L, p.d)
@@ -498,6 +559,17 @@ def out_proj_ln(p: Params, d_model: int, O, W_O_t, H_prev, ln_gamma, ln_beta, ln
     """blossom_out_proj_ln: S = LayerNorm(H_prev + Concat_h(O[:, h]) W^O (+ bias)); W_O_t is [d_model, H*d].
     Returns S, or (S, mean, rstd) with want_stats."""
     import torch
+    mean = rstd = None
+    if want_stats:
+        mean = torch.empty((p.B, p.L), dtype=torch.float32, device=O.device)
+        rstd = torch.empty((p.B, p.L), dtype=torch.float32, device=O.device)
+    if S is not None:
+        rc = (_fast or fastcall()).out_proj_ln(p, d_model, O, W_O_t, bias, H_prev, ln_gamma, ln_beta, ln_eps, S, mean, rstd,
+                                               stream)
+        if rc is not None:
+            if rc:
+                raise BlossomError(rc, "blossom_out_proj_ln")
+            return (S, mean, rstd) if want_stats else S
     dt = _torch_dtype(p)
     _check_tensor(O, (p.B, p.H, p.L, p.d), dt, "O")
     _check_tensor(W_O_t, (d_model, p.H * p.d), dt, "W_O_t")
@@ -508,10 +580,6 @@ def out_proj_ln(p: Params, d_model: int, O, W_O_t, H_prev, ln_gamma, ln_beta, ln
     if S is None:
         S = torch.empty((p.B, p.L, d_model), dtype=dt, device=O.device)
     _check_tensor(S, (p.B, p.L, d_model), dt, "S")
-    mean = rstd = None
-    if want_stats:
-        mean = torch.empty((p.B, p.L), dtype=torch.float32, device=O.device)
-        rstd = torch.empty((p.B, p.L), dtype=torch.float32, device=O.device)
     cp = p.c()
     rc = lib().blossom_out_proj_ln(ctypes.byref(cp), d_model, _ptr(O), _ptr(W_O_t), _ptr(bias), _ptr(H_prev), _ptr(ln_gamma),
                                    _ptr(ln_beta), float(ln_eps), _ptr(S), _ptr(mean), _ptr(rstd), _stream(stream))

@@ -1,4 +1,4 @@
-"""Builds libblossom.so in-tree with hipcc for gfx950 (cross-compiles without a GPU)."""
+"""Builds libblossom.so in-tree with hipcc for gfx950 (cross-compiles without a GPU), and the binding's host module."""
 from __future__ import annotations
 
 import os
@@ -8,6 +8,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libblossom.so")
+FASTCALL = os.path.join(HERE, "_fastcall.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
 # per-file extra flags; select.hip decides integers from fp32 arithmetic and must not be
@@ -40,14 +41,35 @@ def _hipcc() -> str:
     return "hipcc"
 
 
+def fastcall_command(obj: str) -> list[str]:
+    """Compiles csrc/fastcall.cpp: host code only, against the headers of the installed torch and Python."""
+    import sysconfig
+
+    import torch
+    inc = os.path.join(os.path.dirname(torch.__file__), "include")
+    return [_hipcc(), "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-D__HIP_PLATFORM_AMD__=1",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-isystem", inc, "-isystem",
+            sysconfig.get_paths()["include"], "-isystem", "/opt/rocm/include", "-c", os.path.join(CSRC, "fastcall.cpp"), "-o", obj]
+
+
+def link_fastcall(obj: str) -> None:
+    import torch
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = [_hipcc(), "-shared", "-fPIC", "-o", FASTCALL, obj, "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip",
+           "-L" + HERE, "-lblossom", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"link of _fastcall.so failed:\n{r.stdout}\n{r.stderr}")
+
+
 def build_library(verbose: bool = False) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
     hipcc = _hipcc()
 
     def compile_one(item):
         src, extra = item
-        obj = os.path.join(OBJ_DIR, src.replace(".hip", ".o"))
-        cmd = [hipcc, *COMMON, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
+        obj = os.path.join(OBJ_DIR, os.path.splitext(src)[0] + ".o")
+        cmd = [hipcc, *COMMON, *extra, "-c", os.path.join(CSRC, src), "-o", obj] if src.endswith(".hip") else fastcall_command(obj)
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:
             raise RuntimeError(f"hipcc failed for {src}:\n{r.stdout}\n{r.stderr}")
@@ -56,11 +78,12 @@ def build_library(verbose: bool = False) -> str:
         return obj
 
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
-        objs = list(ex.map(compile_one, SOURCES.items()))
+        *objs, host = ex.map(compile_one, [*SOURCES.items(), ("fastcall.cpp", [])])
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
+    link_fastcall(host)
     return LIB
 
 
