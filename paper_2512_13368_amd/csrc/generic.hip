@@ -339,14 +339,48 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D <= 32 ? 4 
 // =============================================================================================
 // Backward, step 1: gate backward per row + per-chunk partial gate-weight gradients.
 //   rowstat[row] = (alpha, dz, D_lt, D_st)
-//   rowB[row]    = (dO.o_lt, dO.o_st, Wg_lt.o_lt, Wg_st.o_st)      (matrix-core path)
-//   rowC[row]    = (Wg_lt.v, Wg_st.v)                               (matrix-core path)
+//   g_x, rowI_x: the branch's rounded upstream gradient and row constants (matrix-core path, see below)
 //   partial[(bh*nchunk+chunk)][0..2D] (2D = bias)
-// D/4 lanes share a row (16-byte loads, whole rows coalesced), several rows per wavefront step;
-// every tensor is read exactly once; the row sums are xor-shuffle reductions over the lanes of
-// a row, the gate-weight partials accumulate in registers and meet in LDS in a fixed order.
+// Every tensor is read exactly once, so memory is the bound, but a row costs five sums over its channels and
+// some sixty instructions that its lanes share: as few lanes as give whole cache lines take a row (4 channels
+// each, for d = 64 twice 4: 8 lanes), the sums are DPP adds inside a row of 16 lanes instead of LDS permutes, and the
+// next rows are requested before the current ones are worked on.  B=128 H=4 L=1024 d=64, lengths U[100,1024]: 77 -> 71 us;
+// B=16 H=8 L=8192: 183 -> 173 us (5.7 TB/s).
+// The gate-weight partials accumulate in registers and meet in LDS in a fixed order.
 // =============================================================================================
 constexpr int kPrepRows = 128;
+
+// four consecutive elements as loaded, and as floats (zeros unless `keep`)
+struct Raw4f { uint4 w; };
+struct Raw4h { uint2 w; };
+__device__ __forceinline__ Raw4f load_raw4(const float *p) { return {*reinterpret_cast<const uint4 *>(p)}; }
+__device__ __forceinline__ Raw4h load_raw4(const bf16_t *p) { return {*reinterpret_cast<const uint2 *>(p)}; }
+__device__ __forceinline__ void unpack4(Raw4f r, bool keep, float *o)
+{
+  o[0] = __uint_as_float(keep ? r.w.x : 0u); o[1] = __uint_as_float(keep ? r.w.y : 0u);
+  o[2] = __uint_as_float(keep ? r.w.z : 0u); o[3] = __uint_as_float(keep ? r.w.w : 0u);
+}
+__device__ __forceinline__ void unpack4(Raw4h r, bool keep, float *o)
+{
+  const uint32_t x = keep ? r.w.x : 0u, y = keep ? r.w.y : 0u;
+  o[0] = mfma::bf_lo(x); o[1] = mfma::bf_hi(x); o[2] = mfma::bf_lo(y); o[3] = mfma::bf_hi(y);
+}
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_of(float x)
+{
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, false));
+}
+// sum over N = 2, 4, 8 or 16 adjacent lanes, the same in all of them
+template <int N>
+__device__ __forceinline__ float lanes_sum(float x)
+{
+  x += dpp_of<0xB1>(x);                  // the neighbour
+  if (N > 2) x += dpp_of<0x4E>(x);       // the other pair of the quad
+  if (N > 4) x += dpp_of<0x141>(x);      // half-row mirror: the other quad (its lanes agree)
+  if (N > 8) x += dpp_of<0x140>(x);      // row mirror: the other half
+  return x;
+}
 
 template <typename T, int D>
 __global__ __launch_bounds__(256) void bwd_prep_kernel(const float *__restrict__ o_lt,
@@ -364,9 +398,11 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(const float *__restrict__
                                                        uint4 *__restrict__ rowI_lt,
                                                        uint4 *__restrict__ rowI_st, KParams p)
 {
-  constexpr int LPR = D / 4;        // lanes per row
-  constexpr int RPW = 64 / LPR;     // rows per wavefront step
-  constexpr int RPS = 4 * RPW;      // rows per workgroup step
+  constexpr int CPL = D >= 64 ? 8 : 4;  // channels per lane, in groups of four D/2 apart
+  constexpr int NG = CPL / 4;
+  constexpr int LPR = D / CPL;          // lanes per row
+  constexpr int RPW = 64 / LPR;         // rows per wavefront step
+  constexpr int RPS = 4 * RPW;          // rows per workgroup step
   constexpr int G = 2 * D + 1;
   __shared__ float red[4 * RPW][G];
   const int t = threadIdx.x;
@@ -379,41 +415,77 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(const float *__restrict__
   const int h = bh % p.H;
   const int n = clamp_len(valid_len[bh / p.H], p.L);
   const int p0 = p.L - n;
+  // rows of blocks that hold no valid position are never read by the kernels that follow: nothing is
+  // written for them (pad rows of a partly valid block are staged with their tile and get zeros)
+  const int first = (p0 / p.b) * p.b;
+  float *out = partial + (size_t)blockIdx.x * G;
+  if ((chunk + 1) * kPrepRows <= first) {
+    for (int c = t; c < G; c += 256) out[c] = 0.0f;
+    return;
+  }
   const size_t head = (size_t)bh * p.L * D;
-  float wl[4], ws[4];
-  load4(gate_w + (size_t)h * 2 * D + c4, wl);
-  load4(gate_w + (size_t)h * 2 * D + D + c4, ws);
-  const float bias = gate_b ? gate_b[h] : 0.0f;
-  float acc_l[4] = {0.0f, 0.0f, 0.0f, 0.0f}, acc_s[4] = {0.0f, 0.0f, 0.0f, 0.0f}, acc_b = 0.0f;
 
-  for (int base = 0; base < kPrepRows; base += RPS) {
-    const int i = chunk * kPrepRows + base + wave * RPW + rg;
-    const bool valid = i < p.L && i >= p0;
-    // rows of blocks that hold no valid position are never read by the kernels that follow: nothing is
-    // written for them (pad rows of a partly valid block are staged with their tile and get zeros)
-    const bool inb = i < p.L && i >= (p0 / p.b) * p.b;
-    float g[4] = {0.f, 0.f, 0.f, 0.f}, ol[4] = {0.f, 0.f, 0.f, 0.f}, os[4] = {0.f, 0.f, 0.f, 0.f};
-    if (valid) {
-      const size_t ro = head + (size_t)i * D + c4;
-      load4(dO + ro, g);
-      load4(o_lt + ro, ol);
-      load4(o_st + ro, os);
+  struct Rows {
+    decltype(load_raw4(dO)) g[NG];
+    Raw4f ol[NG], os[NG];
+    float ll, ls;
+  };
+  const int row0 = chunk * kPrepRows + wave * RPW + rg;
+  auto request = [&](int base, Rows &r) __attribute__((always_inline)) {
+    const int i = min(max(row0 + base, p0), p.L - 1);
+    const size_t ro = head + (size_t)i * D + c4, lr = (size_t)bh * p.L + i;
+#pragma unroll
+    for (int q = 0; q < NG; ++q) {
+      r.g[q] = load_raw4(dO + ro + q * (D / 2));
+      r.ol[q] = load_raw4(o_lt + ro + q * (D / 2));
+      r.os[q] = load_raw4(o_st + ro + q * (D / 2));
     }
+    r.ll = r.ls = 0.0f;
+    if (g_lt) {
+      r.ll = lse_lt[lr];
+      r.ls = lse_st[lr];
+    }
+  };
+  Rows cur, nxt;
+  request(0, cur);
+  float wl[CPL], ws[CPL];
+#pragma unroll
+  for (int q = 0; q < NG; ++q) {
+    unpack4(load_raw4(gate_w + (size_t)h * 2 * D + c4 + q * (D / 2)), true, wl + 4 * q);
+    unpack4(load_raw4(gate_w + (size_t)h * 2 * D + D + c4 + q * (D / 2)), true, ws + 4 * q);
+  }
+  const float bias = gate_b ? gate_b[h] : 0.0f;
+  float acc_l[CPL], acc_s[CPL], acc_b = 0.0f;
+#pragma unroll
+  for (int e = 0; e < CPL; ++e) acc_l[e] = acc_s[e] = 0.0f;
+
+#pragma unroll 1
+  for (int base = 0; base < kPrepRows; base += RPS) {
+    const int i = row0 + base;
+    const bool valid = i < p.L && i >= p0;
+    const bool inb = i < p.L && i >= first;
+    if (base + RPS < kPrepRows) request(base + RPS, nxt);
+    float g[CPL], ol[CPL], os[CPL];
+#pragma unroll
+    for (int q = 0; q < NG; ++q) {
+      unpack4(cur.g[q], valid, g + 4 * q);
+      unpack4(cur.ol[q], valid, ol + 4 * q);
+      unpack4(cur.os[q], valid, os + 4 * q);
+    }
+    const float ll = cur.ll, ls = cur.ls;
+    cur = nxt;
     float a_ll = 0.f, a_ss = 0.f, w_l = 0.f, w_s = 0.f;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    for (int e = 0; e < CPL; ++e) {
       a_ll = fmaf(g[e], ol[e], a_ll);
       a_ss = fmaf(g[e], os[e], a_ss);
       w_l = fmaf(wl[e], ol[e], w_l);
       w_s = fmaf(ws[e], os[e], w_s);
     }
-#pragma unroll
-    for (int off = 1; off < LPR; off <<= 1) {
-      a_ll += __shfl_xor(a_ll, off);
-      a_ss += __shfl_xor(a_ss, off);
-      w_l += __shfl_xor(w_l, off);
-      w_s += __shfl_xor(w_s, off);
-    }
+    a_ll = lanes_sum<LPR>(a_ll);
+    a_ss = lanes_sum<LPR>(a_ss);
+    w_l = lanes_sum<LPR>(w_l);
+    w_s = lanes_sum<LPR>(w_s);
     float4 st = make_float4(0.f, 0.f, 0.f, 0.f);
     float dz = 0.0f, alpha = 0.0f;
     if (valid) {
@@ -429,39 +501,35 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(const float *__restrict__
       // that P*(dO_x.v - c_x) is the exact softmax backward of the rounded gradient (rows with a
       // single key still cancel to zero).  -lse*log2(e) and -c_x are left as three-term bf16
       // splits, the form in which one matrix instruction broadcasts them into an accumulator.
-      uint16_t gl[4], gs[4];
+      uint32_t gl[CPL / 2], gs[CPL / 2];
       float c_l = 0.0f, c_s = 0.0f;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        gl[e] = f32_to_bf16(fmaf(alpha, g[e], dz * wl[e]));
-        gs[e] = f32_to_bf16(fmaf(1.0f - alpha, g[e], dz * ws[e]));
-        c_l = fmaf(bf16_to_f32(gl[e]), ol[e], c_l);
-        c_s = fmaf(bf16_to_f32(gs[e]), os[e], c_s);
+      for (int e = 0; e < CPL; e += 2) {
+        gl[e / 2] = mfma::pack2_bf16(fmaf(alpha, g[e], dz * wl[e]), fmaf(alpha, g[e + 1], dz * wl[e + 1]));
+        gs[e / 2] = mfma::pack2_bf16(fmaf(1.0f - alpha, g[e], dz * ws[e]), fmaf(1.0f - alpha, g[e + 1], dz * ws[e + 1]));
+        c_l = fmaf(mfma::bf_hi(gl[e / 2]), ol[e + 1], fmaf(mfma::bf_lo(gl[e / 2]), ol[e], c_l));
+        c_s = fmaf(mfma::bf_hi(gs[e / 2]), os[e + 1], fmaf(mfma::bf_lo(gs[e / 2]), os[e], c_s));
       }
-#pragma unroll
-      for (int off = 1; off < LPR; off <<= 1) {
-        c_l += __shfl_xor(c_l, off);
-        c_s += __shfl_xor(c_s, off);
-      }
+      c_l = lanes_sum<LPR>(c_l);
+      c_s = lanes_sum<LPR>(c_s);
       if (inb) {
         const size_t ro = head + (size_t)i * D + c4;
-        *reinterpret_cast<uint2 *>(g_lt + ro) =
-            make_uint2((uint32_t)gl[0] | ((uint32_t)gl[1] << 16), (uint32_t)gl[2] | ((uint32_t)gl[3] << 16));
-        *reinterpret_cast<uint2 *>(g_st + ro) =
-            make_uint2((uint32_t)gs[0] | ((uint32_t)gs[1] << 16), (uint32_t)gs[2] | ((uint32_t)gs[3] << 16));
-        if (sub == 0) {
+#pragma unroll
+        for (int q = 0; q < NG; ++q) {
+          *reinterpret_cast<uint2 *>(g_lt + ro + q * (D / 2)) = make_uint2(gl[2 * q], gl[2 * q + 1]);
+          *reinterpret_cast<uint2 *>(g_st + ro + q * (D / 2)) = make_uint2(gs[2 * q], gs[2 * q + 1]);
+        }
+        if (sub < 2) {  // lane 0 of the row writes the long-term constants, lane 1 the short-term ones
           const size_t r = (size_t)bh * p.L + i;
           // pad rows: an exponent of -1e30 makes every probability of the row zero
-          const uint2 l_l = mfma::split3(valid ? -lse_lt[r] * 1.4426950408889634f : -1.0e30f);
-          const uint2 l_s = mfma::split3(valid ? -lse_st[r] * 1.4426950408889634f : -1.0e30f);
-          const uint2 k_l = mfma::split3(-c_l), k_s = mfma::split3(-c_s);
-          rowI_lt[r] = make_uint4(l_l.x, l_l.y, k_l.x, k_l.y);
-          rowI_st[r] = make_uint4(l_s.x, l_s.y, k_s.x, k_s.y);
+          const uint2 l = mfma::split3(valid ? -(sub == 0 ? ll : ls) * 1.4426950408889634f : -1.0e30f);
+          const uint2 k = mfma::split3(-(sub == 0 ? c_l : c_s));
+          (sub == 0 ? rowI_lt : rowI_st)[r] = make_uint4(l.x, l.y, k.x, k.y);
         }
       }
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    for (int e = 0; e < CPL; ++e) {
       acc_l[e] = fmaf(dz, ol[e], acc_l[e]);
       acc_s[e] = fmaf(dz, os[e], acc_s[e]);
     }
@@ -469,13 +537,13 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(const float *__restrict__
   }
   const int slot = wave * RPW + rg;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    red[slot][c4 + e] = acc_l[e];
-    red[slot][D + c4 + e] = acc_s[e];
+  for (int e = 0; e < CPL; ++e) {
+    const int c = c4 + (e & 3) + (e >> 2) * (D / 2);
+    red[slot][c] = acc_l[e];
+    red[slot][D + c] = acc_s[e];
   }
   if (sub == 0) red[slot][2 * D] = acc_b;
   __syncthreads();
-  float *out = partial + (size_t)blockIdx.x * G;
   for (int c = t; c < G; c += 256) {
     float acc = 0.0f;
 #pragma unroll

@@ -72,10 +72,10 @@ __device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 
 // in which one matrix instruction broadcasts a per-row constant into an accumulator
 __device__ __forceinline__ uint2 split3(float x)
 {
-  const uint16_t hi = f32_to_bf16(x);
+  const uint16_t hi = __builtin_bit_cast(uint16_t, (__bf16)x);
   const float r1 = x - bf16_to_f32(hi);
-  const uint16_t mid = f32_to_bf16(r1);
-  const uint16_t lo = f32_to_bf16(r1 - bf16_to_f32(mid));
+  const uint16_t mid = __builtin_bit_cast(uint16_t, (__bf16)r1);
+  const uint16_t lo = __builtin_bit_cast(uint16_t, (__bf16)(r1 - bf16_to_f32(mid)));
   return make_uint2((uint32_t)hi | ((uint32_t)mid << 16), (uint32_t)lo);
 }
 __device__ __forceinline__ float unsplit3(uint32_t x, uint32_t y) { return (bf_lo(x) + bf_hi(x)) + bf_lo(y); }
