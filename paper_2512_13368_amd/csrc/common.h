@@ -105,12 +105,15 @@ __device__ __forceinline__ int clamp_len(int n, int L) { return n < 0 ? 0 : (n >
 
 // Backward of the rotary position embedding on one channel pair (2i, 2i+1) of the row at position m:
 // the transpose rotation, applied to the fp32 gradient before it is rounded to the storage type.
-__device__ __forceinline__ void unrope_pair(const KParams &p, int m, int pair, int half_d, float &g0, float &g1)
+__device__ __forceinline__ void unrope_pair(float c, float s, float &g0, float &g1)
 {
-  const float c = p.rope_cos[(size_t)m * half_d + pair], s = p.rope_sin[(size_t)m * half_d + pair];
   const float a = g0, b = g1;
   g0 = fmaf(c, a, s * b);
   g1 = fmaf(c, b, -(s * a));
+}
+__device__ __forceinline__ void unrope_pair(const KParams &p, int m, int pair, int half_d, float &g0, float &g1)
+{
+  unrope_pair(p.rope_cos[(size_t)m * half_d + pair], p.rope_sin[(size_t)m * half_d + pair], g0, g1);
 }
 template <int D>
 __device__ __forceinline__ void unrope_row(const KParams &p, int m, float (&g)[D])

@@ -68,7 +68,7 @@ struct Stager {
   int wv, ld_row;
   bool ragged;
   int L, NB;
-  unsigned lane_off;  // bytes: (ld_row, chunk) of this lane inside a tile, 8-row slices 0 and 2
+  unsigned lane_off;  // bytes: (ld_row, chunk) of this lane inside a tile (BLK = 32: the chunk alone), 8-row slices 0 and 2
   unsigned lane_odd;  // the same for slices 1 and 3 (row bit 3 set: another swizzle)
   __device__ __forceinline__ void init(int wv_, int lane, int L_, int NB_)
   {
@@ -78,13 +78,26 @@ struct Stager {
     ld_row = 32 * wv + (lane >> 3);
     ragged = L % BLK != 0;
     // LDS chunk position lane&7 holds chunk (lane&7)^swz(row)
-    lane_off = (unsigned)(ld_row * D + ((lane & 7) ^ swz(ld_row)) * 8) * 2u;
-    lane_odd = (unsigned)(ld_row * D + ((lane & 7) ^ swz(ld_row + 8)) * 8) * 2u;
+    lane_off = (unsigned)((BLK == 32 ? 0 : ld_row * D) + ((lane & 7) ^ swz(ld_row)) * 8) * 2u;
+    lane_odd = (unsigned)((BLK == 32 ? 0 : ld_row * D) + ((lane & 7) ^ swz(ld_row + 8)) * 8) * 2u;
   }
   // src_head: first element of the (row, head) slice of the tensor
   __device__ __forceinline__ void stage(const uint16_t *src_head, uint16_t *dst_tile, int blk) const
   {
     constexpr int TILE = BLK * D;
+    if constexpr (BLK == 32) {
+      // (no branch for the last, partial block: its rows past the end are clamped, always masked; a buffer load, for the
+      // compiler counts the global one as a flat access, before which it waits for everything: see REFILL)
+      blk = max(blk, 0);  // (block -1: a skipped list entry, every key masked)
+      const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(src_head), 0, L * (D * 2), 0x00020000);
+      const int row_max = L - 1 - blk * BLK;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const unsigned off = (unsigned)min(ld_row + 8 * u, row_max) * (D * 2) + ((u & 1) ? lane_odd : lane_off);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (lds_void *)(dst_tile + 8 * u * D), 16, off, blk * (TILE * 2), 0, 0);
+      }
+      return;
+    }
     const char *src = reinterpret_cast<const char *>(src_head) + (size_t)max(blk, 0) * (TILE * 2);  // uniform (block -1: a skipped list entry, every key masked)
     lds_void *dst = (lds_void *)(dst_tile + 32 * wv * D);
     if (!ragged || blk != NB - 1) {
@@ -128,23 +141,19 @@ __device__ __forceinline__ void to_operand(const f32x16 &a, bf16x8 (&f)[2])
   }
 }
 
-// row of bf16 (this lane's 4 slabs of 8) scaled by c, as the stationary operand
-__device__ __forceinline__ void load_frags(const uint16_t *row, int lh, float c, bf16x8 (&f)[4])
+// row of bf16 (this lane's 4 slabs of 8) as the stationary operand
+__device__ __forceinline__ void load_frags(const uint16_t *row, int lh, bf16x8 (&f)[4])
 {
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const uint4 raw = *reinterpret_cast<const uint4 *>(row + 16 * kk + 8 * lh);
-    if (c == 1.0f) {
-      f[kk] = __builtin_bit_cast(bf16x8, raw);
-    } else {
-      const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+  for (int kk = 0; kk < 4; ++kk) f[kk] = *reinterpret_cast<const bf16x8 *>(row + 16 * kk + 8 * lh);
+}
+// ... times c (apart from the loads, so that other requests go out before their arrival is waited for)
+__device__ __forceinline__ void scale_frags(float c, bf16x8 (&f)[4])
+{
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        f[kk][2 * e] = (__bf16)(bf_lo(w[e]) * c);
-        f[kk][2 * e + 1] = (__bf16)(bf_hi(w[e]) * c);
-      }
-    }
-  }
+  for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) f[kk][e] = (__bf16)((float)f[kk][e] * c);
 }
 
 // Stores 2 x 16 accumulators (d x rows, transposed) as bf16, scaled, through LDS: the wavefront's 32 rows
@@ -164,23 +173,37 @@ __device__ __forceinline__ void store_rows_bf16(uint16_t *dst_row0, int rows_lef
   const int elq = el & 31, elh = el >> 5;
   const float sc = keep ? scale : 0.0f;
   const bool rot = unrope && p.rope_cos != nullptr;
-  const int m = min(m_row0 + elq, p.L - 1);
+  auto put = [&](int mb, int g, float v0, float v1, float v2, float v3) __attribute__((always_inline)) {
+    uint2 pk;
+    pk.x = pack2_bf16(v0 * sc, v1 * sc);
+    pk.y = pack2_bf16(v2 * sc, v3 * sc);
+    const int chunk = 4 * mb + g;  // 16-byte chunk of the row; this lane fills half elh of it
+    *reinterpret_cast<uint2 *>(pt + elq * D + ((chunk ^ (elq & 7)) * 8) + 4 * elh) = pk;
+  };
+  if (rot) {  // (its own branch around all of it, the tables requested eight pairs at a time)
+    const size_t first = (size_t)min(m_row0 + elq, p.L - 1) * (D / 2) + 2 * elh;
 #pragma unroll
-  for (int mb = 0; mb < 2; ++mb)
+    for (int mb = 0; mb < 2; ++mb) {
+      float2 c[4], s[4];  // channels 32*mb + 8*g + 4*elh + (0..3) are the pairs 16*mb + 4*g + 2*elh + (0, 1)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      float v0 = acc[mb][4 * g], v1 = acc[mb][4 * g + 1], v2 = acc[mb][4 * g + 2], v3 = acc[mb][4 * g + 3];
-      if (rot) {
-        const int pair = 16 * mb + 4 * g + 2 * elh;  // channels 32*mb + 8*g + 4*elh + (0..3)
-        unrope_pair(p, m, pair, D / 2, v0, v1);
-        unrope_pair(p, m, pair + 1, D / 2, v2, v3);
+      for (int g = 0; g < 4; ++g) {
+        c[g] = *reinterpret_cast<const float2 *>(p.rope_cos + first + 16 * mb + 4 * g);
+        s[g] = *reinterpret_cast<const float2 *>(p.rope_sin + first + 16 * mb + 4 * g);
       }
-      uint2 pk;
-      pk.x = pack2_bf16(v0 * sc, v1 * sc);
-      pk.y = pack2_bf16(v2 * sc, v3 * sc);
-      const int chunk = 4 * mb + g;  // 16-byte chunk of the row; this lane fills half elh of it
-      *reinterpret_cast<uint2 *>(pt + elq * D + ((chunk ^ (elq & 7)) * 8) + 4 * elh) = pk;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        float v0 = acc[mb][4 * g], v1 = acc[mb][4 * g + 1], v2 = acc[mb][4 * g + 2], v3 = acc[mb][4 * g + 3];
+        unrope_pair(c[g].x, s[g].x, v0, v1);
+        unrope_pair(c[g].y, s[g].y, v2, v3);
+        put(mb, g, v0, v1, v2, v3);
+      }
     }
+  } else {
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) put(mb, g, acc[mb][4 * g], acc[mb][4 * g + 1], acc[mb][4 * g + 2], acc[mb][4 * g + 3]);
+  }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int rr = 8 * i + (el >> 3), c = el & 7;
@@ -190,6 +213,10 @@ __device__ __forceinline__ void store_rows_bf16(uint16_t *dst_row0, int rows_lef
     if (rr < rows_left) __builtin_nontemporal_store(vv, reinterpret_cast<u32x4_t *>(dst_row0 + (size_t)rr * D + 8 * c));
   }
 }
+
+// s_waitcnt immediates (gfx9 encoding: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8)
+constexpr int kVm0 = (7 << 4) | (15 << 8);             // every vector-memory operation has finished
+constexpr int kLgkm0 = 15 | (7 << 4) | (3 << 14);      // every LDS and scalar-memory operation has
 
 constexpr int kFewKeys = 32;    // rows seeing fewer keys than this get two-term bf16 operands
 
@@ -234,7 +261,7 @@ __device__ __forceinline__ void bwd_dq_body(
     uint16_t *Ks0, uint16_t *Ks1, uint16_t *Vs0, uint16_t *Vs1)
 {
   constexpr int UNITS = BLK / 32;
-  constexpr int TILE = BLK * D;
+  constexpr bool ONE = UNITS == 1;  // a workgroup of one wavefront: see REFILL at bwd_both_mfma_kernel
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -260,11 +287,10 @@ __device__ __forceinline__ void bwd_dq_body(
     return;
   }
 
-  const float c2 = p.scale * kLog2e;
   bf16x8 qf[4], gf[4], gf_next[4];
-  load_frags(Q + rowoff, lh, c2, qf);
-  load_frags(g_st + rowoff, lh, 1.0f, gf);       // the walk starts with the window tiles
-  load_frags(g_lt + rowoff, lh, 1.0f, gf_next);
+  load_frags(Q + rowoff, lh, qf);
+  load_frags(g_st + rowoff, lh, gf);       // the walk starts with the window tiles
+  load_frags(g_lt + rowoff, lh, gf_next);
   // per-row constants (pad rows carry an exponent of -1e30: every probability of the column is zero)
   const uint4 ri_st = rowI_st[lrow];
   const uint4 ri_lt = rowI_lt[lrow];
@@ -359,8 +385,7 @@ __device__ __forceinline__ void bwd_dq_body(
       c1_st_x = ns.x; c1_st_y = ns.y; c1_lt_x = nl.x; c1_lt_y = nl.y;
     }
   }
-  set_init(ri_st.x, ri_st.y, c1_st_x, c1_st_y);
-  __syncthreads();
+  if constexpr (!ONE) __syncthreads();
   // Block id of tile t: window blocks by arithmetic, selected blocks by a scalar load from the
   // selection row (uniform address), issued a whole tile before its value is needed.
   auto tile_of = [&](int t) -> int {
@@ -381,7 +406,8 @@ __device__ __forceinline__ void bwd_dq_body(
   const uint16_t *v_lane = V + head;
   ReadOffsets ro = read_offsets(lane);
 
-  auto tile_body = [&](const uint16_t *ks, const uint16_t *vs, int J, bool short_term) __attribute__((always_inline)) {
+  // (refill: called once the tile has been read to registers, ONE only)
+  auto tile_body = [&](const uint16_t *ks, const uint16_t *vs, int J, bool short_term, auto refill) __attribute__((always_inline)) {
     asm volatile("" : "+v"(ro.row[0]), "+v"(ro.row[1]), "+v"(ro.row[2]), "+v"(ro.row[3]), "+v"(ro.tr[0]), "+v"(ro.tr[1]), "+v"(ro.tr8[0]), "+v"(ro.tr8[1]));
     const bool hp = (short_term ? hp_st : hp_lt) != 0;
     // band-masked by the window, unless Eq. 15 shows the whole block (power-of-two block distance)
@@ -394,6 +420,13 @@ __device__ __forceinline__ void bwd_dq_body(
     const bool any = iq >= lo;
 #pragma unroll
     for (int s = 0; s < UNITS; ++s) {
+      bf16x8 kt[2][2];  // K^T operands of the last product
+      auto read_kt = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int mb = 0; mb < 2; ++mb) kt[t][mb] = lds_tr(ks, 2 * (32 * s + 16 * t) * D + ro.tr[mb], 2 * (32 * s + 16 * t) * D + ro.tr8[mb]);
+      };
       f32x16 sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_row(ks, 2 * 32 * s * D + ro.row[0]), qf[0], s_init, 0, 0, 0);
       f32x16 gacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_row(vs, 2 * 32 * s * D + ro.row[0]), gf[0], g_init, 0, 0, 0);
 #pragma unroll
@@ -405,6 +438,11 @@ __device__ __forceinline__ void bwd_dq_body(
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk)
           gacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_row(vs, 2 * 32 * s * D + ro.row[kk]), gl[kk], gacc, 0, 0, 0);
+      }
+      if constexpr (ONE) {
+        read_kt();
+        __builtin_amdgcn_s_waitcnt(kLgkm0);
+        refill();
       }
       if (masked) {
         const int base = J * BLK + 32 * s + 4 * lh;
@@ -444,12 +482,11 @@ __device__ __forceinline__ void bwd_dq_body(
       for (int i = 0; i < 16; ++i) sacc[i] = __builtin_amdgcn_exp2f(sacc[i]) * gacc[i];  // dS
       bf16x8 dsf[2];
       to_operand(sacc, dsf);
+      if constexpr (!ONE) read_kt();
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-          dq[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_tr(ks, 2 * (32 * s + 16 * t) * D + ro.tr[mb], 2 * (32 * s + 16 * t) * D + ro.tr8[mb]), dsf[t],
-                                                           dq[mb], 0, 0, 0);
+        for (int mb = 0; mb < 2; ++mb) dq[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt[t][mb], dsf[t], dq[mb], 0, 0, 0);
       if (hp) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) sacc[i] -= (float)dsf[i >> 3][i & 7];
@@ -457,41 +494,70 @@ __device__ __forceinline__ void bwd_dq_body(
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
-          for (int mb = 0; mb < 2; ++mb)
-            dq[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_tr(ks, 2 * (32 * s + 16 * t) * D + ro.tr[mb], 2 * (32 * s + 16 * t) * D + ro.tr8[mb]), dsf[t],
-                                                             dq[mb], 0, 0, 0);
+          for (int mb = 0; mb < 2; ++mb) dq[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt[t][mb], dsf[t], dq[mb], 0, 0, 0);
       }
     }
   };
 
+  auto to_long_term = [&]() __attribute__((always_inline)) {  // the long-term tiles start: that branch's gradient and constants
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      gf[kk] = gf_next[kk];
+      gl[kk] = gl_next[kk];
+    }
+    set_init(ri_lt.x, ri_lt.y, c1_lt_x, c1_lt_y);
+  };
   int J_cur = list_entry(tile_of(0));
   int J_nxt = list_entry(tile_of(min(1, n_all - 1)));
   sg.stage(k_lane, Ks0, J_cur);
   sg.stage(v_lane, Vs0, J_cur);
-  __syncthreads();
-  auto step = [&](int t, uint16_t *k_fill, uint16_t *v_fill, const uint16_t *k_cur, const uint16_t *v_cur)
-                  __attribute__((always_inline)) {
-    const int J_after = tile_of(min(t + 2, n_all - 1));  // consumed at the end of this step
-    if (t + 1 < n_all) {
-      sg.stage(k_lane, k_fill, J_nxt);
-      sg.stage(v_lane, v_fill, J_nxt);
+  if constexpr (ONE) {
+    __builtin_amdgcn_sched_barrier(0);  // (the first tile's loads stay the older ones: what the loop's waits count on)
+    sg.stage(k_lane, Ks1, J_nxt);
+    sg.stage(v_lane, Vs1, J_nxt);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  scale_frags(p.scale * kLog2e, qf);
+  set_init(ri_st.x, ri_st.y, c1_st_x, c1_st_y);
+  if constexpr (ONE) {
+    int J_2 = list_entry(tile_of(min(2, n_all - 1)));
+    auto step = [&](int t, uint16_t *ks, uint16_t *vs) __attribute__((always_inline)) {
+      const int J_after = tile_of(min(t + 3, n_all - 1));  // consumed at the end of this step
+      if (t == n_st) to_long_term();
+      tile_body(ks, vs, J_cur, t < n_st, [&]() __attribute__((always_inline)) {
+        sg.stage(k_lane, ks, J_2);
+        sg.stage(v_lane, vs, J_2);
+      });
+      J_cur = J_nxt;
+      J_nxt = J_2;
+      J_2 = list_entry(J_after);
+    };
+    int t = 0;
+    for (; t + 1 < n_all; t += 2) {
+      step(t, Ks0, Vs0);
+      step(t + 1, Ks1, Vs1);
     }
-    if (t == n_st) {  // the long-term tiles start: switch to that branch's gradient and constants
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        gf[kk] = gf_next[kk];
-        gl[kk] = gl_next[kk];
-      }
-      set_init(ri_lt.x, ri_lt.y, c1_lt_x, c1_lt_y);
-    }
-    tile_body(k_cur, v_cur, J_cur, t < n_st);
-    J_cur = J_nxt;
-    J_nxt = list_entry(J_after);
+    if (t < n_all) step(t, Ks0, Vs0);
+    __builtin_amdgcn_s_waitcnt(kVm0);  // (the last two refills are not read, but they write LDS)
+  } else {
     __syncthreads();
-  };
-  for (int t = 0; t < n_all; t += 2) {
-    step(t, Ks1, Vs1, Ks0, Vs0);
-    if (t + 1 < n_all) step(t + 1, Ks0, Vs0, Ks1, Vs1);
+    auto step = [&](int t, uint16_t *k_fill, uint16_t *v_fill, const uint16_t *k_cur, const uint16_t *v_cur)
+                    __attribute__((always_inline)) {
+      const int J_after = tile_of(min(t + 2, n_all - 1));  // consumed at the end of this step
+      if (t + 1 < n_all) {
+        sg.stage(k_lane, k_fill, J_nxt);
+        sg.stage(v_lane, v_fill, J_nxt);
+      }
+      if (t == n_st) to_long_term();
+      tile_body(k_cur, v_cur, J_cur, t < n_st, [] {});
+      J_cur = J_nxt;
+      J_nxt = list_entry(J_after);
+      __syncthreads();
+    };
+    for (int t = 0; t < n_all; t += 2) {
+      step(t, Ks1, Vs1, Ks0, Vs0);
+      if (t + 1 < n_all) step(t + 1, Ks0, Vs0, Ks1, Vs1);
+    }
   }
   {  // (every wavefront is past the last barrier of the walk: the staging rows are free)
     const int row0 = I * BLK + 32 * wv;
@@ -520,7 +586,7 @@ __device__ __forceinline__ void bwd_dkv_body(
 {
   // (rc_s: per-row constants of the staged query tile: splits of -lse2 (x, y) and of -c_x (z, w))
   constexpr int UNITS = BLK / 32;
-  constexpr int TILE = BLK * D;
+  constexpr bool ONE = UNITS == 1;  // a workgroup of one wavefront: see REFILL at bwd_both_mfma_kernel
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -545,10 +611,9 @@ __device__ __forceinline__ void bwd_dkv_body(
     zero_rows(dV + head, J * BLK + 32 * wv, 32, p.L, lane);
     return;
   }
-  const float c2 = p.scale * kLog2e;
   bf16x8 kf[4], vf[4];
-  load_frags(K + rowoff, lh, c2, kf);
-  load_frags(V + rowoff, lh, 1.0f, vf);
+  load_frags(K + rowoff, lh, kf);
+  load_frags(V + rowoff, lh, vf);
   const bf16x8 ones = ones3(lh);
 
   // ---- walk: window part I = J..I_hi, then the inverse selection list ----
@@ -603,7 +668,9 @@ __device__ __forceinline__ void bwd_dkv_body(
     return r;
   };
 
-  auto tile_body = [&](const uint16_t *qs, const uint16_t *gsm, int par, int Iq, bool short_term, bool hp)
+  // (rc_of(s): the row constants of this lane's row in unit s; refill: called once the tile has been read to
+  // registers, ONE only)
+  auto tile_body = [&](const uint16_t *qs, const uint16_t *gsm, auto rc_of, int Iq, bool short_term, bool hp, auto refill)
                        __attribute__((always_inline)) {
     // band-masked by the window, unless Eq. 15 shows the whole block (power-of-two block distance)
     const bool windowed = short_term && !(EQ15 && !sub && is_pow2(Iq - J));
@@ -617,13 +684,28 @@ __device__ __forceinline__ void bwd_dkv_body(
     const bool any = key_ok && hi_i >= lo_i;
 #pragma unroll
     for (int s = 0; s < UNITS; ++s) {
-      const uint4 rc = rc_s[par][32 * s + lq];  // this lane's row of the unit
+      const uint4 rc = rc_of(s);
+      bf16x8 gt[2][2], qt[2][2];  // dO_x^T and Q^T operands of the last products
+      auto read_tr = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int mb = 0; mb < 2; ++mb) {
+            gt[t][mb] = lds_tr(gsm, 2 * (32 * s + 16 * t) * D + ro.tr[mb], 2 * (32 * s + 16 * t) * D + ro.tr8[mb]);
+            qt[t][mb] = lds_tr(qs, 2 * (32 * s + 16 * t) * D + ro.tr[mb], 2 * (32 * s + 16 * t) * D + ro.tr8[mb]);
+          }
+      };
       f32x16 sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(split_operand(rc.x, rc.y), ones, zero16, 0, 0, 0);
       f32x16 gacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(split_operand(rc.z, rc.w), ones, zero16, 0, 0, 0);
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
         sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_row(qs, 2 * 32 * s * D + ro.row[kk]), kf[kk], sacc, 0, 0, 0);
         gacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_row(gsm, 2 * 32 * s * D + ro.row[kk]), vf[kk], gacc, 0, 0, 0);
+      }
+      if constexpr (ONE) {
+        read_tr();
+        __builtin_amdgcn_s_waitcnt(kLgkm0);
+        refill();
       }
       if (masked) {
         const int base = Iq * BLK + 32 * s + 4 * lh;
@@ -668,14 +750,13 @@ __device__ __forceinline__ void bwd_dkv_body(
       bf16x8 pf[2], dsf[2];
       to_operand(sacc, pf);
       to_operand(gacc, dsf);
+      if constexpr (!ONE) read_tr();
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb) {
-          dv[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_tr(gsm, 2 * (32 * s + 16 * t) * D + ro.tr[mb], 2 * (32 * s + 16 * t) * D + ro.tr8[mb]), pf[t],
-                                                           dv[mb], 0, 0, 0);
-          dk[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_tr(qs, 2 * (32 * s + 16 * t) * D + ro.tr[mb], 2 * (32 * s + 16 * t) * D + ro.tr8[mb]), dsf[t],
-                                                           dk[mb], 0, 0, 0);
+          dv[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gt[t][mb], pf[t], dv[mb], 0, 0, 0);
+          dk[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qt[t][mb], dsf[t], dk[mb], 0, 0, 0);
         }
       if (hp) {  // rows with few keys: large P and dS, add the rounding residuals as a second bf16 term
 #pragma unroll
@@ -689,52 +770,88 @@ __device__ __forceinline__ void bwd_dkv_body(
         for (int t = 0; t < 2; ++t)
 #pragma unroll
           for (int mb = 0; mb < 2; ++mb) {
-            dv[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_tr(gsm, 2 * (32 * s + 16 * t) * D + ro.tr[mb], 2 * (32 * s + 16 * t) * D + ro.tr8[mb]), pf[t],
-                                                             dv[mb], 0, 0, 0);
-            dk[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_tr(qs, 2 * (32 * s + 16 * t) * D + ro.tr[mb], 2 * (32 * s + 16 * t) * D + ro.tr8[mb]), dsf[t],
-                                                             dk[mb], 0, 0, 0);
+            dv[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gt[t][mb], pf[t], dv[mb], 0, 0, 0);
+            dk[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qt[t][mb], dsf[t], dk[mb], 0, 0, 0);
           }
       }
     }
   };
 
+  // rows that may see fewer than kFewKeys keys: the first valid rows of a window (or a very
+  // short window), or a query block flagged by the inverse list
+  auto few = [&](int ent, bool win) -> bool {
+    return win ? (p.w < kFewKeys || (ent & kInvBlockMask) * BLK - p0 + 1 < kFewKeys) : (ent >> kInvFewShift) != 0;
+  };
   int ent_cur = entry_of(0);
   int ent_nxt = entry_of(min(1, n_all - 1));
-  {
-    const int I0 = ent_cur & kInvBlockMask;
-    const bool win0 = 0 < n_st;
-    sg.stage(q_lane, Qs0, I0);
-    sg.stage(win0 ? gs_lane : gl_lane, Gs0, I0);
-    const uint4 r0 = row_consts(I0, win0);
-    if (tid < BLK) rc_s[0][tid] = r0;
-  }
-  __syncthreads();
-  auto step = [&](int t, uint16_t *q_fill, uint16_t *g_fill, const uint16_t *q_cur, const uint16_t *g_cur,
-                  int par) __attribute__((always_inline)) {
-    uint4 rn = pad_consts;
-    const bool more = t + 1 < n_all;
-    const int ent_after = entry_of(min(t + 2, n_all - 1));  // consumed at the end of this step
-    if (more) {
-      const int In = ent_nxt & kInvBlockMask;
-      const bool win_n = t + 1 < n_st;
-      rn = row_consts(In, win_n);
-      sg.stage(q_lane, q_fill, In);
-      sg.stage(win_n ? gs_lane : gl_lane, g_fill, In);
+  if constexpr (ONE) {
+    // this lane's row constants of block Iq (rows past the end are replaced when they are used)
+    auto request_rc = [&](int Iq, bool win) __attribute__((always_inline)) -> uint4 {
+      return (win ? rowI_st : rowI_lt)[lbase + min(Iq * BLK + lq, p.L - 1)];
+    };
+    auto fill = [&](uint16_t *qs, uint16_t *gsm, int ent, bool win) __attribute__((always_inline)) -> uint4 {
+      const int Iq = ent & kInvBlockMask;
+      sg.stage(q_lane, qs, Iq);
+      sg.stage(win ? gs_lane : gl_lane, gsm, Iq);
+      return request_rc(Iq, win);
+    };
+    uint4 rc0 = fill(Qs0, Gs0, ent_cur, 0 < n_st);
+    __builtin_amdgcn_sched_barrier(0);  // (the first tile's loads stay the older ones: what the loop's waits count on)
+    uint4 rc1 = fill(Qs1, Gs1, ent_nxt, 1 < n_st);
+    __builtin_amdgcn_sched_barrier(0);
+    scale_frags(p.scale * kLog2e, kf);
+    int ent_2 = entry_of(min(2, n_all - 1));
+    auto step = [&](int t, uint16_t *qs, uint16_t *gsm, uint4 &rc) __attribute__((always_inline)) {
+      const int ent_after = entry_of(min(t + 3, n_all - 1));  // consumed at the end of this step
+      const bool win = t < n_st;
+      const int Iq = ent_cur & kInvBlockMask;
+      tile_body(qs, gsm, [&](int) { return Iq * BLK + lq < p.L ? rc : pad_consts; }, Iq, win, few(ent_cur, win),
+                [&]() __attribute__((always_inline)) { rc = fill(qs, gsm, ent_2, t + 2 < n_st); });
+      ent_cur = ent_nxt;
+      ent_nxt = ent_2;
+      ent_2 = ent_after;
+    };
+    int t = 0;
+    for (; t + 1 < n_all; t += 2) {
+      step(t, Qs0, Gs0, rc0);
+      step(t + 1, Qs1, Gs1, rc1);
     }
-    const bool win = t < n_st;
-    const int Iq = ent_cur & kInvBlockMask;
-    // rows that may see fewer than kFewKeys keys: the first valid rows of a window (or a very
-    // short window), or a query block flagged by the inverse list
-    const bool hp = win ? (p.w < kFewKeys || Iq * BLK - p0 + 1 < kFewKeys) : (ent_cur >> kInvFewShift) != 0;
-    tile_body(q_cur, g_cur, par, Iq, win, hp);
-    if (more && tid < BLK) rc_s[par ^ 1][tid] = rn;
-    ent_cur = ent_nxt;
-    ent_nxt = ent_after;
+    if (t < n_all) step(t, Qs0, Gs0, rc0);
+    __builtin_amdgcn_s_waitcnt(kVm0);  // (the last two refills are not read, but they write LDS)
+  } else {
+    {
+      const int I0 = ent_cur & kInvBlockMask;
+      const bool win0 = 0 < n_st;
+      sg.stage(q_lane, Qs0, I0);
+      sg.stage(win0 ? gs_lane : gl_lane, Gs0, I0);
+      const uint4 r0 = row_consts(I0, win0);
+      scale_frags(p.scale * kLog2e, kf);
+      if (tid < BLK) rc_s[0][tid] = r0;
+    }
     __syncthreads();
-  };
-  for (int t = 0; t < n_all; t += 2) {
-    step(t, Qs1, Gs1, Qs0, Gs0, 0);
-    if (t + 1 < n_all) step(t + 1, Qs0, Gs0, Qs1, Gs1, 1);
+    auto step = [&](int t, uint16_t *q_fill, uint16_t *g_fill, const uint16_t *q_cur, const uint16_t *g_cur,
+                    int par) __attribute__((always_inline)) {
+      uint4 rn = pad_consts;
+      const bool more = t + 1 < n_all;
+      const int ent_after = entry_of(min(t + 2, n_all - 1));  // consumed at the end of this step
+      if (more) {
+        const int In = ent_nxt & kInvBlockMask;
+        const bool win_n = t + 1 < n_st;
+        rn = row_consts(In, win_n);
+        sg.stage(q_lane, q_fill, In);
+        sg.stage(win_n ? gs_lane : gl_lane, g_fill, In);
+      }
+      const bool win = t < n_st;
+      tile_body(q_cur, g_cur, [&](int s) { return rc_s[par][32 * s + lq]; }, ent_cur & kInvBlockMask, win, few(ent_cur, win), [] {});
+      if (more && tid < BLK) rc_s[par ^ 1][tid] = rn;
+      ent_cur = ent_nxt;
+      ent_nxt = ent_after;
+      __syncthreads();
+    };
+    for (int t = 0; t < n_all; t += 2) {
+      step(t, Qs1, Gs1, Qs0, Gs0, 0);
+      if (t + 1 < n_all) step(t + 1, Qs0, Gs0, Qs1, Gs1, 1);
+    }
   }
 
   // ---- residual passes over the query blocks with few-key rows ----
@@ -751,6 +868,7 @@ __device__ __forceinline__ void bwd_dkv_body(
       const int r = tid >> 1, hf = tid & 1;
       const int i = Iq * BLK + r;
       const bool in = i < p.L;
+      const uint16_t keep = in ? 0xFFFFu : 0u;
       const size_t ro = head + (size_t)min(i, p.L - 1) * D + 32 * hf;
       const float4 st = rowstat[lbase + min(i, p.L - 1)];
       const float ax = windowed ? 1.0f - st.x : st.x;
@@ -761,13 +879,18 @@ __device__ __forceinline__ void bwd_dkv_body(
       for (int c = 0; c < 4; ++c) {
         const uint4 raw = *reinterpret_cast<const uint4 *>(dO + ro + 8 * c);
         const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+        float gw[8], ox[8];  // (loaded whole: loads under a condition would be waited for one by one)
+        *reinterpret_cast<float4 *>(gw) = *reinterpret_cast<const float4 *>(wrow + 8 * c);
+        *reinterpret_cast<float4 *>(gw + 4) = *reinterpret_cast<const float4 *>(wrow + 8 * c + 4);
+        *reinterpret_cast<float4 *>(ox) = *reinterpret_cast<const float4 *>(orow + 8 * c);
+        *reinterpret_cast<float4 *>(ox + 4) = *reinterpret_cast<const float4 *>(orow + 8 * c + 4);
         uint32_t out[4];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const float g = (e & 1) ? bf_hi(w[e >> 1]) : bf_lo(w[e >> 1]);
-          const float full = fmaf(ax, g, st.y * wrow[8 * c + e]);
-          const uint16_t lo = in ? f32_to_bf16(full - bf16_to_f32(f32_to_bf16(full))) : (uint16_t)0;
-          corr = fmaf(bf16_to_f32(lo), orow[8 * c + e], corr);
+          const float full = fmaf(ax, g, st.y * gw[e]);
+          const uint16_t lo = f32_to_bf16(full - bf16_to_f32(f32_to_bf16(full))) & keep;
+          corr = fmaf(bf16_to_f32(lo), ox[e], corr);
           if (e & 1) out[e >> 1] |= (uint32_t)lo << 16; else out[e >> 1] = lo;
         }
         const int chunk = (4 * hf + c) ^ swz(r);
@@ -781,21 +904,15 @@ __device__ __forceinline__ void bwd_dkv_body(
       }
     }
     __syncthreads();  // (waits for the staged Q rows of every wavefront as well)
-    tile_body(Qs0, Gs0, 0, Iq, windowed, false);
+    tile_body(Qs0, Gs0, [&](int s) { return rc_s[0][32 * s + lq]; }, Iq, windowed, false, [] {});
     __syncthreads();
   };
-  if (p.w < kFewKeys || J * BLK - p0 + 1 < kFewKeys) {  // the window part: a prefix of the walk
 #pragma unroll 1
-    for (int t = 0; t < n_st; ++t) {
-      const int Iq = entry_of(t);
-      if (!(p.w < kFewKeys || Iq * BLK - p0 + 1 < kFewKeys)) break;
-      residual_pass(Iq, true);
-    }
-  }
-#pragma unroll 1
-  for (int e = 0; e < n_lt; ++e) {  // flagged entries of the inverse list
-    const int ent = __builtin_amdgcn_readfirstlane(my_items[e]);
-    if ((ent >> kInvFewShift) != 0) residual_pass(ent & kInvBlockMask, false);
+  for (int t = 0; t < n_all; ++t) {
+    const bool win = t < n_st;
+    const int ent = __builtin_amdgcn_readfirstlane(entry_of(t));
+    if (few(ent, win)) residual_pass(ent & kInvBlockMask, win);
+    else if (win) t = n_st - 1;  // (in the window part such blocks are a prefix)
   }
 
   {  // (every wavefront is past the last barrier of the walk: the staging rows are free)
@@ -845,6 +962,13 @@ __global__ __launch_bounds__(BLK * 2) __attribute__((amdgpu_waves_per_eu(2, 2)))
 // rest the query blocks.  The two kernels need the same workgroup shape, the same two wavefronts per SIMD and
 // nearly the same LDS, so nothing is lost by the union, and the short dQ workgroups fill the slots that the
 // tail of the skewed dK/dV walks leaves idle (and one launch gap goes).
+//
+// REFILL.  At block size 32 a workgroup is one wavefront, its body of 12 or 18 matrix instructions is shorter than a
+// load's latency under load, and LDS holds two tiles for each of the eight wavefronts of a CU.  So a tile is read to
+// registers whole (the transposed operands too), and its buffer is refilled with the tile after next at once: a load
+// has nearly two bodies to arrive.  The loop issues the same loads on every path and has one exit (an odd last tile is
+// a step of its own), so that the compiler's waits before the LDS reads count exactly past the younger loads.
+// B=128 H=4 L=1024 k=8 w=64, lengths U[100,1024]: 230 -> 202 us; B=32 H=8 L=1997, all of Eq. 15: 267 -> 239 us.
 template <int BLK, bool EQ15, bool SUB>
 __global__ __launch_bounds__(BLK * 2) __attribute__((amdgpu_waves_per_eu(2, 2))) void bwd_both_mfma_kernel(
     BWD_DQ_PARAMS, const int *__restrict__ offs, const int *__restrict__ items, uint16_t *__restrict__ dK,
