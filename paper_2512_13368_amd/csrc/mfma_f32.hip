@@ -98,10 +98,11 @@ __device__ __forceinline__ float recip(float x)
   const float r = __builtin_amdgcn_rcpf(x);
   return fmaf(r, fmaf(-x, r, 1.0f), r);
 }
+// (a comparison and not fminf, which would turn a NaN into 126 and the gate into a finite number)
 __device__ __forceinline__ float sigmoid(float z)
 {
-  const float e = __builtin_amdgcn_exp2f(fminf(-z * kLog2eF, 126.0f));
-  return recip(1.0f + e);
+  const float x = -z * kLog2eF;
+  return recip(1.0f + __builtin_amdgcn_exp2f(x > 126.0f ? 126.0f : x));
 }
 
 // sum and maximum over the four lane groups of a column (rows 0/1, 2/3 then halves of the wavefront swapped in
