@@ -44,7 +44,13 @@
  *     isolated near-zero gradient elements can leave the bound by a small factor.
  *   - Errors: 0 on success, a negative BLOSSOM_ERR_* otherwise.  All argument
  *     checks run before the first HIP call, so they work on a host with no GPU.
- *     No global state; thread-safe.  Inputs are assumed finite.
+ *     No global state; thread-safe.
+ *   - Inputs are assumed finite at the valid positions.  What else a caller hands over comes out
+ *     again: a NaN at a valid position makes the outputs and gradients that depend on it NaN.  It
+ *     reaches no others, and padding positions may hold anything, except in the attention kernels
+ *     for bf16 with d = 64 and block 32 or 64 in a causal form: they multiply whole blocks, so
+ *     there the padding of a partly valid block has to be finite too, and a value that is not
+ *     finite may reach every row of its block.
  */
 #ifndef BLOSSOM_H_
 #define BLOSSOM_H_

@@ -31,6 +31,11 @@
 // in fp32.  Beyond that (or if an output left fp32's range) the walk is repeated with the two row maxima,
 // found by a walk of their own, as references.
 //
+// VALUES THAT ARE NOT FINITE.  A walk multiplies whole tiles, so a masked element adds zero times whatever the tile holds: a NaN
+// or an infinity, in a row of the padding too, would reach every row of its tile.  Such a result is not finite itself,
+// which a few instructions at the end of a walk tell; the walk is then repeated with those elements taken out of the
+// products, and the rows that do see one of them get NaN.  (dQ of a head in LDS: taken out as the head is staged.)
+//
 // The dQ kernel also does the per-row gate pass (alpha, dz, D_x and the gate-weight gradients): a wavefront has
 // its query rows' dO at hand.  It leaves the row constants and the long-term tile words of every query tile for the
 // dK/dV kernel, which finds the query tiles of a key tile by a ballot over those words (no inverse lists).
@@ -143,6 +148,41 @@ __device__ __forceinline__ float max_row(float x)
   x = fmaxf(x, row_ror<4>(x));
   x = fmaxf(x, row_ror<2>(x));
   return fmaxf(x, row_ror<1>(x));
+}
+
+constexpr float kNaN = __builtin_nanf("");
+__device__ __forceinline__ bool finite(float x) { return fabsf(x) <= 3.402823466e38f; }
+// Takes the elements that are not finite out of a tile's operand (element r of lane (q, g): row 4g + r).  lost[r]: NaN where that
+// row held one, to be added to its coefficient in the columns that see the row, else 0.
+template <int N>
+__device__ __forceinline__ void take_out(float (&x)[N][4], int g, float (&lost)[4])
+{
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    bool here = false;
+#pragma unroll
+    for (int mb = 0; mb < N; ++mb) {
+      here |= !finite(x[mb][r]);
+      x[mb][r] = finite(x[mb][r]) ? x[mb][r] : 0.0f;
+    }
+    lost[r] = ((__ballot(here) >> (16 * g)) & 0xFFFFull) != 0ull ? kNaN : 0.0f;
+  }
+}
+template <int N>
+__device__ __forceinline__ float abs_sum(const f32x4 (&a)[N])
+{
+  float x = 0.0f;
+#pragma unroll
+  for (int mb = 0; mb < N; ++mb)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x += fabsf(a[mb][r]);
+  return x;
+}
+template <int N>
+__device__ __forceinline__ void clear(f32x4 (&a)[N])
+{
+#pragma unroll
+  for (int mb = 0; mb < N; ++mb) a[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
 // lane (col, g) holds channels 16*mb + 4g + r of one row in a[mb][r]: stores those below D
@@ -342,17 +382,27 @@ __device__ __forceinline__ void store_lds(float *p, const float (&o)[N])
     for (int i = 0; i < N; i += 4) *reinterpret_cast<float4 *>(p + i) = make_float4(o[i], o[i + 1], o[i + 2], o[i + 3]);
   }
 }
-// two heads' rows from tile T0 on into LDS (rows past the end are zeros)
-template <typename T, int D>
-__device__ __forceinline__ void stage_pair(const T *A, const T *B, float *a_lds, float *b_lds, int L, int T0, int NT, int lane, int wv, int W)
+// two heads' rows from tile T0 on into LDS; rows before p0 (the padding) and past the end are zeros.  CLEAN: elements that are
+// not finite become zeros too.
+template <typename T, int D, bool CLEAN>
+__device__ __forceinline__ void stage_pair(const T *A, const T *B, float *a_lds, float *b_lds, int L, int T0, int NT, int p0, int lane, int wv,
+                                           int W)
 {
   constexpr int CPL = Geo<D>::CPL;
   const int q = lane & 15, g = lane >> 4;
   const Rows<T, D> Ar(A, L, q, g), Br(B, L, q, g);
   for (int t = T0 + wv; t < NT; t += W) {
     float x[CPL], y[CPL];
-    Ar.row(t, x);
-    Br.row(t, y);
+    const unsigned off = t * kTile + q >= p0 ? Ar.row_off + (unsigned)t * Rows<T, D>::TB : kNowhere;
+    load_n<T>(Ar.s, off, x);
+    load_n<T>(Br.s, off, y);
+    if constexpr (CLEAN) {
+#pragma unroll
+      for (int i = 0; i < CPL; ++i) {
+        x[i] = finite(x[i]) ? x[i] : 0.0f;
+        y[i] = finite(y[i]) ? y[i] : 0.0f;
+      }
+    }
     const int at = (t * kTile + q) * kLdsRow<D> + CPL * g;
     store_lds<CPL>(a_lds + at, x);
     store_lds<CPL>(b_lds + at, y);
@@ -537,7 +587,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
   const T *Kh = K + (size_t)kvh * p.L * D, *Vh = V + (size_t)kvh * p.L * D;
   const int pitch = RES ? NT * kTile * kLdsRow<D> : 0;  // floats of a staged tensor
   if constexpr (RES) {
-    stage_pair<T, D>(Kh, Vh, small_lds, small_lds + pitch, p.L, T0, NT, lane, wv, W);
+    stage_pair<T, D, false>(Kh, Vh, small_lds, small_lds + pitch, p.L, T0, NT, p0, lane, wv, W);
     __syncthreads();
   }
   using TileRows = std::conditional_t<RES, LdsRows<D>, Rows<T, D>>;
@@ -700,13 +750,9 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     };
     if (p.sblk <= 1) walk(std::true_type{});
     else walk(std::false_type{});
-    float size = 0.0f;
-#pragma unroll
-    for (int mb = 0; mb < NMB; ++mb)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) size += fabsf(a_lt[mb][r]) + fabsf(a_st[mb][r]);
-    if (!__all(s_max <= kSmallLogit && size < 1.0e37f)) {
-      // large logits, or values near the end of fp32's range: the row maxima of both branches, then the walk against them
+    if (__builtin_expect(!__all(s_max <= kSmallLogit && abs_sum(a_lt) + abs_sum(a_st) < 1.0e37f), 0)) {
+      // large logits, or values near the end of fp32's range or beyond: the row maxima of both branches, then the walk
+      // against them
       float x_lt = kNegInfF, x_st = kNegInfF;
       auto each = [&](auto f) __attribute__((always_inline)) {
         for (int w = T0 >> 5; w <= J_hi >> 5; ++w) {
@@ -730,31 +776,37 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
       ref_lt = x_lt == kNegInfF ? 0.0f : x_lt;
       ref_st = x_st == kNegInfF ? 0.0f : x_st;
       l_lt = l_st = 0.0f;
-#pragma unroll
-      for (int mb = 0; mb < NMB; ++mb) {
-        a_lt[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        a_st[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-      }
+      clear(a_lt);
+      clear(a_st);
       each([&](int J) {
         Kr.row(J, kf);
         Vr.col(J, vf);
         const f32x4 s = logits();
+        float lost[4];
+        take_out(vf, g, lost);
         bool v_lt[4], v_st[4];
         see(std::false_type{}, J, v_lt, v_st);
         float el[4], es[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          el[r] = v_lt[r] ? __builtin_amdgcn_exp2f(s[r] - ref_lt) : 0.0f;
-          es[r] = v_st[r] ? __builtin_amdgcn_exp2f(s[r] - ref_st) : 0.0f;
+          el[r] = v_lt[r] ? __builtin_amdgcn_exp2f(s[r] - ref_lt) + lost[r] : 0.0f;
+          es[r] = v_st[r] ? __builtin_amdgcn_exp2f(s[r] - ref_st) + lost[r] : 0.0f;
         }
         add_lt(el);
         add_st(es);
       });
+#pragma unroll
+      for (int mb = 0; mb < NMB; ++mb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {  // (a row of the padding may have seen some of the padding)
+          a_lt[mb][r] = active ? a_lt[mb][r] : 0.0f;
+          a_st[mb][r] = active ? a_st[mb][r] : 0.0f;
+        }
     }
     // closes a branch: normalised output (zero for rows that take no part), returns the lse
     auto finish = [&](f32x4 (&acc)[NMB], float l, float m) -> float {
       const float lt = sum_g(l);
-      const bool ok = active && lt > 0.0f;
+      const bool ok = active && !(lt <= 0.0f);  // (a NaN stays one)
       const float inv = ok ? recip(lt) : 0.0f;
 #pragma unroll
       for (int mb = 0; mb < NMB; ++mb)
@@ -880,9 +932,10 @@ struct GateSums {
 };
 
 // Query tile I.  sel_head: the head's selection rows (per query block, or per position of its group).  sink() takes the row
-// constants, the selection and the row's Q and dO when do_rows asks for them.
-template <typename T, int D, int BK, bool PERPOS, typename TileRows, typename Sink>
-__device__ __forceinline__ void query_tile(const KParams &p, int I, int T0, int NT, int p0, int lane, const QueryHead &in,
+// constants, the selection and the row's Q and dO when do_rows asks for them.  Returns whether every dQ of the tile is finite.
+// CAREFUL: tile by tile, with the elements that are not finite taken out.
+template <typename T, int D, int BK, bool PERPOS, bool CAREFUL, typename TileRows, typename Sink>
+__device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int NT, int p0, int lane, const QueryHead &in,
                                            const TileRows &Kr, const TileRows &Vr, const int *sel_head, unsigned *my_lds,
                                            GateSums<D> &gate, bool do_rows, bool do_dq, T *dQ_head, Sink &&sink)
 {
@@ -921,7 +974,7 @@ __device__ __forceinline__ void query_tile(const KParams &p, int I, int T0, int 
     }
     gate.gb += dz;
   }
-  if (!do_dq) return;
+  if (!do_dq) return true;
 
 #pragma unroll
   for (int i = 0; i < CPL; ++i) {
@@ -930,37 +983,51 @@ __device__ __forceinline__ void query_tile(const KParams &p, int I, int T0, int 
     os[i] = fmaf(1.0f - al, gr[i], dz * gate.ws[i]);  // dO_st
   }
   f32x4 dq[NMB];
-#pragma unroll
-  for (int mb = 0; mb < NMB; ++mb) dq[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  clear(dq);
   const int kid_q = mask_block(p, iq);
   const int J_hi = p.bidir ? NT - 1 : I;
   Walk wk;
   const int dr = (q >> 2) == g ? (q & 3) : 4;
   float kf[CPL], vf[CPL], kc[NMB][4];
-  auto body = [&](auto kind, auto unit, unsigned &mask) __attribute__((always_inline)) {
-    constexpr int KIND = decltype(kind)::value;
-    constexpr bool LT = KIND <= 1, ST = KIND != 1;
-    const int t = wk.base + __builtin_ctz(mask);
-    mask &= mask - 1;
-    const int t_next = wk.peek();
-    f32x4 s = {0.f, 0.f, 0.f, 0.f}, g_lt = s, g_st = s;
+  auto products = [&](auto lt, auto st, f32x4 &s, f32x4 &g_lt, f32x4 &g_st) __attribute__((always_inline)) {
+    s = g_lt = g_st = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int c = 0; c < CPL; ++c) {
       s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c], qf[c], s, 0, 0, 0);
-      if constexpr (LT) g_lt = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[c], ol[c], g_lt, 0, 0, 0);
-      if constexpr (ST) g_st = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[c], os[c], g_st, 0, 0, 0);
+      if constexpr (decltype(lt)::value) g_lt = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[c], ol[c], g_lt, 0, 0, 0);
+      if constexpr (decltype(st)::value) g_st = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[c], os[c], g_st, 0, 0, 0);
     }
+  };
+  // did the lane's row select the tile, and is the key one that the causal and validity tests let through?
+  auto selected = [&](int t) __attribute__((always_inline)) -> bool {
+    bool x = (wk.lt >> (t & 31)) & 1u;
+    if (PERPOS || BK < kTile) x &= ls.sees(q, t * kTile + 4 * g);
+    return x;
+  };
+  const unsigned span = (unsigned)((p.bidir ? p.L - 1 : iq) - p0);
+  auto seen = [&](int key) __attribute__((always_inline)) -> bool { return (unsigned)(key - p0) <= span; };
+  auto add = [&](const float (&ds)[4]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int mb = 0; mb < NMB; ++mb) dq[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kc[mb][r], ds[r], dq[mb], 0, 0, 0);
+  };
+  auto body = [&](auto kind, auto unit, unsigned &mask) __attribute__((always_inline)) {
+    constexpr int KIND = decltype(kind)::value;
+    const int t = wk.base + __builtin_ctz(mask);
+    mask &= mask - 1;
+    const int t_next = wk.peek();
+    f32x4 s, g_lt, g_st;
+    products(std::bool_constant<KIND <= 1>{}, std::bool_constant<KIND != 1>{}, s, g_lt, g_st);
     Kr.row(t_next, kf);
     Vr.row(t_next, vf);
     const int key0 = t * kTile + 4 * g;
     float ds[4];
     if constexpr (KIND == 0) {
-      const unsigned span = (unsigned)((p.bidir ? p.L - 1 : iq) - p0);
-      bool s_lt = (wk.lt >> (t & 31)) & 1u;
-      if (PERPOS || BK < kTile) s_lt &= ls.sees(q, key0);
+      const bool s_lt = selected(t);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const bool ok = (unsigned)(key0 + r - p0) <= span;
+        const bool ok = seen(key0 + r);
         const bool v_st = ok & st_sees<decltype(unit)::value>(p, iq, key0 + r, kid_q, mask_block(p, key0, r), key0 + r >= p.last_lo);
         const float e = __builtin_amdgcn_exp2f(s[r] - l2_lt), f = __builtin_amdgcn_exp2f(s[r] - l2_st);
         ds[r] = (ok & s_lt ? e : 0.0f) * (g_lt[r] - D_lt);
@@ -987,19 +1054,19 @@ __device__ __forceinline__ void query_tile(const KParams &p, int I, int T0, int 
       for (int r = 0; r < 4; ++r) ds[r] = dr == r ? x : 0.0f;
     }
     if constexpr (TileRows::kNear) Kr.col(t, kc);
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int mb = 0; mb < NMB; ++mb) dq[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kc[mb][r], ds[r], dq[mb], 0, 0, 0);
+    add(ds);
     if constexpr (!TileRows::kNear) Kr.col(t_next, kc);
+  };
+  auto word = [&](int w) __attribute__((always_inline)) {
+    unsigned dia;
+    const unsigned st = st_word<false>(p, I, w, T0, J_hi, lane, dia);
+    const unsigned edge =
+        word_range(w, T0, T0) | word_range(w, I, I) | word_range(w, NT - 1, NT - 1) | word_range(w, p.last_lo / kTile, NT - 1);
+    wk.start(w, ls.word(w), st, edge, dia);
   };
   auto walk = [&](auto unit) __attribute__((always_inline)) {
     for (int w = T0 >> 5; w <= J_hi >> 5; ++w) {
-      unsigned dia;
-      const unsigned st = st_word<false>(p, I, w, T0, J_hi, lane, dia);
-      const unsigned edge =
-          word_range(w, T0, T0) | word_range(w, I, I) | word_range(w, NT - 1, NT - 1) | word_range(w, p.last_lo / kTile, NT - 1);
-      wk.start(w, ls.word(w), st, edge, dia);
+      word(w);
       if (!wk.any()) continue;
       const int t = wk.peek();
       Kr.row(t, kf);
@@ -1011,16 +1078,45 @@ __device__ __forceinline__ void query_tile(const KParams &p, int I, int T0, int 
       while (wk.m3) body(std::integral_constant<int, 3>{}, unit, wk.m3);
     }
   };
-  if (p.sblk <= 1) walk(std::true_type{});
-  else walk(std::false_type{});
+  if constexpr (!CAREFUL) {
+    if (p.sblk <= 1) walk(std::true_type{});
+    else walk(std::false_type{});
+  } else {
+    for (int w = T0 >> 5; w <= J_hi >> 5; ++w) {
+      word(w);
+      for (unsigned m = wk.m0 | wk.m1 | wk.m2 | wk.m3; m; m &= m - 1) {
+        const int t = wk.base + __builtin_ctz(m);
+        Kr.row(t, kf);
+        Vr.row(t, vf);
+        Kr.col(t, kc);
+        f32x4 s, g_lt, g_st;
+        products(std::true_type{}, std::true_type{}, s, g_lt, g_st);
+        float ds[4], lost[4];
+        take_out(kc, g, lost);
+        const bool s_lt = selected(t);
+        const int key0 = t * kTile + 4 * g;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const bool ok = seen(key0 + r);
+          const bool v_st = ok & st_sees<false>(p, iq, key0 + r, kid_q, mask_block(p, key0, r), key0 + r >= p.last_lo);
+          const float e = __builtin_amdgcn_exp2f(s[r] - l2_lt), f = __builtin_amdgcn_exp2f(s[r] - l2_st);
+          ds[r] = ok & s_lt ? fmaf(e, g_lt[r] - D_lt, lost[r]) : 0.0f;
+          ds[r] += v_st ? fmaf(f, g_st[r] - D_st, lost[r]) : 0.0f;
+        }
+        add(ds);
+      }
+    }
+  }
   const int el = fresh_lane(), ei = I * kTile + (el & 15);
   if (ei < p.L) store_grad_row<T, D>(dQ_head + (size_t)ei * D, dq, p.scale, ei >= p0, p, true, ei, el >> 4);
+  return __all((ei < p0) | (ei >= p.L) | finite(abs_sum(dq)));
 }
 
-// Key tile J; kf, vf: this lane's channels of its key and value row (zeros where the row takes no part).  The hpg query heads that
-// read the rows add into the same gradients.  src gives their Q and dO rows, row constants, tile words and selection bits.
-template <typename T, int D, int BK, bool PERPOS, typename Src>
-__device__ __forceinline__ void key_tile(const KParams &p, int J, int T0, int NT, int p0, int lane, float (&kf)[Geo<D>::CPL],
+// Key tile J; kf, vf: this lane's channels of its key and value row (of the padding too, in the first tile with a valid
+// row: a lane keeps to its own column, and those of the padding are stored as zeros).  The hpg query heads that read the
+// rows add into the same gradients.  Returns whether all of them are finite; CAREFUL as above.  src gives their Q and dO rows, row constants, tile words and selection bits.
+template <typename T, int D, int BK, bool PERPOS, bool CAREFUL, typename Src>
+__device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT, int p0, int lane, float (&kf)[Geo<D>::CPL],
                                          const float (&vf)[Geo<D>::CPL], int hpg, const Src &src, T *dK_head, T *dV_head)
 {
   constexpr int CPL = Geo<D>::CPL, NMB = Geo<D>::NMB;
@@ -1029,11 +1125,8 @@ __device__ __forceinline__ void key_tile(const KParams &p, int J, int T0, int NT
   const float c2 = p.scale * kLog2eF;
   const int j = J * kTile + q;
   f32x4 dk[NMB], dv[NMB];
-#pragma unroll
-  for (int mb = 0; mb < NMB; ++mb) {
-    dk[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    dv[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+  clear(dk);
+  clear(dv);
 #pragma unroll
   for (int i = 0; i < CPL; ++i) kf[i] *= c2;
   const int kid_k = mask_block(p, j);
@@ -1069,6 +1162,35 @@ __device__ __forceinline__ void key_tile(const KParams &p, int J, int T0, int NT
       get(4, l_lt);
       get(5, l_st);
     };
+    auto products = [&](f32x4 &s, f32x4 &gv) __attribute__((always_inline)) {
+      s = gv = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < CPL; ++c) {
+        s = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[c], kf[c], s, 0, 0, 0);
+        gv = __builtin_amdgcn_mfma_f32_16x16x4f32(ga[c], vf[c], gv, 0, 0, 0);
+      }
+    };
+    // bit 0 of w4[r]: row r of this lane's four of tile t selected this lane's key block
+    auto selected = [&](int t, unsigned (&w4)[4]) __attribute__((always_inline)) {
+      if constexpr (PERPOS) {
+        const unsigned *sb = src.bits + (t * kTile + 4 * g) * 2 + (Jb >> 5);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) w4[r] = sb[2 * r] >> (Jb & 31);
+      } else if constexpr (BK < kTile) {
+        const unsigned x = src.bits[(t * 2 + (g >> 1)) * NWb + min(Jb >> 5, NWb - 1)] >> (Jb & 31);
+        w4[0] = w4[1] = w4[2] = w4[3] = x;
+      }
+    };
+    // dV^T += dO^T (a P), dK^T += Q^T dS
+    auto add = [&](const float (&pc)[4], const float (&ds)[4]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int mb = 0; mb < NMB; ++mb) {
+          dv[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(gc[mb][r], pc[r], dv[mb], 0, 0, 0);
+          dk[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(qc[mb][r], ds[r], dk[mb], 0, 0, 0);
+        }
+    };
     auto body = [&](auto kind, auto unit, unsigned &mask) __attribute__((always_inline)) {
       constexpr int KIND = decltype(kind)::value;
       constexpr bool LT = KIND <= 1, ST = KIND != 1;
@@ -1076,25 +1198,14 @@ __device__ __forceinline__ void key_tile(const KParams &p, int J, int T0, int NT
       mask &= mask - 1;
       const int t_next = wk.peek();
       if constexpr (near) consts(t);
-      f32x4 s = {0.f, 0.f, 0.f, 0.f}, gv = s;
-#pragma unroll
-      for (int c = 0; c < CPL; ++c) {
-        s = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[c], kf[c], s, 0, 0, 0);
-        gv = __builtin_amdgcn_mfma_f32_16x16x4f32(ga[c], vf[c], gv, 0, 0, 0);
-      }
+      f32x4 s, gv;
+      products(s, gv);
       Qr.row(t_next, qa);
       Gr.row(t_next, ga);
       const int i0 = t * kTile + 4 * g;  // this lane's rows i0 .. i0+3
       float pc[4], ds[4];
-      unsigned w4[4] = {1u, 1u, 1u, 1u};  // bit 0: the row selected this lane's key block
-      if constexpr (LT && PERPOS) {
-        const unsigned *sb = src.bits + i0 * 2 + (Jb >> 5);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) w4[r] = sb[2 * r] >> (Jb & 31);
-      } else if constexpr (LT && BK < kTile) {
-        const unsigned x = src.bits[(t * 2 + (g >> 1)) * NWb + min(Jb >> 5, NWb - 1)] >> (Jb & 31);
-        w4[0] = w4[1] = w4[2] = w4[3] = x;
-      }
+      unsigned w4[4] = {1u, 1u, 1u, 1u};
+      if constexpr (LT) selected(t, w4);
       if constexpr (KIND != 3) {
         const bool in_lt = KIND != 0 || ((wk.lt >> (t & 31)) & 1u) != 0u;
 #pragma unroll
@@ -1139,27 +1250,23 @@ __device__ __forceinline__ void key_tile(const KParams &p, int J, int T0, int NT
         Qr.col(t, qc);
         Gr.col(t, gc);
       }
-      // dV^T += dO^T (a P), dK^T += Q^T dS
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int mb = 0; mb < NMB; ++mb) {
-          dv[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(gc[mb][r], pc[r], dv[mb], 0, 0, 0);
-          dk[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(qc[mb][r], ds[r], dk[mb], 0, 0, 0);
-        }
+      add(pc, ds);
       if constexpr (!near) {
         Qr.col(t_next, qc);
         Gr.col(t_next, gc);
       }
     };
+    auto word = [&](int w) __attribute__((always_inline)) {
+      const int I = w * 32 + (lane & 31);
+      const unsigned tw = src.tile_word(min(max(I, T0), NT - 1), J >> 5);
+      const unsigned lt = (unsigned)__ballot((lane < 32) & ((tw >> (J & 31)) & 1u)) & word_range(w, I_lo, NT - 1);
+      unsigned dia;
+      const unsigned st = st_word<true>(p, J, w, I_lo, NT - 1, lane, dia);
+      wk.start(w, lt, st, last_tile ? 0xFFFFFFFFu : word_range(w, J, J), dia);
+    };
     auto walk = [&](auto unit) __attribute__((always_inline)) {
       for (int w = I_lo >> 5; w <= (NT - 1) >> 5; ++w) {
-        const int I = w * 32 + (lane & 31);
-        const unsigned tw = src.tile_word(min(max(I, T0), NT - 1), J >> 5);
-        const unsigned lt = (unsigned)__ballot((lane < 32) & ((tw >> (J & 31)) & 1u)) & word_range(w, I_lo, NT - 1);
-        unsigned dia;
-        const unsigned st = st_word<true>(p, J, w, I_lo, NT - 1, lane, dia);
-        wk.start(w, lt, st, last_tile ? 0xFFFFFFFFu : word_range(w, J, J), dia);
+        word(w);
         if (!wk.any()) continue;
         const int t = wk.peek();
         Qr.row(t, qa);
@@ -1175,7 +1282,46 @@ __device__ __forceinline__ void key_tile(const KParams &p, int J, int T0, int NT
         while (wk.m3) body(std::integral_constant<int, 3>{}, unit, wk.m3);
       }
     };
-    if (p.sblk <= 1) walk(std::true_type{});
+    auto walk_carefully = [&]() __attribute__((always_inline)) {
+      for (int w = I_lo >> 5; w <= (NT - 1) >> 5; ++w) {
+        word(w);
+        for (unsigned m = wk.m0 | wk.m1 | wk.m2 | wk.m3; m; m &= m - 1) {
+          const int t = wk.base + __builtin_ctz(m);
+          consts(t);
+          Qr.row(t, qa);
+          Gr.row(t, ga);
+          Qr.col(t, qc);
+          Gr.col(t, gc);
+          f32x4 s, gv;
+          products(s, gv);
+          unsigned w4[4] = {1u, 1u, 1u, 1u};
+          selected(t, w4);
+          float lost_q[4], lost_g[4];
+          take_out(qc, g, lost_q);
+          take_out(gc, g, lost_g);
+          const bool in_lt = (wk.lt >> (t & 31)) & 1u;
+          float pc[4], ds[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int i = t * kTile + 4 * g + r;
+            const bool ok = (i >= p0) & (i < p.L) & ((i >= j) | (p.bidir != 0));
+            const bool v_lt = ok & in_lt & ((w4[r] & 1u) != 0u);
+            const bool v_st = ok & st_sees<false>(p, i, j, mask_block(p, i), kid_k, last_k);
+            const float e = __builtin_amdgcn_exp2f(s[r] - l_lt[r]), f = __builtin_amdgcn_exp2f(s[r] - l_st[r]);
+            const float as = 1.0f - al[r];
+            pc[r] = v_lt ? fmaf(al[r], e, lost_g[r]) : 0.0f;
+            pc[r] += v_st ? fmaf(as, f, lost_g[r]) : 0.0f;
+            ds[r] = v_lt ? fmaf(e, fmaf(al[r], gv[r], fmaf(dz[r], wv_lt, -D_lt[r])), lost_q[r]) : 0.0f;
+            ds[r] += v_st ? fmaf(f, fmaf(as, gv[r], fmaf(dz[r], wv_st, -D_st[r])), lost_q[r]) : 0.0f;
+            t_lt += v_lt ? dz[r] * e : 0.0f;
+            t_st += v_st ? dz[r] * f : 0.0f;
+          }
+          add(pc, ds);
+        }
+      }
+    };
+    if constexpr (CAREFUL) walk_carefully();
+    else if (p.sblk <= 1) walk(std::true_type{});
     else walk(std::false_type{});
     // the gate part of dV: sum_i dz_i P_ij times the gate row of the branch
     t_lt = sum_g(t_lt);
@@ -1195,6 +1341,20 @@ __device__ __forceinline__ void key_tile(const KParams &p, int J, int T0, int NT
     store_grad_row<T, D>(dK_head + (size_t)ej * D, dk, p.scale, ej >= p0, p, true, ej, el >> 4);
     store_grad_row<T, D>(dV_head + (size_t)ej * D, dv, 1.0f, ej >= p0, p, false, ej, el >> 4);
   }
+  return __all((ej < p0) | (ej >= p.L) | finite(abs_sum(dk) + abs_sum(dv)));
+}
+
+// A wavefront's query tiles again, for one of which dQ was not finite.  Out of the loop over the tiles and with everything read
+// anew: beside the walk this code took registers from it (a training step at B=32 H=8 L=2000 d=8 375 us, 358 like this).
+template <typename T, int D, int BK, bool PERPOS>
+__device__ __forceinline__ void query_tiles_carefully(const KParams &p, int first, int step, int T0, int NT, int p0, int lane,
+                                                      const QueryHead &in, const Rows<T, D> &Kr, const Rows<T, D> &Vr, const int *sel_head,
+                                                      unsigned *my_lds, const float *gate_w, const float *gate_b, int h, T *dQ_head)
+{
+  GateSums<D> gate(gate_w, gate_b, h, lane >> 4);
+  for (int u = first; u < NT - T0; u += step)
+    query_tile<T, D, BK, PERPOS, true>(p, NT - 1 - u, T0, NT, p0, lane, in, Kr, Vr, sel_head, my_lds, gate, false, true, dQ_head,
+                                       [](auto &&...) {});
 }
 
 }  // namespace
@@ -1207,8 +1367,10 @@ __device__ __forceinline__ void key_tile(const KParams &p, int J, int T0, int NT
 // selection bits per query block (block size 8) or per position.
 // stages: kBwdStageGate writes those and the partial gate gradients, kBwdStageDQ writes dQ (the row constants are
 // formed in either case).
+// (Wavefronts per SIMD, here and in the dK/dV kernel: those that the walk's registers allow, which the compiler would exceed for
+// the repeated walk.)
 template <typename T, int D, int BK, bool PERPOS>
-__global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(D == 32 ? 4 : 5))) void bwd_dq_small_kernel(
+__global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(D == 32 ? 4 : D == 16 ? 5 : 6))) void bwd_dq_small_kernel(
     const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V, const int *__restrict__ valid_len,
     const int *__restrict__ sel, const float *__restrict__ gate_w, const float *__restrict__ gate_b,
     const float *__restrict__ o_lt, const float *__restrict__ o_st, const float *__restrict__ lse_lt,
@@ -1248,20 +1410,24 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
       for (int i = el; i < 2 * ls.NWb; i += 64) ws.sel_bits[((size_t)kvh * NT + I) * 2 * ls.NWb + i] = ls.bits[i];
     }
   };
+  const int *sel_head = sel + (size_t)kvh * (PERPOS ? p.L : p.NB) * p.k;
+  bool good = true;
   for (int u = part * W + wv; u < NT; u += parts * W) {
     const int I = NT - 1 - u;
     if (I < T0 || p0 >= p.L) {  // no valid query
       if (do_dq) zero_fill(dQ_head + I * kTile * D, min(kTile, p.L - I * kTile) * D, fresh_lane());
       continue;
     }
-    query_tile<T, D, BK, PERPOS>(p, I, T0, NT, p0, lane, in, Kr, Vr, sel + (size_t)kvh * (PERPOS ? p.L : p.NB) * p.k, my_lds, gate,
-                                 do_rows, do_dq, dQ_head, sink);
+    good &= query_tile<T, D, BK, PERPOS, false>(p, I, T0, NT, p0, lane, in, Kr, Vr, sel_head, my_lds, gate, do_rows, do_dq, dQ_head, sink);
   }
   if (do_rows) gate.finish(red, ws.partial + ((size_t)bh * parts + part) * GW, lane, wv, W);
+  if (__builtin_expect(!good, 0))
+    query_tiles_carefully<T, D, BK, PERPOS>(p, part * W + wv, parts * W, T0, NT, p0, lane, in, Kr, Vr, sel_head, my_lds, gate_w, gate_b,
+                                            bh % p.H, dQ_head);
 }
 
 template <typename T, int D, int BK, bool PERPOS>
-__global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(D == 32 ? 3 : 4))) void bwd_dkv_small_kernel(
+__global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(D == 32 ? 3 : D == 8 && BK == 16 && !PERPOS ? 5 : 4))) void bwd_dkv_small_kernel(
     const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V, const int *__restrict__ valid_len,
     const float *__restrict__ gate_w, const T *__restrict__ dO, SmallWs ws, T *__restrict__ dK, T *__restrict__ dV, int hpg, int parts,
     KParams p)
@@ -1297,6 +1463,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     }
   } src = {Q, dO, ws.rowc, gate_w, ws.sel_bits + (size_t)bg * (PERPOS ? NT * kTile * 2 : NT * 2 * NWb),
            Slice(ws.tile_words + (size_t)bg * NT * NWt, (size_t)NT * NWt * 4), bg * hpg, p.H, p.L, NT, NWt, q, g};
+  bool good = true;
   for (int J = part * W + wv; J < NT; J += parts * W) {
     if (J < T0 || p0 >= p.L) {  // no valid key
       const int cnt = min(kTile, p.L - J * kTile) * D, el = fresh_lane();
@@ -1307,8 +1474,16 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     float kf[CPL], vf[CPL];
     Kr.row(J, kf);
     Vr.row(J, vf);
-    key_tile<T, D, BK, PERPOS>(p, J, T0, NT, p0, lane, kf, vf, hpg, src, dK + head_kv, dV + head_kv);
+    good &= key_tile<T, D, BK, PERPOS, false>(p, J, T0, NT, p0, lane, kf, vf, hpg, src, dK + head_kv, dV + head_kv);
   }
+  if (__builtin_expect(!good, 0))
+    for (int J = part * W + wv; J < NT; J += parts * W) {
+      if (J < T0) continue;
+      float kf[CPL], vf[CPL];
+      Kr.row(J, kf);
+      Vr.row(J, vf);
+      key_tile<T, D, BK, PERPOS, true>(p, J, T0, NT, p0, lane, kf, vf, hpg, src, dK + head_kv, dV + head_kv);
+    }
 }
 
 // =============================================================================================
@@ -1336,13 +1511,14 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
   const int T0 = p0 / kTile;
   const int q = lane & 15, g = lane >> 4;
   const size_t head_kv = (size_t)bg * p.L * D;
-  const bool do_gate = stages & kBwdStageGate, do_dq = stages & kBwdStageDQ, do_dkv = stages & kBwdStageDKV;
+  const bool do_dq = stages & kBwdStageDQ, do_dkv = stages & kBwdStageDKV;  // (the gate pass belongs to the query tiles)
   const ResLayout lay(p, PERPOS, hpg, overlay, W);
   float *Ks = small_lds, *Vs = Ks + lay.pitch, *QG = small_lds + lay.qg, *rc = small_lds + lay.rowc;
   unsigned *words = reinterpret_cast<unsigned *>(small_lds + lay.words), *bits = words + NT * NWt;
   unsigned *my_lds = reinterpret_cast<unsigned *>(small_lds + lay.waves) + wv * lt_words(p, PERPOS);
 
-  stage_pair<T, D>(K + head_kv, V + head_kv, Ks, Vs, p.L, T0, NT, lane, wv, W);
+  // CLEAN: a row that sees a key or a value that is not finite has saved outputs that are not, and takes its NaN from there
+  stage_pair<T, D, true>(K + head_kv, V + head_kv, Ks, Vs, p.L, T0, NT, p0, lane, wv, W);
   __syncthreads();
   const LdsRows<D> Kr(Ks, q, g), Vr(Vs, q, g);
   const int *sel_head = sel + (size_t)bg * (PERPOS ? p.L : p.NB) * p.k;
@@ -1375,19 +1551,18 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
         if (do_dq) zero_fill(dQ_head + I * kTile * D, min(kTile, p.L - I * kTile) * D, fresh_lane());
         continue;
       }
-      query_tile<T, D, BK, PERPOS>(p, I, T0, NT, p0, lane, in, Kr, Vr, sel_head, my_lds, gate, true, do_dq, dQ_head, sink);
+      query_tile<T, D, BK, PERPOS, false>(p, I, T0, NT, p0, lane, in, Kr, Vr, sel_head, my_lds, gate, true, do_dq, dQ_head, sink);
     }
     if (hl > 0) __syncthreads();
     gate.finish(red, partial + (size_t)bh * GW, lane, wv, W);  // (its barrier also closes the query tiles of the head)
   }
   if (!do_dkv) return;
-  (void)do_gate;
   float kf[CPL], vf[CPL];
   if (overlay) {
     __syncthreads();
     for (int hl = 0; hl < hpg; ++hl) {
       const size_t at = (size_t)(bg * hpg + hl) * p.L * D;
-      stage_pair<T, D>(Q + at, dO + at, QG + 2 * hl * lay.pitch, QG + (2 * hl + 1) * lay.pitch, p.L, T0, NT, lane, wv, W);
+      stage_pair<T, D, false>(Q + at, dO + at, QG + 2 * hl * lay.pitch, QG + (2 * hl + 1) * lay.pitch, p.L, T0, NT, p0, lane, wv, W);
     }
     __syncthreads();
   }
@@ -1405,6 +1580,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     __device__ __forceinline__ unsigned tile_word(int I, int w) const { return words[I * NWt + w]; }
   } src = {QG, rc, gate_w, bits, words, bg * hpg, p.H, NT, NWt, q, g, lay.pitch};
   const Rows<T, D> Kg(K + head_kv, p.L, q, g), Vg(V + head_kv, p.L, q, g);
+  bool good = true;
   for (int u = wv; u < NT; u += W) {
     const int J = (T0 + u) % NT;  // the tiles without a valid key come last
     if (J < T0 || p0 >= p.L) {
@@ -1420,8 +1596,14 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
       Kr.row(J, kf);
       Vr.row(J, vf);
     }
-    key_tile<T, D, BK, PERPOS>(p, J, T0, NT, p0, lane, kf, vf, hpg, src, dK + head_kv, dV + head_kv);
+    good &= key_tile<T, D, BK, PERPOS, false>(p, J, T0, NT, p0, lane, kf, vf, hpg, src, dK + head_kv, dV + head_kv);
   }
+  if (__builtin_expect(!good, 0))
+    for (int u = wv; u < NT - T0; u += W) {
+      Kg.row(T0 + u, kf);
+      Vg.row(T0 + u, vf);
+      key_tile<T, D, BK, PERPOS, true>(p, T0 + u, T0, NT, p0, lane, kf, vf, hpg, src, dK + head_kv, dV + head_kv);
+    }
 }
 
 // =============================================================================================
