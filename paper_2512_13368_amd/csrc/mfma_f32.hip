@@ -27,9 +27,10 @@
 // consecutive elements: one or two 16-byte loads per tile.
 //
 // EXPONENTIALS WITHOUT A RUNNING MAXIMUM.  A walk takes exp2 of the logits themselves, one exponential for both
-// branches, and keeps the largest |logit| it met: up to 60 (log2 units) nothing overflows or loses accuracy
-// in fp32.  Beyond that (or if an output left fp32's range) the walk is repeated with the two row maxima,
-// found by a walk of their own, as references.
+// branches, and keeps the largest |logit| it met (of masked keys too): up to 60 (log2 units) nothing overflows or loses
+// accuracy in fp32.  Beyond that (or if an output left fp32's range) the walk is repeated with the two row maxima,
+// found by a walk of their own, as references.  With every tile beyond it the forward takes 46 us instead of 23 at B=256
+// H=2 L=200 d=32, 595 instead of 332 at B=2048 H=8 L=200 d=16, 245 instead of 87 at B=32 H=8 L=2000 d=8.
 //
 // VALUES THAT ARE NOT FINITE.  A walk multiplies whole tiles, so a masked element adds zero times whatever the tile holds: a NaN
 // or an infinity, in a row of the padding too, would reach every row of its tile.  Such a result is not finite itself,

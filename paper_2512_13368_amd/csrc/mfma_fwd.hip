@@ -17,7 +17,8 @@
 // window block whenever it is also selected) is loaded, multiplied and exponentiated once and masked twice.  The exponentials are
 // those of the logits themselves, with no running maximum: while a row's sum stays within 2^+-60 (and its output finite)
 // nothing has overflowed or been lost in fp32, and bf16 probabilities carry the same exponents.  A block with a row
-// outside that range is walked again with the row maxima, found by a walk of their own, as references.
+// outside that range is walked again with the row maxima, found by a walk of their own, as references: with every block outside
+// it (logits in the hundreds) the forward at B=128 H=4 L=1024, lengths U[100,1024] takes 176 us instead of 56.
 // The walk starts with the block's own tile, whose place is known before anything has been read.
 // A wavefront's life is latency (about ten tiles): at B=128 H=4 L=1024 k=8 w=64, lengths U[100,1024], two walks with online
 // references took 91 us (saving: 139), this one 66 (110).
@@ -175,7 +176,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
   // Lane t: where the short-term tile t stands in the list (-1: nowhere).  Entries outside [0, NB) are skipped
   // wherever they stand: the walk runs up to the last valid one.
   int n_lt = 0, at = -1;
-  bool lt_few = true;  // the selected past blocks hold fewer than kFewKeys valid keys
+  bool lt_few = true;   // the selected past blocks hold fewer than kFewKeys valid keys
+  bool lt_any = dense;  // the list names a block with a valid key up to the own one: every valid row sees a key of it
   const int n_look = min(n_st, 64);
   if (dense) {
     n_lt = I - J_first + 1;
@@ -189,6 +191,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
       // a full earlier block already brings a whole block of keys; only a partial first block may not
       const int vcount = min((J + 1) * BLK, p.L) - max(J * BLK, p0);
       if (__ballot(ok && J < I && vcount >= kFewKeys) != 0ull) lt_few = false;
+      if (__ballot(ok && J <= I && vcount > 0) != 0ull) lt_any = true;
       for (int t = 0; t < n_look; ++t) {
         const unsigned long long hit = __ballot(J == st_tile(t));
         if (hit != 0ull && lane == t && at < 0) at = e0 + __builtin_ctzll(hit);
@@ -449,7 +452,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     return l >= kSumLo && l <= kSumHi;
   };
   auto finish = [&]() __attribute__((always_inline)) -> bool {  // returns whether every row stayed in range
-    bool good = close(l_lt, ref_lt, inv_lt, lse_lt);
+    bool good = close(l_lt, ref_lt, inv_lt, lse_lt) || !lt_any;  // (no key: zeros, and nothing to walk for)
     if (!dense) good = close(l_st, ref_st, inv_st, lse_st) && good;
     else inv_st = 0.0f;
     float z_lt = 0.0f, z_st = 0.0f;

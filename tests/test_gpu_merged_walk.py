@@ -4,7 +4,10 @@ whose exponentials leave fp32's range without a reference, every short-term mask
 import math
 
 import pytest
+import torch
 
+from gpu_util import Dev, params
+from paper_2512_13368_amd import binding as B
 from paper_2512_13368_amd.inputs import WORKLOADS, make_inputs, with_shape
 from test_gpu_parity import run_case
 
@@ -41,3 +44,19 @@ def test_one_walk_for_both_branches(b, L, topk, window, sblk, amp, edit):
     pairs = [0, 1, 2, 5] if L > 1000 else None
     run_case(w, x=x, pairs=pairs, backward=amp == 1, gate_scale=0.4, scale=None if amp == 1 else amp * math.log(2.0),
              sel_edit=_edit if edit else None)
+
+
+def test_an_empty_list_does_not_send_a_block_through_the_walk_again():
+    # no selected block at all: the long-term outputs are zeros, and the short-term ones are those of the one walk, bit for bit
+    # (a second walk would take its exponentials against row maxima)
+    w = with_shape(WORKLOADS["cfg3"], name="walk-empty-list", B=3, H=2, L=300, topk=3, len_lo=1, len_hi=300, seed=2650)
+    x = make_inputs(w)
+    x.valid_len[:2] = [300, 77]
+    dv, p = Dev(x), params(w, save_for_bwd=1)
+    sel = torch.full((w.B, w.H, w.NB, w.topk), -1, dtype=torch.int32, device="cuda")
+    empty = B.attn_fwd(p, dv.Q, dv.K, dv.V, dv.vl, sel, dv.gw, dv.gb)
+    sel[..., 1] = torch.arange(w.NB, device="cuda")
+    own = B.attn_fwd(p, dv.Q, dv.K, dv.V, dv.vl, sel, dv.gw, dv.gb)
+    torch.cuda.synchronize()
+    assert not bool(empty.o_lt.any()) and not bool(empty.lse_lt.any()) and bool(own.o_lt.any())
+    assert torch.equal(empty.o_st, own.o_st) and torch.equal(empty.lse_st, own.lse_st)
