@@ -135,18 +135,32 @@ class Params:
                              self.last_block_only)
 
 
+class _PythonPath:
+    """Stands in for the native marshalling: declines every call, so that the Python path below takes it."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+PYTHON_PATH = _PythonPath()
 _fast = None
 
 
 def fastcall():
     """The native marshalling of the hot calls (csrc/fastcall.cpp).  Each returns the C ABI's error code, or None where an
-    argument is missing or not as expected: then the Python path below allocates, or names what is wrong."""
+    argument is missing or not as expected: then the Python path below allocates, or names what is wrong.  Without the
+    module the Python path marshals every call, with the same kernels and results."""
     global _fast
     if _fast is None:
         import torch  # noqa: F401  (the module is linked against its libraries)
         lib()
-        from . import _fastcall
-        _fast = _fastcall
+        try:
+            from . import _fastcall
+            _fast = _fastcall
+        except ImportError as e:
+            import warnings
+            warnings.warn(f"_fastcall.so cannot be loaded ({e}): calls are marshalled in Python, about 10 us each", RuntimeWarning)
+            _fast = PYTHON_PATH
     return _fast
 
 

@@ -52,40 +52,47 @@ def fastcall_command(obj: str) -> list[str]:
             sysconfig.get_paths()["include"], "-isystem", "/opt/rocm/include", "-c", os.path.join(CSRC, "fastcall.cpp"), "-o", obj]
 
 
-def link_fastcall(obj: str) -> None:
-    import torch
-    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
-    cmd = [_hipcc(), "-shared", "-fPIC", "-o", FASTCALL, obj, "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip",
-           "-L" + HERE, "-lblossom", "-Wl,-rpath,$ORIGIN"]
+def _run(cmd: list[str], what: str, verbose: bool = False) -> None:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
-        raise RuntimeError(f"link of _fastcall.so failed:\n{r.stdout}\n{r.stderr}")
+        raise RuntimeError(f"{what} failed:\n{r.stdout}\n{r.stderr}")
+    if verbose and r.stderr.strip():
+        print(r.stderr)
+
+
+def build_fastcall() -> str:
+    """Compiles and links the binding's host module: needs torch and the library, which does not need it."""
+    import torch
+    os.makedirs(OBJ_DIR, exist_ok=True)
+    obj = os.path.join(OBJ_DIR, "fastcall.o")
+    _run(fastcall_command(obj), "compilation of fastcall.cpp")
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    _run([_hipcc(), "-shared", "-fPIC", "-o", FASTCALL, obj, "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip",
+          "-L" + os.path.dirname(LIB), "-lblossom", "-Wl,-rpath,$ORIGIN"], "link of _fastcall.so")
+    return FASTCALL
 
 
 def build_library(verbose: bool = False) -> str:
+    """Compiles and links libblossom.so, the C ABI: HIP sources alone."""
     os.makedirs(OBJ_DIR, exist_ok=True)
-    hipcc = _hipcc()
 
     def compile_one(item):
         src, extra = item
         obj = os.path.join(OBJ_DIR, os.path.splitext(src)[0] + ".o")
-        cmd = [hipcc, *COMMON, *extra, "-c", os.path.join(CSRC, src), "-o", obj] if src.endswith(".hip") else fastcall_command(obj)
-        r = subprocess.run(cmd, capture_output=True, text=True)
-        if r.returncode != 0:
-            raise RuntimeError(f"hipcc failed for {src}:\n{r.stdout}\n{r.stderr}")
-        if verbose and r.stderr.strip():
-            print(r.stderr)
+        _run([_hipcc(), *COMMON, *extra, "-c", os.path.join(CSRC, src), "-o", obj], f"hipcc on {src}", verbose)
         return obj
 
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
-        *objs, host = ex.map(compile_one, [*SOURCES.items(), ("fastcall.cpp", [])])
-    cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
-    link_fastcall(host)
+        objs = list(ex.map(compile_one, SOURCES.items()))
+    _run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], "link of libblossom.so")
     return LIB
 
 
+def build_all(verbose: bool = False) -> None:
+    """The library first: a host module that does not build leaves it in place."""
+    print(build_library(verbose))
+    print(build_fastcall())
+
+
 if __name__ == "__main__":
-    print(build_library(verbose=True))
+    build_all(verbose=True)
