@@ -1,6 +1,6 @@
-"""GPU parity of the fp32 matrix-instruction kernels for short sequences (fp32 or bf16 storage, d in {8, 16, 32},
-block 8 or 16, K/V or Q/dO of a whole head resident in LDS): forward, dQ and dK/dV against the CPU oracle, at
-the shapes where those kernels take over from the scalar-ALU ones and at the edges of that range."""
+"""GPU parity of the fp32 matrix-instruction kernels for small heads (fp32 or bf16 storage, d in {8, 16, 32}, block 8 or
+16, up to 16384 positions): forward, dQ and dK/dV against the CPU oracle, with a whole head in LDS, with its tiles streamed,
+at the lengths where one takes over from the other, and where the scalar-ALU kernels take over from both."""
 import numpy as np
 import pytest
 import torch
@@ -17,8 +17,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("b,L,topk,window", [
     (16, 200, 4, 16),    # the short-sequence recommender shape (cfg2), with backward
     (16, 197, 4, 16),    # ragged last block
-    (16, 208, 5, 40),    # the longest sequence the resident kernels take at block 16
-    (8, 200, 4, 8),      # block 8: half-filled 16-row tiles, 25 blocks over 8 wavefronts
+    (16, 208, 5, 40),    # 13 whole tiles
+    (8, 200, 4, 8),      # block 8: two blocks per 16-row tile, the last tile half empty
     (8, 51, 2, 8),       # ragged, block 8
     (16, 16, 1, 1),      # one block, own block only, self only
     (16, 33, 3, 500),    # window beyond the sequence, top-k = number of blocks
@@ -33,8 +33,8 @@ def test_short_sequences_forward_backward(b, L, topk, window):
 
 
 def test_sharp_softmax_and_holes():
-    # large logits move the running maximum of the forward's online softmax from tile to tile;
-    # caller-built selection rows with holes are skipped where they stand
+    # logits large enough that a few keys take a row's whole weight; caller-built selection rows with holes are skipped
+    # where they stand
     w = with_shape(WORKLOADS["cfg2"], name="f32mc-sharp", B=4, H=2, L=150, topk=5, window=24, len_lo=40, len_hi=150,
                    seed=951)
     x = make_inputs(w, want_dO=True)
@@ -82,10 +82,26 @@ def test_rope_backward_and_serving_mode():
     assert torch.equal(O[:, :, lo:], f.O[:, :, lo:]) and bool((O[:, :, :lo] == 3.0).all())
 
 
-def test_just_outside_the_resident_range():
-    # one block more than the resident kernels take: the scalar-ALU kernels serve the shape, same answers
-    run_case(with_shape(WORKLOADS["cfg2"], name="f32-L224", B=3, H=2, L=224, len_lo=30, len_hi=224, seed=990),
+@pytest.mark.parametrize("d,L", [
+    (32, 224),
+    (32, 128), (32, 129), (32, 240), (32, 241), (32, 256), (32, 257),
+    (16, 224), (16, 225), (16, 416), (16, 417), (16, 480), (16, 481),
+    (8, 352), (8, 353), (8, 640), (8, 641), (8, 800), (8, 801),
+])
+def test_edges_of_the_resident_range(d, L):
+    # the longest heads (and one position more) whose backward holds Q and dO beside K and V, whose backward holds them in
+    # their place, and whose forward holds K and V; beyond, tiles are streamed
+    run_case(with_shape(WORKLOADS["cfg2"], name=f"f32-d{d}-L{L}", B=3, H=2, L=L, d=d, len_lo=30, len_hi=L, seed=990),
              backward=True)
+
+
+@pytest.mark.parametrize("dtype,d,b", [("fp32", 8, 16), ("bf16", 16, 8), ("bf16", 32, 16)])
+def test_past_the_longest_small_head(dtype, d, b):
+    # 16384 positions are the most those kernels take; here the scalar ones serve the same head sizes and blocks (d = 32, block
+    # 8 in fp32: test_gpu_parity.py, test_many_blocks_backward)
+    w = with_shape(WORKLOADS["cfg2"], name=f"past-{dtype}-d{d}-b{b}", B=1, H=1, L=16384 + 5, d=d, block=b, topk=3, window=b + 3,
+                   dtype=dtype, qkv_scaled=(dtype == "bf16"), len_lo=16384 - 40, len_hi=16384 + 5, seed=995)
+    run_case(w, backward=True, gate_scale=0.4)
 
 
 @pytest.mark.parametrize("dtype,d,b,L,topk,window,sblk", [
@@ -105,16 +121,16 @@ def test_head_sizes_storage_types_and_full_short_term_mask(dtype, d, b, L, topk,
     run_case(w, x=x, backward=True, check_dense=True, gate_scale=0.4)
 
 
-def test_long_rows_with_more_than_64_kb_of_lds():
-    # the efficiency-study length 1000 at the paper's hyperparameters: K and V of a head take 96 KB of LDS,
-    # dK/dV's Q, dO and row constants 120 KB; one workgroup per CU
+def test_efficiency_study_length_1000():
+    # the efficiency-study length 1000 at the paper's hyperparameters: K and V of a head would take 94 KB of LDS, its tiles
+    # are streamed
     w = with_shape(WORKLOADS["cfg2"], name="res-L1000", B=8, H=8, L=1000, d=8, block=16, topk=4, window=8, len_lo=300,
                    len_hi=1000, stis_block=1, seed=1301)
     run_case(w, backward=True, pairs=[0, 7, 21, 38, 63])
 
 
-def test_seeded_random_shapes_in_the_resident_range():
-    # 60 seeded draws over storage type, head size, block size, length, top-k, window, mask block and form
+def test_seeded_random_shapes_of_small_heads():
+    # 60 seeded draws, up to 26 blocks (heads in LDS, and streamed at d = 32), over storage type, head size, block size, length, top-k, window, mask block and form
     rng = np.random.default_rng(4242)
     for case in range(60):
         dtype = "bf16" if rng.random() < 0.35 else "fp32"

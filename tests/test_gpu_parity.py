@@ -173,8 +173,10 @@ def test_shape_matrix(dtype, d, b):
 
 
 @pytest.mark.parametrize("name,shape", [
-    ("cfg1", dict(topk=4)),                                                                  # scalar kernels, fp32
-    ("cfg2", dict(B=4, dtype="bf16", qkv_scaled=True)),                                      # scalar kernels, bf16
+    ("cfg1", dict(topk=4)),                                                                  # fp32 matrix instructions, fp32
+    ("cfg2", dict(B=4, dtype="bf16", qkv_scaled=True)),                                      # fp32 matrix instructions, bf16
+    ("cfg1", dict(topk=4, d=64)),                                                            # scalar kernels, fp32
+    ("cfg2", dict(B=4, d=64, dtype="bf16", qkv_scaled=True)),                                # scalar kernels, bf16
     ("cfg3", dict(B=3, L=32 * 9 + 11, len_lo=40, len_hi=32 * 9 + 11, topk=5)),               # matrix cores, b = 32
     ("cfg4", dict(B=2, H=2, L=64 * 9, len_lo=300, len_hi=64 * 9, topk=6)),                   # matrix cores, b = 64
     ("cfg4", dict(B=1, H=2, L=64 * 70, len_lo=64 * 70, len_hi=64 * 70, topk=67, window=64)),  # a row read in two chunks
@@ -248,7 +250,8 @@ def test_matrix_core_long_walks():
 def test_seeded_random_shapes():
     # Sixty seeded draws of (dtype, d, b, L, k, w, lengths) over everything the library accepts: odd
     # lengths, rows that start in the middle of a block, top-k from 1 to beyond the number of blocks,
-    # windows from 1 to beyond L.  Both kernel families get about half of the draws.
+    # windows from 1 to beyond L.  The bf16 matrix-core kernels get half of the draws, the scalar ones (d = 64, or blocks from
+    # 32) and the fp32 matrix instructions (d = 32, block 8 or 16) the others.
     rng = np.random.default_rng(4242)
     for case in range(60):
         mfma = case % 2 == 0
@@ -341,7 +344,8 @@ def test_bidirectional_serving_mode():
 
 
 @pytest.mark.parametrize("name,shape", [
-    ("cfg1", dict()),                                                          # scalar kernels, fp32
+    ("cfg1", dict()),                                                          # fp32 matrix instructions
+    ("cfg1", dict(d=64)),                                                      # scalar kernels, fp32
     ("cfg3", dict(B=3, L=32 * 9 + 11, len_lo=40, len_hi=32 * 9 + 11)),          # matrix cores, ragged last block
     ("cfg4", dict(B=2, H=2, L=64 * 6, len_lo=100, len_hi=64 * 6)),              # matrix cores, b = 64
     ("cfg4", dict(B=2, H=2, L=64 * 5 + 3, len_lo=64 * 5 + 3, len_hi=64 * 5 + 3, stis_block=64)),
@@ -379,9 +383,9 @@ def test_serving_mode_last_block_only(name, shape):
 
 @pytest.mark.parametrize("b", [32, 64])
 def test_matrix_core_sharp_softmax(b):
-    # logits eight times the usual spread (queries scaled by a power of two, so they stay bf16 values):
-    # probabilities of a tile exceed the forward's acceptance bound again and again, so its softmax
-    # reference has to move many times per row; backward sees probabilities close to one everywhere
+    # logits eight times the usual spread (queries scaled by a power of two, so they stay bf16 values): block 64, whose softmax
+    # keeps a reference, has to move it many times per row (block 32 keeps none: test_gpu_merged_walk.py drives it out of its
+    # range); backward sees probabilities close to one everywhere
     L = 9 * b + 5
     w = with_shape(WORKLOADS["cfg3"], name=f"sharp-{b}", B=2, H=2, L=L, d=64, block=b, topk=4, window=b + 9,
                    len_lo=L - 70, len_hi=L, seed=1200 + b)
@@ -418,7 +422,7 @@ def test_selection_ties():
 
 def test_many_blocks_backward():
     # more than 2048 blocks per row: the inverse selection list then runs with one wavefront per (row, head)
-    # and its counters no longer fit four-fold in LDS; scalar kernels, fp32
+    # and its counters no longer fit four-fold in LDS; scalar kernels (more than 16384 positions), fp32
     w = with_shape(WORKLOADS["cfg1"], name="many-blocks", B=1, H=2, L=8 * 2100 + 3, d=32, block=8, topk=4, window=11,
                    len_lo=8 * 2100 - 50, len_hi=8 * 2100 + 3, seed=77)
     run_case(w, backward=True, gate_scale=0.4)
@@ -437,8 +441,9 @@ def test_edge_cases():
     torch.cuda.synchronize()
     assert_close(host(f.o_lt), host(Od), 1e-5, "o_lt vs dense kernel")
     assert_close(host(f.o_st), host(Od), 1e-5, "o_st vs dense kernel")
-    # every row empty: all outputs and gradients are zero, nothing faults (both kernel families)
-    for wz in (with_shape(base, name="all-empty", B=2), with_shape(WORKLOADS["cfg3"], name="all-empty-mc", B=2, H=2, L=32 * 5 + 7)):
+    # every row empty: all outputs and gradients are zero, nothing faults (each kernel family)
+    for wz in (with_shape(base, name="all-empty", B=2), with_shape(base, name="all-empty-scalar", B=2, d=64),
+               with_shape(WORKLOADS["cfg3"], name="all-empty-mc", B=2, H=2, L=32 * 5 + 7)):
         xz = make_inputs(wz, want_dO=True)
         xz.valid_len[:] = 0
         _, selz, fz, gz = run_case(wz, x=xz, backward=True, check_dense=True)
@@ -448,8 +453,9 @@ def test_edge_cases():
     # k = 1 (own block only), w = 1 (self only), k larger than the number of blocks
     run_case(with_shape(base, name="k1w1", topk=1, window=1), backward=True)
     run_case(with_shape(base, name="kbig", topk=12, window=200), backward=True)
-    # the "unbounded window" idiom: the largest int, in both kernel families
+    # the "unbounded window" idiom: the largest int, in each kernel family
     run_case(with_shape(base, name="wmax", topk=2, window=2**31 - 1), backward=True)
+    run_case(with_shape(base, name="wmax-scalar", topk=2, window=2**31 - 1, d=64), backward=True)
     run_case(with_shape(WORKLOADS["cfg3"], name="wmax-mc", B=2, H=2, L=32 * 6 + 5, len_lo=60, len_hi=32 * 6 + 5, topk=2,
                         window=2**31 - 1), backward=True)
 
@@ -496,7 +502,8 @@ def test_select_with_compressed_keys(dtype, d, b, L, k):
 
 
 @pytest.mark.parametrize("name,shape,scale", [
-    ("cfg1", dict(), 0.4),                                                   # scalar kernels, fp32
+    ("cfg1", dict(), 0.4),                                                   # fp32 matrix instructions
+    ("cfg1", dict(d=64), 0.4),                                               # scalar kernels, fp32
     ("cfg3", dict(B=3, L=32 * 7 + 5, len_lo=30, len_hi=32 * 7 + 5), 0.07),   # matrix cores, b = 32
     ("cfg4", dict(B=2, H=2, L=64 * 5 + 9, len_lo=90, len_hi=64 * 5 + 9), 0.25),  # matrix cores, b = 64, sharper than 1/sqrt(d)
 ])

@@ -13,9 +13,11 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("name,shape", [
-    ("cfg1", dict()),                                                              # scalar kernels, fp32, d = 32
+    ("cfg1", dict()),                                                              # fp32 matrix instructions, fp32, d = 32
+    ("cfg1", dict(d=64)),                                                          # scalar kernels, fp32
+    ("cfg2", dict(B=3, d=64, dtype="bf16", qkv_scaled=True)),                       # scalar kernels, bf16
     ("cfg2", dict(B=6, H=8, d=8, L=197, len_lo=30, len_hi=197, topk=4, window=8)),  # the paper's head size
-    ("cfg2", dict(B=5, dtype="bf16", qkv_scaled=True)),                             # scalar kernels, bf16
+    ("cfg2", dict(B=5, dtype="bf16", qkv_scaled=True)),                             # fp32 matrix instructions, bf16
     ("cfg3", dict(B=4, L=32 * 9 + 11, len_lo=40, len_hi=32 * 9 + 11)),              # matrix cores, b = 32, ragged
     ("cfg4", dict(B=2, H=2, L=64 * 9, len_lo=200, len_hi=64 * 9)),                  # matrix cores, b = 64
 ])
