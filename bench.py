@@ -326,10 +326,14 @@ def measure_workload(w, args, mods, n_sets, headline):
     traffic, traffic_sha = ({}, None) if (w.stis_block or args.shape) else profiled_traffic(w.name)
     roof = lambda k_: roofline_entry(w, k_, ms, table, traffic)
     # the launches of a step: on the bf16 matrix-core shapes a full backward call runs dQ and dK/dV as one kernel
-    # (same condition as the library's dispatch); elsewhere they are two launches
+    # (same condition as the library's dispatch).  The small-head kernels form the row constants in whichever pass runs and hold
+    # the whole backward in one launch where a head fits LDS: a pass alone repeats the others' work, so theirs is taken as one.
+    # Elsewhere dQ and dK/dV are two launches after the per-row pass.
     one_launch = w.dtype == "bf16" and w.d == 64 and w.block in (32, 64) and not w.bidir and \
         (w.stis_block == 0 or (w.stis_block <= w.block and w.stis_block & (w.stis_block - 1) == 0))
-    step_kernels = ["select", "fwd_saving_for_bwd", "bwd_gate"] + (["bwd_dq_dkv"] if one_launch else ["bwd_dq", "bwd_dkv"])
+    small = w.d in (8, 16, 32) and w.block in (8, 16) and w.L <= 16384
+    step_kernels = ["select", "fwd_saving_for_bwd"] + (["bwd"] if small else ["bwd_gate", "bwd_dq_dkv"] if one_launch
+                                                       else ["bwd_gate", "bwd_dq", "bwd_dkv"])
     dominant = max(step_kernels, key=lambda k_: ms[k_])
     out = {
         "ms_per_step": round(ms_per_step, 4),

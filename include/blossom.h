@@ -90,7 +90,8 @@ typedef struct {
                              Eq. 15 as printed, |i-j| < window or |b_q-b_k| = 2^r or j >= L - blk, with
                              mask block blk = stis_block (0 means `block`); the long-term branch takes its
                              k-1 candidates from the blocks on BOTH sides of the query block and sees the
-                             selected blocks whole.  Every shape runs on the scalar kernels in this mode. */
+                             selected blocks whole.  d in {8, 16, 32} with block 8 or 16 runs on the fp32 matrix
+                             instructions, every other shape on the scalar kernels in this mode. */
   int32_t save_for_bwd;   /* fwd only: 1 = also write o_lt, o_st, lse_lt, lse_st                */
   int32_t stis_block;     /* stis_mode 1: mask block size blk of Eq. 15 (>= 1); 0 means `block`.
                              With b_q = i / blk, b_k = j / blk query i sees key j <= i iff
@@ -187,8 +188,9 @@ int blossom_select_positions(const blossom_params *p, int32_t kv_groups, int32_t
  *                        skipped), as blossom_select_positions writes them
  *   O               out  [B,H,L,d]
  *   o_lt, o_st      out  fp32 [B,H,L,d], or NULL;  lse_lt, lse_st  out  fp32 [B,H,L], or NULL
- * Served by the kernels that keep a head's K and V resident in LDS: d in {8, 16, 32}, l' in {8, 16}, at most 64
- * selection blocks, K and V of one (row, group) within 144 KB as fp32 rows (L <= 480 at d = 32, <= 900 at d <= 16);
+ * Served by the small-head kernels (fp32 matrix instructions): d in {8, 16, 32}, l' in {8, 16}, at most 64 selection
+ * blocks, and K and V of one (row, group), as fp32 rows padded to 20 or 36 floats, within 144 KB (L <= 480 at d = 32,
+ * <= 900 at d <= 16);
  * BLOSSOM_ERR_UNSUPPORTED beyond, for stis_mode 2 and for last_block_only.  Needs no workspace.
  */
 int blossom_attn_fwd_positions(const blossom_params *p, int32_t kv_groups, const void *Q, const void *K, const void *V,
@@ -207,8 +209,8 @@ int blossom_attn_fwd_positions(const blossom_params *p, int32_t kv_groups, const
  *   d_gate_w        out  fp32 [H,2d];  d_gate_b  out fp32 [H] or NULL
  *   ws              scratch, >= blossom_workspace_bytes(p, BLOSSOM_WS_BWD), 16-byte aligned
  * Every output element is written (padding rows get zeros); no atomics, so results do not depend on timing.
- * Limits: those of blossom_attn_fwd_positions, with Q, dO and the per-position constants of one head within
- * 144 KB of LDS (L <= 432 at d = 32, <= 736 at d <= 16 with l' = 16; 64 blocks, L <= 512, with l' = 8); BLOSSOM_ERR_UNSUPPORTED beyond.
+ * Limits: those of blossom_attn_fwd_positions with the per-position constants of one head added to the same
+ * 144 KB (L <= 432 at d = 32, <= 736 at d <= 16 with l' = 16; 64 blocks, L <= 512, with l' = 8); BLOSSOM_ERR_UNSUPPORTED beyond.
  */
 int blossom_attn_bwd_positions(const blossom_params *p, int32_t kv_groups, const void *Q, const void *K, const void *V,
                                const int32_t *valid_len, const int32_t *sel_pos, const float *gate_w,

@@ -94,7 +94,7 @@ constexpr int kInvFewShift = 30;
 constexpr int kInvBlockMask = (1 << kInvFewShift) - 1;
 enum : unsigned { kBwdStageGate = 1u, kBwdStageInverse = 2u, kBwdStageDQ = 4u, kBwdStageDKV = 8u, kBwdStageAll = 15u };
 void launch_bwd(const KParams &p, int dtype, const BwdArgs &a, unsigned stages, hipStream_t st);
-// the backward under a per-position selection (resident kernels only): a.sel = sel_pos [B,G,L,k]
+// the backward under a per-position selection (small-head kernels only): a.sel = sel_pos [B,G,L,k]
 void launch_bwd_positions(const KParams &p, int dtype, const BwdArgs &a, int kv_groups, hipStream_t st);
 
 // mfma_fwd.hip: matrix-core forward for bf16, d = 64, b in {32, 64}

@@ -7,7 +7,7 @@
 // Positions are cut into 16-row tiles of v_mfma_f32_16x16x4_f32 (true fp32 products accumulated in fp32)
 // whatever the block size; a selection block of 8 is half a tile and the selection is tested per element.
 // A wavefront takes one query tile (forward, dQ) or one key tile (dK/dV) at a time.  Heads that fit a workgroup's LDS
-// (rows of d + 4 floats, two workgroups per CU: L up to about 200 at d = 32, 450 at d = 16, 750 at d = 8) are staged
+// (rows of d + 4 floats, two workgroups per CU: L up to 256 at d = 32, 480 at d = 16, 800 at d = 8, less in the backward) are staged
 // there, and the backward of such a head is one kernel that reads every tensor once; longer ones stream the tiles
 // they walk from memory (L1 and L2) into operand registers, with neither barriers nor a limit on the length.
 //
