@@ -244,15 +244,58 @@ __device__ __forceinline__ int mask_block(const KParams &p, int pos, int r = 0)
   return (int)fmaf((float)pos, p.sblk_inv, ((float)r + 0.5f) * p.sblk_inv);
 }
 
+// Mask block 1: the first power of two of tiles beyond the tiles that hold a key of the window.  From there on a tile at such a
+// distance shows each row one key, the one at its own offset (`diagonals`).
+__device__ __forceinline__ int first_diagonal(const KParams &p) { return 2 << (31 - __clz(max((p.w + kTile - 2) / kTile, 1))); }
+
 // short-term visibility of (query i, key j + r) that the causal and validity tests let through (those make the difference
 // non-negative in the causal form, so its absolute value serves both forms); plain bit operations, no branches.
-// UNIT: no mask block of Eq. 15, or one of a single position.
-template <bool UNIT>
 __device__ __forceinline__ bool st_sees(const KParams &p, int i, int j, int kid_i, int kid_j, bool last)
 {
-  const unsigned d = abs_diff(i, j);
-  const bool pow2 = UNIT ? (__popc(d) == 1) & (p.sblk != 0) : __popc(abs_diff(kid_i, kid_j)) == 1;
-  return (d < (unsigned)p.w) | pow2 | last;
+  return (abs_diff(i, j) < (unsigned)p.w) | (__popc(abs_diff(kid_i, kid_j)) == 1) | last;
+}
+
+// Four bits a lane: which of the elements 4g .. 4g+3 of a tile its own row sees.  Without Eq. 15, or with its mask block 1,
+// visibility is a function of the distance alone, own - element = 16*dt + c - r with dt tiles between the two and c = q - 4g: the
+// bits of the tiles next to the row's own (dt of 0, 1 and -1) are cut out of one table over distances, once per wavefront.
+// Powers of two from first_diagonal on are left to `diagonals`.  A general tile of the forward takes 35 vector instructions for its
+// masks and sums, 69 with a test per element.
+struct LaneMasks {
+  int c;
+  unsigned near;  // bits 0-3, 4-7, 8-11: dt = 0, 1, -1 (the window and the powers of two of Eq. 15)
+  __device__ __forceinline__ static LaneMasks make(const KParams &p, int q, int g)
+  {
+    LaneMasks m;
+    m.c = q - 4 * g;
+    unsigned long long table = p.w >= 32 ? ~0ull : ((1ull << (2 * p.w - 1)) - 1) << (33 - p.w);  // bit 32 + distance
+    if (p.sblk == 1) table |= 0x0001011600000000ull | 0x00000000D1010000ull;  // 1, 2, 4, 8, 16 on either side
+    auto cut = [&](int x) { return (unsigned)(table >> (32 - x)) & 15u; };  // element r at distance x - r, the table being symmetric
+    m.near = cut(m.c) | cut(m.c + kTile) << 4 | cut(m.c - kTile) << 8;
+    return m;
+  }
+  // elements from x on; elements below x (x counted from the first of the four)
+  __device__ __forceinline__ static unsigned from(int x) { return 15u << clamp4(x); }
+  __device__ __forceinline__ static unsigned below(int x) { return 15u >> (4 - clamp4(x)); }
+  __device__ __forceinline__ static int clamp4(int x) { return min(max(x, 0), 4); }
+  // of the keys from key0 on, those that the causal and validity tests let query row i see
+  __device__ __forceinline__ static unsigned keys(const KParams &p, int key0, int p0, int i)
+  {
+    return from(p0 - key0) & below((p.bidir ? p.L : i + 1) - key0);
+  }
+  __device__ __forceinline__ unsigned st(const KParams &p, int dt) const
+  {
+    const int far = dt < 0 ? -dt : dt;
+    if (far <= 1) return near >> (dt == 0 ? 0 : dt == 1 ? 4 : 8);
+    const int d0 = kTile * dt + c;
+    unsigned m = from(d0 - p.w + 1) & below(d0 + p.w);
+    if (p.sblk == 1 && (far & (far - 1)) == 0 && far < first_diagonal(p)) m |= from(c) & below(c + 1);
+    return m;
+  }
+};
+// x where bit r is set, else zero (of a NaN too)
+__device__ __forceinline__ float keep(float x, unsigned bits, int r)
+{
+  return __uint_as_float(__float_as_uint(x) & (unsigned)__builtin_amdgcn_sbfe((int)bits, r, 1));
 }
 
 // may any query of tile I see any key of tile J in the short-term branch (J <= I in the causal form)?
@@ -327,10 +370,11 @@ struct Rows {
   static constexpr bool kNear = false;  // far: operands are requested a tile ahead
   static constexpr unsigned TB = kTile * D * sizeof(T);  // bytes of a tile
   Slice s;
-  unsigned row_off, col_off;  // this lane's place in a tile
+  unsigned row_off, col_off, own_off;  // this lane's place in a tile
   __device__ __forceinline__ Rows(const T *head, int L, int q, int g) : s(head, (size_t)L * D * sizeof(T))
   {
     row_off = (unsigned)(q * D + Geo<D>::CPL * g) * (unsigned)sizeof(T);
+    own_off = (unsigned)(q * D + ((4 * g) & (D - 1))) * (unsigned)sizeof(T);
     col_off = (unsigned)(4 * g * D + (D < 16 ? (q & (D - 1)) : q)) * (unsigned)sizeof(T);
   }
   // contraction over channels: channels CPL*g .. of row q of tile t
@@ -349,6 +393,12 @@ struct Rows {
         else o[mb][r] = __uint_as_float((unsigned)__builtin_amdgcn_raw_buffer_load_b16(s.d, at, 0, 0) << 16);
       }
   }
+  // row q of the tile, the channels of this lane's accumulators: element r is channel 16*mb + 4g + r (d = 8: repeated likewise)
+  __device__ __forceinline__ void own(int t, float (&o)[Geo<D>::NMB][4]) const
+  {
+#pragma unroll
+    for (int mb = 0; mb < Geo<D>::NMB; ++mb) load_n<T>(s, own_off + (unsigned)t * TB + 16u * mb * (unsigned)sizeof(T), o[mb]);
+  }
 };
 
 // the same from LDS, where a workgroup staged the head as fp32 rows of D + 4 floats (12, 20 or 36: both read patterns are
@@ -358,9 +408,10 @@ constexpr int kLdsRow = D + 4;
 template <int D>
 struct LdsRows {
   static constexpr bool kNear = true;  // near: operands are read where they are used and take no registers before
-  const float *row_at, *col_at;  // this lane's place in tile 0
+  const float *row_at, *col_at, *own_at;  // this lane's place in tile 0
   __device__ __forceinline__ LdsRows(const float *base, int q, int g)
-      : row_at(base + q * kLdsRow<D> + Geo<D>::CPL * g), col_at(base + 4 * g * kLdsRow<D> + (D < 16 ? (q & (D - 1)) : q))
+      : row_at(base + q * kLdsRow<D> + Geo<D>::CPL * g), col_at(base + 4 * g * kLdsRow<D> + (D < 16 ? (q & (D - 1)) : q)),
+        own_at(base + q * kLdsRow<D> + ((4 * g) & (D - 1)))
   {
   }
   __device__ __forceinline__ void row(int t, float (&o)[Geo<D>::CPL]) const { load_n<Geo<D>::CPL>(row_at + t * (kTile * kLdsRow<D>), o); }
@@ -371,6 +422,11 @@ struct LdsRows {
     for (int mb = 0; mb < Geo<D>::NMB; ++mb)
 #pragma unroll
       for (int r = 0; r < 4; ++r) o[mb][r] = at[r * kLdsRow<D> + 16 * mb];
+  }
+  __device__ __forceinline__ void own(int t, float (&o)[Geo<D>::NMB][4]) const
+  {
+#pragma unroll
+    for (int mb = 0; mb < Geo<D>::NMB; ++mb) load_n<4>(own_at + t * (kTile * kLdsRow<D>) + 16 * mb, o[mb]);
   }
 };
 template <int N>
@@ -421,68 +477,115 @@ __device__ __forceinline__ unsigned pair_bits(unsigned long long b)
   return (unsigned)(b | (b >> 16));
 }
 
-// THE WALK.  Tiles are grouped by kind, 32 tiles (a word) at a time, as four bit masks in scalar registers, and each kind
+// THE WALK.  Tiles are grouped by kind, 64 tiles (a word) at a time, as three bit masks in scalar registers, and each kind
 // has a loop of its own whose body is one straight line: no branches, so the accumulators stay in place and the loads of the
 // next tile (of whatever kind) are waited for where they are used.
 //   0 general   both branches, every mask test: tiles of both branches, the diagonal, the first and the last valid tile, and
 //               tiles with last-block keys of Eq. 15
 //   1 lt        long-term only: no mask (per-element selection tests where blocks are smaller than tiles or per position)
 //   2 st        short-term only: window and power-of-two tests
-//   3 diagonal  short-term only, mask block 1: a tile 2, 4, 8 ... tiles away, where each row sees the one key at its own offset
+// A lane classifies a tile, ballots make the words: about 20 instructions, where bit arithmetic on scalars took over a hundred
+// for half as many tiles and the scalar ALU was as busy as the vector ALUs (with the masks as bits, the steps above: 289 and 956 us).
+typedef unsigned long long Word;
 struct Walk {
-  unsigned m0 = 0, m1 = 0, m2 = 0, m3 = 0;  // tiles of the word still to come
-  unsigned lt = 0;                          // long-term tiles of the word
-  int base = 0;                             // first tile of the word
-  // lt_bits, st, edge: tiles of the word in either branch, and those that need every test; dia: candidates of kind 3
-  __device__ __forceinline__ void start(int w, unsigned lt_bits, unsigned st, unsigned edge, unsigned dia)
+  Word m0 = 0, m1 = 0, m2 = 0;  // tiles of the word still to come
+  Word lt = 0;                  // long-term tiles of the word
+  int base = 0;                 // first tile of the word
+  // Word w of the walk of tile X (a query tile when KEY_SIDE is false, else a key tile) over the tiles lo .. hi.  lt_here: the
+  // long-term branch takes the lane's tile.  edge: the lane's tile needs every test.  dia: also the short-term tiles that
+  // `diagonals` takes, for a walk that leaves it out.  with_st: there is a short-term branch.
+  template <bool KEY_SIDE>
+  __device__ __forceinline__ void start(const KParams &p, int X, int w, int lo, int hi, int lane, bool lt_here, bool edge, bool dia,
+                                        bool with_st)
   {
-    base = w * 32;
-    lt = lt_bits;
-    m0 = (lt & st) | (edge & (lt | st));
+    base = w * 64;
+    const int t = base + lane;
+    const bool in = (unsigned)(t - lo) <= (unsigned)(hi - lo);
+    bool st;
+    if (p.sblk > 1) {
+      st = KEY_SIDE ? st_reaches(p, t, X) : st_reaches(p, X, t);
+    } else {
+      const int reach = max((p.w + kTile - 2) / kTile, p.sblk);  // tiles up to this far away hold a key of the window, or the next power of two
+      st = abs_diff(t, X) <= (unsigned)reach;
+      if (p.sblk == 1) {
+        if (dia) st |= __popc(abs_diff(t, X)) == 1;
+        // the last position: its tile is walked by every query tile (that reaches it)
+        st |= (KEY_SIDE ? X : t) >= p.last_lo / kTile;
+      }
+    }
+    st &= with_st;
+    lt = __ballot(in & lt_here);
+    const Word s = __ballot(in & st), e = __ballot(edge);
+    m0 = (lt & s) | (e & (lt | s));
     m1 = lt & ~m0;
-    m3 = st & ~lt & ~m0 & dia;
-    m2 = st & ~lt & ~m0 & ~m3;
+    m2 = s & ~lt & ~m0;
   }
-  __device__ __forceinline__ bool any() const { return (m0 | m1 | m2 | m3) != 0u; }
+  __device__ __forceinline__ Word all() const { return m0 | m1 | m2; }
+  __device__ __forceinline__ static int first(Word m) { return __builtin_ctzll(m); }
   // the first tile still to come (some tile when there is none: a harmless read-ahead)
   __device__ __forceinline__ int peek() const
   {
-    const unsigned m = m0 ? m0 : m1 ? m1 : m2 ? m2 : m3;
-    return base + (m ? __builtin_ctz(m) : 0);
+    const Word m = m0 ? m0 : m1 ? m1 : m2;
+    return base + (m ? first(m) : 0);
   }
+  __device__ __forceinline__ int take(Word &m) const
+  {
+    const int t = base + first(m);
+    m &= m - 1;
+    return t;
+  }
+  __device__ __forceinline__ bool is_lt(int t) const { return (lt >> (t & 63)) & 1ull; }
 };
-// bits of word w for the tiles lo .. hi
-__device__ __forceinline__ unsigned word_range(int w, int lo, int hi)
+
+// THE DIAGONALS of mask block 1.  A row sees one key of a tile 2, 4, 8 ... tiles away (from first_diagonal on), its own offset's:
+// 16 pairs, for which a matrix product would form 256.  They are taken four distances at a time on the vector ALUs instead: every
+// lane multiplies its channels of its row for all four distances, gather_g leaves distance n's sum with lane group n, where the
+// mask and the exponential are, and spread_g hands the four results to all groups, which add them into their accumulators'
+// channels (`own`).  About 12 vector instructions a distance; as tiles of the walk the distances took half of its steps at L=2000
+// (a training step at B=32 H=8 L=2000 d=8 356 us, 302 like this; B=2048 H=8 L=200 d=16 1050 and 996).
+// f(d): tiles X + d, X + 2d, X + 4d, X + 8d (some may lie outside lo .. hi: d times the lane group's power tells).
+template <typename F>
+__device__ __forceinline__ void diagonals(const KParams &p, int X, int lo, int hi, F &&f)
 {
-  const int a = max(lo - w * 32, 0), z = min(hi - w * 32, 31);
-  return a > z ? 0u : (0xFFFFFFFFu >> (31 - z)) & (0xFFFFFFFFu << a);
+  const int d0 = first_diagonal(p);
+  for (int d = d0; d <= X - lo; d <<= 4) f(-d);
+  for (int d = d0; d <= hi - X; d <<= 4) f(d);
 }
-// Short-term tiles of word w for tile X (a query tile when key_side is false, else a key tile), tiles lo .. hi in question
-// (causal: keys up to X, or queries from X on).  dia: those of kind 3.
-template <bool KEY_SIDE>
-__device__ __forceinline__ unsigned st_word(const KParams &p, int X, int w, int lo, int hi, int lane, unsigned &dia)
+// d = 32: the phases of a batch of distances are kept apart: their registers would spill
+template <int D>
+__device__ __forceinline__ void phase_end()
 {
-  dia = 0u;
-  const unsigned range = word_range(w, lo, hi);
-  if (p.sblk > 1) {  // any mask block: one tile per lane
-    const int t = w * 32 + (lane & 31);
-    const bool r = KEY_SIDE ? st_reaches(p, t, X) : st_reaches(p, X, t);
-    return (unsigned)__ballot((lane < 32) & r) & range;
-  }
-  const int reach = (p.w + kTile - 2) / kTile;  // tiles up to this far away hold a key of the window
-  unsigned st = word_range(w, X - reach, X + reach);
-  if (p.sblk == 1) {
-    for (int d = 1; d <= max(X - lo, hi - X); d <<= 1) {
-      const int u = X - d - w * 32, v = X + d - w * 32;
-      const unsigned bits = ((unsigned)u < 32u ? 1u << u : 0u) | ((unsigned)v < 32u ? 1u << v : 0u);
-      st |= bits;
-      if (d > max(reach, 1)) dia |= bits;
-    }
-    // the last position: its tile is walked by every query tile (that reaches it)
-    if (!KEY_SIDE) st |= word_range(w, p.last_lo / kTile, p.last_lo / kTile);
-    else if (X >= p.last_lo / kTile) st = 0xFFFFFFFFu;
-  }
-  return st & range;
+  if constexpr (D == 32) __builtin_amdgcn_sched_barrier(0);
+}
+__device__ __forceinline__ float gather_g(const float (&x)[4])
+{
+  const u32x2_t a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[0]), __float_as_uint(x[1]), false, false);
+  const u32x2_t b = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[2]), __float_as_uint(x[3]), false, false);
+  const float u = __uint_as_float(a[0]) + __uint_as_float(a[1]), v = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+  const u32x2_t c = __builtin_amdgcn_permlane32_swap(__float_as_uint(u), __float_as_uint(v), false, false);
+  return __uint_as_float(c[0]) + __uint_as_float(c[1]);
+}
+__device__ __forceinline__ void spread_g(float x, float (&o)[4])
+{
+  const unsigned u = __float_as_uint(x);
+  const u32x2_t a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const u32x2_t b = __builtin_amdgcn_permlane32_swap(a[0], a[0], false, false);
+  const u32x2_t c = __builtin_amdgcn_permlane32_swap(a[1], a[1], false, false);
+  o[0] = __uint_as_float(b[0]); o[1] = __uint_as_float(c[0]); o[2] = __uint_as_float(b[1]); o[3] = __uint_as_float(c[1]);
+}
+template <int N>
+__device__ __forceinline__ void own_of_row(const float (&x)[N], float (&o)[1][4])  // d = 16: the same channels
+{
+#pragma unroll
+  for (int r = 0; r < 4; ++r) o[0][r] = x[r & (N - 1)];
+}
+template <int N>
+__device__ __forceinline__ void add_own(f32x4 (&acc)[N], float c, const float (&a)[N][4])
+{
+#pragma unroll
+  for (int mb = 0; mb < N; ++mb)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[mb][r] = fmaf(c, a[mb][r], acc[mb][r]);
 }
 
 // What a query tile's wavefront knows about its long-term selection.  In LDS (this wavefront's words): sel rows of
@@ -537,7 +640,7 @@ struct LtSel {
     x |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x122, 0xf, 0xf, false);
     return x | (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x121, 0xf, 0xf, false);
   }
-  __device__ __forceinline__ unsigned word(int w) const { return __builtin_amdgcn_readfirstlane(tiles[w]); }
+  __device__ __forceinline__ bool has_tile(int t) const { return (tiles[t >> 5] >> (t & 31)) & 1u; }
   // did the lane's row select the block of its keys (four keys from key0 on share one)?  Only asked about tiles in `tiles`.
   __device__ __forceinline__ bool sees(int q, int key0) const
   {
@@ -601,6 +704,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     else return Rows<T, D>(Vh, p.L, q, g);
   }();
   const float c2 = p.scale * kLog2eF;
+  const LaneMasks lm = LaneMasks::make(p, q, g);
   unsigned *my_lds = reinterpret_cast<unsigned *>(small_lds + 2 * pitch) + wv * lt_words(p, PERPOS);
 
   for (int hh = 0; hh < heads; ++hh)
@@ -635,15 +739,12 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     const int J_hi = p.bidir ? NT - 1 : I;
     // the walk of word w
     Walk wk;
-    auto word = [&](int w) __attribute__((always_inline)) {
-      unsigned dia = 0u;
-      const unsigned lt = dense ? word_range(w, T0, I) : ls.word(w);
-      const unsigned st = dense ? 0u : st_word<false>(p, I, w, T0, J_hi, lane, dia);
-      unsigned edge = word_range(w, T0, T0) | word_range(w, I, I) | word_range(w, NT - 1, NT - 1) | word_range(w, p.last_lo / kTile, NT - 1);
+    auto word = [&](int w, bool dia) __attribute__((always_inline)) {
+      const int t = w * 64 + lane;
       // (two query blocks per tile: a row's sums must not depend on what the other block selected, which the serving mode does
       // not know, so every short-term tile is general there and the order of the walk follows from the geometry)
-      if (BK < kTile && !PERPOS) edge |= st;
-      wk.start(w, lt, st, edge, dia);
+      const bool edge = (BK < kTile && !PERPOS) | (t == T0) | (t == I) | (t >= min(NT - 1, p.last_lo / kTile));
+      wk.start<false>(p, I, w, T0, J_hi, lane, dense || ls.has_tile(min(t, NT - 1)), edge, dia, !dense);
     };
     f32x4 a_lt[NMB], a_st[NMB];
 #pragma unroll
@@ -673,44 +774,80 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
         for (int mb = 0; mb < NMB; ++mb) a_st[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[mb][r], e[r], a_st[mb], 0, 0, 0);
     };
-    // visibility of this lane's four keys of a general tile
-    auto see = [&](auto unit, int t, bool (&v_lt)[4], bool (&v_st)[4]) __attribute__((always_inline)) {
+    // visibility of this lane's four keys of a general tile: element by element, and as bits where distances decide (`near`)
+    auto see = [&](int t, bool (&v_lt)[4], bool (&v_st)[4]) __attribute__((always_inline)) {
       const int key0 = t * kTile + 4 * g;
       const unsigned span = (unsigned)((p.bidir ? p.L - 1 : iq) - p0);
-      bool s_lt = (wk.lt >> (t & 31)) & 1u;
+      bool s_lt = wk.is_lt(t);
       if ((PERPOS || BK < kTile) && !dense) s_lt &= ls.sees(q, key0);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const bool ok = (unsigned)(key0 + r - p0) <= span;
         v_lt[r] = ok & s_lt;
-        v_st[r] = ok & st_sees<decltype(unit)::value>(p, iq, key0 + r, kid_q, mask_block(p, key0, r), key0 + r >= p.last_lo);
+        v_st[r] = ok & st_sees(p, iq, key0 + r, kid_q, mask_block(p, key0, r), key0 + r >= p.last_lo);
       }
     };
-    const int dr = (q >> 2) == g ? (q & 3) : 4;  // which of the lane's four keys of a diagonal tile its row sees (4: none)
+    auto see_near = [&](int t, unsigned &v_lt, unsigned &v_st) __attribute__((always_inline)) {
+      const int key0 = t * kTile + 4 * g;
+      const unsigned ok = LaneMasks::keys(p, key0, p0, iq);
+      v_st = (lm.st(p, I - t) | LaneMasks::from(p.last_lo - key0)) & ok;
+      bool s_lt = wk.is_lt(t);
+      if ((PERPOS || BK < kTile) && !dense) s_lt &= ls.sees(q, key0);
+      v_lt = s_lt ? ok : 0u;
+    };
+    if (p.sblk == 1 && !dense)
+      diagonals(p, I, T0, J_hi, [&](int d) __attribute__((always_inline)) {
+        float s[4], e[4], vo[4][NMB][4];
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+          float kr[CPL];
+          Kr.row(min(max(I + d * (1 << n), T0), NT - 1), kr);
+          s[n] = dot_n(qf, kr, 0.0f);
+        }
+        phase_end<D>();
+#pragma unroll
+        for (int n = 0; n < 4; ++n) Vr.own(min(max(I + d * (1 << n), T0), NT - 1), vo[n]);
+        const float x = gather_g(s);
+        const int key = iq + kTile * d * (1 << g);
+        const bool ok = active & (key >= p0) & (key < p.last_lo);
+        s_max = fmaxf(s_max, ok ? fabsf(x) : 0.0f);
+        const float ex = ok ? __builtin_amdgcn_exp2f(x) : 0.0f;
+        l_st += ex;
+        spread_g(ex, e);
+#pragma unroll
+        for (int n = 0; n < 4; ++n) add_own(a_st, e[n], vo[n]);
+      });
     // one tile: the next one's keys are requested as soon as this one's are in the matrix cores, its values at the end
-    auto body = [&](auto kind, auto unit, unsigned &mask) __attribute__((always_inline)) {
+    auto body = [&](auto kind, auto unit, Word &mask) __attribute__((always_inline)) {
       constexpr int KIND = decltype(kind)::value;
-      const int t = wk.base + __builtin_ctz(mask);
-      mask &= mask - 1;
-      const int t_next = wk.peek();
+      constexpr bool UNIT = decltype(unit)::value;
+      const int t = wk.take(mask), t_next = wk.peek();
       const f32x4 s = logits();
       Kr.row(t_next, kf);
       if constexpr (TileRows::kNear) Vr.col(t, vf);
       s_max = fmaxf(fmaxf(s_max, fabsf(s[0])), fabsf(s[1]));
       s_max = fmaxf(fmaxf(s_max, fabsf(s[2])), fabsf(s[3]));
       float e[4];
-      if constexpr (KIND != 3) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) e[r] = __builtin_amdgcn_exp2f(s[r]);
-      }
+      for (int r = 0; r < 4; ++r) e[r] = __builtin_amdgcn_exp2f(s[r]);
       if constexpr (KIND == 0) {
-        bool v_lt[4], v_st[4];
-        see(unit, t, v_lt, v_st);
         float el[4], es[4];
+        if constexpr (UNIT) {
+          unsigned v_lt, v_st;
+          see_near(t, v_lt, v_st);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          el[r] = v_lt[r] ? e[r] : 0.0f;
-          es[r] = v_st[r] ? e[r] : 0.0f;
+          for (int r = 0; r < 4; ++r) {
+            el[r] = keep(e[r], v_lt, r);
+            es[r] = keep(e[r], v_st, r);
+          }
+        } else {
+          bool v_lt[4], v_st[4];
+          see(t, v_lt, v_st);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            el[r] = v_lt[r] ? e[r] : 0.0f;
+            es[r] = v_st[r] ? e[r] : 0.0f;
+          }
         }
         add_lt(el);
         add_st(es);
@@ -721,32 +858,30 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
           for (int r = 0; r < 4; ++r) e[r] = v ? e[r] : 0.0f;
         }
         add_lt(e);
-      } else if constexpr (KIND == 2) {
-        const int key0 = t * kTile + 4 * g;
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          e[r] = st_sees<decltype(unit)::value>(p, iq, key0 + r, kid_q, mask_block(p, key0, r), false) ? e[r] : 0.0f;
-        add_st(e);
       } else {
-        const float sd = dr == 0 ? s[0] : dr == 1 ? s[1] : dr == 2 ? s[2] : s[3];
-        const float ed = __builtin_amdgcn_exp2f(sd);
+        if constexpr (UNIT) {
+          const unsigned v = lm.st(p, I - t);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) e[r] = dr == r ? ed : 0.0f;
+          for (int r = 0; r < 4; ++r) e[r] = keep(e[r], v, r);
+        } else {
+          const int key0 = t * kTile + 4 * g;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) e[r] = st_sees(p, iq, key0 + r, kid_q, mask_block(p, key0, r), false) ? e[r] : 0.0f;
+        }
         add_st(e);
       }
       if constexpr (!TileRows::kNear) Vr.col(t_next, vf);
     };
     auto walk = [&](auto unit) __attribute__((always_inline)) {
-      for (int w = T0 >> 5; w <= J_hi >> 5; ++w) {
-        word(w);
-        if (!wk.any()) continue;
+      for (int w = T0 >> 6; w <= J_hi >> 6; ++w) {
+        word(w, false);
+        if (!wk.all()) continue;
         const int t = wk.peek();
         Kr.row(t, kf);
         if constexpr (!TileRows::kNear) Vr.col(t, vf);
         while (wk.m0) body(std::integral_constant<int, 0>{}, unit, wk.m0);
         while (wk.m1) body(std::integral_constant<int, 1>{}, unit, wk.m1);
         while (wk.m2) body(std::integral_constant<int, 2>{}, unit, wk.m2);
-        while (wk.m3) body(std::integral_constant<int, 3>{}, unit, wk.m3);
       }
     };
     if (p.sblk <= 1) walk(std::true_type{});
@@ -756,16 +891,16 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
       // against them
       float x_lt = kNegInfF, x_st = kNegInfF;
       auto each = [&](auto f) __attribute__((always_inline)) {
-        for (int w = T0 >> 5; w <= J_hi >> 5; ++w) {
-          word(w);
-          for (unsigned m = wk.m0 | wk.m1 | wk.m2 | wk.m3; m; m &= m - 1) f(wk.base + __builtin_ctz(m));
+        for (int w = T0 >> 6; w <= J_hi >> 6; ++w) {
+          word(w, true);
+          for (Word m = wk.all(); m;) f(wk.take(m));
         }
       };
       each([&](int J) {
         Kr.row(J, kf);
         const f32x4 s = logits();
         bool v_lt[4], v_st[4];
-        see(std::false_type{}, J, v_lt, v_st);
+        see(J, v_lt, v_st);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           x_lt = fmaxf(x_lt, v_lt[r] ? s[r] : kNegInfF);
@@ -786,7 +921,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
         float lost[4];
         take_out(vf, g, lost);
         bool v_lt[4], v_st[4];
-        see(std::false_type{}, J, v_lt, v_st);
+        see(J, v_lt, v_st);
         float el[4], es[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -891,18 +1026,25 @@ struct QueryHead {
   {
   }
 };
-// the gate of one head, this lane's channels of its row, and the running gradient sums of the rows this wavefront took
+// the gate of one head, and the running gradient sums of the rows this wavefront took over this lane's channels
 template <int D>
 struct GateSums {
-  float wl[Geo<D>::CPL], ws[Geo<D>::CPL], bias, gl[Geo<D>::CPL], gs[Geo<D>::CPL], gb;
-  __device__ __forceinline__ GateSums(const float *gate_w, const float *gate_b, int h, int g)
+  const float *w;
+  float bias, gl[Geo<D>::CPL], gs[Geo<D>::CPL], gb;
+  __device__ __forceinline__ GateSums(const float *gate_w, const float *gate_b, int h) : w(gate_w + (size_t)h * 2 * D)
   {
-    load_n<Geo<D>::CPL>(gate_w + (size_t)h * 2 * D + Geo<D>::CPL * g, wl);
-    load_n<Geo<D>::CPL>(gate_w + (size_t)h * 2 * D + D + Geo<D>::CPL * g, ws);
     bias = gate_b ? gate_b[h] : 0.0f;
     zero_n(gl);
     zero_n(gs);
     gb = 0.0f;
+  }
+  // this lane's weights, read anew for every tile: in registers through the walk of d = 32 they make others spill
+  __device__ __forceinline__ void weights(int g, float (&wl)[Geo<D>::CPL], float (&ws)[Geo<D>::CPL]) const
+  {
+    int at = Geo<D>::CPL * g;
+    asm volatile("" : "+v"(at));
+    load_n<Geo<D>::CPL>(w + at, wl);
+    load_n<Geo<D>::CPL>(w + at + D, ws);
   }
   // sums over the 16 rows of the lanes, then over the workgroup's W wavefronts in order, to out[2D+1]; red: [kMaxWaves][2D+1] in LDS
   __device__ __forceinline__ void finish(float (*red)[2 * D + 1], float *out, int lane, int wv, int W)
@@ -938,14 +1080,15 @@ struct GateSums {
 template <typename T, int D, int BK, bool PERPOS, bool CAREFUL, typename TileRows, typename Sink>
 __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int NT, int p0, int lane, const QueryHead &in,
                                            const TileRows &Kr, const TileRows &Vr, const int *sel_head, unsigned *my_lds,
-                                           GateSums<D> &gate, bool do_rows, bool do_dq, T *dQ_head, Sink &&sink)
+                                           GateSums<D> &gate, const LaneMasks &lm, bool do_rows, bool do_dq, T *dQ_head, Sink &&sink)
 {
   constexpr int CPL = Geo<D>::CPL, NMB = Geo<D>::NMB;
   const int q = lane & 15, g = lane >> 4;
   const float c2 = p.scale * kLog2eF;
   const int iq = I * kTile + q;
   const bool active = iq < p.L && iq >= p0;
-  float qf[CPL], gr[CPL], ol[CPL], os[CPL];
+  float qf[CPL], gr[CPL], ol[CPL], os[CPL], wl[CPL], ws[CPL];
+  gate.weights(g, wl, ws);
   const unsigned e_at = active ? (unsigned)(iq * D + CPL * g) : kNowhere / 4;  // rows that take no part read zeros
   load_n<T>(in.dO, e_at * (unsigned)sizeof(T), gr);
   load_n<float>(in.o_lt, e_at * 4u, ol);
@@ -961,7 +1104,7 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
 
   // ---- gate pass of the tile's rows ----
   const float a_ll = sum_g(dot_n(gr, ol, 0.0f)), a_ss = sum_g(dot_n(gr, os, 0.0f));
-  const float w_l = sum_g(dot_n(gate.wl, ol, 0.0f)), w_s = sum_g(dot_n(gate.ws, os, 0.0f));
+  const float w_l = sum_g(dot_n(wl, ol, 0.0f)), w_s = sum_g(dot_n(ws, os, 0.0f));
   float al = sigmoid(gate.bias + w_l + w_s);
   float dz = (a_ll - a_ss) * al * (1.0f - al);
   float D_lt = al * a_ll + dz * w_l, D_st = (1.0f - al) * a_ss + dz * w_s;
@@ -980,15 +1123,14 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
 #pragma unroll
   for (int i = 0; i < CPL; ++i) {
     qf[i] *= c2;
-    ol[i] = fmaf(al, gr[i], dz * gate.wl[i]);         // dO_lt of this lane's row
-    os[i] = fmaf(1.0f - al, gr[i], dz * gate.ws[i]);  // dO_st
+    ol[i] = fmaf(al, gr[i], dz * wl[i]);         // dO_lt of this lane's row
+    os[i] = fmaf(1.0f - al, gr[i], dz * ws[i]);  // dO_st
   }
   f32x4 dq[NMB];
   clear(dq);
   const int kid_q = mask_block(p, iq);
   const int J_hi = p.bidir ? NT - 1 : I;
   Walk wk;
-  const int dr = (q >> 2) == g ? (q & 3) : 4;
   float kf[CPL], vf[CPL], kc[NMB][4];
   auto products = [&](auto lt, auto st, f32x4 &s, f32x4 &g_lt, f32x4 &g_st) __attribute__((always_inline)) {
     s = g_lt = g_st = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -1001,7 +1143,7 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
   };
   // did the lane's row select the tile, and is the key one that the causal and validity tests let through?
   auto selected = [&](int t) __attribute__((always_inline)) -> bool {
-    bool x = (wk.lt >> (t & 31)) & 1u;
+    bool x = wk.is_lt(t);
     if (PERPOS || BK < kTile) x &= ls.sees(q, t * kTile + 4 * g);
     return x;
   };
@@ -1013,11 +1155,10 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
 #pragma unroll
       for (int mb = 0; mb < NMB; ++mb) dq[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kc[mb][r], ds[r], dq[mb], 0, 0, 0);
   };
-  auto body = [&](auto kind, auto unit, unsigned &mask) __attribute__((always_inline)) {
+  auto body = [&](auto kind, auto unit, Word &mask) __attribute__((always_inline)) {
     constexpr int KIND = decltype(kind)::value;
-    const int t = wk.base + __builtin_ctz(mask);
-    mask &= mask - 1;
-    const int t_next = wk.peek();
+    constexpr bool UNIT = decltype(unit)::value;
+    const int t = wk.take(mask), t_next = wk.peek();
     f32x4 s, g_lt, g_st;
     products(std::bool_constant<KIND <= 1>{}, std::bool_constant<KIND != 1>{}, s, g_lt, g_st);
     Kr.row(t_next, kf);
@@ -1026,13 +1167,24 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
     float ds[4];
     if constexpr (KIND == 0) {
       const bool s_lt = selected(t);
+      unsigned v_lt = 0u, v_st = 0u;
+      if constexpr (UNIT) {
+        const unsigned ok = LaneMasks::keys(p, key0, p0, iq);
+        v_st = (lm.st(p, I - t) | LaneMasks::from(p.last_lo - key0)) & ok;
+        v_lt = s_lt ? ok : 0u;
+      }
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const bool ok = seen(key0 + r);
-        const bool v_st = ok & st_sees<decltype(unit)::value>(p, iq, key0 + r, kid_q, mask_block(p, key0, r), key0 + r >= p.last_lo);
-        const float e = __builtin_amdgcn_exp2f(s[r] - l2_lt), f = __builtin_amdgcn_exp2f(s[r] - l2_st);
-        ds[r] = (ok & s_lt ? e : 0.0f) * (g_lt[r] - D_lt);
-        ds[r] = fmaf(v_st ? f : 0.0f, g_st[r] - D_st, ds[r]);
+        float e = __builtin_amdgcn_exp2f(s[r] - l2_lt), f = __builtin_amdgcn_exp2f(s[r] - l2_st);
+        if constexpr (UNIT) {
+          e = keep(e, v_lt, r);
+          f = keep(f, v_st, r);
+        } else {
+          const bool ok = seen(key0 + r);
+          e = ok & s_lt ? e : 0.0f;
+          f = ok & st_sees(p, iq, key0 + r, kid_q, mask_block(p, key0, r), key0 + r >= p.last_lo) ? f : 0.0f;
+        }
+        ds[r] = fmaf(f, g_st[r] - D_st, e * (g_lt[r] - D_lt));
       }
     } else if constexpr (KIND == 1) {
       const bool v = (PERPOS || BK < kTile) ? ls.sees(q, key0) : true;
@@ -1041,34 +1193,29 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
         const float e = __builtin_amdgcn_exp2f(s[r] - l2_lt);
         ds[r] = ((PERPOS || BK < kTile) ? (v ? e : 0.0f) : e) * (g_lt[r] - D_lt);
       }
-    } else if constexpr (KIND == 2) {
+    } else {
+      const unsigned v = UNIT ? lm.st(p, I - t) : 0u;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float e = __builtin_amdgcn_exp2f(s[r] - l2_st);
-        ds[r] = (st_sees<decltype(unit)::value>(p, iq, key0 + r, kid_q, mask_block(p, key0, r), false) ? e : 0.0f) * (g_st[r] - D_st);
+        float e = __builtin_amdgcn_exp2f(s[r] - l2_st);
+        if constexpr (UNIT) e = keep(e, v, r);
+        else e = st_sees(p, iq, key0 + r, kid_q, mask_block(p, key0, r), false) ? e : 0.0f;
+        ds[r] = e * (g_st[r] - D_st);
       }
-    } else {
-      const float sd = dr == 0 ? s[0] : dr == 1 ? s[1] : dr == 2 ? s[2] : s[3];
-      const float gd = dr == 0 ? g_st[0] : dr == 1 ? g_st[1] : dr == 2 ? g_st[2] : g_st[3];
-      const float x = __builtin_amdgcn_exp2f(sd - l2_st) * (gd - D_st);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) ds[r] = dr == r ? x : 0.0f;
     }
     if constexpr (TileRows::kNear) Kr.col(t, kc);
     add(ds);
     if constexpr (!TileRows::kNear) Kr.col(t_next, kc);
   };
   auto word = [&](int w) __attribute__((always_inline)) {
-    unsigned dia;
-    const unsigned st = st_word<false>(p, I, w, T0, J_hi, lane, dia);
-    const unsigned edge =
-        word_range(w, T0, T0) | word_range(w, I, I) | word_range(w, NT - 1, NT - 1) | word_range(w, p.last_lo / kTile, NT - 1);
-    wk.start(w, ls.word(w), st, edge, dia);
+    const int t = w * 64 + lane;
+    const bool edge = (t == T0) | (t == I) | (t >= min(NT - 1, p.last_lo / kTile));
+    wk.start<false>(p, I, w, T0, J_hi, lane, ls.has_tile(min(t, NT - 1)), edge, CAREFUL, true);
   };
   auto walk = [&](auto unit) __attribute__((always_inline)) {
-    for (int w = T0 >> 5; w <= J_hi >> 5; ++w) {
+    for (int w = T0 >> 6; w <= J_hi >> 6; ++w) {
       word(w);
-      if (!wk.any()) continue;
+      if (!wk.all()) continue;
       const int t = wk.peek();
       Kr.row(t, kf);
       Vr.row(t, vf);
@@ -1076,17 +1223,41 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
       while (wk.m0) body(std::integral_constant<int, 0>{}, unit, wk.m0);
       while (wk.m1) body(std::integral_constant<int, 1>{}, unit, wk.m1);
       while (wk.m2) body(std::integral_constant<int, 2>{}, unit, wk.m2);
-      while (wk.m3) body(std::integral_constant<int, 3>{}, unit, wk.m3);
     }
   };
   if constexpr (!CAREFUL) {
+    if (p.sblk == 1)
+      diagonals(p, I, T0, J_hi, [&](int d) __attribute__((always_inline)) {
+        float s[4], x[4], ko[4][NMB][4];
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+          float kr[CPL], vr[CPL];
+          const int t = min(max(I + d * (1 << n), T0), NT - 1);
+          Kr.row(t, kr);
+          Vr.row(t, vr);
+          s[n] = dot_n(qf, kr, 0.0f);
+          x[n] = dot_n(os, vr, 0.0f);
+          if constexpr (D == 16) own_of_row(kr, ko[n]);
+        }
+        phase_end<D>();
+        if constexpr (D != 16) {
+#pragma unroll
+          for (int n = 0; n < 4; ++n) Kr.own(min(max(I + d * (1 << n), T0), NT - 1), ko[n]);
+        }
+        const float e = __builtin_amdgcn_exp2f(gather_g(s) - l2_st), gv = gather_g(x);
+        const int key = iq + kTile * d * (1 << g);
+        const bool ok = (key >= p0) & (key < p.last_lo);
+        spread_g(ok ? e * (gv - D_st) : 0.0f, x);
+#pragma unroll
+        for (int n = 0; n < 4; ++n) add_own(dq, x[n], ko[n]);
+      });
     if (p.sblk <= 1) walk(std::true_type{});
     else walk(std::false_type{});
   } else {
-    for (int w = T0 >> 5; w <= J_hi >> 5; ++w) {
+    for (int w = T0 >> 6; w <= J_hi >> 6; ++w) {
       word(w);
-      for (unsigned m = wk.m0 | wk.m1 | wk.m2 | wk.m3; m; m &= m - 1) {
-        const int t = wk.base + __builtin_ctz(m);
+      for (Word m = wk.all(); m;) {
+        const int t = wk.take(m);
         Kr.row(t, kf);
         Vr.row(t, vf);
         Kr.col(t, kc);
@@ -1099,7 +1270,7 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const bool ok = seen(key0 + r);
-          const bool v_st = ok & st_sees<false>(p, iq, key0 + r, kid_q, mask_block(p, key0, r), key0 + r >= p.last_lo);
+          const bool v_st = ok & st_sees(p, iq, key0 + r, kid_q, mask_block(p, key0, r), key0 + r >= p.last_lo);
           const float e = __builtin_amdgcn_exp2f(s[r] - l2_lt), f = __builtin_amdgcn_exp2f(s[r] - l2_st);
           ds[r] = ok & s_lt ? fmaf(e, g_lt[r] - D_lt, lost[r]) : 0.0f;
           ds[r] += v_st ? fmaf(f, g_st[r] - D_st, lost[r]) : 0.0f;
@@ -1135,7 +1306,7 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
   const int I_lo = p.bidir ? T0 : J;
   const int Jb = j / BK;  // this lane's key block
   const bool last_tile = J * kTile + kTile - 1 >= p.last_lo;  // holds last-block keys
-  const int dr = (q >> 2) == g ? (q & 3) : 4;
+  const LaneMasks lm = LaneMasks::make(p, q, g);
 
   for (int hl = 0; hl < hpg; ++hl) {
     const auto Qr = src.q_rows(hl);
@@ -1192,12 +1363,10 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
           dk[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(qc[mb][r], ds[r], dk[mb], 0, 0, 0);
         }
     };
-    auto body = [&](auto kind, auto unit, unsigned &mask) __attribute__((always_inline)) {
+    auto body = [&](auto kind, auto unit, Word &mask) __attribute__((always_inline)) {
       constexpr int KIND = decltype(kind)::value;
-      constexpr bool LT = KIND <= 1, ST = KIND != 1;
-      const int t = wk.base + __builtin_ctz(mask);
-      mask &= mask - 1;
-      const int t_next = wk.peek();
+      constexpr bool LT = KIND <= 1, ST = KIND != 1, UNIT = decltype(unit)::value;
+      const int t = wk.take(mask), t_next = wk.peek();
       if constexpr (near) consts(t);
       f32x4 s, gv;
       products(s, gv);
@@ -1207,42 +1376,40 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
       float pc[4], ds[4];
       unsigned w4[4] = {1u, 1u, 1u, 1u};
       if constexpr (LT) selected(t, w4);
-      if constexpr (KIND != 3) {
-        const bool in_lt = KIND != 0 || ((wk.lt >> (t & 31)) & 1u) != 0u;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          bool ok = true;
-          if constexpr (KIND == 0) ok = (i0 + r >= j) | (p.bidir != 0);
-          pc[r] = ds[r] = 0.0f;
-          if constexpr (LT) {
-            const float e = __builtin_amdgcn_exp2f(s[r] - l_lt[r]);
-            const float pr = (KIND == 0 || PERPOS || BK < kTile) ? (ok & in_lt & ((w4[r] & 1u) != 0u) ? e : 0.0f) : e;
-            pc[r] = al[r] * pr;
-            ds[r] = pr * fmaf(al[r], gv[r], fmaf(dz[r], wv_lt, -D_lt[r]));
-            t_lt = fmaf(dz[r], pr, t_lt);
-          }
-          if constexpr (ST) {
-            const float e = __builtin_amdgcn_exp2f(s[r] - l_st[r]);
-            const float pr = ok & st_sees<decltype(unit)::value>(p, i0 + r, j, mask_block(p, i0, r), kid_k, KIND == 0 ? last_k : false) ? e : 0.0f;
-            const float as = 1.0f - al[r];
-            pc[r] = fmaf(as, pr, pc[r]);
-            ds[r] = fmaf(pr, fmaf(as, gv[r], fmaf(dz[r], wv_st, -D_st[r])), ds[r]);
-            t_st = fmaf(dz[r], pr, t_st);
-          }
+      const bool in_lt = KIND != 0 || wk.is_lt(t);
+      unsigned v_lt = 15u, v_st = 0u;  // UNIT: the masks as bits
+      if constexpr (UNIT) {
+        if constexpr (ST) v_st = lm.st(p, J - t);
+        if constexpr (KIND == 0) {
+          const unsigned ok = LaneMasks::from(p.bidir ? 0 : j - i0);
+          v_st = (last_k ? 15u : v_st) & ok;
+          v_lt = in_lt ? ok : 0u;
         }
-      } else {
-        auto pick = [&](const float (&x)[4]) { return dr == 0 ? x[0] : dr == 1 ? x[1] : dr == 2 ? x[2] : x[3]; };
-        const float sd = dr == 0 ? s[0] : dr == 1 ? s[1] : dr == 2 ? s[2] : s[3];
-        const float gd = dr == 0 ? gv[0] : dr == 1 ? gv[1] : dr == 2 ? gv[2] : gv[3];
-        const float zd = pick(dz), as = 1.0f - pick(al);
-        const float e = __builtin_amdgcn_exp2f(sd - pick(l_st));
-        const float pr = dr < 4 ? e : 0.0f;
-        const float xp = as * pr, xs = pr * fmaf(as, gd, fmaf(zd, wv_st, -pick(D_st)));
-        t_st = fmaf(zd, pr, t_st);
+      }
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          pc[r] = dr == r ? xp : 0.0f;
-          ds[r] = dr == r ? xs : 0.0f;
+      for (int r = 0; r < 4; ++r) {
+        bool ok = true;
+        if constexpr (KIND == 0 && !UNIT) ok = (i0 + r >= j) | (p.bidir != 0);
+        pc[r] = ds[r] = 0.0f;
+        if constexpr (LT) {
+          const float e = __builtin_amdgcn_exp2f(s[r] - l_lt[r]);
+          float pr = e;
+          if constexpr (KIND == 0 && UNIT) pr = keep(pr, v_lt, r);
+          if constexpr (KIND == 0 && !UNIT) pr = ok & in_lt ? pr : 0.0f;
+          if constexpr (PERPOS || BK < kTile) pr = keep(pr, w4[r], 0);
+          pc[r] = al[r] * pr;
+          ds[r] = pr * fmaf(al[r], gv[r], fmaf(dz[r], wv_lt, -D_lt[r]));
+          t_lt = fmaf(dz[r], pr, t_lt);
+        }
+        if constexpr (ST) {
+          const float e = __builtin_amdgcn_exp2f(s[r] - l_st[r]);
+          float pr = e;
+          if constexpr (UNIT) pr = keep(pr, v_st, r);
+          else pr = ok & st_sees(p, i0 + r, j, mask_block(p, i0, r), kid_k, KIND == 0 ? last_k : false) ? pr : 0.0f;
+          const float as = 1.0f - al[r];
+          pc[r] = fmaf(as, pr, pc[r]);
+          ds[r] = fmaf(pr, fmaf(as, gv[r], fmaf(dz[r], wv_st, -D_st[r])), ds[r]);
+          t_st = fmaf(dz[r], pr, t_st);
         }
       }
       if constexpr (!near) {
@@ -1258,17 +1425,14 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
       }
     };
     auto word = [&](int w) __attribute__((always_inline)) {
-      const int I = w * 32 + (lane & 31);
-      const unsigned tw = src.tile_word(min(max(I, T0), NT - 1), J >> 5);
-      const unsigned lt = (unsigned)__ballot((lane < 32) & ((tw >> (J & 31)) & 1u)) & word_range(w, I_lo, NT - 1);
-      unsigned dia;
-      const unsigned st = st_word<true>(p, J, w, I_lo, NT - 1, lane, dia);
-      wk.start(w, lt, st, last_tile ? 0xFFFFFFFFu : word_range(w, J, J), dia);
+      const int t = w * 64 + lane;
+      const unsigned tw = src.tile_word(min(max(t, T0), NT - 1), J >> 5);
+      wk.start<true>(p, J, w, I_lo, NT - 1, lane, (tw >> (J & 31)) & 1u, last_tile | (t == J), CAREFUL, true);
     };
     auto walk = [&](auto unit) __attribute__((always_inline)) {
-      for (int w = I_lo >> 5; w <= (NT - 1) >> 5; ++w) {
+      for (int w = I_lo >> 6; w <= (NT - 1) >> 6; ++w) {
         word(w);
-        if (!wk.any()) continue;
+        if (!wk.all()) continue;
         const int t = wk.peek();
         Qr.row(t, qa);
         Gr.row(t, ga);
@@ -1280,14 +1444,13 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
         while (wk.m0) body(std::integral_constant<int, 0>{}, unit, wk.m0);
         while (wk.m1) body(std::integral_constant<int, 1>{}, unit, wk.m1);
         while (wk.m2) body(std::integral_constant<int, 2>{}, unit, wk.m2);
-        while (wk.m3) body(std::integral_constant<int, 3>{}, unit, wk.m3);
       }
     };
     auto walk_carefully = [&]() __attribute__((always_inline)) {
-      for (int w = I_lo >> 5; w <= (NT - 1) >> 5; ++w) {
+      for (int w = I_lo >> 6; w <= (NT - 1) >> 6; ++w) {
         word(w);
-        for (unsigned m = wk.m0 | wk.m1 | wk.m2 | wk.m3; m; m &= m - 1) {
-          const int t = wk.base + __builtin_ctz(m);
+        for (Word m = wk.all(); m;) {
+          const int t = wk.take(m);
           consts(t);
           Qr.row(t, qa);
           Gr.row(t, ga);
@@ -1300,14 +1463,14 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
           float lost_q[4], lost_g[4];
           take_out(qc, g, lost_q);
           take_out(gc, g, lost_g);
-          const bool in_lt = (wk.lt >> (t & 31)) & 1u;
+          const bool in_lt = wk.is_lt(t);
           float pc[4], ds[4];
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const int i = t * kTile + 4 * g + r;
             const bool ok = (i >= p0) & (i < p.L) & ((i >= j) | (p.bidir != 0));
             const bool v_lt = ok & in_lt & ((w4[r] & 1u) != 0u);
-            const bool v_st = ok & st_sees<false>(p, i, j, mask_block(p, i), kid_k, last_k);
+            const bool v_st = ok & st_sees(p, i, j, mask_block(p, i), kid_k, last_k);
             const float e = __builtin_amdgcn_exp2f(s[r] - l_lt[r]), f = __builtin_amdgcn_exp2f(s[r] - l_st[r]);
             const float as = 1.0f - al[r];
             pc[r] = v_lt ? fmaf(al[r], e, lost_g[r]) : 0.0f;
@@ -1321,6 +1484,47 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
         }
       }
     };
+    if constexpr (!CAREFUL)
+      if (p.sblk == 1)
+        diagonals(p, J, I_lo, NT - 1, [&](int d) __attribute__((always_inline)) {
+          float s[4], x[4], qo[4][NMB][4], go[4][NMB][4];
+#pragma unroll
+          for (int n = 0; n < 4; ++n) {
+            float qr[CPL], gr[CPL];
+            const int t = min(max(J + d * (1 << n), I_lo), NT - 1);
+            Qr.row(t, qr);
+            Gr.row(t, gr);
+            s[n] = dot_n(kf, qr, 0.0f);
+            x[n] = dot_n(vf, gr, 0.0f);
+            if constexpr (D == 16) {
+              own_of_row(qr, qo[n]);
+              own_of_row(gr, go[n]);
+            }
+          }
+          phase_end<D>();
+          if constexpr (D != 16) {
+#pragma unroll
+            for (int n = 0; n < 4; ++n) {
+              const int t = min(max(J + d * (1 << n), I_lo), NT - 1);
+              Qr.own(t, qo[n]);
+              Gr.own(t, go[n]);
+            }
+          }
+          // this lane group's distance
+          const int i = j + kTile * d * (1 << g), tg = min(max(J + d * (1 << g), I_lo), NT - 1);
+          auto constant = [&](int k) { return src.row_constant(hl, tg, k); };
+          const float e = __builtin_amdgcn_exp2f(gather_g(s) - constant(5)), gd = gather_g(x);
+          const float pr = (i >= p0) & (i < p.L) & !last_k ? e : 0.0f;
+          const float zd = constant(1), as = 1.0f - constant(0);
+          t_st = fmaf(zd, pr, t_st);
+          spread_g(as * pr, s);
+          spread_g(pr * fmaf(as, gd, fmaf(zd, wv_st, -constant(3))), x);
+#pragma unroll
+          for (int n = 0; n < 4; ++n) {
+            add_own(dv, s[n], go[n]);
+            add_own(dk, x[n], qo[n]);
+          }
+        });
     if constexpr (CAREFUL) walk_carefully();
     else if (p.sblk <= 1) walk(std::true_type{});
     else walk(std::false_type{});
@@ -1352,9 +1556,10 @@ __device__ __forceinline__ void query_tiles_carefully(const KParams &p, int firs
                                                       const QueryHead &in, const Rows<T, D> &Kr, const Rows<T, D> &Vr, const int *sel_head,
                                                       unsigned *my_lds, const float *gate_w, const float *gate_b, int h, T *dQ_head)
 {
-  GateSums<D> gate(gate_w, gate_b, h, lane >> 4);
+  GateSums<D> gate(gate_w, gate_b, h);
+  const LaneMasks lm{};
   for (int u = first; u < NT - T0; u += step)
-    query_tile<T, D, BK, PERPOS, true>(p, NT - 1 - u, T0, NT, p0, lane, in, Kr, Vr, sel_head, my_lds, gate, false, true, dQ_head,
+    query_tile<T, D, BK, PERPOS, true>(p, NT - 1 - u, T0, NT, p0, lane, in, Kr, Vr, sel_head, my_lds, gate, lm, false, true, dQ_head,
                                        [](auto &&...) {});
 }
 
@@ -1392,9 +1597,10 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
   const int kvh = PERPOS ? bh / hpg : bh;
   const Rows<T, D> Kr(K + (size_t)kvh * p.L * D, p.L, q, g), Vr(V + (size_t)kvh * p.L * D, p.L, q, g);
   const QueryHead in(Q, dO, o_lt, o_st, lse_lt, lse_st, bh, p.L, D);
-  GateSums<D> gate(gate_w, gate_b, bh % p.H, g);
+  GateSums<D> gate(gate_w, gate_b, bh % p.H);
   unsigned *my_lds = reinterpret_cast<unsigned *>(small_lds) + wv * lt_words(p, PERPOS);
   T *dQ_head = dQ + (size_t)bh * p.L * D;
+  const LaneMasks lm = LaneMasks::make(p, q, g);
   const bool do_rows = stages & kBwdStageGate, do_dq = stages & kBwdStageDQ;
   auto sink = [&](int I, float al, float dz, float D_lt, float D_st, float l2_lt, float l2_st, const LtSel<BK, PERPOS> &ls, const auto &,
                   const auto &) __attribute__((always_inline)) {
@@ -1419,7 +1625,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
       if (do_dq) zero_fill(dQ_head + I * kTile * D, min(kTile, p.L - I * kTile) * D, fresh_lane());
       continue;
     }
-    good &= query_tile<T, D, BK, PERPOS, false>(p, I, T0, NT, p0, lane, in, Kr, Vr, sel_head, my_lds, gate, do_rows, do_dq, dQ_head, sink);
+    good &= query_tile<T, D, BK, PERPOS, false>(p, I, T0, NT, p0, lane, in, Kr, Vr, sel_head, my_lds, gate, lm, do_rows, do_dq, dQ_head, sink);
   }
   if (do_rows) gate.finish(red, ws.partial + ((size_t)bh * parts + part) * GW, lane, wv, W);
   if (__builtin_expect(!good, 0))
@@ -1457,6 +1663,11 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     {
       const Slice rc(rowc + (size_t)(bh0 + hl) * NT * (6 * kTile), (size_t)NT * (6 * kTile) * 4);
       load_n<float>(rc, (unsigned)(I * (6 * kTile) + 16 * k + 4 * g) * 4u, x);
+    }
+    __device__ __forceinline__ float row_constant(int hl, int I, int k) const  // of row q of tile I
+    {
+      const Slice rc(rowc + (size_t)(bh0 + hl) * NT * (6 * kTile), (size_t)NT * (6 * kTile) * 4);
+      return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rc.d, (unsigned)(I * (6 * kTile) + 16 * k + q) * 4u, 0, 0));
     }
     __device__ __forceinline__ unsigned tile_word(int I, int w) const
     {
@@ -1522,11 +1733,12 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
   stage_pair<T, D, true>(K + head_kv, V + head_kv, Ks, Vs, p.L, T0, NT, p0, lane, wv, W);
   __syncthreads();
   const LdsRows<D> Kr(Ks, q, g), Vr(Vs, q, g);
+  const LaneMasks lm = LaneMasks::make(p, q, g);
   const int *sel_head = sel + (size_t)bg * (PERPOS ? p.L : p.NB) * p.k;
   for (int hl = 0; hl < hpg; ++hl) {
     const int bh = bg * hpg + hl;
     const QueryHead in(Q, dO, o_lt, o_st, lse_lt, lse_st, bh, p.L, D);
-    GateSums<D> gate(gate_w, gate_b, bh % p.H, g);
+    GateSums<D> gate(gate_w, gate_b, bh % p.H);
     T *dQ_head = dQ + (size_t)bh * p.L * D;
     auto sink = [&](int I, float al, float dz, float D_lt, float D_st, float l2_lt, float l2_st, const LtSel<BK, PERPOS> &ls,
                     const float (&qf)[CPL], const float (&gr)[CPL]) __attribute__((always_inline)) {
@@ -1552,7 +1764,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
         if (do_dq) zero_fill(dQ_head + I * kTile * D, min(kTile, p.L - I * kTile) * D, fresh_lane());
         continue;
       }
-      query_tile<T, D, BK, PERPOS, false>(p, I, T0, NT, p0, lane, in, Kr, Vr, sel_head, my_lds, gate, true, do_dq, dQ_head, sink);
+      query_tile<T, D, BK, PERPOS, false>(p, I, T0, NT, p0, lane, in, Kr, Vr, sel_head, my_lds, gate, lm, true, do_dq, dQ_head, sink);
     }
     if (hl > 0) __syncthreads();
     gate.finish(red, partial + (size_t)bh * GW, lane, wv, W);  // (its barrier also closes the query tiles of the head)
@@ -1578,6 +1790,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     {
       load_n<4>(rc + (hl * NT + I) * (6 * kTile) + 16 * k + 4 * g, x);
     }
+    __device__ __forceinline__ float row_constant(int hl, int I, int k) const { return rc[(hl * NT + I) * (6 * kTile) + 16 * k + q]; }
     __device__ __forceinline__ unsigned tile_word(int I, int w) const { return words[I * NWt + w]; }
   } src = {QG, rc, gate_w, bits, words, bg * hpg, p.H, NT, NWt, q, g, lay.pitch};
   const Rows<T, D> Kg(K + head_kv, p.L, q, g), Vg(V + head_kv, p.L, q, g);

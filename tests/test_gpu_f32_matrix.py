@@ -172,3 +172,22 @@ def test_many_heads_streamed_tiles_and_large_logits(dtype, d, b, B_, H, L, sblk,
     x.Q *= np.float32(amp)
     pairs = None if B_ * H < 64 else [0, 1, H, B_ * H // 2 + 1, B_ * H - 1]
     run_case(with_shape(w, backward=False), x=x, pairs=pairs, backward=True, gate_scale=0.4)
+
+
+@pytest.mark.parametrize("d,window,L,sblk,bidir", [
+    (8, 1, 130, 1, False),     # the window is the query itself: the powers of two up to 16 come from the neighbouring tile
+    (8, 2, 1100, 1, False),    # distances up to 1024, 70 tiles: two batches of four distances, two words of tiles
+    (16, 17, 300, 1, False),   # the window ends with the neighbouring tile ...
+    (16, 18, 300, 1, False),   # ... one position into the next: distance 32 is then a test of the walk, 64 the first diagonal
+    (16, 33, 513, 1, True),    # the table of distances is full; both directions; past 32 tiles
+    (32, 31, 290, 1, False),   # streamed at d = 32
+    (32, 50, 120, 1, True),    # in LDS, three tiles of window either side
+    (8, 70, 400, 0, False),    # no Eq. 15: window tiles two and more away, whole and cut
+    (32, 40, 1030, 2, True),   # a larger mask block: every test element by element
+])
+def test_window_against_powers_of_two(d, window, L, sblk, bidir):
+    w = with_shape(WORKLOADS["cfg2"], name=f"pow2-d{d}-w{window}-L{L}", B=3, H=2, L=L, d=d, block=16, topk=3, window=window,
+                   len_lo=1, len_hi=L, stis_block=sblk, bidir=bidir, seed=2300 + d + window + L)
+    x = make_inputs(w, want_dO=True)
+    x.valid_len[:] = [L, L - 21, 40]
+    run_case(with_shape(w, backward=False), x=x, backward=True, gate_scale=0.4)
