@@ -57,6 +57,46 @@ __device__ __forceinline__ void zero_rows(T *head_ptr, int row0, int nrows, int 
   for (int o = lane * 16; o < bytes; o += 1024) __builtin_nontemporal_store(z, reinterpret_cast<u32x4_t *>(base + o));
 }
 
+// Masks of a lane's 16 elements of a 32 x 32 accumulator tile, element i being row 4*half + 8*(i/4) + i%4 of the tile, as bits over
+// the 32 rows: bits lo .. hi (any integers; hi < lo: none); and the elements of `x` whose bit is set, `other` in the place of the
+// rest (of a NaN too).  Two vector instructions an element; a range test takes three and a scalar one.
+__device__ __forceinline__ unsigned row_bits(int lo, int hi)
+{
+  const unsigned up_to = hi < 0 ? 0u : 0xFFFFFFFFu >> (31 - min(hi, 31));
+  return lo > 31 ? 0u : up_to & (0xFFFFFFFFu << max(lo, 0));
+}
+__device__ __forceinline__ void keep_rows(f32x16 &x, unsigned bits, int half, float other = 0.0f)
+{
+  const int m = (int)(bits >> (4 * half));
+  const unsigned rest = __float_as_uint(other);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const unsigned keep = (unsigned)__builtin_amdgcn_sbfe(m, 8 * (i >> 2) + (i & 3), 1);
+    x[i] = __uint_as_float((__float_as_uint(x[i]) & keep) | (rest & ~keep));
+  }
+}
+
+// Direct global->LDS loads of 16 bytes a lane, lane l's to dst + 16*l, and the waits that go with them.  In assembly: of the
+// compiler's own form it assumes that any LDS read may touch what is on its way, so a read from a buffer chosen at run time, and
+// every __syncthreads(), waits for all of it, also for what was requested for later.  With these the kernel counts its
+// outstanding requests itself: arrived<N>() returns when at most the last N of the wavefront's are still on their way,
+// arrived_all<N>() when that holds for every wavefront of the workgroup (and every wavefront's LDS reads so far are done).
+__device__ __forceinline__ unsigned lds_address(const void *p) { return (unsigned)(uintptr_t)(const lds_void *)p; }
+__device__ __forceinline__ void load_to_lds(const char *base, unsigned off, unsigned lds)
+{
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory", "m0");
+}
+template <int N>
+__device__ __forceinline__ void arrived()
+{
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+template <int N>
+__device__ __forceinline__ void arrived_all()
+{
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
 // two floats -> one register of two bf16 (round to nearest even in hardware: v_cvt_pk_bf16_f32)
 __device__ __forceinline__ uint32_t pack2_bf16(float a, float b)
 {

@@ -258,8 +258,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
   const int hp_lt = dense ? I * BLK - p0 + 1 < kFewKeys : __builtin_amdgcn_readfirstlane((int)lt_few);
 
   // Zeroes the entries of `x` that the row does not see.
-  // long-term: p0 <= key <= q; window: max(p0, q - w + 1) <= key <= q; per lane one range test on the element's
-  // compile-time key offset
+  // long-term: p0 <= key <= q; window: max(p0, q - w + 1) <= key <= q
   auto mask = [&](int J, bool short_term, f32x16 &x) __attribute__((always_inline)) {
     // (The query row is rebuilt from the lane id inside a volatile asm: everything derived
     // below would otherwise be loop invariant, get hoisted, and sit in registers or spill
@@ -273,9 +272,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     int wlo = q - p.w + 1;
     if (EQ15 && q >= p.last_lo) wlo = min(wlo, p.last_lo);  // third case of Eq. 15: the last block is visible to its own rows
     const int lo = windowed ? max(p0, wlo) : p0;
-    const int base = J * BLK + 4 * lh_;
-    const unsigned span = (unsigned)(q - lo);  // wraps to huge when q < lo: handled by `any`
-    const bool any = q >= lo;
     if (EQ15 && sub && windowed && J < J_lo && J * BLK >= p0) {
       // A block I - 2^r' below the window range, all of it valid: no key of it lies in a window or in
       // the last block, and a mask-block distance 2^r' * (BLK / blk) + delta with |delta| < BLK / blk <=
@@ -290,6 +286,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     }
     if (EQ15 && sub && windowed) {
       // window range as above, or (valid, causal and) a power-of-two mask-block distance, or a last-block key
+      const int base = J * BLK + 4 * lh_;
+      const unsigned span = (unsigned)(q - lo);  // wraps to huge when q < lo: handled by `any`
+      const bool any = q >= lo;
       const unsigned cspan = (unsigned)(q - p0);
       const bool cany = q >= p0;
       const int qmb = q >> sub_sh;
@@ -303,12 +302,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
       }
       return;
     }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int key = base + 8 * (i >> 2) + (i & 3);
-      const bool vis = any & ((unsigned)(key - lo) <= span);
-      x[i] = vis ? x[i] : 0.0f;
-    }
+    keep_rows(x, row_bits(lo - J * BLK, q - J * BLK), lh_);
   };
   // does every row of the block see the whole tile? (uniform)
   auto whole_lt = [&](int J) { return J < I && J * BLK >= p0; };

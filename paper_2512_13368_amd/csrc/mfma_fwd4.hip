@@ -9,6 +9,12 @@
 // A tile is staged cooperatively (each wavefront moves 16 of its 64 rows of K and of V with direct
 // global->LDS loads) and read by all four, so the tile loop has one workgroup barrier per tile;
 // tiles are requested two steps ahead into three buffer pairs.
+// The vector ALUs bound the loop (busy two thirds of the time, the matrix pipe a quarter: a tile's exponentials alone take 16 x 16
+// cycles).  With requests that really stay on their way for two steps (load_to_lds) and masks as bits, selection + forward at
+// B=16 H=8 L=8192 k=16 w=128 take 512 us, 530 before.  Tried and taken back: one walk over both branches without a
+// reference, as at block 32: 504 us, but probabilities of nearly equal logits then lie on either side of one, where bf16 is
+// half as fine as below it (errors of the branch outputs 1.2e-3 and 1.6e-3 instead of 0.8e-3 and 1.1e-3), and keeping them below
+// one takes 16 registers or a subtraction per element more.
 //
 // Per tile a wavefront computes S^T = K Q^T with four v_mfma_f32_32x32x16_bf16 (keys are the M
 // dimension: a lane owns one query column and 16 of its logits), the first of which takes minus the
@@ -35,7 +41,6 @@ constexpr int kFewKeys4 = 32;          // rows seeing fewer keys than this get t
 constexpr float kSumLimit4 = 4096.0f;  // a lane's 16 probabilities of a tile may sum to this (16 * 2^kRaise4)
 constexpr int BLK4 = 64;
 
-constexpr int vmcnt_imm4(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
 
 }  // namespace
 
@@ -144,18 +149,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   const int J_rag = p.L % BLK != 0 ? p.NB - 1 : -2;  // the one block whose rows run past the end, if any
   auto stage = [&](const char *src_head, unsigned lane_off, unsigned odd_xor, uint16_t *dst_tile, int J) __attribute__((always_inline)) {
     const unsigned joff = (unsigned)max(J, 0) * (unsigned)(TILE * 2);  // uniform (block -1: a skipped list entry, all masked)
-    lds_void *dst = (lds_void *)(dst_tile + 16 * wv * D);
-    if (J != J_rag) {
-      __builtin_amdgcn_global_load_lds((glb_void *)(src_head + (joff + lane_off)), dst, 16, 0, 0);
-      __builtin_amdgcn_global_load_lds((glb_void *)(src_head + (joff + (lane_off ^ odd_xor))), dst, 16, 1024, 0);
-    } else {  // last, partial block: rows past the end are clamped (they are causally masked anyway)
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int over = max(0, J * BLK + ld_row + 8 * u - (p.L - 1));
-        const unsigned off = joff + ((u & 1) ? lane_off ^ odd_xor : lane_off) + (unsigned)((8 * u - over) * D * 2);
-        __builtin_amdgcn_global_load_lds((glb_void *)(src_head + off), (lds_void *)(dst_tile + (16 * wv + 8 * u) * D), 16, 0, 0);
-      }
+    const unsigned dst = lds_address(dst_tile) + 16 * wv * D * 2;
+    unsigned second = 8 * D * 2;  // bytes from the first slice's source rows to the second's
+    if (J == J_rag) {  // last, partial block: rows past the end are clamped (they are causally masked anyway)
+      const int over = J * BLK + ld_row - (p.L - 1);
+      lane_off -= (unsigned)(max(over, 0) * (D * 2));
+      second -= (unsigned)((max(over + 8, 0) - max(over, 0)) * (D * 2));
     }
+    load_to_lds(src_head + joff, lane_off, dst);
+    load_to_lds(src_head + joff, (lane_off ^ odd_xor) + second, dst + 8 * D * 2);
   };
 
   // the first tile is on its way while the rest of the prologue runs
@@ -258,8 +260,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     hp_lt = __builtin_amdgcn_readfirstlane((int)lt_few);
   }
 
-  // visible <=> lo <= key <= iq with lo = max(p0, iq - w + 1); per lane one range test on the element's
-  // compile-time key offset
+  // visible <=> lo <= key <= iq with lo = max(p0, iq - w + 1)
   auto mask = [&](int J, bool windowed, f32x16 &s) __attribute__((always_inline)) {
     int ql;  // (rebuilt from the lane id inside a volatile asm so that nothing below is hoisted out of the walk)
     asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ql));
@@ -269,9 +270,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     int wlo = q - p.w + 1;
     if (EQ15 && q >= p.last_lo) wlo = min(wlo, p.last_lo);  // third case of Eq. 15
     const int lo = windowed ? max(p0, wlo) : p0;
-    const int base = J * BLK + 32 * kh + 4 * lh_;
-    const unsigned span = (unsigned)(q - lo);
-    const bool any = q >= lo;
     if (EQ15 && sub && windowed && J < J_lo && J * BLK >= p0) {
       const int qo = q & (BLK - 1);
       const int kb = 32 * kh + 4 * lh_;
@@ -283,6 +281,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
       return;
     }
     if (EQ15 && sub && windowed) {
+      const int base = J * BLK + 32 * kh + 4 * lh_;
+      const unsigned span = (unsigned)(q - lo);
+      const bool any = q >= lo;
       const unsigned cspan = (unsigned)(q - p0);
       const bool cany = q >= p0;
       const int qmb = q >> sub_sh;
@@ -296,12 +297,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
       }
       return;
     }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int key = base + 8 * (i >> 2) + (i & 3);
-      const bool vis = any & ((unsigned)(key - lo) <= span);
-      s[i] = vis ? s[i] : kNegInf;
-    }
+    const int base = J * BLK + 32 * kh;
+    keep_rows(s, row_bits(lo - base, q - base), lh_, kNegInf);
   };
   auto row_max = [&](const f32x16 &s) __attribute__((always_inline)) -> float {
     float m4[4];
@@ -417,18 +414,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   f32x16 fin;
   auto close_branch = [&](uint16_t *kx, uint16_t *vx) __attribute__((always_inline)) -> float {
     __syncthreads();  // every wavefront is past its operand reads of kx, vx: they become exchange space
-    float *area = reinterpret_cast<float *>(wv < 2 ? kx : vx);       // 2 wavefronts x 4 KB per buffer
-    float *mine = area + (wv & 1) * 1024;                            // [16][64] floats
+    float4 *mine = reinterpret_cast<float4 *>(wv < 2 ? kx : vx) + (wv & 1) * 256 + lane;  // [4][64]: 2 wavefronts x 4 KB per buffer
     const int pw = wv ^ 2;                                           // partner: same query group, other key half
-    const float *theirs = reinterpret_cast<const float *>(pw < 2 ? kx : vx) + (pw & 1) * 1024;
+    const float4 *theirs = reinterpret_cast<const float4 *>(pw < 2 ? kx : vx) + (pw & 1) * 256 + lane;
+    auto put = [&](const f32x16 &a) __attribute__((always_inline)) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) mine[64 * g] = make_float4(a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]);
+    };
     const float l_mine = l_run + __shfl_xor(l_run, 32);
     if (kh == 0) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) mine[i * 64 + lane] = oacc[1][i];
+      put(oacc[1]);
       fin = oacc[0];
     } else {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) mine[i * 64 + lane] = oacc[0][i];
+      put(oacc[0]);
       fin = oacc[1];
     }
     if (lh == 0) {
@@ -447,7 +445,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     const float inv = ok ? 1.0f / l_tot : 0.0f;
     const float ga = fa * inv, gb = fb * inv;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) fin[i] = fin[i] * ga + theirs[i * 64 + lane] * gb;
+    for (int g = 0; g < 4; ++g) {
+      const float4 t = theirs[64 * g];
+      fin[4 * g] = fin[4 * g] * ga + t.x * gb;
+      fin[4 * g + 1] = fin[4 * g + 1] * ga + t.y * gb;
+      fin[4 * g + 2] = fin[4 * g + 2] * ga + t.z * gb;
+      fin[4 * g + 3] = fin[4 * g + 3] * ga + t.w * gb;
+    }
     __syncthreads();  // the partner has read this wavefront's rows: they may be refilled
     return ok ? (m + __log2f(l_tot)) * kLn2 : 0.0f;
   };
@@ -467,11 +471,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   if (n_all > 1) {
     stage(Kh, k_lane, 64u, Ks1, J_n1);
     stage(Vh, v_lane, 0u, Vs1, J_n1);
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm4(4));
+    arrived_all<4>();  // tile 0 and the gate weights are in LDS
   } else {
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm4(0));
+    arrived_all<0>();
   }
-  __syncthreads();  // tile 0 and the gate weights are in LDS
   auto step = [&](int t, uint16_t *k_cur, uint16_t *v_cur, uint16_t *k_fill, uint16_t *v_fill) __attribute__((always_inline)) {
     const bool more = t + 2 < n_all;
     if (more) {
@@ -489,9 +492,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
       reset();
       set_ref(0.0f);
     }
-    if (more) __builtin_amdgcn_s_waitcnt(vmcnt_imm4(4));
-    else __builtin_amdgcn_s_waitcnt(vmcnt_imm4(0));
-    __syncthreads();
+    if (more) arrived_all<4>();
+    else arrived_all<0>();
   };
   for (int t = 0; t < n_all; t += 3) {
     step(t, Ks0, Vs0, Ks2, Vs2);
