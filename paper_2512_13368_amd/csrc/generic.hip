@@ -1119,7 +1119,7 @@ static void launch_bwd_small_all(const KParams &p, int dtype, const BwdArgs &a, 
   small_ws_bytes(p, &w, reinterpret_cast<char *>(a.ws));
   launch_bwd_small(p, dtype, a, w, stages, kv_groups, st);
   if (launch_failed()) return;
-  if (stages & kBwdStageGate) launch_gate_reduce(p, a, w.partial, small_partial_rows(p, kv_groups), st);
+  if (stages & kBwdStageGate) launch_gate_reduce(p, a, w.partial, small_partial_rows(p, dtype, kv_groups), st);
 }
 
 void launch_bwd_positions(const KParams &p, int dtype, const BwdArgs &a, int kv_groups, hipStream_t st)

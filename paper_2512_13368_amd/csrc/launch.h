@@ -116,7 +116,7 @@ void launch_fwd_small(const KParams &p, int dtype, const FwdArgs &a, hipStream_t
 bool fwd_positions_supported(const KParams &p);
 bool bwd_positions_supported(const KParams &p);
 size_t small_ws_bytes(const KParams &p, SmallWs *w, char *base);  // carves w from base, returns the total
-int small_partial_rows(const KParams &p, int kv_groups);
+int small_partial_rows(const KParams &p, int dtype, int kv_groups);
 void launch_bwd_small(const KParams &p, int dtype, const BwdArgs &a, const SmallWs &w, unsigned stages, int kv_groups,
                       hipStream_t st);
 

@@ -5,6 +5,7 @@
 // the 64 x 64 bf16 tiles of the other matrix-core kernels would be mostly padding there.
 //
 // Positions are cut into 16-row tiles of v_mfma_f32_16x16x4_f32 (true fp32 products accumulated in fp32)
+// (bf16 storage from d = 16 on: on the bf16 matrix instructions with the same accuracy, see THE MATRIX OPERANDS)
 // whatever the block size; a selection block of 8 is half a tile and the selection is tested per element.
 // A wavefront takes one query tile (forward, dQ) or one key tile (dK/dV) at a time.  Heads that fit a workgroup's LDS
 // (rows of d + 4 floats, two workgroups per CU: L up to 256 at d = 32, 480 at d = 16, 800 at d = 8, less in the backward) are staged
@@ -151,23 +152,151 @@ __device__ __forceinline__ float max_row(float x)
   return fmaxf(x, row_ror<1>(x));
 }
 
-constexpr float kNaN = __builtin_nanf("");
 __device__ __forceinline__ bool finite(float x) { return fabsf(x) <= 3.402823466e38f; }
+
+// THE MATRIX OPERANDS.  Row: a lane's channels of one row, for contractions over channels; Col: its four rows of one channel, for
+// contractions over rows, whose other side is four fp32 coefficients; Split: a row of fp32 values.
+// fp32 storage, and bf16 at d = 8: floats for v_mfma_f32_16x16x4_f32.
+// bf16 storage from d = 16 on: the stored bits for v_mfma_f32_16x16x16_bf16 and 16x16x32, one instruction where the fp32 form takes four
+// or eight, at half the cycles: products of two stored rows are exact either way, and an fp32 side enters as the exact sum of three
+// bf16 terms.  (Against 64 bits the bf16 forms err less, sums of 32 products 2.9e-8 against 3.5e-8, three-term ones of 16
+// 3.3e-8 against 7.3e-8: they round once per instruction.)  At d = 16 a contraction over rows would save nothing: the split
+// of its coefficients takes 22 vector instructions.  A training step at B=256 H=2 L=200 d=32 in the bidirectional form: 145 us
+// with everything as floats, 89 like this.
+template <typename T, int D>
+struct Operands {
+  static constexpr bool kBf = std::is_same<T, bf16_t>::value && D >= 16, kBfCol = kBf && D == 32;
+  static constexpr int CPL = Geo<D>::CPL;
+  struct RowF { float v[CPL]; };
+  struct RowB { unsigned w[CPL / 2]; };
+  struct ColF { float v[4]; };
+  struct ColB { unsigned w[2]; };
+  using Row = std::conditional_t<kBf, RowB, RowF>;
+  using Col = std::conditional_t<kBfCol, ColB, ColF>;
+  struct Split { Row term[kBf ? 3 : 1]; };
+
+  static __device__ __forceinline__ void floats(const Row &a, float (&o)[CPL])
+  {
+#pragma unroll
+    for (int i = 0; i < CPL; ++i) {
+      if constexpr (kBf) o[i] = __uint_as_float((i & 1) ? a.w[i / 2] & 0xFFFF0000u : a.w[i / 2] << 16);
+      else o[i] = a.v[i];
+    }
+  }
+  static __device__ __forceinline__ void clean(Row &a)  // elements that are not finite become zeros
+  {
+    if constexpr (kBf) {
+#pragma unroll
+      for (int i = 0; i < CPL / 2; ++i) {
+        a.w[i] &= (a.w[i] & 0x7F80u) == 0x7F80u ? 0xFFFF0000u : ~0u;
+        a.w[i] &= (a.w[i] & 0x7F800000u) == 0x7F800000u ? 0xFFFFu : ~0u;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < CPL; ++i) a.v[i] = finite(a.v[i]) ? a.v[i] : 0.0f;
+    }
+  }
+  // what the query (or key) side of the logits is multiplied by before (kBf: the logits themselves, after)
+  static __device__ __forceinline__ void scale(Row &a, float c)
+  {
+    if constexpr (!kBf) {
+#pragma unroll
+      for (int i = 0; i < CPL; ++i) a.v[i] *= c;
+    }
+  }
+  static __device__ __forceinline__ f32x4 dot(const Row &a, const Row &b, f32x4 c)
+  {
+    if constexpr (kBf && D == 32) {
+      return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(mfma::bf16x8, a), __builtin_bit_cast(mfma::bf16x8, b), c, 0, 0, 0);
+    } else if constexpr (kBf) {
+      return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(mfma::s16x4, a), __builtin_bit_cast(mfma::s16x4, b), c, 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int i = 0; i < CPL; ++i) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[i], b.v[i], c, 0, 0, 0);
+      return c;
+    }
+  }
+  static __device__ __forceinline__ f32x4 dot(const Row &a, const Split &b, f32x4 c)
+  {
+    if constexpr (kBf) c = dot(a, b.term[1], dot(a, b.term[2], c));
+    return dot(a, b.term[0], c);
+  }
+  // x, y -> their upper halves in one register, what is left of them
+  static __device__ __forceinline__ unsigned upper(float &x, float &y)
+  {
+    const unsigned a = __float_as_uint(x), b = __float_as_uint(y);
+    x -= __uint_as_float(a & 0xFFFF0000u);
+    y -= __uint_as_float(b & 0xFFFF0000u);
+    return __builtin_amdgcn_perm(b, a, 0x07060302u);
+  }
+  static __device__ __forceinline__ Split split(const float (&x)[CPL])
+  {
+    Split s;
+    if constexpr (kBf) {
+#pragma unroll
+      for (int i = 0; i < CPL; i += 2) {
+        float a = x[i], b = x[i + 1];
+#pragma unroll
+        for (int t = 0; t < 3; ++t) s.term[t].w[i / 2] = upper(a, b);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < CPL; ++i) s.term[0].v[i] = x[i];
+    }
+    return s;
+  }
+  // acc += sum over the lanes' rows of e times the operand
+  static __device__ __forceinline__ void add(const Col (&a)[Geo<D>::NMB], const float (&e)[4], f32x4 (&acc)[Geo<D>::NMB])
+  {
+    if constexpr (kBfCol) {
+      ColB c[3];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        float x = e[2 * i], y = e[2 * i + 1];
+#pragma unroll
+        for (int t = 0; t < 3; ++t) c[t].w[i] = upper(x, y);
+      }
+#pragma unroll
+      for (int t = 2; t >= 0; --t)
+#pragma unroll
+        for (int mb = 0; mb < Geo<D>::NMB; ++mb)
+          acc[mb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(mfma::s16x4, a[mb]), __builtin_bit_cast(mfma::s16x4, c[t]),
+                                                              acc[mb], 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int mb = 0; mb < Geo<D>::NMB; ++mb) acc[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mb].v[r], e[r], acc[mb], 0, 0, 0);
+    }
+  }
+  static __device__ __forceinline__ Col col(float x0, float x1, float x2, float x3)  // (of stored values)
+  {
+    if constexpr (kBfCol) return ColB{{upper(x0, x1), upper(x2, x3)}};
+    else return ColF{{x0, x1, x2, x3}};
+  }
+};
+
+constexpr float kNaN = __builtin_nanf("");
 // Takes the elements that are not finite out of a tile's operand (element r of lane (q, g): row 4g + r).  lost[r]: NaN where that
 // row held one, to be added to its coefficient in the columns that see the row, else 0.
-template <int N>
-__device__ __forceinline__ void take_out(float (&x)[N][4], int g, float (&lost)[4])
+template <typename T, int D>
+__device__ __forceinline__ void take_out(typename Operands<T, D>::Col (&a)[Geo<D>::NMB], int g, float (&lost)[4])
 {
+  float x[Geo<D>::NMB][4];
+  bool here[4] = {false, false, false, false};
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    bool here = false;
+  for (int mb = 0; mb < Geo<D>::NMB; ++mb) {
 #pragma unroll
-    for (int mb = 0; mb < N; ++mb) {
-      here |= !finite(x[mb][r]);
+    for (int r = 0; r < 4; ++r) {
+      if constexpr (Operands<T, D>::kBfCol) x[mb][r] = __uint_as_float((r & 1) ? a[mb].w[r / 2] & 0xFFFF0000u : a[mb].w[r / 2] << 16);
+      else x[mb][r] = a[mb].v[r];
+      here[r] |= !finite(x[mb][r]);
       x[mb][r] = finite(x[mb][r]) ? x[mb][r] : 0.0f;
     }
-    lost[r] = ((__ballot(here) >> (16 * g)) & 0xFFFFull) != 0ull ? kNaN : 0.0f;
+    a[mb] = Operands<T, D>::col(x[mb][0], x[mb][1], x[mb][2], x[mb][3]);
   }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) lost[r] = ((__ballot(here[r]) >> (16 * g)) & 0xFFFFull) != 0ull ? kNaN : 0.0f;
 }
 template <int N>
 __device__ __forceinline__ float abs_sum(const f32x4 (&a)[N])
@@ -355,6 +484,28 @@ __device__ __forceinline__ void load_n(const Slice &s, unsigned off, float (&o)[
   }
 }
 
+// N bytes' worth of registers as they stand
+template <int N>
+__device__ __forceinline__ void load_raw(const Slice &s, unsigned off, unsigned (&w)[N])
+{
+  if constexpr (N == 1) {
+    w[0] = __builtin_amdgcn_raw_buffer_load_b32(s.d, off, 0, 0);
+  } else if constexpr (N == 2) {
+    const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(s.d, off, 0, 0);
+    w[0] = v[0]; w[1] = v[1];
+  } else {
+    const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(s.d, off, 0, 0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = v[e];
+  }
+}
+template <typename T, int D>
+__device__ __forceinline__ void load_op(const Slice &s, unsigned off, typename Operands<T, D>::Row &o)
+{
+  if constexpr (Operands<T, D>::kBf) load_raw(s, off, o.w);
+  else load_n<T>(s, off, o.v);
+}
+
 // The lane id, rebuilt where it stands: addresses formed from it are not computed ahead of a walk and kept in registers
 // through it.
 __device__ __forceinline__ int fresh_lane()
@@ -378,20 +529,30 @@ struct Rows {
     col_off = (unsigned)(4 * g * D + (D < 16 ? (q & (D - 1)) : q)) * (unsigned)sizeof(T);
   }
   // contraction over channels: channels CPL*g .. of row q of tile t
+  __device__ __forceinline__ void op(int t, typename Operands<T, D>::Row &o) const { load_op<T, D>(s, row_off + (unsigned)t * TB, o); }
   __device__ __forceinline__ void row(int t, float (&o)[Geo<D>::CPL]) const { load_n<T>(s, row_off + (unsigned)t * TB, o); }
   // contraction over the tile's rows: element r is row 4g + r, channel 16*mb + q (d = 8: the upper eight output rows
   // repeat the lower ones and are never stored)
-  __device__ __forceinline__ void col(int t, float (&o)[Geo<D>::NMB][4]) const
+  __device__ __forceinline__ void col(int t, typename Operands<T, D>::Col (&o)[Geo<D>::NMB]) const
   {
     const unsigned off = col_off + (unsigned)t * TB;
 #pragma unroll
-    for (int mb = 0; mb < Geo<D>::NMB; ++mb)
+    for (int mb = 0; mb < Geo<D>::NMB; ++mb) {
+      unsigned x[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const unsigned at = off + (unsigned)((r * D + 16 * mb) * sizeof(T));
-        if constexpr (sizeof(T) == 4) o[mb][r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(s.d, at, 0, 0));
-        else o[mb][r] = __uint_as_float((unsigned)__builtin_amdgcn_raw_buffer_load_b16(s.d, at, 0, 0) << 16);
+        if constexpr (sizeof(T) == 4) x[r] = __builtin_amdgcn_raw_buffer_load_b32(s.d, at, 0, 0);
+        else x[r] = (unsigned)__builtin_amdgcn_raw_buffer_load_b16(s.d, at, 0, 0);
       }
+      if constexpr (Operands<T, D>::kBfCol) {
+        o[mb].w[0] = x[0] | x[1] << 16;
+        o[mb].w[1] = x[2] | x[3] << 16;
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[mb].v[r] = __uint_as_float(sizeof(T) == 4 ? x[r] : x[r] << 16);
+      }
+    }
   }
   // row q of the tile, the channels of this lane's accumulators: element r is channel 16*mb + 4g + r (d = 8: repeated likewise)
   __device__ __forceinline__ void own(int t, float (&o)[Geo<D>::NMB][4]) const
@@ -401,34 +562,6 @@ struct Rows {
   }
 };
 
-// the same from LDS, where a workgroup staged the head as fp32 rows of D + 4 floats (12, 20 or 36: both read patterns are
-// conflict free and rows stay 16-byte aligned)
-template <int D>
-constexpr int kLdsRow = D + 4;
-template <int D>
-struct LdsRows {
-  static constexpr bool kNear = true;  // near: operands are read where they are used and take no registers before
-  const float *row_at, *col_at, *own_at;  // this lane's place in tile 0
-  __device__ __forceinline__ LdsRows(const float *base, int q, int g)
-      : row_at(base + q * kLdsRow<D> + Geo<D>::CPL * g), col_at(base + 4 * g * kLdsRow<D> + (D < 16 ? (q & (D - 1)) : q)),
-        own_at(base + q * kLdsRow<D> + ((4 * g) & (D - 1)))
-  {
-  }
-  __device__ __forceinline__ void row(int t, float (&o)[Geo<D>::CPL]) const { load_n<Geo<D>::CPL>(row_at + t * (kTile * kLdsRow<D>), o); }
-  __device__ __forceinline__ void col(int t, float (&o)[Geo<D>::NMB][4]) const
-  {
-    const float *at = col_at + t * (kTile * kLdsRow<D>);
-#pragma unroll
-    for (int mb = 0; mb < Geo<D>::NMB; ++mb)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) o[mb][r] = at[r * kLdsRow<D> + 16 * mb];
-  }
-  __device__ __forceinline__ void own(int t, float (&o)[Geo<D>::NMB][4]) const
-  {
-#pragma unroll
-    for (int mb = 0; mb < Geo<D>::NMB; ++mb) load_n<4>(own_at + t * (kTile * kLdsRow<D>) + 16 * mb, o[mb]);
-  }
-};
 template <int N>
 __device__ __forceinline__ void store_lds(float *p, const float (&o)[N])
 {
@@ -439,30 +572,105 @@ __device__ __forceinline__ void store_lds(float *p, const float (&o)[N])
     for (int i = 0; i < N; i += 4) *reinterpret_cast<float4 *>(p + i) = make_float4(o[i], o[i + 1], o[i + 2], o[i + 3]);
   }
 }
+// the same from LDS, where a workgroup staged the head: fp32 rows of D + 4 floats (12, 20 or 36), or the bf16 bits themselves in rows
+// of D + 4 (d = 16) or D + 8 halfwords: every read pattern is conflict free, rows stay aligned for a row operand's load
+template <typename T, int D>
+constexpr int kLdsRow = Operands<T, D>::kBf ? (D == 32 ? 20 : 10) : D + 4;  // in floats
+template <typename T, int D>
+struct LdsRows {
+  static constexpr bool kNear = true;  // near: operands are read where they are used and take no registers before
+  static constexpr bool kBf = Operands<T, D>::kBf;
+  static constexpr int R = kLdsRow<T, D>, NMB = Geo<D>::NMB, CPL = Geo<D>::CPL;
+  const float *row_at, *col_at, *own_at;  // this lane's place in tile 0
+  __device__ __forceinline__ LdsRows(const float *base, int q, int g)
+  {
+    if constexpr (kBf) {  // (col: the transposing read takes rows 4g .. 4g+3, 16 channels of them spread over 16 lanes)
+      row_at = base + q * R + CPL / 2 * g;
+      col_at = base + (4 * g + (q >> 2)) * R + 2 * (q & 3);
+      own_at = base + q * R + 2 * g;
+    } else {
+      row_at = base + q * R + CPL * g;
+      col_at = base + 4 * g * R + (D < 16 ? (q & (D - 1)) : q);
+      own_at = base + q * R + ((4 * g) & (D - 1));
+    }
+  }
+  __device__ __forceinline__ void op(int t, typename Operands<T, D>::Row &o) const
+  {
+    const float *at = row_at + t * (kTile * R);
+    if constexpr (kBf && D == 32) {
+      const uint4 v = *reinterpret_cast<const uint4 *>(at);
+      o.w[0] = v.x; o.w[1] = v.y; o.w[2] = v.z; o.w[3] = v.w;
+    } else if constexpr (kBf) {
+      const uint2 v = *reinterpret_cast<const uint2 *>(at);
+      o.w[0] = v.x; o.w[1] = v.y;
+    } else {
+      load_n<CPL>(at, o.v);
+    }
+  }
+  __device__ __forceinline__ void row(int t, float (&o)[CPL]) const
+  {
+    typename Operands<T, D>::Row x;
+    op(t, x);
+    Operands<T, D>::floats(x, o);
+  }
+  __device__ __forceinline__ void col(int t, typename Operands<T, D>::Col (&o)[NMB]) const
+  {
+    const float *at = col_at + t * (kTile * R);
+#pragma unroll
+    for (int mb = 0; mb < NMB; ++mb) {
+      if constexpr (kBf) {
+        const u32x2_t v = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((mfma::lds_s16x4 *)(at + 8 * mb)));
+        if constexpr (Operands<T, D>::kBfCol) {
+          o[mb].w[0] = v[0]; o[mb].w[1] = v[1];
+        } else {
+          o[mb].v[0] = __uint_as_float(v[0] << 16);
+          o[mb].v[1] = __uint_as_float(v[0] & 0xFFFF0000u);
+          o[mb].v[2] = __uint_as_float(v[1] << 16);
+          o[mb].v[3] = __uint_as_float(v[1] & 0xFFFF0000u);
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[mb].v[r] = at[r * R + 16 * mb];
+      }
+    }
+  }
+  __device__ __forceinline__ void own(int t, float (&o)[NMB][4]) const
+  {
+#pragma unroll
+    for (int mb = 0; mb < NMB; ++mb) {
+      const float *at = own_at + t * (kTile * R) + (kBf ? 8 : 16) * mb;
+      if constexpr (kBf) load4(reinterpret_cast<const bf16_t *>(at), o[mb]);
+      else load_n<4>(at, o[mb]);
+    }
+  }
+  // where a row's operand stands: `base` as above
+  static __device__ __forceinline__ void put(float *base, int row, int g, const typename Operands<T, D>::Row &x)
+  {
+    float *at = base + row * R + (kBf ? CPL / 2 : CPL) * g;
+    if constexpr (kBf && D == 32) *reinterpret_cast<uint4 *>(at) = make_uint4(x.w[0], x.w[1], x.w[2], x.w[3]);
+    else if constexpr (kBf) *reinterpret_cast<uint2 *>(at) = make_uint2(x.w[0], x.w[1]);
+    else store_lds(at, x.v);
+  }
+};
 // two heads' rows from tile T0 on into LDS; rows before p0 (the padding) and past the end are zeros.  CLEAN: elements that are
 // not finite become zeros too.
 template <typename T, int D, bool CLEAN>
 __device__ __forceinline__ void stage_pair(const T *A, const T *B, float *a_lds, float *b_lds, int L, int T0, int NT, int p0, int lane, int wv,
                                            int W)
 {
-  constexpr int CPL = Geo<D>::CPL;
   const int q = lane & 15, g = lane >> 4;
   const Rows<T, D> Ar(A, L, q, g), Br(B, L, q, g);
   for (int t = T0 + wv; t < NT; t += W) {
-    float x[CPL], y[CPL];
+    typename Operands<T, D>::Row x, y;
     const unsigned off = t * kTile + q >= p0 ? Ar.row_off + (unsigned)t * Rows<T, D>::TB : kNowhere;
-    load_n<T>(Ar.s, off, x);
-    load_n<T>(Br.s, off, y);
+    load_op<T, D>(Ar.s, off, x);
+    load_op<T, D>(Br.s, off, y);
     if constexpr (CLEAN) {
-#pragma unroll
-      for (int i = 0; i < CPL; ++i) {
-        x[i] = finite(x[i]) ? x[i] : 0.0f;
-        y[i] = finite(y[i]) ? y[i] : 0.0f;
-      }
+      Operands<T, D>::clean(x);
+      Operands<T, D>::clean(y);
     }
-    const int at = (t * kTile + q) * kLdsRow<D> + CPL * g;
-    store_lds<CPL>(a_lds + at, x);
-    store_lds<CPL>(b_lds + at, y);
+    LdsRows<T, D>::put(a_lds, t * kTile + q, g, x);
+    LdsRows<T, D>::put(b_lds, t * kTile + q, g, y);
   }
 }
 
@@ -689,21 +897,22 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
   const bool dense = sel == nullptr;
   const int row_lo = (p.NB - p.nq) * BK;  // first row that is written (serving mode: the last block's)
   const T *Kh = K + (size_t)kvh * p.L * D, *Vh = V + (size_t)kvh * p.L * D;
-  const int pitch = RES ? NT * kTile * kLdsRow<D> : 0;  // floats of a staged tensor
+  const int pitch = RES ? NT * kTile * kLdsRow<T, D> : 0;  // floats of a staged tensor
   if constexpr (RES) {
     stage_pair<T, D, false>(Kh, Vh, small_lds, small_lds + pitch, p.L, T0, NT, p0, lane, wv, W);
     __syncthreads();
   }
-  using TileRows = std::conditional_t<RES, LdsRows<D>, Rows<T, D>>;
+  using TileRows = std::conditional_t<RES, LdsRows<T, D>, Rows<T, D>>;
   const TileRows Kr = [&] {
-    if constexpr (RES) return LdsRows<D>(small_lds, q, g);
+    if constexpr (RES) return LdsRows<T, D>(small_lds, q, g);
     else return Rows<T, D>(Kh, p.L, q, g);
   }();
   const TileRows Vr = [&] {
-    if constexpr (RES) return LdsRows<D>(small_lds + pitch, q, g);
+    if constexpr (RES) return LdsRows<T, D>(small_lds + pitch, q, g);
     else return Rows<T, D>(Vh, p.L, q, g);
   }();
-  const float c2 = p.scale * kLog2eF;
+  using Ops = Operands<T, D>;
+  const float c2 = p.scale * kLog2eF, kc = Ops::kBf ? c2 : 1.0f;  // (kc: what a product of rows is still to be multiplied by)
   const LaneMasks lm = LaneMasks::make(p, q, g);
   unsigned *my_lds = reinterpret_cast<unsigned *>(small_lds + 2 * pitch) + wv * lt_words(p, PERPOS);
 
@@ -727,14 +936,13 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
       }
       continue;
     }
-    float qf[CPL];
-    load_n<T>(Qs, active ? (unsigned)(iq * D + CPL * g) * (unsigned)sizeof(T) : kNowhere, qf);
+    typename Ops::Row qf;
+    load_op<T, D>(Qs, active ? (unsigned)(iq * D + CPL * g) * (unsigned)sizeof(T) : kNowhere, qf);
     LtSel<BK, PERPOS> ls;
     if (!dense)
       ls.build(p, my_lds, PERPOS ? nullptr : sel + ((size_t)bh * p.NB + I * (kTile / BK)) * p.k,
                PERPOS && active ? sel + ((size_t)kvh * p.L + iq) * p.k : nullptr, I, iq, p0, lane);
-#pragma unroll
-    for (int i = 0; i < CPL; ++i) qf[i] *= c2;
+    Ops::scale(qf, c2);
     const int kid_q = mask_block(p, iq);
     const int J_hi = p.bidir ? NT - 1 : I;
     // the walk of word w
@@ -753,26 +961,16 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
       a_st[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     float l_lt = 0.0f, l_st = 0.0f, ref_lt = 0.0f, ref_st = 0.0f, s_max = 0.0f;
-    float kf[CPL], vf[NMB][4];
-    auto logits = [&]() -> f32x4 {
-      f32x4 s = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int c = 0; c < CPL; ++c) s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c], qf[c], s, 0, 0, 0);
-      return s;
-    };
+    typename Ops::Row kf;
+    typename Ops::Col vf[NMB];
+    auto logits = [&]() -> f32x4 { return Ops::dot(kf, qf, f32x4{0.f, 0.f, 0.f, 0.f}); };  // (times kc)
     auto add_lt = [&](const float (&e)[4]) __attribute__((always_inline)) {
       l_lt += (e[0] + e[1]) + (e[2] + e[3]);
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int mb = 0; mb < NMB; ++mb) a_lt[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[mb][r], e[r], a_lt[mb], 0, 0, 0);
+      Ops::add(vf, e, a_lt);
     };
     auto add_st = [&](const float (&e)[4]) __attribute__((always_inline)) {
       l_st += (e[0] + e[1]) + (e[2] + e[3]);
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int mb = 0; mb < NMB; ++mb) a_st[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[mb][r], e[r], a_st[mb], 0, 0, 0);
+      Ops::add(vf, e, a_st);
     };
     // visibility of this lane's four keys of a general tile: element by element, and as bits where distances decide (`near`)
     auto see = [&](int t, bool (&v_lt)[4], bool (&v_st)[4]) __attribute__((always_inline)) {
@@ -795,14 +993,16 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
       if ((PERPOS || BK < kTile) && !dense) s_lt &= ls.sees(q, key0);
       v_lt = s_lt ? ok : 0u;
     };
-    if (p.sblk == 1 && !dense)
+    if (p.sblk == 1 && !dense) {
+      float qd[CPL];
+      Ops::floats(qf, qd);
       diagonals(p, I, T0, J_hi, [&](int d) __attribute__((always_inline)) {
         float s[4], e[4], vo[4][NMB][4];
 #pragma unroll
         for (int n = 0; n < 4; ++n) {
           float kr[CPL];
           Kr.row(min(max(I + d * (1 << n), T0), NT - 1), kr);
-          s[n] = dot_n(qf, kr, 0.0f);
+          s[n] = dot_n(qd, kr, 0.0f);
         }
         phase_end<D>();
 #pragma unroll
@@ -811,25 +1011,26 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
         const int key = iq + kTile * d * (1 << g);
         const bool ok = active & (key >= p0) & (key < p.last_lo);
         s_max = fmaxf(s_max, ok ? fabsf(x) : 0.0f);
-        const float ex = ok ? __builtin_amdgcn_exp2f(x) : 0.0f;
+        const float ex = ok ? __builtin_amdgcn_exp2f(kc * x) : 0.0f;
         l_st += ex;
         spread_g(ex, e);
 #pragma unroll
         for (int n = 0; n < 4; ++n) add_own(a_st, e[n], vo[n]);
       });
+    }
     // one tile: the next one's keys are requested as soon as this one's are in the matrix cores, its values at the end
     auto body = [&](auto kind, auto unit, Word &mask) __attribute__((always_inline)) {
       constexpr int KIND = decltype(kind)::value;
       constexpr bool UNIT = decltype(unit)::value;
       const int t = wk.take(mask), t_next = wk.peek();
       const f32x4 s = logits();
-      Kr.row(t_next, kf);
+      Kr.op(t_next, kf);
       if constexpr (TileRows::kNear) Vr.col(t, vf);
       s_max = fmaxf(fmaxf(s_max, fabsf(s[0])), fabsf(s[1]));
       s_max = fmaxf(fmaxf(s_max, fabsf(s[2])), fabsf(s[3]));
       float e[4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) e[r] = __builtin_amdgcn_exp2f(s[r]);
+      for (int r = 0; r < 4; ++r) e[r] = __builtin_amdgcn_exp2f(kc * s[r]);
       if constexpr (KIND == 0) {
         float el[4], es[4];
         if constexpr (UNIT) {
@@ -877,7 +1078,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
         word(w, false);
         if (!wk.all()) continue;
         const int t = wk.peek();
-        Kr.row(t, kf);
+        Kr.op(t, kf);
         if constexpr (!TileRows::kNear) Vr.col(t, vf);
         while (wk.m0) body(std::integral_constant<int, 0>{}, unit, wk.m0);
         while (wk.m1) body(std::integral_constant<int, 1>{}, unit, wk.m1);
@@ -886,7 +1087,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     };
     if (p.sblk <= 1) walk(std::true_type{});
     else walk(std::false_type{});
-    if (__builtin_expect(!__all(s_max <= kSmallLogit && abs_sum(a_lt) + abs_sum(a_st) < 1.0e37f), 0)) {
+    if (__builtin_expect(!__all(s_max * kc <= kSmallLogit && abs_sum(a_lt) + abs_sum(a_st) < 1.0e37f), 0)) {
       // large logits, or values near the end of fp32's range or beyond: the row maxima of both branches, then the walk
       // against them
       float x_lt = kNegInfF, x_st = kNegInfF;
@@ -897,8 +1098,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
         }
       };
       each([&](int J) {
-        Kr.row(J, kf);
-        const f32x4 s = logits();
+        Kr.op(J, kf);
+        const f32x4 s = logits() * kc;
         bool v_lt[4], v_st[4];
         see(J, v_lt, v_st);
 #pragma unroll
@@ -915,11 +1116,11 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
       clear(a_lt);
       clear(a_st);
       each([&](int J) {
-        Kr.row(J, kf);
+        Kr.op(J, kf);
         Vr.col(J, vf);
-        const f32x4 s = logits();
+        const f32x4 s = logits() * kc;
         float lost[4];
-        take_out(vf, g, lost);
+        take_out<T, D>(vf, g, lost);
         bool v_lt[4], v_st[4];
         see(J, v_lt, v_st);
         float el[4], es[4];
@@ -1001,10 +1202,11 @@ namespace {
 // selection bits, the wavefronts' selection words
 struct ResLayout {
   int pitch, qg, rowc, words, waves, total;
-  __host__ __device__ ResLayout(const KParams &p, bool perpos, int hpg, int overlay, int W)
+  // row: floats of a staged row
+  __host__ __device__ ResLayout(const KParams &p, int row, bool perpos, int hpg, int overlay, int W)
   {
     const int NT = (p.L + kTile - 1) / kTile, rows = NT * kTile;
-    pitch = rows * (p.d + 4);
+    pitch = rows * row;
     qg = overlay ? 0 : 2 * pitch;
     rowc = overlay ? 2 * hpg * pitch : 2 * pitch + 2 * hpg * pitch;
     words = rowc + hpg * 6 * rows;
@@ -1084,16 +1286,18 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
 {
   constexpr int CPL = Geo<D>::CPL, NMB = Geo<D>::NMB;
   const int q = lane & 15, g = lane >> 4;
-  const float c2 = p.scale * kLog2eF;
+  const float c2 = p.scale * kLog2eF, kc = Operands<T, D>::kBf ? c2 : 1.0f;  // (kc: what a product of rows is still to be multiplied by)
   const int iq = I * kTile + q;
   const bool active = iq < p.L && iq >= p0;
-  float qf[CPL], gr[CPL], ol[CPL], os[CPL], wl[CPL], ws[CPL];
+  using Ops = Operands<T, D>;
+  typename Ops::Row qf, g_op;
+  float gr[CPL], ol[CPL], os[CPL], wl[CPL], ws[CPL];
   gate.weights(g, wl, ws);
   const unsigned e_at = active ? (unsigned)(iq * D + CPL * g) : kNowhere / 4;  // rows that take no part read zeros
-  load_n<T>(in.dO, e_at * (unsigned)sizeof(T), gr);
+  load_op<T, D>(in.dO, e_at * (unsigned)sizeof(T), g_op);
   load_n<float>(in.o_lt, e_at * 4u, ol);
   load_n<float>(in.o_st, e_at * 4u, os);
-  load_n<T>(in.Q, e_at * (unsigned)sizeof(T), qf);
+  load_op<T, D>(in.Q, e_at * (unsigned)sizeof(T), qf);
   const unsigned l_at = active ? 4u * (unsigned)iq : kNowhere;
   float l2_lt = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(in.lse_lt.d, l_at, 0, 0)) * kLog2eF;
   float l2_st = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(in.lse_st.d, l_at, 0, 0)) * kLog2eF;
@@ -1103,6 +1307,7 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
            PERPOS && active ? sel_head + (size_t)iq * p.k : nullptr, I, iq, p0, lane);
 
   // ---- gate pass of the tile's rows ----
+  Ops::floats(g_op, gr);
   const float a_ll = sum_g(dot_n(gr, ol, 0.0f)), a_ss = sum_g(dot_n(gr, os, 0.0f));
   const float w_l = sum_g(dot_n(wl, ol, 0.0f)), w_s = sum_g(dot_n(ws, os, 0.0f));
   float al = sigmoid(gate.bias + w_l + w_s);
@@ -1110,7 +1315,7 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
   float D_lt = al * a_ll + dz * w_l, D_st = (1.0f - al) * a_ss + dz * w_s;
   if (!active) al = dz = D_lt = D_st = 0.0f;
   if (do_rows) {
-    sink(I, al, dz, D_lt, D_st, l2_lt, l2_st, ls, qf, gr);
+    sink(I, al, dz, D_lt, D_st, l2_lt, l2_st, ls, qf, g_op);
 #pragma unroll
     for (int i = 0; i < CPL; ++i) {
       gate.gl[i] = fmaf(dz, ol[i], gate.gl[i]);
@@ -1120,26 +1325,25 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
   }
   if (!do_dq) return true;
 
+  Ops::scale(qf, c2);
 #pragma unroll
   for (int i = 0; i < CPL; ++i) {
-    qf[i] *= c2;
     ol[i] = fmaf(al, gr[i], dz * wl[i]);         // dO_lt of this lane's row
     os[i] = fmaf(1.0f - al, gr[i], dz * ws[i]);  // dO_st
   }
+  const typename Ops::Split gl_op = Ops::split(ol), gs_op = Ops::split(os);
   f32x4 dq[NMB];
   clear(dq);
   const int kid_q = mask_block(p, iq);
   const int J_hi = p.bidir ? NT - 1 : I;
   Walk wk;
-  float kf[CPL], vf[CPL], kc[NMB][4];
+  typename Ops::Row kf, vf;
+  typename Ops::Col kt[NMB];
   auto products = [&](auto lt, auto st, f32x4 &s, f32x4 &g_lt, f32x4 &g_st) __attribute__((always_inline)) {
-    s = g_lt = g_st = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) {
-      s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c], qf[c], s, 0, 0, 0);
-      if constexpr (decltype(lt)::value) g_lt = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[c], ol[c], g_lt, 0, 0, 0);
-      if constexpr (decltype(st)::value) g_st = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[c], os[c], g_st, 0, 0, 0);
-    }
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    s = Ops::dot(kf, qf, zero);  // (times kc)
+    if constexpr (decltype(lt)::value) g_lt = Ops::dot(vf, gl_op, zero);
+    if constexpr (decltype(st)::value) g_st = Ops::dot(vf, gs_op, zero);
   };
   // did the lane's row select the tile, and is the key one that the causal and validity tests let through?
   auto selected = [&](int t) __attribute__((always_inline)) -> bool {
@@ -1149,20 +1353,16 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
   };
   const unsigned span = (unsigned)((p.bidir ? p.L - 1 : iq) - p0);
   auto seen = [&](int key) __attribute__((always_inline)) -> bool { return (unsigned)(key - p0) <= span; };
-  auto add = [&](const float (&ds)[4]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int mb = 0; mb < NMB; ++mb) dq[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kc[mb][r], ds[r], dq[mb], 0, 0, 0);
-  };
+  auto add = [&](const float (&ds)[4]) __attribute__((always_inline)) { Ops::add(kt, ds, dq); };
+  auto arg = [&](float s, float l) __attribute__((always_inline)) -> float { return Ops::kBf ? fmaf(kc, s, -l) : s - l; };
   auto body = [&](auto kind, auto unit, Word &mask) __attribute__((always_inline)) {
     constexpr int KIND = decltype(kind)::value;
     constexpr bool UNIT = decltype(unit)::value;
     const int t = wk.take(mask), t_next = wk.peek();
     f32x4 s, g_lt, g_st;
     products(std::bool_constant<KIND <= 1>{}, std::bool_constant<KIND != 1>{}, s, g_lt, g_st);
-    Kr.row(t_next, kf);
-    Vr.row(t_next, vf);
+    Kr.op(t_next, kf);
+    Vr.op(t_next, vf);
     const int key0 = t * kTile + 4 * g;
     float ds[4];
     if constexpr (KIND == 0) {
@@ -1175,7 +1375,7 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        float e = __builtin_amdgcn_exp2f(s[r] - l2_lt), f = __builtin_amdgcn_exp2f(s[r] - l2_st);
+        float e = __builtin_amdgcn_exp2f(arg(s[r], l2_lt)), f = __builtin_amdgcn_exp2f(arg(s[r], l2_st));
         if constexpr (UNIT) {
           e = keep(e, v_lt, r);
           f = keep(f, v_st, r);
@@ -1190,22 +1390,22 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
       const bool v = (PERPOS || BK < kTile) ? ls.sees(q, key0) : true;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float e = __builtin_amdgcn_exp2f(s[r] - l2_lt);
+        const float e = __builtin_amdgcn_exp2f(arg(s[r], l2_lt));
         ds[r] = ((PERPOS || BK < kTile) ? (v ? e : 0.0f) : e) * (g_lt[r] - D_lt);
       }
     } else {
       const unsigned v = UNIT ? lm.st(p, I - t) : 0u;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        float e = __builtin_amdgcn_exp2f(s[r] - l2_st);
+        float e = __builtin_amdgcn_exp2f(arg(s[r], l2_st));
         if constexpr (UNIT) e = keep(e, v, r);
         else e = st_sees(p, iq, key0 + r, kid_q, mask_block(p, key0, r), false) ? e : 0.0f;
         ds[r] = e * (g_st[r] - D_st);
       }
     }
-    if constexpr (TileRows::kNear) Kr.col(t, kc);
+    if constexpr (TileRows::kNear) Kr.col(t, kt);
     add(ds);
-    if constexpr (!TileRows::kNear) Kr.col(t_next, kc);
+    if constexpr (!TileRows::kNear) Kr.col(t_next, kt);
   };
   auto word = [&](int w) __attribute__((always_inline)) {
     const int t = w * 64 + lane;
@@ -1217,16 +1417,18 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
       word(w);
       if (!wk.all()) continue;
       const int t = wk.peek();
-      Kr.row(t, kf);
-      Vr.row(t, vf);
-      if constexpr (!TileRows::kNear) Kr.col(t, kc);
+      Kr.op(t, kf);
+      Vr.op(t, vf);
+      if constexpr (!TileRows::kNear) Kr.col(t, kt);
       while (wk.m0) body(std::integral_constant<int, 0>{}, unit, wk.m0);
       while (wk.m1) body(std::integral_constant<int, 1>{}, unit, wk.m1);
       while (wk.m2) body(std::integral_constant<int, 2>{}, unit, wk.m2);
     }
   };
   if constexpr (!CAREFUL) {
-    if (p.sblk == 1)
+    if (p.sblk == 1) {
+      float qd[CPL];
+      Ops::floats(qf, qd);
       diagonals(p, I, T0, J_hi, [&](int d) __attribute__((always_inline)) {
         float s[4], x[4], ko[4][NMB][4];
 #pragma unroll
@@ -1235,7 +1437,7 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
           const int t = min(max(I + d * (1 << n), T0), NT - 1);
           Kr.row(t, kr);
           Vr.row(t, vr);
-          s[n] = dot_n(qf, kr, 0.0f);
+          s[n] = dot_n(qd, kr, 0.0f);
           x[n] = dot_n(os, vr, 0.0f);
           if constexpr (D == 16) own_of_row(kr, ko[n]);
         }
@@ -1244,13 +1446,14 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
 #pragma unroll
           for (int n = 0; n < 4; ++n) Kr.own(min(max(I + d * (1 << n), T0), NT - 1), ko[n]);
         }
-        const float e = __builtin_amdgcn_exp2f(gather_g(s) - l2_st), gv = gather_g(x);
+        const float e = __builtin_amdgcn_exp2f(arg(gather_g(s), l2_st)), gv = gather_g(x);
         const int key = iq + kTile * d * (1 << g);
         const bool ok = (key >= p0) & (key < p.last_lo);
         spread_g(ok ? e * (gv - D_st) : 0.0f, x);
 #pragma unroll
         for (int n = 0; n < 4; ++n) add_own(dq, x[n], ko[n]);
       });
+    }
     if (p.sblk <= 1) walk(std::true_type{});
     else walk(std::false_type{});
   } else {
@@ -1258,20 +1461,20 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
       word(w);
       for (Word m = wk.all(); m;) {
         const int t = wk.take(m);
-        Kr.row(t, kf);
-        Vr.row(t, vf);
-        Kr.col(t, kc);
+        Kr.op(t, kf);
+        Vr.op(t, vf);
+        Kr.col(t, kt);
         f32x4 s, g_lt, g_st;
         products(std::true_type{}, std::true_type{}, s, g_lt, g_st);
         float ds[4], lost[4];
-        take_out(kc, g, lost);
+        take_out<T, D>(kt, g, lost);
         const bool s_lt = selected(t);
         const int key0 = t * kTile + 4 * g;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const bool ok = seen(key0 + r);
           const bool v_st = ok & st_sees(p, iq, key0 + r, kid_q, mask_block(p, key0, r), key0 + r >= p.last_lo);
-          const float e = __builtin_amdgcn_exp2f(s[r] - l2_lt), f = __builtin_amdgcn_exp2f(s[r] - l2_st);
+          const float e = __builtin_amdgcn_exp2f(arg(s[r], l2_lt)), f = __builtin_amdgcn_exp2f(arg(s[r], l2_st));
           ds[r] = ok & s_lt ? fmaf(e, g_lt[r] - D_lt, lost[r]) : 0.0f;
           ds[r] += v_st ? fmaf(f, g_st[r] - D_st, lost[r]) : 0.0f;
         }
@@ -1288,19 +1491,19 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
 // row: a lane keeps to its own column, and those of the padding are stored as zeros).  The hpg query heads that read the
 // rows add into the same gradients.  Returns whether all of them are finite; CAREFUL as above.  src gives their Q and dO rows, row constants, tile words and selection bits.
 template <typename T, int D, int BK, bool PERPOS, bool CAREFUL, typename Src>
-__device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT, int p0, int lane, float (&kf)[Geo<D>::CPL],
-                                         const float (&vf)[Geo<D>::CPL], int hpg, const Src &src, T *dK_head, T *dV_head)
+__device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT, int p0, int lane, typename Operands<T, D>::Row &kf,
+                                         const typename Operands<T, D>::Row &vf, int hpg, const Src &src, T *dK_head, T *dV_head)
 {
   constexpr int CPL = Geo<D>::CPL, NMB = Geo<D>::NMB;
   const int q = lane & 15, g = lane >> 4;
   const int NWb = (p.NB + 31) / 32;
-  const float c2 = p.scale * kLog2eF;
+  using Ops = Operands<T, D>;
+  const float c2 = p.scale * kLog2eF, kc = Ops::kBf ? c2 : 1.0f;  // (kc: what a product of rows is still to be multiplied by)
   const int j = J * kTile + q;
   f32x4 dk[NMB], dv[NMB];
   clear(dk);
   clear(dv);
-#pragma unroll
-  for (int i = 0; i < CPL; ++i) kf[i] *= c2;
+  Ops::scale(kf, c2);
   const int kid_k = mask_block(p, j);
   const bool last_k = j >= p.last_lo;
   const int I_lo = p.bidir ? T0 : J;
@@ -1316,14 +1519,16 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
     float t_lt = 0.0f, t_st = 0.0f;  // sum_i dz_i P_ij per branch
     float wv_lt, wv_st;              // Wg_x . v_j
     {
-      float wl[CPL], ws[CPL];
+      float wl[CPL], ws[CPL], vd[CPL];
+      Ops::floats(vf, vd);
       load_n<CPL>(wrow + CPL * g, wl);
       load_n<CPL>(wrow + D + CPL * g, ws);
-      wv_lt = sum_g(dot_n(wl, vf, 0.0f));
-      wv_st = sum_g(dot_n(ws, vf, 0.0f));
+      wv_lt = sum_g(dot_n(wl, vd, 0.0f));
+      wv_st = sum_g(dot_n(ws, vd, 0.0f));
     }
     Walk wk;
-    float qa[CPL], ga[CPL], qc[NMB][4], gc[NMB][4];
+    typename Ops::Row qa, ga;
+    typename Ops::Col qc[NMB], gc[NMB];
     float al[4], dz[4], D_lt[4], D_st[4], l_lt[4], l_st[4];  // row constants of this lane's four query rows
     auto consts = [&](int I) __attribute__((always_inline)) {
       auto get = [&](int k, float (&x)[4]) { src.constant(hl, I, k, x); };
@@ -1335,13 +1540,11 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
       get(5, l_st);
     };
     auto products = [&](f32x4 &s, f32x4 &gv) __attribute__((always_inline)) {
-      s = gv = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int c = 0; c < CPL; ++c) {
-        s = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[c], kf[c], s, 0, 0, 0);
-        gv = __builtin_amdgcn_mfma_f32_16x16x4f32(ga[c], vf[c], gv, 0, 0, 0);
-      }
+      const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+      s = Ops::dot(qa, kf, zero);  // (times kc)
+      gv = Ops::dot(ga, vf, zero);
     };
+    auto arg = [&](float s, float l) __attribute__((always_inline)) -> float { return Ops::kBf ? fmaf(kc, s, -l) : s - l; };
     // bit 0 of w4[r]: row r of this lane's four of tile t selected this lane's key block
     auto selected = [&](int t, unsigned (&w4)[4]) __attribute__((always_inline)) {
       if constexpr (PERPOS) {
@@ -1355,13 +1558,8 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
     };
     // dV^T += dO^T (a P), dK^T += Q^T dS
     auto add = [&](const float (&pc)[4], const float (&ds)[4]) __attribute__((always_inline)) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int mb = 0; mb < NMB; ++mb) {
-          dv[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(gc[mb][r], pc[r], dv[mb], 0, 0, 0);
-          dk[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(qc[mb][r], ds[r], dk[mb], 0, 0, 0);
-        }
+      Ops::add(gc, pc, dv);
+      Ops::add(qc, ds, dk);
     };
     auto body = [&](auto kind, auto unit, Word &mask) __attribute__((always_inline)) {
       constexpr int KIND = decltype(kind)::value;
@@ -1370,8 +1568,8 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
       if constexpr (near) consts(t);
       f32x4 s, gv;
       products(s, gv);
-      Qr.row(t_next, qa);
-      Gr.row(t_next, ga);
+      Qr.op(t_next, qa);
+      Gr.op(t_next, ga);
       const int i0 = t * kTile + 4 * g;  // this lane's rows i0 .. i0+3
       float pc[4], ds[4];
       unsigned w4[4] = {1u, 1u, 1u, 1u};
@@ -1392,7 +1590,7 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
         if constexpr (KIND == 0 && !UNIT) ok = (i0 + r >= j) | (p.bidir != 0);
         pc[r] = ds[r] = 0.0f;
         if constexpr (LT) {
-          const float e = __builtin_amdgcn_exp2f(s[r] - l_lt[r]);
+          const float e = __builtin_amdgcn_exp2f(arg(s[r], l_lt[r]));
           float pr = e;
           if constexpr (KIND == 0 && UNIT) pr = keep(pr, v_lt, r);
           if constexpr (KIND == 0 && !UNIT) pr = ok & in_lt ? pr : 0.0f;
@@ -1402,7 +1600,7 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
           t_lt = fmaf(dz[r], pr, t_lt);
         }
         if constexpr (ST) {
-          const float e = __builtin_amdgcn_exp2f(s[r] - l_st[r]);
+          const float e = __builtin_amdgcn_exp2f(arg(s[r], l_st[r]));
           float pr = e;
           if constexpr (UNIT) pr = keep(pr, v_st, r);
           else pr = ok & st_sees(p, i0 + r, j, mask_block(p, i0, r), kid_k, KIND == 0 ? last_k : false) ? pr : 0.0f;
@@ -1434,8 +1632,8 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
         word(w);
         if (!wk.all()) continue;
         const int t = wk.peek();
-        Qr.row(t, qa);
-        Gr.row(t, ga);
+        Qr.op(t, qa);
+        Gr.op(t, ga);
         if constexpr (!near) {
           consts(t);
           Qr.col(t, qc);
@@ -1452,8 +1650,8 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
         for (Word m = wk.all(); m;) {
           const int t = wk.take(m);
           consts(t);
-          Qr.row(t, qa);
-          Gr.row(t, ga);
+          Qr.op(t, qa);
+          Gr.op(t, ga);
           Qr.col(t, qc);
           Gr.col(t, gc);
           f32x4 s, gv;
@@ -1461,8 +1659,8 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
           unsigned w4[4] = {1u, 1u, 1u, 1u};
           selected(t, w4);
           float lost_q[4], lost_g[4];
-          take_out(qc, g, lost_q);
-          take_out(gc, g, lost_g);
+          take_out<T, D>(qc, g, lost_q);
+          take_out<T, D>(gc, g, lost_g);
           const bool in_lt = wk.is_lt(t);
           float pc[4], ds[4];
 #pragma unroll
@@ -1471,7 +1669,7 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
             const bool ok = (i >= p0) & (i < p.L) & ((i >= j) | (p.bidir != 0));
             const bool v_lt = ok & in_lt & ((w4[r] & 1u) != 0u);
             const bool v_st = ok & st_sees(p, i, j, mask_block(p, i), kid_k, last_k);
-            const float e = __builtin_amdgcn_exp2f(s[r] - l_lt[r]), f = __builtin_amdgcn_exp2f(s[r] - l_st[r]);
+            const float e = __builtin_amdgcn_exp2f(arg(s[r], l_lt[r])), f = __builtin_amdgcn_exp2f(arg(s[r], l_st[r]));
             const float as = 1.0f - al[r];
             pc[r] = v_lt ? fmaf(al[r], e, lost_g[r]) : 0.0f;
             pc[r] += v_st ? fmaf(as, f, lost_g[r]) : 0.0f;
@@ -1485,7 +1683,10 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
       }
     };
     if constexpr (!CAREFUL)
-      if (p.sblk == 1)
+      if (p.sblk == 1) {
+        float kd[CPL], vd[CPL];
+        Ops::floats(kf, kd);
+        Ops::floats(vf, vd);
         diagonals(p, J, I_lo, NT - 1, [&](int d) __attribute__((always_inline)) {
           float s[4], x[4], qo[4][NMB][4], go[4][NMB][4];
 #pragma unroll
@@ -1494,8 +1695,8 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
             const int t = min(max(J + d * (1 << n), I_lo), NT - 1);
             Qr.row(t, qr);
             Gr.row(t, gr);
-            s[n] = dot_n(kf, qr, 0.0f);
-            x[n] = dot_n(vf, gr, 0.0f);
+            s[n] = dot_n(kd, qr, 0.0f);
+            x[n] = dot_n(vd, gr, 0.0f);
             if constexpr (D == 16) {
               own_of_row(qr, qo[n]);
               own_of_row(gr, go[n]);
@@ -1513,7 +1714,7 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
           // this lane group's distance
           const int i = j + kTile * d * (1 << g), tg = min(max(J + d * (1 << g), I_lo), NT - 1);
           auto constant = [&](int k) { return src.row_constant(hl, tg, k); };
-          const float e = __builtin_amdgcn_exp2f(gather_g(s) - constant(5)), gd = gather_g(x);
+          const float e = __builtin_amdgcn_exp2f(arg(gather_g(s), constant(5))), gd = gather_g(x);
           const float pr = (i >= p0) & (i < p.L) & !last_k ? e : 0.0f;
           const float zd = constant(1), as = 1.0f - constant(0);
           t_st = fmaf(zd, pr, t_st);
@@ -1525,6 +1726,7 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
             add_own(dk, x[n], qo[n]);
           }
         });
+      }
     if constexpr (CAREFUL) walk_carefully();
     else if (p.sblk <= 1) walk(std::true_type{});
     else walk(std::false_type{});
@@ -1683,17 +1885,17 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
       zero_fill(dV + head_kv + (size_t)J * kTile * D, cnt, el);
       continue;
     }
-    float kf[CPL], vf[CPL];
-    Kr.row(J, kf);
-    Vr.row(J, vf);
+    typename Operands<T, D>::Row kf, vf;
+    Kr.op(J, kf);
+    Vr.op(J, vf);
     good &= key_tile<T, D, BK, PERPOS, false>(p, J, T0, NT, p0, lane, kf, vf, hpg, src, dK + head_kv, dV + head_kv);
   }
   if (__builtin_expect(!good, 0))
     for (int J = part * W + wv; J < NT; J += parts * W) {
       if (J < T0) continue;
-      float kf[CPL], vf[CPL];
-      Kr.row(J, kf);
-      Vr.row(J, vf);
+      typename Operands<T, D>::Row kf, vf;
+      Kr.op(J, kf);
+      Vr.op(J, vf);
       key_tile<T, D, BK, PERPOS, true>(p, J, T0, NT, p0, lane, kf, vf, hpg, src, dK + head_kv, dV + head_kv);
     }
 }
@@ -1724,7 +1926,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
   const int q = lane & 15, g = lane >> 4;
   const size_t head_kv = (size_t)bg * p.L * D;
   const bool do_dq = stages & kBwdStageDQ, do_dkv = stages & kBwdStageDKV;  // (the gate pass belongs to the query tiles)
-  const ResLayout lay(p, PERPOS, hpg, overlay, W);
+  const ResLayout lay(p, kLdsRow<T, D>, PERPOS, hpg, overlay, W);
   float *Ks = small_lds, *Vs = Ks + lay.pitch, *QG = small_lds + lay.qg, *rc = small_lds + lay.rowc;
   unsigned *words = reinterpret_cast<unsigned *>(small_lds + lay.words), *bits = words + NT * NWt;
   unsigned *my_lds = reinterpret_cast<unsigned *>(small_lds + lay.waves) + wv * lt_words(p, PERPOS);
@@ -1732,7 +1934,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
   // CLEAN: a row that sees a key or a value that is not finite has saved outputs that are not, and takes its NaN from there
   stage_pair<T, D, true>(K + head_kv, V + head_kv, Ks, Vs, p.L, T0, NT, p0, lane, wv, W);
   __syncthreads();
-  const LdsRows<D> Kr(Ks, q, g), Vr(Vs, q, g);
+  const LdsRows<T, D> Kr(Ks, q, g), Vr(Vs, q, g);
   const LaneMasks lm = LaneMasks::make(p, q, g);
   const int *sel_head = sel + (size_t)bg * (PERPOS ? p.L : p.NB) * p.k;
   for (int hl = 0; hl < hpg; ++hl) {
@@ -1741,14 +1943,13 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     GateSums<D> gate(gate_w, gate_b, bh % p.H);
     T *dQ_head = dQ + (size_t)bh * p.L * D;
     auto sink = [&](int I, float al, float dz, float D_lt, float D_st, float l2_lt, float l2_st, const LtSel<BK, PERPOS> &ls,
-                    const float (&qf)[CPL], const float (&gr)[CPL]) __attribute__((always_inline)) {
+                    const typename Operands<T, D>::Row &q_op, const typename Operands<T, D>::Row &g_op) __attribute__((always_inline)) {
       float *c = rc + (hl * NT + I) * (6 * kTile);
       c[lane] = g == 0 ? al : g == 1 ? dz : g == 2 ? D_lt : D_st;
       if (g < 2) c[64 + lane] = g == 0 ? l2_lt : l2_st;
       if (!overlay) {
-        const int at = 2 * hl * lay.pitch + (I * kTile + q) * kLdsRow<D> + CPL * g;
-        store_lds<CPL>(QG + at, qf);
-        store_lds<CPL>(QG + lay.pitch + at, gr);
+        LdsRows<T, D>::put(QG + 2 * hl * lay.pitch, I * kTile + q, g, q_op);
+        LdsRows<T, D>::put(QG + (2 * hl + 1) * lay.pitch, I * kTile + q, g, g_op);
       }
       if (hl > 0) return;
       for (int i = lane; i < NWt; i += 64) words[I * NWt + i] = ls.tiles[i];
@@ -1770,7 +1971,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     gate.finish(red, partial + (size_t)bh * GW, lane, wv, W);  // (its barrier also closes the query tiles of the head)
   }
   if (!do_dkv) return;
-  float kf[CPL], vf[CPL];
+  typename Operands<T, D>::Row kf, vf;
   if (overlay) {
     __syncthreads();
     for (int hl = 0; hl < hpg; ++hl) {
@@ -1783,8 +1984,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     const float *qg, *rc, *gate_w;
     const unsigned *bits, *words;
     int bh0, H, NT, NWt, q, g, pitch;
-    __device__ __forceinline__ LdsRows<D> q_rows(int hl) const { return LdsRows<D>(qg + 2 * hl * pitch, q, g); }
-    __device__ __forceinline__ LdsRows<D> g_rows(int hl) const { return LdsRows<D>(qg + (2 * hl + 1) * pitch, q, g); }
+    __device__ __forceinline__ LdsRows<T, D> q_rows(int hl) const { return LdsRows<T, D>(qg + 2 * hl * pitch, q, g); }
+    __device__ __forceinline__ LdsRows<T, D> g_rows(int hl) const { return LdsRows<T, D>(qg + (2 * hl + 1) * pitch, q, g); }
     __device__ __forceinline__ const float *gate_row(int hl) const { return gate_w + (size_t)((bh0 + hl) % H) * 2 * D; }
     __device__ __forceinline__ void constant(int hl, int I, int k, float (&x)[4]) const
     {
@@ -1804,18 +2005,18 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
       continue;
     }
     if (overlay) {
-      Kg.row(J, kf);
-      Vg.row(J, vf);
+      Kg.op(J, kf);
+      Vg.op(J, vf);
     } else {
-      Kr.row(J, kf);
-      Vr.row(J, vf);
+      Kr.op(J, kf);
+      Vr.op(J, vf);
     }
     good &= key_tile<T, D, BK, PERPOS, false>(p, J, T0, NT, p0, lane, kf, vf, hpg, src, dK + head_kv, dV + head_kv);
   }
   if (__builtin_expect(!good, 0))
     for (int u = wv; u < NT - T0; u += W) {
-      Kg.row(T0 + u, kf);
-      Vg.row(T0 + u, vf);
+      Kg.op(T0 + u, kf);
+      Vg.op(T0 + u, vf);
       key_tile<T, D, BK, PERPOS, true>(p, T0 + u, T0, NT, p0, lane, kf, vf, hpg, src, dK + head_kv, dV + head_kv);
     }
 }
@@ -1851,24 +2052,26 @@ SmallPlan stream_plan(const KParams &p, int units, size_t words_per_wave)
   s.parts = std::max(1, std::min((NT + s.waves - 1) / s.waves, want));
   return s;
 }
-SmallPlan fwd_plan(const KParams &p, bool perpos, int hpg)
+// floats of a staged row: kLdsRow
+int lds_row(const KParams &p, int dtype) { return dtype == 1 && p.d >= 16 ? (p.d == 32 ? 20 : 10) : p.d + 4; }
+SmallPlan fwd_plan(const KParams &p, int dtype, bool perpos, int hpg)
 {
   const size_t rows = (size_t)(p.L + kTile - 1) / kTile * kTile;
   const int units = p.B * p.H / hpg;
   SmallPlan s{true, false, res_waves(units), 1, 0};
-  s.lds = (2 * rows * (p.d + 4) + (size_t)s.waves * lt_words(p, perpos)) * sizeof(float);
+  s.lds = (2 * rows * lds_row(p, dtype) + (size_t)s.waves * lt_words(p, perpos)) * sizeof(float);
   if (p.nq == p.NB && s.lds <= kSmallLds) return s;
   s = stream_plan(p, p.B * p.H, lt_words(p, perpos));
   if (p.nq != p.NB) s = SmallPlan{false, false, 1, 1, lt_words(p, perpos) * sizeof(float)};  // serving mode: one query tile per head
   return s;
 }
-SmallPlan bwd_plan(const KParams &p, bool perpos, int hpg)
+SmallPlan bwd_plan(const KParams &p, int dtype, bool perpos, int hpg)
 {
   const int units = p.B * p.H / hpg;
   // with many heads four small workgroups per CU beat two that hold everything (B=2048 H=8 L=200 d=16: 672 against 917 us)
   for (int overlay = many_heads(units) ? 1 : 0; overlay < 2; ++overlay) {
     SmallPlan s{true, overlay != 0, res_waves(units), 1, 0};
-    s.lds = (size_t)ResLayout(p, perpos, hpg, overlay, s.waves).total * sizeof(float);
+    s.lds = (size_t)ResLayout(p, lds_row(p, dtype), perpos, hpg, overlay, s.waves).total * sizeof(float);
     if (s.lds <= kSmallLds) return s;
   }
   return stream_plan(p, p.B * p.H, lt_words(p, perpos));
@@ -1932,9 +2135,9 @@ size_t small_ws_bytes(const KParams &p, SmallWs *w, char *base)
   w->partial = reinterpret_cast<float *>(take(BH * NT * (2 * p.d + 1) * sizeof(float)));  // (at most one row per tile)
   return off;
 }
-int small_partial_rows(const KParams &p, int kv_groups)
+int small_partial_rows(const KParams &p, int dtype, int kv_groups)
 {
-  return bwd_plan(p, kv_groups > 0, kv_groups > 0 ? p.H / kv_groups : 1).parts;
+  return bwd_plan(p, dtype, kv_groups > 0, kv_groups > 0 ? p.H / kv_groups : 1).parts;
 }
 
 template <typename T>
@@ -1942,7 +2145,7 @@ static void launch_fwd_small_t(const KParams &p, const FwdArgs &a, hipStream_t s
 {
   const bool perpos = a.kv_groups > 0;
   const int hpg = perpos ? p.H / a.kv_groups : 1;
-  const SmallPlan pl = fwd_plan(p, perpos, hpg);
+  const SmallPlan pl = fwd_plan(p, std::is_same<T, float>::value ? 0 : 1, perpos, hpg);
   const int grid = p.B * p.H / (pl.res ? hpg : 1) * pl.parts;
   with_small_dims(p, [&](auto dim, auto bk) {
     constexpr int D = decltype(dim)::value, BK = decltype(bk)::value;
@@ -1969,7 +2172,7 @@ static void launch_bwd_small_t(const KParams &p, const BwdArgs &a, const SmallWs
   const bool perpos = kv_groups > 0;
   const int hpg = perpos ? p.H / kv_groups : 1;
   if ((stages & (kBwdStageGate | kBwdStageDQ | kBwdStageDKV)) == 0) return;
-  const SmallPlan pl = bwd_plan(p, perpos, hpg);
+  const SmallPlan pl = bwd_plan(p, std::is_same<T, float>::value ? 0 : 1, perpos, hpg);
   with_small_dims(p, [&](auto dim, auto bk) {
     constexpr int D = decltype(dim)::value, BK = decltype(bk)::value;
     if (pl.res) {

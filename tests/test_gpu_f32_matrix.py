@@ -191,3 +191,31 @@ def test_window_against_powers_of_two(d, window, L, sblk, bidir):
     x = make_inputs(w, want_dO=True)
     x.valid_len[:] = [L, L - 21, 40]
     run_case(with_shape(w, backward=False), x=x, backward=True, gate_scale=0.4)
+
+
+@pytest.mark.parametrize("d,b,B_,H,L,sblk,bidir", [
+    (32, 16, 2, 2, 416, 0, False),    # the longest bf16 heads at d = 32 whose forward and backward hold everything in LDS, and past it
+    (32, 16, 2, 2, 500, 16, True),    # streamed
+    (16, 8, 2, 2, 830, 1, False),
+    (16, 16, 2, 2, 1100, 0, False),
+    (32, 8, 1030, 2, 33, 1, True),    # 2060 heads: shared buffers
+    (16, 16, 3, 2, 47, 3, False),
+])
+def test_bf16_rows_as_they_are_stored(d, b, B_, H, L, sblk, bidir):
+    # products of bf16 rows on the bf16 matrix instructions, fp32 sides as three terms: the saved branch outputs and lse keep fp32's
+    # accuracy against the oracle (bf16 itself would be off by 2e-3)
+    w = with_shape(WORKLOADS["cfg2"], name=f"bf16-d{d}-b{b}-L{L}", B=B_, H=H, L=L, d=d, block=b, topk=3, window=b + 3, dtype="bf16",
+                   qkv_scaled=True, len_lo=1, len_hi=L, stis_block=sblk, bidir=bidir, backward=False, seed=2800 + d + L)
+    x = make_inputs(w, want_dO=True)
+    x.valid_len[:2] = [L, max(1, L - b - 3)]
+    pairs = None if B_ * H < 64 else [0, 1, H, B_ * H // 2 + 1, B_ * H - 1]
+    run_case(w, x=x, pairs=pairs, backward=True, gate_scale=0.4)
+    dv, p = Dev(x), params(w, save_for_bwd=1)
+    f = B.attn_fwd(p, dv.Q, dv.K, dv.V, dv.vl, B.select_blocks(p, dv.Q, dv.K, dv.vl), dv.gw, dv.gb)
+    torch.cuda.synchronize()
+    bh = np.asarray(pairs if pairs is not None else range(B_ * H), np.int32)
+    sel = oracle.select_blocks(x.Q, x.K, x.valid_len, b, 3, bidir=bidir)
+    fr = oracle.attn_fwd(x.Q, x.K, x.V, x.valid_len, sel, x.gate_w, x.gate_b, b, 3, b + 3, bh_list=bh, stis_block=sblk, bidir=bidir)
+    take = lambda t: host(t).reshape(B_ * H, *t.shape[2:])[bh]
+    for name in ("o_lt", "o_st", "lse_lt", "lse_st"):
+        assert_close(take(getattr(f, name)), getattr(fr, name), TOL["fp32"], name)
