@@ -410,15 +410,18 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(const float *__restrict__
   const int sub = lane % LPR, rg = lane / LPR;
   const int c4 = sub * 4;
   const int nchunk = (p.L + kPrepRows - 1) / kPrepRows;
-  const int bh = blockIdx.x / nchunk;
-  const int chunk = blockIdx.x % nchunk;
+  // (chunk by chunk the workgroups would go to the XCDs in turn, and where there are eight chunks to a head, or a multiple, one XCD
+  // would have the last, always valid ones to do and another nothing but padding)
+  const unsigned vid = mfma::xcd_spread(blockIdx.x, gridDim.x / nchunk, nchunk);
+  const int bh = (int)(vid / nchunk);
+  const int chunk = (int)(vid % nchunk);
   const int h = bh % p.H;
   const int n = clamp_len(valid_len[bh / p.H], p.L);
   const int p0 = p.L - n;
   // rows of blocks that hold no valid position are never read by the kernels that follow: nothing is
   // written for them (pad rows of a partly valid block are staged with their tile and get zeros)
   const int first = (p0 / p.b) * p.b;
-  float *out = partial + (size_t)blockIdx.x * G;
+  float *out = partial + (size_t)vid * G;
   if ((chunk + 1) * kPrepRows <= first) {
     for (int c = t; c < G; c += 256) out[c] = 0.0f;
     return;

@@ -272,7 +272,7 @@ __device__ __forceinline__ void bwd_dq_body(
   const int lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: MFMA regions must be scalar branches
   const int lq = lane & 31, lh = lane >> 5;
-  const unsigned vid = xcd_remap(pid, (unsigned)(p.B * p.H * p.NB));
+  const unsigned vid = xcd_spread(pid, (unsigned)(p.B * p.H), (unsigned)p.NB);
   const int bh = (int)(vid / p.NB);
   const int I = p.NB - 1 - (int)(vid % p.NB);
   const int n = clamp_len(valid_len[bh / p.H], p.L);
@@ -596,7 +596,7 @@ __device__ __forceinline__ void bwd_dkv_body(
   const int lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lq = lane & 31, lh = lane >> 5;
-  const unsigned vid = xcd_remap(pid, (unsigned)(p.B * p.H * p.NB));
+  const unsigned vid = xcd_spread(pid, (unsigned)(p.B * p.H), (unsigned)p.NB);
   const int bh = (int)(vid / p.NB);
   const int J = (int)(vid % p.NB);  // early key blocks are selected by more query blocks: start them first
   const int n = clamp_len(valid_len[bh / p.H], p.L);

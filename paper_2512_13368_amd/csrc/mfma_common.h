@@ -22,15 +22,23 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kNegInf = -__builtin_huge_valf();
 
-// Maps the hardware workgroup id (dealt round-robin over the 8 XCDs) to a virtual id such that
-// each XCD works through a contiguous range: all blocks of a head then share one L2.
-__device__ __forceinline__ unsigned xcd_remap(unsigned pid, unsigned total)
+// Maps the hardware workgroup id (dealt round-robin over the 8 XCDs) to a virtual id in units of `per` ids each, a unit being what
+// shares data (a head): all ids of a unit go to one XCD and meet in its L2, and units go to the XCDs in turn.  (Handing each XCD
+// a contiguous range of units would give it whole batch rows, whose lengths differ: at B=32 H=8, lengths U[200,1997], the
+// fullest XCD had a third more than the average to do and the others waited for it.)  The units beyond a multiple of 8 are
+// spread over the XCDs in contiguous ranges of ids.
+__device__ __forceinline__ unsigned xcd_spread(unsigned pid, unsigned units, unsigned per)
 {
   constexpr unsigned X = 8;
-  const unsigned per = (total + X - 1) / X;  // ids of a "tall" XCD
+  const unsigned whole = units / X * X * per, xcd = pid % X;
+  if (pid < whole) {
+    const unsigned local = pid / X, u = local / per;
+    return (u * X + xcd) * per + (local - u * per);
+  }
+  const unsigned total = units % X * per, local = (pid - whole) / X;
+  const unsigned tall_per = (total + X - 1) / X;  // ids of a "tall" XCD
   const unsigned tall = total % X ? total % X : X;
-  const unsigned xcd = pid % X, local = pid / X;
-  return xcd < tall ? xcd * per + local : tall * per + (xcd - tall) * (per - 1) + local;
+  return whole + (xcd < tall ? xcd * tall_per + local : tall * tall_per + (xcd - tall) * (tall_per - 1) + local);
 }
 
 // A staged tile is BLK rows of 128 bytes; 16-byte chunk c of row r sits at chunk position

@@ -885,7 +885,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
   extern __shared__ __attribute__((aligned(16))) float small_lds[];  // RES: K and V rows; then the wavefronts' selection words
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = blockDim.x >> 6;
-  const unsigned vid = mfma::xcd_remap(blockIdx.x, gridDim.x);
+  const unsigned vid = mfma::xcd_spread(blockIdx.x, gridDim.x / parts, parts);
   const int heads = RES ? hpg : 1;  // query heads of this workgroup
   const int bh0 = (int)(vid / parts) * heads, part = (int)(vid % parts);
   const int b = bh0 / p.H;
@@ -1790,7 +1790,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
   __shared__ float red[kMaxWaves][GW];
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = blockDim.x >> 6;
-  const unsigned vid = mfma::xcd_remap(blockIdx.x, gridDim.x);
+  const unsigned vid = mfma::xcd_spread(blockIdx.x, gridDim.x / parts, parts);
   const int bh = (int)(vid / parts), part = (int)(vid % parts);
   const int NT = (p.L + kTile - 1) / kTile, NWt = (NT + 31) / 32;
   const int p0 = p.L - clamp_len(valid_len[bh / p.H], p.L);
@@ -1844,7 +1844,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
   constexpr int CPL = Geo<D>::CPL;
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = blockDim.x >> 6;
-  const unsigned vid = mfma::xcd_remap(blockIdx.x, gridDim.x);
+  const unsigned vid = mfma::xcd_spread(blockIdx.x, gridDim.x / parts, parts);
   const int bg = (int)(vid / parts), part = (int)(vid % parts);
   const int NT = (p.L + kTile - 1) / kTile, NWt = (NT + 31) / 32, NWb = (p.NB + 31) / 32;
   const int p0 = p.L - clamp_len(valid_len[bg / (p.H / hpg)], p.L);

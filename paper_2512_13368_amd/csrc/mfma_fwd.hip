@@ -70,7 +70,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
   const int lane = threadIdx.x;
   const int lq = lane & 31;  // query column (and key row of the K operand, d row of the V^T operand)
   const int lh = lane >> 5;  // which half of each 16-wide contraction slab
-  const unsigned vid = xcd_remap(blockIdx.x, (unsigned)(p.B * p.H * p.nq));
+  const unsigned vid = xcd_spread(blockIdx.x, (unsigned)(p.B * p.H), (unsigned)p.nq);
   const int bh = (int)(vid / p.nq);
   const int I = p.NB - 1 - (int)(vid % p.nq);
   const int h = bh % p.H;

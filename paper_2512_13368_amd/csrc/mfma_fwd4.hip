@@ -72,7 +72,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   const int kh = wv >> 1;  // key half: rows 32*kh .. 32*kh+31 of every tile; after a merge: channels 32*kh ..
   const int lq = lane & 31;
   const int lh = lane >> 5;
-  const unsigned vid = xcd_remap(blockIdx.x, (unsigned)(p.B * p.H * p.nq));
+  const unsigned vid = xcd_spread(blockIdx.x, (unsigned)(p.B * p.H), (unsigned)p.nq);
   const int bh = (int)(vid / p.nq);
   const int I = p.NB - 1 - (int)(vid % p.nq);
   const int h = bh % p.H;

@@ -10,6 +10,7 @@
 
 #include "common.h"
 #include "launch.h"
+#include "mfma_common.h"
 
 namespace blossom {
 
@@ -474,8 +475,10 @@ __global__ __launch_bounds__(256) void score_topk_kernel(const float *__restrict
 {
   extern __shared__ __attribute__((aligned(16))) float sel_lds[];
   const int chunks = (p.nq + rows - 1) / rows;
-  const int bh = blockIdx.x / chunks;
-  const int I0 = p.NB - p.nq + (int)(blockIdx.x % chunks) * rows, I1 = min(I0 + rows, p.NB);
+  // (a head's chunks on one XCD, which has the means in its L2; in turn they would give one XCD the last, longest chunks of all)
+  const unsigned vid = mfma::xcd_spread(blockIdx.x, gridDim.x / chunks, chunks);
+  const int bh = (int)(vid / chunks);
+  const int I0 = p.NB - p.nq + (int)(vid % chunks) * rows, I1 = min(I0 + rows, p.NB);
   float *q_s = sel_lds, *k_s = q_s + rows * (D + 4);
   const int p0 = p.L - clamp_len(valid_len[bh / p.H], p.L);
   auto stage = [&](float *to, const float *from, int lo, int hi) {  // eight loads in flight per thread
