@@ -57,6 +57,41 @@ __device__ __forceinline__ void pool_batches(const T *__restrict__ src, int lo, 
   }
 }
 
+// The same for a whole number of pairs of eight rows: the next eight are requested before the last eight are added, and no row
+// needs a test (pooling at B=16 H=8 L=8192 d=64 b=64: 55.6 -> 53.9 us, K alone 29.3 -> 27.8; where blocks of one wavefront
+// differ in their valid rows, as in the selection of a whole head, both forms would run: 24 -> 29 us at L=1024).
+template <typename T, int D, int EPT>
+__device__ __forceinline__ void pool_rows(const T *__restrict__ src, int n, float (&a)[EPT])
+{
+  using V = std::conditional_t<EPT * sizeof(T) == 16, uint4, uint2>;
+  constexpr int R = 8;
+  V u[R], v[R];
+  auto request = [&](V (&x)[R], int t) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < R; ++i) x[i] = *reinterpret_cast<const V *>(src + (size_t)(t + i) * D);
+  };
+  auto add = [&](const V (&x)[R]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      float f[EPT];
+      unpack(x[i], f);
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) a[e] = a[e] + f[e];
+    }
+  };
+  request(u, 0);
+  request(v, R);
+  int t = 2 * R;
+  for (; t < n; t += 2 * R) {
+    add(u);
+    request(u, t);
+    add(v);
+    request(v, t + R);
+  }
+  add(u);
+  add(v);
+}
+
 template <typename T, int D, int EPT>
 __device__ __forceinline__ void pool_block(const T *__restrict__ src, int lo, int hi, float (&a)[EPT])
 {
@@ -105,7 +140,14 @@ __global__ __launch_bounds__(256) void pool_kernel(const T *__restrict__ Q, cons
   }
   const int p0 = p.L - clamp_len(valid_len[bh / p.H], p.L);
   const int lo = max(J * p.b, p0), hi = min((J + 1) * p.b, p.L);
-  pool_block<T, D, EPT>((which ? K : Q) + (size_t)bh * p.L * D + c0, lo, hi, a);
+  const T *src = (which ? K : Q) + (size_t)bh * p.L * D + c0;
+  if (hi - lo >= 32 && hi - lo == p.b) {
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) a[e] = 0.0f;
+    pool_rows<T, D>(src + (size_t)lo * D, p.b, a);
+  } else {
+    pool_block<T, D, EPT>(src, lo, hi, a);
+  }
   if (!which) {
 #pragma unroll
     for (int e = 0; e < EPT; e += 4)
