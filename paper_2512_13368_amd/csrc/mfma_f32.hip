@@ -818,9 +818,14 @@ struct LtSel {
     row = 0ull;
     if constexpr (PERPOS) {
       if (sel_pos)
-        for (int e = 0; e < p.k; ++e) {
-          const int J = sel_pos[e];
-          if (J >= 0 && J < p.NB && J * BK <= iq && (J + 1) * BK > p0) row |= 1ull << J;
+        // four requests at a time: a loop of single ones waited for memory k times (B=2048 H=8 over 4 L=200 d=8: 1093 us, 1060 so)
+        for (int e = 0; e < p.k; e += 4) {
+          int J[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) J[i] = sel_pos[min(e + i, p.k - 1)];
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (J[i] >= 0 && J[i] < p.NB && J[i] * BK <= iq && (J[i] + 1) * BK > p0) row |= 1ull << J[i];
         }
       unsigned lo = (unsigned)row, hi = (unsigned)(row >> 32);
       lo = or_row(lo);
