@@ -8,7 +8,7 @@
 // (bf16 storage from d = 16 on: on the bf16 matrix instructions with the same accuracy, see THE MATRIX OPERANDS)
 // whatever the block size; a selection block of 8 is half a tile and the selection is tested per element.
 // A wavefront takes one query tile (forward, dQ) or one key tile (dK/dV) at a time.  Heads that fit a workgroup's LDS
-// (rows of d + 4 floats, two workgroups per CU: L up to 256 at d = 32, 480 at d = 16, 800 at d = 8, less in the backward) are staged
+// (small_lds_limit; fp32: L up to 256 at d = 32, 272 at d = 16, 688 at d = 8, less in the backward) are staged
 // there, and the backward of such a head is one kernel that reads every tensor once; longer ones stream the tiles
 // they walk from memory (L1 and L2) into operand registers, with neither barriers nor a limit on the length.
 //
@@ -69,6 +69,8 @@ template <int D>
 struct Geo {
   static constexpr int CPL = D / 4;            // channels per lane of a channel contraction: CPL*g .. CPL*g + CPL-1
   static constexpr int NMB = (D + 15) / 16;    // 16-channel output blocks (d = 8 fills half of one)
+  static constexpr bool kQuads = D == 8;       // contractions over rows by quads of channels (Operands::add)
+  static constexpr int NACC = kQuads ? 2 : NMB;  // their accumulators
 };
 
 // CPL consecutive elements as floats
@@ -246,9 +248,19 @@ struct Operands {
     return s;
   }
   // acc += sum over the lanes' rows of e times the operand
-  static __device__ __forceinline__ void add(const Col (&a)[Geo<D>::NMB], const float (&e)[4], f32x4 (&acc)[Geo<D>::NMB])
+  // d = 8: sixteen blocks of 4x4 in one instruction, the operand's quad of channels 4h .. 4h+3 handed to the four blocks of a lane
+  // group.  Lane (q, g) then holds the part of the sum over its rows 4g .. 4g+3 (channel 4h + r of row q in acc[h][r]; total()
+  // closes it): half the matrix cores' time of the 16-row form, of which d = 8 fills half, and sums that err less (dK at L=1000:
+  // 2.8e-7 against 3.3e-7).  With the distances taken by lane groups (add_row), B=32 H=8 L=2000: dK/dV 129 -> 103 us, dQ 79 -> 69.
+  static __device__ __forceinline__ void add(const Col (&a)[Geo<D>::NMB], const float (&e)[4], f32x4 (&acc)[Geo<D>::NACC])
   {
-    if constexpr (kBfCol) {
+    if constexpr (Geo<D>::kQuads) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        acc[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[0].v[r], e[r], acc[0], 2, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[0].v[r], e[r], acc[1], 2, 1, 0);
+      }
+    } else if constexpr (kBfCol) {
       ColB c[3];
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
@@ -313,6 +325,24 @@ __device__ __forceinline__ void clear(f32x4 (&a)[N])
 {
 #pragma unroll
   for (int mb = 0; mb < N; ++mb) a[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+}
+
+// the sums over all lane groups, as the accumulators of the 16-row form hold them: channel 16*mb + 4g + r (modulo 8 at d = 8)
+template <int D>
+__device__ __forceinline__ void total(const f32x4 (&a)[Geo<D>::NACC], f32x4 (&o)[Geo<D>::NMB])
+{
+  if constexpr (Geo<D>::kQuads) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const u32x2_t x = __builtin_amdgcn_permlane16_swap(__float_as_uint(a[0][r]), __float_as_uint(a[1][r]), false, false);
+      const unsigned y = __float_as_uint(__uint_as_float(x[0]) + __uint_as_float(x[1]));
+      const u32x2_t z = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+      o[0][r] = __uint_as_float(z[0]) + __uint_as_float(z[1]);
+    }
+  } else {
+#pragma unroll
+    for (int mb = 0; mb < Geo<D>::NMB; ++mb) o[mb] = a[mb];
+  }
 }
 
 // lane (col, g) holds channels 16*mb + 4g + r of one row in a[mb][r]: stores those below D
@@ -525,14 +555,13 @@ struct Rows {
   __device__ __forceinline__ Rows(const T *head, int L, int q, int g) : s(head, (size_t)L * D * sizeof(T))
   {
     row_off = (unsigned)(q * D + Geo<D>::CPL * g) * (unsigned)sizeof(T);
-    own_off = (unsigned)(q * D + ((4 * g) & (D - 1))) * (unsigned)sizeof(T);
+    own_off = (unsigned)(q * D + (D == 8 ? 0 : (4 * g) & (D - 1))) * (unsigned)sizeof(T);
     col_off = (unsigned)(4 * g * D + (D < 16 ? (q & (D - 1)) : q)) * (unsigned)sizeof(T);
   }
   // contraction over channels: channels CPL*g .. of row q of tile t
   __device__ __forceinline__ void op(int t, typename Operands<T, D>::Row &o) const { load_op<T, D>(s, row_off + (unsigned)t * TB, o); }
   __device__ __forceinline__ void row(int t, float (&o)[Geo<D>::CPL]) const { load_n<T>(s, row_off + (unsigned)t * TB, o); }
-  // contraction over the tile's rows: element r is row 4g + r, channel 16*mb + q (d = 8: the upper eight output rows
-  // repeat the lower ones and are never stored)
+  // contraction over the tile's rows: element r is row 4g + r, channel 16*mb + q (d = 8: lanes q and q + 8 hold the same)
   __device__ __forceinline__ void col(int t, typename Operands<T, D>::Col (&o)[Geo<D>::NMB]) const
   {
     const unsigned off = col_off + (unsigned)t * TB;
@@ -554,7 +583,9 @@ struct Rows {
       }
     }
   }
-  // row q of the tile, the channels of this lane's accumulators: element r is channel 16*mb + 4g + r (d = 8: repeated likewise)
+  // all eight channels of row q (d = 8)
+  __device__ __forceinline__ void whole(int t, float (&o)[D]) const { load_n<T>(s, own_off + (unsigned)t * TB, o); }
+  // row q of the tile, the channels of this lane's accumulators: element r is channel 16*mb + 4g + r
   __device__ __forceinline__ void own(int t, float (&o)[Geo<D>::NMB][4]) const
   {
 #pragma unroll
@@ -572,10 +603,11 @@ __device__ __forceinline__ void store_lds(float *p, const float (&o)[N])
     for (int i = 0; i < N; i += 4) *reinterpret_cast<float4 *>(p + i) = make_float4(o[i], o[i + 1], o[i + 2], o[i + 3]);
   }
 }
-// the same from LDS, where a workgroup staged the head: fp32 rows of D + 4 floats (12, 20 or 36), or the bf16 bits themselves in rows
-// of D + 4 (d = 16) or D + 8 halfwords: every read pattern is conflict free, rows stay aligned for a row operand's load
+// the same from LDS, where a workgroup staged the head: fp32 rows of D + 4 floats (20 or 36; d = 8: 8), or the bf16 bits themselves in
+// rows of D + 4 (d = 16) or D + 8 halfwords: every read pattern is conflict free, rows stay aligned for a row operand's load.
+// (d = 8 in rows of 12: three backward workgroups per CU where the registers allow four, positions at B=2048 L=200 635 us, 569 so)
 template <typename T, int D>
-constexpr int kLdsRow = Operands<T, D>::kBf ? (D == 32 ? 20 : 10) : D + 4;  // in floats
+constexpr int kLdsRow = Operands<T, D>::kBf ? (D == 32 ? 20 : 10) : D == 8 ? 8 : D + 4;  // in floats
 template <typename T, int D>
 struct LdsRows {
   static constexpr bool kNear = true;  // near: operands are read where they are used and take no registers before
@@ -591,7 +623,7 @@ struct LdsRows {
     } else {
       row_at = base + q * R + CPL * g;
       col_at = base + 4 * g * R + (D < 16 ? (q & (D - 1)) : q);
-      own_at = base + q * R + ((4 * g) & (D - 1));
+      own_at = base + q * R + (D == 8 ? 0 : 4 * g & (D - 1));
     }
   }
   __device__ __forceinline__ void op(int t, typename Operands<T, D>::Row &o) const
@@ -634,6 +666,7 @@ struct LdsRows {
       }
     }
   }
+  __device__ __forceinline__ void whole(int t, float (&o)[D]) const { load_n<D>(own_at + t * (kTile * R), o); }
   __device__ __forceinline__ void own(int t, float (&o)[NMB][4]) const
   {
 #pragma unroll
@@ -747,7 +780,7 @@ struct Walk {
 
 // THE DIAGONALS of mask block 1.  A row sees one key of a tile 2, 4, 8 ... tiles away (from first_diagonal on), its own offset's:
 // 16 pairs, for which a matrix product would form 256.  They are taken four distances at a time on the vector ALUs instead: every
-// lane multiplies its channels of its row for all four distances, gather_g leaves distance n's sum with lane group n, where the
+// lane multiplies its channels of its row for all four distances (d = 8: see add_row), gather_g leaves distance n's sum with lane group n, where the
 // mask and the exponential are, and spread_g hands the four results to all groups, which add them into their accumulators'
 // channels (`own`).  About 12 vector instructions a distance; as tiles of the walk the distances took half of its steps at L=2000
 // (a training step at B=32 H=8 L=2000 d=8 356 us, 302 like this; B=2048 H=8 L=200 d=16 1050 and 996).
@@ -780,6 +813,23 @@ __device__ __forceinline__ void spread_g(float x, float (&o)[4])
   const u32x2_t b = __builtin_amdgcn_permlane32_swap(a[0], a[0], false, false);
   const u32x2_t c = __builtin_amdgcn_permlane32_swap(a[1], a[1], false, false);
   o[0] = __uint_as_float(b[0]); o[1] = __uint_as_float(c[0]); o[2] = __uint_as_float(b[1]); o[3] = __uint_as_float(c[1]);
+}
+// d = 8: a row is two 16-byte loads, so a lane group takes a whole distance by itself and adds to its own part of the sums
+// (Operands::add): nothing to gather or to spread
+__device__ __forceinline__ void whole_row(const float (&x)[2], float (&o)[8])  // a row spread over the lane groups, into each of them
+{
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    float y[4];
+    spread_g(x[i], y);
+#pragma unroll
+    for (int n = 0; n < 4; ++n) o[2 * n + i] = y[n];
+  }
+}
+__device__ __forceinline__ void add_row(f32x4 (&acc)[2], float c, const float (&a)[8])
+{
+#pragma unroll
+  for (int i = 0; i < 8; ++i) acc[i / 4][i % 4] = fmaf(c, a[i], acc[i / 4][i % 4]);
 }
 template <int N>
 __device__ __forceinline__ void own_of_row(const float (&x)[N], float (&o)[1][4])  // d = 16: the same channels
@@ -886,7 +936,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     T *__restrict__ O, float *__restrict__ o_lt_out, float *__restrict__ o_st_out, float *__restrict__ lse_lt_out,
     float *__restrict__ lse_st_out, int hpg, int parts, KParams p)
 {
-  constexpr int CPL = Geo<D>::CPL, NMB = Geo<D>::NMB;
+  constexpr int CPL = Geo<D>::CPL, NMB = Geo<D>::NMB, NACC = Geo<D>::NACC;
   extern __shared__ __attribute__((aligned(16))) float small_lds[];  // RES: K and V rows; then the wavefronts' selection words
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = blockDim.x >> 6;
@@ -959,12 +1009,9 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
       const bool edge = (BK < kTile && !PERPOS) | (t == T0) | (t == I) | (t >= min(NT - 1, p.last_lo / kTile));
       wk.start<false>(p, I, w, T0, J_hi, lane, dense || ls.has_tile(min(t, NT - 1)), edge, dia, !dense);
     };
-    f32x4 a_lt[NMB], a_st[NMB];
-#pragma unroll
-    for (int mb = 0; mb < NMB; ++mb) {
-      a_lt[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-      a_st[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
+    f32x4 a_lt[NACC], a_st[NACC];
+    clear(a_lt);
+    clear(a_st);
     float l_lt = 0.0f, l_st = 0.0f, ref_lt = 0.0f, ref_st = 0.0f, s_max = 0.0f;
     typename Ops::Row kf;
     typename Ops::Col vf[NMB];
@@ -1001,7 +1048,22 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     if (p.sblk == 1 && !dense) {
       float qd[CPL];
       Ops::floats(qf, qd);
+      float qw[CPL * 4];
+      if constexpr (D == 8) whole_row(qd, qw);
       diagonals(p, I, T0, J_hi, [&](int d) __attribute__((always_inline)) {
+        if constexpr (D == 8) {
+          const int t = min(max(I + d * (1 << g), T0), NT - 1), key = iq + kTile * d * (1 << g);
+          float kr[D], vr[D];
+          Kr.whole(t, kr);
+          Vr.whole(t, vr);
+          const float x = dot_n(qw, kr, 0.0f);
+          const bool ok = active & (key >= p0) & (key < p.last_lo);
+          s_max = fmaxf(s_max, ok ? fabsf(x) : 0.0f);
+          const float ex = ok ? __builtin_amdgcn_exp2f(kc * x) : 0.0f;
+          l_st += ex;
+          add_row(a_st, ex, vr);
+          return;
+        } else {
         float s[4], e[4], vo[4][NMB][4];
 #pragma unroll
         for (int n = 0; n < 4; ++n) {
@@ -1021,6 +1083,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
         spread_g(ex, e);
 #pragma unroll
         for (int n = 0; n < 4; ++n) add_own(a_st, e[n], vo[n]);
+        }
       });
     }
     // one tile: the next one's keys are requested as soon as this one's are in the matrix cores, its values at the end
@@ -1138,7 +1201,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
         add_st(es);
       });
 #pragma unroll
-      for (int mb = 0; mb < NMB; ++mb)
+      for (int mb = 0; mb < NACC; ++mb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {  // (a row of the padding may have seen some of the padding)
           a_lt[mb][r] = active ? a_lt[mb][r] : 0.0f;
@@ -1146,7 +1209,9 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
         }
     }
     // closes a branch: normalised output (zero for rows that take no part), returns the lse
-    auto finish = [&](f32x4 (&acc)[NMB], float l, float m) -> float {
+    f32x4 o_lt[NMB], o_st[NMB];
+    auto finish = [&](const f32x4 (&part)[NACC], f32x4 (&acc)[NMB], float l, float m) -> float {
+      total<D>(part, acc);
       const float lt = sum_g(l);
       const bool ok = active && !(lt <= 0.0f);  // (a NaN stays one)
       const float inv = ok ? recip(lt) : 0.0f;
@@ -1159,13 +1224,13 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     const int el = fresh_lane(), eg = el >> 4, ei = I * kTile + (el & 15);
     const bool in_range = ei < p.L && ei >= row_lo;
     const size_t lrow = (size_t)bh * p.L + ei, rowoff = lrow * D;
-    const float lse_lt = finish(a_lt, l_lt, ref_lt);
+    const float lse_lt = finish(a_lt, o_lt, l_lt, ref_lt);
     if (dense) {
-      if (in_range) store_row4<T, D>(O + rowoff, a_lt, eg);
+      if (in_range) store_row4<T, D>(O + rowoff, o_lt, eg);
       if (in_range && eg == 0 && lse_lt_out) lse_lt_out[lrow] = lse_lt;
       continue;
     }
-    const float lse_st = finish(a_st, l_st, ref_st);
+    const float lse_st = finish(a_st, o_st, l_st, ref_st);
 
     // ---- gate and blend (Eq. 18-19) ----
     const float *wl = gate_w + (size_t)h * 2 * D;
@@ -1177,18 +1242,18 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
         load_n<4>(wl + 16 * mb + 4 * eg, x);
         load_n<4>(wl + D + 16 * mb + 4 * eg, y);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) z = fmaf(y[r], a_st[mb][r], fmaf(x[r], a_lt[mb][r], z));
+        for (int r = 0; r < 4; ++r) z = fmaf(y[r], o_st[mb][r], fmaf(x[r], o_lt[mb][r], z));
       }
     z = sum_g(z) + (gate_b ? gate_b[h] : 0.0f);
     const float alpha = sigmoid(z);
     if (in_range) {
-      if (o_lt_out) store_row4<float, D>(o_lt_out + rowoff, a_lt, eg);
-      if (o_st_out) store_row4<float, D>(o_st_out + rowoff, a_st, eg);
+      if (o_lt_out) store_row4<float, D>(o_lt_out + rowoff, o_lt, eg);
+      if (o_st_out) store_row4<float, D>(o_st_out + rowoff, o_st, eg);
       f32x4 o[NMB];
 #pragma unroll
       for (int mb = 0; mb < NMB; ++mb)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) o[mb][r] = alpha * a_lt[mb][r] + (1.0f - alpha) * a_st[mb][r];
+        for (int r = 0; r < 4; ++r) o[mb][r] = alpha * o_lt[mb][r] + (1.0f - alpha) * o_st[mb][r];
       store_row4<T, D>(O + rowoff, o, eg);
       if (eg == 0) {
         if (lse_lt_out) lse_lt_out[lrow] = lse_lt;
@@ -1289,7 +1354,7 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
                                            const TileRows &Kr, const TileRows &Vr, const int *sel_head, unsigned *my_lds,
                                            GateSums<D> &gate, const LaneMasks &lm, bool do_rows, bool do_dq, T *dQ_head, Sink &&sink)
 {
-  constexpr int CPL = Geo<D>::CPL, NMB = Geo<D>::NMB;
+  constexpr int CPL = Geo<D>::CPL, NMB = Geo<D>::NMB, NACC = Geo<D>::NACC;
   const int q = lane & 15, g = lane >> 4;
   const float c2 = p.scale * kLog2eF, kc = Operands<T, D>::kBf ? c2 : 1.0f;  // (kc: what a product of rows is still to be multiplied by)
   const int iq = I * kTile + q;
@@ -1337,8 +1402,8 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
     os[i] = fmaf(1.0f - al, gr[i], dz * ws[i]);  // dO_st
   }
   const typename Ops::Split gl_op = Ops::split(ol), gs_op = Ops::split(os);
-  f32x4 dq[NMB];
-  clear(dq);
+  f32x4 dq_part[NACC], dq[NMB];
+  clear(dq_part);
   const int kid_q = mask_block(p, iq);
   const int J_hi = p.bidir ? NT - 1 : I;
   Walk wk;
@@ -1358,7 +1423,7 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
   };
   const unsigned span = (unsigned)((p.bidir ? p.L - 1 : iq) - p0);
   auto seen = [&](int key) __attribute__((always_inline)) -> bool { return (unsigned)(key - p0) <= span; };
-  auto add = [&](const float (&ds)[4]) __attribute__((always_inline)) { Ops::add(kt, ds, dq); };
+  auto add = [&](const float (&ds)[4]) __attribute__((always_inline)) { Ops::add(kt, ds, dq_part); };
   auto arg = [&](float s, float l) __attribute__((always_inline)) -> float { return Ops::kBf ? fmaf(kc, s, -l) : s - l; };
   auto body = [&](auto kind, auto unit, Word &mask) __attribute__((always_inline)) {
     constexpr int KIND = decltype(kind)::value;
@@ -1434,7 +1499,21 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
     if (p.sblk == 1) {
       float qd[CPL];
       Ops::floats(qf, qd);
+      float qw[CPL * 4], ow[CPL * 4];
+      if constexpr (D == 8) {
+        whole_row(qd, qw);
+        whole_row(os, ow);
+      }
       diagonals(p, I, T0, J_hi, [&](int d) __attribute__((always_inline)) {
+        if constexpr (D == 8) {
+          const int t = min(max(I + d * (1 << g), T0), NT - 1), key = iq + kTile * d * (1 << g);
+          float kr[D], vr[D];
+          Kr.whole(t, kr);
+          Vr.whole(t, vr);
+          const float e = __builtin_amdgcn_exp2f(arg(dot_n(qw, kr, 0.0f), l2_st));
+          const bool ok = (key >= p0) & (key < p.last_lo);
+          add_row(dq_part, ok ? e * (dot_n(ow, vr, 0.0f) - D_st) : 0.0f, kr);
+        } else {
         float s[4], x[4], ko[4][NMB][4];
 #pragma unroll
         for (int n = 0; n < 4; ++n) {
@@ -1456,7 +1535,8 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
         const bool ok = (key >= p0) & (key < p.last_lo);
         spread_g(ok ? e * (gv - D_st) : 0.0f, x);
 #pragma unroll
-        for (int n = 0; n < 4; ++n) add_own(dq, x[n], ko[n]);
+        for (int n = 0; n < 4; ++n) add_own(dq_part, x[n], ko[n]);
+        }
       });
     }
     if (p.sblk <= 1) walk(std::true_type{});
@@ -1487,6 +1567,7 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
       }
     }
   }
+  total<D>(dq_part, dq);
   const int el = fresh_lane(), ei = I * kTile + (el & 15);
   if (ei < p.L) store_grad_row<T, D>(dQ_head + (size_t)ei * D, dq, p.scale, ei >= p0, p, true, ei, el >> 4);
   return __all((ei < p0) | (ei >= p.L) | finite(abs_sum(dq)));
@@ -1499,15 +1580,15 @@ template <typename T, int D, int BK, bool PERPOS, bool CAREFUL, typename Src>
 __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT, int p0, int lane, typename Operands<T, D>::Row &kf,
                                          const typename Operands<T, D>::Row &vf, int hpg, const Src &src, T *dK_head, T *dV_head)
 {
-  constexpr int CPL = Geo<D>::CPL, NMB = Geo<D>::NMB;
+  constexpr int CPL = Geo<D>::CPL, NMB = Geo<D>::NMB, NACC = Geo<D>::NACC;
   const int q = lane & 15, g = lane >> 4;
   const int NWb = (p.NB + 31) / 32;
   using Ops = Operands<T, D>;
   const float c2 = p.scale * kLog2eF, kc = Ops::kBf ? c2 : 1.0f;  // (kc: what a product of rows is still to be multiplied by)
   const int j = J * kTile + q;
-  f32x4 dk[NMB], dv[NMB];
-  clear(dk);
-  clear(dv);
+  f32x4 dk_part[NACC], dv_part[NACC];
+  clear(dk_part);
+  clear(dv_part);
   Ops::scale(kf, c2);
   const int kid_k = mask_block(p, j);
   const bool last_k = j >= p.last_lo;
@@ -1563,8 +1644,8 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
     };
     // dV^T += dO^T (a P), dK^T += Q^T dS
     auto add = [&](const float (&pc)[4], const float (&ds)[4]) __attribute__((always_inline)) {
-      Ops::add(gc, pc, dv);
-      Ops::add(qc, ds, dk);
+      Ops::add(gc, pc, dv_part);
+      Ops::add(qc, ds, dk_part);
     };
     auto body = [&](auto kind, auto unit, Word &mask) __attribute__((always_inline)) {
       constexpr int KIND = decltype(kind)::value;
@@ -1692,7 +1773,26 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
         float kd[CPL], vd[CPL];
         Ops::floats(kf, kd);
         Ops::floats(vf, vd);
+        float kw[CPL * 4], vw[CPL * 4];
+        if constexpr (D == 8) {
+          whole_row(kd, kw);
+          whole_row(vd, vw);
+        }
         diagonals(p, J, I_lo, NT - 1, [&](int d) __attribute__((always_inline)) {
+          // this lane group's distance
+          const int i = j + kTile * d * (1 << g), tg = min(max(J + d * (1 << g), I_lo), NT - 1);
+          auto constant = [&](int k) { return src.row_constant(hl, tg, k); };
+          const bool ok = (i >= p0) & (i < p.L) & !last_k;
+          if constexpr (D == 8) {
+            float qr[D], gr[D];
+            Qr.whole(tg, qr);
+            Gr.whole(tg, gr);
+            const float e = __builtin_amdgcn_exp2f(arg(dot_n(kw, qr, 0.0f), constant(5)));
+            const float pr = ok ? e : 0.0f, zd = constant(1), as = 1.0f - constant(0);
+            t_st = fmaf(zd, pr, t_st);
+            add_row(dv_part, as * pr, gr);
+            add_row(dk_part, pr * fmaf(as, dot_n(vw, gr, 0.0f), fmaf(zd, wv_st, -constant(3))), qr);
+          } else {
           float s[4], x[4], qo[4][NMB][4], go[4][NMB][4];
 #pragma unroll
           for (int n = 0; n < 4; ++n) {
@@ -1716,19 +1816,17 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
               Gr.own(t, go[n]);
             }
           }
-          // this lane group's distance
-          const int i = j + kTile * d * (1 << g), tg = min(max(J + d * (1 << g), I_lo), NT - 1);
-          auto constant = [&](int k) { return src.row_constant(hl, tg, k); };
           const float e = __builtin_amdgcn_exp2f(arg(gather_g(s), constant(5))), gd = gather_g(x);
-          const float pr = (i >= p0) & (i < p.L) & !last_k ? e : 0.0f;
+          const float pr = ok ? e : 0.0f;
           const float zd = constant(1), as = 1.0f - constant(0);
           t_st = fmaf(zd, pr, t_st);
           spread_g(as * pr, s);
           spread_g(pr * fmaf(as, gd, fmaf(zd, wv_st, -constant(3))), x);
 #pragma unroll
           for (int n = 0; n < 4; ++n) {
-            add_own(dv, s[n], go[n]);
-            add_own(dk, x[n], qo[n]);
+            add_own(dv_part, s[n], go[n]);
+            add_own(dk_part, x[n], qo[n]);
+          }
           }
         });
       }
@@ -1736,18 +1834,31 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
     else if (p.sblk <= 1) walk(std::true_type{});
     else walk(std::false_type{});
     // the gate part of dV: sum_i dz_i P_ij times the gate row of the branch
-    t_lt = sum_g(t_lt);
-    t_st = sum_g(t_st);
+    if constexpr (Geo<D>::kQuads) {  // (a lane's part of the sums, like the accumulators)
 #pragma unroll
-    for (int mb = 0; mb < NMB; ++mb)
-      if (16 * mb + 4 * g < D) {
+      for (int h = 0; h < NACC; ++h) {
+        float x[4], y[4];
+        load_n<4>(wrow + 4 * h, x);
+        load_n<4>(wrow + D + 4 * h, y);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dv_part[h][r] += fmaf(t_lt, x[r], t_st * y[r]);
+      }
+    } else {
+      t_lt = sum_g(t_lt);
+      t_st = sum_g(t_st);
+#pragma unroll
+      for (int mb = 0; mb < NMB; ++mb) {
         float x[4], y[4];
         load_n<4>(wrow + 16 * mb + 4 * g, x);
         load_n<4>(wrow + D + 16 * mb + 4 * g, y);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) dv[mb][r] += fmaf(t_lt, x[r], t_st * y[r]);
+        for (int r = 0; r < 4; ++r) dv_part[mb][r] += fmaf(t_lt, x[r], t_st * y[r]);
       }
+    }
   }
+  f32x4 dk[NMB], dv[NMB];
+  total<D>(dk_part, dk);
+  total<D>(dv_part, dv);
   const int el = fresh_lane(), ej = J * kTile + (el & 15);
   if (ej < p.L) {
     store_grad_row<T, D>(dK_head + (size_t)ej * D, dk, p.scale, ej >= p0, p, true, ej, el >> 4);
@@ -1781,9 +1892,9 @@ __device__ __forceinline__ void query_tiles_carefully(const KParams &p, int firs
 // stages: kBwdStageGate writes those and the partial gate gradients, kBwdStageDQ writes dQ (the row constants are
 // formed in either case).
 // (Wavefronts per SIMD, here and in the dK/dV kernel: those that the walk's registers allow, which the compiler would exceed for
-// the repeated walk.)
+// the repeated walk.  d = 8 at B=32 H=8 L=2000: dQ with six 78 us, with five 69.)
 template <typename T, int D, int BK, bool PERPOS>
-__global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(D == 32 ? 4 : D == 16 ? 5 : 6))) void bwd_dq_small_kernel(
+__global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(D == 32 ? 4 : 5))) void bwd_dq_small_kernel(
     const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V, const int *__restrict__ valid_len,
     const int *__restrict__ sel, const float *__restrict__ gate_w, const float *__restrict__ gate_b,
     const float *__restrict__ o_lt, const float *__restrict__ o_st, const float *__restrict__ lse_lt,
@@ -1841,7 +1952,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
 }
 
 template <typename T, int D, int BK, bool PERPOS>
-__global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(D == 32 ? 3 : D == 8 && BK == 16 && !PERPOS ? 5 : 4))) void bwd_dkv_small_kernel(
+__global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(D == 32 ? 3 : 4))) void bwd_dkv_small_kernel(
     const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V, const int *__restrict__ valid_len,
     const float *__restrict__ gate_w, const T *__restrict__ dO, SmallWs ws, T *__restrict__ dK, T *__restrict__ dV, int hpg, int parts,
     KParams p)
@@ -2043,7 +2154,10 @@ struct SmallPlan {
   int waves, parts;
   size_t lds;
 };
-constexpr size_t kSmallLds = 80 * 1024 - 4096;  // two workgroups per CU
+// LDS up to which a workgroup holds whole heads: two of them per CU at d = 32, three below, whose lighter walks want the wavefronts
+// (a training step, us, by limit 76 / 50 / 40 KB: B=300 H=8 d=16 L=300 296 / 280 / 277, L=450 446 / 422 / 421, d=8 L=450 289 / 288 / 297,
+// L=600 455 / 414 / 416; B=32 d=8 L=1000 110 / 98 / -; B=1024 H=2 d=32 L=200 339 / 410 / 411)
+size_t small_lds_limit(const KParams &p) { return p.d == 32 ? 76 * 1024 : 44 * 1024; }
 // Few heads: eight wavefronts each, a head's latency counts.  Many: four, whose shares are longer and better balanced (always a
 // multiple of the four SIMDs: with five or six wavefronts the backward took 1.4 times as long).
 bool many_heads(int units) { return units >= 2048; }
@@ -2058,14 +2172,14 @@ SmallPlan stream_plan(const KParams &p, int units, size_t words_per_wave)
   return s;
 }
 // floats of a staged row: kLdsRow
-int lds_row(const KParams &p, int dtype) { return dtype == 1 && p.d >= 16 ? (p.d == 32 ? 20 : 10) : p.d + 4; }
+int lds_row(const KParams &p, int dtype) { return dtype == 1 && p.d >= 16 ? (p.d == 32 ? 20 : 10) : p.d == 8 ? 8 : p.d + 4; }
 SmallPlan fwd_plan(const KParams &p, int dtype, bool perpos, int hpg)
 {
   const size_t rows = (size_t)(p.L + kTile - 1) / kTile * kTile;
   const int units = p.B * p.H / hpg;
   SmallPlan s{true, false, res_waves(units), 1, 0};
   s.lds = (2 * rows * lds_row(p, dtype) + (size_t)s.waves * lt_words(p, perpos)) * sizeof(float);
-  if (p.nq == p.NB && s.lds <= kSmallLds) return s;
+  if (p.nq == p.NB && s.lds <= small_lds_limit(p)) return s;
   s = stream_plan(p, p.B * p.H, lt_words(p, perpos));
   if (p.nq != p.NB) s = SmallPlan{false, false, 1, 1, lt_words(p, perpos) * sizeof(float)};  // serving mode: one query tile per head
   return s;
@@ -2077,7 +2191,7 @@ SmallPlan bwd_plan(const KParams &p, int dtype, bool perpos, int hpg)
   for (int overlay = many_heads(units) ? 1 : 0; overlay < 2; ++overlay) {
     SmallPlan s{true, overlay != 0, res_waves(units), 1, 0};
     s.lds = (size_t)ResLayout(p, lds_row(p, dtype), perpos, hpg, overlay, s.waves).total * sizeof(float);
-    if (s.lds <= kSmallLds) return s;
+    if (s.lds <= small_lds_limit(p)) return s;
   }
   return stream_plan(p, p.B * p.H, lt_words(p, perpos));
 }

@@ -87,6 +87,8 @@ def test_rope_backward_and_serving_mode():
     (32, 128), (32, 129), (32, 240), (32, 241), (32, 256), (32, 257),
     (16, 224), (16, 225), (16, 416), (16, 417), (16, 480), (16, 481),
     (8, 352), (8, 353), (8, 640), (8, 641), (8, 800), (8, 801),
+    (16, 128), (16, 129), (16, 240), (16, 241), (16, 272), (16, 273),
+    (8, 288), (8, 289), (8, 496), (8, 497), (8, 688), (8, 689),
 ])
 def test_edges_of_the_resident_range(d, L):
     # the longest heads (and one position more) whose backward holds Q and dO beside K and V, whose backward holds them in
@@ -177,6 +179,9 @@ def test_many_heads_streamed_tiles_and_large_logits(dtype, d, b, B_, H, L, sblk,
 @pytest.mark.parametrize("d,window,L,sblk,bidir", [
     (8, 1, 130, 1, False),     # the window is the query itself: the powers of two up to 16 come from the neighbouring tile
     (8, 2, 1100, 1, False),    # distances up to 1024, 70 tiles: two batches of four distances, two words of tiles
+    (8, 5, 330, 1, True),      # d = 8, both directions: parts of the sums in the lane groups, a lane group to a distance
+    (8, 3, 33, 1, False),      # ... a last tile of one row, distances past either end
+    (8, 1, 2500, 1, True),     # ... streamed
     (16, 17, 300, 1, False),   # the window ends with the neighbouring tile ...
     (16, 18, 300, 1, False),   # ... one position into the next: distance 32 is then a test of the walk, 64 the first diagonal
     (16, 33, 513, 1, True),    # the table of distances is full; both directions; past 32 tiles
