@@ -11,6 +11,7 @@
 // far keys of each row (power-of-two distances, last block) are read straight from memory by the
 // row's own lanes instead of being walked tile by tile.
 #include "common.h"
+#include "gate_reduce.h"
 #include "launch.h"
 #include "mfma_common.h"
 
@@ -337,6 +338,104 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D <= 32 ? 4 
 }
 
 // =============================================================================================
+// Backward: inverse selection list.  For each key block J of a (row, head): the list of
+// query blocks I whose selection holds J, in a fixed, deterministic order.
+// offs [B*H,(NB+1)], items [B*H,NB*k].
+// One workgroup of W wavefronts per (row, head); wavefront w owns a contiguous range of query
+// blocks and its own counters.  Counting and filling use LDS integer atomics, one selection
+// row per wavefront instruction: a row lists distinct blocks, and the LDS executes one
+// wavefront's instructions in order, so the order inside a wavefront's range is that of the
+// fill loop: by 64-entry chunk of the selection row, then by I (ascending in I whenever
+// topk <= 64); the ranges are laid out one after the other per key block (the scan hands each
+// wavefront its base).  The consumers sum over the list and need no particular order, only the
+// same one on every run.
+// =============================================================================================
+constexpr int kInvWaves = 4;      // wavefronts per (row, head) when the counters fit
+constexpr int kInvWavesMaxNB = 2048;
+
+// lds: cnt[W][NB+1], then few[NB+1] bytes
+__device__ __forceinline__ void inverse_list(const int *__restrict__ sel, const int *__restrict__ valid_len, int *__restrict__ offs,
+                                             int *__restrict__ items, const KParams &p, int bh, int *inv_lds)
+{
+  const int W = blockDim.x >> 6;
+  const int stride = p.NB + 1;
+  int *cnt = inv_lds;
+  unsigned char *few = reinterpret_cast<unsigned char *>(inv_lds + W * stride);  // query block whose selected
+                                                                                  // past blocks hold few valid keys
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wv = tid >> 6;
+  const int *s = sel + (size_t)bh * p.NB * p.k;
+  int *o = offs + (size_t)bh * (p.NB + 1);
+  int *it = items + (size_t)bh * p.NB * p.k;
+  const int p0 = p.L - clamp_len(valid_len[bh / p.H], p.L);
+  const int per = (p.NB + W - 1) / W;
+  const int I_lo = wv * per, I_hi = min(p.NB, I_lo + per);
+  int *mine = cnt + wv * stride;
+  for (int x = tid; x < W * stride; x += blockDim.x) cnt[x] = 0;
+  for (int J = tid; J <= p.NB; J += blockDim.x) few[J] = 1;
+  __syncthreads();
+  for (int e0 = 0; e0 < p.k; e0 += 64) {
+    const int e = e0 + lane;
+#pragma unroll 8
+    for (int I = I_lo; I < I_hi; ++I) {
+      const int J = e < p.k ? s[(size_t)I * p.k + e] : -1;
+      if (J >= 0 && J < p.NB && (J <= I || p.bidir)) atomicAdd(&mine[J], 1);
+      // an earlier block with at least kInvFewKeys valid keys gives every row of I that many keys
+      const int vcount = min((J + 1) * p.b, p.L) - max(J * p.b, p0);
+      if (__ballot(J >= 0 && J < I && vcount >= kInvFewKeys) != 0ull && lane == 0) few[I] = 0;
+    }
+  }
+  __syncthreads();
+  // exclusive scan over (key block, wavefront) in chunks of 64 key blocks; o[NB] receives the total
+  if (wv == 0) {
+    int carry = 0;
+    for (int J0 = 0; J0 <= p.NB; J0 += 64) {
+      const int J = J0 + lane;
+      int c = 0;
+      if (J < p.NB)
+        for (int w = 0; w < W; ++w) c += cnt[w * stride + J];
+      int incl = c;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const int up = __shfl_up(incl, off);
+        if (lane >= off) incl += up;
+      }
+      if (J <= p.NB) {
+        int base = carry + incl - c;
+        o[J] = base;
+        if (J < p.NB)
+          for (int w = 0; w < W; ++w) {
+            const int cw = cnt[w * stride + J];
+            cnt[w * stride + J] = base;
+            base += cw;
+          }
+      }
+      carry += __shfl(incl, 63);
+    }
+  }
+  __syncthreads();
+  for (int e0 = 0; e0 < p.k; e0 += 64) {
+    const int e = e0 + lane;
+#pragma unroll 8
+    for (int I = I_lo; I < I_hi; ++I) {
+      const int J = e < p.k ? s[(size_t)I * p.k + e] : -1;
+      if (J >= 0 && J < p.NB && (J <= I || p.bidir)) it[atomicAdd(&mine[J], 1)] = I | ((int)few[I] << kInvFewShift);
+    }
+  }
+}
+size_t inverse_list_lds(const KParams &p, int W) { return (size_t)W * (p.NB + 1) * sizeof(int) + (size_t)(p.NB + 1 + 3) / 4 * 4; }
+
+__global__ __launch_bounds__(64 * kInvWaves) void inverse_list_kernel(const int *__restrict__ sel,
+                                                                      const int *__restrict__ valid_len,
+                                                                      int *__restrict__ offs, int *__restrict__ items,
+                                                                      KParams p)
+{
+  extern __shared__ int inv_lds[];
+  inverse_list(sel, valid_len, offs, items, p, blockIdx.x, inv_lds);
+}
+
+// =============================================================================================
 // Backward, step 1: gate backward per row + per-chunk partial gate-weight gradients.
 //   rowstat[row] = (alpha, dz, D_lt, D_st)
 //   g_x, rowI_x: the branch's rounded upstream gradient and row constants (matrix-core path, see below)
@@ -348,7 +447,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D <= 32 ? 4 
 // B=16 H=8 L=8192: 183 -> 173 us (5.7 TB/s).
 // The gate-weight partials accumulate in registers and meet in LDS in a fixed order.
 // =============================================================================================
+// The first `lists` workgroups make the inverse selection lists instead: a chain of latencies (8 us at B=128 H=4 L=1024, 26 at B=16
+// H=8 L=8192 as a launch of its own) beside work that waits for memory.
 constexpr int kPrepRows = 128;
+constexpr size_t kPrepListLds = 8320;  // LDS that every head size has for them: up to 488 blocks
 
 // four consecutive elements as loaded, and as floats (zeros unless `keep`)
 struct Raw4f { uint4 w; };
@@ -396,7 +498,8 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(const float *__restrict__
                                                        uint16_t *__restrict__ g_lt,
                                                        uint16_t *__restrict__ g_st,
                                                        uint4 *__restrict__ rowI_lt,
-                                                       uint4 *__restrict__ rowI_st, KParams p)
+                                                       uint4 *__restrict__ rowI_st, const int *__restrict__ sel,
+                                                       int *__restrict__ offs, int *__restrict__ items, int lists, KParams p)
 {
   constexpr int CPL = D >= 64 ? 8 : 4;  // channels per lane, in groups of four D/2 apart
   constexpr int NG = CPL / 4;
@@ -404,7 +507,12 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(const float *__restrict__
   constexpr int RPW = 64 / LPR;         // rows per wavefront step
   constexpr int RPS = 4 * RPW;          // rows per workgroup step
   constexpr int G = 2 * D + 1;
+  static_assert(sizeof(float) * 4 * RPW * G >= kPrepListLds && 4 == kInvWaves, "the lists use the same LDS and wavefronts");
   __shared__ float red[4 * RPW][G];
+  if ((int)blockIdx.x < lists) {
+    inverse_list(sel, valid_len, offs, items, p, blockIdx.x, reinterpret_cast<int *>(&red[0][0]));
+    return;
+  }
   const int t = threadIdx.x;
   const int wave = t >> 6, lane = t & 63;
   const int sub = lane % LPR, rg = lane / LPR;
@@ -412,7 +520,7 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(const float *__restrict__
   const int nchunk = (p.L + kPrepRows - 1) / kPrepRows;
   // (chunk by chunk the workgroups would go to the XCDs in turn, and where there are eight chunks to a head, or a multiple, one XCD
   // would have the last, always valid ones to do and another nothing but padding)
-  const unsigned vid = mfma::xcd_spread(blockIdx.x, gridDim.x / nchunk, nchunk);
+  const unsigned vid = mfma::xcd_spread(blockIdx.x - lists, (gridDim.x - lists) / nchunk, nchunk);
   const int bh = (int)(vid / nchunk);
   const int chunk = (int)(vid % nchunk);
   const int h = bh % p.H;
@@ -555,9 +663,7 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(const float *__restrict__
   }
 }
 
-// Reduction of the partial gate gradients over batch rows and chunks, in a fixed order: a workgroup owns
-// kGateCols of the 2d+1 columns of one head, 64 threads per column take every 64th partial row in four running
-// sums, and a tree over the 64 closes the column.  One launch: at these sizes (a few MB at most) a second
+// The partial gate gradients' sum, where no other kernel takes it along.  One launch: at these sizes (a few MB at most) a second
 // level costs more in launching (4-5 us) than it saves in reading.
 constexpr int kGateCols = 16;
 
@@ -565,34 +671,8 @@ __global__ __launch_bounds__(1024) void bwd_gate_reduce_kernel(const float *__re
                                                                float *__restrict__ d_gate_w,
                                                                float *__restrict__ d_gate_b, int nchunk, KParams p)
 {
-  __shared__ float red[64][kGateCols + 1];
-  const int h = blockIdx.x;
-  const int G = 2 * p.d + 1;
-  const int N = p.B * nchunk;  // partial rows of this head, ordered by (batch row, chunk)
-  const int x = threadIdx.x % kGateCols, y = threadIdx.x / kGateCols;
-  const int c = blockIdx.y * kGateCols + x;
-  float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  if (c < G) {
-    auto at = [&](int nn) -> float {
-      const int r = nn / nchunk, ch = nn - r * nchunk;
-      return partial[(((size_t)r * p.H + h) * nchunk + ch) * G + c];
-    };
-    int nn = y;
-    for (; nn + 192 < N; nn += 256) {
-      const float v0 = at(nn), v1 = at(nn + 64), v2 = at(nn + 128), v3 = at(nn + 192);
-      acc[0] += v0; acc[1] += v1; acc[2] += v2; acc[3] += v3;
-    }
-    for (; nn < N; nn += 64) acc[0] += at(nn);
-  }
-  red[y][x] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
-  for (int half = 32; half >= 1; half >>= 1) {
-    __syncthreads();
-    if (y < half) red[y][x] += red[y + half][x];
-  }
-  if (y == 0 && c < G) {
-    if (c < 2 * p.d) d_gate_w[(size_t)h * 2 * p.d + c] = red[0][x];
-    else if (d_gate_b) d_gate_b[h] = red[0][x];
-  }
+  __shared__ float red[kGateRows][kGateCols + 1];
+  gate_reduce<1024, kGateCols>(partial, d_gate_w, d_gate_b, nchunk, p, blockIdx.x, blockIdx.y * kGateCols, red);
 }
 
 // =============================================================================================
@@ -748,97 +828,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D <= 32 ? 3 
     for (int c = 0; c < D; ++c) dq[c] *= p.scale;
     unrope_row<D>(p, i, dq);
     store_row<T, D>(dQ + rowoff, dq);
-  }
-}
-
-// =============================================================================================
-// Backward, step 3: inverse selection list.  For each key block J of a (row, head): the list of
-// query blocks I whose selection holds J, in a fixed, deterministic order.
-// offs [B*H,(NB+1)], items [B*H,NB*k].
-// One workgroup of W wavefronts per (row, head); wavefront w owns a contiguous range of query
-// blocks and its own counters.  Counting and filling use LDS integer atomics, one selection
-// row per wavefront instruction: a row lists distinct blocks, and the LDS executes one
-// wavefront's instructions in order, so the order inside a wavefront's range is that of the
-// fill loop: by 64-entry chunk of the selection row, then by I (ascending in I whenever
-// topk <= 64); the ranges are laid out one after the other per key block (the scan hands each
-// wavefront its base).  The consumers sum over the list and need no particular order, only the
-// same one on every run.
-// =============================================================================================
-constexpr int kInvWaves = 4;      // wavefronts per (row, head) when the counters fit
-constexpr int kInvWavesMaxNB = 2048;
-
-__global__ __launch_bounds__(64 * kInvWaves) void inverse_list_kernel(const int *__restrict__ sel,
-                                                                      const int *__restrict__ valid_len,
-                                                                      int *__restrict__ offs, int *__restrict__ items,
-                                                                      KParams p)
-{
-  extern __shared__ int inv_lds[];  // cnt[W][NB+1], then few[NB+1] bytes
-  const int W = blockDim.x >> 6;
-  const int stride = p.NB + 1;
-  int *cnt = inv_lds;
-  unsigned char *few = reinterpret_cast<unsigned char *>(inv_lds + W * stride);  // query block whose selected
-                                                                                  // past blocks hold few valid keys
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wv = tid >> 6;
-  const int bh = blockIdx.x;
-  const int *s = sel + (size_t)bh * p.NB * p.k;
-  int *o = offs + (size_t)bh * (p.NB + 1);
-  int *it = items + (size_t)bh * p.NB * p.k;
-  const int p0 = p.L - clamp_len(valid_len[bh / p.H], p.L);
-  const int per = (p.NB + W - 1) / W;
-  const int I_lo = wv * per, I_hi = min(p.NB, I_lo + per);
-  int *mine = cnt + wv * stride;
-  for (int x = tid; x < W * stride; x += blockDim.x) cnt[x] = 0;
-  for (int J = tid; J <= p.NB; J += blockDim.x) few[J] = 1;
-  __syncthreads();
-  for (int e0 = 0; e0 < p.k; e0 += 64) {
-    const int e = e0 + lane;
-#pragma unroll 8
-    for (int I = I_lo; I < I_hi; ++I) {
-      const int J = e < p.k ? s[(size_t)I * p.k + e] : -1;
-      if (J >= 0 && J < p.NB && (J <= I || p.bidir)) atomicAdd(&mine[J], 1);
-      // an earlier block with at least kInvFewKeys valid keys gives every row of I that many keys
-      const int vcount = min((J + 1) * p.b, p.L) - max(J * p.b, p0);
-      if (__ballot(J >= 0 && J < I && vcount >= kInvFewKeys) != 0ull && lane == 0) few[I] = 0;
-    }
-  }
-  __syncthreads();
-  // exclusive scan over (key block, wavefront) in chunks of 64 key blocks; o[NB] receives the total
-  if (wv == 0) {
-    int carry = 0;
-    for (int J0 = 0; J0 <= p.NB; J0 += 64) {
-      const int J = J0 + lane;
-      int c = 0;
-      if (J < p.NB)
-        for (int w = 0; w < W; ++w) c += cnt[w * stride + J];
-      int incl = c;
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const int up = __shfl_up(incl, off);
-        if (lane >= off) incl += up;
-      }
-      if (J <= p.NB) {
-        int base = carry + incl - c;
-        o[J] = base;
-        if (J < p.NB)
-          for (int w = 0; w < W; ++w) {
-            const int cw = cnt[w * stride + J];
-            cnt[w * stride + J] = base;
-            base += cw;
-          }
-      }
-      carry += __shfl(incl, 63);
-    }
-  }
-  __syncthreads();
-  for (int e0 = 0; e0 < p.k; e0 += 64) {
-    const int e = e0 + lane;
-#pragma unroll 8
-    for (int I = I_lo; I < I_hi; ++I) {
-      const int J = e < p.k ? s[(size_t)I * p.k + e] : -1;
-      if (J >= 0 && J < p.NB && (J <= I || p.bidir)) it[atomicAdd(&mine[J], 1)] = I | ((int)few[I] << kInvFewShift);
-    }
   }
 }
 
@@ -1137,17 +1126,20 @@ static void launch_bwd_t(const KParams &p, int dtype, const BwdArgs &a, unsigned
   const unsigned BH = (unsigned)(p.B * p.H);
   const bool mfma = bwd_mfma_supported(p, dtype);
 
+  const bool with_lists = (stages & kBwdStageGate) && (stages & kBwdStageInverse) && inverse_list_lds(p, kInvWaves) <= kPrepListLds &&
+                          (unsigned long long)BH * (w.nchunk + 1) <= 0x7FFFFFFFull;
   if (stages & kBwdStageGate) {
-    BLOSSOM_LAUNCH((bwd_prep_kernel<T, D>), dim3(BH * w.nchunk), dim3(256), 0, st,
+    const unsigned lists = with_lists ? BH : 0u;
+    BLOSSOM_LAUNCH((bwd_prep_kernel<T, D>), dim3(BH * w.nchunk + lists), dim3(256), 0, st,
                        (const float *)a.o_lt, (const float *)a.o_st, (const T *)a.dO, a.valid_len, a.gate_w,
-                       a.gate_b, w.rowstat, w.partial, a.lse_lt, a.lse_st, w.g_lt, w.g_st, w.rowI_lt, w.rowI_st, p);
-    launch_gate_reduce(p, a, w.partial, w.nchunk, st);
+                       a.gate_b, w.rowstat, w.partial, a.lse_lt, a.lse_st, w.g_lt, w.g_st, w.rowI_lt, w.rowI_st, a.sel,
+                       w.offs, w.items, (int)lists, p);
+    if (!mfma || !bwd_mfma_takes_gate(p, stages)) launch_gate_reduce(p, a, w.partial, w.nchunk, st);
     if (launch_failed()) return;
   }
-  if (stages & kBwdStageInverse) {
+  if ((stages & kBwdStageInverse) && !with_lists) {
     const int W = p.NB <= kInvWavesMaxNB ? kInvWaves : 1;
-    const size_t lds = (size_t)W * (p.NB + 1) * sizeof(int) + (size_t)(p.NB + 1 + 3) / 4 * 4;
-    BLOSSOM_LAUNCH(inverse_list_kernel, dim3(BH), dim3(64 * W), lds, st, a.sel, a.valid_len, w.offs, w.items,
+    BLOSSOM_LAUNCH(inverse_list_kernel, dim3(BH), dim3(64 * W), inverse_list_lds(p, W), st, a.sel, a.valid_len, w.offs, w.items,
                        p);
   }
   if (mfma) {

@@ -122,6 +122,7 @@ void launch_bwd_small(const KParams &p, int dtype, const BwdArgs &a, const Small
 
 // mfma_bwd.hip: matrix-core dQ and dK/dV for bf16, d = 64, b in {32, 64}
 bool bwd_mfma_supported(const KParams &p, int dtype);
+bool bwd_mfma_takes_gate(const KParams &p, unsigned stages);  // does it sum the partial gate gradients too?
 void launch_bwd_mfma(const KParams &p, const BwdArgs &a, const BwdWorkspace &w, unsigned stages, hipStream_t st);
 
 // out_proj.hip: output projection + residual + LayerNorm around the attention (Eq. 4, the equation after Eq. 19)

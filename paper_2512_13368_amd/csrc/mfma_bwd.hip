@@ -29,6 +29,7 @@
 // masks are bits (two instructions an element instead of four, and 5 to 20 spilled registers fewer), and at block 64 a unit of
 // 32 keys (queries) none of the wavefront's rows sees (keys are seen by) is skipped.  A training step at B=16 H=8 L=8192 k=16
 // w=128 2078 -> 2042 us with both, at B=128 H=4 L=1024 k=8 w=64 in blocks of 32 403 -> 398 us.
+#include "gate_reduce.h"
 #include "launch.h"
 #include "mfma_common.h"
 
@@ -961,10 +962,17 @@ __global__ __launch_bounds__(BLK * 2) __attribute__((amdgpu_waves_per_eu(2, 2)))
   bwd_dkv_body<BLK, EQ15, SUB>(BWD_DKV_ARGS, p, blockIdx.x, lds_t0, lds_t1, lds_t2, lds_t3, rc_s);
 }
 
+// workgroups that sum the partial gate gradients: kGateCols columns of a head each
+constexpr int kGateCols = 8;
+__host__ __device__ inline int gate_groups(const KParams &p) { return (2 * p.d + kGateCols) / kGateCols; }
+inline unsigned gate_workgroups(const KParams &p) { return ((unsigned)(p.H * gate_groups(p)) + 7u) / 8u * 8u; }
+
 // dQ and dK/dV in ONE launch (the full backward call): the first B*H*NB workgroups take the key blocks, the
 // rest the query blocks.  The two kernels need the same workgroup shape, the same two wavefronts per SIMD and
 // nearly the same LDS, so nothing is lost by the union, and the short dQ workgroups fill the slots that the
-// tail of the skewed dK/dV walks leaves idle (and one launch gap goes).
+// tail of the skewed dK/dV walks leaves idle (and one launch gap goes).  Before them come `gate_wgs` workgroups, a multiple of 8 so
+// that the others keep their XCDs, that sum the partial gate gradients (7.5 us as a launch of its own at B=128 H=4 L=1024; at
+// block size 64 the walks come out slower beside that code, 1280 against 1240 us at B=16 H=8 L=8192, and it stays a launch of its own).
 //
 // REFILL.  At block size 32 a workgroup is one wavefront, its body of 12 or 18 matrix instructions is shorter than a
 // load's latency under load, and LDS holds two tiles for each of the eight wavefronts of a CU.  So a tile is read to
@@ -975,13 +983,27 @@ __global__ __launch_bounds__(BLK * 2) __attribute__((amdgpu_waves_per_eu(2, 2)))
 template <int BLK, bool EQ15, bool SUB>
 __global__ __launch_bounds__(BLK * 2) __attribute__((amdgpu_waves_per_eu(2, 2))) void bwd_both_mfma_kernel(
     BWD_DQ_PARAMS, const int *__restrict__ offs, const int *__restrict__ items, uint16_t *__restrict__ dK,
-    uint16_t *__restrict__ dV, KParams p)
+    uint16_t *__restrict__ dV, const float *__restrict__ partial, float *__restrict__ d_gate_w, float *__restrict__ d_gate_b, int nchunk,
+    unsigned gate_wgs, KParams p)
 {
   BWD_LDS_TILES(BLK);  // the four staging tiles serve either role
   __shared__ __attribute__((aligned(16))) uint4 rc_s[2][BLK];
-  const unsigned n = (unsigned)(p.B * p.H * p.NB);
-  if (blockIdx.x < n) bwd_dkv_body<BLK, EQ15, SUB>(BWD_DKV_ARGS, p, blockIdx.x, lds_t0, lds_t1, lds_t2, lds_t3, rc_s);
-  else bwd_dq_body<BLK, EQ15, SUB>(BWD_DQ_ARGS, p, blockIdx.x - n, lds_t0, lds_t1, lds_t2, lds_t3);
+  if (BLK == 32 && blockIdx.x < gate_wgs) {
+    const int groups = gate_groups(p), h = blockIdx.x / groups;
+    if (h < p.H)
+      gate_reduce<BLK * 2, kGateCols>(partial, d_gate_w, d_gate_b, nchunk, p, h, (blockIdx.x - h * groups) * kGateCols,
+                                      reinterpret_cast<float(*)[kGateCols + 1]>(lds_t0));
+    return;
+  }
+  const unsigned n = (unsigned)(p.B * p.H * p.NB), id = blockIdx.x - gate_wgs;
+  if (id < n) bwd_dkv_body<BLK, EQ15, SUB>(BWD_DKV_ARGS, p, id, lds_t0, lds_t1, lds_t2, lds_t3, rc_s);
+  else bwd_dq_body<BLK, EQ15, SUB>(BWD_DQ_ARGS, p, id - n, lds_t0, lds_t1, lds_t2, lds_t3);
+}
+
+bool bwd_mfma_takes_gate(const KParams &p, unsigned stages)
+{
+  constexpr unsigned all = kBwdStageGate | kBwdStageDQ | kBwdStageDKV;
+  return p.b == 32 && (stages & all) == all && 2ull * p.B * p.H * p.NB + gate_workgroups(p) <= 0x7FFFFFFFull;
 }
 
 bool bwd_mfma_supported(const KParams &p, int dtype)
@@ -1008,10 +1030,12 @@ void launch_bwd_mfma(const KParams &p, const BwdArgs &a, const BwdWorkspace &w, 
   const bool eq15 = p.sblk != 0;
   const bool sub = eq15 && p.sblk < p.b;  // mask block smaller than the tile
   if (do_dq && do_dkv && 2ull * grid <= 0x7FFFFFFFull) {
+    const unsigned gate_wgs = bwd_mfma_takes_gate(p, stages) ? gate_workgroups(p) : 0u;
     auto go = [&](auto kernel, unsigned threads) {
-      hipLaunchKernelGGL(kernel, dim3(2 * grid), dim3(threads), 0, st, u16(a.Q), u16(a.K), u16(a.V), a.valid_len, a.sel,
+      hipLaunchKernelGGL(kernel, dim3(2 * grid + gate_wgs), dim3(threads), 0, st, u16(a.Q), u16(a.K), u16(a.V), a.valid_len, a.sel,
                          w.g_lt, w.g_st, w.rowI_lt, w.rowI_st, u16(a.dO), w.rowstat, a.gate_w, (const float *)a.o_lt,
-                         (const float *)a.o_st, (uint16_t *)a.dQ, w.offs, w.items, (uint16_t *)a.dK, (uint16_t *)a.dV, p);
+                         (const float *)a.o_st, (uint16_t *)a.dQ, w.offs, w.items, (uint16_t *)a.dK, (uint16_t *)a.dV, w.partial, a.d_gate_w, a.d_gate_b,
+                         w.nchunk, gate_wgs, p);
     };
     if (p.b == 32) {
       if (sub) go(bwd_both_mfma_kernel<32, true, true>, 64);

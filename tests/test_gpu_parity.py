@@ -428,6 +428,15 @@ def test_many_blocks_backward():
     run_case(w, backward=True, gate_scale=0.4)
 
 
+@pytest.mark.parametrize("L", [8 * 488, 8 * 488 + 1])
+def test_inverse_lists_beside_the_gate_pass(L):
+    # the most blocks whose lists are made by workgroups of the gate pass, in its LDS, and one more; three heads: the gate pass'
+    # workgroups start at an id that is no multiple of eight
+    w = with_shape(WORKLOADS["cfg1"], name=f"lists-L{L}", B=1, H=3, L=L, d=64, block=8, topk=5, window=11, len_lo=L - 50, len_hi=L,
+                   seed=78)
+    run_case(w, backward=True, gate_scale=0.4)
+
+
 def test_edge_cases():
     base = with_shape(WORKLOADS["cfg1"], name="edge", B=5, H=2, L=50, seed=301)
     x = make_inputs(base, want_dO=True)
