@@ -56,10 +56,11 @@ struct PosParams {
   float fscale;
 };
 
-// ---- Eq. 8-9: compressed keys, transposed: kcmpT [B*G][d][M] ----
+// ---- Eq. 8-9: compressed keys: [B*G][d][M] for a wavefront per position, whose lanes are blocks, [B*G][M][d] for a lane per
+// position, where a block's channels are one scalar load ----
 template <typename T, int D>
 __global__ __launch_bounds__(256) void cmp_pool_kernel(const T *__restrict__ K, const int *__restrict__ valid_len,
-                                                       float *__restrict__ kcmpT, PosParams p)
+                                                       float *__restrict__ kcmp, bool by_block, PosParams p)
 {
   constexpr int LPT = D / 4;
   const long task = (long)blockIdx.x * (256 / LPT) + threadIdx.x / LPT;
@@ -78,9 +79,9 @@ __global__ __launch_bounds__(256) void cmp_pool_kernel(const T *__restrict__ K, 
     for (int e = 0; e < 4; ++e) a[e] = a[e] + x[e];
   }
   const int cnt = hi - lo;
+  const size_t at = by_block ? (size_t)task * D + c4 : ((size_t)bg * D + c4) * p.M + m;
 #pragma unroll
-  for (int e = 0; e < 4; ++e)
-    kcmpT[((size_t)bg * D + c4 + e) * p.M + m] = cnt > 0 ? __fdiv_rn(a[e], (float)cnt) : 0.0f;
+  for (int e = 0; e < 4; ++e) kcmp[at + (by_block ? e : (size_t)e * p.M)] = cnt > 0 ? __fdiv_rn(a[e], (float)cnt) : 0.0f;
 }
 
 // ---- Eq. 10-13: one wavefront per (row, group, position) ----
@@ -210,11 +211,14 @@ __global__ __launch_bounds__(256) void pos_select_kernel(const T *__restrict__ Q
 // lane: logits, softmax, Eq. 11 and the group sums run as plain sequential loops in exactly the order of the
 // arithmetic recipe above (so the integers are those of the wavefront-per-position kernel), the scores sit in an
 // LDS column per lane (index*64 + lane: no bank conflicts), and the top-k is k-1 passes over the candidates.
-// The compression-block index is the same in every lane of a step, so the compressed keys are broadcast loads.
+// The compression-block index is the same in every lane of a step, so the compressed keys are scalar loads.
+// What bounds it is latency and instruction issue: all loops run to the bound of the wavefront's last position, which is uniform, with
+// the lanes that end earlier masked, so that they unroll and the LDS reads and exponentials of several steps overlap (B=2048, 8 heads
+// over 4, L=200, d=8: 103 us with loops per lane and a key's channels M floats apart, 87 like this).
 constexpr int kLaneMaxBlocks = 64;
 
 template <typename T, int D>
-__global__ __launch_bounds__(64) void pos_select_lane_kernel(const T *__restrict__ Q, const float *__restrict__ kcmpT,
+__global__ __launch_bounds__(64) void pos_select_lane_kernel(const T *__restrict__ Q, const float *__restrict__ kcmp,
                                                              const int *__restrict__ valid_len, int *__restrict__ sel,
                                                              PosParams p)
 {
@@ -225,6 +229,7 @@ __global__ __launch_bounds__(64) void pos_select_lane_kernel(const T *__restrict
   const int t = (blockIdx.x % chunks) * 64 + lane;
   const int r = bg / p.G, g = bg % p.G;
   const int Hg = p.H / p.G;
+  constexpr int kAhead = D >= 32 ? 1 : 32 / D;  // blocks whose channels are requested together: up to 32 scalar registers
   float *es = lane_lds + lane;
   float *sg = lane_lds + (size_t)p.M * 64 + lane;
   const int p0 = p.L - clamp_len(valid_len[r], p.L);
@@ -234,16 +239,17 @@ __global__ __launch_bounds__(64) void pos_select_lane_kernel(const T *__restrict
     for (int e = 0; e < p.k; ++e) out[e] = -1;
     return;
   }
-  int m_hi = -1;
-  if (t - p.l + 1 >= 0) m_hi = min(p.M - 1, (t - p.l + 1) / p.s);
+  // eligible compression blocks, of this position and of the wavefront's last one (which bounds the loops)
+  const int t_end = min(p.L - 1, (int)(blockIdx.x % chunks) * 64 + 63);
+  auto last_block = [&](int at) { return at - p.l + 1 >= 0 ? min(p.M - 1, (at - p.l + 1) / p.s) : -1; };
+  const int m_hi = last_block(t), m_end = last_block(t_end);
   const int need = p0 - p.l + 1;
   const int m_lo = need <= 0 ? 0 : (need + p.s - 1) / p.s;
-  const int n_m = m_hi - m_lo + 1;
+  const int n_m = m_hi - m_lo + 1, n_end = m_end - m_lo + 1;
   const int jt = t / p.lsel, j_first = p0 / p.lsel;
-  const int n_cand = jt - j_first;  // candidates j_first .. jt-1
+  const int n_cand = jt - j_first, cand_end = t_end / p.lsel - j_first;  // candidates j_first .. jt-1
   const int ra = p.lsel / p.s, rc = p.l / p.s;
-  for (int j = 0; j < n_cand; ++j) sg[j * 64] = 0.0f;
-  const float *km = kcmpT + (size_t)bg * D * p.M;
+  const float *km = kcmp + (size_t)bg * p.M * D;
   for (int hh = 0; hh < Hg; ++hh) {
     const T *qrow = Q + (((size_t)r * p.H + (size_t)g * Hg + hh) * p.L + t) * D;
     float q[D];
@@ -254,55 +260,65 @@ __global__ __launch_bounds__(64) void pos_select_lane_kernel(const T *__restrict
 #pragma unroll
       for (int e = 0; e < 4; ++e) q[4 * c4 + e] = x[e];
     }
-    if (n_m > 0) {
-      float mx = -__builtin_huge_valf();
-      for (int m = m_lo; m <= m_hi; ++m) {  // Eq. 10: logits
-        float acc = 0.0f;
+    float mx = -__builtin_huge_valf();
+#pragma unroll kAhead
+    for (int i = 0; i < n_end; ++i) {  // Eq. 10: logits
+      float acc = 0.0f;
 #pragma unroll
-        for (int c = 0; c < D; ++c) acc = __fmaf_rn(q[c], km[(size_t)c * p.M + m], acc);
-        const float x = __fmul_rn(acc, p.fscale);
-        es[(m - m_lo) * 64] = x;
-        mx = fmaxf(mx, x);
-      }
-      float z = 0.0f;  // the normaliser: one sequential sum in ascending block order
-      for (int i = 0; i < n_m; ++i) {
-        const float e = canon_exp(__fsub_rn(es[i * 64], mx));
-        es[i * 64] = e;
-        z = z + e;
-      }
-      for (int i = 0; i < n_m; ++i) es[i * 64] = __fdiv_rn(es[i * 64], z);
+      for (int c = 0; c < D; ++c) acc = __fmaf_rn(q[c], km[(size_t)(m_lo + i) * D + c], acc);
+      const float x = __fmul_rn(acc, p.fscale);
+      es[i * 64] = x;
+      mx = i < n_m ? fmaxf(mx, x) : mx;
     }
-    for (int j = j_first; j < jt; ++j) {  // Eq. 11 in its printed loop order, Eq. 12 over the heads
+    float z = 0.0f;  // the normaliser: one sequential sum in ascending block order (blocks past the last one add +0)
+#pragma unroll 4
+    for (int i = 0; i < n_end; ++i) {
+      const float e = canon_exp(__fsub_rn(es[i * 64], mx));
+      es[i * 64] = e;
+      z = z + (i < n_m ? e : 0.0f);
+    }
+#pragma unroll 4
+    for (int i = 0; i < n_end; ++i) es[i * 64] = __fdiv_rn(es[i * 64], z);
+#pragma unroll 2
+    for (int jj = 0; jj < cand_end; ++jj) {  // Eq. 11 in its printed loop order, Eq. 12 over the heads
       float acc = 0.0f;
       for (int a = 0; a < ra; ++a)
         for (int c = 0; c < rc; ++c) {
-          const int idx = ra * j - a - c;
-          if (idx >= m_lo && idx <= m_hi) acc = acc + es[(idx - m_lo) * 64];
+          const int idx = ra * (j_first + jj) - a - c;
+          if (idx >= m_lo && idx <= m_end) {
+            const float e = es[(idx - m_lo) * 64];
+            acc = idx <= m_hi ? acc + e : acc;
+          }
         }
-      sg[(j - j_first) * 64] = sg[(j - j_first) * 64] + acc;
+      sg[jj * 64] = (hh == 0 ? 0.0f : sg[jj * 64]) + acc;
     }
   }
   // Eq. 13: the own block and the best min(k-1, n_cand) earlier ones by (score descending, index ascending)
   const int take = min(p.k - 1, n_cand);
+  unsigned *img = reinterpret_cast<unsigned *>(sg);
+#pragma unroll 4
+  for (int j = 0; j < cand_end; ++j) img[j * 64] = score_image(sg[j * 64]);
   unsigned long long chosen = 0ull;
-  for (int pass = 0; pass < take; ++pass) {
+  for (int pass = 0; pass < min(p.k - 1, cand_end); ++pass) {
     int best = -1;
     unsigned best_img = 0u;
-    for (int j = 0; j < n_cand; ++j) {
-      if ((chosen >> j) & 1ull) continue;
-      const unsigned img = score_image(sg[j * 64]);
-      if (best < 0 || img > best_img) {  // strictly greater: equal scores keep the lower index
+#pragma unroll 4
+    for (int j = 0; j < cand_end; ++j) {
+      const unsigned x = img[j * 64];
+      const bool open = (j < n_cand) & (((chosen >> j) & 1ull) == 0ull);
+      if (open & ((best < 0) | (x > best_img))) {  // strictly greater: equal scores keep the lower index
         best = j;
-        best_img = img;
+        best_img = x;
       }
     }
-    chosen |= 1ull << best;
+    if (pass < take) chosen |= 1ull << best;
   }
-  int base = 0;
-  for (int j = 0; j < n_cand; ++j)
-    if ((chosen >> j) & 1ull) out[base++] = j_first + j;
-  out[base++] = jt;
-  for (; base < p.k; ++base) out[base] = -1;
+  for (int e = 0; e < take; ++e) {
+    out[e] = j_first + __builtin_ctzll(chosen);
+    chosen &= chosen - 1;
+  }
+  out[take] = jt;
+  for (int e = take + 1; e < p.k; ++e) out[e] = -1;
 }
 
 int fill_pos_params(const blossom_params *p, int G, int l, int s, float score_scale, PosParams *pp)
@@ -329,13 +345,14 @@ template <typename T, int D>
 void launch_pos(const PosParams &pp, const void *Q, const void *K, const int *valid_len, int *sel, float *kcmpT,
                 hipStream_t st)
 {
+  const bool by_lane = pp.M <= kLaneMaxBlocks && pp.NBs <= kLaneMaxBlocks;  // short sequences: a lane per position
   if (pp.M > 0) {
     const long tasks = (long)pp.B * pp.G * pp.M;
     const int per_wg = 256 / (D / 4);
     BLOSSOM_LAUNCH((cmp_pool_kernel<T, D>), dim3((unsigned)((tasks + per_wg - 1) / per_wg)), dim3(256), 0, st,
-                   (const T *)K, valid_len, kcmpT, pp);
+                   (const T *)K, valid_len, kcmpT, by_lane, pp);
   }
-  if (pp.M <= kLaneMaxBlocks && pp.NBs <= kLaneMaxBlocks) {  // short sequences: a lane per position
+  if (by_lane) {
     const unsigned chunks = (unsigned)((pp.L + 63) / 64);
     const size_t lds_lane = 64 * (size_t)(pp.M + pp.NBs) * sizeof(float);
     hipLaunchKernelGGL((pos_select_lane_kernel<T, D>), dim3((unsigned)(pp.B * pp.G) * chunks), dim3(64), lds_lane, st,
