@@ -443,8 +443,8 @@ __global__ __launch_bounds__(64 * kInvWaves) void inverse_list_kernel(const int 
 // Every tensor is read exactly once, so memory is the bound, but a row costs five sums over its channels and
 // some sixty instructions that its lanes share: as few lanes as give whole cache lines take a row (4 channels
 // each, for d = 64 twice 4: 8 lanes), the sums are DPP adds inside a row of 16 lanes instead of LDS permutes, and the
-// next rows are requested before the current ones are worked on.  B=128 H=4 L=1024 d=64, lengths U[100,1024]: 77 -> 71 us;
-// B=16 H=8 L=8192: 183 -> 173 us (5.7 TB/s).
+// next rows are requested before the current ones are worked on.  B=128 H=4 L=1024 d=64, lengths U[100,1024]: 77 -> 71 us, 59 with the
+// heads to the XCDs in turn; B=16 H=8 L=8192: 183 -> 175 us (5.7 TB/s).
 // The gate-weight partials accumulate in registers and meet in LDS in a fixed order.
 // =============================================================================================
 // The first `lists` workgroups make the inverse selection lists instead: a chain of latencies (8 us at B=128 H=4 L=1024, 26 at B=16

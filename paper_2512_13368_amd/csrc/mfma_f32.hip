@@ -4,8 +4,8 @@
 // or 128 over 2 to 8 heads, selection block 16, histories of 200 items, up to 2000 in the efficiency study);
 // the 64 x 64 bf16 tiles of the other matrix-core kernels would be mostly padding there.
 //
-// Positions are cut into 16-row tiles of v_mfma_f32_16x16x4_f32 (true fp32 products accumulated in fp32)
-// (bf16 storage from d = 16 on: on the bf16 matrix instructions with the same accuracy, see THE MATRIX OPERANDS)
+// Positions are cut into 16-row tiles of v_mfma_f32_16x16x4_f32 (true fp32 products accumulated in fp32; d = 8: contractions over
+// rows as 4x4 blocks; bf16 storage from d = 16 on: the bf16 matrix instructions with the same accuracy; see THE MATRIX OPERANDS)
 // whatever the block size; a selection block of 8 is half a tile and the selection is tested per element.
 // A wavefront takes one query tile (forward, dQ) or one key tile (dK/dV) at a time.  Heads that fit a workgroup's LDS
 // (small_lds_limit; fp32: L up to 256 at d = 32, 272 at d = 16, 688 at d = 8, less in the backward) are staged
@@ -30,8 +30,8 @@
 // EXPONENTIALS WITHOUT A RUNNING MAXIMUM.  A walk takes exp2 of the logits themselves, one exponential for both
 // branches, and keeps the largest |logit| it met (of masked keys too): up to 60 (log2 units) nothing overflows or loses
 // accuracy in fp32.  Beyond that (or if an output left fp32's range) the walk is repeated with the two row maxima,
-// found by a walk of their own, as references.  With every tile beyond it the forward takes 46 us instead of 23 at B=256
-// H=2 L=200 d=32, 595 instead of 332 at B=2048 H=8 L=200 d=16, 245 instead of 87 at B=32 H=8 L=2000 d=8.
+// found by a walk of their own, as references.  With every tile beyond it the forward takes 46 us instead of 22 at B=256
+// H=2 L=200 d=32, 560 instead of 292 at B=2048 H=8 L=200 d=16, 192 instead of 56 at B=32 H=8 L=2000 d=8.
 //
 // VALUES THAT ARE NOT FINITE.  A walk multiplies whole tiles, so a masked element adds zero times whatever the tile holds: a NaN
 // or an infinity, in a row of the padding too, would reach every row of its tile.  Such a result is not finite itself,
