@@ -22,6 +22,9 @@ pytestmark = pytest.mark.gpu
     (2, 2, 1025, 8, 8, 4, "fp32", 0, False),      # 129
     (70, 4, 4100, 64, 64, 8, "bf16", 0, False),   # pooling apart, sixteen rows per workgroup, ragged last block
     (4, 2, 2040, 64, 32, 8, "bf16", 0, True),     # the last block alone
+    (50, 4, 1037, 16, 16, 4, "bf16", 2, False),   # few picks, two candidates per lane, the own block among them
+    (3, 2, 2040, 64, 32, 3, "bf16", 0, True),     # few picks for the last block alone
+    (3, 2, 1000, 8, 8, 1, "fp32", 0, False),      # nothing to pick beside the own block
 ])
 def test_selection_at_the_limits_of_its_kernels(rows, H, L, d, b, k, dtype, stis, last):
     rng = np.random.default_rng(L + k)
