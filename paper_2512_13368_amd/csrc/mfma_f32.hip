@@ -58,7 +58,7 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr float kLog2eF = 1.4426950408889634f;
-constexpr float kLn2F = 0.6931471805599453f;
+constexpr float kLn2F = 0.6931471805599453f, kLn2Low = (float)(0.6931471805599453 - (double)kLn2F);  // ln 2 in two parts
 constexpr float kNegInfF = -__builtin_huge_valf();
 constexpr float kHugeF = 1.0e30f;
 constexpr int kTile = 16;
@@ -784,6 +784,11 @@ struct Walk {
 // mask and the exponential are, and spread_g hands the four results to all groups, which add them into their accumulators'
 // channels (`own`).  About 12 vector instructions a distance; as tiles of the walk the distances took half of its steps at L=2000
 // (a training step at B=32 H=8 L=2000 d=8 356 us, 302 like this; B=2048 H=8 L=200 d=16 1050 and 996).
+// They come after the walk, whose registers they may then use (ahead of it d = 32 spilled, and short calls waited for them), and whose
+// sums are not rounded at the size these large terms give them (dQ at d = 16 against 64 bits 1.028 of the error of tiles, 1.014
+// so; the rest is the rounding of products formed on the vector ALUs, and the lse makes up for it, see the forward).
+// The backward at d = 8 takes them first: its sums are a lane group's own parts, and the walk runs 2 % faster (L=1657: 69.0 and
+// 70.3 us).
 // f(d): tiles X + d, X + 2d, X + 4d, X + 8d (some may lie outside lo .. hi: d times the lane group's power tells).
 template <typename F>
 __device__ __forceinline__ void diagonals(const KParams &p, int X, int lo, int hi, F &&f)
@@ -792,6 +797,8 @@ __device__ __forceinline__ void diagonals(const KParams &p, int X, int lo, int h
   for (int d = d0; d <= X - lo; d <<= 4) f(-d);
   for (int d = d0; d <= hi - X; d <<= 4) f(d);
 }
+template <int D>
+constexpr bool kFarFirst = Geo<D>::kQuads;
 // d = 32: the phases of a batch of distances are kept apart: their registers would spill
 template <int D>
 __device__ __forceinline__ void phase_end()
@@ -1045,47 +1052,6 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
       if ((PERPOS || BK < kTile) && !dense) s_lt &= ls.sees(q, key0);
       v_lt = s_lt ? ok : 0u;
     };
-    if (p.sblk == 1 && !dense) {
-      float qd[CPL];
-      Ops::floats(qf, qd);
-      float qw[CPL * 4];
-      if constexpr (D == 8) whole_row(qd, qw);
-      diagonals(p, I, T0, J_hi, [&](int d) __attribute__((always_inline)) {
-        if constexpr (D == 8) {
-          const int t = min(max(I + d * (1 << g), T0), NT - 1), key = iq + kTile * d * (1 << g);
-          float kr[D], vr[D];
-          Kr.whole(t, kr);
-          Vr.whole(t, vr);
-          const float x = dot_n(qw, kr, 0.0f);
-          const bool ok = active & (key >= p0) & (key < p.last_lo);
-          s_max = fmaxf(s_max, ok ? fabsf(x) : 0.0f);
-          const float ex = ok ? __builtin_amdgcn_exp2f(kc * x) : 0.0f;
-          l_st += ex;
-          add_row(a_st, ex, vr);
-          return;
-        } else {
-        float s[4], e[4], vo[4][NMB][4];
-#pragma unroll
-        for (int n = 0; n < 4; ++n) {
-          float kr[CPL];
-          Kr.row(min(max(I + d * (1 << n), T0), NT - 1), kr);
-          s[n] = dot_n(qd, kr, 0.0f);
-        }
-        phase_end<D>();
-#pragma unroll
-        for (int n = 0; n < 4; ++n) Vr.own(min(max(I + d * (1 << n), T0), NT - 1), vo[n]);
-        const float x = gather_g(s);
-        const int key = iq + kTile * d * (1 << g);
-        const bool ok = active & (key >= p0) & (key < p.last_lo);
-        s_max = fmaxf(s_max, ok ? fabsf(x) : 0.0f);
-        const float ex = ok ? __builtin_amdgcn_exp2f(kc * x) : 0.0f;
-        l_st += ex;
-        spread_g(ex, e);
-#pragma unroll
-        for (int n = 0; n < 4; ++n) add_own(a_st, e[n], vo[n]);
-        }
-      });
-    }
     // one tile: the next one's keys are requested as soon as this one's are in the matrix cores, its values at the end
     auto body = [&](auto kind, auto unit, Word &mask) __attribute__((always_inline)) {
       constexpr int KIND = decltype(kind)::value;
@@ -1155,6 +1121,47 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     };
     if (p.sblk <= 1) walk(std::true_type{});
     else walk(std::false_type{});
+    if (p.sblk == 1 && !dense) {
+      float qd[CPL];
+      Ops::floats(qf, qd);
+      float qw[CPL * 4];
+      if constexpr (D == 8) whole_row(qd, qw);
+      diagonals(p, I, T0, J_hi, [&](int d) __attribute__((always_inline)) {
+        if constexpr (D == 8) {
+          const int t = min(max(I + d * (1 << g), T0), NT - 1), key = iq + kTile * d * (1 << g);
+          float kr[D], vr[D];
+          Kr.whole(t, kr);
+          Vr.whole(t, vr);
+          const float x = dot_n(qw, kr, 0.0f);
+          const bool ok = active & (key >= p0) & (key < p.last_lo);
+          s_max = fmaxf(s_max, ok ? fabsf(x) : 0.0f);
+          const float ex = ok ? __builtin_amdgcn_exp2f(kc * x) : 0.0f;
+          l_st += ex;
+          add_row(a_st, ex, vr);
+          return;
+        } else {
+        float s[4], e[4], vo[4][NMB][4];
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+          float kr[CPL];
+          Kr.row(min(max(I + d * (1 << n), T0), NT - 1), kr);
+          s[n] = dot_n(qd, kr, 0.0f);
+        }
+        phase_end<D>();
+#pragma unroll
+        for (int n = 0; n < 4; ++n) Vr.own(min(max(I + d * (1 << n), T0), NT - 1), vo[n]);
+        const float x = gather_g(s);
+        const int key = iq + kTile * d * (1 << g);
+        const bool ok = active & (key >= p0) & (key < p.last_lo);
+        s_max = fmaxf(s_max, ok ? fabsf(x) : 0.0f);
+        const float ex = ok ? __builtin_amdgcn_exp2f(kc * x) : 0.0f;
+        l_st += ex;
+        spread_g(ex, e);
+#pragma unroll
+        for (int n = 0; n < 4; ++n) add_own(a_st, e[n], vo[n]);
+        }
+      });
+    }
     if (__builtin_expect(!__all(s_max * kc <= kSmallLogit && abs_sum(a_lt) + abs_sum(a_st) < 1.0e37f), 0)) {
       // large logits, or values near the end of fp32's range or beyond: the row maxima of both branches, then the walk
       // against them
@@ -1208,9 +1215,9 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
           a_st[mb][r] = active ? a_st[mb][r] : 0.0f;
         }
     }
-    // closes a branch: normalised output (zero for rows that take no part), returns the lse
+    // closes a branch: normalised output, returns the row's sum (both zero for rows that take no part)
     f32x4 o_lt[NMB], o_st[NMB];
-    auto finish = [&](const f32x4 (&part)[NACC], f32x4 (&acc)[NMB], float l, float m) -> float {
+    auto finish = [&](const f32x4 (&part)[NACC], f32x4 (&acc)[NMB], float l) -> float {
       total<D>(part, acc);
       const float lt = sum_g(l);
       const bool ok = active && !(lt <= 0.0f);  // (a NaN stays one)
@@ -1219,18 +1226,25 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
       for (int mb = 0; mb < NMB; ++mb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[mb][r] *= inv;
-      return ok ? (m + __builtin_amdgcn_logf(lt)) * kLn2F : 0.0f;
+      return ok ? lt : 0.0f;
+    };
+    // log sum exp from a row's sum.  The hardware's logarithm is off by an ulp of its own size, some 5, and every probability of the
+    // backward would carry that: what it misses is l * 2^-log - 1 (errors against 64 bits 0.6 of those without, of dQ, dK and dV 0.9;
+    // 0.05 us of a call of 6).
+    auto lse = [&](float l, float m) -> float {
+      const float log = __builtin_amdgcn_logf(l), missed = fmaf(l, __builtin_amdgcn_exp2f(-log), -1.0f);
+      return l == 0.0f ? 0.0f : fmaf(m + log, kLn2F, fmaf(m + log, kLn2Low, missed));
     };
     const int el = fresh_lane(), eg = el >> 4, ei = I * kTile + (el & 15);
     const bool in_range = ei < p.L && ei >= row_lo;
     const size_t lrow = (size_t)bh * p.L + ei, rowoff = lrow * D;
-    const float lse_lt = finish(a_lt, o_lt, l_lt, ref_lt);
+    const float sum_lt = finish(a_lt, o_lt, l_lt);
     if (dense) {
       if (in_range) store_row4<T, D>(O + rowoff, o_lt, eg);
-      if (in_range && eg == 0 && lse_lt_out) lse_lt_out[lrow] = lse_lt;
+      if (in_range && eg == 0 && lse_lt_out) lse_lt_out[lrow] = lse(sum_lt, ref_lt);
       continue;
     }
-    const float lse_st = finish(a_st, o_st, l_st, ref_st);
+    const float sum_st = finish(a_st, o_st, l_st);
 
     // ---- gate and blend (Eq. 18-19) ----
     const float *wl = gate_w + (size_t)h * 2 * D;
@@ -1256,8 +1270,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
         for (int r = 0; r < 4; ++r) o[mb][r] = alpha * o_lt[mb][r] + (1.0f - alpha) * o_st[mb][r];
       store_row4<T, D>(O + rowoff, o, eg);
       if (eg == 0) {
-        if (lse_lt_out) lse_lt_out[lrow] = lse_lt;
-        if (lse_st_out) lse_st_out[lrow] = lse_st;
+        if (lse_lt_out) lse_lt_out[lrow] = lse(sum_lt, ref_lt);
+        if (lse_st_out) lse_st_out[lrow] = lse(sum_st, ref_st);
       }
     }
   }
@@ -1496,7 +1510,7 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
     }
   };
   if constexpr (!CAREFUL) {
-    if (p.sblk == 1) {
+    auto far_keys = [&]() __attribute__((always_inline)) {
       float qd[CPL];
       Ops::floats(qf, qd);
       float qw[CPL * 4], ow[CPL * 4];
@@ -1538,9 +1552,11 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
         for (int n = 0; n < 4; ++n) add_own(dq_part, x[n], ko[n]);
         }
       });
-    }
+    };
+    if (kFarFirst<D> && p.sblk == 1) far_keys();
     if (p.sblk <= 1) walk(std::true_type{});
     else walk(std::false_type{});
+    if (!kFarFirst<D> && p.sblk == 1) far_keys();
   } else {
     for (int w = T0 >> 6; w <= J_hi >> 6; ++w) {
       word(w);
@@ -1768,71 +1784,75 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
         }
       }
     };
-    if constexpr (!CAREFUL)
-      if (p.sblk == 1) {
-        float kd[CPL], vd[CPL];
-        Ops::floats(kf, kd);
-        Ops::floats(vf, vd);
-        float kw[CPL * 4], vw[CPL * 4];
-        if constexpr (D == 8) {
-          whole_row(kd, kw);
-          whole_row(vd, vw);
-        }
-        diagonals(p, J, I_lo, NT - 1, [&](int d) __attribute__((always_inline)) {
-          // this lane group's distance
-          const int i = j + kTile * d * (1 << g), tg = min(max(J + d * (1 << g), I_lo), NT - 1);
-          auto constant = [&](int k) { return src.row_constant(hl, tg, k); };
-          const bool ok = (i >= p0) & (i < p.L) & !last_k;
-          if constexpr (D == 8) {
-            float qr[D], gr[D];
-            Qr.whole(tg, qr);
-            Gr.whole(tg, gr);
-            const float e = __builtin_amdgcn_exp2f(arg(dot_n(kw, qr, 0.0f), constant(5)));
-            const float pr = ok ? e : 0.0f, zd = constant(1), as = 1.0f - constant(0);
-            t_st = fmaf(zd, pr, t_st);
-            add_row(dv_part, as * pr, gr);
-            add_row(dk_part, pr * fmaf(as, dot_n(vw, gr, 0.0f), fmaf(zd, wv_st, -constant(3))), qr);
-          } else {
-          float s[4], x[4], qo[4][NMB][4], go[4][NMB][4];
-#pragma unroll
-          for (int n = 0; n < 4; ++n) {
-            float qr[CPL], gr[CPL];
-            const int t = min(max(J + d * (1 << n), I_lo), NT - 1);
-            Qr.row(t, qr);
-            Gr.row(t, gr);
-            s[n] = dot_n(kd, qr, 0.0f);
-            x[n] = dot_n(vd, gr, 0.0f);
-            if constexpr (D == 16) {
-              own_of_row(qr, qo[n]);
-              own_of_row(gr, go[n]);
-            }
-          }
-          phase_end<D>();
-          if constexpr (D != 16) {
-#pragma unroll
-            for (int n = 0; n < 4; ++n) {
-              const int t = min(max(J + d * (1 << n), I_lo), NT - 1);
-              Qr.own(t, qo[n]);
-              Gr.own(t, go[n]);
-            }
-          }
-          const float e = __builtin_amdgcn_exp2f(arg(gather_g(s), constant(5))), gd = gather_g(x);
-          const float pr = ok ? e : 0.0f;
-          const float zd = constant(1), as = 1.0f - constant(0);
-          t_st = fmaf(zd, pr, t_st);
-          spread_g(as * pr, s);
-          spread_g(pr * fmaf(as, gd, fmaf(zd, wv_st, -constant(3))), x);
-#pragma unroll
-          for (int n = 0; n < 4; ++n) {
-            add_own(dv_part, s[n], go[n]);
-            add_own(dk_part, x[n], qo[n]);
-          }
-          }
-        });
+    auto far_queries = [&]() __attribute__((always_inline)) {
+      float kd[CPL], vd[CPL];
+      Ops::floats(kf, kd);
+      Ops::floats(vf, vd);
+      float kw[CPL * 4], vw[CPL * 4];
+      if constexpr (D == 8) {
+        whole_row(kd, kw);
+        whole_row(vd, vw);
       }
-    if constexpr (CAREFUL) walk_carefully();
-    else if (p.sblk <= 1) walk(std::true_type{});
-    else walk(std::false_type{});
+      diagonals(p, J, I_lo, NT - 1, [&](int d) __attribute__((always_inline)) {
+        // this lane group's distance
+        const int i = j + kTile * d * (1 << g), tg = min(max(J + d * (1 << g), I_lo), NT - 1);
+        auto constant = [&](int k) { return src.row_constant(hl, tg, k); };
+        const bool ok = (i >= p0) & (i < p.L) & !last_k;
+        if constexpr (D == 8) {
+          float qr[D], gr[D];
+          Qr.whole(tg, qr);
+          Gr.whole(tg, gr);
+          const float e = __builtin_amdgcn_exp2f(arg(dot_n(kw, qr, 0.0f), constant(5)));
+          const float pr = ok ? e : 0.0f, zd = constant(1), as = 1.0f - constant(0);
+          t_st = fmaf(zd, pr, t_st);
+          add_row(dv_part, as * pr, gr);
+          add_row(dk_part, pr * fmaf(as, dot_n(vw, gr, 0.0f), fmaf(zd, wv_st, -constant(3))), qr);
+        } else {
+        float s[4], x[4], qo[4][NMB][4], go[4][NMB][4];
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+          float qr[CPL], gr[CPL];
+          const int t = min(max(J + d * (1 << n), I_lo), NT - 1);
+          Qr.row(t, qr);
+          Gr.row(t, gr);
+          s[n] = dot_n(kd, qr, 0.0f);
+          x[n] = dot_n(vd, gr, 0.0f);
+          if constexpr (D == 16) {
+            own_of_row(qr, qo[n]);
+            own_of_row(gr, go[n]);
+          }
+        }
+        phase_end<D>();
+        if constexpr (D != 16) {
+#pragma unroll
+          for (int n = 0; n < 4; ++n) {
+            const int t = min(max(J + d * (1 << n), I_lo), NT - 1);
+            Qr.own(t, qo[n]);
+            Gr.own(t, go[n]);
+          }
+        }
+        const float e = __builtin_amdgcn_exp2f(arg(gather_g(s), constant(5))), gd = gather_g(x);
+        const float pr = ok ? e : 0.0f;
+        const float zd = constant(1), as = 1.0f - constant(0);
+        t_st = fmaf(zd, pr, t_st);
+        spread_g(as * pr, s);
+        spread_g(pr * fmaf(as, gd, fmaf(zd, wv_st, -constant(3))), x);
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+          add_own(dv_part, s[n], go[n]);
+          add_own(dk_part, x[n], qo[n]);
+        }
+        }
+      });
+    };
+    if constexpr (CAREFUL) {
+      walk_carefully();
+    } else {
+      if (kFarFirst<D> && p.sblk == 1) far_queries();
+      if (p.sblk <= 1) walk(std::true_type{});
+      else walk(std::false_type{});
+      if (!kFarFirst<D> && p.sblk == 1) far_queries();
+    }
     // the gate part of dV: sum_i dz_i P_ij times the gate row of the branch
     if constexpr (Geo<D>::kQuads) {  // (a lane's part of the sums, like the accumulators)
 #pragma unroll

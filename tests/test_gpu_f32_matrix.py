@@ -224,3 +224,29 @@ def test_bf16_rows_as_they_are_stored(d, b, B_, H, L, sblk, bidir):
     take = lambda t: host(t).reshape(B_ * H, *t.shape[2:])[bh]
     for name in ("o_lt", "o_st", "lse_lt", "lse_st"):
         assert_close(take(getattr(f, name)), getattr(fr, name), TOL["fp32"], name)
+
+
+@pytest.mark.parametrize("d,L,limit", [
+    (8, 200, 2.42e-7),
+    (16, 200, 2.55e-7),
+    (16, 450, 2.76e-7),   # streamed
+    (32, 200, 2.67e-7),
+])
+def test_errors_against_64_bits(d, L, limit):
+    # fp32 under mask block 1, where single keys at powers of two are taken on the vector ALUs: dQ errs no more than where the matrix
+    # cores formed every product (`limit`: measured so, on these inputs), and the lse little more than a result of about 5 does by
+    # being rounded (2^-21 / sqrt(12) of it: 3e-8; the row's sum and its logarithm are to add no more than half as much)
+    w = with_shape(WORKLOADS["cfg2"], name=f"exact-d{d}-L{L}", B=12, H=4, L=L, d=d, block=16, topk=4, window=8, len_lo=L // 10, len_hi=L,
+                   stis_block=1, seed=3100 + d + L)
+    x = make_inputs(w, want_dO=True)
+    dv, p = Dev(x), params(w, save_for_bwd=1)
+    sel = B.select_blocks(p, dv.Q, dv.K, dv.vl)
+    f = B.attn_fwd(p, dv.Q, dv.K, dv.V, dv.vl, sel, dv.gw, dv.gb)
+    g = B.attn_bwd(p, dv.Q, dv.K, dv.V, dv.vl, sel, dv.gw, dv.gb, f, dv.dO)
+    torch.cuda.synchronize()
+    args = (x.Q, x.K, x.V, x.valid_len, sel.cpu().numpy(), x.gate_w, x.gate_b)
+    fr = oracle.attn_fwd(*args, 16, 4, 8, stis_block=1)
+    dQ = oracle.attn_bwd(*args, x.dO, 16, 4, 8, stis_block=1).dQ
+    err = lambda got, ref: float(np.linalg.norm(host(got).reshape(ref.shape) - ref) / np.linalg.norm(ref))
+    assert err(f.lse_lt, fr.lse_lt) < 4.5e-8 and err(f.lse_st, fr.lse_st) < 4.5e-8
+    assert err(g.dQ, dQ) < limit
