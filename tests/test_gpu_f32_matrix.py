@@ -250,3 +250,23 @@ def test_errors_against_64_bits(d, L, limit):
     err = lambda got, ref: float(np.linalg.norm(host(got).reshape(ref.shape) - ref) / np.linalg.norm(ref))
     assert err(f.lse_lt, fr.lse_lt) < 4.5e-8 and err(f.lse_st, fr.lse_st) < 4.5e-8
     assert err(g.dQ, dQ) < limit
+
+
+@pytest.mark.parametrize("d,L,sblk", [(32, 400, 0), (16, 400, 1), (8, 395, 0), (8, 1600, 4)])
+def test_serving_mode_at_block_8(d, L, sblk):
+    # two query blocks to a tile, most of their selected tiles beyond the window: a row of the last block has the same bits whether the
+    # block beside it selected anything or not, and the full forward agrees with the oracle
+    w = with_shape(WORKLOADS["cfg1"], name=f"serve8-d{d}-L{L}", B=6, H=3, L=L, d=d, block=8, topk=5, window=9, len_lo=40, len_hi=L,
+                   stis_block=sblk, seed=3300 + d + L)
+    x = make_inputs(w)
+    dv = Dev(x)
+    sel = B.select_blocks(params(w), dv.Q, dv.K, dv.vl)
+    full = B.attn_fwd(params(w), dv.Q, dv.K, dv.V, dv.vl, sel, dv.gw, dv.gb).O
+    last = torch.full_like(sel, -7)
+    last[:, :, -1] = sel[:, :, -1]
+    O = B.attn_fwd(params(w, last_block_only=1), dv.Q, dv.K, dv.V, dv.vl, last, dv.gw, dv.gb, out=B.FwdOut(torch.zeros_like(full))).O
+    torch.cuda.synchronize()
+    lo = (w.NB - 1) * 8
+    assert torch.equal(O[:, :, lo:], full[:, :, lo:])
+    fr = oracle.attn_fwd(x.Q, x.K, x.V, x.valid_len, sel.cpu().numpy(), x.gate_w, x.gate_b, 8, 5, 9, stis_block=sblk)
+    assert_close(host(full).reshape(fr.O.shape), fr.O, TOL["fp32"], "O")
