@@ -948,7 +948,12 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
   extern __shared__ __attribute__((aligned(16))) float small_lds[];  // RES: K and V rows; then the wavefronts' selection words
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = blockDim.x >> 6;
-  const unsigned vid = mfma::xcd_spread(blockIdx.x, gridDim.x / parts, parts);
+  // (one workgroup to a head: the map is the identity, at the price of three divisions, some 75 dependent scalar instructions before
+  // the first load: selection + forward at B=40 H=8 L=170 d=16 b=8 17.9 us with it, 17.6 without.  With rows of 128 bytes, d = 32 in
+  // fp32, it is the other way round: L=87 b=16 15.7 and 16.0.)
+  constexpr bool direct = RES && D * sizeof(T) < 128;
+  const unsigned vid = direct ? blockIdx.x : mfma::xcd_spread(blockIdx.x, gridDim.x / parts, parts);
+  if constexpr (direct) parts = 1;
   const int heads = RES ? hpg : 1;  // query heads of this workgroup
   const int bh0 = (int)(vid / parts) * heads, part = (int)(vid % parts);
   const int b = bh0 / p.H;
