@@ -418,13 +418,15 @@ __device__ __forceinline__ bool st_sees(const KParams &p, int i, int j, int kid_
 // visibility is a function of the distance alone, own - element = 16*dt + c - r with dt tiles between the two and c = q - 4g: the
 // bits of the tiles next to the row's own (dt of 0, 1 and -1) are cut out of one table over distances, once per wavefront.
 // Powers of two from first_diagonal on are left to `diagonals`.  A general tile of the forward takes 35 vector instructions for its
-// masks and sums, 69 with a test per element.
+// masks and sums, 69 with a test per element.  (Larger mask blocks are tested element by element, and no table is made: selection +
+// forward at B=40 H=8 L=87 d=16 bf16 with mask block 16, in both directions, 16.6 us with it, 16.3 without.)
 struct LaneMasks {
   int c;
   unsigned near;  // bits 0-3, 4-7, 8-11: dt = 0, 1, -1 (the window and the powers of two of Eq. 15)
   __device__ __forceinline__ static LaneMasks make(const KParams &p, int q, int g)
   {
-    LaneMasks m;
+    LaneMasks m{};
+    if (p.sblk > 1) return m;
     m.c = q - 4 * g;
     unsigned long long table = p.w >= 32 ? ~0ull : ((1ull << (2 * p.w - 1)) - 1) << (33 - p.w);  // bit 32 + distance
     if (p.sblk == 1) table |= 0x0001011600000000ull | 0x00000000D1010000ull;  // 1, 2, 4, 8, 16 on either side
