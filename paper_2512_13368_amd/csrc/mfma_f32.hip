@@ -2185,7 +2185,9 @@ struct SmallPlan {
 // LDS up to which a workgroup holds whole heads: two of them per CU at d = 32, three below, whose lighter walks want the wavefronts
 // (a training step, us, by limit 76 / 50 / 40 KB: B=300 H=8 d=16 L=300 296 / 280 / 277, L=450 446 / 422 / 421, d=8 L=450 289 / 288 / 297,
 // L=600 455 / 414 / 416; B=32 d=8 L=1000 110 / 98 / -; B=1024 H=2 d=32 L=200 339 / 410 / 411)
-size_t small_lds_limit(const KParams &p) { return p.d == 32 ? 76 * 1024 : 44 * 1024; }
+constexpr int kCUs = 256;
+constexpr size_t kTwoPerCU = 76 * 1024;
+size_t small_lds_limit(const KParams &p) { return p.d == 32 ? kTwoPerCU : 44 * 1024; }
 // Few heads: eight wavefronts each, a head's latency counts.  Many: four, whose shares are longer and better balanced (always a
 // multiple of the four SIMDs: with five or six wavefronts the backward took 1.4 times as long).
 bool many_heads(int units) { return units >= 2048; }
@@ -2194,8 +2196,8 @@ SmallPlan stream_plan(const KParams &p, int units, size_t words_per_wave)
 {
   const int NT = (p.L + kTile - 1) / kTile;
   SmallPlan s{false, false, 4, 1, 4 * words_per_wave * sizeof(float)};
-  // enough workgroups for about two rounds of the chip's wavefronts (256 CUs x 20), at most one tile per wavefront
-  const int want = (2 * 256 * 20 + units * s.waves - 1) / (units * s.waves);
+  // enough workgroups for about two rounds of the chip's wavefronts (20 per CU), at most one tile per wavefront
+  const int want = (2 * kCUs * 20 + units * s.waves - 1) / (units * s.waves);
   s.parts = std::max(1, std::min((NT + s.waves - 1) / s.waves, want));
   return s;
 }
@@ -2215,11 +2217,22 @@ SmallPlan fwd_plan(const KParams &p, int dtype, bool perpos, int hpg)
 SmallPlan bwd_plan(const KParams &p, int dtype, bool perpos, int hpg)
 {
   const int units = p.B * p.H / hpg;
-  // with many heads four small workgroups per CU beat two that hold everything (B=2048 H=8 L=200 d=16: 672 against 917 us)
+  // with many heads four small workgroups per CU beat two that hold everything (B=2048 H=8 L=200 d=16: 672 against 917 us); with so
+  // few that no CU has more than two to hold, everything fits beside a second one (gradients at B=82 H=4 L=174 d=16: 50.8 us with
+  // everything in LDS, 52.3 with Q and dO read again; B=40 H=8 L=170 d=16, a whole step 47.5 and 48.4)
+  auto bytes = [&](const SmallPlan &s) {
+    return (size_t)ResLayout(p, lds_row(p, dtype), perpos, hpg, s.overlay, s.waves).total * sizeof(float);
+  };
   for (int overlay = many_heads(units) ? 1 : 0; overlay < 2; ++overlay) {
     SmallPlan s{true, overlay != 0, res_waves(units), 1, 0};
-    s.lds = (size_t)ResLayout(p, lds_row(p, dtype), perpos, hpg, overlay, s.waves).total * sizeof(float);
-    if (s.lds <= small_lds_limit(p)) return s;
+    s.lds = bytes(s);
+    if (s.lds > small_lds_limit(p)) continue;
+    const SmallPlan all{true, false, s.waves, 1, 0};
+    if (s.overlay && units <= 2 * kCUs && bytes(all) <= kTwoPerCU) {
+      s = all;
+      s.lds = bytes(all);
+    }
+    return s;
   }
   return stream_plan(p, p.B * p.H, lt_words(p, perpos));
 }

@@ -199,7 +199,7 @@ def test_window_against_powers_of_two(d, window, L, sblk, bidir):
 
 
 @pytest.mark.parametrize("d,b,B_,H,L,sblk,bidir", [
-    (32, 16, 2, 2, 416, 0, False),    # the longest bf16 heads at d = 32 whose forward and backward hold everything in LDS, and past it
+    (32, 16, 2, 2, 416, 0, False),    # the longest bf16 heads at d = 32 whose backward is in LDS
     (32, 16, 2, 2, 500, 16, True),    # streamed
     (16, 8, 2, 2, 830, 1, False),
     (16, 16, 2, 2, 1100, 0, False),
@@ -270,3 +270,28 @@ def test_serving_mode_at_block_8(d, L, sblk):
     assert torch.equal(O[:, :, lo:], full[:, :, lo:])
     fr = oracle.attn_fwd(x.Q, x.K, x.V, x.valid_len, sel.cpu().numpy(), x.gate_w, x.gate_b, 8, 5, 9, stis_block=sblk)
     assert_close(host(full).reshape(fr.O.shape), fr.O, TOL["fp32"], "O")
+
+
+@pytest.mark.parametrize("d,b,L", [
+    (16, 16, 416), (16, 16, 417), (16, 8, 416), (16, 8, 417), (16, 16, 560), (16, 16, 561), (16, 8, 560), (16, 8, 561),
+    (32, 16, 224), (32, 16, 225), (32, 8, 224), (32, 8, 225), (32, 16, 416), (32, 16, 417), (32, 8, 416), (32, 8, 417),
+    (32, 16, 480), (32, 16, 481), (32, 8, 480), (32, 8, 481),
+])
+def test_edges_of_the_resident_range_in_bf16(d, b, L):
+    # rows as they are stored take half the LDS: the longest heads (and one position more) whose backward holds Q and dO beside K and V
+    # (d = 32: 224; d = 16: all the backward takes), whose backward is in LDS (416) and whose forward is (560, 480)
+    run_case(with_shape(WORKLOADS["cfg2"], name=f"bf16-d{d}-b{b}-L{L}", B=3, H=2, L=L, d=d, block=b, dtype="bf16", qkv_scaled=True, len_lo=30,
+                        len_hi=L, seed=991), backward=True)
+
+
+@pytest.mark.parametrize("dtype,d,B_,H,L", [
+    ("fp32", 16, 128, 4, 129),                               # 512 heads: Q and dO beside K and V ...
+    ("fp32", 16, 171, 3, 128), ("fp32", 16, 171, 3, 129),    # ... 513: up to 128, in their place beyond
+    ("bf16", 16, 171, 3, 240), ("bf16", 16, 171, 3, 241),
+    ("fp32", 8, 171, 3, 288), ("fp32", 8, 171, 3, 289), ("fp32", 8, 171, 3, 496), ("fp32", 8, 171, 3, 497),
+])
+def test_edges_of_the_resident_range_with_more_heads(dtype, d, B_, H, L):
+    w = with_shape(WORKLOADS["cfg2"], name=f"{dtype}-d{d}-L{L}", B=B_, H=H, L=L, d=d, dtype=dtype, qkv_scaled=(dtype == "bf16"), len_lo=30,
+                   len_hi=L, backward=False, seed=992)
+    x = make_inputs(w, want_dO=True)
+    run_case(w, x=x, pairs=[0, 1, B_ * H // 2 + 1, B_ * H - 1], backward=True, gate_scale=0.4)
