@@ -143,21 +143,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   const char *Kh = reinterpret_cast<const char *>(K + head);
   const char *Vh = reinterpret_cast<const char *>(V + head);
   const int ld_row = 16 * wv + (lane >> 3);  // + 8 for the second slice
-  const unsigned k_lane = (unsigned)(ld_row * D + ((lane & 7) ^ (lane >> 4)) * 8) * 2u;            // bytes
-  const unsigned v_lane = (unsigned)(ld_row * D + ((lane & 7) ^ (2 * ((lane >> 3) & 3))) * 8) * 2u;  // bytes
+  // bytes, from a slice before the head on (the second slice's load adds kLdsSlice itself)
+  const unsigned k_lane = (unsigned)(ld_row * D + ((lane & 7) ^ (lane >> 4)) * 8) * 2u + kLdsSlice;
+  const unsigned v_lane = (unsigned)(ld_row * D + ((lane & 7) ^ (2 * ((lane >> 3) & 3))) * 8) * 2u + kLdsSlice;
+  static_assert(8 * D * 2 == kLdsSlice, "a slice is eight rows");
   // (offsets inside a head stay below 2^31 bytes: one uniform 64-bit base per tensor, 32-bit lane offsets)
   const int J_rag = p.L % BLK != 0 ? p.NB - 1 : -2;  // the one block whose rows run past the end, if any
   auto stage = [&](const char *src_head, unsigned lane_off, unsigned odd_xor, uint16_t *dst_tile, int J) __attribute__((always_inline)) {
     const unsigned joff = (unsigned)max(J, 0) * (unsigned)(TILE * 2);  // uniform (block -1: a skipped list entry, all masked)
     const unsigned dst = lds_address(dst_tile) + 16 * wv * D * 2;
-    unsigned second = 8 * D * 2;  // bytes from the first slice's source rows to the second's
+    unsigned less = 0u;  // bytes by which the second slice's source rows follow the first's closer than a slice
     if (J == J_rag) {  // last, partial block: rows past the end are clamped (they are causally masked anyway)
       const int over = J * BLK + ld_row - (p.L - 1);
       lane_off -= (unsigned)(max(over, 0) * (D * 2));
-      second -= (unsigned)((max(over + 8, 0) - max(over, 0)) * (D * 2));
+      less = (unsigned)((max(over + 8, 0) - max(over, 0)) * (D * 2));
     }
-    load_to_lds(src_head + joff, lane_off, dst);
-    load_to_lds(src_head + joff, (lane_off ^ odd_xor) + second, dst + 8 * D * 2);
+    load_to_lds(src_head - kLdsSlice + joff, lane_off, (lane_off ^ odd_xor) - less, dst);
   };
 
   // the first tile is on its way while the rest of the prologue runs

@@ -1,5 +1,6 @@
 """The C library stands without torch's headers and without the binding's host module; the binding works without the latter."""
 import os
+import subprocess
 import sys
 
 import pytest
@@ -29,3 +30,22 @@ def test_binding_without_the_host_module(monkeypatch):
     with pytest.warns(RuntimeWarning, match="_fastcall"), pytest.raises(ValueError, match="^Q: expected contiguous cuda tensor"):
         B.select_blocks(p, torch.zeros(1, 1, 8, 8), torch.zeros(1, 1, 8, 8), torch.zeros(1, dtype=torch.int32))
     assert B.fastcall() is B.PYTHON_PATH
+
+
+def test_loads_to_lds_hand_m0_back(tmp_path):
+    # m0 is the compiler's: it keeps no promise about a value of its own there across assembly that changes it, and says so
+    src = tmp_path / "probe.hip"
+    src.write_text(f'#include "{build.CSRC}/mfma_common.h"\n'
+                   'using namespace blossom;\n'
+                   '__global__ void probe(const char *from, uint4 *to) {\n'
+                   '  __shared__ uint4 rows[128];\n'
+                   '  mfma::load_to_lds(from, threadIdx.x * 16u, threadIdx.x * 16u, __builtin_amdgcn_readfirstlane(mfma::lds_address(rows)));\n'
+                   '  mfma::arrived_all<0>();\n'
+                   '  to[threadIdx.x] = rows[threadIdx.x + 64];\n'
+                   '}\n')
+    out = tmp_path / "probe.s"
+    r = subprocess.run([build._hipcc(), *build.COMMON, "--cuda-device-only", "-S", str(src), "-o", str(out)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    assert "reserved" not in r.stderr, r.stderr
+    moves = [line.split() for line in out.read_text().splitlines() if "m0" in line and "s_mov_b32" in line]
+    assert len(moves) == 3 and moves[0][2] == "m0" and moves[2][1:] == ["m0,", moves[0][1].rstrip(",")], moves
