@@ -354,10 +354,12 @@ __device__ __forceinline__ float lane_value(float v, int lane)
 {
   return __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(v), lane));
 }
-// Few picks (the paper's three): the largest image is taken as often, with all that equal it.  Its cost goes with the picks, the search's
-// with how far apart the images lie: three of 125 candidates at B=32 H=8 L=2000 d=8 20 us against 25, seven of 63 at B=32 H=8 L=1997
-// d=64 18.5 against 16.6.
-constexpr int kFewPicks = 4;
+// Few picks (the paper's three): the largest image is taken as often, with all that equal it.  Its cost goes with the passes (one more in
+// the bidirectional form, where the own block is a candidate), the search's with how far apart the images lie.  Selection alone,
+// us, passes against search: three passes at B=32 H=8 L=2000 d=8 14.6 / 20.9, L=1997 d=64 b=32 25.6 / 26.8; five 16.8 / 20.0 and 26.6 / 26.8,
+// bidirectional at B=128 H=8 L=1024 d=64 b=16 68.6 / 69.8; six 17.8 / 20.2 and 27.1 / 26.9, 70.0 / 70.2; seven 18.9 / 20.1 and 27.5 / 27.4,
+// 71.6 / 70.3.
+constexpr int kFewPasses = 5;
 // the largest over the wavefront, in a scalar register: inside rows of 16 lanes, then the four rows
 __device__ __forceinline__ unsigned lanes_max(unsigned x)
 {
@@ -414,7 +416,7 @@ __device__ __forceinline__ void pick_rows(QRow &&q, const float *k_s, int *__res
     for (int s = 0; s < SLOTS; ++s)
       u[r][s] = J[s] >= c.J_end ? 0u : p.bidir && J[s] == I0 + r ? ~0u : score_image(acc[r][s]);
   }
-  if (p.k - 1 <= kFewPicks) {
+  if (p.k - 1 + p.bidir <= kFewPasses) {
     unsigned v[R][SLOTS];
 #pragma unroll
     for (int r = 0; r < R; ++r) {

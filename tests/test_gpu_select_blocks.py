@@ -25,6 +25,9 @@ pytestmark = pytest.mark.gpu
     (50, 4, 1037, 16, 16, 4, "bf16", 2, False),   # few picks, two candidates per lane, the own block among them
     (3, 2, 2040, 64, 32, 3, "bf16", 0, True),     # few picks for the last block alone
     (3, 2, 1000, 8, 8, 1, "fp32", 0, False),      # nothing to pick beside the own block
+    (50, 4, 1037, 16, 16, 6, "fp32", 0, False),   # five passes: the most ...
+    (50, 4, 1037, 16, 16, 7, "fp32", 0, False),   # ... six: the search
+    (50, 4, 1037, 16, 16, 5, "bf16", 2, False),   # five in the bidirectional form
 ])
 def test_selection_at_the_limits_of_its_kernels(rows, H, L, d, b, k, dtype, stis, last):
     rng = np.random.default_rng(L + k)
