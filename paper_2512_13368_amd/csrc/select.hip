@@ -141,7 +141,10 @@ __global__ __launch_bounds__(256) void pool_kernel(const T *__restrict__ Q, cons
   const int p0 = p.L - clamp_len(valid_len[bh / p.H], p.L);
   const int lo = max(J * p.b, p0), hi = min((J + 1) * p.b, p.L);
   const T *src = (which ? K : Q) + (size_t)bh * p.L * D + c0;
-  if (hi - lo >= 32 && hi - lo == p.b) {
+  // (A ragged block among a wavefront's whole ones makes it run both loops, worth it while that block is a quarter of one at most:
+  // selection with d=64 b=64, us, both loops and one for all, B=4 H=4 L=5105, 49 rows left over, 12.2 / 11.0; B=9 H=4 L=3396, 4 rows,
+  // 10.5 / 12.2; B=2 H=4 L=2637, 13 rows, 9.4 / 9.8; with b=32 B=1 H=8 L=1242, 26 rows, 9.2 / 8.5.)
+  if (p.b >= 32 && __all(hi - lo == p.b || hi - lo <= p.b / 4) && hi - lo == p.b) {
 #pragma unroll
     for (int e = 0; e < EPT; ++e) a[e] = 0.0f;
     pool_rows<T, D>(src + (size_t)lo * D, p.b, a);

@@ -45,3 +45,26 @@ def test_selection_at_the_limits_of_its_kernels(rows, H, L, d, b, k, dtype, stis
     if last:
         sel, want = sel[:, :, -1], want[:, :, -1]
     np.testing.assert_array_equal(sel, want)
+
+
+@pytest.mark.parametrize("L,d,b,k,last", [
+    (2632, 64, 64, 9, False), (2576, 64, 64, 9, True),   # 8 rows left over; 16, a quarter of a block
+    (2577, 64, 64, 9, False), (2609, 64, 64, 9, True),   # 17, 49: a wavefront with that block sums all of its blocks row by row
+    (2600, 64, 32, 9, False), (2601, 64, 32, 9, True),   # 8, a quarter; 9
+    (2591, 32, 32, 9, False), (2560, 32, 32, 9, False),  # 31; none
+    (5150, 16, 64, 9, False), (5151, 8, 64, 9, False),   # a wavefront with many blocks, 30 and 31 rows left over
+])
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_pooling_beside_a_ragged_block(L, d, b, k, last, dtype):
+    # whole blocks are pooled by a loop of their own, histories that start inside a block leave another ragged one at the front
+    rng = np.random.default_rng(L + d)
+    Q, K = (rng.integers(-2, 3, size=(3, 4, L, d)).astype(np.float32) for _ in range(2))
+    vl = np.array([L, L - b - 3, L // 2 + 5], np.int32)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    p = B.Params(3, 4, L, d, b, k, 8, B.BF16 if dtype == "bf16" else B.F32, last_block_only=int(last))
+    dev = [torch.from_numpy(t).cuda() for t in (Q, K, vl)]
+    sel = B.select_blocks(p, dev[0].to(dt), dev[1].to(dt), dev[2]).cpu().numpy()
+    want = oracle.select_blocks(Q, K, vl, b, k)
+    if last:
+        sel, want = sel[:, :, -1], want[:, :, -1]
+    np.testing.assert_array_equal(sel, want)
