@@ -89,21 +89,17 @@ __device__ __forceinline__ void keep_rows(f32x16 &x, unsigned bits, int half, fl
 // and every __syncthreads(), waits for all of it, also for what was requested for later.  With these the kernel counts its
 // outstanding requests itself: arrived_all<N>() returns when at most the last N of every wavefront of the workgroup are still on
 // their way (and every wavefront's LDS reads so far are done).
-// The destination goes through m0, which the compiler takes to be its own: it is handed back as it was.  The second load's
-// offset counts for both of its addresses, so the pair needs m0 once: B=16 H=8 L=8192 d=64 b=64 takes as long as with m0 left changed
-// (handed back by each load: selection + forward 0.8 % longer, 0.6 % with the last position alone).
+// The destination is an operand in m0, which the compiler therefore sets and knows of (saved and put back by the assembly, which
+// did as much for its safety: forward of the last position alone up to 0.7 % longer at B <= 9).  The second load's offset counts for both of
+// its addresses, so the pair needs m0 once.
 __device__ __forceinline__ unsigned lds_address(const void *p) { return (unsigned)(uintptr_t)(const lds_void *)p; }
 constexpr int kLdsSlice = 1024;
 // from base + off0, and from base + off1 + kLdsSlice
 __device__ __forceinline__ void load_to_lds(const char *base, unsigned off0, unsigned off1, unsigned lds)
 {
-  unsigned m0;
-  asm volatile(
-      "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %4\n\t"
-      "global_load_lds_dwordx4 %3, %4 offset:%5\n\ts_mov_b32 m0, %0"
-      : "=&s"(m0)
-      : "s"(lds), "v"(off0), "v"(off1), "s"(base), "n"(kLdsSlice)
-      : "memory");
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\tglobal_load_lds_dwordx4 %2, %3 offset:%4" ::"{m0}"(lds), "v"(off0), "v"(off1),
+               "s"(base), "n"(kLdsSlice)
+               : "memory");
 }
 template <int N>
 __device__ __forceinline__ void arrived_all()
