@@ -165,9 +165,10 @@ __device__ __forceinline__ bool finite(float x) { return fabsf(x) <= 3.402823466
 // 3.3e-8 against 7.3e-8: they round once per instruction.)  At d = 16 a contraction over rows would save nothing: the split
 // of its coefficients takes 22 vector instructions.  A training step at B=256 H=2 L=200 d=32 in the bidirectional form: 145 us
 // with everything as floats, 89 like this.
+constexpr bool stored_bits(bool bf16, int d) { return bf16 && d >= 16; }
 template <typename T, int D>
 struct Operands {
-  static constexpr bool kBf = std::is_same<T, bf16_t>::value && D >= 16, kBfCol = kBf && D == 32;
+  static constexpr bool kBf = stored_bits(std::is_same<T, bf16_t>::value, D), kBfCol = kBf && D == 32;
   static constexpr int CPL = Geo<D>::CPL;
   struct RowF { float v[CPL]; };
   struct RowB { unsigned w[CPL / 2]; };
@@ -608,8 +609,10 @@ __device__ __forceinline__ void store_lds(float *p, const float (&o)[N])
 // the same from LDS, where a workgroup staged the head: fp32 rows of D + 4 floats (20 or 36; d = 8: 8), or the bf16 bits themselves in
 // rows of D + 4 (d = 16) or D + 8 halfwords: every read pattern is conflict free, rows stay aligned for a row operand's load.
 // (d = 8 in rows of 12: three backward workgroups per CU where the registers allow four, positions at B=2048 L=200 635 us, 569 so)
+// In floats; the kernels lay their LDS out with it, the launches size it.
+constexpr int lds_row(bool bf16, int d) { return stored_bits(bf16, d) ? (d == 32 ? 20 : 10) : d == 8 ? 8 : d + 4; }
 template <typename T, int D>
-constexpr int kLdsRow = Operands<T, D>::kBf ? (D == 32 ? 20 : 10) : D == 8 ? 8 : D + 4;  // in floats
+constexpr int kLdsRow = lds_row(std::is_same<T, bf16_t>::value, D);
 template <typename T, int D>
 struct LdsRows {
   static constexpr bool kNear = true;  // near: operands are read where they are used and take no registers before
@@ -2201,14 +2204,12 @@ SmallPlan stream_plan(const KParams &p, int units, size_t words_per_wave)
   s.parts = std::max(1, std::min((NT + s.waves - 1) / s.waves, want));
   return s;
 }
-// floats of a staged row: kLdsRow
-int lds_row(const KParams &p, int dtype) { return dtype == 1 && p.d >= 16 ? (p.d == 32 ? 20 : 10) : p.d == 8 ? 8 : p.d + 4; }
 SmallPlan fwd_plan(const KParams &p, int dtype, bool perpos, int hpg)
 {
   const size_t rows = (size_t)(p.L + kTile - 1) / kTile * kTile;
   const int units = p.B * p.H / hpg;
   SmallPlan s{true, false, res_waves(units), 1, 0};
-  s.lds = (2 * rows * lds_row(p, dtype) + (size_t)s.waves * lt_words(p, perpos)) * sizeof(float);
+  s.lds = (2 * rows * lds_row(dtype == 1, p.d) + (size_t)s.waves * lt_words(p, perpos)) * sizeof(float);
   if (p.nq == p.NB && s.lds <= small_lds_limit(p)) return s;
   s = stream_plan(p, p.B * p.H, lt_words(p, perpos));
   if (p.nq != p.NB) s = SmallPlan{false, false, 1, 1, lt_words(p, perpos) * sizeof(float)};  // serving mode: one query tile per head
@@ -2221,7 +2222,7 @@ SmallPlan bwd_plan(const KParams &p, int dtype, bool perpos, int hpg)
   // few that no CU has more than two to hold, everything fits beside a second one (gradients at B=82 H=4 L=174 d=16: 50.8 us with
   // everything in LDS, 52.3 with Q and dO read again; B=40 H=8 L=170 d=16, a whole step 47.5 and 48.4)
   auto bytes = [&](const SmallPlan &s) {
-    return (size_t)ResLayout(p, lds_row(p, dtype), perpos, hpg, s.overlay, s.waves).total * sizeof(float);
+    return (size_t)ResLayout(p, lds_row(dtype == 1, p.d), perpos, hpg, s.overlay, s.waves).total * sizeof(float);
   };
   for (int overlay = many_heads(units) ? 1 : 0; overlay < 2; ++overlay) {
     SmallPlan s{true, overlay != 0, res_waves(units), 1, 0};
