@@ -146,14 +146,6 @@ __device__ __forceinline__ float sum_row(float x)
   x += row_ror<2>(x);
   return x + row_ror<1>(x);
 }
-__device__ __forceinline__ float max_row(float x)
-{
-  x = fmaxf(x, row_ror<8>(x));
-  x = fmaxf(x, row_ror<4>(x));
-  x = fmaxf(x, row_ror<2>(x));
-  return fmaxf(x, row_ror<1>(x));
-}
-
 __device__ __forceinline__ bool finite(float x) { return fabsf(x) <= 3.402823466e38f; }
 
 // THE MATRIX OPERANDS.  Row: a lane's channels of one row, for contractions over channels; Col: its four rows of one channel, for
@@ -1988,7 +1980,6 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     const float *__restrict__ gate_w, const T *__restrict__ dO, SmallWs ws, T *__restrict__ dK, T *__restrict__ dV, int hpg, int parts,
     KParams p)
 {
-  constexpr int CPL = Geo<D>::CPL;
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = blockDim.x >> 6;
   const unsigned vid = mfma::xcd_spread(blockIdx.x, gridDim.x / parts, parts);
@@ -2061,7 +2052,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     const float *__restrict__ lse_st, const T *__restrict__ dO, T *__restrict__ dQ, T *__restrict__ dK, T *__restrict__ dV,
     float *__restrict__ partial, int hpg, int overlay, unsigned stages, KParams p)
 {
-  constexpr int CPL = Geo<D>::CPL, GW = 2 * D + 1;
+  constexpr int GW = 2 * D + 1;
   extern __shared__ __attribute__((aligned(16))) float small_lds[];
   __shared__ float red[kMaxWaves][GW];
   const int lane = threadIdx.x & 63;
