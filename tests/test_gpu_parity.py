@@ -437,6 +437,16 @@ def test_inverse_lists_beside_the_gate_pass(L):
     run_case(w, backward=True, gate_scale=0.4)
 
 
+@pytest.mark.parametrize("L", [8192, 8193, 8392])
+def test_gate_sums_beside_the_backward_of_long_histories(L):
+    # bf16, d = 64, block 32: 64 partial sums to a head and row, as many as are taken at a time, and more; the second row's first
+    # ones are of padding
+    w = with_shape(WORKLOADS["cfg3"], name=f"gate-L{L}", B=2, H=2, L=L, topk=3, window=40, len_lo=300, len_hi=L, seed=79)
+    x = make_inputs(w, want_dO=True)
+    x.valid_len[:] = [L, 300]
+    run_case(w, x=x, backward=True, gate_scale=0.4)
+
+
 def test_edge_cases():
     base = with_shape(WORKLOADS["cfg1"], name="edge", B=5, H=2, L=50, seed=301)
     x = make_inputs(base, want_dO=True)
