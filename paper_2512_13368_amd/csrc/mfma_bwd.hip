@@ -26,9 +26,10 @@
 // two-term bf16 sums.
 //
 // Matrix pipe and vector ALUs share the issue and are busy 85 % of the time together, so what a tile does not need is left out:
-// masks are bits (two instructions an element instead of four, and 5 to 20 spilled registers fewer), and at block 64 a unit of
-// 32 keys (queries) none of the wavefront's rows sees (keys are seen by) is skipped.  A training step at B=16 H=8 L=8192 k=16
-// w=128 2078 -> 2042 us with both, at B=128 H=4 L=1024 k=8 w=64 in blocks of 32 403 -> 398 us.
+// masks are bits (two instructions an element instead of four; three of the six one-launch kernels shed their four spilled registers,
+// the one with mask blocks smaller than its tile of 32 keeps its sixteen), and at block 64 a unit of 32 keys (queries) none of
+// the wavefront's rows sees (keys are seen by) is skipped.  A training step at B=16 H=8 L=8192 k=16 w=128 2078 -> 2042 us with both, at
+// B=128 H=4 L=1024 k=8 w=64 in blocks of 32 403 -> 398 us.
 #include "gate_reduce.h"
 #include "launch.h"
 #include "mfma_common.h"

@@ -599,8 +599,11 @@ __device__ __forceinline__ void store_lds(float *p, const float (&o)[N])
   }
 }
 // the same from LDS, where a workgroup staged the head: fp32 rows of D + 4 floats (20 or 36; d = 8: 8), or the bf16 bits themselves in
-// rows of D + 4 (d = 16) or D + 8 halfwords: every read pattern is conflict free, rows stay aligned for a row operand's load.
-// (d = 8 in rows of 12: three backward workgroups per CU where the registers allow four, positions at B=2048 L=200 635 us, 569 so)
+// rows of D + 4 (d = 16) or D + 8 halfwords; rows stay aligned for a row operand's load.  Of the LDS' index cycles bank conflicts take
+// a quarter at d = 32 in fp32, a third there in bf16 and at d = 16, and at d = 8, whose rows q and q + 8 share their banks, half in the forward
+// and two fifths in the backward (profiles/small_heads_pipe_counters.txt); the LDS is busy 4 to 22 % of the time.  Without conflicts cost
+// more: d = 8 in rows of 12, three backward workgroups per CU where the registers allow four, positions at B=2048 L=200 635 us, 569
+// so; the 16-byte halves of rows q >= 8 swapped, two fifths of the conflicts less and the whole of it 1-3 % slower.
 // In floats; the kernels lay their LDS out with it, the launches size it.
 constexpr int lds_row(bool bf16, int d) { return stored_bits(bf16, d) ? (d == 32 ? 20 : 10) : d == 8 ? 8 : d + 4; }
 template <typename T, int D>
@@ -782,10 +785,10 @@ struct Walk {
 // mask and the exponential are, and spread_g hands the four results to all groups, which add them into their accumulators'
 // channels (`own`).  About 12 vector instructions a distance; as tiles of the walk the distances took half of its steps at L=2000
 // (a training step at B=32 H=8 L=2000 d=8 356 us, 302 like this; B=2048 H=8 L=200 d=16 1050 and 996).
-// They come after the walk, whose registers they may then use (ahead of it d = 32 spilled, and short calls waited for them), and whose
-// sums are not rounded at the size these large terms give them (dQ at d = 16 against 64 bits 1.028 of the error of tiles, 1.014
-// so; the rest is the rounding of products formed on the vector ALUs, and the lse makes up for it, see the forward).
-// The backward at d = 8 takes them first: its sums are a lane group's own parts, and the walk runs 2 % faster (L=1657: 69.0 and
+// They come after the walk: they may then use its registers (ahead of it d = 32 spilled), and the walk's sums are not rounded at the
+// size of these large terms (dQ at L=450 d=16 against 64 bits: ahead 1.028 times the error that tiles had, so 1.014; the rest is the
+// rounding of products on the vector ALUs, and the lse more than makes up for it, see the forward).
+// The backward at d = 8 takes them first: its sums are a lane group's own parts, and its walk runs 2 % faster so (L=1657: 69.0 and
 // 70.3 us).
 // f(d): tiles X + d, X + 2d, X + 4d, X + 8d (some may lie outside lo .. hi: d times the lane group's power tells).
 template <typename F>
