@@ -436,13 +436,15 @@ struct LaneMasks {
   {
     return from(p0 - key0) & below((p.bidir ? p.L : i + 1) - key0);
   }
+  // FAR: those too
+  template <bool FAR = false>
   __device__ __forceinline__ unsigned st(const KParams &p, int dt) const
   {
     const int far = dt < 0 ? -dt : dt;
     if (far <= 1) return near >> (dt == 0 ? 0 : dt == 1 ? 4 : 8);
     const int d0 = kTile * dt + c;
     unsigned m = from(d0 - p.w + 1) & below(d0 + p.w);
-    if (p.sblk == 1 && (far & (far - 1)) == 0 && far < first_diagonal(p)) m |= from(c) & below(c + 1);
+    if (p.sblk == 1 && (far & (far - 1)) == 0 && (FAR || far < first_diagonal(p))) m |= from(c) & below(c + 1);
     return m;
   }
 };
@@ -800,6 +802,12 @@ __device__ __forceinline__ void diagonals(const KParams &p, int X, int lo, int h
 }
 template <int D>
 constexpr bool kFarFirst = Geo<D>::kQuads;
+// The backward from d = 16 on under a selection per position leaves them in the walk: nearly every tile is walked there for some row's
+// selection, and these keys cost it a mask, where a batch of distances costs the time of a tile.  Gradients with them and without, us:
+// B=300 H=4 over 2 L=200 d=32 222 and 170 (204 with a tile of its own kind for a distance), B=700 H=8 over 4 L=180 d=16 289 and 275; in the
+// forward they gain at d = 32 too (61.7 and 64.6).
+template <int D, bool PERPOS>
+constexpr bool kDiagonals = !(PERPOS && D >= 16);
 // d = 32: the phases of a batch of distances are kept apart: their registers would spill
 template <int D>
 __device__ __forceinline__ void phase_end()
@@ -1375,6 +1383,7 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
                                            GateSums<D> &gate, const LaneMasks &lm, bool do_rows, bool do_dq, T *dQ_head, Sink &&sink)
 {
   constexpr int CPL = Geo<D>::CPL, NMB = Geo<D>::NMB, NACC = Geo<D>::NACC;
+  constexpr bool kDiag = kDiagonals<D, PERPOS>;
   const int q = lane & 15, g = lane >> 4;
   const float c2 = p.scale * kLog2eF, kc = Operands<T, D>::kBf ? c2 : 1.0f;  // (kc: what a product of rows is still to be multiplied by)
   const int iq = I * kTile + q;
@@ -1460,7 +1469,7 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
       unsigned v_lt = 0u, v_st = 0u;
       if constexpr (UNIT) {
         const unsigned ok = LaneMasks::keys(p, key0, p0, iq);
-        v_st = (lm.st(p, I - t) | LaneMasks::from(p.last_lo - key0)) & ok;
+        v_st = (lm.st<!kDiag>(p, I - t) | LaneMasks::from(p.last_lo - key0)) & ok;
         v_lt = s_lt ? ok : 0u;
       }
 #pragma unroll
@@ -1484,7 +1493,7 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
         ds[r] = ((PERPOS || BK < kTile) ? (v ? e : 0.0f) : e) * (g_lt[r] - D_lt);
       }
     } else {
-      const unsigned v = UNIT ? lm.st(p, I - t) : 0u;
+      const unsigned v = UNIT ? lm.st<!kDiag>(p, I - t) : 0u;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         float e = __builtin_amdgcn_exp2f(arg(s[r], l2_st));
@@ -1500,7 +1509,7 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
   auto word = [&](int w) __attribute__((always_inline)) {
     const int t = w * 64 + lane;
     const bool edge = (t == T0) | (t == I) | (t >= min(NT - 1, p.last_lo / kTile));
-    wk.start<false>(p, I, w, T0, J_hi, lane, ls.has_tile(min(t, NT - 1)), edge, CAREFUL, true);
+    wk.start<false>(p, I, w, T0, J_hi, lane, ls.has_tile(min(t, NT - 1)), edge, CAREFUL || !kDiag, true);
   };
   auto walk = [&](auto unit) __attribute__((always_inline)) {
     for (int w = T0 >> 6; w <= J_hi >> 6; ++w) {
@@ -1559,10 +1568,10 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
         }
       });
     };
-    if (kFarFirst<D> && p.sblk == 1) far_keys();
+    if (kDiag && kFarFirst<D> && p.sblk == 1) far_keys();
     if (p.sblk <= 1) walk(std::true_type{});
     else walk(std::false_type{});
-    if (!kFarFirst<D> && p.sblk == 1) far_keys();
+    if (kDiag && !kFarFirst<D> && p.sblk == 1) far_keys();
   } else {
     for (int w = T0 >> 6; w <= J_hi >> 6; ++w) {
       word(w);
@@ -1603,6 +1612,7 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
                                          const typename Operands<T, D>::Row &vf, int hpg, const Src &src, T *dK_head, T *dV_head)
 {
   constexpr int CPL = Geo<D>::CPL, NMB = Geo<D>::NMB, NACC = Geo<D>::NACC;
+  constexpr bool kDiag = kDiagonals<D, PERPOS>;
   const int q = lane & 15, g = lane >> 4;
   const int NWb = (p.NB + 31) / 32;
   using Ops = Operands<T, D>;
@@ -1685,7 +1695,7 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
       const bool in_lt = KIND != 0 || wk.is_lt(t);
       unsigned v_lt = 15u, v_st = 0u;  // UNIT: the masks as bits
       if constexpr (UNIT) {
-        if constexpr (ST) v_st = lm.st(p, J - t);
+        if constexpr (ST) v_st = lm.st<!kDiag>(p, J - t);
         if constexpr (KIND == 0) {
           const unsigned ok = LaneMasks::from(p.bidir ? 0 : j - i0);
           v_st = (last_k ? 15u : v_st) & ok;
@@ -1733,7 +1743,7 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
     auto word = [&](int w) __attribute__((always_inline)) {
       const int t = w * 64 + lane;
       const unsigned tw = src.tile_word(min(max(t, T0), NT - 1), J >> 5);
-      wk.start<true>(p, J, w, I_lo, NT - 1, lane, (tw >> (J & 31)) & 1u, last_tile | (t == J), CAREFUL, true);
+      wk.start<true>(p, J, w, I_lo, NT - 1, lane, (tw >> (J & 31)) & 1u, last_tile | (t == J), CAREFUL || !kDiag, true);
     };
     auto walk = [&](auto unit) __attribute__((always_inline)) {
       for (int w = I_lo >> 6; w <= (NT - 1) >> 6; ++w) {
@@ -1854,10 +1864,10 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
     if constexpr (CAREFUL) {
       walk_carefully();
     } else {
-      if (kFarFirst<D> && p.sblk == 1) far_queries();
+      if (kDiag && kFarFirst<D> && p.sblk == 1) far_queries();
       if (p.sblk <= 1) walk(std::true_type{});
       else walk(std::false_type{});
-      if (!kFarFirst<D> && p.sblk == 1) far_queries();
+      if (kDiag && !kFarFirst<D> && p.sblk == 1) far_queries();
     }
     // the gate part of dV: sum_i dz_i P_ij times the gate row of the branch
     if constexpr (Geo<D>::kQuads) {  // (a lane's part of the sums, like the accumulators)

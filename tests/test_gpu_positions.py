@@ -171,6 +171,21 @@ def test_backward_under_a_per_position_selection(dtype, Bn, H, G, L, d, l, s, ls
         assert torch.equal(a, b2)
 
 
+@pytest.mark.parametrize("dtype,Bn,H,G,L,d,lsel,k,window", [
+    ("fp32", 3, 4, 2, 33, 32, 16, 3, 1),      # a last tile of one row, no window beyond the position itself
+    ("fp32", 3, 4, 2, 128, 32, 16, 4, 8),     # a head of a group in LDS
+    ("fp32", 3, 4, 2, 432, 32, 16, 4, 40),    # the longest, streamed; three tiles of window: the first power of two beyond is 64
+    ("fp32", 3, 8, 4, 200, 16, 16, 4, 8),
+    ("fp32", 2, 4, 2, 736, 16, 16, 1, 18),    # the longest; the own block alone, so that most powers of two lie in no selected tile
+    ("bf16", 3, 4, 2, 150, 32, 8, 4, 9),
+    ("bf16", 3, 4, 4, 333, 16, 16, 4, 8),
+    ("fp32", 3, 8, 2, 500, 8, 8, 4, 8),       # d = 8: powers of two on the vector ALUs
+])
+def test_backward_under_a_per_position_selection_and_mask_block_1(dtype, Bn, H, G, L, d, lsel, k, window):
+    # from d = 16 on the keys at powers of two stay in the walk's tiles, selected or not
+    test_backward_under_a_per_position_selection(dtype, Bn, H, G, L, d, 16, 8, lsel, k, window, 1, 1)
+
+
 def test_per_position_attention_limits():
     z = lambda *s: torch.zeros(s, device="cuda")
     vl = torch.tensor([64], dtype=torch.int32, device="cuda")
