@@ -787,11 +787,12 @@ struct Walk {
 // mask and the exponential are, and spread_g hands the four results to all groups, which add them into their accumulators'
 // channels (`own`).  About 12 vector instructions a distance; as tiles of the walk the distances took half of its steps at L=2000
 // (a training step at B=32 H=8 L=2000 d=8 356 us, 302 like this; B=2048 H=8 L=200 d=16 1050 and 996).
-// They come after the walk: they may then use its registers (ahead of it d = 32 spilled), and the walk's sums are not rounded at the
-// size of these large terms (dQ at L=450 d=16 against 64 bits: ahead 1.028 times the error that tiles had, so 1.014; the rest is the
-// rounding of products on the vector ALUs, and the lse more than makes up for it, see the forward).
-// The backward at d = 8 takes them first: its sums are a lane group's own parts, and its walk runs 2 % faster so (L=1657: 69.0 and
-// 70.3 us).
+// They come after the walk: they may then use its registers (ahead of it d = 32 and the forward at d = 8 spilled), and the walk's sums are
+// not rounded at the size of these large terms (dQ at L=450 d=16 against 64 bits: ahead 1.028 times the error that tiles had, so
+// 1.014; the rest is the rounding of products on the vector ALUs, and the lse more than makes up for it, see the forward).
+// First they are where that is better: the forward of bf16 rows at d = 32, whose walk adds with fewer roundings (o_st at L=1000: 1.04 of
+// the error after it) and has the registers; the backward at d = 8, whose sums are a lane group's own parts and whose walk runs 2 %
+// faster so (L=1657: 69.0 and 70.3 us).
 // f(d): tiles X + d, X + 2d, X + 4d, X + 8d (some may lie outside lo .. hi: d times the lane group's power tells).
 template <typename F>
 __device__ __forceinline__ void diagonals(const KParams &p, int X, int lo, int hi, F &&f)
@@ -853,13 +854,14 @@ __device__ __forceinline__ void own_of_row(const float (&x)[N], float (&o)[1][4]
 #pragma unroll
   for (int r = 0; r < 4; ++r) o[0][r] = x[r & (N - 1)];
 }
+// four distances' products, summed before they meet the accumulators: one rounding at their size instead of four
 template <int N>
-__device__ __forceinline__ void add_own(f32x4 (&acc)[N], float c, const float (&a)[N][4])
+__device__ __forceinline__ void add_own(f32x4 (&acc)[N], const float (&c)[4], const float (&a)[4][N][4])
 {
 #pragma unroll
   for (int mb = 0; mb < N; ++mb)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) acc[mb][r] = fmaf(c, a[mb][r], acc[mb][r]);
+    for (int r = 0; r < 4; ++r) acc[mb][r] += fmaf(c[3], a[3][mb][r], fmaf(c[2], a[2][mb][r], fmaf(c[1], a[1][mb][r], c[0] * a[0][mb][r])));
 }
 
 // What a query tile's wavefront knows about its long-term selection.  In LDS (this wavefront's words): sel rows of
@@ -1133,9 +1135,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
         while (wk.m2) body(std::integral_constant<int, 2>{}, unit, wk.m2);
       }
     };
-    if (p.sblk <= 1) walk(std::true_type{});
-    else walk(std::false_type{});
-    if (p.sblk == 1 && !dense) {
+    auto far_keys = [&]() __attribute__((always_inline)) {
       float qd[CPL];
       Ops::floats(qf, qd);
       float qw[CPL * 4];
@@ -1171,11 +1171,15 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
         const float ex = ok ? __builtin_amdgcn_exp2f(kc * x) : 0.0f;
         l_st += ex;
         spread_g(ex, e);
-#pragma unroll
-        for (int n = 0; n < 4; ++n) add_own(a_st, e[n], vo[n]);
+        add_own(a_st, e, vo);
         }
       });
-    }
+    };
+    constexpr bool far_first = D == 32 && Ops::kBf;
+    if (far_first && p.sblk == 1 && !dense) far_keys();
+    if (p.sblk <= 1) walk(std::true_type{});
+    else walk(std::false_type{});
+    if (!far_first && p.sblk == 1 && !dense) far_keys();
     if (__builtin_expect(!__all(s_max * kc <= kSmallLogit && abs_sum(a_lt) + abs_sum(a_st) < 1.0e37f), 0)) {
       // large logits, or values near the end of fp32's range or beyond: the row maxima of both branches, then the walk
       // against them
@@ -1563,8 +1567,7 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
         const int key = iq + kTile * d * (1 << g);
         const bool ok = (key >= p0) & (key < p.last_lo);
         spread_g(ok ? e * (gv - D_st) : 0.0f, x);
-#pragma unroll
-        for (int n = 0; n < 4; ++n) add_own(dq_part, x[n], ko[n]);
+        add_own(dq_part, x, ko);
         }
       });
     };
@@ -1853,11 +1856,8 @@ __device__ __forceinline__ bool key_tile(const KParams &p, int J, int T0, int NT
         t_st = fmaf(zd, pr, t_st);
         spread_g(as * pr, s);
         spread_g(pr * fmaf(as, gd, fmaf(zd, wv_st, -constant(3))), x);
-#pragma unroll
-        for (int n = 0; n < 4; ++n) {
-          add_own(dv_part, s[n], go[n]);
-          add_own(dk_part, x[n], qo[n]);
-        }
+        add_own(dv_part, s, go);
+        add_own(dk_part, x, qo);
         }
       });
     };
