@@ -2104,13 +2104,14 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
 // K and V are staged, the query tiles run (each leaving its Q and dO rows, row constants and selection in LDS), then the key
 // tiles.  Every tensor comes from memory once, in two round trips.  overlay: Q and dO do not fit beside K and V; they take
 // their place after the query tiles, read a second time (from L2).
-template <typename T, int D, int BK, bool PERPOS>
+// ORDER: see HEADS BY LENGTH (a kernel of its own: beside it, though never taken, the code cost B=2048 H=8 L=200 1-2 %).
+template <typename T, int D, int BK, bool PERPOS, bool ORDER>
 __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(4))) void bwd_res_kernel(
     const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V, const int *__restrict__ valid_len,
     const int *__restrict__ sel, const float *__restrict__ gate_w, const float *__restrict__ gate_b,
     const float *__restrict__ o_lt, const float *__restrict__ o_st, const float *__restrict__ lse_lt,
     const float *__restrict__ lse_st, const T *__restrict__ dO, T *__restrict__ dQ, T *__restrict__ dK, T *__restrict__ dV,
-    float *__restrict__ partial, int hpg, int overlay, int by_length, unsigned stages, KParams p)
+    float *__restrict__ partial, int hpg, int overlay, unsigned stages, KParams p)
 {
   constexpr int GW = 2 * D + 1;
   extern __shared__ __attribute__((aligned(16))) float small_lds[];
@@ -2118,8 +2119,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = blockDim.x >> 6;
   // (row, key/value head)
-  int bg = (int)blockIdx.x;
-  if (__builtin_expect(by_length, 0)) bg = __builtin_amdgcn_readfirstlane(unit_by_length(valid_len, p, p.H / hpg, blockIdx.x, gridDim.x));
+  const int bg = ORDER ? __builtin_amdgcn_readfirstlane(unit_by_length(valid_len, p, p.H / hpg, blockIdx.x, gridDim.x)) : (int)blockIdx.x;
   const int NT = (p.L + kTile - 1) / kTile, NWt = (NT + 31) / 32, NWb = (p.NB + 31) / 32;
   const int p0 = p.L - clamp_len(valid_len[bg / (p.H / hpg)], p.L);
   const int T0 = p0 / kTile;
@@ -2399,10 +2399,10 @@ static void launch_bwd_small_t(const KParams &p, const BwdArgs &a, const SmallWs
         hipLaunchKernelGGL(kernel, dim3((unsigned)(p.B * p.H / hpg)), dim3(64 * pl.waves), pl.lds, st, (const T *)a.Q,
                            (const T *)a.K, (const T *)a.V, a.valid_len, a.sel, a.gate_w, a.gate_b, (const float *)a.o_lt,
                            (const float *)a.o_st, a.lse_lt, a.lse_st, (const T *)a.dO, (T *)a.dQ, (T *)a.dK, (T *)a.dV, w.partial,
-                           hpg, (int)pl.overlay, (int)order_by_length(p, p.B * p.H / hpg), stages, p);
+                           hpg, (int)pl.overlay, stages, p);
       };
-      if (perpos) go(bwd_res_kernel<T, D, BK, true>);
-      else go(bwd_res_kernel<T, D, BK, false>);
+      if (order_by_length(p, p.B * p.H / hpg)) perpos ? go(bwd_res_kernel<T, D, BK, true, true>) : go(bwd_res_kernel<T, D, BK, false, true>);
+      else perpos ? go(bwd_res_kernel<T, D, BK, true, false>) : go(bwd_res_kernel<T, D, BK, false, false>);
       return;
     }
     if (stages & (kBwdStageGate | kBwdStageDQ)) {
