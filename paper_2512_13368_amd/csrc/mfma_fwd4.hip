@@ -359,7 +359,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     const bool windowed = short_term && !(EQ15 && !sub && is_pow2(I - J));
     asm volatile("" : "+v"(koff[0]), "+v"(koff[1]), "+v"(koff[2]), "+v"(koff[3]), "+v"(voff[0]), "+v"(voff[1]));
     // long-term tiles of whole earlier blocks (the usual case) need neither a mask nor any other test
-    bool full = !short_term && (unsigned)(J - J_whole) < (unsigned)(I - J_whole);
+    // (I < J_whole, a block with padding: none)
+    bool full = !short_term && (unsigned)(J - J_whole) < (unsigned)max(I - J_whole, 0);
     if (!full) {
       const int k_lo = J * BLK + 32 * kh, k_hi = k_lo + 31;
       const int q_lo = qbase, q_hi = qbase + 31;

@@ -212,6 +212,22 @@ def test_selection_rows_with_holes(name, shape):
     run_case(w, backward=True, gate_scale=0.4, sel_edit=punch)
 
 
+@pytest.mark.parametrize("b", [32, 64])
+def test_a_hole_in_front_of_the_own_block(b):
+    # the first block with a valid query (padding before it) lists an entry that is no block, then itself
+    L = 5 * b
+    w = with_shape(WORKLOADS["cfg4"], name=f"hole-in-front-{b}", B=2, H=2, L=L, block=b, topk=3, window=b, len_lo=1, len_hi=L, seed=640 + b)
+    x = make_inputs(w, want_dO=True)
+    x.valid_len[:] = [L - b - 5, 2 * b + 9]
+
+    def shift(sel):
+        for r, first in ((0, 1), (1, 2)):
+            sel[r, :, first] = [-1, first, -1]
+        return sel
+
+    run_case(w, x=x, backward=True, gate_scale=0.4, sel_edit=shift)
+
+
 @pytest.mark.parametrize("b,topk,window", [(64, 1, 5), (64, 2, 40), (32, 1, 200), (32, 2, 7), (64, 3, 20)])
 def test_matrix_core_few_key_rows(b, topk, window):
     # bf16 d=64 (the matrix-core kernels) where rows see only a few keys far beyond the first blocks:
