@@ -437,14 +437,15 @@ __global__ __launch_bounds__(64 * kInvWaves) void inverse_list_kernel(const int 
 
 // =============================================================================================
 // Backward, step 1: gate backward per row + per-chunk partial gate-weight gradients.
-//   rowstat[row] = (alpha, dz, D_lt, D_st)
-//   g_x, rowI_x: the branch's rounded upstream gradient and row constants (matrix-core path, see below)
+//   rowstat[row] = (alpha, dz, D_lt, D_st); in the matrix-core path (y_lt, y_st, -c_lt, -c_st) and rowI_x the row constants of
+//   branch x, see below
 //   partial[(bh*nchunk+chunk)][0..2D] (2D = bias)
 // Every tensor is read exactly once, so memory is the bound, but a row costs five sums over its channels and
 // some sixty instructions that its lanes share: as few lanes as give whole cache lines take a row (4 channels
 // each, for d = 64 twice 4: 8 lanes), the sums are DPP adds inside a row of 16 lanes instead of LDS permutes, and the
 // next rows are requested before the current ones are worked on.  B=128 H=4 L=1024 d=64, lengths U[100,1024]: 77 -> 71 us, 59 with the
-// heads to the XCDs in turn; B=16 H=8 L=8192: 183 -> 175 us (5.7 TB/s).
+// heads to the XCDs in turn; B=16 H=8 L=8192: 183 -> 175 us (5.7 TB/s).  Since it writes no gradients of the branches for the
+// matrix-core kernels, 52 and 148 us (5.0 TB/s).
 // The gate-weight partials accumulate in registers and meet in LDS in a fixed order.
 // =============================================================================================
 // The first `lists` workgroups make the inverse selection lists instead: a chain of latencies (8 us at B=128 H=4 L=1024, 26 at B=16
@@ -495,8 +496,6 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(const float *__restrict__
                                                        float *__restrict__ partial,
                                                        const float *__restrict__ lse_lt,
                                                        const float *__restrict__ lse_st,
-                                                       uint16_t *__restrict__ g_lt,
-                                                       uint16_t *__restrict__ g_st,
                                                        uint4 *__restrict__ rowI_lt,
                                                        uint4 *__restrict__ rowI_st, const int *__restrict__ sel,
                                                        int *__restrict__ offs, int *__restrict__ items, int lists, KParams p)
@@ -552,7 +551,7 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(const float *__restrict__
       r.os[q] = load_raw4(o_st + ro + q * (D / 2));
     }
     r.ll = r.ls = 0.0f;
-    if (g_lt) {
+    if (rowI_lt) {
       r.ll = lse_lt[lr];
       r.ls = lse_st[lr];
     }
@@ -605,40 +604,38 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(const float *__restrict__
       dz = (a_ll - a_ss) * alpha * (1.0f - alpha);
       st = make_float4(alpha, dz, alpha * a_ll + dz * w_l, (1.0f - alpha) * a_ss + dz * w_s);
     }
-    if (inb && sub == 0) rowstat[(size_t)bh * p.L + i] = st;
-    if (g_lt) {
-      // Matrix-core path: the upstream gradient of each branch, dO_x = a_x*dO + dz*Wg_x, rounded
-      // to bf16 once, and the row constant c_x = dO_x.o_x taken with the SAME rounded values, so
-      // that P*(dO_x.v - c_x) is the exact softmax backward of the rounded gradient (rows with a
-      // single key still cancel to zero).  -lse*log2(e) and -c_x are left as three-term bf16
-      // splits, the form in which one matrix instruction broadcasts them into an accumulator.
-      uint32_t gl[CPL / 2], gs[CPL / 2];
+    if (rowI_lt) {
+      // Matrix-core path: the upstream gradient of branch x is a_x*(dO + y_x*Wg_x), a_lt = alpha, a_st = 1 - alpha, y_lt = (1-alpha)*t,
+      // y_st = alpha*t, t = dO.(o_lt - o_st); y_x as the two bf16 terms that the kernels read.  Two row constants stand beside it:
+      // D_x = (dO + y_x*Wg_x).o_x, and c_x, the same with the bracket rounded to bf16, as dQ takes it.  rowI_x (x: s0 s1, y: D2 s2,
+      // z: D0 D1, w: y0 y1): the three-term bf16 splits of -lse*log2(e) + log2(a_x) and of -D_x and the terms of y_x, in the
+      // order in which one matrix instruction takes them.
+      const float t = a_ll - a_ss;
+      const uint32_t yl2 = mfma::split2((1.0f - alpha) * t), ys2 = mfma::split2(alpha * t);
+      const float yl = mfma::unsplit2(yl2), ys = mfma::unsplit2(ys2);
       float c_l = 0.0f, c_s = 0.0f;
 #pragma unroll
       for (int e = 0; e < CPL; e += 2) {
-        gl[e / 2] = mfma::pack2_bf16(fmaf(alpha, g[e], dz * wl[e]), fmaf(alpha, g[e + 1], dz * wl[e + 1]));
-        gs[e / 2] = mfma::pack2_bf16(fmaf(1.0f - alpha, g[e], dz * ws[e]), fmaf(1.0f - alpha, g[e + 1], dz * ws[e + 1]));
-        c_l = fmaf(mfma::bf_hi(gl[e / 2]), ol[e + 1], fmaf(mfma::bf_lo(gl[e / 2]), ol[e], c_l));
-        c_s = fmaf(mfma::bf_hi(gs[e / 2]), os[e + 1], fmaf(mfma::bf_lo(gs[e / 2]), os[e], c_s));
+        const uint32_t gl = mfma::pack2_bf16(fmaf(yl, wl[e], g[e]), fmaf(yl, wl[e + 1], g[e + 1]));
+        const uint32_t gs = mfma::pack2_bf16(fmaf(ys, ws[e], g[e]), fmaf(ys, ws[e + 1], g[e + 1]));
+        c_l = fmaf(mfma::bf_hi(gl), ol[e + 1], fmaf(mfma::bf_lo(gl), ol[e], c_l));
+        c_s = fmaf(mfma::bf_hi(gs), os[e + 1], fmaf(mfma::bf_lo(gs), os[e], c_s));
       }
       c_l = lanes_sum<LPR>(c_l);
       c_s = lanes_sum<LPR>(c_s);
-      if (inb) {
-        const size_t ro = head + (size_t)i * D + c4;
-#pragma unroll
-        for (int q = 0; q < NG; ++q) {
-          *reinterpret_cast<uint2 *>(g_lt + ro + q * (D / 2)) = make_uint2(gl[2 * q], gl[2 * q + 1]);
-          *reinterpret_cast<uint2 *>(g_st + ro + q * (D / 2)) = make_uint2(gs[2 * q], gs[2 * q + 1]);
-        }
-        if (sub < 2) {  // lane 0 of the row writes the long-term constants, lane 1 the short-term ones
-          const size_t r = (size_t)bh * p.L + i;
-          // pad rows: an exponent of -1e30 makes every probability of the row zero
-          const uint2 l = mfma::split3(valid ? -(sub == 0 ? ll : ls) * 1.4426950408889634f : -1.0e30f);
-          const uint2 k = mfma::split3(-(sub == 0 ? c_l : c_s));
-          (sub == 0 ? rowI_lt : rowI_st)[r] = make_uint4(l.x, l.y, k.x, k.y);
-        }
+      st = make_float4(valid ? yl : 0.0f, valid ? ys : 0.0f, valid ? -c_l : 0.0f, valid ? -c_s : 0.0f);
+      if (inb && sub < 2) {  // lane 0 of the row writes the long-term constants, lane 1 the short-term ones
+        const size_t r = (size_t)bh * p.L + i;
+        const float a = sub == 0 ? alpha : 1.0f - alpha;
+        // an exponent of -1e30 makes every probability of the row zero: of pad rows, and of a branch whose weight is (log2 of it:
+        // the probabilities come out multiplied by the weight)
+        const float e2 = -(sub == 0 ? ll : ls) * 1.4426950408889634f + __log2f(a);
+        const uint2 l = mfma::split3(valid && !(a < 1.17549435e-38f) ? e2 : -1.0e30f);
+        const uint2 k = mfma::split3(valid ? -(sub == 0 ? fmaf(yl, w_l, a_ll) : fmaf(ys, w_s, a_ss)) : 0.0f);
+        (sub == 0 ? rowI_lt : rowI_st)[r] = make_uint4(l.x, k.y | l.y << 16, k.x, valid ? (sub == 0 ? yl2 : ys2) : 0u);
       }
     }
+    if (inb && sub == 0) rowstat[(size_t)bh * p.L + i] = st;
 #pragma unroll
     for (int e = 0; e < CPL; ++e) {
       acc_l[e] = fmaf(dz, ol[e], acc_l[e]);
@@ -1080,10 +1077,6 @@ BwdWorkspace bwd_carve(const KParams &p, int dtype, void *ws)
   w.partial = reinterpret_cast<float *>(base + off);
   off = align256(off + BH * w.nchunk * (2 * p.d + 1) * sizeof(float));
   if (bwd_mfma_supported(p, dtype)) {
-    w.g_lt = reinterpret_cast<uint16_t *>(base + off);
-    off = align256(off + BH * p.L * p.d * sizeof(uint16_t));
-    w.g_st = reinterpret_cast<uint16_t *>(base + off);
-    off = align256(off + BH * p.L * p.d * sizeof(uint16_t));
     w.rowI_lt = reinterpret_cast<uint4 *>(base + off);
     off = align256(off + BH * p.L * sizeof(uint4));
     w.rowI_st = reinterpret_cast<uint4 *>(base + off);
@@ -1132,7 +1125,7 @@ static void launch_bwd_t(const KParams &p, int dtype, const BwdArgs &a, unsigned
     const unsigned lists = with_lists ? BH : 0u;
     BLOSSOM_LAUNCH((bwd_prep_kernel<T, D>), dim3(BH * w.nchunk + lists), dim3(256), 0, st,
                        (const float *)a.o_lt, (const float *)a.o_st, (const T *)a.dO, a.valid_len, a.gate_w,
-                       a.gate_b, w.rowstat, w.partial, a.lse_lt, a.lse_st, w.g_lt, w.g_st, w.rowI_lt, w.rowI_st, a.sel,
+                       a.gate_b, w.rowstat, w.partial, a.lse_lt, a.lse_st, w.rowI_lt, w.rowI_st, a.sel,
                        w.offs, w.items, (int)lists, p);
     if (!mfma || !bwd_mfma_takes_gate(p, stages)) launch_gate_reduce(p, a, w.partial, w.nchunk, st);
     if (launch_failed()) return;

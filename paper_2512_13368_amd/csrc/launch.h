@@ -57,14 +57,12 @@ void launch_select(const KParams &p, int dtype, const void *Q, const void *K, bo
 
 // Backward workspace, carved from the caller's buffer.
 struct BwdWorkspace {
-  float4 *rowstat;   // [B*H*L] (alpha, dz, D_lt, D_st)
+  float4 *rowstat;   // [B*H*L] (alpha, dz, D_lt, D_st); matrix-core path: (y_lt, y_st, -c_lt, -c_st), see bwd_prep_kernel
   int *offs;         // [B*H,(NB+1)] inverse selection list: offsets
   int *items;        // [B*H,NB*k]   inverse selection list: query blocks per key block, in a fixed order;
                      //              bit kInvFewShift marks a query block whose long-term rows may see few keys
   float *partial;    // [B*H*nchunk,(2d+1)] partial gate-weight gradients
-  // matrix-core path only: per-branch upstream gradient dO_x = a_x*dO + dz*Wg_x in bf16, and per
-  // row the three-term bf16 splits of (-lse_x*log2(e), -dO_x.o_x) as (hi|mid<<16, lo) pairs
-  uint16_t *g_lt, *g_st;      // [B*H*L,d]
+  // matrix-core path only: the row constants of a branch as bf16 terms, see bwd_prep_kernel
   uint4 *rowI_lt, *rowI_st;   // [B*H*L]
   int nchunk;
   size_t total;

@@ -2,26 +2,29 @@
 // stationary) and dK/dV (key-block stationary), chain rule through Eq. 1 and Eq. 16-19 with
 // the selection held fixed.
 //
-// The upstream gradient of branch x is dO_x = a_x*dO + dz*Wg_x (a_lt = alpha, a_st = 1-alpha;
-// gate backward).  The per-row pass rounds it to bf16 ONCE and derives the row constant
-// c_x = dO_x.o_x from the same rounded values; then
-//   dS_ij = P_ij * (dO_x,i.v_j - c_x,i),   dV_j = sum_i P_ij dO_x,i,   dK_j = sum_i dS_ij q_i,
-//   dQ_i = sum_j dS_ij k_j
-// is the exact softmax backward of the rounded gradient: the cancellation that rows with one
-// or two keys rely on (dO_x.v_j = c_x when P = 1) survives, and the kernels are left with one
-// exponential, one multiply and the bf16 conversions per score.
+// The upstream gradient of branch x is a_x*(dO + y_x*Wg_x) (a_lt = alpha, a_st = 1-alpha; gate backward, y_x per row): the caller's
+// dO, a factor and a rank-one term.  It is never formed in memory.  With P' = a_x*P (log2(a_x) goes into the exponent)
+//   dS_ij = P'_ij * (dO_i.v_j + y_i*u_j - D_i),  u_j = Wg_x.v_j,  D_i = (dO_i + y_i*Wg_x).o_x,i
+//   dV_j = sum_i P'_ij dO_i + (sum_i P'_ij y_i) Wg_x,   dK_j = sum_i dS_ij q_i,   dQ_i = sum_j dS_ij k_j
+// In dK/dV dO enters as it is, and the rank-one term to 2^-17: the cancellation that rows with one or two keys rely on
+// (dO.v_j + y*u_j = D when P = 1) survives.  In dQ, where a lane keeps its row, the bracket dO + y_x*Wg_x is rounded to bf16 once and
+// its row constant c_x is taken with the same rounded values.  With two rounded gradients in memory and residual passes of dK/dV for
+// rows with few keys a training step at B=128 H=4 L=1024 k=8 w=64 in blocks of 32 took 352 us (the per-row pass 62, these kernels
+// 190) instead of 337 (52, 188), at B=32 H=8 L=1997 with all of Eq. 15 494 instead of 488, at B=16 H=8 L=8192 k=16 w=128 in
+// blocks of 64 the same 2045 (181 and 1206 instead of 148 and 1240: sixteen more additions a unit for the sums of P'*y); dK and
+// dV came out with 5 % larger errors.
 //
 // Accumulators start at minus a per-row constant, so the MFMA result is directly what the next
-// step needs: the exponent S'' = c*q.k - lse*log2(e) (Q or K pre-multiplied by c =
-// scale*log2(e)) and dO_x,i.v_j - c_x,i.  The constants arrive as three-term bf16 splits (exact).
-// dK/dV, where they change with every query tile, broadcasts them into the accumulator by one
-// extra matrix instruction (ones x split); dQ, where a lane keeps its row for the whole walk,
+// step needs: the exponent S'' = c*q.k - lse*log2(e) + log2(a_x) (Q or K pre-multiplied by c =
+// scale*log2(e)) and the bracket of dS.  The constants arrive as three-term bf16 splits (exact), y as two terms.
+// dK/dV, where they change with every query tile, brings them into the accumulator by one
+// extra matrix instruction (row terms x ones, and x the terms of u_j); dQ, where a lane keeps its row for the whole walk,
 // holds them as two 16-register blocks that the first matrix instruction of each product
 // takes as its C operand.  Either way no per-element VALU initialisation is needed.  (Reading
 // the dK/dV constants from LDS straight into a C block was measured slower: that kernel
 // already issues 25 LDS reads per 18 matrix instructions.)  Probabilities and dS leave the accumulator
 // registers as the B operand of the next product without moving between lanes; the matching
-// A operands (K^T, Q^T, dO_x^T) come from LDS through the transposing ds_read_b64_tr_b16.
+// A operands (K^T, Q^T, dO^T) come from LDS through the transposing ds_read_b64_tr_b16.
 // Query blocks whose rows may see only a few keys (large probabilities) feed P and dS as
 // two-term bf16 sums.
 //
@@ -222,27 +225,50 @@ __device__ __forceinline__ void store_rows_bf16(uint16_t *dst_row0, int rows_lef
 }
 
 // s_waitcnt immediates (gfx9 encoding: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8)
-constexpr int kVm0 = (7 << 4) | (15 << 8);             // every vector-memory operation has finished
+constexpr int vmcnt_imm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }  // all but the n youngest
+constexpr int kVm0 = vmcnt_imm(0);                     // every vector-memory operation has finished
 constexpr int kLgkm0 = 15 | (7 << 4) | (3 << 14);      // every LDS and scalar-memory operation has
 
 constexpr int kFewKeys = 32;    // rows seeing fewer keys than this get two-term bf16 operands
 
-// ones[.][0..2] in the half of the wavefront that holds contraction slots 0..7: multiplied with a
-// three-term split it broadcasts the split's value along the other dimension of the tile
-__device__ __forceinline__ bf16x8 ones3(int lh)
+// Row constants (bwd_prep_kernel) as MFMA operands for the exponent and for the bracket, and what both meet: ones, and the lane's
+// u_j = Wg_x.v_j in three terms (the other half of the wavefront holds the slots 8..15).  Slots that are not used meet zeros, or are
+// zeros and meet something finite.
+__device__ __forceinline__ bf16x8 exponent_operand(const uint4 &r) { return __builtin_bit_cast(bf16x8, make_uint4(r.x, r.y, 0u, 0u)); }
+__device__ __forceinline__ bf16x8 bracket_operand(const uint4 &r) { return __builtin_bit_cast(bf16x8, make_uint4(r.z, r.y << 16, r.w, r.w)); }
+__device__ __forceinline__ bf16x8 column_terms(float u, int lh)
 {
-  bf16x8 o;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) o[e] = (__bf16)((lh == 0 && e < 3) ? 1.0f : 0.0f);
-  return o;
+  constexpr uint32_t one = 0x3F80u;
+  const uint2 t = split3(u);
+  const uint32_t hi = t.x & 0xFFFFu, mid = t.x >> 16, lo = t.y;
+  return __builtin_bit_cast(bf16x8, lh == 0 ? make_uint4(one | one << 16, one << 16, hi | hi << 16, mid | mid << 16)
+                                            : make_uint4(0u, 0u, lo | lo << 16, 0u));
 }
 
-// a packed split (hi | mid << 16, lo) as an MFMA operand (slots 0..2; lanes of the other half
-// meet zeros of ones3 and may hold anything finite)
-__device__ __forceinline__ bf16x8 split_operand(uint32_t x, uint32_t y)
+// Where the sixteen rows of a lane's accumulator are found in its row of 16 lanes: lane l holds the value of tile row acc_row(l), and
+// sum_rows adds sum_i P[i] * value(row of P[i]) with the value as a DPP operand (row_newbcast), without a register for each.
+__device__ __forceinline__ int acc_row(int lane) { return 8 * ((lane >> 2) & 3) + 4 * (lane >> 5) + (lane & 3); }
+// (In assembly: the compiler makes sixteen moves of it.  A DPP operand may be read two states after it was written.)
+__device__ __forceinline__ void sum_rows(const f32x16 &P, float x, float &sum)
 {
-  const uint4 raw = make_uint4(x, y, 0u, 0u);
-  return __builtin_bit_cast(bf16x8, raw);
+#define ROW(n) "\n\tv_fmac_f32_dpp %0, %1, %" #n " row_newbcast:"
+#define ALL " row_mask:0xf bank_mask:0xf"
+  asm("s_nop 1" ROW(2) "0" ALL ROW(3) "1" ALL ROW(4) "2" ALL ROW(5) "3" ALL ROW(6) "4" ALL ROW(7) "5" ALL ROW(8) "6" ALL ROW(9) "7" ALL
+      ROW(10) "8" ALL ROW(11) "9" ALL ROW(12) "10" ALL ROW(13) "11" ALL ROW(14) "12" ALL ROW(15) "13" ALL ROW(16) "14" ALL ROW(17) "15" ALL
+      : "+v"(sum)
+      : "v"(x), "v"(P[0]), "v"(P[1]), "v"(P[2]), "v"(P[3]), "v"(P[4]), "v"(P[5]), "v"(P[6]), "v"(P[7]), "v"(P[8]), "v"(P[9]), "v"(P[10]),
+        "v"(P[11]), "v"(P[12]), "v"(P[13]), "v"(P[14]), "v"(P[15]));
+#undef ALL
+#undef ROW
+}
+
+// this lane's 32 channels of a branch's gate weights (the slabs of load_frags)
+__device__ __forceinline__ void load_gate(const float *w, int lh, float (&g)[4][8])
+{
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+    for (int e = 0; e < 8; e += 4) load4(w + 16 * kk + 8 * lh + e, reinterpret_cast<float(&)[4]>(g[kk][e]));
 }
 
 }  // namespace
@@ -250,7 +276,7 @@ __device__ __forceinline__ bf16x8 split_operand(uint32_t x, uint32_t y)
 // =============================================================================================
 // dQ: one workgroup per (row, head, query block), one wavefront per 32 query rows.
 //   per 32-key unit:  S''^T = K (cQ)^T - lse2       (keys x queries, lane owns a query column)
-//                     G^T   = V dO_x^T - c_x
+//                     G^T   = V (dO + y_x*Wg_x)^T - c_x
 //                     dS^T  = 2^S'' * G^T  -> bf16 -> B operand
 //                     dQ^T += K^T dS^T      (K^T through the transposing LDS read)
 // EQ15: the short-term mask is all of Eq. 15, with mask block BLK or (SUB) a power of two below it;
@@ -261,9 +287,8 @@ __device__ __forceinline__ bf16x8 split_operand(uint32_t x, uint32_t y)
 template <int BLK, bool EQ15, bool SUB>
 __device__ __forceinline__ void bwd_dq_body(
     const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K, const uint16_t *__restrict__ V,
-    const int *__restrict__ valid_len, const int *__restrict__ sel, const uint16_t *__restrict__ g_lt,
-    const uint16_t *__restrict__ g_st, const uint4 *__restrict__ rowI_lt, const uint4 *__restrict__ rowI_st,
-    const uint16_t *__restrict__ dO, const float4 *__restrict__ rowstat, const float *__restrict__ gate_w,
+    const int *__restrict__ valid_len, const int *__restrict__ sel, const uint4 *__restrict__ rowI_lt,
+    const uint4 *__restrict__ rowI_st, const uint16_t *__restrict__ dO, const float4 *__restrict__ rowstat, const float *__restrict__ gate_w,
     const float *__restrict__ o_lt, const float *__restrict__ o_st, uint16_t *__restrict__ dQ, KParams p, unsigned pid,
     uint16_t *Ks0, uint16_t *Ks1, uint16_t *Vs0, uint16_t *Vs1)
 {
@@ -294,19 +319,23 @@ __device__ __forceinline__ void bwd_dq_body(
     return;
   }
 
-  bf16x8 qf[4], gf[4], gf_next[4];
+  bf16x8 qf[4], gf[4], gf_next[4];  // gf: the short-term bracket (the walk starts with the window tiles), gf_next: the long-term one
   load_frags(Q + rowoff, lh, qf);
-  load_frags(g_st + rowoff, lh, gf);       // the walk starts with the window tiles
-  load_frags(g_lt + rowoff, lh, gf_next);
+  load_frags(dO + rowoff, lh, gf);
+  const float *gate = gate_w + (size_t)(bh % p.H) * 2 * D;
+  float w_lt[4][8], w_st[4][8];
+  load_gate(gate, lh, w_lt);
+  load_gate(gate + D, lh, w_st);
+  const float4 rs = rowstat[lrow];  // y_lt, y_st, -c_lt, -c_st
   // per-row constants (pad rows carry an exponent of -1e30: every probability of the column is zero)
   const uint4 ri_st = rowI_st[lrow];
   const uint4 ri_lt = rowI_lt[lrow];
-  // s_init, g_init: -lse2[i] and -c_x[i] of this lane's row in every accumulator slot.  The
+  // s_init, g_init: -lse2[i] (with log2(a_x)) and -c_x[i] of this lane's row in every accumulator slot.  The
   // first matrix instruction of each product takes them as its C operand, so the logits and
   // dP - c_x leave the matrix cores with the row terms already applied.
   f32x16 s_init, g_init;
-  auto set_init = [&](uint32_t sx, uint32_t sy, uint32_t cx, uint32_t cy) __attribute__((always_inline)) {
-    const float a = unsplit3(sx, sy), b = unsplit3(cx, cy);
+  auto set_init = [&](uint32_t sx, uint32_t sy, float b) __attribute__((always_inline)) {
+    const float a = unsplit3(sx, sy >> 16);
 #pragma unroll
     for (int i = 0; i < 16; ++i) { s_init[i] = a; g_init[i] = b; }
     asm volatile("" : "+v"(s_init), "+v"(g_init));  // register blocks, not one value copied at each use
@@ -352,45 +381,39 @@ __device__ __forceinline__ void bwd_dq_body(
   const int hp_st = __builtin_amdgcn_readfirstlane((int)(p.w < kFewKeys || q0 - p0 + 1 < kFewKeys));
   const int hp_lt = __builtin_amdgcn_readfirstlane((int)lt_few);
   const int n_all = n_st + n_lt;
-  // For those rows the bf16 rounding of dO_x itself would show as well (dS is large, and the
-  // small projections dO_x.(v_j - o) lose relative accuracy): the residual dO_x - bf16(dO_x) is
-  // rebuilt from dO, alpha, dz and the gate weights exactly as the per-row pass formed it, and
-  // enters as a second B operand; the row constant gains the matching residual.o_x.
+  // For those rows the bf16 rounding of the bracket itself would show as well (dS is large, and the
+  // small projections of it on v_j - o lose relative accuracy): its residual enters as a second B operand, and the row constant
+  // gains the matching residual.o_x.
   bf16x8 gl[4], gl_next[4];
-  uint32_t c1_st_x = ri_st.z, c1_st_y = ri_st.w, c1_lt_x = ri_lt.z, c1_lt_y = ri_lt.w;
+  float c1_lt = rs.z, c1_st = rs.w;
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
     for (int e = 0; e < 8; ++e) { gl[kk][e] = (__bf16)0.0f; gl_next[kk][e] = (__bf16)0.0f; }
   if (hp_st | hp_lt) {
-    const float4 st = rowstat[lrow];
-    const float *wrow = gate_w + (size_t)(bh % p.H) * 2 * D;
-    float corr_st = 0.0f, corr_lt = 0.0f;
+    bf16x8 dof[4];
+    load_frags(dO + rowoff, lh, dof);
+    auto residual = [&](const float *w, float y, const float *o_row, bf16x8 (&lo)[4]) __attribute__((always_inline)) -> float {
+      float corr = 0.0f;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const uint4 raw = *reinterpret_cast<const uint4 *>(dO + rowoff + 16 * kk + 8 * lh);
-      const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+      for (int kk = 0; kk < 4; ++kk) {
+        float g[8], o[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int dd = 16 * kk + 8 * lh + e;
-        const float g = (e & 1) ? bf_hi(w[e >> 1]) : bf_lo(w[e >> 1]);
-        const float full_l = fmaf(st.x, g, st.y * wrow[dd]);
-        const float full_s = fmaf(1.0f - st.x, g, st.y * wrow[D + dd]);
-        const __bf16 lo_l = (__bf16)(full_l - bf16_to_f32(f32_to_bf16(full_l)));
-        const __bf16 lo_s = (__bf16)(full_s - bf16_to_f32(f32_to_bf16(full_s)));
-        gl_next[kk][e] = lo_l;
-        gl[kk][e] = lo_s;
-        corr_lt = fmaf((float)lo_l, o_lt[rowoff + dd], corr_lt);
-        corr_st = fmaf((float)lo_s, o_st[rowoff + dd], corr_st);
+        for (int e = 0; e < 8; e += 4) {
+          load4(w + 16 * kk + 8 * lh + e, reinterpret_cast<float(&)[4]>(g[e]));
+          load4(o_row + 16 * kk + 8 * lh + e, reinterpret_cast<float(&)[4]>(o[e]));
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float full = fmaf(y, g[e], (float)dof[kk][e]);
+          lo[kk][e] = (__bf16)(q_ok ? full - (float)(__bf16)full : 0.0f);
+          corr = fmaf((float)lo[kk][e], o[e], corr);
+        }
       }
-    }
-    corr_lt += __shfl_xor(corr_lt, 32);
-    corr_st += __shfl_xor(corr_st, 32);
-    const uint2 ns = split3(unsplit3(ri_st.z, ri_st.w) - corr_st);
-    const uint2 nl = split3(unsplit3(ri_lt.z, ri_lt.w) - corr_lt);
-    if (q_ok) {
-      c1_st_x = ns.x; c1_st_y = ns.y; c1_lt_x = nl.x; c1_lt_y = nl.y;
-    }
+      return q_ok ? corr + __shfl_xor(corr, 32) : 0.0f;
+    };
+    c1_lt -= residual(gate, rs.x, o_lt + rowoff, gl_next);
+    c1_st -= residual(gate + D, rs.y, o_st + rowoff, gl);
   }
   if constexpr (!ONE) __syncthreads();
   // Block id of tile t: window blocks by arithmetic, selected blocks by a scalar load from the
@@ -511,7 +534,7 @@ __device__ __forceinline__ void bwd_dq_body(
       gf[kk] = gf_next[kk];
       gl[kk] = gl_next[kk];
     }
-    set_init(ri_lt.x, ri_lt.y, c1_lt_x, c1_lt_y);
+    set_init(ri_lt.x, ri_lt.y, c1_lt);
   };
   int J_cur = list_entry(tile_of(0));
   int J_nxt = list_entry(tile_of(min(1, n_all - 1)));
@@ -524,12 +547,22 @@ __device__ __forceinline__ void bwd_dq_body(
     __builtin_amdgcn_sched_barrier(0);
   }
   scale_frags(p.scale * kLog2e, qf);
-  set_init(ri_st.x, ri_st.y, c1_st_x, c1_st_y);
+  // the brackets (zeros in a pad row: dO may hold anything there)
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float g = (float)gf[kk][e];
+      gf_next[kk][e] = (__bf16)(q_ok ? fmaf(rs.x, w_lt[kk][e], g) : 0.0f);
+      gf[kk][e] = (__bf16)(q_ok ? fmaf(rs.y, w_st[kk][e], g) : 0.0f);
+    }
+  set_init(ri_st.x, ri_st.y, c1_st);
   if constexpr (ONE) {
     int J_2 = list_entry(tile_of(min(2, n_all - 1)));
     auto step = [&](int t, uint16_t *ks, uint16_t *vs) __attribute__((always_inline)) {
       const int J_after = tile_of(min(t + 3, n_all - 1));  // consumed at the end of this step
       if (t == n_st) to_long_term();
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(8));  // the tile is there; the next one's eight loads may be on their way
       tile_body(ks, vs, J_cur, t < n_st, [&]() __attribute__((always_inline)) {
         sg.stage(k_lane, ks, J_2);
         sg.stage(v_lane, vs, J_2);
@@ -574,23 +607,22 @@ __device__ __forceinline__ void bwd_dq_body(
 // =============================================================================================
 // dK, dV: one workgroup per (row, head, key block), one wavefront per 32 key rows; walks the
 // query blocks whose window reaches the key block, then those that selected it (inverse list).
-//   per 32-query unit:  S'' = Q (cK)^T - lse2[i]   (queries x keys, lane owns a key column)
-//                       G   = dO_x V^T - c_x[i]
-//                       P = 2^S'',  dS = P*G
-//                       dV^T += dO_x^T P,  dK^T += Q^T dS
+//   per 32-query unit:  S'' = Q (cK)^T - lse2[i] + log2(a_x[i])   (queries x keys, lane owns a key column)
+//                       G   = dO V^T + y_x[i]*u_x[j] - D_x[i]
+//                       P' = 2^S'',  dS = P'*G
+//                       dV^T += dO^T P',  dK^T += Q^T dS,  r_x[j] += sum_i P'*y_x[i]
+//   and at the end dV^T += Wg_lt r_lt + Wg_st r_st
 // =============================================================================================
 
 template <int BLK, bool EQ15, bool SUB>
 __device__ __forceinline__ void bwd_dkv_body(
     const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K, const uint16_t *__restrict__ V,
-    const int *__restrict__ valid_len, const uint16_t *__restrict__ g_lt, const uint16_t *__restrict__ g_st,
-    const uint4 *__restrict__ rowI_lt, const uint4 *__restrict__ rowI_st, const int *__restrict__ offs,
-    const int *__restrict__ items, const uint16_t *__restrict__ dO, const float4 *__restrict__ rowstat,
-    const float *__restrict__ gate_w, const float *__restrict__ o_lt, const float *__restrict__ o_st,
-    uint16_t *__restrict__ dK, uint16_t *__restrict__ dV, KParams p, unsigned pid, uint16_t *Qs0, uint16_t *Qs1,
-    uint16_t *Gs0, uint16_t *Gs1, uint4 (*rc_s)[BLK])
+    const int *__restrict__ valid_len, const uint4 *__restrict__ rowI_lt, const uint4 *__restrict__ rowI_st,
+    const int *__restrict__ offs, const int *__restrict__ items, const uint16_t *__restrict__ dO,
+    const float *__restrict__ gate_w, uint16_t *__restrict__ dK, uint16_t *__restrict__ dV, KParams p, unsigned pid,
+    uint16_t *Qs0, uint16_t *Qs1, uint16_t *Gs0, uint16_t *Gs1, uint4 *rc0, uint4 *rc1)
 {
-  // (rc_s: per-row constants of the staged query tile: splits of -lse2 (x, y) and of -c_x (z, w))
+  // (rc0, rc1: 64 row constants each, of the staged query tiles)
   constexpr int UNITS = BLK / 32;
   constexpr bool ONE = UNITS == 1;  // a workgroup of one wavefront: see REFILL at bwd_both_mfma_kernel
 
@@ -620,7 +652,7 @@ __device__ __forceinline__ void bwd_dkv_body(
   bf16x8 kf[4], vf[4];
   load_frags(K + rowoff, lh, kf);
   load_frags(V + rowoff, lh, vf);
-  const bf16x8 ones = ones3(lh);
+  const float *gate = gate_w + (size_t)(bh % p.H) * 2 * D;
 
   // ---- walk: window part I = J..I_hi, then the inverse selection list ----
   const long last_q = (long)J * BLK + (BLK - 1) + (p.w - 1);
@@ -658,8 +690,7 @@ __device__ __forceinline__ void bwd_dkv_body(
   Stager<BLK> sg;
   sg.init(wv, lane, p.L, p.NB);
   const uint16_t *q_lane = Q + head;  // (row, head) slices; the stager adds block and lane offsets
-  const uint16_t *gl_lane = g_lt + head;
-  const uint16_t *gs_lane = g_st + head;
+  const uint16_t *g_lane = dO + head;
   ReadOffsets ro = read_offsets(lane);
   const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   const uint4 pad_consts = make_uint4(0x0000f149u, 0u, 0u, 0u);  // -1e30 as (hi, 0, 0): probability zero
@@ -674,10 +705,31 @@ __device__ __forceinline__ void bwd_dkv_body(
     return r;
   };
 
-  // (rc_of(s): the row constants of this lane's row in unit s; refill: called once the tile has been read to
-  // registers, ONE only)
-  auto tile_body = [&](const uint16_t *qs, const uint16_t *gsm, auto rc_of, int Iq, bool short_term, bool hp, auto refill)
-                       __attribute__((always_inline)) {
+  bf16x8 u_terms;                  // of the branch the walk is in, short-term first
+  float u_lt;
+  float r_sum = 0.0f, r_st = 0.0f;  // this lane's part of r_x, of the branch the walk is in and of the short-term one
+  auto gate_products = [&]() __attribute__((always_inline)) {
+    auto product = [&](const float *w) __attribute__((always_inline)) -> float {
+      float g[4][8], u = 0.0f;
+      load_gate(w, lh, g);
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) u = fmaf(g[kk][e], (float)vf[kk][e], u);
+      return u + __shfl_xor(u, 32);
+    };
+    u_lt = product(gate);
+    u_terms = column_terms(product(gate + D), lh);
+  };
+  auto to_long_term = [&]() __attribute__((always_inline)) {
+    u_terms = column_terms(u_lt, lh);
+    r_st = r_sum;
+    r_sum = 0.0f;
+  };
+
+  // (rcs: the tile's row constants; refill: called once the tile has been read to registers, ONE only)
+  auto tile_body = [&](const uint16_t *qs, uint16_t *gsm, const uint4 *rcs, int Iq, bool short_term, bool hp,
+                       auto refill) __attribute__((always_inline)) {
     // band-masked by the window, unless Eq. 15 shows the whole block (power-of-two block distance)
     const bool windowed = short_term && !(EQ15 && !sub && is_pow2(Iq - J));
     asm volatile("" : "+v"(ro.row[0]), "+v"(ro.row[1]), "+v"(ro.row[2]), "+v"(ro.row[3]), "+v"(ro.tr[0]), "+v"(ro.tr[1]), "+v"(ro.tr8[0]), "+v"(ro.tr8[1]));
@@ -688,14 +740,21 @@ __device__ __forceinline__ void bwd_dkv_body(
     const int hi_i = windowed && !(EQ15 && j >= p.last_lo) ? min(p.L - 1, j + p.w - 1) : p.L - 1;
     const unsigned span = (unsigned)(hi_i - lo_i);
     const bool any = key_ok && hi_i >= lo_i;
+    if (Iq * BLK < p0) {  // dO is the caller's in the padding too, where a product may overflow (either wavefront writes the same zeros)
+      if constexpr (ONE) __builtin_amdgcn_s_waitcnt(kVm0);
+      for (int o = 16 * lane; o < (p0 - Iq * BLK) * (D * 2); o += 1024)
+        *reinterpret_cast<uint4 *>(reinterpret_cast<char *>(gsm) + o) = make_uint4(0u, 0u, 0u, 0u);
+    }
 #pragma unroll
     for (int s = 0; s < UNITS; ++s) {
       if constexpr (!ONE) {  // none of the 32 query rows sees a key of the wavefront: earlier than all of them, padding, past the window
         const int i_lo = Iq * BLK + 32 * s, i_hi = i_lo + 31, j0 = J * BLK + 32 * wv;
         if (i_hi < j0 || i_hi < p0 || j0 + 31 < p0 || (!EQ15 && windowed && i_lo > j0 + 31 + p.w - 1)) continue;
       }
-      const uint4 rc = rc_of(s);
-      bf16x8 gt[2][2], qt[2][2];  // dO_x^T and Q^T operands of the last products
+      uint4 rc = rcs[32 * s + lq];
+      if (ONE && Iq * BLK + lq >= p.L) rc = pad_consts;
+      const uint32_t y = rcs[32 * s + acc_row(lane)].w;
+      bf16x8 gt[2][2], qt[2][2];  // dO^T and Q^T operands of the last products
       auto read_tr = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int t = 0; t < 2; ++t)
@@ -705,8 +764,8 @@ __device__ __forceinline__ void bwd_dkv_body(
             qt[t][mb] = lds_tr(qs, 2 * (32 * s + 16 * t) * D + ro.tr[mb], 2 * (32 * s + 16 * t) * D + ro.tr8[mb]);
           }
       };
-      f32x16 sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(split_operand(rc.x, rc.y), ones, zero16, 0, 0, 0);
-      f32x16 gacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(split_operand(rc.z, rc.w), ones, zero16, 0, 0, 0);
+      f32x16 sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(exponent_operand(rc), u_terms, zero16, 0, 0, 0);
+      f32x16 gacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bracket_operand(rc), u_terms, zero16, 0, 0, 0);
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
         sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_row(qs, 2 * 32 * s * D + ro.row[kk]), kf[kk], sacc, 0, 0, 0);
@@ -749,7 +808,7 @@ __device__ __forceinline__ void bwd_dkv_body(
       }
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        sacc[i] = __builtin_amdgcn_exp2f(sacc[i]);  // P
+        sacc[i] = __builtin_amdgcn_exp2f(sacc[i]);  // P'
         gacc[i] *= sacc[i];                         // dS
       }
       bf16x8 pf[2], dsf[2];
@@ -763,6 +822,7 @@ __device__ __forceinline__ void bwd_dkv_body(
           dv[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gt[t][mb], pf[t], dv[mb], 0, 0, 0);
           dk[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qt[t][mb], dsf[t], dk[mb], 0, 0, 0);
         }
+      sum_rows(sacc, unsplit2(y), r_sum);
       if (hp) {  // rows with few keys: large P and dS, add the rounding residuals as a second bf16 term
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
@@ -790,28 +850,29 @@ __device__ __forceinline__ void bwd_dkv_body(
   int ent_cur = entry_of(0);
   int ent_nxt = entry_of(min(1, n_all - 1));
   if constexpr (ONE) {
-    // this lane's row constants of block Iq (rows past the end are replaced when they are used)
-    auto request_rc = [&](int Iq, bool win) __attribute__((always_inline)) -> uint4 {
-      return (win ? rowI_st : rowI_lt)[lbase + min(Iq * BLK + lq, p.L - 1)];
-    };
-    auto fill = [&](uint16_t *qs, uint16_t *gsm, int ent, bool win) __attribute__((always_inline)) -> uint4 {
+    // (the row constants go straight to LDS too, ten registers less; rows past the end are replaced when they are used)
+    auto fill = [&](uint16_t *qs, uint16_t *gsm, uint4 *rc, int ent, bool win) __attribute__((always_inline)) {
       const int Iq = ent & kInvBlockMask;
       sg.stage(q_lane, qs, Iq);
-      sg.stage(win ? gs_lane : gl_lane, gsm, Iq);
-      return request_rc(Iq, win);
+      sg.stage(g_lane, gsm, Iq);
+      const uint4 *src_head = (win ? rowI_st : rowI_lt) + lbase;
+      const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(src_head), 0, p.L * (int)sizeof(uint4), 0x00020000);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (lds_void *)rc, 16, (unsigned)min(Iq * BLK + lq, p.L - 1) * (unsigned)sizeof(uint4), 0, 0, 0);
     };
-    uint4 rc0 = fill(Qs0, Gs0, ent_cur, 0 < n_st);
+    fill(Qs0, Gs0, rc0, ent_cur, 0 < n_st);
     __builtin_amdgcn_sched_barrier(0);  // (the first tile's loads stay the older ones: what the loop's waits count on)
-    uint4 rc1 = fill(Qs1, Gs1, ent_nxt, 1 < n_st);
+    fill(Qs1, Gs1, rc1, ent_nxt, 1 < n_st);
     __builtin_amdgcn_sched_barrier(0);
+    gate_products();
     scale_frags(p.scale * kLog2e, kf);
     int ent_2 = entry_of(min(2, n_all - 1));
-    auto step = [&](int t, uint16_t *qs, uint16_t *gsm, uint4 &rc) __attribute__((always_inline)) {
+    auto step = [&](int t, uint16_t *qs, uint16_t *gsm, uint4 *rc) __attribute__((always_inline)) {
       const int ent_after = entry_of(min(t + 3, n_all - 1));  // consumed at the end of this step
       const bool win = t < n_st;
       const int Iq = ent_cur & kInvBlockMask;
-      tile_body(qs, gsm, [&](int) { return Iq * BLK + lq < p.L ? rc : pad_consts; }, Iq, win, few(ent_cur, win),
-                [&]() __attribute__((always_inline)) { rc = fill(qs, gsm, ent_2, t + 2 < n_st); });
+      if (t == n_st) to_long_term();
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(9));  // the tile is there; the next one's nine loads may be on their way
+      tile_body(qs, gsm, rc, Iq, win, few(ent_cur, win), [&]() __attribute__((always_inline)) { fill(qs, gsm, rc, ent_2, t + 2 < n_st); });
       ent_cur = ent_nxt;
       ent_nxt = ent_2;
       ent_2 = ent_after;
@@ -828,14 +889,15 @@ __device__ __forceinline__ void bwd_dkv_body(
       const int I0 = ent_cur & kInvBlockMask;
       const bool win0 = 0 < n_st;
       sg.stage(q_lane, Qs0, I0);
-      sg.stage(win0 ? gs_lane : gl_lane, Gs0, I0);
+      sg.stage(g_lane, Gs0, I0);
       const uint4 r0 = row_consts(I0, win0);
+      gate_products();
       scale_frags(p.scale * kLog2e, kf);
-      if (tid < BLK) rc_s[0][tid] = r0;
+      if (tid < BLK) rc0[tid] = r0;
     }
     __syncthreads();
-    auto step = [&](int t, uint16_t *q_fill, uint16_t *g_fill, const uint16_t *q_cur, const uint16_t *g_cur,
-                    int par) __attribute__((always_inline)) {
+    auto step = [&](int t, uint16_t *q_fill, uint16_t *g_fill, const uint16_t *q_cur, uint16_t *g_cur,
+                    const uint4 *rc_cur, uint4 *rc_fill) __attribute__((always_inline)) {
       uint4 rn = pad_consts;
       const bool more = t + 1 < n_all;
       const int ent_after = entry_of(min(t + 2, n_all - 1));  // consumed at the end of this step
@@ -844,80 +906,39 @@ __device__ __forceinline__ void bwd_dkv_body(
         const bool win_n = t + 1 < n_st;
         rn = row_consts(In, win_n);
         sg.stage(q_lane, q_fill, In);
-        sg.stage(win_n ? gs_lane : gl_lane, g_fill, In);
+        sg.stage(g_lane, g_fill, In);
       }
       const bool win = t < n_st;
-      tile_body(q_cur, g_cur, [&](int s) { return rc_s[par][32 * s + lq]; }, ent_cur & kInvBlockMask, win, few(ent_cur, win), [] {});
-      if (more && tid < BLK) rc_s[par ^ 1][tid] = rn;
+      if (t == n_st) to_long_term();
+      tile_body(q_cur, g_cur, rc_cur, ent_cur & kInvBlockMask, win, few(ent_cur, win), [] {});
+      if (more && tid < BLK) rc_fill[tid] = rn;
       ent_cur = ent_nxt;
       ent_nxt = ent_after;
       __syncthreads();
     };
     for (int t = 0; t < n_all; t += 2) {
-      step(t, Qs1, Gs1, Qs0, Gs0, 0);
-      if (t + 1 < n_all) step(t + 1, Qs0, Gs0, Qs1, Gs1, 1);
+      step(t, Qs1, Gs1, Qs0, Gs0, rc0, rc1);
+      if (t + 1 < n_all) step(t + 1, Qs0, Gs0, Qs1, Gs1, rc1, rc0);
     }
   }
 
-  // ---- residual passes over the query blocks with few-key rows ----
-  // There the probabilities are near one, dV holds single terms P*dO_x of full size and dS
-  // projections of dO_x that are small against its norm, so the bf16 rounding of dO_x itself
-  // would show.  Everything above is linear in dO_x: the tile is simply walked a second time
-  // with the residual dO_x - bf16(dO_x) in place of dO_x and residual.o_x in place of c_x.  The
-  // residual tile is rebuilt in LDS from dO, alpha, dz and the gate weights exactly as the
-  // per-row pass formed dO_x.  (Rare: the first blocks of a row, or top-k below three.)
-  auto residual_pass = [&](int Iq, bool windowed) __attribute__((always_inline)) {
-    sg.stage(q_lane, Qs0, Iq);
-    {
-      // thread -> (row, half of d): 32 residuals each, written as four swizzled 16-byte chunks
-      const int r = tid >> 1, hf = tid & 1;
-      const int i = Iq * BLK + r;
-      const bool in = i < p.L;
-      const uint16_t keep = in ? 0xFFFFu : 0u;
-      const size_t ro = head + (size_t)min(i, p.L - 1) * D + 32 * hf;
-      const float4 st = rowstat[lbase + min(i, p.L - 1)];
-      const float ax = windowed ? 1.0f - st.x : st.x;
-      const float *wrow = gate_w + (size_t)(bh % p.H) * 2 * D + (windowed ? D : 0) + 32 * hf;
-      const float *orow = (windowed ? o_st : o_lt) + ro;
-      float corr = 0.0f;
+  // ---- the rank-one terms of dV ----
+  if (n_all <= n_st) to_long_term();
+  const float r_lt = r_sum + __shfl_xor(r_sum, 32);
+  r_st += __shfl_xor(r_st, 32);
+  asm volatile("" : "+v"(dv[0]), "+v"(dv[1]), "+v"(dk[0]), "+v"(dk[1]));
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const uint4 raw = *reinterpret_cast<const uint4 *>(dO + ro + 8 * c);
-        const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
-        float gw[8], ox[8];  // (loaded whole: loads under a condition would be waited for one by one)
-        *reinterpret_cast<float4 *>(gw) = *reinterpret_cast<const float4 *>(wrow + 8 * c);
-        *reinterpret_cast<float4 *>(gw + 4) = *reinterpret_cast<const float4 *>(wrow + 8 * c + 4);
-        *reinterpret_cast<float4 *>(ox) = *reinterpret_cast<const float4 *>(orow + 8 * c);
-        *reinterpret_cast<float4 *>(ox + 4) = *reinterpret_cast<const float4 *>(orow + 8 * c + 4);
-        uint32_t out[4];
+  for (int mb = 0; mb < 2; ++mb) {
+    f32x16 more;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float g = (e & 1) ? bf_hi(w[e >> 1]) : bf_lo(w[e >> 1]);
-          const float full = fmaf(ax, g, st.y * gw[e]);
-          const uint16_t lo = f32_to_bf16(full - bf16_to_f32(f32_to_bf16(full))) & keep;
-          corr = fmaf(bf16_to_f32(lo), ox[e], corr);
-          if (e & 1) out[e >> 1] |= (uint32_t)lo << 16; else out[e >> 1] = lo;
-        }
-        const int chunk = (4 * hf + c) ^ swz(r);
-        *reinterpret_cast<uint4 *>(Gs0 + r * D + chunk * 8) = make_uint4(out[0], out[1], out[2], out[3]);
-      }
-      corr += __shfl_xor(corr, 1);
-      if (hf == 0) {
-        const uint4 base = in ? (windowed ? rowI_st : rowI_lt)[lbase + i] : pad_consts;
-        const uint2 k = split3(-corr);
-        rc_s[0][r] = make_uint4(base.x, base.y, k.x, k.y);
-      }
+    for (int g = 0; g < 4; ++g) {
+      float wl[4], ws[4];
+      load4(gate + 32 * mb + 8 * g + 4 * lh, wl);
+      load4(gate + D + 32 * mb + 8 * g + 4 * lh, ws);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) more[4 * g + e] = fmaf(wl[e], r_lt, ws[e] * r_st);
     }
-    __syncthreads();  // (waits for the staged Q rows of every wavefront as well)
-    tile_body(Qs0, Gs0, [&](int s) { return rc_s[0][32 * s + lq]; }, Iq, windowed, false, [] {});
-    __syncthreads();
-  };
-#pragma unroll 1
-  for (int t = 0; t < n_all; ++t) {
-    const bool win = t < n_st;
-    const int ent = __builtin_amdgcn_readfirstlane(entry_of(t));
-    if (few(ent, win)) residual_pass(ent & kInvBlockMask, win);
-    else if (win) t = n_st - 1;  // (in the window part such blocks are a prefix)
+    dv[mb] += more;
   }
 
   {  // (every wavefront is past the last barrier of the walk: the staging rows are free)
@@ -935,12 +956,12 @@ __device__ __forceinline__ void bwd_dkv_body(
 
 #define BWD_DQ_PARAMS                                                                                              \
   const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K, const uint16_t *__restrict__ V,                  \
-      const int *__restrict__ valid_len, const int *__restrict__ sel, const uint16_t *__restrict__ g_lt,           \
-      const uint16_t *__restrict__ g_st, const uint4 *__restrict__ rowI_lt, const uint4 *__restrict__ rowI_st,     \
-      const uint16_t *__restrict__ dO, const float4 *__restrict__ rowstat, const float *__restrict__ gate_w,       \
+      const int *__restrict__ valid_len, const int *__restrict__ sel, const uint4 *__restrict__ rowI_lt,           \
+      const uint4 *__restrict__ rowI_st, const uint16_t *__restrict__ dO, const float4 *__restrict__ rowstat,      \
+      const float *__restrict__ gate_w,                                                                            \
       const float *__restrict__ o_lt, const float *__restrict__ o_st, uint16_t *__restrict__ dQ
-#define BWD_DQ_ARGS Q, K, V, valid_len, sel, g_lt, g_st, rowI_lt, rowI_st, dO, rowstat, gate_w, o_lt, o_st, dQ
-#define BWD_DKV_ARGS Q, K, V, valid_len, g_lt, g_st, rowI_lt, rowI_st, offs, items, dO, rowstat, gate_w, o_lt, o_st, dK, dV
+#define BWD_DQ_ARGS Q, K, V, valid_len, sel, rowI_lt, rowI_st, dO, rowstat, gate_w, o_lt, o_st, dQ
+#define BWD_DKV_ARGS Q, K, V, valid_len, rowI_lt, rowI_st, offs, items, dO, gate_w, dK, dV
 
 template <int BLK, bool EQ15, bool SUB>
 __global__ __launch_bounds__(BLK * 2) __attribute__((amdgpu_waves_per_eu(2, 2))) void bwd_dq_mfma_kernel(BWD_DQ_PARAMS, KParams p)
@@ -952,15 +973,14 @@ __global__ __launch_bounds__(BLK * 2) __attribute__((amdgpu_waves_per_eu(2, 2)))
 template <int BLK, bool EQ15, bool SUB>
 __global__ __launch_bounds__(BLK * 2) __attribute__((amdgpu_waves_per_eu(2, 2))) void bwd_dkv_mfma_kernel(
     const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K, const uint16_t *__restrict__ V,
-    const int *__restrict__ valid_len, const uint16_t *__restrict__ g_lt, const uint16_t *__restrict__ g_st,
-    const uint4 *__restrict__ rowI_lt, const uint4 *__restrict__ rowI_st, const int *__restrict__ offs,
-    const int *__restrict__ items, const uint16_t *__restrict__ dO, const float4 *__restrict__ rowstat,
-    const float *__restrict__ gate_w, const float *__restrict__ o_lt, const float *__restrict__ o_st,
-    uint16_t *__restrict__ dK, uint16_t *__restrict__ dV, KParams p)
+    const int *__restrict__ valid_len, const uint4 *__restrict__ rowI_lt, const uint4 *__restrict__ rowI_st,
+    const int *__restrict__ offs, const int *__restrict__ items, const uint16_t *__restrict__ dO,
+    const float *__restrict__ gate_w, uint16_t *__restrict__ dK, uint16_t *__restrict__ dV, KParams p)
 {
   BWD_LDS_TILES(BLK);
-  __shared__ __attribute__((aligned(16))) uint4 rc_s[2][BLK];
-  bwd_dkv_body<BLK, EQ15, SUB>(BWD_DKV_ARGS, p, blockIdx.x, lds_t0, lds_t1, lds_t2, lds_t3, rc_s);
+  __shared__ __attribute__((aligned(1024))) uint4 lds_rc0[64];
+  __shared__ __attribute__((aligned(1024))) uint4 lds_rc1[64];
+  bwd_dkv_body<BLK, EQ15, SUB>(BWD_DKV_ARGS, p, blockIdx.x, lds_t0, lds_t1, lds_t2, lds_t3, lds_rc0, lds_rc1);
 }
 
 // workgroups that sum the partial gate gradients: kGateCols columns of a head each
@@ -979,7 +999,8 @@ inline unsigned gate_workgroups(const KParams &p) { return ((unsigned)(p.H * gat
 // load's latency under load, and LDS holds two tiles for each of the eight wavefronts of a CU.  So a tile is read to
 // registers whole (the transposed operands too), and its buffer is refilled with the tile after next at once: a load
 // has nearly two bodies to arrive.  The loop issues the same loads on every path and has one exit (an odd last tile is
-// a step of its own), so that the compiler's waits before the LDS reads count exactly past the younger loads.
+// a step of its own), so that a wait at the head of a step counts exactly past the younger loads: a wait of the kernel's own, for
+// the compiler does not reliably put one between loads to LDS and the reads of it.
 // B=128 H=4 L=1024 k=8 w=64, lengths U[100,1024]: 230 -> 202 us; B=32 H=8 L=1997, all of Eq. 15: 267 -> 239 us.
 template <int BLK, bool EQ15, bool SUB>
 __global__ __launch_bounds__(BLK * 2) __attribute__((amdgpu_waves_per_eu(2, 2))) void bwd_both_mfma_kernel(
@@ -988,7 +1009,8 @@ __global__ __launch_bounds__(BLK * 2) __attribute__((amdgpu_waves_per_eu(2, 2)))
     unsigned gate_wgs, KParams p)
 {
   BWD_LDS_TILES(BLK);  // the four staging tiles serve either role
-  __shared__ __attribute__((aligned(16))) uint4 rc_s[2][BLK];
+  __shared__ __attribute__((aligned(1024))) uint4 lds_rc0[64];
+  __shared__ __attribute__((aligned(1024))) uint4 lds_rc1[64];
   if (BLK == 32 && blockIdx.x < gate_wgs) {
     const int groups = gate_groups(p), h = blockIdx.x / groups;
     if (h < p.H)
@@ -997,7 +1019,7 @@ __global__ __launch_bounds__(BLK * 2) __attribute__((amdgpu_waves_per_eu(2, 2)))
     return;
   }
   const unsigned n = (unsigned)(p.B * p.H * p.NB), id = blockIdx.x - gate_wgs;
-  if (id < n) bwd_dkv_body<BLK, EQ15, SUB>(BWD_DKV_ARGS, p, id, lds_t0, lds_t1, lds_t2, lds_t3, rc_s);
+  if (id < n) bwd_dkv_body<BLK, EQ15, SUB>(BWD_DKV_ARGS, p, id, lds_t0, lds_t1, lds_t2, lds_t3, lds_rc0, lds_rc1);
   else bwd_dq_body<BLK, EQ15, SUB>(BWD_DQ_ARGS, p, id - n, lds_t0, lds_t1, lds_t2, lds_t3);
 }
 
@@ -1020,13 +1042,12 @@ void launch_bwd_mfma(const KParams &p, const BwdArgs &a, const BwdWorkspace &w, 
   auto u16 = [](const void *x) { return reinterpret_cast<const uint16_t *>(x); };
   auto go_dq = [&](auto kernel, unsigned threads) {
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, st, u16(a.Q), u16(a.K), u16(a.V), a.valid_len, a.sel,
-                       w.g_lt, w.g_st, w.rowI_lt, w.rowI_st, u16(a.dO), w.rowstat, a.gate_w, (const float *)a.o_lt,
+                       w.rowI_lt, w.rowI_st, u16(a.dO), w.rowstat, a.gate_w, (const float *)a.o_lt,
                        (const float *)a.o_st, (uint16_t *)a.dQ, p);
   };
   auto go_dkv = [&](auto kernel, unsigned threads) {
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, st, u16(a.Q), u16(a.K), u16(a.V), a.valid_len, w.g_lt,
-                       w.g_st, w.rowI_lt, w.rowI_st, w.offs, w.items, u16(a.dO), w.rowstat, a.gate_w,
-                       (const float *)a.o_lt, (const float *)a.o_st, (uint16_t *)a.dK, (uint16_t *)a.dV, p);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, st, u16(a.Q), u16(a.K), u16(a.V), a.valid_len, w.rowI_lt,
+                       w.rowI_st, w.offs, w.items, u16(a.dO), a.gate_w, (uint16_t *)a.dK, (uint16_t *)a.dV, p);
   };
   const bool eq15 = p.sblk != 0;
   const bool sub = eq15 && p.sblk < p.b;  // mask block smaller than the tile
@@ -1034,7 +1055,7 @@ void launch_bwd_mfma(const KParams &p, const BwdArgs &a, const BwdWorkspace &w, 
     const unsigned gate_wgs = bwd_mfma_takes_gate(p, stages) ? gate_workgroups(p) : 0u;
     auto go = [&](auto kernel, unsigned threads) {
       hipLaunchKernelGGL(kernel, dim3(2 * grid + gate_wgs), dim3(threads), 0, st, u16(a.Q), u16(a.K), u16(a.V), a.valid_len, a.sel,
-                         w.g_lt, w.g_st, w.rowI_lt, w.rowI_st, u16(a.dO), w.rowstat, a.gate_w, (const float *)a.o_lt,
+                         w.rowI_lt, w.rowI_st, u16(a.dO), w.rowstat, a.gate_w, (const float *)a.o_lt,
                          (const float *)a.o_st, (uint16_t *)a.dQ, w.offs, w.items, (uint16_t *)a.dK, (uint16_t *)a.dV, w.partial, a.d_gate_w, a.d_gate_b,
                          w.nchunk, gate_wgs, p);
     };

@@ -130,5 +130,14 @@ __device__ __forceinline__ uint2 split3(float x)
 }
 __device__ __forceinline__ float unsplit3(uint32_t x, uint32_t y) { return (bf_lo(x) + bf_hi(x)) + bf_lo(y); }
 
+// x as hi + lo with bf16 terms, packed hi | lo << 16
+__device__ __forceinline__ uint32_t split2(float x)
+{
+  const uint16_t hi = __builtin_bit_cast(uint16_t, (__bf16)x);
+  const uint16_t lo = __builtin_bit_cast(uint16_t, (__bf16)(x - bf16_to_f32(hi)));
+  return (uint32_t)hi | ((uint32_t)lo << 16);
+}
+__device__ __forceinline__ float unsplit2(uint32_t x) { return bf_lo(x) + bf_hi(x); }
+
 }  // namespace mfma
 }  // namespace blossom

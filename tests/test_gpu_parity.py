@@ -228,6 +228,21 @@ def test_a_hole_in_front_of_the_own_block(b):
     run_case(w, x=x, backward=True, gate_scale=0.4, sel_edit=shift)
 
 
+@pytest.mark.parametrize("b", [32, 64])
+def test_a_gate_that_shuts_a_branch(b):
+    # one head's gate closes the long-term branch, the other's the short-term one (a weight of zero, whose logarithm goes into no
+    # exponent); dO in the padding of a partly valid block is the largest there is, and its products overflow
+    L = 4 * b + 9
+    w = with_shape(WORKLOADS["cfg4"], name=f"shut-{b}", B=2, H=2, L=L, block=b, topk=2, window=b + 3, len_lo=1, len_hi=L, backward=False,
+                   seed=670 + b)
+    x = make_inputs(w, want_dO=True)
+    x.valid_len[:] = [L - b // 2, b + 5]
+    x.gate_b[:] = [-200.0, 200.0]
+    for r in range(w.B):
+        x.dO[r, :, : L - int(x.valid_len[r])] = torch.finfo(torch.bfloat16).max
+    run_case(w, x=x, backward=True, pairs=range(4))  # (all of them; the gate's own gradients are zero in fp32, e^-200 in exact arithmetic)
+
+
 @pytest.mark.parametrize("b,topk,window", [(64, 1, 5), (64, 2, 40), (32, 1, 200), (32, 2, 7), (64, 3, 20)])
 def test_matrix_core_few_key_rows(b, topk, window):
     # bf16 d=64 (the matrix-core kernels) where rows see only a few keys far beyond the first blocks:
