@@ -594,60 +594,74 @@ __global__ __launch_bounds__(256) void score_topk_kernel(const float *__restrict
     pick_by_rows<D>(q_s, k_s, out, I0, I1, p0, p);
 }
 
-// More than 128 blocks: one wavefront per (row, head, query block), lane-strided candidates, keys (the image above
+// More than 128 blocks: a workgroup per (row, head, query block), thread-strided candidates, keys (the image above
 // NB-1-J: unique, one unsigned comparison) in LDS.  A candidate is selected iff fewer than `take` candidates beat it;
 // ballots and prefix popcounts emit the list in ascending order.
+// Latency is the bound, so a candidate has a thread of its own, 32 of its channels are requested before the first is used, and the
+// ranks are counted without a wait.  Selection at d=64 b=32 L=8192, 256 blocks, with a wavefront per row, the same with these requests,
+// and with these threads, us: the last block alone at B=16 H=8 84 / 54 / 39, at B=1 H=8 59 / 27 / 12; every block at B=1 H=8
+// 61 / 32 / 26, B=4 92 / 87 / 54, B=16 204 / 191 / 182.
 template <int D>
-__global__ __launch_bounds__(64) void score_topk_many_kernel(const float *__restrict__ qsum,
-                                                             const float *__restrict__ kmeanT,
-                                                             const int *__restrict__ valid_len,
-                                                             int *__restrict__ sel, KParams p)
+__global__ __launch_bounds__(1024) void score_topk_many_kernel(const float *__restrict__ qsum,
+                                                               const float *__restrict__ kmeanT,
+                                                               const int *__restrict__ valid_len,
+                                                               int *__restrict__ sel, KParams p)
 {
-  __shared__ float qs[D];
+  __shared__ __attribute__((aligned(16))) float qs[D];
+  __shared__ unsigned long long chosen_s[64];   // per 64 candidates (NB <= 4096)
   extern __shared__ unsigned long long key_s[];  // NB keys (sized at launch: a static worst-case array would cap the occupancy)
-  const int lane = threadIdx.x;
+  const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63;
   const int I = p.NB - p.nq + (int)(blockIdx.x % p.nq);
   const int bh = blockIdx.x / p.nq;
   const int p0 = p.L - clamp_len(valid_len[bh / p.H], p.L);
   int *out = sel + ((size_t)bh * p.NB + I) * p.k;
   const Candidates cd = candidates(p, p0, I);
   if (!cd.any) {
-    for (int e = lane; e < p.k; e += 64) out[e] = -1;
+    for (int e = tid; e < p.k; e += nt) out[e] = -1;
     return;
   }
-  for (int c = lane; c < D; c += 64) qs[c] = qsum[((size_t)bh * p.NB + I) * D + c];
+  for (int c = tid; c < D; c += nt) qs[c] = qsum[((size_t)bh * p.NB + I) * D + c];
   __syncthreads();
   const float *km = kmeanT + (size_t)bh * D * p.NB;
-  for (int J = cd.J_first + lane; J < cd.J_end; J += 64) {
+  for (int J = cd.J_first + tid; J < cd.J_end; J += nt) {
+    constexpr int R = D < 32 ? D : 32;  // channels on their way at a time
+    const float *from = km + J;
     float acc = 0.0f;
-#pragma unroll 8
-    for (int c = 0; c < D; ++c) acc = __fmaf_rn(qs[c], km[(size_t)c * p.NB + J], acc);
+#pragma unroll 1
+    for (int c0 = 0; c0 < D; c0 += R) {
+      float v[R];
+#pragma unroll
+      for (int c = 0; c < R; ++c, from += p.NB) v[c] = *from;
+#pragma unroll
+      for (int c = 0; c < R; ++c) acc = __fmaf_rn(qs[c0 + c], v[c], acc);
+    }
     key_s[J] = J == I ? ~0ull : ((unsigned long long)score_image(acc) << 32) | (unsigned)(p.NB - 1 - J);
   }
   __syncthreads();
-  int base = 0;
-  for (int J0 = cd.J_first; J0 < cd.J_end; J0 += 64) {
+  auto below = [&](unsigned long long m) { return __popcll(m & ((1ull << lane) - 1ull)); };
+  for (int J0 = cd.J_first + (tid & ~63); J0 < cd.J_end; J0 += nt) {
     const int J = J0 + lane;
-    bool chosen = false;
+    int rank = cd.take;
     if (J < cd.J_end) {
       const unsigned long long mine = key_s[J];
-      int rank = 0;
+      rank = 0;
+#pragma unroll 8
       for (int Jo = cd.J_first; Jo < cd.J_end; ++Jo) rank += key_s[Jo] > mine ? 1 : 0;
-      chosen = rank < cd.take;
     }
-    const unsigned long long mask = __ballot(chosen);
-    if (chosen) {
-      const unsigned long long below = mask & ((1ull << lane) - 1ull);
-      out[base + __popcll(below)] = J;
-    }
-    base += __popcll(mask);
+    const unsigned long long mask = __ballot(rank < cd.take);
+    if (lane == 0) chosen_s[(J0 - cd.J_first) >> 6] = mask;
   }
-  // base == take here; causal form: the own block closes the list; the rest is padding
-  if (!p.bidir) {
-    if (lane == 0) out[base] = I;
-    ++base;
+  __syncthreads();
+  for (int J0 = cd.J_first + (tid & ~63); J0 < cd.J_end; J0 += nt) {
+    const int c = (J0 - cd.J_first) >> 6;
+    int base = 0;
+    for (int o = 0; o < c; ++o) base += __popcll(chosen_s[o]);
+    const unsigned long long mask = chosen_s[c];
+    if ((mask >> lane) & 1ull) out[base + below(mask)] = J0 + lane;
   }
-  for (int e = base + lane; e < p.k; e += 64) out[e] = -1;
+  // `take` are selected; causal form: the own block closes the list; the rest is padding
+  if (!p.bidir && tid == 0) out[cd.take] = I;
+  for (int e = cd.take + (p.bidir ? 0 : 1) + tid; e < p.k; e += nt) out[e] = -1;
 }
 
 // ---- launchers ----------------------------------------------------------------------------
@@ -692,7 +706,8 @@ static void launch_select_t(const KParams &p, const void *Q, const void *K, bool
                    valid_len, qsum, kmean, p);
   }
   if (p.NB > kRowBlocks) {
-    hipLaunchKernelGGL((score_topk_many_kernel<D>), dim3((unsigned)(p.B * p.H * p.nq)), dim3(64),
+    const int threads = std::min(1024, (p.NB + 63) / 64 * 64);
+    hipLaunchKernelGGL((score_topk_many_kernel<D>), dim3((unsigned)(p.B * p.H * p.nq)), dim3((unsigned)threads),
                        (size_t)p.NB * sizeof(unsigned long long), st, qsum, kmean, valid_len, sel, p);
     return;
   }
