@@ -372,19 +372,28 @@ __device__ __forceinline__ void inverse_list(const int *__restrict__ sel, const 
   const int per = (p.NB + W - 1) / W;
   const int I_lo = wv * per, I_hi = min(p.NB, I_lo + per);
   int *mine = cnt + wv * stride;
+  // entry e of each of the wavefront's rows in turn, eight rows on their way at a time (one load a row, waited for, before)
+  auto each_row = [&](int e, auto f) __attribute__((always_inline)) {
+    for (int I0 = I_lo; I0 < I_hi; I0 += 8) {
+      int J[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) J[i] = s[(size_t)min(I0 + i, I_hi - 1) * p.k + min(e, p.k - 1)];
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (I0 + i < I_hi) f(I0 + i, e < p.k ? J[i] : -1);
+    }
+  };
   for (int x = tid; x < W * stride; x += blockDim.x) cnt[x] = 0;
   for (int J = tid; J <= p.NB; J += blockDim.x) few[J] = 1;
   __syncthreads();
   for (int e0 = 0; e0 < p.k; e0 += 64) {
     const int e = e0 + lane;
-#pragma unroll 8
-    for (int I = I_lo; I < I_hi; ++I) {
-      const int J = e < p.k ? s[(size_t)I * p.k + e] : -1;
+    each_row(e, [&](int I, int J) __attribute__((always_inline)) {
       if (J >= 0 && J < p.NB && (J <= I || p.bidir)) atomicAdd(&mine[J], 1);
       // an earlier block with at least kInvFewKeys valid keys gives every row of I that many keys
       const int vcount = min((J + 1) * p.b, p.L) - max(J * p.b, p0);
       if (__ballot(J >= 0 && J < I && vcount >= kInvFewKeys) != 0ull && lane == 0) few[I] = 0;
-    }
+    });
   }
   __syncthreads();
   // exclusive scan over (key block, wavefront) in chunks of 64 key blocks; o[NB] receives the total
@@ -417,11 +426,9 @@ __device__ __forceinline__ void inverse_list(const int *__restrict__ sel, const 
   __syncthreads();
   for (int e0 = 0; e0 < p.k; e0 += 64) {
     const int e = e0 + lane;
-#pragma unroll 8
-    for (int I = I_lo; I < I_hi; ++I) {
-      const int J = e < p.k ? s[(size_t)I * p.k + e] : -1;
+    each_row(e, [&](int I, int J) __attribute__((always_inline)) {
       if (J >= 0 && J < p.NB && (J <= I || p.bidir)) it[atomicAdd(&mine[J], 1)] = I | ((int)few[I] << kInvFewShift);
-    }
+    });
   }
 }
 size_t inverse_list_lds(const KParams &p, int W) { return (size_t)W * (p.NB + 1) * sizeof(int) + (size_t)(p.NB + 1 + 3) / 4 * 4; }
@@ -445,12 +452,13 @@ __global__ __launch_bounds__(64 * kInvWaves) void inverse_list_kernel(const int 
 // each, for d = 64 twice 4: 8 lanes), the sums are DPP adds inside a row of 16 lanes instead of LDS permutes, and the
 // next rows are requested before the current ones are worked on.  B=128 H=4 L=1024 d=64, lengths U[100,1024]: 77 -> 71 us, 59 with the
 // heads to the XCDs in turn; B=16 H=8 L=8192: 183 -> 175 us (5.7 TB/s).  Since it writes no gradients of the branches for the
-// matrix-core kernels, 52 and 148 us (5.0 TB/s).
+// matrix-core kernels, 52 and 148 us; with chunks of 64 rows, whose last ones leave fewer CUs idle than those of 128, and the lists'
+// rows eight at a time, 48 and 142 (5.2 TB/s).
 // The gate-weight partials accumulate in registers and meet in LDS in a fixed order.
 // =============================================================================================
 // The first `lists` workgroups make the inverse selection lists instead: a chain of latencies (8 us at B=128 H=4 L=1024, 26 at B=16
 // H=8 L=8192 as a launch of its own) beside work that waits for memory.
-constexpr int kPrepRows = 128;
+constexpr int kPrepRows = 64;
 constexpr size_t kPrepListLds = 8320;  // LDS that every head size has for them: up to 488 blocks
 
 // four consecutive elements as loaded, and as floats (zeros unless `keep`)
