@@ -10,8 +10,8 @@
 // (dO.v_j + y*u_j = D when P = 1) survives.  In dQ, where a lane keeps its row, the bracket dO + y_x*Wg_x is rounded to bf16 once and
 // its row constant c_x is taken with the same rounded values.  With two rounded gradients in memory and residual passes of dK/dV for
 // rows with few keys a training step at B=128 H=4 L=1024 k=8 w=64 in blocks of 32 took 352 us (the per-row pass 62, these kernels
-// 190) instead of 337 (52, 188), at B=32 H=8 L=1997 with all of Eq. 15 494 instead of 488, at B=16 H=8 L=8192 k=16 w=128 in
-// blocks of 64 the same 2045 (181 and 1206 instead of 148 and 1240: sixteen more additions a unit for the sums of P'*y); dK and
+// 190) instead of 327 (48, 185), at B=32 H=8 L=1997 with all of Eq. 15 494 instead of 478, at B=16 H=8 L=8192 k=16 w=128 in
+// blocks of 64 2000 instead of 1975 (181 and 1206 against 142 and 1230: sixteen more additions a unit for the sums of P'*y); dK and
 // dV came out with 5 % larger errors.
 //
 // Accumulators start at minus a per-row constant, so the MFMA result is directly what the next
@@ -326,7 +326,7 @@ __device__ __forceinline__ void bwd_dq_body(
   float w_lt[4][8], w_st[4][8];
   load_gate(gate, lh, w_lt);
   load_gate(gate + D, lh, w_st);
-  const float4 rs = rowstat[lrow];  // y_lt, y_st, -c_lt, -c_st
+  const float4 rs = rowstat[lrow];  // y_lt, y_st, -c_lt, -c_st; zeros in a pad row of a block with a valid one
   // per-row constants (pad rows carry an exponent of -1e30: every probability of the column is zero)
   const uint4 ri_st = rowI_st[lrow];
   const uint4 ri_lt = rowI_lt[lrow];
@@ -547,15 +547,18 @@ __device__ __forceinline__ void bwd_dq_body(
     __builtin_amdgcn_sched_barrier(0);
   }
   scale_frags(p.scale * kLog2e, qf);
-  // the brackets (zeros in a pad row: dO may hold anything there)
+  // the brackets; zeros in a pad row, where dO may hold anything and y is zero
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk)
+  for (int kk = 0; kk < 4; ++kk) {
+    uint4 raw = __builtin_bit_cast(uint4, gf[kk]);
+    raw = make_uint4(q_ok ? raw.x : 0u, q_ok ? raw.y : 0u, q_ok ? raw.z : 0u, q_ok ? raw.w : 0u);
+    const bf16x8 g8 = __builtin_bit_cast(bf16x8, raw);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const float g = (float)gf[kk][e];
-      gf_next[kk][e] = (__bf16)(q_ok ? fmaf(rs.x, w_lt[kk][e], g) : 0.0f);
-      gf[kk][e] = (__bf16)(q_ok ? fmaf(rs.y, w_st[kk][e], g) : 0.0f);
+      gf_next[kk][e] = (__bf16)fmaf(rs.x, w_lt[kk][e], (float)g8[e]);
+      gf[kk][e] = (__bf16)fmaf(rs.y, w_st[kk][e], (float)g8[e]);
     }
+  }
   set_init(ri_st.x, ri_st.y, c1_st);
   if constexpr (ONE) {
     int J_2 = list_entry(tile_of(min(2, n_all - 1)));
@@ -751,8 +754,7 @@ __device__ __forceinline__ void bwd_dkv_body(
         const int i_lo = Iq * BLK + 32 * s, i_hi = i_lo + 31, j0 = J * BLK + 32 * wv;
         if (i_hi < j0 || i_hi < p0 || j0 + 31 < p0 || (!EQ15 && windowed && i_lo > j0 + 31 + p.w - 1)) continue;
       }
-      uint4 rc = rcs[32 * s + lq];
-      if (ONE && Iq * BLK + lq >= p.L) rc = pad_consts;
+      const uint4 rc = rcs[32 * s + lq];
       const uint32_t y = rcs[32 * s + acc_row(lane)].w;
       bf16x8 gt[2][2], qt[2][2];  // dO^T and Q^T operands of the last products
       auto read_tr = [&]() __attribute__((always_inline)) {
@@ -850,7 +852,7 @@ __device__ __forceinline__ void bwd_dkv_body(
   int ent_cur = entry_of(0);
   int ent_nxt = entry_of(min(1, n_all - 1));
   if constexpr (ONE) {
-    // (the row constants go straight to LDS too, ten registers less; rows past the end are replaced when they are used)
+    // (the row constants go straight to LDS too, ten registers less; rows past the end take the last one's, and are masked)
     auto fill = [&](uint16_t *qs, uint16_t *gsm, uint4 *rc, int ent, bool win) __attribute__((always_inline)) {
       const int Iq = ent & kInvBlockMask;
       sg.stage(q_lane, qs, Iq);
@@ -926,19 +928,20 @@ __device__ __forceinline__ void bwd_dkv_body(
   if (n_all <= n_st) to_long_term();
   const float r_lt = r_sum + __shfl_xor(r_sum, 32);
   r_st += __shfl_xor(r_st, 32);
-  asm volatile("" : "+v"(dv[0]), "+v"(dv[1]), "+v"(dk[0]), "+v"(dk[1]));
+  // (As products of three-term splits, long-term in the lower half of the contraction, short-term in the upper one.  Two vector
+  // instructions for each element, the weights loaded in that layout, a select for each element of dQ's brackets and a test for
+  // each row constant were 6 % of the vector instructions at B=128 H=4 L=1024 k=8 w=64, and 333 instead of 327 us a training step.)
+  {
+    const uint2 r = split3(lh == 0 ? r_lt : r_st);
+    const uint32_t rh = r.x & 0xFFFFu, rm = r.x >> 16, rl = r.y;
+    const bf16x8 cols = __builtin_bit_cast(bf16x8, make_uint4(rh | rm << 16, rh | rm << 16, rl | rh << 16, 0u));
 #pragma unroll
-  for (int mb = 0; mb < 2; ++mb) {
-    f32x16 more;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      float wl[4], ws[4];
-      load4(gate + 32 * mb + 8 * g + 4 * lh, wl);
-      load4(gate + D + 32 * mb + 8 * g + 4 * lh, ws);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) more[4 * g + e] = fmaf(wl[e], r_lt, ws[e] * r_st);
+    for (int mb = 0; mb < 2; ++mb) {
+      const uint2 w = split3(gate[lh * D + 32 * mb + lq]);
+      const uint32_t wh = w.x & 0xFFFFu, wm = w.x >> 16, wl = w.y;
+      const bf16x8 rows = __builtin_bit_cast(bf16x8, make_uint4(wh | wh << 16, wm | wm << 16, wh | wl << 16, 0u));
+      dv[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rows, cols, dv[mb], 0, 0, 0);
     }
-    dv[mb] += more;
   }
 
   {  // (every wavefront is past the last barrier of the walk: the staging rows are free)
