@@ -75,6 +75,14 @@ __device__ __forceinline__ float from_f32<float>(float x) { return x; }
 template <>
 __device__ __forceinline__ bf16_t from_f32<bf16_t>(float x) { return bf16_t{f32_to_bf16(x)}; }
 
+// A load that the caches need not keep.
+template <typename V>
+__device__ __forceinline__ V load_once(const V *p)
+{
+  typedef unsigned words __attribute__((ext_vector_type(sizeof(V) / 4)));
+  return __builtin_bit_cast(V, __builtin_nontemporal_load(reinterpret_cast<const words *>(p)));
+}
+
 // Load 4 consecutive elements (16-byte aligned for fp32, 8-byte for bf16) as floats.
 __device__ __forceinline__ void load4(const float *p, float (&o)[4])
 {

@@ -459,6 +459,10 @@ __global__ __launch_bounds__(64 * kInvWaves) void inverse_list_kernel(const int 
 // The first `lists` workgroups make the inverse selection lists instead: a chain of latencies (8 us at B=128 H=4 L=1024, 26 at B=16
 // H=8 L=8192 as a launch of its own) beside work that waits for memory.
 constexpr int kPrepRows = 64;
+// Branch outputs from a quarter of the last-level cache on leave it to Q, K, V and dO, which the kernels that follow read: a training
+// step at B=32 H=8 L=700 d=64 b=32 113.5 -> 106.5 us, B=128 H=4 L=1024 324 -> 312.5, B=16 H=8 L=8192 1907 -> 1900; at B=16 H=8 L=500
+// (33 MB) 57.8 without and 58.4 with.
+constexpr size_t kStreamBytes = 64u << 20;
 constexpr size_t kPrepListLds = 8320;  // LDS that every head size has for them: up to 488 blocks
 
 // four consecutive elements as loaded, and as floats (zeros unless `keep`)
@@ -493,7 +497,8 @@ __device__ __forceinline__ float lanes_sum(float x)
   return x;
 }
 
-template <typename T, int D>
+// STREAM: the branch outputs, which nothing reads again, are read past the caches (see kStreamBytes).
+template <typename T, int D, bool STREAM>
 __global__ __launch_bounds__(256) void bwd_prep_kernel(const float *__restrict__ o_lt,
                                                        const float *__restrict__ o_st,
                                                        const T *__restrict__ dO,
@@ -555,8 +560,13 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(const float *__restrict__
 #pragma unroll
     for (int q = 0; q < NG; ++q) {
       r.g[q] = load_raw4(dO + ro + q * (D / 2));
-      r.ol[q] = load_raw4(o_lt + ro + q * (D / 2));
-      r.os[q] = load_raw4(o_st + ro + q * (D / 2));
+      if constexpr (STREAM) {
+        r.ol[q] = {load_once(reinterpret_cast<const uint4 *>(o_lt + ro + q * (D / 2)))};
+        r.os[q] = {load_once(reinterpret_cast<const uint4 *>(o_st + ro + q * (D / 2)))};
+      } else {
+        r.ol[q] = load_raw4(o_lt + ro + q * (D / 2));
+        r.os[q] = load_raw4(o_st + ro + q * (D / 2));
+      }
     }
     r.ll = r.ls = 0.0f;
     if (rowI_lt) {
@@ -1131,10 +1141,14 @@ static void launch_bwd_t(const KParams &p, int dtype, const BwdArgs &a, unsigned
                           (unsigned long long)BH * (w.nchunk + 1) <= 0x7FFFFFFFull;
   if (stages & kBwdStageGate) {
     const unsigned lists = with_lists ? BH : 0u;
-    BLOSSOM_LAUNCH((bwd_prep_kernel<T, D>), dim3(BH * w.nchunk + lists), dim3(256), 0, st,
-                       (const float *)a.o_lt, (const float *)a.o_st, (const T *)a.dO, a.valid_len, a.gate_w,
-                       a.gate_b, w.rowstat, w.partial, a.lse_lt, a.lse_st, w.rowI_lt, w.rowI_st, a.sel,
-                       w.offs, w.items, (int)lists, p);
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(BH * w.nchunk + lists), dim3(256), 0, st, (const float *)a.o_lt, (const float *)a.o_st,
+                         (const T *)a.dO, a.valid_len, a.gate_w, a.gate_b, w.rowstat, w.partial, a.lse_lt, a.lse_st, w.rowI_lt, w.rowI_st,
+                         a.sel, w.offs, w.items, (int)lists, p);
+    };
+    if ((size_t)BH * p.L * 2 * D * sizeof(float) >= kStreamBytes) go(bwd_prep_kernel<T, D, true>);
+    else go(bwd_prep_kernel<T, D, false>);
+    if (launch_failed()) return;
     if (!mfma || !bwd_mfma_takes_gate(p, stages)) launch_gate_reduce(p, a, w.partial, w.nchunk, st);
     if (launch_failed()) return;
   }
