@@ -60,7 +60,7 @@ __device__ __forceinline__ void pool_batches(const T *__restrict__ src, int lo, 
 // The same for a whole number of pairs of eight rows: the next eight are requested before the last eight are added, and no row
 // needs a test (pooling at B=16 H=8 L=8192 d=64 b=64: 55.6 -> 53.9 us, K alone 29.3 -> 27.8; where blocks of one wavefront
 // differ in their valid rows, as in the selection of a whole head, both forms would run: 24 -> 29 us at L=1024).
-template <typename T, int D, int EPT>
+template <bool STREAM, typename T, int D, int EPT>
 __device__ __forceinline__ void pool_rows(const T *__restrict__ src, int n, float (&a)[EPT])
 {
   using V = std::conditional_t<EPT * sizeof(T) == 16, uint4, uint2>;
@@ -68,7 +68,11 @@ __device__ __forceinline__ void pool_rows(const T *__restrict__ src, int n, floa
   V u[R], v[R];
   auto request = [&](V (&x)[R], int t) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < R; ++i) x[i] = *reinterpret_cast<const V *>(src + (size_t)(t + i) * D);
+    for (int i = 0; i < R; ++i) {
+      const V *row = reinterpret_cast<const V *>(src + (size_t)(t + i) * D);
+      if constexpr (STREAM) x[i] = load_once(row);
+      else x[i] = *row;
+    }
   };
   auto add = [&](const V (&x)[R]) __attribute__((always_inline)) {
 #pragma unroll
@@ -101,19 +105,23 @@ __device__ __forceinline__ void pool_block(const T *__restrict__ src, int lo, in
   else pool_batches<T, D, 8>(src, lo, hi, a);
 }
 
-// Where the mean of channel c of key block J of head bh goes: rows of d channels, or (more than kRowBlocks blocks) transposed.
+// Where the mean of channel c of key block J of head bh goes: rows of d channels, or transposed, for the scoring with a thread per
+// candidate: beyond kRowBlocks blocks, and for the last block alone beyond half of that (selection + forward at d=64 b=64 L=6000, us, with
+// rows and transposed: B=1 H=8 25.1 / 24.6, B=5 28.0 / 27.2, B=12 36.3 / 36.0; with 63 blocks, B=12 H=8 L=2000 b=32, 28.2 / 28.7).
 constexpr int kRowBlocks = 128;
+__host__ __device__ __forceinline__ bool means_in_rows(const KParams &p) { return p.NB <= (p.nq == 1 ? kRowBlocks / 2 : kRowBlocks); }
 template <int D>
-__device__ __forceinline__ size_t kmean_at(int bh, int J, int c, int NB)
+__device__ __forceinline__ size_t kmean_at(int bh, int J, int c, const KParams &p)
 {
-  return NB <= kRowBlocks ? ((size_t)bh * NB + J) * D + c : ((size_t)bh * D + c) * NB + J;
+  return means_in_rows(p) ? ((size_t)bh * p.NB + J) * D + c : ((size_t)bh * D + c) * p.NB + J;
 }
 
 // ---- pooling ------------------------------------------------------------------------------
 // One lane owns 16 bytes of channels of one block of one tensor.  qsum [B,H,NB,d] (unnormalised sums of Q), kmean: above.
 // KCMP: K holds compressed keys [B,H,NB,d] supplied by the caller (Eq. 9 with the caller's phi);
 // they are copied as they are instead of being pooled.
-template <typename T, int D, bool KCMP>
+// STREAM: whole blocks are read past the caches (see kStreamBytes).
+template <typename T, int D, bool KCMP, bool STREAM>
 __global__ __launch_bounds__(256) void pool_kernel(const T *__restrict__ Q, const T *__restrict__ K,
                                                    const int *__restrict__ valid_len,
                                                    float *__restrict__ qsum, float *__restrict__ kmean,
@@ -135,7 +143,7 @@ __global__ __launch_bounds__(256) void pool_kernel(const T *__restrict__ Q, cons
 #pragma unroll
     for (int e = 0; e < EPT; e += 4) load4(K + ((size_t)bh * p.NB + J) * D + c0 + e, reinterpret_cast<float(&)[4]>(a[e]));
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) kmean[kmean_at<D>(bh, J, c0 + e, p.NB)] = a[e];
+    for (int e = 0; e < EPT; ++e) kmean[kmean_at<D>(bh, J, c0 + e, p)] = a[e];
     return;
   }
   const int p0 = p.L - clamp_len(valid_len[bh / p.H], p.L);
@@ -147,7 +155,7 @@ __global__ __launch_bounds__(256) void pool_kernel(const T *__restrict__ Q, cons
   if (p.b >= 32 && __all(hi - lo == p.b || hi - lo <= p.b / 4) && hi - lo == p.b) {
 #pragma unroll
     for (int e = 0; e < EPT; ++e) a[e] = 0.0f;
-    pool_rows<T, D>(src + (size_t)lo * D, p.b, a);
+    pool_rows<STREAM, T, D>(src + (size_t)lo * D, p.b, a);
   } else {
     pool_block<T, D, EPT>(src, lo, hi, a);
   }
@@ -159,7 +167,7 @@ __global__ __launch_bounds__(256) void pool_kernel(const T *__restrict__ Q, cons
     const float fc = (float)(hi - lo);
 #pragma unroll
     for (int e = 0; e < EPT; ++e)
-      kmean[kmean_at<D>(bh, J, c0 + e, p.NB)] = hi > lo ? __fdiv_rn(a[e], fc) : 0.0f;
+      kmean[kmean_at<D>(bh, J, c0 + e, p)] = hi > lo ? __fdiv_rn(a[e], fc) : 0.0f;
   }
 }
 
@@ -240,7 +248,7 @@ __global__ __launch_bounds__(256) void rope_pool_kernel(const T *__restrict__ Q,
       qsum[((size_t)bh * p.NB + J) * D + c] = a;
     } else {
       const int cnt = hi - lo;
-      kmean[kmean_at<D>(bh, J, c, p.NB)] = cnt > 0 ? __fdiv_rn(a, (float)cnt) : 0.0f;
+      kmean[kmean_at<D>(bh, J, c, p)] = cnt > 0 ? __fdiv_rn(a, (float)cnt) : 0.0f;
     }
   }
 }
@@ -555,7 +563,7 @@ __global__ __launch_bounds__(1024) void select_head_kernel(const T *__restrict__
     pick_by_rows<D>(q_s, k_s, out, p.NB - p.nq, p.NB, p0, p);
 }
 
-// Scoring and top-k of pooled rows, up to 128 blocks: a workgroup per kScoreRows query blocks of a head (or per head,
+// Scoring and top-k of pooled rows, means in rows: a workgroup per kScoreRows query blocks of a head (or per head,
 // where the pairs do it), which holds the head's key means in LDS.
 constexpr int kScoreRows = 16;
 template <int D>
@@ -594,7 +602,7 @@ __global__ __launch_bounds__(256) void score_topk_kernel(const float *__restrict
     pick_by_rows<D>(q_s, k_s, out, I0, I1, p0, p);
 }
 
-// More than 128 blocks: a workgroup per (row, head, query block), thread-strided candidates, keys (the image above
+// Means stored transposed (means_in_rows): a workgroup per (row, head, query block), thread-strided candidates, keys (the image above
 // NB-1-J: unique, one unsigned comparison) in LDS.  A candidate is selected iff fewer than `take` candidates beat it;
 // ballots and prefix popcounts emit the list in ascending order.
 // Latency is the bound, so a candidate has a thread of its own, 32 of its channels are requested before the first is used, and the
@@ -677,6 +685,11 @@ static bool one_workgroup_per_head(const KParams &p, size_t elem)
   return p.NB <= kPairBlocks || (long)p.B * p.H >= kHeads;
 }
 
+// Keys of the last block's selection that half the last-level cache does not hold are read past the caches: nothing reads most of them
+// again, and pooling at B=16 H=8 L=8192 d=64 b=64 takes 24 instead of 27 us (select + forward 52.4 -> 49.5; b=32 61 -> 58.5).  Smaller ones
+// may be in the cache, from whoever made them (B=12 H=8 L=6000, 74 MB, 35.8 without and 36.6 with), and the keys of a whole
+// selection are read again by the forward (B=700 H=8 L=200 d=16 fp32, 143 MB, 111.7 and 115.0).
+constexpr size_t kStreamBytes = 128u << 20;
 template <typename T, int D>
 static void launch_select_t(const KParams &p, const void *Q, const void *K, bool kcmp, const int *valid_len,
                             int *sel, void *ws, void *Q_rot, void *K_rot, hipStream_t st)
@@ -695,17 +708,21 @@ static void launch_select_t(const KParams &p, const void *Q, const void *K, bool
   const int per_wg = 256 / (D / 4);
   const unsigned grid = (unsigned)((tasks + per_wg - 1) / per_wg);
   if (kcmp) {
-    BLOSSOM_LAUNCH((pool_kernel<T, D, true>), dim3(grid), dim3(256), 0, st, (const T *)Q, (const T *)K,
+    BLOSSOM_LAUNCH((pool_kernel<T, D, true, false>), dim3(grid), dim3(256), 0, st, (const T *)Q, (const T *)K,
                    valid_len, qsum, kmean, p);
   } else if (p.rope_cos) {
     const long rgrid = 2L * p.B * p.H * ((p.L + kRopeRows - 1) / kRopeRows);
     BLOSSOM_LAUNCH((rope_pool_kernel<T, D>), dim3((unsigned)rgrid), dim3(256), 0, st,
                    (const T *)Q, (const T *)K, valid_len, qsum, kmean, (T *)Q_rot, (T *)K_rot, p);
   } else {
-    BLOSSOM_LAUNCH((pool_kernel<T, D, false>), dim3(grid), dim3(256), 0, st, (const T *)Q, (const T *)K,
-                   valid_len, qsum, kmean, p);
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, st, (const T *)Q, (const T *)K, valid_len, qsum, kmean, p);
+    };
+    const bool stream = p.nq == 1 && (size_t)p.B * p.H * p.L * D * sizeof(T) >= kStreamBytes;
+    stream ? go(pool_kernel<T, D, false, true>) : go(pool_kernel<T, D, false, false>);
+    if (launch_failed()) return;
   }
-  if (p.NB > kRowBlocks) {
+  if (!means_in_rows(p)) {
     const int threads = std::min(1024, (p.NB + 63) / 64 * 64);
     hipLaunchKernelGGL((score_topk_many_kernel<D>), dim3((unsigned)(p.B * p.H * p.nq)), dim3((unsigned)threads),
                        (size_t)p.NB * sizeof(unsigned long long), st, qsum, kmean, valid_len, sel, p);

@@ -29,6 +29,8 @@ pytestmark = pytest.mark.gpu
     (50, 4, 1037, 16, 16, 7, "fp32", 0, False),   # ... six: the search
     (50, 4, 1037, 16, 16, 5, "bf16", 2, False),   # five in the bidirectional form
     (3, 2, 4128, 64, 32, 5, "bf16", 0, True),     # 129 blocks: a thread per candidate, for the last block ...
+    (3, 2, 2048, 64, 32, 5, "bf16", 0, True),     # 64 blocks, the last one alone: rows of means ...
+    (3, 2, 2049, 64, 32, 5, "bf16", 0, True),     # ... 65: a thread per candidate
     (3, 2, 3088, 16, 16, 200, "bf16", 2, False),  # ... and for every one, 193 of them, all taken
     (3, 2, 8243, 8, 8, 6, "fp32", 0, False),      # 1031 blocks: more than a workgroup has threads
 ])
