@@ -458,7 +458,8 @@ __global__ __launch_bounds__(64 * kInvWaves) void inverse_list_kernel(const int 
 // =============================================================================================
 // The first `lists` workgroups make the inverse selection lists instead: a chain of latencies (8 us at B=128 H=4 L=1024, 26 at B=16
 // H=8 L=8192 as a launch of its own) beside work that waits for memory.
-constexpr int kPrepRows = 64;
+// Rows of a chunk: as many as the workgroup takes in two steps (d >= 32) or in one.
+__host__ __device__ constexpr int prep_rows(int d) { return d == 8 ? 128 : 64; }
 // Branch outputs from a quarter of the last-level cache on leave it to Q, K, V and dO, which the kernels that follow read: a training
 // step at B=32 H=8 L=700 d=64 b=32 113.5 -> 106.5 us, B=128 H=4 L=1024 324 -> 312.5, B=16 H=8 L=8192 1907 -> 1900; at B=16 H=8 L=500
 // (33 MB) 57.8 without and 58.4 with.
@@ -529,7 +530,9 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(const float *__restrict__
   const int wave = t >> 6, lane = t & 63;
   const int sub = lane % LPR, rg = lane / LPR;
   const int c4 = sub * 4;
-  const int nchunk = (p.L + kPrepRows - 1) / kPrepRows;
+  constexpr int ROWS = prep_rows(D);
+  static_assert(ROWS % RPS == 0, "whole steps: a row must not be counted in two chunks");
+  const int nchunk = (p.L + ROWS - 1) / ROWS;
   // (chunk by chunk the workgroups would go to the XCDs in turn, and where there are eight chunks to a head, or a multiple, one XCD
   // would have the last, always valid ones to do and another nothing but padding)
   const unsigned vid = mfma::xcd_spread(blockIdx.x - lists, (gridDim.x - lists) / nchunk, nchunk);
@@ -542,7 +545,7 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(const float *__restrict__
   // written for them (pad rows of a partly valid block are staged with their tile and get zeros)
   const int first = (p0 / p.b) * p.b;
   float *out = partial + (size_t)vid * G;
-  if ((chunk + 1) * kPrepRows <= first) {
+  if ((chunk + 1) * ROWS <= first) {
     for (int c = t; c < G; c += 256) out[c] = 0.0f;
     return;
   }
@@ -553,7 +556,7 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(const float *__restrict__
     Raw4f ol[NG], os[NG];
     float ll, ls;
   };
-  const int row0 = chunk * kPrepRows + wave * RPW + rg;
+  const int row0 = chunk * ROWS + wave * RPW + rg;
   auto request = [&](int base, Rows &r) __attribute__((always_inline)) {
     const int i = min(max(row0 + base, p0), p.L - 1);
     const size_t ro = head + (size_t)i * D + c4, lr = (size_t)bh * p.L + i;
@@ -588,11 +591,11 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(const float *__restrict__
   for (int e = 0; e < CPL; ++e) acc_l[e] = acc_s[e] = 0.0f;
 
 #pragma unroll 1
-  for (int base = 0; base < kPrepRows; base += RPS) {
+  for (int base = 0; base < ROWS; base += RPS) {
     const int i = row0 + base;
     const bool valid = i < p.L && i >= p0;
     const bool inb = i < p.L && i >= first;
-    if (base + RPS < kPrepRows) request(base + RPS, nxt);
+    if (base + RPS < ROWS) request(base + RPS, nxt);
     float g[CPL], ol[CPL], os[CPL];
 #pragma unroll
     for (int q = 0; q < NG; ++q) {
@@ -1084,7 +1087,7 @@ BwdWorkspace bwd_carve(const KParams &p, int dtype, void *ws)
   BwdWorkspace w{};
   char *base = reinterpret_cast<char *>(ws);
   const size_t BH = (size_t)p.B * p.H;
-  w.nchunk = (p.L + kPrepRows - 1) / kPrepRows;
+  w.nchunk = (p.L + prep_rows(p.d) - 1) / prep_rows(p.d);
   size_t off = 0;
   w.rowstat = reinterpret_cast<float4 *>(base + off);
   off = align256(off + BH * p.L * sizeof(float4));
