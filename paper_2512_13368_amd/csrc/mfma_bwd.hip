@@ -231,18 +231,20 @@ constexpr int kLgkm0 = 15 | (7 << 4) | (3 << 14);      // every LDS and scalar-m
 
 constexpr int kFewKeys = 32;    // rows seeing fewer keys than this get two-term bf16 operands
 
-// Row constants (bwd_prep_kernel) as MFMA operands for the exponent and for the bracket, and what both meet: ones, and the lane's
-// u_j = Wg_x.v_j in three terms (the other half of the wavefront holds the slots 8..15).  Slots that are not used meet zeros, or are
-// zeros and meet something finite.
-__device__ __forceinline__ bf16x8 exponent_operand(const uint4 &r) { return __builtin_bit_cast(bf16x8, make_uint4(r.x, r.y, 0u, 0u)); }
-__device__ __forceinline__ bf16x8 bracket_operand(const uint4 &r) { return __builtin_bit_cast(bf16x8, make_uint4(r.z, r.y << 16, r.w, r.w)); }
-__device__ __forceinline__ bf16x8 column_terms(float u, int lh)
+// A row's constants (bwd_prep_kernel) are an MFMA operand as they are loaded, s0 s1 | D2 s2 | D0 D1 | y0 y1, in both halves of the
+// wavefront.  What they meet picks the exponent's constant, or -D and y times the lane's u_j = Wg_x.v_j (two terms, one in each half: as
+// exact as y).  Slots that are not meant meet zeros and have to be finite.
+__device__ __forceinline__ bf16x8 row_operand(const uint4 &r) { return __builtin_bit_cast(bf16x8, r); }
+__device__ __forceinline__ bf16x8 exponent_columns(int lh)
 {
   constexpr uint32_t one = 0x3F80u;
-  const uint2 t = split3(u);
-  const uint32_t hi = t.x & 0xFFFFu, mid = t.x >> 16, lo = t.y;
-  return __builtin_bit_cast(bf16x8, lh == 0 ? make_uint4(one | one << 16, one << 16, hi | hi << 16, mid | mid << 16)
-                                            : make_uint4(0u, 0u, lo | lo << 16, 0u));
+  return __builtin_bit_cast(bf16x8, lh == 0 ? make_uint4(one | one << 16, one << 16, 0u, 0u) : make_uint4(0u, 0u, 0u, 0u));
+}
+__device__ __forceinline__ bf16x8 bracket_columns(float u, int lh)
+{
+  constexpr uint32_t one = 0x3F80u;
+  const uint32_t t = split2(u), term = lh == 0 ? t & 0xFFFFu : t >> 16;
+  return __builtin_bit_cast(bf16x8, make_uint4(0u, lh == 0 ? one : 0u, lh == 0 ? one | one << 16 : 0u, term | term << 16));
 }
 
 // Where the sixteen rows of a lane's accumulator are found in its row of 16 lanes: lane l holds the value of tile row acc_row(l), and
@@ -708,6 +710,7 @@ __device__ __forceinline__ void bwd_dkv_body(
     return r;
   };
 
+  const bf16x8 s_terms = exponent_columns(lh);
   bf16x8 u_terms;                  // of the branch the walk is in, short-term first
   float u_lt;
   float r_sum = 0.0f, r_st = 0.0f;  // this lane's part of r_x, of the branch the walk is in and of the short-term one
@@ -722,10 +725,10 @@ __device__ __forceinline__ void bwd_dkv_body(
       return u + __shfl_xor(u, 32);
     };
     u_lt = product(gate);
-    u_terms = column_terms(product(gate + D), lh);
+    u_terms = bracket_columns(product(gate + D), lh);
   };
   auto to_long_term = [&]() __attribute__((always_inline)) {
-    u_terms = column_terms(u_lt, lh);
+    u_terms = bracket_columns(u_lt, lh);
     r_st = r_sum;
     r_sum = 0.0f;
   };
@@ -766,8 +769,8 @@ __device__ __forceinline__ void bwd_dkv_body(
             qt[t][mb] = lds_tr(qs, 2 * (32 * s + 16 * t) * D + ro.tr[mb], 2 * (32 * s + 16 * t) * D + ro.tr8[mb]);
           }
       };
-      f32x16 sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(exponent_operand(rc), u_terms, zero16, 0, 0, 0);
-      f32x16 gacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bracket_operand(rc), u_terms, zero16, 0, 0, 0);
+      f32x16 sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_operand(rc), s_terms, zero16, 0, 0, 0);
+      f32x16 gacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_operand(rc), u_terms, zero16, 0, 0, 0);
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
         sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_row(qs, 2 * 32 * s * D + ro.row[kk]), kf[kk], sacc, 0, 0, 0);
