@@ -2268,7 +2268,20 @@ int res_waves(int units) { return many_heads(units) ? 4 : 8; }
 // More than one head to a CU (with one the order is of no account), and not so many that they average out.  The forward, a third of
 // the backward's time, only where the order pays for itself: two heads to a CU of at least 128 positions, or several query heads a
 // workgroup (B=250 H=8 L=200 d=16 44.2 us in turn, 47.9 by length; B=128 H=4 L=60 d=32 9.9 and 11.3; per position B=500 80.0 and 73.6).
-bool order_by_length(const KParams &p, int units) { return units > kCUs && !many_heads(units) && p.B <= kOrderRows; }
+// Short heads end before the order is found, and the more heads a CU takes one after another the more often it is found and the less
+// it gives, so both of them bound the length from which it is used (a training step, order found in the backward / heads in turn, us:
+// d=16 units 400 L=60 32.0 / 30.7, L=100 39.0 / 38.6, L=140 43.7 / 44.1, L=200 51.4 / 56.4; units 1200 L=60 57.3 / 53.6, L=100 69.8 / 66.1,
+// L=140 77.8 / 76.3, L=200 95.9 / 98.3.  d=32 units 512 L=60 41.5 / 41.4, L=100 52.7 / 55.5; units 1500 L=100 95.8 / 91.2, L=140
+// 108.9 / 109.1.  Per position, in both passes, units 400 L=40 46.7 / 43.8, L=70 55.5 / 54.0, L=100 63.9 / 66.0, L=200 99.1 / 123.1;
+// units 1800 L=100 159.8 / 151.3, L=140 186.5 / 187.8, L=200 250 / 276).
+int shortest_ordered(const KParams &p, int units, bool perpos)
+{
+  return perpos ? 68 + units / 20 : p.d == 32 ? 16 + units / 10 : 96 + units / 14;
+}
+bool order_by_length(const KParams &p, int units, bool perpos)
+{
+  return units > kCUs && !many_heads(units) && p.B <= kOrderRows && p.L >= shortest_ordered(p, units, perpos);
+}
 SmallPlan stream_plan(const KParams &p, int units, size_t words_per_wave)
 {
   const int NT = (p.L + kTile - 1) / kTile;
@@ -2389,7 +2402,7 @@ static void launch_fwd_small_t(const KParams &p, const FwdArgs &a, hipStream_t s
       hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * pl.waves), pl.lds, st, (const T *)a.Q, (const T *)a.K,
                          (const T *)a.V, a.valid_len, a.dense ? nullptr : a.sel, a.gate_w, a.gate_b, (T *)a.O,
                          (float *)a.o_lt, (float *)a.o_st, a.lse_lt, a.lse_st, hpg, pl.parts,
-                         (int)(pl.res && order_by_length(p, grid) && (perpos || (grid <= 2 * kCUs && p.L >= 128))), p);
+                         (int)(pl.res && order_by_length(p, grid, perpos) && (perpos || (grid <= 2 * kCUs && p.L >= 128))), p);
     };
     if (perpos) pl.res ? go(fwd_small_kernel<T, D, BK, true, true>) : go(fwd_small_kernel<T, D, BK, true, false>);
     else pl.res ? go(fwd_small_kernel<T, D, BK, false, true>) : go(fwd_small_kernel<T, D, BK, false, false>);
@@ -2419,7 +2432,7 @@ static void launch_bwd_small_t(const KParams &p, const BwdArgs &a, const SmallWs
                            (const float *)a.o_st, a.lse_lt, a.lse_st, (const T *)a.dO, (T *)a.dQ, (T *)a.dK, (T *)a.dV, w.partial,
                            hpg, (int)pl.overlay, stages, p);
       };
-      if (order_by_length(p, p.B * p.H / hpg)) perpos ? go(bwd_res_kernel<T, D, BK, true, true>) : go(bwd_res_kernel<T, D, BK, false, true>);
+      if (order_by_length(p, p.B * p.H / hpg, perpos)) perpos ? go(bwd_res_kernel<T, D, BK, true, true>) : go(bwd_res_kernel<T, D, BK, false, true>);
       else perpos ? go(bwd_res_kernel<T, D, BK, true, false>) : go(bwd_res_kernel<T, D, BK, false, false>);
       return;
     }

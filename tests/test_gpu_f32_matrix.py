@@ -34,12 +34,13 @@ def test_short_sequences_forward_backward(b, L, topk, window):
 
 @pytest.mark.parametrize("Bn,H", [(130, 2), (64, 8), (171, 3), (512, 2), (513, 2)])
 def test_heads_taken_by_length(Bn, H):
-    # more heads than CUs: one turn and a bit, two whole turns, two and a bit, as many rows as are ordered, one more
-    w = with_shape(WORKLOADS["cfg2"], name=f"f32mc-order-B{Bn}-H{H}", B=Bn, H=H, L=130, d=8, block=16, topk=2, window=4, len_lo=1,
-                   len_hi=130, seed=960 + Bn)
+    # more heads than CUs: one turn and a bit, two whole turns, two and a bit, as many rows as are ordered, one more (L: from where
+    # the order is used at all of them)
+    w = with_shape(WORKLOADS["cfg2"], name=f"f32mc-order-B{Bn}-H{H}", B=Bn, H=H, L=210, d=8, block=16, topk=2, window=4, len_lo=1,
+                   len_hi=210, seed=960 + Bn)
     x = make_inputs(w, want_dO=True)
     x.valid_len[1::3] = x.valid_len[1]                                  # lengths that many rows share
-    x.valid_len[[0, 2, 5, Bn - 1]] = [130, 0, 131, -3]                  # longest, empty, past either end
+    x.valid_len[[0, 2, 5, Bn - 1]] = [210, 0, 211, -3]                  # longest, empty, past either end
     run_case(w, x=x, backward=True, gate_scale=0.4)
 
 
