@@ -429,8 +429,8 @@ __device__ __forceinline__ void bwd_dq_body(
   };
 
   // a raw tile-list value when it is consumed (a whole tile after its scalar load was issued): entries
-  // outside [0, NB) become -1, a tile whose keys are all masked
-  auto list_entry = [&](int raw) -> int { return (unsigned)raw < (unsigned)p.NB ? raw : -1; };
+  // outside [0, NB) and blocks after the query block become -1, a tile whose keys are all masked
+  auto list_entry = [&](int raw) -> int { return (unsigned)raw <= (unsigned)I ? raw : -1; };
 
   Stager<BLK> sg;
   sg.init(wv, lane, p.L, p.NB);

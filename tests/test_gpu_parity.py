@@ -228,6 +228,35 @@ def test_a_hole_in_front_of_the_own_block(b):
     run_case(w, x=x, backward=True, gate_scale=0.4, sel_edit=shift)
 
 
+@pytest.mark.parametrize("name,shape", [
+    ("cfg1", dict(topk=4)),                                                                    # fp32 matrix instructions, fp32
+    ("cfg2", dict(B=3, dtype="bf16", qkv_scaled=True)),                                        # fp32 matrix instructions, bf16
+    ("cfg1", dict(topk=4, d=64)),                                                              # scalar kernels
+    ("cfg3", dict(B=3, L=32 * 9 + 11, len_lo=40, len_hi=32 * 9 + 11, topk=5)),                 # matrix cores, b = 32
+    ("cfg3", dict(B=3, L=32 * 9, len_lo=40, len_hi=32 * 9, topk=5, stis_block=32)),            # ... with all of Eq. 15
+    ("cfg4", dict(B=3, H=2, L=64 * 7 + 20, len_lo=200, len_hi=64 * 7 + 20, topk=6)),           # matrix cores, b = 64
+    ("cfg4", dict(B=3, H=2, L=64 * 7, len_lo=200, len_hi=64 * 7, topk=6, stis_block=1)),       # ... with all of Eq. 15
+])
+def test_selection_rows_that_name_later_blocks(name, shape):
+    # caller-built rows list blocks after the query block: they contribute nothing, in forward and backward alike
+    w = with_shape(WORKLOADS[name], name=name + "-later", **shape)
+
+    def later(sel):
+        NB = sel.shape[2]
+        for I in range(NB):
+            for r in range(sel.shape[0]):
+                for h in range(sel.shape[1]):
+                    row = sel[r, h, I]
+                    others = [e for e in range(w.topk) if row[e] != I]
+                    if (row == I).any():
+                        for e, J in zip(others[(I + r) % 2:], dict.fromkeys([min(I + 1, NB - 1), NB - 1])):
+                            if J > I:
+                                row[e] = J
+        return sel
+
+    run_case(w, backward=True, gate_scale=0.4, sel_edit=later)
+
+
 @pytest.mark.parametrize("b", [32, 64])
 def test_a_gate_that_shuts_a_branch(b):
     # one head's gate closes the long-term branch, the other's the short-term one (a weight of zero, whose logarithm goes into no
