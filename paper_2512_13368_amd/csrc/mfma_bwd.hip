@@ -98,7 +98,6 @@ struct Stager {
     if constexpr (BLK == 32) {
       // (no branch for the last, partial block: its rows past the end are clamped, always masked; a buffer load, for the
       // compiler counts the global one as a flat access, before which it waits for everything: see REFILL)
-      blk = max(blk, 0);  // (block -1: a skipped list entry, every key masked)
       const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(src_head), 0, L * (D * 2), 0x00020000);
       const int row_max = L - 1 - blk * BLK;
 #pragma unroll
@@ -108,7 +107,7 @@ struct Stager {
       }
       return;
     }
-    const char *src = reinterpret_cast<const char *>(src_head) + (size_t)max(blk, 0) * (TILE * 2);  // uniform (block -1: a skipped list entry, every key masked)
+    const char *src = reinterpret_cast<const char *>(src_head) + (size_t)max(blk, 0) * (TILE * 2);  // uniform (block -1: a skipped list entry, not read)
     lds_void *dst = (lds_void *)(dst_tile + 32 * wv * D);
     if (!ragged || blk != NB - 1) {
       __builtin_amdgcn_global_load_lds((glb_void *)(src + lane_off), dst, 16, 0, 0);
@@ -429,14 +428,20 @@ __device__ __forceinline__ void bwd_dq_body(
   };
 
   // a raw tile-list value when it is consumed (a whole tile after its scalar load was issued): entries
-  // outside [0, NB) and blocks after the query block become -1, a tile whose keys are all masked
-  auto list_entry = [&](int raw) -> int { return (unsigned)raw <= (unsigned)I ? raw : -1; };
+  // outside [0, NB), blocks after the query block and blocks of nothing but padding, whose values may be anything, become -1, a
+  // tile whose keys are all masked and which holds the rows of the own block
+  auto list_entry = [&](int raw) -> int { return (unsigned)(raw - J_first) <= (unsigned)(I - J_first) ? raw : -1; };
 
   Stager<BLK> sg;
   sg.init(wv, lane, p.L, p.NB);
   const uint16_t *k_lane = K + head;  // (row, head) slices; the stager adds block and lane offsets
   const uint16_t *v_lane = V + head;
   ReadOffsets ro = read_offsets(lane);
+  auto stage_tile = [&](uint16_t *ks, uint16_t *vs, int J) __attribute__((always_inline)) {
+    if (ONE) J = J < 0 ? I : J;
+    sg.stage(k_lane, ks, J);
+    sg.stage(v_lane, vs, J);
+  };
 
   // (refill: called once the tile has been read to registers, ONE only)
   auto tile_body = [&](const uint16_t *ks, const uint16_t *vs, int J, bool short_term, auto refill) __attribute__((always_inline)) {
@@ -540,12 +545,10 @@ __device__ __forceinline__ void bwd_dq_body(
   };
   int J_cur = list_entry(tile_of(0));
   int J_nxt = list_entry(tile_of(min(1, n_all - 1)));
-  sg.stage(k_lane, Ks0, J_cur);
-  sg.stage(v_lane, Vs0, J_cur);
+  stage_tile(Ks0, Vs0, J_cur);
   if constexpr (ONE) {
     __builtin_amdgcn_sched_barrier(0);  // (the first tile's loads stay the older ones: what the loop's waits count on)
-    sg.stage(k_lane, Ks1, J_nxt);
-    sg.stage(v_lane, Vs1, J_nxt);
+    stage_tile(Ks1, Vs1, J_nxt);
     __builtin_amdgcn_sched_barrier(0);
   }
   scale_frags(p.scale * kLog2e, qf);
@@ -568,10 +571,7 @@ __device__ __forceinline__ void bwd_dq_body(
       const int J_after = tile_of(min(t + 3, n_all - 1));  // consumed at the end of this step
       if (t == n_st) to_long_term();
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(8));  // the tile is there; the next one's eight loads may be on their way
-      tile_body(ks, vs, J_cur, t < n_st, [&]() __attribute__((always_inline)) {
-        sg.stage(k_lane, ks, J_2);
-        sg.stage(v_lane, vs, J_2);
-      });
+      tile_body(ks, vs, J_cur, t < n_st, [&]() __attribute__((always_inline)) { stage_tile(ks, vs, J_2); });
       J_cur = J_nxt;
       J_nxt = J_2;
       J_2 = list_entry(J_after);
@@ -588,10 +588,7 @@ __device__ __forceinline__ void bwd_dq_body(
     auto step = [&](int t, uint16_t *k_fill, uint16_t *v_fill, const uint16_t *k_cur, const uint16_t *v_cur)
                     __attribute__((always_inline)) {
       const int J_after = tile_of(min(t + 2, n_all - 1));  // consumed at the end of this step
-      if (t + 1 < n_all) {
-        sg.stage(k_lane, k_fill, J_nxt);
-        sg.stage(v_lane, v_fill, J_nxt);
-      }
+      if (t + 1 < n_all) stage_tile(k_fill, v_fill, J_nxt);
       if (t == n_st) to_long_term();
       tile_body(k_cur, v_cur, J_cur, t < n_st, [] {});
       J_cur = J_nxt;

@@ -90,7 +90,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
   auto ld_offset = [&](int l) { return (unsigned)((l >> 3) * D + ((l & 7) ^ swz(l >> 3)) * 8) * 2u; };  // bytes; odd 8-row slices: ^ 32
   auto stage = [&](const char *src_head, uint16_t *dst_tile, int J) __attribute__((always_inline)) {
     const unsigned ld_lane = ld_offset(fresh_lane());
-    J = max(J, 0);  // (block -1: any block will do, it is skipped)
+    J = J < 0 ? I : J;  // (block -1, whose exponentials are all masked: values that are certainly finite)
     const char *src = src_head + (size_t)J * (TILE * 2);  // uniform
     lds_void *dst = (lds_void *)dst_tile;
     if (J != J_rag) {
@@ -227,11 +227,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     while (e < n_lt && !dense && __ballot(at == e) != 0ull) ++e;
     return e;
   };
-  // its block; entries outside [0, NB) become -1, a tile that is skipped
+  // its block; entries outside [0, NB) and blocks of nothing but padding, whose values may be anything, become -1, a tile that is skipped
   auto list_block = [&](int e) -> int {
     typedef const int __attribute__((address_space(4))) *const_int_ptr;  // read-only: loads become scalar
     const int J = __builtin_amdgcn_readfirstlane(dense ? J_first + e : ((const_int_ptr)my_sel)[e]);
-    return (unsigned)J < (unsigned)p.NB ? J : -1;
+    return J >= J_first && J < p.NB ? J : -1;
   };
   struct Place {  // what is still to be walked
     unsigned long long both, only;

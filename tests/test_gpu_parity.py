@@ -257,6 +257,32 @@ def test_selection_rows_that_name_later_blocks(name, shape):
     run_case(w, backward=True, gate_scale=0.4, sel_edit=later)
 
 
+@pytest.mark.parametrize("b,stis_block,topk", [(32, 0, 3), (32, 32, 3), (32, 8, 2), (64, 0, 3), (64, 64, 3), (64, 1, 2)])
+def test_blocks_of_padding_may_hold_anything(b, stis_block, topk):
+    # the matrix-core kernels, which multiply whole blocks: those of nothing but padding hold NaN, also where a caller-built row names
+    # one of them, or an entry that is no block
+    L = 6 * b + 9
+    w = with_shape(WORKLOADS["cfg4"], name=f"padding-{b}-{stis_block}", B=4, H=2, L=L, block=b, topk=topk, window=b + 3, len_lo=1,
+                   len_hi=L, stis_block=stis_block, seed=680 + b + stis_block)
+    x = make_inputs(w, want_dO=True)
+    x.valid_len[:] = [L - 1, L - b - b // 2, 3 * b + 5, 4]
+    first = (L - x.valid_len) // b
+    for r in range(w.B):
+        for t in (x.Q, x.K, x.V, x.dO):
+            t[r, :, : first[r] * b] = np.nan
+
+    def padding_named(sel):
+        for r in range(w.B):
+            for I in range(first[r], w.NB):
+                e = next(e for e in range(topk) if sel[r, 0, I, e] != I)
+                sel[r, 0, I, e] = 0 if first[r] > 0 else -1      # a block of padding, if the row has one
+                if I % 2:
+                    sel[r, 1, I, e] = -1
+        return sel
+
+    run_case(w, x=x, backward=True, gate_scale=0.4, check_dense=True, sel_edit=padding_named)
+
+
 @pytest.mark.parametrize("b", [32, 64])
 def test_a_gate_that_shuts_a_branch(b):
     # one head's gate closes the long-term branch, the other's the short-term one (a weight of zero, whose logarithm goes into no
