@@ -513,6 +513,8 @@ __device__ __forceinline__ void bwd_dq_body(
         } else {
           keep_rows(sacc, row_bits(lo - J * BLK - 32 * s, iq - J * BLK - 32 * s), lh, kNegInf);
         }
+        // the padding's values may be any finite ones, whose products overflow: no infinity for a probability of zero to meet
+        if (J * BLK < p0) keep_rows(gacc, row_bits(p0 - J * BLK - 32 * s, 31), lh);
       }
 #pragma unroll
       for (int i = 0; i < 16; ++i) sacc[i] = __builtin_amdgcn_exp2f(sacc[i]) * gacc[i];  // dS
@@ -712,6 +714,13 @@ __device__ __forceinline__ void bwd_dkv_body(
   float u_lt;
   float r_sum = 0.0f, r_st = 0.0f;  // this lane's part of r_x, of the branch the walk is in and of the short-term one
   auto gate_products = [&]() __attribute__((always_inline)) {
+    if (J * BLK < p0) {  // the products of a padded key's value may overflow
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        const uint4 v = __builtin_bit_cast(uint4, vf[kk]);
+        vf[kk] = __builtin_bit_cast(bf16x8, make_uint4(key_ok ? v.x : 0u, key_ok ? v.y : 0u, key_ok ? v.z : 0u, key_ok ? v.w : 0u));
+      }
+    }
     auto product = [&](const float *w) __attribute__((always_inline)) -> float {
       float g[4][8], u = 0.0f;
       load_gate(w, lh, g);

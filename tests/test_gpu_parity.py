@@ -283,6 +283,21 @@ def test_blocks_of_padding_may_hold_anything(b, stis_block, topk):
     run_case(w, x=x, backward=True, gate_scale=0.4, check_dense=True, sel_edit=padding_named)
 
 
+@pytest.mark.parametrize("b,stis_block,topk", [(32, 0, 3), (32, 32, 3), (32, 8, 2), (64, 0, 3), (64, 64, 3), (64, 1, 2)])
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_padding_of_a_partly_valid_block_may_hold_any_finite_value(b, stis_block, topk, sign):
+    # the matrix-core kernels: the largest there is in all four tensors, whose products overflow
+    L = 6 * b + 9
+    w = with_shape(WORKLOADS["cfg4"], name=f"large-padding-{b}-{stis_block}", B=4, H=2, L=L, block=b, topk=topk, window=b + 3, len_lo=1,
+                   len_hi=L, stis_block=stis_block, seed=690 + b + stis_block)
+    x = make_inputs(w, want_dO=True)
+    x.valid_len[:] = [L - 1, L - b - b // 2, 3 * b + 5, 4]  # (of a block of 64 also one whose first half is padding)
+    for r in range(w.B):
+        for t in (x.Q, x.K, x.V, x.dO):
+            t[r, :, : L - x.valid_len[r]] = sign * torch.finfo(torch.bfloat16).max
+    run_case(w, x=x, backward=True, gate_scale=0.4, check_dense=True)
+
+
 @pytest.mark.parametrize("b", [32, 64])
 def test_a_gate_that_shuts_a_branch(b):
     # one head's gate closes the long-term branch, the other's the short-term one (a weight of zero, whose logarithm goes into no
