@@ -44,6 +44,16 @@ def test_heads_taken_by_length(Bn, H):
     run_case(w, x=x, backward=True, gate_scale=0.4)
 
 
+@pytest.mark.parametrize("d,Bn,H", [(16, 130, 2), (32, 64, 8), (8, 130, 4)])
+def test_heads_taken_by_length_in_bf16(d, Bn, H):
+    w = with_shape(WORKLOADS["cfg2"], name=f"f32mc-order-bf16-d{d}-B{Bn}-H{H}", B=Bn, H=H, L=150, d=d, block=16, topk=2, window=4,
+                   dtype="bf16", qkv_scaled=True, len_lo=1, len_hi=150, seed=970 + d)
+    x = make_inputs(w, want_dO=True)
+    x.valid_len[1::3] = x.valid_len[1]
+    x.valid_len[[0, 2, 5, Bn - 1]] = [150, 0, 151, -3]
+    run_case(w, x=x, backward=True, gate_scale=0.4)
+
+
 def test_sharp_softmax_and_holes():
     # logits large enough that a few keys take a row's whole weight; caller-built selection rows with holes are skipped
     # where they stand

@@ -29,6 +29,8 @@ def _inputs(dtype, Bn, H, L, d, Dm, seed):
     ("bf16", 3, 4, 128, 64, 256, False),   # the L = 1024 workloads' layer (4 heads of 64): two position halves per workgroup
     ("bf16", 1, 4, 77, 64, 256, True),     # shorter than one tile
     ("bf16", 2, 2, 130, 64, 512, False),   # projection to a wider model (H*d = 128)
+    ("bf16", 3, 8, 1397, 64, 512, True),   # H_prev past the caches, ragged last tile ...
+    ("bf16", 7, 4, 1187, 64, 256, False),  # ... and with two position halves per workgroup
     ("fp32", 3, 2, 200, 32, 64, True),     # the short-sequence shapes (hidden 64), scalar kernel
     ("fp32", 2, 8, 61, 8, 64, False),      # the paper's own setting: 8 heads of 8
     ("bf16", 2, 8, 50, 16, 128, True),     # bf16 outside the matrix-core shapes

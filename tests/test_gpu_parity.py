@@ -599,6 +599,8 @@ def test_small_head_dims(dtype, d, H, L, b, k, w, sblk):
     ("fp32", 8, 16, 200, 4),
     ("bf16", 64, 64, 1000, 5),
     ("bf16", 16, 32, 417, 2),
+    ("fp32", 16, 8, 517, 5),     # 65 blocks: a thread per candidate, for the last block alone
+    ("bf16", 64, 32, 4101, 6),   # 129: for every block
 ])
 def test_select_with_compressed_keys(dtype, d, b, L, k):
     # blossom_select_blocks_cmp: the caller's compressed keys replace the block means (Eq. 9 with a

@@ -116,7 +116,7 @@ def test_attention_under_a_per_position_selection(dtype, Bn, H, G, L, d, l, s, l
     ("bf16", 2, 4, 4, 333, 16, 32, 16, 16, 6, 20, 1, 16),  # bf16 storage, no sharing, three rounds of key blocks
     ("fp32", 2, 2, 1, 16, 16, 16, 16, 16, 1, 1, 0, 0),     # one block, own block only, self only
 ])
-def test_backward_under_a_per_position_selection(dtype, Bn, H, G, L, d, l, s, lsel, k, window, stis_mode, stis_block):
+def test_backward_under_a_per_position_selection(dtype, Bn, H, G, L, d, l, s, lsel, k, window, stis_mode, stis_block, lengths=()):
     # forward + backward under the selection blossom_select_positions writes, against the oracle's backward under
     # the same per-position rows (its K, V and rows repeated per head; the gradients of a shared key head added up)
     from gpu_util import TOL, assert_close, host
@@ -133,6 +133,8 @@ def test_backward_under_a_per_position_selection(dtype, Bn, H, G, L, d, l, s, ls
     vl[0] = L
     if Bn > 2:
         vl[2] = min(L, lsel + 3)     # a row whose first blocks hold no valid position
+    for r, n in lengths:
+        vl[r] = n
     print(f"per-position backward {dtype} B{Bn} H{H} G{G} L{L} d{d} l'{lsel} k{k} w{window} stis {stis_mode}/{stis_block}", flush=True)
     dt = B.F32 if dtype == "fp32" else B.BF16
     p_sel = B.Params(Bn, H, L, d, lsel, k, 1, dt)
@@ -184,6 +186,19 @@ def test_backward_under_a_per_position_selection(dtype, Bn, H, G, L, d, l, s, ls
 def test_backward_under_a_per_position_selection_and_mask_block_1(dtype, Bn, H, G, L, d, lsel, k, window):
     # from d = 16 on the keys at powers of two stay in the walk's tiles, selected or not
     test_backward_under_a_per_position_selection(dtype, Bn, H, G, L, d, 16, 8, lsel, k, window, 1, 1)
+
+
+@pytest.mark.parametrize("dtype,Bn,H,G,L,d", [
+    ("fp32", 130, 8, 4, 150, 8),    # 520 groups of two heads
+    ("bf16", 130, 8, 4, 150, 16),
+    ("fp32", 260, 2, 1, 150, 16),   # one group to a row
+    ("bf16", 90, 4, 4, 150, 8),     # no sharing
+])
+def test_groups_taken_by_length(dtype, Bn, H, G, L, d):
+    # more groups than CUs: forward and backward take them in the order of their rows' lengths, among them many equal ones, empty
+    # rows and a full last one
+    lengths = [(r, 77) for r in range(3, Bn, 3)] + [(4, 0), (5, 0), (Bn - 1, L)]
+    test_backward_under_a_per_position_selection(dtype, Bn, H, G, L, d, 32, 16, 16, 3, 8, 1, 1, lengths)
 
 
 def test_per_position_attention_limits():

@@ -63,9 +63,10 @@ def test_rope_select_forward_backward(name, shape):
             assert float(g.dQ[r, :, :p0].abs().max()) == 0.0 and float(g.dK[r, :, :p0].abs().max()) == 0.0
 
 
-def test_rope_serving_mode_and_random_angles():
+@pytest.mark.parametrize("L", [32 * 6 + 7, 32 * 64 + 7])   # 65 blocks: a thread per candidate, for the last block alone
+def test_rope_serving_mode_and_random_angles(L):
     # serving mode rotates all of K and the last query block; arbitrary tables (not cos/sin of anything) are legal input
-    w = with_shape(WORKLOADS["cfg3"], name="rope-serve", B=3, H=2, L=32 * 6 + 7, len_lo=50, len_hi=32 * 6 + 7)
+    w = with_shape(WORKLOADS["cfg3"], name="rope-serve", B=3, H=2, L=L, len_lo=50, len_hi=L)
     x = make_inputs(w)
     rng = np.random.default_rng(5)
     ang = rng.uniform(-3.0, 3.0, (w.L, w.d // 2))
