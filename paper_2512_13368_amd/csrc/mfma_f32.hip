@@ -955,49 +955,76 @@ __host__ __device__ inline int lt_words(const KParams &p, bool perpos)
 }
 
 
-// HEADS BY LENGTH.  A few heads to a CU, all of them there from the start: the launch lasts as long as the fullest CU, and which
-// lengths meet there was chance.  The workgroups therefore take the units (heads, or groups) in the order of their rows' lengths,
-// the longest first, and where all fit two to a CU the second half the other way round: the longest beside the shortest.  Every
-// wavefront finds its own place in that order: it holds all lengths (64 to a register), settles bit by bit the length that stands at its rank
-// and takes the row among those of that length, ties by index; 0.4 us, none where all lengths agree.
-// A training step at B=256 H=2 L=200 d=32, lengths U[20,200], fp32 88.8 -> 73.6 us (backward 58.5 -> 46.3), in bf16 without a causal
-// mask 86.2 -> 72.6; gradients at B=512 H=2 103 -> 94, at B=100 H=8 d=16 56.7 -> 48.8, per position at B=500 over 4 groups 189 -> 170.
+// HEADS BY LENGTH.  A few heads to a CU: the launch lasts as long as the fullest CU, and which lengths meet there was chance.  The
+// workgroups therefore take the units (heads, or groups) in the order of their rows' lengths, the longest first; where all are there
+// from the start, two to a CU, the second of them the other way round: the longest beside the shortest.  One wavefront of a workgroup
+// finds the place: it holds all lengths (64 to a register), settles two bits at a time the length that stands at its rank and takes the
+// row among those of that length, ties by index.  Lengths that differ by less than an eighth of the longest stay in turn (beyond a quarter they never do).
 constexpr int kOrderRows = 512;
 constexpr int kCUs = 256;
-__device__ __forceinline__ int unit_by_length(const int *valid_len, const KParams &p, int per_row, unsigned pid, unsigned units)
+struct Unit {
+  int id, valid;  // and the length of its row
+};
+__device__ __forceinline__ Unit unit_by_length(const int *valid_len, const KParams &p, int per_row, unsigned pid, unsigned units)
 {
   constexpr int N = kOrderRows / 64;
   const int lane = threadIdx.x & 63;
+  const int in_turn = clamp_len(valid_len[pid / per_row], p.L);  // (beside the other loads, not after them)
   int len[N];
+  // f(i) for the registers that hold rows, four at a time
+  auto each = [&](auto f) __attribute__((always_inline)) {
 #pragma unroll
-  for (int i = 0; i < N; ++i) len[i] = valid_len[min(64 * i + lane, p.B - 1)];
-  int differs = 0;
+    for (int i0 = 0; i0 < N; i0 += 4)
+      if (i0 == 0 || 64 * i0 < p.B)
 #pragma unroll
-  for (int i = 0; i < N; ++i) differs |= len[i] ^ len[0];
-  if (__all(differs == 0 && len[0] == __builtin_amdgcn_readfirstlane(len[0]))) return (int)pid;
-#pragma unroll
-  for (int i = 0; i < N; ++i) len[i] = 64 * i + lane < p.B ? clamp_len(len[i], p.L) : -1;
-  const unsigned turn = pid / kCUs, last = min((turn + 1) * kCUs, units) - 1;
-  const unsigned place = turn % 2 == 0 ? pid : last - (pid - turn * kCUs);
-  const int rank = (int)place / per_row;
-  auto at_least = [&](int x) {
-    int c = 0;
-#pragma unroll
-    for (int i = 0; i < N; ++i) c += __popcll(__ballot(len[i] >= x));
-    return c;
+        for (int i = i0; i < i0 + 4; ++i) f(i);
   };
-  int x = 0;  // the largest length that more than `rank` rows reach
-  for (int bit = 31 - __builtin_clz((unsigned)p.L); bit >= 0; --bit)
-    if (at_least(x | 1 << bit) > rank) x |= 1 << bit;
-  int left = rank - at_least(x + 1), row = 0;
 #pragma unroll
-  for (int i = 0; i < N; ++i) {
+  for (int i = 0; i < N; ++i) len[i] = -1;
+  each([&](int i) { len[i] = valid_len[min(64 * i + lane, p.B - 1)]; });
+  int longest = 0, shortest = p.L;
+  each([&](int i) {
+    len[i] = clamp_len(len[i], p.L);
+    longest = max(longest, len[i]);
+    shortest = min(shortest, len[i]);
+    if (64 * i + lane >= p.B) len[i] = -1;
+  });
+  // (every lane's lengths with those of lane 0)
+  longest = max(longest, __builtin_amdgcn_readfirstlane(longest));
+  shortest = min(shortest, __builtin_amdgcn_readfirstlane(shortest));
+  if (__ballot(8 * (longest - shortest) >= longest) == 0ull) return {(int)pid, in_turn};
+  const unsigned place = pid >= kCUs && units <= 2 * kCUs ? units - 1 - (pid - kCUs) : pid;
+  const int rank = (int)place / per_row;
+  // the largest length that more than `rank` rows reach, two bits at a time
+  int x = 0;
+  for (int bit = (31 - __builtin_clz((unsigned)p.L)) & ~1; bit >= 0; bit -= 2) {
+    int c[3] = {0, 0, 0};
+    each([&](int i) {
+#pragma unroll
+      for (int n = 0; n < 3; ++n) c[n] += __popcll(__ballot(len[i] >= (x | (n + 1) << bit)));
+    });
+    x |= ((c[0] > rank) + (c[1] > rank) + (c[2] > rank)) << bit;
+  }
+  int left = rank, row = 0;
+  each([&](int i) { left -= __popcll(__ballot(len[i] > x)); });
+  each([&](int i) {
     const unsigned long long m = __ballot(len[i] == x);
     const int n = __popcll(m), before = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
     if (left >= 0 && left < n) row = 64 * i + __builtin_ctzll(__ballot(len[i] == x && before == left));
     left -= n;
+  });
+  return {row * per_row + (int)place % per_row, x};
+}
+// the unit of this workgroup, the same in all of its wavefronts
+__device__ __forceinline__ Unit place_by_length(const int *valid_len, const KParams &p, int per_row, int wv)
+{
+  __shared__ Unit mine;
+  if (wv == 0) {
+    const Unit u = unit_by_length(valid_len, p, per_row, blockIdx.x, gridDim.x);
+    if ((threadIdx.x & 63) == 0) mine = u;
   }
-  return row * per_row + (int)place % per_row;
+  __syncthreads();
+  return {__builtin_amdgcn_readfirstlane(mine.id), __builtin_amdgcn_readfirstlane(mine.valid)};
 }
 
 }  // namespace
@@ -1010,12 +1037,14 @@ __device__ __forceinline__ int unit_by_length(const int *valid_len, const KParam
 // selection blocks of BK positions; head h reads the keys and values of group h / (H/G).
 // `parts` workgroups share the query tiles of a head.  sel == nullptr: dense causal attention.
 // RES: the workgroup stages the keys and values in LDS first, and serves all hpg query heads that read them.
-template <typename T, int D, int BK, bool PERPOS, bool RES>
+// ORDER: see HEADS BY LENGTH (a kernel of its own, as in the backward: beside it, never taken, the code cost selection + forward at B=225 H=8
+// d=8 L=200 2 %).
+template <typename T, int D, int BK, bool PERPOS, bool RES, bool ORDER>
 __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(D == 32 ? 5 : 6))) void fwd_small_kernel(
     const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V, const int *__restrict__ valid_len,
     const int *__restrict__ sel, const float *__restrict__ gate_w, const float *__restrict__ gate_b,
     T *__restrict__ O, float *__restrict__ o_lt_out, float *__restrict__ o_st_out, float *__restrict__ lse_lt_out,
-    float *__restrict__ lse_st_out, int hpg, int parts, int by_length, KParams p)
+    float *__restrict__ lse_st_out, int hpg, int parts, KParams p)
 {
   constexpr int CPL = Geo<D>::CPL, NMB = Geo<D>::NMB, NACC = Geo<D>::NACC;
   extern __shared__ __attribute__((aligned(16))) float small_lds[];  // RES: K and V rows; then the wavefronts' selection words
@@ -1026,14 +1055,19 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
   // fp32, it is the other way round: L=87 b=16 15.7 and 16.0.)
   constexpr bool direct = RES && D * sizeof(T) < 128;
   unsigned vid;
-  if (RES && __builtin_expect(by_length, 0)) vid = (unsigned)__builtin_amdgcn_readfirstlane(unit_by_length(valid_len, p, p.H / hpg, blockIdx.x, gridDim.x));
-  else vid = direct ? blockIdx.x : mfma::xcd_spread(blockIdx.x, gridDim.x / parts, parts);
+  int valid;
+  if constexpr (ORDER) {
+    const Unit u = place_by_length(valid_len, p, p.H / hpg, wv);
+    vid = (unsigned)u.id;
+    valid = u.valid;
+  } else vid = direct ? blockIdx.x : mfma::xcd_spread(blockIdx.x, gridDim.x / parts, parts);
   if constexpr (direct) parts = 1;
   const int heads = RES ? hpg : 1;  // query heads of this workgroup
   const int bh0 = (int)(vid / parts) * heads, part = (int)(vid % parts);
   const int b = bh0 / p.H;
   const int NT = (p.L + kTile - 1) / kTile;
-  const int p0 = p.L - clamp_len(valid_len[b], p.L);
+  if constexpr (!ORDER) valid = clamp_len(valid_len[b], p.L);
+  const int p0 = p.L - valid;
   const int T0 = p0 / kTile;  // (beyond the last tile of a row without a valid position)
   const int q = lane & 15, g = lane >> 4;
   const int kvh = PERPOS ? bh0 / hpg : bh0;
@@ -2137,9 +2171,13 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = blockDim.x >> 6;
   // (row, key/value head)
-  const int bg = ORDER ? __builtin_amdgcn_readfirstlane(unit_by_length(valid_len, p, p.H / hpg, blockIdx.x, gridDim.x)) : (int)blockIdx.x;
+  const Unit unit = [&]() -> Unit {
+    if constexpr (ORDER) return place_by_length(valid_len, p, p.H / hpg, wv);
+    else return {(int)blockIdx.x, clamp_len(valid_len[blockIdx.x / (p.H / hpg)], p.L)};
+  }();
+  const int bg = unit.id;
   const int NT = (p.L + kTile - 1) / kTile, NWt = (NT + 31) / 32, NWb = (p.NB + 31) / 32;
-  const int p0 = p.L - clamp_len(valid_len[bg / (p.H / hpg)], p.L);
+  const int p0 = p.L - unit.valid;
   const int T0 = p0 / kTile;
   const int q = lane & 15, g = lane >> 4;
   const size_t head_kv = (size_t)bg * p.L * D;
@@ -2269,14 +2307,20 @@ int res_waves(int units) { return many_heads(units) ? 4 : 8; }
 // the backward's time, only where the order pays for itself: two heads to a CU of at least 128 positions, or several query heads a
 // workgroup (B=250 H=8 L=200 d=16 44.2 us in turn, 47.9 by length; B=128 H=4 L=60 d=32 9.9 and 11.3; per position B=500 80.0 and 73.6).
 // Short heads end before the order is found, and the more heads a CU takes one after another the more often it is found and the less
-// it gives, so both of them bound the length from which it is used (a training step, order found in the backward / heads in turn, us:
-// d=16 units 400 L=60 32.0 / 30.7, L=100 39.0 / 38.6, L=140 43.7 / 44.1, L=200 51.4 / 56.4; units 1200 L=60 57.3 / 53.6, L=100 69.8 / 66.1,
-// L=140 77.8 / 76.3, L=200 95.9 / 98.3.  d=32 units 512 L=60 41.5 / 41.4, L=100 52.7 / 55.5; units 1500 L=100 95.8 / 91.2, L=140
-// 108.9 / 109.1.  Per position, in both passes, units 400 L=40 46.7 / 43.8, L=70 55.5 / 54.0, L=100 63.9 / 66.0, L=200 99.1 / 123.1;
-// units 1800 L=100 159.8 / 151.3, L=140 186.5 / 187.8, L=200 250 / 276).
+// it gives, so both of them bound the length from which it is used (a training step, fp32, lengths U[L/10,L], in order / in turn, us):
+//   units          300                    600                    1200                   1800
+//   d = 8   L=60   26.6 / 26.6   L=100   41.8 / 41.0   L=100   61.7 / 61.2   L=130   92.6 / 90.8
+//          L=100   31.6 / 32.2   L=130   46.8 / 48.3   L=130   67.9 / 69.3   L=200  110.9 / 113.7
+//   d = 16  L=60   27.8 / 27.9    L=60   37.8 / 37.6    L=60   54.3 / 53.3   L=100   91.8 / 89.6
+//          L=100   34.3 / 35.7   L=100   45.6 / 46.0   L=100   67.4 / 68.6   L=130  109.4 / 110.2
+//   d = 32  L=60   36.3 / 37.3    L=60   47.9 / 50.7    L=60   73.4 / 74.5    L=60  100.2 / 97.7
+//          L=200   67.4 / 77.5   L=200   95.4 / 110.6  L=200  160 / 175      L=100  140.4 / 141.1
+//   per position, in both passes
+//           L=40   41.6 / 42.5    L=40   56.0 / 55.3    L=70  103.9 / 101.7  L=100  161 / 158
+//           L=70   49.8 / 53.3    L=70   70.1 / 72.1   L=100  118.3 / 120.7  L=130  189 / 191
 int shortest_ordered(const KParams &p, int units, bool perpos)
 {
-  return perpos ? 68 + units / 20 : p.d == 32 ? 16 + units / 10 : 96 + units / 14;
+  return perpos ? 30 + units / 18 : p.d == 32 ? 30 + units / 25 : (p.d == 16 ? 60 : 80) + units / 20;
 }
 bool order_by_length(const KParams &p, int units, bool perpos)
 {
@@ -2401,11 +2445,12 @@ static void launch_fwd_small_t(const KParams &p, const FwdArgs &a, hipStream_t s
       want_lds(kernel, pl.lds);
       hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * pl.waves), pl.lds, st, (const T *)a.Q, (const T *)a.K,
                          (const T *)a.V, a.valid_len, a.dense ? nullptr : a.sel, a.gate_w, a.gate_b, (T *)a.O,
-                         (float *)a.o_lt, (float *)a.o_st, a.lse_lt, a.lse_st, hpg, pl.parts,
-                         (int)(pl.res && order_by_length(p, grid, perpos) && (perpos || (grid <= 2 * kCUs && p.L >= 128))), p);
+                         (float *)a.o_lt, (float *)a.o_st, a.lse_lt, a.lse_st, hpg, pl.parts, p);
     };
-    if (perpos) pl.res ? go(fwd_small_kernel<T, D, BK, true, true>) : go(fwd_small_kernel<T, D, BK, true, false>);
-    else pl.res ? go(fwd_small_kernel<T, D, BK, false, true>) : go(fwd_small_kernel<T, D, BK, false, false>);
+    if (pl.res && order_by_length(p, grid, perpos) && (perpos || (grid <= 2 * kCUs && p.L >= 128)))
+      perpos ? go(fwd_small_kernel<T, D, BK, true, true, true>) : go(fwd_small_kernel<T, D, BK, false, true, true>);
+    else if (perpos) pl.res ? go(fwd_small_kernel<T, D, BK, true, true, false>) : go(fwd_small_kernel<T, D, BK, true, false, false>);
+    else pl.res ? go(fwd_small_kernel<T, D, BK, false, true, false>) : go(fwd_small_kernel<T, D, BK, false, false, false>);
   });
 }
 
