@@ -37,6 +37,12 @@
 #include "launch.h"
 #include "mfma_common.h"
 
+// x * y, and zero where either is zero, whatever the other: the padding's values may be any finite ones, whose products overflow, and no
+// infinity is to meet a probability of zero.  (v_mul_legacy_f32, as the compiler's intrinsic: in assembly it would not wait for a
+// matrix instruction's result.  Dropping the products of padded keys by a mask instead: a training step at B=64 H=8 L=500 b=64, lengths
+// U[50,500], 195.3 us; with this 192.4, as without either.)
+__device__ float mul_or_zero(float x, float y) __asm("llvm.amdgcn.fmul.legacy");
+
 namespace blossom {
 
 using namespace mfma;
@@ -513,11 +519,10 @@ __device__ __forceinline__ void bwd_dq_body(
         } else {
           keep_rows(sacc, row_bits(lo - J * BLK - 32 * s, iq - J * BLK - 32 * s), lh, kNegInf);
         }
-        // the padding's values may be any finite ones, whose products overflow: no infinity for a probability of zero to meet
-        if (J * BLK < p0) keep_rows(gacc, row_bits(p0 - J * BLK - 32 * s, 31), lh);
       }
 #pragma unroll
-      for (int i = 0; i < 16; ++i) sacc[i] = __builtin_amdgcn_exp2f(sacc[i]) * gacc[i];  // dS
+      for (int i = 0; i < 16; ++i)  // dS
+        sacc[i] = mul_or_zero(__builtin_amdgcn_exp2f(sacc[i]), gacc[i]);
       bf16x8 dsf[2];
       to_operand(sacc, dsf);
       if constexpr (!ONE) read_kt();
