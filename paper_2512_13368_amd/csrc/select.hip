@@ -120,7 +120,7 @@ __device__ __forceinline__ size_t kmean_at(int bh, int J, int c, const KParams &
 // One lane owns 16 bytes of channels of one block of one tensor.  qsum [B,H,NB,d] (unnormalised sums of Q), kmean: above.
 // KCMP: K holds compressed keys [B,H,NB,d] supplied by the caller (Eq. 9 with the caller's phi);
 // they are copied as they are instead of being pooled.
-// STREAM: whole blocks are read past the caches (see kStreamBytes).
+// STREAM: whole blocks are read past the caches (see kKeysOnceBytes).
 template <typename T, int D, bool KCMP, bool STREAM>
 __global__ __launch_bounds__(256) void pool_kernel(const T *__restrict__ Q, const T *__restrict__ K,
                                                    const int *__restrict__ valid_len,
@@ -685,11 +685,17 @@ static bool one_workgroup_per_head(const KParams &p, size_t elem)
   return p.NB <= kPairBlocks || (long)p.B * p.H >= kHeads;
 }
 
-// Keys of the last block's selection that half the last-level cache does not hold are read past the caches: nothing reads most of them
-// again, and pooling at B=16 H=8 L=8192 d=64 b=64 takes 24 instead of 27 us (select + forward 52.4 -> 49.5; b=32 61 -> 58.5).  Smaller ones
-// may be in the cache, from whoever made them (B=12 H=8 L=6000, 74 MB, 35.8 without and 36.6 with), and the keys of a whole
-// selection are read again by the forward (B=700 H=8 L=200 d=16 fp32, 143 MB, 111.7 and 115.0).
-constexpr size_t kStreamBytes = 128u << 20;
+// Keys of the last block's selection are read past the caches where there are many: nothing reads most of them again, and pooling at
+// B=16 H=8 L=8192 d=64 b=64 takes 24 instead of 27 us.  Fewer may be in the last-level cache (256 MB), from whoever made them, and those of
+// a whole selection are read again by the forward (B=700 H=8 L=200 d=16 fp32, 143 MB, 111.7 us without and 115.0 with).  Selection +
+// forward of the last block, H=8 d=64 b=64 bf16, through / past the caches, us, with other keys than the last call's, and (a copy of
+// them in both figures) with keys written right before the call:
+//   64 MB  B=16 H=4 L=8192  37.2 / 37.9    64.4 / 65.7       101 MB  B=16 L=6500  46.4 / 44.9   83.9 / 83.6
+//   70 MB  B=16 L=4500      38.7 / 38.6    66.4 / 66.4       117 MB  B=16 L=7500  48.7 / 47.2   92.4 / 92.0
+//   85 MB  B=16 L=5500      43.7 / 42.7    76.2 / 75.8       128 MB  B=16 L=8192  52.4 / 49.4   98.6 / 97.9
+//   96 MB  B=12 L=8192      45.6 / 44.0    81.4 / 82.2       256 MB  B=32 L=8192  80.5 / 74.9    188 / 171
+// The line lies where both gain.  (The same keys in one call after another: 101 MB 41.9 / 44.9, 256 MB 71.9 / 74.6, 512 MB 145 / 131.)
+constexpr size_t kKeysOnceBytes = 100u << 20;
 template <typename T, int D>
 static void launch_select_t(const KParams &p, const void *Q, const void *K, bool kcmp, const int *valid_len,
                             int *sel, void *ws, void *Q_rot, void *K_rot, hipStream_t st)
@@ -718,7 +724,7 @@ static void launch_select_t(const KParams &p, const void *Q, const void *K, bool
     auto go = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, st, (const T *)Q, (const T *)K, valid_len, qsum, kmean, p);
     };
-    const bool stream = p.nq == 1 && (size_t)p.B * p.H * p.L * D * sizeof(T) >= kStreamBytes;
+    const bool stream = p.nq == 1 && (size_t)p.B * p.H * p.L * D * sizeof(T) >= kKeysOnceBytes;
     stream ? go(pool_kernel<T, D, false, true>) : go(pool_kernel<T, D, false, false>);
     if (launch_failed()) return;
   }

@@ -52,6 +52,28 @@ def test_selection_at_the_limits_of_its_kernels(rows, H, L, d, b, k, dtype, stis
     np.testing.assert_array_equal(sel, want)
 
 
+@pytest.mark.parametrize("dtype,rows,H,L,b,k", [("bf16", 17, 8, 6413, 64, 12), ("fp32", 21, 4, 5003, 32, 9)])
+def test_last_block_of_many_keys(dtype, rows, H, L, b, k):
+    # 106 and 102 MB of keys, which the last block's selection reads past the caches: the row that the selection of every block has
+    rng = np.random.default_rng(L)
+    Q, K = (rng.integers(-2, 3, size=(rows, H, L, 64), dtype=np.int8).astype(np.float32) for _ in range(2))
+    vl = rng.integers(1, L + 1, size=rows).astype(np.int32)
+    vl[:3] = [L, L - b - 3, 1]
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    Qd, Kd, vld = torch.from_numpy(Q).cuda().to(dt), torch.from_numpy(K).cuda().to(dt), torch.from_numpy(vl).cuda()
+    assert Kd.numel() * Kd.element_size() > 100 << 20
+
+    def last_row(**kw):
+        p = B.Params(rows, H, L, 64, b, k, 8, B.BF16 if dtype == "bf16" else B.F32, **kw)
+        return B.select_blocks(p, Qd, Kd, vld)[:, :, -1].cpu().numpy()
+
+    last = last_row(last_block_only=1)
+    np.testing.assert_array_equal(last, last_row())
+    pairs = np.array([0, H + 1, 2 * H, rows * H - 1], np.int32)
+    want = oracle.select_blocks(Q, K, vl, b, k, bh_list=pairs)[:, :, -1]
+    np.testing.assert_array_equal(last.reshape(-1, k)[pairs], want.reshape(-1, k)[pairs])
+
+
 @pytest.mark.parametrize("L,d,b,k,last", [
     (2632, 64, 64, 9, False), (2576, 64, 64, 9, True),   # 8 rows left over; 16, a quarter of a block
     (2577, 64, 64, 9, False), (2609, 64, 64, 9, True),   # 17, 49: a wavefront with that block sums all of its blocks row by row
