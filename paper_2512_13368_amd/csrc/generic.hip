@@ -463,7 +463,7 @@ __host__ __device__ constexpr int prep_rows(int d) { return d == 8 ? 128 : 64; }
 // Branch outputs from a quarter of the last-level cache on leave it to Q, K, V and dO, which the kernels that follow read: a training
 // step at B=32 H=8 L=700 d=64 b=32 113.5 -> 106.5 us, B=128 H=4 L=1024 324 -> 312.5, B=16 H=8 L=8192 1907 -> 1900; at B=16 H=8 L=500
 // (33 MB) 57.8 without and 58.4 with.
-constexpr size_t kStreamBytes = 64u << 20;
+constexpr size_t kBranchesOnceBytes = 64u << 20;
 constexpr size_t kPrepListLds = 8320;  // LDS that every head size has for them: up to 488 blocks
 
 // four consecutive elements as loaded, and as floats (zeros unless `keep`)
@@ -498,7 +498,7 @@ __device__ __forceinline__ float lanes_sum(float x)
   return x;
 }
 
-// STREAM: the branch outputs, which nothing reads again, are read past the caches (see kStreamBytes).
+// STREAM: the branch outputs, which nothing reads again, are read past the caches (see kBranchesOnceBytes).
 template <typename T, int D, bool STREAM>
 __global__ __launch_bounds__(256) void bwd_prep_kernel(const float *__restrict__ o_lt,
                                                        const float *__restrict__ o_st,
@@ -1149,7 +1149,7 @@ static void launch_bwd_t(const KParams &p, int dtype, const BwdArgs &a, unsigned
                          (const T *)a.dO, a.valid_len, a.gate_w, a.gate_b, w.rowstat, w.partial, a.lse_lt, a.lse_st, w.rowI_lt, w.rowI_st,
                          a.sel, w.offs, w.items, (int)lists, p);
     };
-    if ((size_t)BH * p.L * 2 * D * sizeof(float) >= kStreamBytes) go(bwd_prep_kernel<T, D, true>);
+    if ((size_t)BH * p.L * 2 * D * sizeof(float) >= kBranchesOnceBytes) go(bwd_prep_kernel<T, D, true>);
     else go(bwd_prep_kernel<T, D, false>);
     if (launch_failed()) return;
     if (!mfma || !bwd_mfma_takes_gate(p, stages)) launch_gate_reduce(p, a, w.partial, w.nchunk, st);

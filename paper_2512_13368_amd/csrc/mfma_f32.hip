@@ -355,7 +355,10 @@ __device__ __forceinline__ void store4_once(bf16_t *p, const float (&o)[4])
 // lane (col, g) holds channels 16*mb + 4g + r of one row in a[mb][r]: stores those below D
 // ONCE: a branch output, read by one later kernel if at all.  Those and the gradients written past the caches leave them to Q, K, V and
 // dO: a training step at B=256 H=2 L=200 d=32 fp32 75.1 -> 74.0 us, in bf16 without a causal mask 73.9 -> 72.9, B=2048 H=8 d=16 940 -> 930,
-// per position at d=8 902 -> 897, B=32 H=8 L=2000 d=8 242.2 -> 240.3.
+// per position at d=8 902 -> 897, B=32 H=8 L=2000 d=8 242.2 -> 240.3.  Small calls, whose branch outputs the caches would hold until
+// the backward reads them, take no longer either (through / past the caches): B=4 H=8 L=100 d=16 25.3 / 25.3, B=16 H=2 L=200 d=32 52.3 / 52.3, B=32
+// H=8 L=200 d=8 35.4 / 35.5, B=64 H=8 L=100 d=16 40.2 / 39.6; the largest losses of 26 shapes from B=4 to 128 were 0.5 % (per position, B=64 L=150
+// 72.4 / 72.7) and 0.4 % (bf16, B=128 H=2 L=200 d=32 44.5 / 44.7).
 template <typename T, int D, bool ONCE = false>
 __device__ __forceinline__ void store_row4(T *dst_row, const f32x4 (&a)[Geo<D>::NMB], int g)
 {

@@ -144,8 +144,8 @@ __device__ __forceinline__ int op_feature(int mb, int m) { return 32 * ((m >> 2)
 
 // STREAM: H_prev, which nothing here reads again, is read past the caches and leaves them to what the kernels that follow read.  A layer's
 // training step, us: B=32 H=8 L=1997 476.5 -> 469.7, B=30 H=8 L=1800 400.9 -> 395.2, B=16 H=8 L=500 (H_prev 8 MB) 105.5 -> 104.6; at
-// B=8 H=4 L=300 (1 MB) 53.0 without and 53.6 with.
-constexpr size_t kStreamBytes = 4u << 20;
+// B=8 H=4 L=300 (1 MB) 53.0 without and 53.6 with.  The line is what an XCD's L2 holds, 4 MB: between those two, and no sharper than they are.
+constexpr size_t kHprevOnceBytes = 4u << 20;
 template <int DM, bool STREAM>
 __global__ __launch_bounds__(64 * OpGeo<DM>::kWaves) void outproj_mfma_kernel(
     const uint16_t *__restrict__ O, const uint16_t *__restrict__ Wt, const float *__restrict__ bias,
@@ -400,7 +400,7 @@ void launch_out_proj(const OutProjArgs &a, hipStream_t st)
                          a.bias, (const uint16_t *)a.Hprev, a.gamma, a.beta, a.eps, (uint16_t *)a.S, a.mean, a.rstd, a.B, a.H,
                          a.L);
     };
-    const bool stream = (size_t)a.B * a.L * a.Dm * sizeof(uint16_t) >= kStreamBytes;
+    const bool stream = (size_t)a.B * a.L * a.Dm * sizeof(uint16_t) >= kHprevOnceBytes;
     if (a.Dm == 256) stream ? go(outproj_mfma_kernel<256, true>) : go(outproj_mfma_kernel<256, false>);
     else stream ? go(outproj_mfma_kernel<512, true>) : go(outproj_mfma_kernel<512, false>);
     return;
