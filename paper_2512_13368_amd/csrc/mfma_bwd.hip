@@ -10,9 +10,9 @@
 // (dO.v_j + y*u_j = D when P = 1) survives.  In dQ, where a lane keeps its row, the bracket dO + y_x*Wg_x is rounded to bf16 once and
 // its row constant c_x is taken with the same rounded values.  With two rounded gradients in memory and residual passes of dK/dV for
 // rows with few keys a training step at B=128 H=4 L=1024 k=8 w=64 in blocks of 32 took 345 us (the per-row pass 62, these kernels
-// 190) instead of 309 (47, 178), at B=32 H=8 L=1997 with all of Eq. 15 509 instead of 485, at B=16 H=8 L=8192 k=16 w=128 in
-// blocks of 64 2000 instead of 1945 (181 and 1206 against 130 and 1230: sixteen more additions a unit for the sums of P'*y); dK and
-// dV came out with 5 % larger errors.
+// 190) instead of 309 (47, 178), at B=32 H=8 L=1997 with all of Eq. 15 488 instead of 467.  At B=16 H=8 L=8192 k=16 w=128 in
+// blocks of 64, 2012 instead of 1999 (181 and 1206 against 130 and 1230), it is even but for what two boxes differ by: sixteen more
+// additions a unit for the sums of P'*y.  dK and dV came out with 5 % larger errors.
 //
 // Accumulators start at minus a per-row constant, so the MFMA result is directly what the next
 // step needs: the exponent S'' = c*q.k - lse*log2(e) + log2(a_x) (Q or K pre-multiplied by c =
