@@ -400,7 +400,14 @@ __device__ __forceinline__ void zero_fill(T *dst, int count, int lane)
   const int pieces = count * (int)sizeof(T) / 16;
   for (int i = lane; i < pieces; i += 64) q[i] = make_uint4(0u, 0u, 0u, 0u);
 }
-
+// the same by lanes `from`, `from` + `step` ...
+template <typename T>
+__device__ __forceinline__ void zero_rows_from(T *dst, int count, int from, int step)
+{
+  uint4 *q = reinterpret_cast<uint4 *>(dst);
+  const int pieces = count * (int)sizeof(T) / 16;
+  for (int i = from; i < pieces; i += step) q[i] = make_uint4(0u, 0u, 0u, 0u);
+}
 
 __device__ __forceinline__ unsigned abs_diff(int a, int b)  // both non-negative
 {
@@ -474,6 +481,44 @@ __device__ __forceinline__ float keep(float x, unsigned bits, int r)
 {
   return __uint_as_float(__float_as_uint(x) & (unsigned)__builtin_amdgcn_sbfe((int)bits, r, 1));
 }
+
+// THE NEAR FORM: causal, without Eq. 15 or with its mask block 1, and a window that ends within the tile before the row's own (w <= 17).
+// The short-term branch is then the row's own tile, the one before and the diagonals; every mask of those two tiles is the same
+// for all tiles of a wavefront, and is kept as four scalars, one per element of a lane (bit l: lane l's element r): a masked element
+// costs one v_cndmask on a scalar pair, and what tiles combine (padding, the tile's own triangle, whether it is selected) is scalar work.
+// The two tiles of the forward's short-term branch take 54 vector instructions, 125 with masks as bits.
+typedef unsigned long long Word;
+__host__ __device__ __forceinline__ bool near_form(const KParams &p) { return p.bidir == 0 && p.sblk <= 1 && p.w <= kTile + 1; }
+__device__ __forceinline__ bool in_lanes(Word m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+// the lanes (q, g) with 4g + r <= q, and with 4g + r >= q
+constexpr Word triangle(int r, bool upper)
+{
+  Word m = 0;
+  for (int l = 0; l < 64; ++l)
+    if (upper ? 4 * (l >> 4) + r >= (l & 15) : 4 * (l >> 4) + r <= (l & 15)) m |= 1ull << l;
+  return m;
+}
+// the lanes with 4g + r >= x (0 <= x <= 16)
+__device__ __forceinline__ Word elements_from(int x, int r)
+{
+  const int n = 16 * ((x - r + 3) >> 2);
+  return n >= 64 ? 0ull : ~0ull << n;
+}
+struct NearMasks {  // (made on the host)
+  Word own[4], next[4];  // short-term: the row's (key's) own tile, the tile before (after) it
+  NearMasks(const KParams &p, bool key_side)
+  {
+    for (int r = 0; r < 4; ++r) {
+      own[r] = next[r] = 0;
+      for (int l = 0; l < 64; ++l) {
+        const int x = 4 * (l >> 4) + r - (l & 15), d = key_side ? x : -x;  // distance between the lane's row and its element
+        auto sees = [&](int d) { return d >= 0 && (d < p.w || (p.sblk == 1 && is_pow2(d))); };
+        own[r] |= (Word)sees(d) << l;
+        next[r] |= (Word)sees(d + kTile) << l;
+      }
+    }
+  }
+};
 
 // may any query of tile I see any key of tile J in the short-term branch (J <= I in the causal form)?
 __device__ __forceinline__ bool st_reaches(const KParams &p, int I, int J)
@@ -709,24 +754,35 @@ struct LdsRows {
   }
 };
 // two heads' rows from tile T0 on into LDS; rows before p0 (the padding) and past the end are zeros.  CLEAN: elements that are
-// not finite become zeros too.
+// not finite become zeros too.  A wavefront requests up to four of its tiles (d = 32: two) before it waits for the first.
 template <typename T, int D, bool CLEAN>
 __device__ __forceinline__ void stage_pair(const T *A, const T *B, float *a_lds, float *b_lds, int L, int T0, int NT, int p0, int lane, int wv,
                                            int W)
 {
+  constexpr int N = D == 32 ? 2 : 4;
   const int q = lane & 15, g = lane >> 4;
   const Rows<T, D> Ar(A, L, q, g), Br(B, L, q, g);
-  for (int t = T0 + wv; t < NT; t += W) {
-    typename Operands<T, D>::Row x, y;
-    const unsigned off = t * kTile + q >= p0 ? Ar.row_off + (unsigned)t * Rows<T, D>::TB : kNowhere;
-    load_op<T, D>(Ar.s, off, x);
-    load_op<T, D>(Br.s, off, y);
-    if constexpr (CLEAN) {
-      Operands<T, D>::clean(x);
-      Operands<T, D>::clean(y);
+  for (int t0 = T0 + wv; t0 < NT; t0 += N * W) {
+    typename Operands<T, D>::Row x[N], y[N];
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+      const int t = t0 + n * W;
+      const unsigned off = (t < NT) & (t * kTile + q >= p0) ? Ar.row_off + (unsigned)t * Rows<T, D>::TB : kNowhere;
+      load_op<T, D>(Ar.s, off, x[n]);
+      load_op<T, D>(Br.s, off, y[n]);
     }
-    LdsRows<T, D>::put(a_lds, t * kTile + q, g, x);
-    LdsRows<T, D>::put(b_lds, t * kTile + q, g, y);
+    asm volatile("" ::: "memory");  // (the requests are not moved to where their rows are used)
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+      const int t = t0 + n * W;
+      if (t >= NT) break;
+      if constexpr (CLEAN) {
+        Operands<T, D>::clean(x[n]);
+        Operands<T, D>::clean(y[n]);
+      }
+      LdsRows<T, D>::put(a_lds, t * kTile + q, g, x[n]);
+      LdsRows<T, D>::put(b_lds, t * kTile + q, g, y[n]);
+    }
   }
 }
 
@@ -750,7 +806,6 @@ __device__ __forceinline__ unsigned pair_bits(unsigned long long b)
 //   2 st        short-term only: window and power-of-two tests
 // A lane classifies a tile, ballots make the words: about 20 instructions, where bit arithmetic on scalars took over a hundred
 // for half as many tiles and the scalar ALU was as busy as the vector ALUs (with the masks as bits, the steps above: 289 and 956 us).
-typedef unsigned long long Word;
 struct Walk {
   Word m0 = 0, m1 = 0, m2 = 0;  // tiles of the word still to come
   Word lt = 0;                  // long-term tiles of the word
@@ -893,46 +948,72 @@ struct LtSel {
   static constexpr int NROW = PERPOS ? 0 : kTile / BK;
   unsigned *bits, *tiles;
   int NWb;
-  unsigned long long row;
+  unsigned long long row, all;  // (per position: and the tiles that any of the rows selected)
 
-  // sel rows: of query block x0 on (or, per position, of this lane's position: nullptr where it takes no part).  p0: the
+  // sel rows: of query block x0 on, or, per position, of this lane's position (which may take no part).  p0: the
   // first valid position.  Entries outside [0, NB), later blocks (causal form) and blocks without a valid key drop out.
-  __device__ __forceinline__ void build(const KParams &p, unsigned *lds, const int *sel_rows, const int *sel_pos, int I, int iq,
-                                        int p0, int lane)
+  // `first`: the entries as `request` fetched them, per position the first four of this lane's row, else entry e in lane e
+  static constexpr int kFirst = PERPOS ? 4 : 1;
+  static __device__ __forceinline__ void request(const KParams &p, const int *sel_head, int I, int iq, int lane, int (&first)[kFirst])
+  {
+    if constexpr (PERPOS) {
+      const int *row = sel_head + (size_t)min(iq, p.L - 1) * p.k;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) first[i] = row[min(i, p.k - 1)];
+    } else {
+      const int rows = min(NROW, p.NB - I * NROW);  // (two blocks to a tile: the last tile may have one)
+      first[0] = sel_head[(size_t)I * NROW * p.k + min(lane, rows * p.k - 1)];
+    }
+  }
+  __device__ __forceinline__ void build(const KParams &p, unsigned *lds, const int *sel_rows, const int *sel_pos, bool takes_part, int I,
+                                        int iq, int p0, int lane, const int (&first)[kFirst])
   {
     NWb = (p.NB + 31) / 32;
     const int NWt = ((p.L + kTile - 1) / kTile + 31) / 32;
     bits = lds;
     tiles = lds + NROW * NWb;
-    row = 0ull;
+    row = all = 0ull;
     if constexpr (PERPOS) {
-      if (sel_pos)
-        // four requests at a time: a loop of single ones waited for memory k times (B=2048 H=8 over 4 L=200 d=8: 1093 us, 1060 so)
-        for (int e = 0; e < p.k; e += 4) {
-          int J[4];
+      // (later blocks and blocks without a valid key may stay: no walk asks about their tiles; with two blocks to a tile it does)
+      auto taken = [&](int J) { return (unsigned)J < (unsigned)p.NB && (BK == kTile || (J * BK <= iq && (J + 1) * BK > p0)); };
+      const bool half = p.NB <= 32;
+      auto add = [&](const int (&J)[4]) __attribute__((always_inline)) {
+        if (half) {
+          unsigned x = 0u;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) J[i] = sel_pos[min(e + i, p.k - 1)];
+          for (int i = 0; i < 4; ++i) x |= taken(J[i]) ? 1u << J[i] : 0u;
+          row |= x;
+        } else {
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (J[i] >= 0 && J[i] < p.NB && J[i] * BK <= iq && (J[i] + 1) * BK > p0) row |= 1ull << J[i];
+          for (int i = 0; i < 4; ++i) row |= taken(J[i]) ? 1ull << J[i] : 0ull;
         }
-      unsigned lo = (unsigned)row, hi = (unsigned)(row >> 32);
-      lo = or_row(lo);
-      hi = or_row(hi);
-      const unsigned long long all = ((unsigned long long)__builtin_amdgcn_readfirstlane(hi) << 32) | __builtin_amdgcn_readfirstlane(lo);
-      if (lane < NWt) tiles[lane] = BK == kTile ? (lane == 0 ? (unsigned)all : (unsigned)(all >> 32)) : pair_bits(all);
+      };
+      add(first);  // (apart from the others: a load in the loop, though never issued, would have this wait for all that are on their way)
+      // four requests at a time: a loop of single ones waited for memory k times (B=2048 H=8 over 4 L=200 d=8: 1093 us, 1060 so)
+      for (int e = 4; e < p.k; e += 4) {
+        int J[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) J[i] = sel_pos[min(e + i, p.k - 1)];
+        add(J);
+      }
+      if (!takes_part) row = 0ull;
+      all = (unsigned)__builtin_amdgcn_readfirstlane(or_row((unsigned)row));
+      if (!half) all |= (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane(or_row((unsigned)(row >> 32))) << 32;
+      if (BK < kTile) all = pair_bits(all);
+      if (lane < NWt) tiles[lane] = lane == 0 ? (unsigned)all : (unsigned)(all >> 32);
     } else {
       for (int i = lane; i < NROW * NWb + NWt; i += 64) bits[i] = 0u;
-      for (int i = lane; i < NROW * p.k; i += 64) {
+      auto add = [&](int i, int J) __attribute__((always_inline)) {
         const int xr = NROW == 1 ? 0 : (i >= p.k ? 1 : 0);
         const int x = I * NROW + xr;
-        if (x >= p.NB) continue;
-        const int J = sel_rows[i];  // (consecutive rows are contiguous)
-        if (J < 0 || J >= p.NB || (J > x && !p.bidir) || (J + 1) * BK <= p0) continue;
+        if (i >= NROW * p.k || x >= p.NB || J < 0 || J >= p.NB || (J > x && !p.bidir) || (J + 1) * BK <= p0) return;
         atomicOr(&bits[xr * NWb + (J >> 5)], 1u << (J & 31));
         const int t = J * BK / kTile;
         atomicOr(&tiles[t >> 5], 1u << (t & 31));
-      }
+      };
+      add(lane, first[0]);  // (consecutive rows are contiguous)
+      const int count = min(NROW, p.NB - I * NROW) * p.k;
+      for (int i = lane + 64; i < count; i += 64) add(i, sel_rows[i]);
     }
   }
   static __device__ __forceinline__ unsigned or_row(unsigned x)
@@ -950,6 +1031,22 @@ struct LtSel {
     if constexpr (PERPOS) return (row >> Jb) & 1ull;
     else if constexpr (BK < kTile) return (bits[(q / BK) * NWb + (Jb >> 5)] >> (Jb & 31)) & 1u;
     else return true;
+  }
+};
+// the same of a tile of the near form with one block to a tile: the entries stay in registers, 64 at a time, lane e holding entry e
+struct PickedTiles {
+  const int *rows;
+  int k, J;
+  // tiles 64w .. 64w + 63, whatever else the entries name
+  __device__ __forceinline__ Word word(int w, int lane) const
+  {
+    Word m = 0;
+    auto add = [&](int x, int count) __attribute__((always_inline)) {
+      for (Word b = __ballot((x >> 6) == w && lane < count); b; b &= b - 1) m |= 1ull << (__builtin_amdgcn_readlane(x, __builtin_ctzll(b)) & 63);
+    };
+    add(J, k);  // (apart from the others: a load in the loop, though never issued, would have this wait for all that are on their way)
+    for (int e0 = 64; e0 < k; e0 += 64) add(rows[min(e0 + lane, k - 1)], k - e0);
+    return m;
   }
 };
 __host__ __device__ inline int lt_words(const KParams &p, bool perpos)
@@ -1119,9 +1216,12 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     typename Ops::Row qf;
     load_op<T, D>(Qs, active ? (unsigned)(iq * D + CPL * g) * (unsigned)sizeof(T) : kNowhere, qf);
     LtSel<BK, PERPOS> ls;
-    if (!dense)
+    if (!dense) {
+      int first[LtSel<BK, PERPOS>::kFirst];
+      ls.request(p, sel + (PERPOS ? (size_t)kvh * p.L : (size_t)bh * p.NB) * p.k, I, iq, lane, first);
       ls.build(p, my_lds, PERPOS ? nullptr : sel + ((size_t)bh * p.NB + I * (kTile / BK)) * p.k,
-               PERPOS && active ? sel + ((size_t)kvh * p.L + iq) * p.k : nullptr, I, iq, p0, lane);
+               sel + ((size_t)kvh * p.L + min(iq, p.L - 1)) * p.k, active, I, iq, p0, lane, first);
+    }
     Ops::scale(qf, c2);
     const int kid_q = mask_block(p, iq);
     const int J_hi = p.bidir ? NT - 1 : I;
@@ -1398,6 +1498,400 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
 }
 
 // =============================================================================================
+// forward, THE NEAR FORM (see there)
+// =============================================================================================
+// A query tile walks itself, the tile before, its long-term tiles below (the first valid one, which may hold padding, first) and the
+// diagonals.  Bound by the latency of a wavefront's own chain at three to four wavefronts a SIMD (half of their time went on waits,
+// 566 vector and 420 scalar instructions a tile) rather than by a pipe, so:
+//  - What a tile needs from memory is requested a tile ahead and has arrived before the stores go out: loads and stores finish in
+//    order, and a wait for loads issued behind a tile's stores was a wait for those stores.
+//  - The selection is read from registers, entry by entry, where LDS words were cleared, set by atomics and read back.
+//  - Masks are scalars, the walk is three straight pieces, row sums and the lse of both branches are closed together.
+// us, with fwd_small_kernel / with this: B=256 H=2 L=200 d=32 19.6 / 17.8, B=2048 H=8 L=200 d=16 284 / 210, per position at d=8 240 /
+// 199, B=32 H=8 L=2000 d=8 (streamed) 60.5 / 53.5; selection + forward at B=4 H=2 L=50 d=32 10.2 / 9.3.
+template <typename T, int D, int BK, bool PERPOS, bool RES, bool ORDER>
+__global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(RES ? (D == 32 || PERPOS ? 4 : 5) : 5))) void fwd_near_kernel(
+    const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V, const int *__restrict__ valid_len,
+    const int *__restrict__ sel, const float *__restrict__ gate_w, const float *__restrict__ gate_b,
+    T *__restrict__ O, float *__restrict__ o_lt_out, float *__restrict__ o_st_out, float *__restrict__ lse_lt_out,
+    float *__restrict__ lse_st_out, int hpg, int parts, NearMasks nm, KParams p)
+{
+  constexpr int CPL = Geo<D>::CPL, NMB = Geo<D>::NMB, NACC = Geo<D>::NACC;
+  constexpr bool kPicked = !PERPOS && BK == kTile;
+  using Ops = Operands<T, D>;
+  using Sel = LtSel<BK, PERPOS>;
+  extern __shared__ __attribute__((aligned(16))) float small_lds[];  // RES: K and V rows; then the wavefronts' selection words
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = blockDim.x >> 6;
+  constexpr bool direct = RES && D * sizeof(T) < 128;  // (see fwd_small_kernel)
+  unsigned vid;
+  int valid;
+  if constexpr (ORDER) {
+    const Unit u = place_by_length(valid_len, p, p.H / hpg, wv);
+    vid = (unsigned)u.id;
+    valid = u.valid;
+  } else vid = direct ? blockIdx.x : mfma::xcd_spread(blockIdx.x, gridDim.x / parts, parts);
+  if constexpr (RES) parts = 1;
+  const int heads = RES && PERPOS ? hpg : 1;  // query heads of this workgroup
+  const int bh0 = (int)(vid / parts) * heads, part = (int)(vid % parts);
+  const int NT = (p.L + kTile - 1) / kTile;
+  if constexpr (!ORDER) valid = clamp_len(valid_len[bh0 / p.H], p.L);
+  const int p0 = p.L - valid;
+  const int T0 = p0 / kTile;  // (beyond the last tile of a row without a valid position)
+  const int q = lane & 15, g = lane >> 4;
+  const int kvh = PERPOS ? bh0 / hpg : bh0;
+  const int row_lo = (p.NB - p.nq) * BK;  // first row that is written (serving mode: the last block's)
+  const int I_lo = row_lo / kTile;
+  const T *Kh = K + (size_t)kvh * p.L * D, *Vh = V + (size_t)kvh * p.L * D;
+  const int pitch = RES ? NT * kTile * kLdsRow<T, D> : 0;  // floats of a staged tensor
+
+  // what a query tile needs from memory, requested a tile ahead
+  struct Request {
+    typename Ops::Row q;
+    int sel[Sel::kFirst];
+    __device__ __forceinline__ void arrived()
+    {
+      unsigned *w = reinterpret_cast<unsigned *>(this);
+#pragma unroll
+      for (unsigned i = 0; i < sizeof(Request) / 4; ++i) asm volatile("" : "+v"(w[i]));
+    }
+  };
+  const int *sel_unit = sel + (PERPOS ? (size_t)kvh * p.L : (size_t)bh0 * p.NB) * p.k;
+  auto request = [&](int hh, int I, Request &x) __attribute__((always_inline)) {
+    const int iq = I * kTile + q;
+    const Slice Qs(Q + (size_t)(bh0 + hh) * p.L * D, (size_t)p.L * D * sizeof(T));
+    load_op<T, D>(Qs, iq < p.L && iq >= p0 ? (unsigned)(iq * D + CPL * g) * (unsigned)sizeof(T) : kNowhere, x.q);
+    Sel::request(p, sel_unit, I, iq, lane, x.sel);
+    asm volatile("" ::: "memory");
+  };
+  // the (tile, head) pairs of the workgroup in turn, its wavefronts one each; the next one of this wavefront's
+  struct Item {
+    int I, hh;
+  };
+  const int dI = parts * W / heads, dh = parts * W - dI * heads;
+  auto item_after = [&](Item x) -> Item {
+    if (heads == 1) return {x.I - dI, 0};
+    x.hh += dh;
+    return x.hh >= heads ? Item{x.I - dI - 1, x.hh - heads} : Item{x.I - dI, x.hh};
+  };
+  const int start = part * W + wv;
+  Item it{NT - 1 - start / heads, start % heads};
+  Request now;
+  request(it.hh, max(it.I, 0), now);
+  if constexpr (RES) {
+    stage_pair<T, D, false>(Kh, Vh, small_lds, small_lds + pitch, p.L, T0, NT, p0, lane, wv, W);
+    __syncthreads();
+  }
+  using TileRows = std::conditional_t<RES, LdsRows<T, D>, Rows<T, D>>;
+  const TileRows Kr = [&] {
+    if constexpr (RES) return LdsRows<T, D>(small_lds, q, g);
+    else return Rows<T, D>(Kh, p.L, q, g);
+  }();
+  const TileRows Vr = [&] {
+    if constexpr (RES) return LdsRows<T, D>(small_lds + pitch, q, g);
+    else return Rows<T, D>(Vh, p.L, q, g);
+  }();
+  const float c2 = p.scale * kLog2eF, kc = Ops::kBf ? c2 : 1.0f;  // (kc: what a product of rows is still to be multiplied by)
+  unsigned *my_lds = reinterpret_cast<unsigned *>(small_lds + 2 * pitch) + wv * lt_words(p, PERPOS);
+  Word valid_keys[4];  // of the first tile
+#pragma unroll
+  for (int r = 0; r < 4; ++r) valid_keys[r] = elements_from(p0 & (kTile - 1), r);
+
+  const int I_first = p0 >= p.L ? NT : max(I_lo, T0);
+  const int h0 = bh0 % p.H;
+  for (; it.I >= I_first; it = item_after(it)) {
+    const int I = it.I, hh = it.hh, bh = bh0 + hh;
+    const int iq = I * kTile + q;
+    const bool active = iq < p.L && iq >= p0;
+    typename Ops::Row qf = now.q;
+    int first[Sel::kFirst];
+#pragma unroll
+    for (int i = 0; i < Sel::kFirst; ++i) first[i] = now.sel[i];
+    const Item next = item_after(it);
+    if (next.I >= I_first) request(next.hh, next.I, now);
+    Sel ls;
+    if constexpr (!kPicked)
+      ls.build(p, my_lds, PERPOS ? nullptr : sel_unit + (size_t)I * (kTile / BK) * p.k, sel_unit + (size_t)min(iq, p.L - 1) * p.k, active, I, iq,
+               p0, lane, first);
+    // the head's gate
+    const int h = h0 + hh;
+    const float *wg = gate_w + (size_t)h * 2 * D + (4 * g & (D - 1));
+    const float bias = gate_b ? gate_b[h] : 0.0f;
+    float w_lt[NMB][4], w_st[NMB][4];
+#pragma unroll
+    for (int mb = 0; mb < NMB; ++mb) {
+      load_n<4>(wg + 16 * mb, w_lt[mb]);
+      load_n<4>(wg + 16 * mb + D, w_st[mb]);
+    }
+    asm volatile("" ::: "memory");
+    Ops::scale(qf, c2);
+    // the long-term tiles of word w, whatever else the entries name
+    auto tiles_of = [&](int w) __attribute__((always_inline)) -> Word {
+      if constexpr (kPicked) return PickedTiles{sel_unit + (size_t)I * p.k, p.k, first[0]}.word(w, lane);
+      else if constexpr (PERPOS) return ls.all;
+      else return __ballot(ls.has_tile(min(w * 64 + lane, NT - 1)));
+    };
+    f32x4 a_lt[NACC], a_st[NACC];
+    clear(a_lt);
+    clear(a_st);
+    float l_lt = 0.0f, l_st = 0.0f, ref_lt = 0.0f, ref_st = 0.0f, s_max = 0.0f;
+    typename Ops::Row kf;
+    typename Ops::Col vf[NMB];
+    auto logits = [&]() -> f32x4 { return Ops::dot(kf, qf, f32x4{0.f, 0.f, 0.f, 0.f}); };  // (times kc)
+    auto add_lt = [&](const float (&e)[4]) __attribute__((always_inline)) {
+      l_lt += (e[0] + e[1]) + (e[2] + e[3]);
+      Ops::add(vf, e, a_lt);
+    };
+    auto add_st = [&](const float (&e)[4]) __attribute__((always_inline)) {
+      l_st += (e[0] + e[1]) + (e[2] + e[3]);
+      Ops::add(vf, e, a_st);
+    };
+    // one tile; the next one's keys are requested as soon as this one's are in the matrix cores, its values at the end
+    auto tile = [&](auto lt, auto st, auto masked, int t, int t_next, const Word (&m_lt)[4], const Word (&m_st)[4])
+                    __attribute__((always_inline)) {
+      constexpr bool LT = decltype(lt)::value, ST = decltype(st)::value, MASKED = decltype(masked)::value;
+      const f32x4 s = logits();
+      Kr.op(t_next, kf);
+      if constexpr (TileRows::kNear) Vr.col(t, vf);
+      s_max = fmaxf(fmaxf(s_max, fabsf(s[0])), fabsf(s[1]));
+      s_max = fmaxf(fmaxf(s_max, fabsf(s[2])), fabsf(s[3]));
+      float e[4], el[4], es[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) e[r] = __builtin_amdgcn_exp2f(kc * s[r]);
+      bool mine = true;
+      if constexpr (LT && (PERPOS || BK < kTile)) mine = ls.sees(q, t * kTile + 4 * g);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if constexpr (LT) el[r] = mine && (!MASKED || in_lanes(m_lt[r])) ? e[r] : 0.0f;
+        if constexpr (ST) es[r] = in_lanes(m_st[r]) ? e[r] : 0.0f;
+      }
+      if constexpr (LT) add_lt(el);
+      if constexpr (ST) add_st(es);
+      if constexpr (!TileRows::kNear) Vr.col(t_next, vf);
+    };
+    auto walk = [&]() __attribute__((always_inline)) {
+      constexpr auto yes = std::true_type{};
+      constexpr auto no = std::false_type{};
+      constexpr bool kOneWord = RES || PERPOS;
+      const int w0 = kOneWord ? 0 : T0 >> 6, wI = kOneWord ? 0 : I >> 6;
+      Kr.op(I, kf);
+      if constexpr (!TileRows::kNear) Vr.col(I, vf);
+      const Word at_I = tiles_of(wI);
+      const bool own = (at_I >> (I & 63)) & 1ull;
+      const bool before = (wI != w0 && (I & 63) == 0 ? tiles_of(wI - 1) : at_I) >> ((I - 1) & 63) & 1ull;
+      // of word w, the tiles from the first valid one to the last but one before I
+      auto rest_of = [&](int w) __attribute__((always_inline)) -> Word {
+        Word m = w == wI ? at_I : tiles_of(w);
+        if (w == w0) m &= ~0ull << (T0 & 63);
+        if (w == (I - 1) >> 6) m &= (1ull << ((I - 1) & 63)) - 1ull;
+        return w > (I - 1) >> 6 ? 0ull : m;
+      };
+      Word rest = I > T0 ? rest_of(w0) : 0ull;
+      auto next_of = [&](int w, Word m) __attribute__((always_inline)) -> int { return m ? 64 * w + __builtin_ctzll(m) : I; };
+      Word m_lt[4], m_st[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const Word ok = I == T0 ? valid_keys[r] : ~0ull;
+        m_lt[r] = own ? triangle(r, false) & ok : 0ull;
+        m_st[r] = nm.own[r] & ok;
+      }
+      tile(yes, yes, yes, I, max(I - 1, T0), m_lt, m_st);
+      if (I == T0) return;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        m_lt[r] = I - 1 == T0 ? valid_keys[r] : ~0ull;
+        m_st[r] = nm.next[r] & m_lt[r];
+      }
+      if (before) tile(yes, yes, yes, I - 1, next_of(w0, rest), m_lt, m_st);
+      else tile(no, yes, yes, I - 1, next_of(w0, rest), m_lt, m_st);
+      for (int w = w0;;) {
+        if (w == w0 && (rest >> (T0 & 63)) & 1ull) {
+          rest &= rest - 1;
+          tile(yes, no, yes, T0, next_of(w, rest), valid_keys, valid_keys);
+        }
+        while (rest) {
+          const int t = 64 * w + __builtin_ctzll(rest);
+          rest &= rest - 1;
+          tile(yes, no, no, t, next_of(w, rest), m_lt, m_st);
+        }
+        if (kOneWord || ++w > wI) break;
+        rest = rest_of(w);
+        Kr.op(next_of(w, rest), kf);
+        if constexpr (!TileRows::kNear) Vr.col(next_of(w, rest), vf);
+      }
+    };
+    auto far_keys = [&]() __attribute__((always_inline)) {
+      float qd[CPL];
+      Ops::floats(qf, qd);
+      float qw[CPL * 4];
+      if constexpr (D == 8) whole_row(qd, qw);
+      diagonals(p, I, T0, I, [&](int d) __attribute__((always_inline)) {
+        const int key = iq + kTile * d * (1 << g);
+        const bool ok = active & (key >= p0);
+        if constexpr (D == 8) {
+          const int t = max(I + d * (1 << g), T0);
+          float kr[D], vr[D];
+          Kr.whole(t, kr);
+          Vr.whole(t, vr);
+          const float x = dot_n(qw, kr, 0.0f);
+          s_max = fmaxf(s_max, ok ? fabsf(x) : 0.0f);
+          const float ex = ok ? __builtin_amdgcn_exp2f(kc * x) : 0.0f;
+          l_st += ex;
+          add_row(a_st, ex, vr);
+        } else {
+          float s[4], e[4], vo[4][NMB][4];
+#pragma unroll
+          for (int n = 0; n < 4; ++n) {
+            float kr[CPL];
+            Kr.row(max(I + d * (1 << n), T0), kr);
+            s[n] = dot_n(qd, kr, 0.0f);
+          }
+          phase_end<D>();
+#pragma unroll
+          for (int n = 0; n < 4; ++n) Vr.own(max(I + d * (1 << n), T0), vo[n]);
+          const float x = gather_g(s);
+          s_max = fmaxf(s_max, ok ? fabsf(x) : 0.0f);
+          const float ex = ok ? __builtin_amdgcn_exp2f(kc * x) : 0.0f;
+          l_st += ex;
+          spread_g(ex, e);
+          add_own(a_st, e, vo);
+        }
+      });
+    };
+    constexpr bool far_first = D == 32 && Ops::kBf;
+    if (far_first && p.sblk == 1) far_keys();
+    walk();
+    if (!far_first && p.sblk == 1) far_keys();
+    if (__builtin_expect(__ballot(!((s_max * kc <= kSmallLogit) & (abs_sum(a_lt) + abs_sum(a_st) < 1.0e37f))) != 0ull, 0)) {
+      // large logits, or values near the end of fp32's range or beyond: the row maxima of both branches, then the walk
+      // against them, tile by tile with every test
+      float x_lt = kNegInfF, x_st = kNegInfF;
+      auto each = [&](auto f) __attribute__((always_inline)) {
+        for (int w = T0 >> 6; w <= I >> 6; ++w) {
+          const Word m = tiles_of(w);
+          for (int t = max(T0, 64 * w); t <= min(I, 64 * w + 63); ++t) {
+            const bool in_lt = (m >> (t & 63)) & 1ull;
+            if (!in_lt && t < I - 1 && !(p.sblk == 1 && __popc(I - t) == 1)) continue;
+            Kr.op(t, kf);
+            const f32x4 s = logits() * kc;
+            const int key0 = t * kTile + 4 * g;
+            bool s_lt = in_lt, v_lt[4], v_st[4];
+            if (PERPOS || BK < kTile) s_lt &= ls.sees(q, key0);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const int dist = iq - (key0 + r);
+              const bool ok = (dist >= 0) & (key0 + r >= p0);
+              v_lt[r] = ok & s_lt;
+              v_st[r] = ok & ((dist < p.w) | ((p.sblk == 1) & (__popc(dist) == 1)));
+            }
+            f(t, s, v_lt, v_st);
+          }
+        }
+      };
+      each([&](int, const f32x4 &s, const bool (&v_lt)[4], const bool (&v_st)[4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          x_lt = fmaxf(x_lt, v_lt[r] ? s[r] : kNegInfF);
+          x_st = fmaxf(x_st, v_st[r] ? s[r] : kNegInfF);
+        }
+      });
+      x_lt = max_g(x_lt);
+      x_st = max_g(x_st);
+      ref_lt = x_lt == kNegInfF ? 0.0f : x_lt;
+      ref_st = x_st == kNegInfF ? 0.0f : x_st;
+      l_lt = l_st = 0.0f;
+      clear(a_lt);
+      clear(a_st);
+      each([&](int t, const f32x4 &s, const bool (&v_lt)[4], const bool (&v_st)[4]) __attribute__((always_inline)) {
+        Vr.col(t, vf);
+        float lost[4];
+        take_out<T, D>(vf, g, lost);
+        float el[4], es[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          el[r] = v_lt[r] ? __builtin_amdgcn_exp2f(s[r] - ref_lt) + lost[r] : 0.0f;
+          es[r] = v_st[r] ? __builtin_amdgcn_exp2f(s[r] - ref_st) + lost[r] : 0.0f;
+        }
+        add_lt(el);
+        add_st(es);
+      });
+#pragma unroll
+      for (int mb = 0; mb < NACC; ++mb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {  // (a row of the padding may have seen some of the padding)
+          a_lt[mb][r] = active ? a_lt[mb][r] : 0.0f;
+          a_st[mb][r] = active ? a_st[mb][r] : 0.0f;
+        }
+    }
+    // ---- both branches' row sums, long-term in the even lane groups, short-term in the odd ones; the lse and 1 / sum of each ----
+    const int el = fresh_lane(), eg = el >> 4, er = el & 15, ei = I * kTile + er;
+    float sum;
+    {
+      const u32x2_t a = __builtin_amdgcn_permlane16_swap(__float_as_uint(l_lt), __float_as_uint(l_st), false, false);
+      const unsigned u = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
+      const u32x2_t b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+      sum = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+    }
+    const bool ok = (ei < p.L) & (ei >= p0) & !(sum <= 0.0f);  // (a NaN stays one)
+    const unsigned inv = __float_as_uint(ok ? recip(sum) : 0.0f);
+    const u32x2_t invs = __builtin_amdgcn_permlane16_swap(inv, inv, false, false);
+    f32x4 o_lt[NMB], o_st[NMB];
+    total<D>(a_lt, o_lt);
+    total<D>(a_st, o_st);
+#pragma unroll
+    for (int mb = 0; mb < NMB; ++mb) {
+      o_lt[mb] *= __uint_as_float(invs[0]);
+      o_st[mb] *= __uint_as_float(invs[1]);
+    }
+
+    // ---- gate and blend (Eq. 18-19) ----
+    float z = 0.0f;
+#pragma unroll
+    for (int mb = 0; mb < NMB; ++mb)
+      if (16 * mb + 4 * eg < D) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) z = fmaf(w_st[mb][r], o_st[mb][r], fmaf(w_lt[mb][r], o_lt[mb][r], z));
+      }
+    z = sum_g(z) + bias;
+    const float alpha = sigmoid(z);
+    // (the next tile's rows have arrived before the stores go out: a wait for them behind those would be one for the stores)
+    now.arrived();
+    if (ei < p.L && ei >= row_lo) {
+      const unsigned at = (unsigned)ei * D;
+      const size_t head = (size_t)bh * p.L;
+      if (o_lt_out) store_row4<float, D, true>(o_lt_out + head * D + at, o_lt, eg);
+      if (o_st_out) store_row4<float, D, true>(o_st_out + head * D + at, o_st, eg);
+      f32x4 o[NMB];
+#pragma unroll
+      for (int mb = 0; mb < NMB; ++mb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[mb][r] = alpha * o_lt[mb][r] + (1.0f - alpha) * o_st[mb][r];
+      store_row4<T, D>(O + head * D + at, o, eg);
+      // log sum exp from a row's sum (see fwd_small_kernel)
+      const float ref = eg == 0 ? ref_lt : ref_st;
+      const float log = __builtin_amdgcn_logf(sum), missed = fmaf(sum, __builtin_amdgcn_exp2f(-log), -1.0f);
+      const float lse = ok ? fmaf(ref + log, kLn2F, fmaf(ref + log, kLn2Low, missed)) : 0.0f;
+      if (lse_lt_out && eg == 0) lse_lt_out[head + (unsigned)ei] = lse;
+      if (lse_st_out && eg == 1) lse_st_out[head + (unsigned)ei] = lse;
+    }
+  }
+  // positions before the first tile with a valid one: zeros
+  const int end = p0 >= p.L ? p.L : T0 * kTile;
+  if (end > row_lo)
+    for (int hh = 0; hh < heads; ++hh) {
+      const size_t first = (size_t)(bh0 + hh) * p.L + row_lo;
+      const int rows = end - row_lo, from = (part * W + wv) * 64 + lane, step = parts * W * 64;
+      zero_rows_from(O + first * D, rows * D, from, step);
+      if (o_lt_out) zero_rows_from(o_lt_out + first * D, rows * D, from, step);
+      if (o_st_out) zero_rows_from(o_st_out + first * D, rows * D, from, step);
+      for (int i = from; i < rows; i += step) {
+        if (lse_lt_out) lse_lt_out[first + i] = 0.0f;
+        if (lse_st_out) lse_st_out[first + i] = 0.0f;
+      }
+    }
+}
+
+// =============================================================================================
 // backward of one query tile (gate pass, dQ) and of one key tile (dK, dV)
 // =============================================================================================
 namespace {
@@ -1508,8 +2002,10 @@ __device__ __forceinline__ bool query_tile(const KParams &p, int I, int T0, int 
   float l2_st = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(in.lse_st.d, l_at, 0, 0)) * kLog2eF;
   if (!active) l2_lt = l2_st = kHugeF;
   LtSel<BK, PERPOS> ls;
+  int first[LtSel<BK, PERPOS>::kFirst];
+  ls.request(p, sel_head, I, iq, lane, first);
   ls.build(p, my_lds, PERPOS ? nullptr : sel_head + (size_t)I * (kTile / BK) * p.k,
-           PERPOS && active ? sel_head + (size_t)iq * p.k : nullptr, I, iq, p0, lane);
+           sel_head + (size_t)min(iq, p.L - 1) * p.k, active, I, iq, p0, lane, first);
 
   // ---- gate pass of the tile's rows ----
   Ops::floats(g_op, gr);
@@ -2450,7 +2946,21 @@ static void launch_fwd_small_t(const KParams &p, const FwdArgs &a, hipStream_t s
                          (const T *)a.V, a.valid_len, a.dense ? nullptr : a.sel, a.gate_w, a.gate_b, (T *)a.O,
                          (float *)a.o_lt, (float *)a.o_st, a.lse_lt, a.lse_st, hpg, pl.parts, p);
     };
-    if (pl.res && order_by_length(p, grid, perpos) && (perpos || (grid <= 2 * kCUs && p.L >= 128)))
+    const bool ordered = pl.res && order_by_length(p, grid, perpos) && (perpos || (grid <= 2 * kCUs && p.L >= 128));
+    if (near_form(p) && !a.dense) {
+      const NearMasks nm(p, false);
+      auto go = [&](auto kernel) {
+        want_lds(kernel, pl.lds);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * pl.waves), pl.lds, st, (const T *)a.Q, (const T *)a.K,
+                           (const T *)a.V, a.valid_len, a.sel, a.gate_w, a.gate_b, (T *)a.O, (float *)a.o_lt, (float *)a.o_st,
+                           a.lse_lt, a.lse_st, hpg, pl.parts, nm, p);
+      };
+      if (ordered) perpos ? go(fwd_near_kernel<T, D, BK, true, true, true>) : go(fwd_near_kernel<T, D, BK, false, true, true>);
+      else if (perpos) pl.res ? go(fwd_near_kernel<T, D, BK, true, true, false>) : go(fwd_near_kernel<T, D, BK, true, false, false>);
+      else pl.res ? go(fwd_near_kernel<T, D, BK, false, true, false>) : go(fwd_near_kernel<T, D, BK, false, false, false>);
+      return;
+    }
+    if (ordered)
       perpos ? go(fwd_small_kernel<T, D, BK, true, true, true>) : go(fwd_small_kernel<T, D, BK, false, true, true>);
     else if (perpos) pl.res ? go(fwd_small_kernel<T, D, BK, true, true, false>) : go(fwd_small_kernel<T, D, BK, true, false, false>);
     else pl.res ? go(fwd_small_kernel<T, D, BK, false, true, false>) : go(fwd_small_kernel<T, D, BK, false, false, false>);
