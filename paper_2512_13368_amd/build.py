@@ -24,6 +24,7 @@ SOURCES = {
     "mfma_fwd.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-fno-strict-aliasing"],
     "mfma_fwd4.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-fno-strict-aliasing"],
     "mfma_f32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+    "mfma_f32_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],  # (the same source, bf16 storage)
     "mfma_bwd.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "probe.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "out_proj.hip": ["-fno-strict-aliasing"],

@@ -111,12 +111,14 @@ struct SmallWs {
 };
 bool small_supported(const KParams &p);
 void launch_fwd_small(const KParams &p, int dtype, const FwdArgs &a, hipStream_t st);
+void launch_fwd_small_bf16(const KParams &p, const FwdArgs &a, hipStream_t st);
 bool fwd_positions_supported(const KParams &p);
 bool bwd_positions_supported(const KParams &p);
 size_t small_ws_bytes(const KParams &p, SmallWs *w, char *base);  // carves w from base, returns the total
 int small_partial_rows(const KParams &p, int dtype, int kv_groups);
 void launch_bwd_small(const KParams &p, int dtype, const BwdArgs &a, const SmallWs &w, unsigned stages, int kv_groups,
                       hipStream_t st);
+void launch_bwd_small_bf16(const KParams &p, const BwdArgs &a, const SmallWs &w, unsigned stages, int kv_groups, hipStream_t st);
 
 // mfma_bwd.hip: matrix-core dQ and dK/dV for bf16, d = 64, b in {32, 64}
 bool bwd_mfma_supported(const KParams &p, int dtype);

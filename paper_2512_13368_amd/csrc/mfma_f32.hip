@@ -754,14 +754,20 @@ struct LdsRows {
   }
 };
 // two heads' rows from tile T0 on into LDS; rows before p0 (the padding) and past the end are zeros.  CLEAN: elements that are
-// not finite become zeros too.  A wavefront requests up to four of its tiles (d = 32: two) before it waits for the first.
-template <typename T, int D, bool CLEAN>
+// not finite become zeros too.  A wavefront requests N of its tiles before it waits for the first.
+// between(): called once, by every wavefront, after the first requests and before the first row is written.
+template <int D>
+constexpr int kStageAhead = D == 32 ? 2 : 4;
+struct Nothing {
+  __device__ __forceinline__ void operator()() const {}
+};
+template <typename T, int D, bool CLEAN, int N = 1, typename Between = Nothing>
 __device__ __forceinline__ void stage_pair(const T *A, const T *B, float *a_lds, float *b_lds, int L, int T0, int NT, int p0, int lane, int wv,
-                                           int W)
+                                           int W, Between &&between = {})
 {
-  constexpr int N = D == 32 ? 2 : 4;
   const int q = lane & 15, g = lane >> 4;
   const Rows<T, D> Ar(A, L, q, g), Br(B, L, q, g);
+  if (T0 + wv >= NT) between();
   for (int t0 = T0 + wv; t0 < NT; t0 += N * W) {
     typename Operands<T, D>::Row x[N], y[N];
 #pragma unroll
@@ -771,7 +777,8 @@ __device__ __forceinline__ void stage_pair(const T *A, const T *B, float *a_lds,
       load_op<T, D>(Ar.s, off, x[n]);
       load_op<T, D>(Br.s, off, y[n]);
     }
-    asm volatile("" ::: "memory");  // (the requests are not moved to where their rows are used)
+    if constexpr (N > 1) asm volatile("" ::: "memory");  // (the requests are not moved to where their rows are used)
+    if (t0 == T0 + wv) between();
 #pragma unroll
     for (int n = 0; n < N; ++n) {
       const int t = t0 + n * W;
@@ -1510,7 +1517,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
 // us, with fwd_small_kernel / with this: B=256 H=2 L=200 d=32 19.6 / 17.8, B=2048 H=8 L=200 d=16 284 / 210, per position at d=8 240 /
 // 199, B=32 H=8 L=2000 d=8 (streamed) 60.5 / 53.5; selection + forward at B=4 H=2 L=50 d=32 10.2 / 9.3.
 template <typename T, int D, int BK, bool PERPOS, bool RES, bool ORDER>
-__global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(RES ? (D == 32 || PERPOS ? 4 : 5) : 5))) void fwd_near_kernel(
+__global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(D == 32 || (RES && PERPOS) ? 4 : 5))) void fwd_near_kernel(
     const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V, const int *__restrict__ valid_len,
     const int *__restrict__ sel, const float *__restrict__ gate_w, const float *__restrict__ gate_b,
     T *__restrict__ O, float *__restrict__ o_lt_out, float *__restrict__ o_st_out, float *__restrict__ lse_lt_out,
@@ -1557,11 +1564,11 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     }
   };
   const int *sel_unit = sel + (PERPOS ? (size_t)kvh * p.L : (size_t)bh0 * p.NB) * p.k;
-  auto request = [&](int hh, int I, Request &x) __attribute__((always_inline)) {
+  auto request = [&](int hh, int I, Request &x) __attribute__((always_inline)) {  // (any I: see QueryIn)
     const int iq = I * kTile + q;
     const Slice Qs(Q + (size_t)(bh0 + hh) * p.L * D, (size_t)p.L * D * sizeof(T));
     load_op<T, D>(Qs, iq < p.L && iq >= p0 ? (unsigned)(iq * D + CPL * g) * (unsigned)sizeof(T) : kNowhere, x.q);
-    Sel::request(p, sel_unit, I, iq, lane, x.sel);
+    Sel::request(p, sel_unit, max(I, 0), max(iq, 0), lane, x.sel);
     asm volatile("" ::: "memory");
   };
   // the (tile, head) pairs of the workgroup in turn, its wavefronts one each; the next one of this wavefront's
@@ -1577,9 +1584,9 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
   const int start = part * W + wv;
   Item it{NT - 1 - start / heads, start % heads};
   Request now;
-  request(it.hh, max(it.I, 0), now);
+  request(it.hh, it.I, now);
   if constexpr (RES) {
-    stage_pair<T, D, false>(Kh, Vh, small_lds, small_lds + pitch, p.L, T0, NT, p0, lane, wv, W);
+    stage_pair<T, D, false, kStageAhead<D>>(Kh, Vh, small_lds, small_lds + pitch, p.L, T0, NT, p0, lane, wv, W);
     __syncthreads();
   }
   using TileRows = std::conditional_t<RES, LdsRows<T, D>, Rows<T, D>>;
@@ -1608,7 +1615,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
     for (int i = 0; i < Sel::kFirst; ++i) first[i] = now.sel[i];
     const Item next = item_after(it);
-    if (next.I >= I_first) request(next.hh, next.I, now);
+    request(next.hh, next.I, now);
     Sel ls;
     if constexpr (!kPicked)
       ls.build(p, my_lds, PERPOS ? nullptr : sel_unit + (size_t)I * (kTile / BK) * p.k, sel_unit + (size_t)min(iq, p.L - 1) * p.k, active, I, iq,
@@ -1899,7 +1906,7 @@ namespace {
 // LDS of bwd_res_kernel, in floats: K and V, per head Q and dO (overlay: in the place of K and V), row constants, tile words and
 // selection bits, the wavefronts' selection words
 struct ResLayout {
-  int pitch, qg, rowc, words, waves, total;
+  int pitch, qg, rowc, words, waves, gates, red, total;
   // row: floats of a staged row
   __host__ __device__ ResLayout(const KParams &p, int row, bool perpos, int hpg, int overlay, int W)
   {
@@ -1910,7 +1917,10 @@ struct ResLayout {
     words = rowc + hpg * 6 * rows;
     waves = words + NT * ((NT + 31) / 32) + (perpos ? 2 * rows : p.b < kTile ? 2 * NT * ((p.NB + 31) / 32) : 0);
     waves = (waves + 3) / 4 * 4;
-    total = waves + W * lt_words(p, perpos);
+    // (the near form: the heads' gate rows, and every wavefront's gate sums of every head)
+    gates = waves + (W * lt_words(p, perpos) + 3) / 4 * 4;
+    red = gates + hpg * 2 * p.d;
+    total = near_form(p) ? red + hpg * W * (2 * p.d + 1) : waves + W * lt_words(p, perpos);
   }
 };
 
@@ -2515,6 +2525,593 @@ __device__ __forceinline__ void query_tiles_carefully(const KParams &p, int firs
                                        [](auto &&...) {});
 }
 
+// The gate gradient sums of a head's rows that a wavefront takes, in registers until leave().  d = 32: the walk needs the seventeen
+// registers, so every tile's sums over its rows go to LDS at once (mine[2D + 1], cleared by the caller): spilled registers in bf16 18 -> 1,
+// with two blocks to a tile in fp32 53 -> 24, a whole training step at B=180 H=4 L=150 d=32 b=8 fp32 98.5 us with them in registers, 89.2 so.
+template <int D>
+struct NearGateSums {
+  static constexpr int CPL = Geo<D>::CPL;
+  static constexpr bool kInLds = D == 32;
+  float bias, *mine, gl[kInLds ? 1 : CPL], gs[kInLds ? 1 : CPL], gb;
+  __device__ __forceinline__ NearGateSums(const float *gate_b, int h, float *mine_) : bias(gate_b ? gate_b[h] : 0.0f), mine(mine_)
+  {
+    zero_n(gl);
+    zero_n(gs);
+    gb = 0.0f;
+  }
+  __device__ __forceinline__ void add(float dz, const float (&ol)[CPL], const float (&os)[CPL], int lane)
+  {
+    if constexpr (kInLds) {
+      const int q = lane & 15, g = lane >> 4;
+      float x[CPL], y[CPL];
+#pragma unroll
+      for (int i = 0; i < CPL; ++i) {
+        x[i] = sum_row(dz * ol[i]);
+        y[i] = sum_row(dz * os[i]);
+      }
+      const float z = sum_row(dz);
+      if (q == 0) {
+#pragma unroll
+        for (int i = 0; i < CPL; ++i) {
+          mine[CPL * g + i] += x[i];
+          mine[D + CPL * g + i] += y[i];
+        }
+        if (g == 0) mine[2 * D] += z;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < CPL; ++i) {
+        gl[i] = fmaf(dz, ol[i], gl[i]);
+        gs[i] = fmaf(dz, os[i], gs[i]);
+      }
+      gb += dz;
+    }
+  }
+  __device__ __forceinline__ void leave(int lane)
+  {
+    if constexpr (!kInLds) {
+      const int q = lane & 15, g = lane >> 4;
+#pragma unroll
+      for (int i = 0; i < CPL; ++i) {
+        gl[i] = sum_row(gl[i]);
+        gs[i] = sum_row(gs[i]);
+      }
+      gb = sum_row(gb);
+      if (q == 0) {
+#pragma unroll
+        for (int i = 0; i < CPL; ++i) {
+          mine[CPL * g + i] = gl[i];
+          mine[D + CPL * g + i] = gs[i];
+        }
+        if (g == 0) mine[2 * D] = gb;
+      }
+    }
+  }
+};
+
+// THE NEAR FORM of the two (see there).  What a query tile needs from memory, requested a tile ahead.
+template <typename T, int D, int BK, bool PERPOS>
+struct QueryIn {
+  using Ops = Operands<T, D>;
+  typename Ops::Row q, g;
+  float ol[Geo<D>::CPL], os[Geo<D>::CPL], lse[2];
+  int sel[LtSel<BK, PERPOS>::kFirst];
+  // (d = 32: 27 or 35 registers, which the walk needs; the request goes out between the walk and the stores)
+  static constexpr bool kEarly = D < 32;
+  // any: is there such a tile?  (Nothing is read when there is none, but the registers are written: a request under a branch would
+  // keep what they held alive through the walk before it.)
+  __device__ __forceinline__ void request(const KParams &p, int I, int p0, int lane, const QueryHead &in, const int *sel_head, bool any)
+  {
+    I = any ? I : 0;
+    const int iq = I * kTile + (lane & 15);
+    const bool active = any & (iq < p.L) & (iq >= p0);
+    const unsigned at = active ? (unsigned)(iq * D + Geo<D>::CPL * (lane >> 4)) : kNowhere / 4;  // rows that take no part read zeros
+    load_op<T, D>(in.dO, at * (unsigned)sizeof(T), g);
+    load_n<float>(in.o_lt, at * 4u, ol);
+    load_n<float>(in.o_st, at * 4u, os);
+    load_op<T, D>(in.Q, at * (unsigned)sizeof(T), q);
+    const unsigned l_at = active ? 4u * (unsigned)iq : kNowhere;
+    lse[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(in.lse_lt.d, l_at, 0, 0));
+    lse[1] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(in.lse_st.d, l_at, 0, 0));
+    LtSel<BK, PERPOS>::request(p, sel_head, I, iq, lane, sel);
+    asm volatile("" ::: "memory");
+  }
+  // Waits for them: before a tile's stores go out, for behind those a wait for them would be one for the stores.
+  __device__ __forceinline__ void arrived()
+  {
+    unsigned *w = reinterpret_cast<unsigned *>(this);
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(QueryIn) / 4; ++i) asm volatile("" : "+v"(w[i]));
+  }
+};
+
+// Query tile I, whose rows are in `x`; more(x) requests the next one's there.  w_gate: the head's gate row in LDS.  sink: as in
+// query_tile, with the long-term tiles (tiles_of(word)) beside the selection.
+template <typename T, int D, int BK, bool PERPOS, bool ONE_WORD, typename TileRows, typename More, typename Sink>
+__device__ __forceinline__ bool near_query_tile(const KParams &p, int I, int T0, int NT, int p0, int lane, QueryIn<T, D, BK, PERPOS> &x,
+                                                const TileRows &Kr, const TileRows &Vr, const int *sel_head, unsigned *my_lds,
+                                                const float *w_gate, NearGateSums<D> &gate, const NearMasks &nm, const Word (&valid_keys)[4],
+                                                bool do_rows, bool do_dq, T *dQ_head, More &&more, Sink &&sink)
+{
+  constexpr int CPL = Geo<D>::CPL, NMB = Geo<D>::NMB, NACC = Geo<D>::NACC;
+  constexpr bool kDiag = kDiagonals<D, PERPOS>, kPicked = !PERPOS && BK == kTile;
+  using Ops = Operands<T, D>;
+  using Sel = LtSel<BK, PERPOS>;
+  const int q = lane & 15, g = lane >> 4;
+  const float c2 = p.scale * kLog2eF, kc = Ops::kBf ? c2 : 1.0f;  // (kc: what a product of rows is still to be multiplied by)
+  const int iq = I * kTile + q;
+  const bool active = iq < p.L && iq >= p0;
+  typename Ops::Row qf = x.q, g_op = x.g;
+  float ol[CPL], os[CPL], gr[CPL], wl[CPL], ws[CPL];
+  int first[Sel::kFirst];
+#pragma unroll
+  for (int i = 0; i < CPL; ++i) {
+    ol[i] = x.ol[i];
+    os[i] = x.os[i];
+  }
+#pragma unroll
+  for (int i = 0; i < Sel::kFirst; ++i) first[i] = x.sel[i];
+  const float l2_lt = active ? x.lse[0] * kLog2eF : kHugeF, l2_st = active ? x.lse[1] * kLog2eF : kHugeF;
+  if constexpr (QueryIn<T, D, BK, PERPOS>::kEarly) more(x);
+  load_n<CPL>(w_gate + CPL * g, wl);
+  load_n<CPL>(w_gate + D + CPL * g, ws);
+  Sel ls;
+  if constexpr (!kPicked)
+    ls.build(p, my_lds, PERPOS ? nullptr : sel_head + (size_t)I * (kTile / BK) * p.k, sel_head + (size_t)min(iq, p.L - 1) * p.k, active, I, iq,
+             p0, lane, first);
+  auto tiles_of = [&](int w) __attribute__((always_inline)) -> Word {
+    if constexpr (kPicked) return PickedTiles{sel_head + (size_t)I * p.k, p.k, first[0]}.word(w, lane);
+    else if constexpr (PERPOS) return ls.all;
+    else return __ballot(ls.has_tile(min(w * 64 + lane, NT - 1)));
+  };
+
+  // ---- gate pass of the tile's rows ----
+  Ops::floats(g_op, gr);
+  float al, dz, D_lt, D_st;
+  {
+    const float part[4] = {dot_n(gr, ol, 0.0f), dot_n(gr, os, 0.0f), dot_n(wl, ol, 0.0f), dot_n(ws, os, 0.0f)};
+    float sum[4];  // dO.o_lt, dO.o_st, Wg_lt.o_lt, Wg_st.o_st
+    spread_g(gather_g(part), sum);
+    al = sigmoid(gate.bias + sum[2] + sum[3]);
+    dz = (sum[0] - sum[1]) * al * (1.0f - al);
+    D_lt = al * sum[0] + dz * sum[2];
+    D_st = (1.0f - al) * sum[1] + dz * sum[3];
+  }
+  if (!active) al = dz = D_lt = D_st = 0.0f;
+  const int w0 = ONE_WORD ? 0 : T0 >> 6, wI = ONE_WORD ? 0 : I >> 6;
+  const Word at_I = tiles_of(wI);
+  if (do_rows) {
+    sink(I, al, dz, D_lt, D_st, l2_lt, l2_st, ls, qf, g_op, [&](int w) __attribute__((always_inline)) { return w == wI ? at_I : tiles_of(w); });
+    gate.add(dz, ol, os, lane);
+  }
+  if (!do_dq) return true;
+
+  Ops::scale(qf, c2);
+#pragma unroll
+  for (int i = 0; i < CPL; ++i) {
+    ol[i] = fmaf(al, gr[i], dz * wl[i]);         // dO_lt of this lane's row
+    os[i] = fmaf(1.0f - al, gr[i], dz * ws[i]);  // dO_st
+  }
+  const typename Ops::Split gl_op = Ops::split(ol), gs_op = Ops::split(os);
+  f32x4 dq_part[NACC], dq[NMB];
+  clear(dq_part);
+  typename Ops::Row kf, vf;
+  typename Ops::Col kt[NMB];
+  auto arg = [&](float s, float l) __attribute__((always_inline)) -> float { return Ops::kBf ? fmaf(kc, s, -l) : s - l; };
+  auto tile = [&](auto lt, auto st, auto masked, int t, int t_next, const Word (&m_lt)[4], const Word (&m_st)[4])
+                  __attribute__((always_inline)) {
+    constexpr bool LT = decltype(lt)::value, ST = decltype(st)::value, MASKED = decltype(masked)::value;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    const f32x4 s = Ops::dot(kf, qf, zero);  // (times kc)
+    f32x4 g_lt, g_st;
+    if constexpr (LT) g_lt = Ops::dot(vf, gl_op, zero);
+    if constexpr (ST) g_st = Ops::dot(vf, gs_op, zero);
+    Kr.op(t_next, kf);
+    Vr.op(t_next, vf);
+    bool mine = true;
+    if constexpr (LT && (PERPOS || BK < kTile)) mine = ls.sees(q, t * kTile + 4 * g);
+    float ds[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      ds[r] = 0.0f;
+      if constexpr (LT) {
+        const float e = __builtin_amdgcn_exp2f(arg(s[r], l2_lt));
+        ds[r] = (mine && (!MASKED || in_lanes(m_lt[r])) ? e : 0.0f) * (g_lt[r] - D_lt);
+      }
+      if constexpr (ST) {
+        const float f = __builtin_amdgcn_exp2f(arg(s[r], l2_st)), fm = in_lanes(m_st[r]) ? f : 0.0f;
+        ds[r] = LT ? fmaf(fm, g_st[r] - D_st, ds[r]) : fm * (g_st[r] - D_st);
+      }
+    }
+    if constexpr (TileRows::kNear) Kr.col(t, kt);
+    Ops::add(kt, ds, dq_part);
+    if constexpr (!TileRows::kNear) Kr.col(t_next, kt);
+  };
+  auto walk = [&]() __attribute__((always_inline)) {
+    constexpr auto yes = std::true_type{};
+    constexpr auto no = std::false_type{};
+    auto request = [&](int t) __attribute__((always_inline)) {
+      Kr.op(t, kf);
+      Vr.op(t, vf);
+      if constexpr (!TileRows::kNear) Kr.col(t, kt);
+    };
+    request(I);
+    const bool own = (at_I >> (I & 63)) & 1ull;
+    const bool before = (wI != w0 && (I & 63) == 0 ? tiles_of(wI - 1) : at_I) >> ((I - 1) & 63) & 1ull;
+    // of word w, the tiles from the first valid one to the last but one before I
+    auto rest_of = [&](int w) __attribute__((always_inline)) -> Word {
+      Word m = w == wI ? at_I : tiles_of(w);
+      if (w == w0) m &= ~0ull << (T0 & 63);
+      if (w == (I - 1) >> 6) m &= (1ull << ((I - 1) & 63)) - 1ull;
+      return w > (I - 1) >> 6 ? 0ull : m;
+    };
+    Word rest = I > T0 ? rest_of(w0) : 0ull;
+    auto next_of = [&](int w, Word m) __attribute__((always_inline)) -> int { return m ? 64 * w + __builtin_ctzll(m) : I; };
+    Word m_lt[4], m_st[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const Word ok = I == T0 ? valid_keys[r] : ~0ull;
+      m_lt[r] = own ? triangle(r, false) & ok : 0ull;
+      m_st[r] = nm.own[r] & ok;
+    }
+    tile(yes, yes, yes, I, max(I - 1, T0), m_lt, m_st);
+    if (I == T0) return;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      m_lt[r] = I - 1 == T0 ? valid_keys[r] : ~0ull;
+      m_st[r] = nm.next[r] & m_lt[r];
+    }
+    if (before) tile(yes, yes, yes, I - 1, next_of(w0, rest), m_lt, m_st);
+    else tile(no, yes, yes, I - 1, next_of(w0, rest), m_lt, m_st);
+    if constexpr (!kDiag) {  // (per position: a single word)
+      if (p.sblk == 1)
+        for (int d = 2; I - d >= T0; d *= 2) {
+          const int t = I - d;
+          const bool here = (rest >> (t & 63)) & 1ull;
+          rest &= ~(1ull << (t & 63));
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            m_lt[r] = t == T0 ? valid_keys[r] : ~0ull;
+            m_st[r] = triangle(r, false) & triangle(r, true) & m_lt[r];
+          }
+          if (TileRows::kNear || d == 2) request(t);
+          const int t_next = I - 2 * d >= T0 ? I - 2 * d : next_of(w0, rest);
+          if (here) tile(yes, yes, yes, t, t_next, m_lt, m_st);
+          else tile(no, yes, yes, t, t_next, m_lt, m_st);
+        }
+    }
+    for (int w = w0;;) {
+      if (w == w0 && (rest >> (T0 & 63)) & 1ull) {
+        rest &= rest - 1;
+        tile(yes, no, yes, T0, next_of(w, rest), valid_keys, valid_keys);
+      }
+      while (rest) {
+        const int t = 64 * w + __builtin_ctzll(rest);
+        rest &= rest - 1;
+        tile(yes, no, no, t, next_of(w, rest), m_lt, m_st);
+      }
+      if (ONE_WORD || ++w > wI) break;
+      rest = rest_of(w);
+      request(next_of(w, rest));
+    }
+  };
+  auto far_keys = [&]() __attribute__((always_inline)) {
+    float qd[CPL];
+    Ops::floats(qf, qd);
+    float qw[CPL * 4], ow[CPL * 4];
+    if constexpr (D == 8) {
+      whole_row(qd, qw);
+      whole_row(os, ow);
+    }
+    diagonals(p, I, T0, I, [&](int d) __attribute__((always_inline)) {
+      const bool ok = iq + kTile * d * (1 << g) >= p0;
+      if constexpr (D == 8) {
+        const int t = max(I + d * (1 << g), T0);
+        float kr[D], vr[D];
+        Kr.whole(t, kr);
+        Vr.whole(t, vr);
+        const float e = __builtin_amdgcn_exp2f(arg(dot_n(qw, kr, 0.0f), l2_st));
+        add_row(dq_part, ok ? e * (dot_n(ow, vr, 0.0f) - D_st) : 0.0f, kr);
+      } else {
+        float s[4], y[4], ko[4][NMB][4];
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+          float kr[CPL], vr[CPL];
+          const int t = max(I + d * (1 << n), T0);
+          Kr.row(t, kr);
+          Vr.row(t, vr);
+          s[n] = dot_n(qd, kr, 0.0f);
+          y[n] = dot_n(os, vr, 0.0f);
+          if constexpr (D == 16) own_of_row(kr, ko[n]);
+        }
+        phase_end<D>();
+        if constexpr (D != 16) {
+#pragma unroll
+          for (int n = 0; n < 4; ++n) Kr.own(max(I + d * (1 << n), T0), ko[n]);
+        }
+        const float e = __builtin_amdgcn_exp2f(arg(gather_g(s), l2_st)), gv = gather_g(y);
+        spread_g(ok ? e * (gv - D_st) : 0.0f, y);
+        add_own(dq_part, y, ko);
+      }
+    });
+  };
+  if (kDiag && kFarFirst<D> && p.sblk == 1) far_keys();
+  walk();
+  if (kDiag && !kFarFirst<D> && p.sblk == 1) far_keys();
+  total<D>(dq_part, dq);
+  if constexpr (QueryIn<T, D, BK, PERPOS>::kEarly) x.arrived();
+  else more(x);
+  const int el = fresh_lane(), ei = I * kTile + (el & 15);
+  if (ei < p.L) store_grad_row<T, D>(dQ_head + (unsigned)ei * D, dq, p.scale, ei >= p0, p, true, ei, el >> 4);
+  return __ballot(!((ei < p0) | (ei >= p.L) | finite(abs_sum(dq)))) == 0ull;
+}
+
+// Key tile J; its rows in kf, vf as in key_tile.  more() requests the next tile's rows, arrived() waits for them before the stores.
+template <typename T, int D, int BK, bool PERPOS, bool ONE_WORD, typename Src, typename More, typename Arrived>
+__device__ __forceinline__ bool near_key_tile(const KParams &p, int J, int T0, int NT, int p0, int lane, typename Operands<T, D>::Row kf,
+                                              const typename Operands<T, D>::Row vf, int hpg, const Src &src, const NearMasks &nm, T *dK_head,
+                                              T *dV_head, More &&more, Arrived &&arrived)
+{
+  constexpr int CPL = Geo<D>::CPL, NMB = Geo<D>::NMB, NACC = Geo<D>::NACC;
+  constexpr bool kDiag = kDiagonals<D, PERPOS>;
+  using Ops = Operands<T, D>;
+  const int q = lane & 15, g = lane >> 4;
+  const int NWb = (p.NB + 31) / 32;
+  const float c2 = p.scale * kLog2eF, kc = Ops::kBf ? c2 : 1.0f;  // (kc: what a product of rows is still to be multiplied by)
+  const int j = J * kTile + q;
+  f32x4 dk_part[NACC], dv_part[NACC];
+  clear(dk_part);
+  clear(dv_part);
+  Ops::scale(kf, c2);
+  const int Jb = j / BK;  // this lane's key block
+  // the query tiles of word w, from J on, that selected the tile
+  const int wJ = ONE_WORD ? 0 : J >> 6, wE = ONE_WORD ? 0 : (NT - 1) >> 6;
+  auto tiles_of = [&](int w) __attribute__((always_inline)) -> Word {
+    const int t = w * 64 + lane;
+    const unsigned tw = src.tile_word(min(max(t, T0), NT - 1), J >> 5);
+    return __ballot((t >= J) & (t < NT) & ((tw >> (J & 31)) & 1u));
+  };
+  const Word at_J = tiles_of(wJ);
+  constexpr bool kEarly = D < 32;
+  if constexpr (kEarly) more();
+
+  for (int hl = 0; hl < hpg; ++hl) {
+    const auto Qr = src.q_rows(hl);
+    const auto Gr = src.g_rows(hl);
+    constexpr bool near = decltype(src.q_rows(0))::kNear;
+    const float *wrow = src.gate_row(hl);
+    float t_lt = 0.0f, t_st = 0.0f;  // sum_i dz_i P_ij per branch
+    float wv_lt, wv_st;              // Wg_x . v_j
+    {
+      float wl[CPL], ws[CPL], vd[CPL];
+      Ops::floats(vf, vd);
+      load_n<CPL>(wrow + CPL * g, wl);
+      load_n<CPL>(wrow + D + CPL * g, ws);
+      wv_lt = sum_g(dot_n(wl, vd, 0.0f));
+      wv_st = sum_g(dot_n(ws, vd, 0.0f));
+    }
+    typename Ops::Row qa, ga;
+    typename Ops::Col qc[NMB], gc[NMB];
+    float al[4], dz[4], D_lt[4], D_st[4], l_lt[4], l_st[4];  // row constants of this lane's four query rows
+    auto consts = [&](int I) __attribute__((always_inline)) {
+      auto get = [&](int k, float (&x)[4]) { src.constant(hl, I, k, x); };
+      get(0, al);
+      get(1, dz);
+      get(2, D_lt);
+      get(3, D_st);
+      get(4, l_lt);
+      get(5, l_st);
+    };
+    auto arg = [&](float s, float l) __attribute__((always_inline)) -> float { return Ops::kBf ? fmaf(kc, s, -l) : s - l; };
+    auto tile = [&](auto lt, auto st, auto masked, int t, int t_next, const Word (&m_lt)[4], const Word (&m_st)[4])
+                    __attribute__((always_inline)) {
+      constexpr bool LT = decltype(lt)::value, ST = decltype(st)::value, MASKED = decltype(masked)::value;
+      if constexpr (near) consts(t);
+      const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+      const f32x4 s = Ops::dot(qa, kf, zero), gv = Ops::dot(ga, vf, zero);  // (s: times kc)
+      Qr.op(t_next, qa);
+      Gr.op(t_next, ga);
+      unsigned w4[4] = {1u, 1u, 1u, 1u};  // bit 0: the row selected this lane's key block
+      if constexpr (LT && PERPOS) {
+        const unsigned *sb = src.bits + (t * kTile + 4 * g) * 2 + (Jb >> 5);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) w4[r] = sb[2 * r] >> (Jb & 31);
+      } else if constexpr (LT && BK < kTile) {
+        const unsigned x = src.bits[(t * 2 + (g >> 1)) * NWb + min(Jb >> 5, NWb - 1)] >> (Jb & 31);
+        w4[0] = w4[1] = w4[2] = w4[3] = x;
+      }
+      float pc[4], ds[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        pc[r] = ds[r] = 0.0f;
+        if constexpr (LT) {
+          float pr = __builtin_amdgcn_exp2f(arg(s[r], l_lt[r]));
+          if constexpr (MASKED) pr = in_lanes(m_lt[r]) ? pr : 0.0f;
+          if constexpr (PERPOS || BK < kTile) pr = keep(pr, w4[r], 0);
+          pc[r] = al[r] * pr;
+          ds[r] = pr * fmaf(al[r], gv[r], fmaf(dz[r], wv_lt, -D_lt[r]));
+          t_lt = fmaf(dz[r], pr, t_lt);
+        }
+        if constexpr (ST) {
+          const float e = __builtin_amdgcn_exp2f(arg(s[r], l_st[r])), pr = in_lanes(m_st[r]) ? e : 0.0f;
+          const float as = 1.0f - al[r], x = fmaf(as, gv[r], fmaf(dz[r], wv_st, -D_st[r]));
+          pc[r] = LT ? fmaf(as, pr, pc[r]) : as * pr;
+          ds[r] = LT ? fmaf(pr, x, ds[r]) : pr * x;
+          t_st = fmaf(dz[r], pr, t_st);
+        }
+      }
+      if constexpr (!near) {
+        consts(t_next);
+      } else {
+        Qr.col(t, qc);
+        Gr.col(t, gc);
+      }
+      Ops::add(gc, pc, dv_part);  // dV^T += dO^T (a P), dK^T += Q^T dS
+      Ops::add(qc, ds, dk_part);
+      if constexpr (!near) {
+        Qr.col(t_next, qc);
+        Gr.col(t_next, gc);
+      }
+    };
+    auto request = [&](int t) __attribute__((always_inline)) {
+      Qr.op(t, qa);
+      Gr.op(t, ga);
+      if constexpr (!near) {
+        consts(t);
+        Qr.col(t, qc);
+        Gr.col(t, gc);
+      }
+    };
+    auto walk = [&]() __attribute__((always_inline)) {
+      constexpr auto yes = std::true_type{};
+      constexpr auto no = std::false_type{};
+      request(J);
+      const bool own = (at_J >> (J & 63)) & 1ull;
+      const bool after = (wE != wJ && ((J + 1) & 63) == 0 ? tiles_of(wJ + 1) : at_J) >> ((J + 1) & 63) & 1ull;
+      // of word w, the tiles from the second after J on
+      auto rest_of = [&](int w) __attribute__((always_inline)) -> Word {
+        Word m = w == wJ ? at_J : tiles_of(w);
+        if (w == wJ) m &= ~1ull << (J & 63);
+        if (w == (J + 1) >> 6) m &= ~(1ull << ((J + 1) & 63));
+        return m;
+      };
+      Word rest = rest_of(wJ);
+      auto next_of = [&](int w, Word m) __attribute__((always_inline)) -> int { return m ? 64 * w + __builtin_ctzll(m) : J; };
+      Word m_lt[4], m_st[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        m_lt[r] = own ? triangle(r, true) : 0ull;
+        m_st[r] = nm.own[r];
+      }
+      tile(yes, yes, yes, J, min(J + 1, NT - 1), m_lt, m_st);
+      if (J == NT - 1) return;
+      if (after) tile(yes, yes, no, J + 1, next_of(wJ, rest), m_lt, nm.next);
+      else tile(no, yes, no, J + 1, next_of(wJ, rest), m_lt, nm.next);
+      if constexpr (!kDiag) {  // (per position: a single word)
+        if (p.sblk == 1)
+          for (int d = 2; J + d < NT; d *= 2) {
+            const int t = J + d;
+            const bool here = (rest >> (t & 63)) & 1ull;
+            rest &= ~(1ull << (t & 63));
+#pragma unroll
+            for (int r = 0; r < 4; ++r) m_st[r] = triangle(r, false) & triangle(r, true);
+            if (near || d == 2) request(t);
+            const int t_next = J + 2 * d < NT ? J + 2 * d : next_of(wJ, rest);
+            if (here) tile(yes, yes, no, t, t_next, m_lt, m_st);
+            else tile(no, yes, no, t, t_next, m_lt, m_st);
+          }
+      }
+      for (int w = wJ;;) {
+        while (rest) {
+          const int t = 64 * w + __builtin_ctzll(rest);
+          rest &= rest - 1;
+          tile(yes, no, no, t, next_of(w, rest), m_lt, m_st);
+        }
+        if (ONE_WORD || ++w > wE) break;
+        rest = rest_of(w);
+        request(next_of(w, rest));
+      }
+    };
+    auto far_queries = [&]() __attribute__((always_inline)) {
+      float kd[CPL], vd[CPL];
+      Ops::floats(kf, kd);
+      Ops::floats(vf, vd);
+      float kw[CPL * 4], vw[CPL * 4];
+      if constexpr (D == 8) {
+        whole_row(kd, kw);
+        whole_row(vd, vw);
+      }
+      diagonals(p, J, J, NT - 1, [&](int d) __attribute__((always_inline)) {
+        // this lane group's distance
+        const int i = j + kTile * d * (1 << g), tg = min(J + d * (1 << g), NT - 1);
+        auto constant = [&](int k) { return src.row_constant(hl, tg, k); };
+        const bool ok = i < p.L;
+        if constexpr (D == 8) {
+          float qr[D], gr[D];
+          Qr.whole(tg, qr);
+          Gr.whole(tg, gr);
+          const float e = __builtin_amdgcn_exp2f(arg(dot_n(kw, qr, 0.0f), constant(5)));
+          const float pr = ok ? e : 0.0f, zd = constant(1), as = 1.0f - constant(0);
+          t_st = fmaf(zd, pr, t_st);
+          add_row(dv_part, as * pr, gr);
+          add_row(dk_part, pr * fmaf(as, dot_n(vw, gr, 0.0f), fmaf(zd, wv_st, -constant(3))), qr);
+        } else {
+          float s[4], x[4], qo[4][NMB][4], go[4][NMB][4];
+#pragma unroll
+          for (int n = 0; n < 4; ++n) {
+            float qr[CPL], gr[CPL];
+            const int t = min(J + d * (1 << n), NT - 1);
+            Qr.row(t, qr);
+            Gr.row(t, gr);
+            s[n] = dot_n(kd, qr, 0.0f);
+            x[n] = dot_n(vd, gr, 0.0f);
+            if constexpr (D == 16) {
+              own_of_row(qr, qo[n]);
+              own_of_row(gr, go[n]);
+            }
+          }
+          phase_end<D>();
+          if constexpr (D != 16) {
+#pragma unroll
+            for (int n = 0; n < 4; ++n) {
+              const int t = min(J + d * (1 << n), NT - 1);
+              Qr.own(t, qo[n]);
+              Gr.own(t, go[n]);
+            }
+          }
+          const float e = __builtin_amdgcn_exp2f(arg(gather_g(s), constant(5))), gd = gather_g(x);
+          const float pr = ok ? e : 0.0f;
+          const float zd = constant(1), as = 1.0f - constant(0);
+          t_st = fmaf(zd, pr, t_st);
+          spread_g(as * pr, s);
+          spread_g(pr * fmaf(as, gd, fmaf(zd, wv_st, -constant(3))), x);
+          add_own(dv_part, s, go);
+          add_own(dk_part, x, qo);
+        }
+      });
+    };
+    if (kDiag && kFarFirst<D> && p.sblk == 1) far_queries();
+    walk();
+    if (kDiag && !kFarFirst<D> && p.sblk == 1) far_queries();
+    // the gate part of dV: sum_i dz_i P_ij times the gate row of the branch
+    if constexpr (Geo<D>::kQuads) {  // (a lane's part of the sums, like the accumulators)
+#pragma unroll
+      for (int h = 0; h < NACC; ++h) {
+        float x[4], y[4];
+        load_n<4>(wrow + 4 * h, x);
+        load_n<4>(wrow + D + 4 * h, y);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dv_part[h][r] += fmaf(t_lt, x[r], t_st * y[r]);
+      }
+    } else {
+      t_lt = sum_g(t_lt);
+      t_st = sum_g(t_st);
+#pragma unroll
+      for (int mb = 0; mb < NMB; ++mb) {
+        float x[4], y[4];
+        load_n<4>(wrow + 16 * mb + 4 * g, x);
+        load_n<4>(wrow + D + 16 * mb + 4 * g, y);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dv_part[mb][r] += fmaf(t_lt, x[r], t_st * y[r]);
+      }
+    }
+  }
+  f32x4 dk[NMB], dv[NMB];
+  total<D>(dk_part, dk);
+  total<D>(dv_part, dv);
+  if constexpr (kEarly) arrived();
+  else more();
+  const int el = fresh_lane(), ej = J * kTile + (el & 15);
+  if (ej < p.L) {
+    store_grad_row<T, D>(dK_head + (unsigned)ej * D, dk, p.scale, ej >= p0, p, true, ej, el >> 4);
+    store_grad_row<T, D>(dV_head + (unsigned)ej * D, dv, 1.0f, ej >= p0, p, false, ej, el >> 4);
+  }
+  return __ballot(!((ej < p0) | (ej >= p.L) | finite(abs_sum(dk) + abs_sum(dv)))) == 0ull;
+}
+
+// the n-th tile of a wavefront of W: there and back, so that the shorter walks of a round meet the longer ones of the next
+__device__ __forceinline__ int to_and_fro(int n, int wv, int W) { return n * W + ((n & 1) ? W - 1 - wv : wv); }
+
 }  // namespace
 
 // =============================================================================================
@@ -2777,6 +3374,191 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
 }
 
 // =============================================================================================
+// backward, whole heads in LDS, THE NEAR FORM
+// =============================================================================================
+// As bwd_res_kernel, and as in fwd_near_kernel: what the next tile needs is on its way during the walk and has arrived before the stores
+// go out, masks are scalars, the selection stays in registers.  The (tile, head) pairs of a group are dealt out over all of its heads
+// without a barrier between them, there and back; Q and dO are requested before the barrier that closes K and V; the gate row lies
+// in LDS.  us, with bwd_res_kernel / with this: B=2048 H=8 L=200 d=16 605 / 550 (vector instructions 1390 a pair of tiles before),
+// per position at d=8 561 / 507, B=256 H=2 L=200 d=32 44.4 / 40.0.
+template <typename T, int D, int BK, bool PERPOS, bool ORDER>
+__global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(4))) void bwd_near_kernel(
+    const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V, const int *__restrict__ valid_len,
+    const int *__restrict__ sel, const float *__restrict__ gate_w, const float *__restrict__ gate_b,
+    const float *__restrict__ o_lt, const float *__restrict__ o_st, const float *__restrict__ lse_lt,
+    const float *__restrict__ lse_st, const T *__restrict__ dO, T *__restrict__ dQ, T *__restrict__ dK, T *__restrict__ dV,
+    float *__restrict__ partial, int hpg, int overlay, unsigned stages, NearMasks nm_q, NearMasks nm_k, KParams p)
+{
+  constexpr int GW = 2 * D + 1;
+  using Ops = Operands<T, D>;
+  extern __shared__ __attribute__((aligned(16))) float small_lds[];
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = blockDim.x >> 6;
+  if constexpr (!PERPOS) hpg = 1;
+  // (row, key/value head)
+  const Unit unit = [&]() -> Unit {
+    if constexpr (ORDER) return place_by_length(valid_len, p, p.H / hpg, wv);
+    else return {(int)blockIdx.x, clamp_len(valid_len[blockIdx.x / (p.H / hpg)], p.L)};
+  }();
+  const int bg = unit.id;
+  const int NT = (p.L + kTile - 1) / kTile, NWt = (NT + 31) / 32, NWb = (p.NB + 31) / 32;
+  const int p0 = p.L - unit.valid;
+  const int T0 = p0 / kTile;
+  const int q = lane & 15, g = lane >> 4;
+  const size_t head_kv = (size_t)bg * p.L * D;
+  const bool do_dq = stages & kBwdStageDQ, do_dkv = stages & kBwdStageDKV;  // (the gate pass belongs to the query tiles)
+  const ResLayout lay(p, kLdsRow<T, D>, PERPOS, hpg, overlay, W);
+  float *Ks = small_lds, *Vs = Ks + lay.pitch, *QG = small_lds + lay.qg, *rc = small_lds + lay.rowc;
+  float *gates = small_lds + lay.gates, *red = small_lds + lay.red;
+  unsigned *words = reinterpret_cast<unsigned *>(small_lds + lay.words), *bits = words + NT * NWt;
+  unsigned *my_lds = reinterpret_cast<unsigned *>(small_lds + lay.waves) + wv * lt_words(p, PERPOS);
+  const int bh0 = bg * hpg, h0 = bh0 % p.H;
+  const int count = p0 >= p.L ? 0 : NT - T0;  // tiles with a valid position
+
+  // ---- query tiles: pair (tile, head) number x is tile NT - 1 - x % count of head x / count ----
+  const int *sel_head = sel + (size_t)bg * (PERPOS ? p.L : p.NB) * p.k;
+  auto head = [&](int hl) { return QueryHead(Q, dO, o_lt, o_st, lse_lt, lse_st, bh0 + hl, p.L, D); };
+  const int pairs = count * hpg;
+  int n = 0, x = wv, hl = 0, at = wv;  // this wavefront's next pair: number, head, place in the head
+  while (at >= count && hl < hpg - 1) at -= count, ++hl;
+  QueryIn<T, D, BK, PERPOS> in;
+  in.request(p, NT - 1 - at, p0, lane, head(hl), sel_head, x < pairs);
+  for (int i = threadIdx.x; i < hpg * 2 * D; i += blockDim.x) gates[i] = gate_w[(size_t)h0 * 2 * D + i];
+  if constexpr (NearGateSums<D>::kInLds)
+    for (int i = threadIdx.x; i < hpg * W * GW; i += blockDim.x) red[i] = 0.0f;
+  // CLEAN: a row that sees a key or a value that is not finite has saved outputs that are not, and takes its NaN from there
+  stage_pair<T, D, true, kStageAhead<D>>(K + head_kv, V + head_kv, Ks, Vs, p.L, T0, NT, p0, lane, wv, W);
+  __syncthreads();
+  const LdsRows<T, D> Kr(Ks, q, g), Vr(Vs, q, g);
+  Word valid_keys[4];  // of the first tile
+#pragma unroll
+  for (int r = 0; r < 4; ++r) valid_keys[r] = elements_from(p0 & (kTile - 1), r);
+  for (int hh = 0; hh < hpg; ++hh) {
+    NearGateSums<D> gate(gate_b, h0 + hh, red + (hh * W + wv) * GW);
+    T *dQ_head = dQ + (size_t)(bh0 + hh) * p.L * D;
+    auto sink = [&](int I, float al, float dz, float D_lt, float D_st, float l2_lt, float l2_st, const LtSel<BK, PERPOS> &ls,
+                    const typename Ops::Row &q_op, const typename Ops::Row &g_op, auto &&tiles_of) __attribute__((always_inline)) {
+      float *c = rc + (hh * NT + I) * (6 * kTile);
+      c[lane] = g == 0 ? al : g == 1 ? dz : g == 2 ? D_lt : D_st;
+      if (g < 2) c[64 + lane] = g == 0 ? l2_lt : l2_st;
+      if (!overlay) {
+        LdsRows<T, D>::put(QG + 2 * hh * lay.pitch, I * kTile + q, g, q_op);
+        LdsRows<T, D>::put(QG + (2 * hh + 1) * lay.pitch, I * kTile + q, g, g_op);
+      }
+      if (hh > 0) return;
+      const Word all = tiles_of(0);
+      if (lane < NWt) words[I * NWt + lane] = lane == 0 ? (unsigned)all : (unsigned)(all >> 32);
+      if constexpr (PERPOS) {
+        if (g == 0) *reinterpret_cast<unsigned long long *>(bits + (I * kTile + q) * 2) = ls.row;
+      } else if constexpr (BK < kTile) {
+        for (int i = lane; i < 2 * NWb; i += 64) bits[I * 2 * NWb + i] = ls.bits[i];
+      }
+    };
+    while (x < pairs && hl <= hh) {
+      const int I = NT - 1 - at;
+      ++n;
+      const int x_next = to_and_fro(n, wv, W);
+      at += x_next - x;
+      x = x_next;
+      while (at >= count && hl < hpg) at -= count, ++hl;
+      near_query_tile<T, D, BK, PERPOS, true>(
+          p, I, T0, NT, p0, lane, in, Kr, Vr, sel_head, my_lds, gates + hh * 2 * D, gate, nm_q, valid_keys, true, do_dq, dQ_head,
+          [&](QueryIn<T, D, BK, PERPOS> &next) __attribute__((always_inline)) {
+            next.request(p, NT - 1 - at, p0, lane, head(min(hl, hpg - 1)), sel_head, x < pairs);
+          },
+          sink);
+    }
+    gate.leave(lane);
+  }
+
+  // ---- between the two: Q and dO take the place of K and V (overlay), the gate sums are closed ----
+  typename Ops::Row kf, vf, kn, vn;
+  const Rows<T, D> Kg(K + head_kv, p.L, q, g), Vg(V + head_kv, p.L, q, g);
+  auto fetch = [&](int u) __attribute__((always_inline)) {
+    const unsigned off = u < count ? Kg.row_off + (unsigned)(T0 + u) * Rows<T, D>::TB : kNowhere;
+    load_op<T, D>(Kg.s, off, kn);
+    load_op<T, D>(Vg.s, off, vn);
+    asm volatile("" ::: "memory");
+  };
+  if (do_dkv) fetch(wv);
+  if (overlay && do_dkv) {
+    for (int hh = 0; hh < hpg; ++hh) {
+      const size_t from = (size_t)(bh0 + hh) * p.L * D;
+      stage_pair<T, D, false, kStageAhead<D>>(Q + from, dO + from, QG + 2 * hh * lay.pitch, QG + (2 * hh + 1) * lay.pitch, p.L, T0, NT, p0, lane, wv, W,
+                              [&] {
+                                if (hh == 0) __syncthreads();
+                              });
+    }
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < hpg * GW; i += blockDim.x) {
+    const int hh = i / GW, c = i - hh * GW;
+    float a = 0.0f;
+    for (int w = 0; w < W; ++w) a += red[(hh * W + w) * GW + c];
+    partial[(size_t)(bh0 + hh) * GW + c] = a;
+  }
+  bool good = true;
+  if (do_dkv) {
+    struct {
+      const float *qg, *rc, *gates;
+      const unsigned *bits, *words;
+      int NT, NWt, q, g, pitch;
+      __device__ __forceinline__ LdsRows<T, D> q_rows(int hl) const { return LdsRows<T, D>(qg + 2 * hl * pitch, q, g); }
+      __device__ __forceinline__ LdsRows<T, D> g_rows(int hl) const { return LdsRows<T, D>(qg + (2 * hl + 1) * pitch, q, g); }
+      __device__ __forceinline__ const float *gate_row(int hl) const { return gates + hl * 2 * D; }
+      __device__ __forceinline__ void constant(int hl, int I, int k, float (&x)[4]) const
+      {
+        load_n<4>(rc + (hl * NT + I) * (6 * kTile) + 16 * k + 4 * g, x);
+      }
+      __device__ __forceinline__ float row_constant(int hl, int I, int k) const { return rc[(hl * NT + I) * (6 * kTile) + 16 * k + q]; }
+      __device__ __forceinline__ unsigned tile_word(int I, int w) const { return words[I * NWt + w]; }
+    } src = {QG, rc, gates, bits, words, NT, NWt, q, g, lay.pitch};
+    for (int n = 0, u = wv; u < count;) {
+      const int J = T0 + u;
+      kf = kn;
+      vf = vn;
+      u = to_and_fro(++n, wv, W);
+      good &= near_key_tile<T, D, BK, PERPOS, true>(
+          p, J, T0, NT, p0, lane, kf, vf, hpg, src, nm_k, dK + head_kv, dV + head_kv, [&]() __attribute__((always_inline)) { fetch(u); },
+          [&]() __attribute__((always_inline)) {
+            unsigned *a = reinterpret_cast<unsigned *>(&kn), *b = reinterpret_cast<unsigned *>(&vn);
+#pragma unroll
+            for (unsigned i = 0; i < sizeof(kn) / 4; ++i) asm volatile("" : "+v"(a[i]), "+v"(b[i]));
+          });
+    }
+    if (__builtin_expect(!good, 0)) {
+      struct {
+        const float *qg, *rc, *gate_w;
+        const unsigned *bits, *words;
+        int NT, NWt, q, g, pitch;
+        __device__ __forceinline__ LdsRows<T, D> q_rows(int hl) const { return LdsRows<T, D>(qg + 2 * hl * pitch, q, g); }
+        __device__ __forceinline__ LdsRows<T, D> g_rows(int hl) const { return LdsRows<T, D>(qg + (2 * hl + 1) * pitch, q, g); }
+        __device__ __forceinline__ const float *gate_row(int hl) const { return gate_w + (size_t)hl * 2 * D; }
+        __device__ __forceinline__ void constant(int hl, int I, int k, float (&x)[4]) const
+        {
+          load_n<4>(rc + (hl * NT + I) * (6 * kTile) + 16 * k + 4 * g, x);
+        }
+        __device__ __forceinline__ float row_constant(int hl, int I, int k) const { return rc[(hl * NT + I) * (6 * kTile) + 16 * k + q]; }
+        __device__ __forceinline__ unsigned tile_word(int I, int w) const { return words[I * NWt + w]; }
+      } again = {QG, rc, gate_w + (size_t)h0 * 2 * D, bits, words, NT, NWt, q, g, lay.pitch};
+      for (int n = 0, u = wv; u < count; u = to_and_fro(++n, wv, W)) {
+        Kg.op(T0 + u, kf);
+        Vg.op(T0 + u, vf);
+        key_tile<T, D, BK, PERPOS, true>(p, T0 + u, T0, NT, p0, lane, kf, vf, hpg, again, dK + head_kv, dV + head_kv);
+      }
+    }
+  }
+  // ---- positions before the first tile with a valid one: zeros ----
+  const int rows = min((NT - count) * kTile, p.L);
+  for (int hh = 0; hh < hpg; ++hh)
+    if (do_dq) zero_rows_from(dQ + (size_t)(bh0 + hh) * p.L * D, rows * D, (int)threadIdx.x, (int)blockDim.x);
+  if (do_dkv) {
+    zero_rows_from(dK + head_kv, rows * D, (int)threadIdx.x, (int)blockDim.x);
+    zero_rows_from(dV + head_kv, rows * D, (int)threadIdx.x, (int)blockDim.x);
+  }
+}
+
+// =============================================================================================
 // launchers
 // =============================================================================================
 namespace {
@@ -2900,37 +3682,6 @@ void with_small_dims(const KParams &p, F &&f)
 
 }  // namespace
 
-bool small_supported(const KParams &p) { return small_shape(p); }
-
-bool fwd_positions_supported(const KParams &p)
-{
-  return small_shape(p) && !p.bidir && p.NB <= 64 && p.nq == p.NB && pos_fwd_limit_bytes(p) <= kPosLimit;
-}
-bool bwd_positions_supported(const KParams &p) { return fwd_positions_supported(p) && pos_bwd_limit_bytes(p) <= kPosLimit; }
-
-size_t small_ws_bytes(const KParams &p, SmallWs *w, char *base)
-{
-  if (!small_shape(p)) return 0;
-  const size_t BH = (size_t)p.B * p.H, NT = (size_t)(p.L + kTile - 1) / kTile;
-  const size_t NWt = (NT + 31) / 32, NWb = ((size_t)p.NB + 31) / 32;
-  size_t off = 0;
-  auto take = [&](size_t bytes) {
-    char *at = base + off;
-    off += (bytes + 255) & ~(size_t)255;
-    return at;
-  };
-  w->rowc = reinterpret_cast<float *>(take(BH * NT * 6 * kTile * sizeof(float)));
-  w->tile_words = reinterpret_cast<unsigned *>(take(BH * NT * NWt * sizeof(unsigned)));
-  const size_t per_tile = std::max(p.b < kTile ? 2 * NWb : (size_t)1, bwd_positions_supported(p) ? (size_t)2 * kTile : (size_t)0);
-  w->sel_bits = reinterpret_cast<unsigned *>(take(BH * NT * per_tile * sizeof(unsigned)));
-  w->partial = reinterpret_cast<float *>(take(BH * NT * (2 * p.d + 1) * sizeof(float)));  // (at most one row per tile)
-  return off;
-}
-int small_partial_rows(const KParams &p, int dtype, int kv_groups)
-{
-  return bwd_plan(p, dtype, kv_groups > 0, kv_groups > 0 ? p.H / kv_groups : 1).parts;
-}
-
 template <typename T>
 static void launch_fwd_small_t(const KParams &p, const FwdArgs &a, hipStream_t st)
 {
@@ -2967,12 +3718,6 @@ static void launch_fwd_small_t(const KParams &p, const FwdArgs &a, hipStream_t s
   });
 }
 
-void launch_fwd_small(const KParams &p, int dtype, const FwdArgs &a, hipStream_t st)
-{
-  if (dtype == 0) launch_fwd_small_t<float>(p, a, st);
-  else launch_fwd_small_t<bf16_t>(p, a, st);
-}
-
 template <typename T>
 static void launch_bwd_small_t(const KParams &p, const BwdArgs &a, const SmallWs &w, unsigned stages, int kv_groups, hipStream_t st)
 {
@@ -2990,6 +3735,19 @@ static void launch_bwd_small_t(const KParams &p, const BwdArgs &a, const SmallWs
                            (const float *)a.o_st, a.lse_lt, a.lse_st, (const T *)a.dO, (T *)a.dQ, (T *)a.dK, (T *)a.dV, w.partial,
                            hpg, (int)pl.overlay, stages, p);
       };
+      if (near_form(p)) {
+        const NearMasks nm_q(p, false), nm_k(p, true);
+        auto go = [&](auto kernel) {
+          want_lds(kernel, pl.lds);
+          hipLaunchKernelGGL(kernel, dim3((unsigned)(p.B * p.H / hpg)), dim3(64 * pl.waves), pl.lds, st, (const T *)a.Q,
+                             (const T *)a.K, (const T *)a.V, a.valid_len, a.sel, a.gate_w, a.gate_b, (const float *)a.o_lt,
+                             (const float *)a.o_st, a.lse_lt, a.lse_st, (const T *)a.dO, (T *)a.dQ, (T *)a.dK, (T *)a.dV, w.partial,
+                             hpg, (int)pl.overlay, stages, nm_q, nm_k, p);
+        };
+        if (order_by_length(p, p.B * p.H / hpg, perpos)) perpos ? go(bwd_near_kernel<T, D, BK, true, true>) : go(bwd_near_kernel<T, D, BK, false, true>);
+        else perpos ? go(bwd_near_kernel<T, D, BK, true, false>) : go(bwd_near_kernel<T, D, BK, false, false>);
+        return;
+      }
       if (order_by_length(p, p.B * p.H / hpg, perpos)) perpos ? go(bwd_res_kernel<T, D, BK, true, true>) : go(bwd_res_kernel<T, D, BK, false, true>);
       else perpos ? go(bwd_res_kernel<T, D, BK, true, false>) : go(bwd_res_kernel<T, D, BK, false, false>);
       return;
@@ -3017,12 +3775,57 @@ static void launch_bwd_small_t(const KParams &p, const BwdArgs &a, const SmallWs
   });
 }
 
+#ifdef BLOSSOM_SMALL_BF16
+void launch_fwd_small_bf16(const KParams &p, const FwdArgs &a, hipStream_t st) { launch_fwd_small_t<bf16_t>(p, a, st); }
+void launch_bwd_small_bf16(const KParams &p, const BwdArgs &a, const SmallWs &w, unsigned stages, int kv_groups, hipStream_t st)
+{
+  launch_bwd_small_t<bf16_t>(p, a, w, stages, kv_groups, st);
+}
+#else
+bool small_supported(const KParams &p) { return small_shape(p); }
+
+bool fwd_positions_supported(const KParams &p)
+{
+  return small_shape(p) && !p.bidir && p.NB <= 64 && p.nq == p.NB && pos_fwd_limit_bytes(p) <= kPosLimit;
+}
+bool bwd_positions_supported(const KParams &p) { return fwd_positions_supported(p) && pos_bwd_limit_bytes(p) <= kPosLimit; }
+
+size_t small_ws_bytes(const KParams &p, SmallWs *w, char *base)
+{
+  if (!small_shape(p)) return 0;
+  const size_t BH = (size_t)p.B * p.H, NT = (size_t)(p.L + kTile - 1) / kTile;
+  const size_t NWt = (NT + 31) / 32, NWb = ((size_t)p.NB + 31) / 32;
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    char *at = base + off;
+    off += (bytes + 255) & ~(size_t)255;
+    return at;
+  };
+  w->rowc = reinterpret_cast<float *>(take(BH * NT * 6 * kTile * sizeof(float)));
+  w->tile_words = reinterpret_cast<unsigned *>(take(BH * NT * NWt * sizeof(unsigned)));
+  const size_t per_tile = std::max(p.b < kTile ? 2 * NWb : (size_t)1, bwd_positions_supported(p) ? (size_t)2 * kTile : (size_t)0);
+  w->sel_bits = reinterpret_cast<unsigned *>(take(BH * NT * per_tile * sizeof(unsigned)));
+  w->partial = reinterpret_cast<float *>(take(BH * NT * (2 * p.d + 1) * sizeof(float)));  // (at most one row per tile)
+  return off;
+}
+int small_partial_rows(const KParams &p, int dtype, int kv_groups)
+{
+  return bwd_plan(p, dtype, kv_groups > 0, kv_groups > 0 ? p.H / kv_groups : 1).parts;
+}
+
+void launch_fwd_small(const KParams &p, int dtype, const FwdArgs &a, hipStream_t st)
+{
+  if (dtype == 0) launch_fwd_small_t<float>(p, a, st);
+  else launch_fwd_small_bf16(p, a, st);
+}
+
 // gate pass and dQ, then dK/dV; kv_groups > 0: a.sel holds one row per position and group
 void launch_bwd_small(const KParams &p, int dtype, const BwdArgs &a, const SmallWs &w, unsigned stages, int kv_groups,
                       hipStream_t st)
 {
   if (dtype == 0) launch_bwd_small_t<float>(p, a, w, stages, kv_groups, st);
-  else launch_bwd_small_t<bf16_t>(p, a, w, stages, kv_groups, st);
+  else launch_bwd_small_bf16(p, a, w, stages, kv_groups, st);
 }
+#endif
 
 }  // namespace blossom
