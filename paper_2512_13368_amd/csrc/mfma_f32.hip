@@ -2631,7 +2631,7 @@ template <typename T, int D, int BK, bool PERPOS, bool ONE_WORD, typename TileRo
 __device__ __forceinline__ bool near_query_tile(const KParams &p, int I, int T0, int NT, int p0, int lane, QueryIn<T, D, BK, PERPOS> &x,
                                                 const TileRows &Kr, const TileRows &Vr, const int *sel_head, unsigned *my_lds,
                                                 const float *w_gate, NearGateSums<D> &gate, const NearMasks &nm, const Word (&valid_keys)[4],
-                                                bool do_rows, bool do_dq, T *dQ_head, More &&more, Sink &&sink)
+                                                bool do_rows, bool do_dq, T *dQ_head, More &&more, Sink &&sink, float *turn = nullptr)
 {
   constexpr int CPL = Geo<D>::CPL, NMB = Geo<D>::NMB, NACC = Geo<D>::NACC;
   constexpr bool kDiag = kDiagonals<D, PERPOS>, kPicked = !PERPOS && BK == kTile;
@@ -2702,6 +2702,7 @@ __device__ __forceinline__ bool near_query_tile(const KParams &p, int I, int T0,
                   __attribute__((always_inline)) {
     constexpr bool LT = decltype(lt)::value, ST = decltype(st)::value, MASKED = decltype(masked)::value;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (!TileRows::kNear) LdsRows<T, D>::put(turn, q, g, kf);
     const f32x4 s = Ops::dot(kf, qf, zero);  // (times kc)
     f32x4 g_lt, g_st;
     if constexpr (LT) g_lt = Ops::dot(vf, gl_op, zero);
@@ -2724,8 +2725,8 @@ __device__ __forceinline__ bool near_query_tile(const KParams &p, int I, int T0,
       }
     }
     if constexpr (TileRows::kNear) Kr.col(t, kt);
+    else LdsRows<T, D>(turn, q, g).col(0, kt);
     Ops::add(kt, ds, dq_part);
-    if constexpr (!TileRows::kNear) Kr.col(t_next, kt);
   };
   auto walk = [&]() __attribute__((always_inline)) {
     constexpr auto yes = std::true_type{};
@@ -2733,7 +2734,6 @@ __device__ __forceinline__ bool near_query_tile(const KParams &p, int I, int T0,
     auto request = [&](int t) __attribute__((always_inline)) {
       Kr.op(t, kf);
       Vr.op(t, vf);
-      if constexpr (!TileRows::kNear) Kr.col(t, kt);
     };
     request(I);
     const bool own = (at_I >> (I & 63)) & 1ull;
@@ -2850,7 +2850,7 @@ __device__ __forceinline__ bool near_query_tile(const KParams &p, int I, int T0,
 template <typename T, int D, int BK, bool PERPOS, bool ONE_WORD, typename Src, typename More, typename Arrived>
 __device__ __forceinline__ bool near_key_tile(const KParams &p, int J, int T0, int NT, int p0, int lane, typename Operands<T, D>::Row kf,
                                               const typename Operands<T, D>::Row vf, int hpg, const Src &src, const NearMasks &nm, T *dK_head,
-                                              T *dV_head, More &&more, Arrived &&arrived)
+                                              T *dV_head, More &&more, Arrived &&arrived, float *turn = nullptr)
 {
   constexpr int CPL = Geo<D>::CPL, NMB = Geo<D>::NMB, NACC = Geo<D>::NACC;
   constexpr bool kDiag = kDiagonals<D, PERPOS>;
@@ -2893,8 +2893,14 @@ __device__ __forceinline__ bool near_key_tile(const KParams &p, int J, int T0, i
     typename Ops::Row qa, ga;
     typename Ops::Col qc[NMB], gc[NMB];
     float al[4], dz[4], D_lt[4], D_st[4], l_lt[4], l_st[4];  // row constants of this lane's four query rows
+    // streamed: the tiles' rows go through this wavefront's part of LDS (see turn_floats), the constants 16 bytes a lane
+    constexpr int kTurn = kTile * kLdsRow<T, D>;
+    float raw[4] = {0.f, 0.f, 0.f, 0.f};
     auto consts = [&](int I) __attribute__((always_inline)) {
-      auto get = [&](int k, float (&x)[4]) { src.constant(hl, I, k, x); };
+      auto get = [&](int k, float (&x)[4]) {
+        if constexpr (near) src.constant(hl, I, k, x);
+        else load_n<4>(turn + 2 * kTurn + 16 * k + 4 * g, x);
+      };
       get(0, al);
       get(1, dz);
       get(2, D_lt);
@@ -2906,11 +2912,17 @@ __device__ __forceinline__ bool near_key_tile(const KParams &p, int J, int T0, i
     auto tile = [&](auto lt, auto st, auto masked, int t, int t_next, const Word (&m_lt)[4], const Word (&m_st)[4])
                     __attribute__((always_inline)) {
       constexpr bool LT = decltype(lt)::value, ST = decltype(st)::value, MASKED = decltype(masked)::value;
-      if constexpr (near) consts(t);
+      if constexpr (!near) {
+        LdsRows<T, D>::put(turn, q, g, qa);
+        LdsRows<T, D>::put(turn + kTurn, q, g, ga);
+        if (lane < 24) store_lds(turn + 2 * kTurn + 4 * lane, raw);
+      }
+      consts(t);
       const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
       const f32x4 s = Ops::dot(qa, kf, zero), gv = Ops::dot(ga, vf, zero);  // (s: times kc)
       Qr.op(t_next, qa);
       Gr.op(t_next, ga);
+      if constexpr (!near) src.constants(hl, t_next, lane, raw);
       unsigned w4[4] = {1u, 1u, 1u, 1u};  // bit 0: the row selected this lane's key block
       if constexpr (LT && PERPOS) {
         const unsigned *sb = src.bits + (t * kTile + 4 * g) * 2 + (Jb >> 5);
@@ -2940,27 +2952,20 @@ __device__ __forceinline__ bool near_key_tile(const KParams &p, int J, int T0, i
           t_st = fmaf(dz[r], pr, t_st);
         }
       }
-      if constexpr (!near) {
-        consts(t_next);
-      } else {
+      if constexpr (near) {
         Qr.col(t, qc);
         Gr.col(t, gc);
+      } else {
+        LdsRows<T, D>(turn, q, g).col(0, qc);
+        LdsRows<T, D>(turn + kTurn, q, g).col(0, gc);
       }
       Ops::add(gc, pc, dv_part);  // dV^T += dO^T (a P), dK^T += Q^T dS
       Ops::add(qc, ds, dk_part);
-      if constexpr (!near) {
-        Qr.col(t_next, qc);
-        Gr.col(t_next, gc);
-      }
     };
     auto request = [&](int t) __attribute__((always_inline)) {
       Qr.op(t, qa);
       Gr.op(t, ga);
-      if constexpr (!near) {
-        consts(t);
-        Qr.col(t, qc);
-        Gr.col(t, gc);
-      }
+      if constexpr (!near) src.constants(hl, t, lane, raw);
     };
     auto walk = [&]() __attribute__((always_inline)) {
       constexpr auto yes = std::true_type{};
@@ -3109,6 +3114,15 @@ __device__ __forceinline__ bool near_key_tile(const KParams &p, int J, int T0, i
   return __ballot(!((ej < p0) | (ej >= p.L) | finite(abs_sum(dk) + abs_sum(dv)))) == 0ull;
 }
 
+// A wavefront's part of LDS where streamed tiles are turned: `tensors` tiles of rows, read back by columns (an operand by columns is
+// four loads and more of one element a lane, sixteen vector-memory instructions a tile in dK/dV, whose address unit they filled), and
+// the tile's row constants.
+constexpr int kStreamWaves = 4;
+template <typename T, int D>
+constexpr int turn_floats(int tensors)
+{
+  return tensors * kTile * kLdsRow<T, D> + 6 * kTile;
+}
 // the n-th tile of a wavefront of W: there and back, so that the shorter walks of a round meet the longer ones of the next
 __device__ __forceinline__ int to_and_fro(int n, int wv, int W) { return n * W + ((n & 1) ? W - 1 - wv : wv); }
 
@@ -3559,6 +3573,187 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
 }
 
 // =============================================================================================
+// backward, heads streamed from memory, THE NEAR FORM
+// =============================================================================================
+// As bwd_dq_small_kernel and bwd_dkv_small_kernel, and as bwd_near_kernel.  Tiles are turned in LDS (turn_floats): dK/dV issued sixteen
+// vector-memory instructions a tile and waited for the address unit, five now.  us, before / now, B=32 H=8 L=2000 d=8: dQ 70 / 64, dK/dV
+// 104 / 83; a whole step 240 / 202, at B=16 H=8 L=1500 d=16 150 / 132.  (The forward's values turned the same way: 53.3 / 52.5 and, at
+// d=16, slower: its five instructions a tile stay.)
+template <typename T, int D, int BK, bool PERPOS>
+__global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(D == 8 ? 5 : 4))) void bwd_dq_near_kernel(
+    const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V, const int *__restrict__ valid_len,
+    const int *__restrict__ sel, const float *__restrict__ gate_w, const float *__restrict__ gate_b,
+    const float *__restrict__ o_lt, const float *__restrict__ o_st, const float *__restrict__ lse_lt,
+    const float *__restrict__ lse_st, const T *__restrict__ dO, T *__restrict__ dQ, SmallWs ws, int hpg, int parts,
+    unsigned stages, NearMasks nm, KParams p)
+{
+  constexpr int GW = 2 * D + 1;
+  extern __shared__ __attribute__((aligned(16))) float small_lds[];  // the wavefronts' selection words
+  __shared__ __attribute__((aligned(16))) float gate_s[2 * D];
+  __shared__ float red[kStreamWaves][GW];
+  __shared__ __attribute__((aligned(16))) float turn_s[kStreamWaves][turn_floats<T, D>(1)];
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = blockDim.x >> 6;
+  const unsigned vid = mfma::xcd_spread(blockIdx.x, gridDim.x / parts, parts);
+  const int bh = (int)(vid / parts), part = (int)(vid % parts);
+  const int b = bh / p.H, h = bh - b * p.H;
+  const int NT = (p.L + kTile - 1) / kTile, NWt = (NT + 31) / 32;
+  const int p0 = p.L - clamp_len(valid_len[b], p.L);
+  const int T0 = p0 / kTile;
+  const int I_first = p0 >= p.L ? NT : T0;
+  const int q = lane & 15, g = lane >> 4;
+  const int kvh = PERPOS ? bh / hpg : bh;
+  const int *sel_head = sel + (size_t)kvh * (PERPOS ? p.L : p.NB) * p.k;
+  const QueryHead head(Q, dO, o_lt, o_st, lse_lt, lse_st, bh, p.L, D);
+  int I = NT - 1 - (part * W + wv);
+  QueryIn<T, D, BK, PERPOS> in;
+  in.request(p, I, p0, lane, head, sel_head, I >= I_first);
+  for (int i = threadIdx.x; i < 2 * D; i += blockDim.x) gate_s[i] = gate_w[(size_t)h * 2 * D + i];
+  const Rows<T, D> Kr(K + (size_t)kvh * p.L * D, p.L, q, g), Vr(V + (size_t)kvh * p.L * D, p.L, q, g);
+  float *mine = red[wv];
+  if (lane < GW) mine[lane] = 0.0f;
+  if (lane + 64 < GW) mine[lane + 64] = 0.0f;
+  NearGateSums<D> gate(gate_b, h, mine);
+  unsigned *my_lds = reinterpret_cast<unsigned *>(small_lds) + wv * lt_words(p, PERPOS);
+  T *dQ_head = dQ + (size_t)bh * p.L * D;
+  const bool do_rows = stages & kBwdStageGate, do_dq = stages & kBwdStageDQ;
+  Word valid_keys[4];  // of the first tile
+#pragma unroll
+  for (int r = 0; r < 4; ++r) valid_keys[r] = elements_from(p0 & (kTile - 1), r);
+  auto sink = [&](int I, float al, float dz, float D_lt, float D_st, float l2_lt, float l2_st, const LtSel<BK, PERPOS> &ls, const auto &,
+                  const auto &, auto &&tiles_of) __attribute__((always_inline)) {
+    const int el = fresh_lane(), eq = el & 15, eg = el >> 4;
+    float *rc = ws.rowc + ((size_t)bh * NT + I) * (6 * kTile);
+    // lane group 0 writes alpha, group 1 dz, 2 D_lt, 3 D_st; groups 0 and 1 then the two lse
+    rc[el] = eg == 0 ? al : eg == 1 ? dz : eg == 2 ? D_lt : D_st;
+    if (eg < 2) rc[64 + el] = eg == 0 ? l2_lt : l2_st;
+    if (PERPOS && bh % hpg != 0) return;
+    unsigned *words = ws.tile_words + ((size_t)kvh * NT + I) * NWt;
+    for (int w = 0; w <= I >> 6; ++w) {  // (no key tile after I asks)
+      const Word m = tiles_of(w);
+      if (el < min(2, NWt - 2 * w)) words[2 * w + el] = el == 0 ? (unsigned)m : (unsigned)(m >> 32);
+    }
+    if constexpr (PERPOS) {
+      if (eg == 0) *reinterpret_cast<unsigned long long *>(ws.sel_bits + ((size_t)kvh * NT * kTile + I * kTile + eq) * 2) = ls.row;
+    } else if constexpr (BK < kTile) {
+      for (int i = el; i < 2 * ls.NWb; i += 64) ws.sel_bits[((size_t)kvh * NT + I) * 2 * ls.NWb + i] = ls.bits[i];
+    }
+  };
+  __syncthreads();
+  bool good = true;
+  while (I >= I_first) {
+    const int now = I;
+    I -= parts * W;
+    good &= near_query_tile<T, D, BK, PERPOS, PERPOS>(
+        p, now, T0, NT, p0, lane, in, Kr, Vr, sel_head, my_lds, gate_s, gate, nm, valid_keys, do_rows, do_dq, dQ_head,
+        [&](QueryIn<T, D, BK, PERPOS> &next) __attribute__((always_inline)) { next.request(p, I, p0, lane, head, sel_head, I >= I_first); }, sink,
+        turn_s[wv]);
+  }
+  if (do_rows) {
+    gate.leave(lane);
+    __syncthreads();
+    for (int c = threadIdx.x; c < GW; c += blockDim.x) {
+      float a = 0.0f;
+      for (int w = 0; w < W; ++w) a += red[w][c];
+      ws.partial[((size_t)bh * parts + part) * GW + c] = a;
+    }
+  }
+  if (__builtin_expect(!good, 0))
+    query_tiles_carefully<T, D, BK, PERPOS>(p, part * W + wv, parts * W, T0, NT, p0, lane, head, Kr, Vr, sel_head, my_lds, gate_w, gate_b, h,
+                                            dQ_head);
+  // positions before the first tile with a valid one: zeros
+  if (do_dq)
+    zero_rows_from(dQ_head, min(I_first * kTile, p.L) * D, part * (int)blockDim.x + (int)threadIdx.x, parts * (int)blockDim.x);
+}
+
+template <typename T, int D, int BK, bool PERPOS>
+__global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(D == 32 ? 3 : 4))) void bwd_dkv_near_kernel(
+    const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V, const int *__restrict__ valid_len,
+    const float *__restrict__ gate_w, const T *__restrict__ dO, SmallWs ws, T *__restrict__ dK, T *__restrict__ dV, int hpg, int parts,
+    NearMasks nm, KParams p)
+{
+  __shared__ __attribute__((aligned(16))) float turn_s[kStreamWaves][turn_floats<T, D>(2)];
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = blockDim.x >> 6;
+  const unsigned vid = mfma::xcd_spread(blockIdx.x, gridDim.x / parts, parts);
+  const int bg = (int)(vid / parts), part = (int)(vid % parts);
+  const int NT = (p.L + kTile - 1) / kTile, NWt = (NT + 31) / 32, NWb = (p.NB + 31) / 32;
+  const int p0 = p.L - clamp_len(valid_len[bg / (p.H / hpg)], p.L);
+  const int T0 = p0 / kTile;
+  const int count = p0 >= p.L ? 0 : NT - T0;  // tiles with a valid position
+  const int q = lane & 15, g = lane >> 4;
+  const size_t head_kv = (size_t)bg * p.L * D;
+  const Rows<T, D> Kr(K + head_kv, p.L, q, g), Vr(V + head_kv, p.L, q, g);
+  typename Operands<T, D>::Row kf, vf, kn, vn;
+  auto fetch = [&](int J) __attribute__((always_inline)) {
+    const unsigned off = J < NT && count > 0 ? Kr.row_off + (unsigned)J * Rows<T, D>::TB : kNowhere;
+    load_op<T, D>(Kr.s, off, kn);
+    load_op<T, D>(Vr.s, off, vn);
+    asm volatile("" ::: "memory");
+  };
+  // (the first tile of this wavefront's that is not before T0)
+  const int first = part * W + wv, step = parts * W;
+  const int J0 = first >= T0 ? first : first + (T0 - first + step - 1) / step * step;
+  fetch(J0);
+  struct {
+    const T *Q, *dO;
+    const float *rowc, *gate_w;
+    const unsigned *bits;
+    Slice words;
+    int bh0, H, L, NT, NWt, q, g;
+    __device__ __forceinline__ Rows<T, D> q_rows(int hl) const { return Rows<T, D>(Q + (size_t)(bh0 + hl) * L * D, L, q, g); }
+    __device__ __forceinline__ Rows<T, D> g_rows(int hl) const { return Rows<T, D>(dO + (size_t)(bh0 + hl) * L * D, L, q, g); }
+    __device__ __forceinline__ const float *gate_row(int hl) const { return gate_w + (size_t)((bh0 + hl) % H) * 2 * D; }
+    __device__ __forceinline__ void constant(int hl, int I, int k, float (&x)[4]) const
+    {
+      const Slice rc(rowc + (size_t)(bh0 + hl) * NT * (6 * kTile), (size_t)NT * (6 * kTile) * 4);
+      load_n<float>(rc, (unsigned)(I * (6 * kTile) + 16 * k + 4 * g) * 4u, x);
+    }
+    __device__ __forceinline__ void constants(int hl, int I, int lane, float (&x)[4]) const  // all of them, 16 bytes a lane
+    {
+      const Slice rc(rowc + (size_t)(bh0 + hl) * NT * (6 * kTile), (size_t)NT * (6 * kTile) * 4);
+      load_n<float>(rc, lane < 24 ? (unsigned)(I * (6 * kTile) + 4 * lane) * 4u : kNowhere, x);
+    }
+    __device__ __forceinline__ float row_constant(int hl, int I, int k) const  // of row q of tile I
+    {
+      const Slice rc(rowc + (size_t)(bh0 + hl) * NT * (6 * kTile), (size_t)NT * (6 * kTile) * 4);
+      return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rc.d, (unsigned)(I * (6 * kTile) + 16 * k + q) * 4u, 0, 0));
+    }
+    __device__ __forceinline__ unsigned tile_word(int I, int w) const
+    {
+      return __builtin_amdgcn_raw_buffer_load_b32(words.d, 4u * (unsigned)(I * NWt + w), 0, 0);
+    }
+  } src = {Q, dO, ws.rowc, gate_w, ws.sel_bits + (size_t)bg * (PERPOS ? NT * kTile * 2 : NT * 2 * NWb),
+           Slice(ws.tile_words + (size_t)bg * NT * NWt, (size_t)NT * NWt * 4), bg * hpg, p.H, p.L, NT, NWt, q, g};
+  bool good = true;
+  if (count > 0)
+    for (int J = J0; J < NT;) {
+      const int now = J;
+      kf = kn;
+      vf = vn;
+      J += step;
+      good &= near_key_tile<T, D, BK, PERPOS, PERPOS>(
+          p, now, T0, NT, p0, lane, kf, vf, hpg, src, nm, dK + head_kv, dV + head_kv, [&]() __attribute__((always_inline)) { fetch(J); },
+          [&]() __attribute__((always_inline)) {
+            unsigned *a = reinterpret_cast<unsigned *>(&kn), *b = reinterpret_cast<unsigned *>(&vn);
+#pragma unroll
+            for (unsigned i = 0; i < sizeof(kn) / 4; ++i) asm volatile("" : "+v"(a[i]), "+v"(b[i]));
+          },
+          turn_s[wv]);
+    }
+  if (__builtin_expect(!good, 0))
+    for (int J = J0; J < NT; J += step) {
+      Kr.op(J, kf);
+      Vr.op(J, vf);
+      key_tile<T, D, BK, PERPOS, true>(p, J, T0, NT, p0, lane, kf, vf, hpg, src, dK + head_kv, dV + head_kv);
+    }
+  // positions before the first tile with a valid one: zeros
+  const int rows = min((NT - count) * kTile, p.L);
+  zero_rows_from(dK + head_kv, rows * D, part * (int)blockDim.x + (int)threadIdx.x, parts * (int)blockDim.x);
+  zero_rows_from(dV + head_kv, rows * D, part * (int)blockDim.x + (int)threadIdx.x, parts * (int)blockDim.x);
+}
+
+// =============================================================================================
 // launchers
 // =============================================================================================
 namespace {
@@ -3607,10 +3802,26 @@ bool order_by_length(const KParams &p, int units, bool perpos)
 {
   return units > kCUs && !many_heads(units) && p.B <= kOrderRows && p.L >= shortest_ordered(p, units, perpos);
 }
-SmallPlan stream_plan(const KParams &p, int units, size_t words_per_wave)
+// per_simd: wavefronts a SIMD holds of a kernel whose tiles cost about the same (dQ of the near form).  Its workgroups then come in
+// the number that ends together: rounds of the chip times a wavefront's tiles and its start, half a tile.  (us, by the first rule / so:
+// B=16 H=8 L=1500 d=16 44.5 / 38.0, B=24 H=8 L=700 d=16 29.9 / 28.1, B=32 H=8 L=2000 d=8 63.2 / 63.9.  dK/dV, whose walks differ, 82.4 / 87.0
+// there, and the forward at B=24 L=700 19.9 / 20.9: not for those.)
+SmallPlan stream_plan(const KParams &p, int units, size_t words_per_wave, int per_simd = 0)
 {
   const int NT = (p.L + kTile - 1) / kTile;
-  SmallPlan s{false, false, 4, 1, 4 * words_per_wave * sizeof(float)};
+  SmallPlan s{false, false, kStreamWaves, 1, kStreamWaves * words_per_wave * sizeof(float)};
+  if (per_simd > 0) {
+    int best = 0;
+    for (int parts = 1; parts <= (NT + s.waves - 1) / s.waves; ++parts) {
+      const int rounds = (units * parts + kCUs * per_simd - 1) / (kCUs * per_simd), tiles = (NT + s.waves * parts - 1) / (s.waves * parts);
+      const int cost = rounds * (2 * tiles + 1);
+      if (best == 0 || cost < best) {
+        best = cost;
+        s.parts = parts;
+      }
+    }
+    return s;
+  }
   // enough workgroups for about two rounds of the chip's wavefronts (20 per CU), at most one tile per wavefront
   const int want = (2 * kCUs * 20 + units * s.waves - 1) / (units * s.waves);
   s.parts = std::max(1, std::min((NT + s.waves - 1) / s.waves, want));
@@ -3647,7 +3858,7 @@ SmallPlan bwd_plan(const KParams &p, int dtype, bool perpos, int hpg)
     }
     return s;
   }
-  return stream_plan(p, p.B * p.H, lt_words(p, perpos));
+  return stream_plan(p, p.B * p.H, lt_words(p, perpos), near_form(p) ? (p.d == 8 ? 5 : 4) : 0);
 }
 
 // The per-position form has limits that its callers know (144 KB of fp32 rows of 20 or 36 floats, see the header).
@@ -3750,6 +3961,28 @@ static void launch_bwd_small_t(const KParams &p, const BwdArgs &a, const SmallWs
       }
       if (order_by_length(p, p.B * p.H / hpg, perpos)) perpos ? go(bwd_res_kernel<T, D, BK, true, true>) : go(bwd_res_kernel<T, D, BK, false, true>);
       else perpos ? go(bwd_res_kernel<T, D, BK, true, false>) : go(bwd_res_kernel<T, D, BK, false, false>);
+      return;
+    }
+    if (near_form(p)) {
+      if (stages & (kBwdStageGate | kBwdStageDQ)) {
+        auto go = [&](auto kernel) {
+          hipLaunchKernelGGL(kernel, dim3((unsigned)(p.B * p.H * pl.parts)), dim3(64 * pl.waves), pl.lds, st, (const T *)a.Q,
+                             (const T *)a.K, (const T *)a.V, a.valid_len, a.sel, a.gate_w, a.gate_b, (const float *)a.o_lt,
+                             (const float *)a.o_st, a.lse_lt, a.lse_st, (const T *)a.dO, (T *)a.dQ, w, hpg, pl.parts, stages,
+                             NearMasks(p, false), p);
+        };
+        perpos ? go(bwd_dq_near_kernel<T, D, BK, true>) : go(bwd_dq_near_kernel<T, D, BK, false>);
+        if (launch_failed()) return;
+      }
+      if (stages & kBwdStageDKV) {
+        const SmallPlan pk = stream_plan(p, p.B * p.H / hpg, 0);
+        auto go = [&](auto kernel) {
+          hipLaunchKernelGGL(kernel, dim3((unsigned)(p.B * p.H / hpg * pk.parts)), dim3(64 * pk.waves), 0, st, (const T *)a.Q,
+                             (const T *)a.K, (const T *)a.V, a.valid_len, a.gate_w, (const T *)a.dO, w, (T *)a.dK, (T *)a.dV, hpg,
+                             pk.parts, NearMasks(p, true), p);
+        };
+        perpos ? go(bwd_dkv_near_kernel<T, D, BK, true>) : go(bwd_dkv_near_kernel<T, D, BK, false>);
+      }
       return;
     }
     if (stages & (kBwdStageGate | kBwdStageDQ)) {
