@@ -42,12 +42,6 @@ constexpr float kSumHi = 1.152921504606847e18f, kSumLo = 1.0f / kSumHi;  // 2^60
 // leaves the other counters alone (gfx9 encoding: vmcnt in bits 3:0 and 15:14, expcnt 6:4,
 // lgkmcnt 11:8).
 constexpr int vmcnt_imm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
-constexpr int kSplit = 4;  // wavefronts that share the last query block's walk (a power of two)
-// ... where every workgroup has a CU to itself and the list has four entries or more.  Selection + forward, us, one wavefront / four: B=4 H=8
-// L=1024 k=4 16.8 / 15.8, B=32 H=8 L=2000 k=8 25.3 / 22.2, B=28 H=8 L=600 k=16 w=128 24.4 / 18.3; k=2 15.1 / 15.3 (nothing to share); 512
-// workgroups, B=64 H=8 L=1500 k=8, 33.5 / 36.0 (two to a CU, each with its prologue four times).  Up to 16 blocks the last block's
-// outputs stay, bit for bit, those of a run over all blocks, which a sum in parts does not give.
-constexpr int kSplitList = 4, kSplitBlocks = 16;
 // The lane id, opaque to the compiler: what is derived from it is computed where it is used.
 __device__ __forceinline__ int fresh_lane()
 {
@@ -61,28 +55,19 @@ constexpr int kLgkm0 = 15 | (7 << 4) | (3 << 14);  // lgkmcnt(0), the others at 
 
 // EQ15: the short-term mask is all of Eq. 15 with mask block BLK, or (SUB) a power of two below it
 // (compile-time, so that the plain causal window compiles to exactly the code it had without it)
-// SPLIT: kSplit wavefronts for a query block, for the last one alone, whose workgroups leave CUs idle and last as long as one chain of
-// tiles does.  The tiles of the walk are dealt out in turn; without a reference the parts are plain sums, which the first wavefront adds
-// (and it alone repeats the walk where a row left the range).  Selection + forward at B=16 H=8 L=8192 k=16 w=128: 59.1 -> 51.4 us, all
-// of it this kernel's; with all of Eq. 15 at B=8 H=4 L=3000 k=10 24.9 -> 19.4.
-template <bool EQ15, bool SUB, bool SPLIT>
-__global__ __launch_bounds__(SPLIT ? 64 * kSplit : 64) __attribute__((amdgpu_waves_per_eu(3, 3))) void fwd_mfma_kernel(
+template <bool EQ15, bool SUB>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void fwd_mfma_kernel(
     const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K, const uint16_t *__restrict__ V,
     const int *__restrict__ valid_len, const int *__restrict__ sel, const float *__restrict__ gate_w,
     const float *__restrict__ gate_b, uint16_t *__restrict__ O, float *__restrict__ o_lt_out,
     float *__restrict__ o_st_out, float *__restrict__ lse_lt_out, float *__restrict__ lse_st_out, int dense,
     KParams p)
 {
-  constexpr int WAVES = SPLIT ? kSplit : 1;
-  __shared__ __attribute__((aligned(1024))) uint16_t Ks_all[WAVES * TILE];
-  __shared__ __attribute__((aligned(1024))) uint16_t Vs_all[WAVES * TILE];
-  __shared__ float4 part_s[SPLIT ? (kSplit - 1) * 16 * 64 : 1];  // SPLIT: the outputs of the wavefronts after the first ...
-  __shared__ float part_l[SPLIT ? (kSplit - 1) * 2 * 64 : 1];    // ... and their row sums
+  __shared__ __attribute__((aligned(1024))) uint16_t Ks[TILE];
+  __shared__ __attribute__((aligned(1024))) uint16_t Vs[TILE];
   __shared__ float gate_s[2 * D];  // this head's gate weights, fetched at the start, used at the very end
 
-  const int lane = SPLIT ? threadIdx.x & 63 : threadIdx.x;
-  const int wv = SPLIT ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
-  uint16_t *const Ks = Ks_all + wv * TILE, *const Vs = Vs_all + wv * TILE;
+  const int lane = threadIdx.x;
   const int lq = lane & 31;  // query column (and key row of the K operand, d row of the V^T operand)
   const int lh = lane >> 5;  // which half of each 16-wide contraction slab
   const unsigned vid = xcd_spread(blockIdx.x, (unsigned)(p.B * p.H), (unsigned)p.nq);
@@ -134,7 +119,6 @@ __global__ __launch_bounds__(SPLIT ? 64 * kSplit : 64) __attribute__((amdgpu_wav
   const bool q_ok = iq < p.L && iq >= p0;
 
   if (min((I + 1) * BLK, p.L) <= p0) {  // no valid query in the block: zero outputs
-    if (SPLIT && wv > 0) return;
     zero_rows(O + head, qbase, 32, p.L, lane);
     if (o_lt_out) {
       zero_rows(o_lt_out + head, qbase, 32, p.L, lane);
@@ -159,10 +143,8 @@ __global__ __launch_bounds__(SPLIT ? 64 * kSplit : 64) __attribute__((amdgpu_wav
   float gate_mine[2];
 #pragma unroll
   for (int c = 0; c < 2; ++c) gate_mine[c] = dense ? 0.0f : gate_w[(size_t)h * 2 * D + c * 64 + lane];
-  if (!SPLIT || wv == 0) {
-    stage(Kh, Ks, I);  // the walk's first tile
-    stage(Vh, Vs, I);
-  }
+  stage(Kh, Ks, I);  // the walk's first tile
+  stage(Vh, Vs, I);
 
 
   // ---- the short-term tiles: window blocks J_lo..I; with the full mask of Eq. 15 also the blocks I - 2^r below them,
@@ -217,8 +199,7 @@ __global__ __launch_bounds__(SPLIT ? 64 * kSplit : 64) __attribute__((amdgpu_wav
     }
   }
 #pragma unroll
-  for (int c = 0; c < 2; ++c)
-    if (!SPLIT || wv == 0) gate_s[c * 64 + lane] = gate_mine[c];
+  for (int c = 0; c < 2; ++c) gate_s[c * 64 + lane] = gate_mine[c];
 
   // Q^T operand: lane (query lq, half lh) holds c*Q[iq][16*kk + 8*lh .. +7] for the 4 slabs kk,
   // c = scale*log2(e), rounded to bf16: the matrix cores then produce base-2 exponents directly.
@@ -257,28 +238,6 @@ __global__ __launch_bounds__(SPLIT ? 64 * kSplit : 64) __attribute__((amdgpu_wav
     int far, e;
   };
   const Place start{both_st, only_st, 64, list_next(0)};
-  // SPLIT: this wavefront's share, every kSplit-th tile of the whole walk in its order (short-term tiles beyond 64 are the first's)
-  auto own_next = [&](int e) -> int {
-    for (int i = 0; i < WAVES; ++i) e = list_next(e + 1);
-    return e;
-  };
-  auto own_share = [&]() -> Place {
-    if (!SPLIT) return start;
-    int rank = 0;
-    auto deal = [&](unsigned long long m) -> unsigned long long {
-      unsigned long long mine = 0ull;
-      for (; m != 0ull; m &= m - 1, ++rank)
-        if ((rank & (WAVES - 1)) == wv) mine |= m & (0ull - m);
-      return mine;
-    };
-    Place w = start;
-    w.both = deal(both_st);
-    w.only = deal(only_st);
-    w.far = wv == 0 ? 64 : max(64, n_st);
-    for (int i = (wv - rank) & (WAVES - 1); i > 0; --i) w.e = list_next(w.e + 1);
-    return w;
-  };
-  const Place mine = own_share();
   auto left = [&](const Place &w) { return w.both != 0ull || w.only != 0ull || w.far < n_st || w.e < n_lt; };
   auto tile_at = [&](const Place &w) -> int {
     if (w.both != 0ull) return st_tile((int)__builtin_ctzll(w.both));
@@ -429,14 +388,14 @@ __global__ __launch_bounds__(SPLIT ? 64 * kSplit : 64) __attribute__((amdgpu_wav
     for (int i = 0; i < 16; ++i) s[i] = __builtin_amdgcn_exp2f(s[i]);
   };
   clear();
-  if (SPLIT ? left(mine) && (wv > 0 || tile_at(mine) != I) : tile_at(mine) != I) {  // (the own block is not selected, or dense)
+  if (tile_at(start) != I) {  // (the own block is not selected, or dense)
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-    stage(Kh, Ks, tile_at(mine));
-    stage(Vh, Vs, tile_at(mine));
+    stage(Kh, Ks, tile_at(start));
+    stage(Vh, Vs, tile_at(start));
   }
   // (straight-line loops per kind of tile: accumulators updated under a condition are copied at every join)
   auto walk = [&](auto hp) __attribute__((always_inline)) {
-    Place w = mine;
+    Place w = start;
     int J = tile_at(w);
 #pragma unroll 1
     while (w.both != 0ull) {
@@ -464,7 +423,7 @@ __global__ __launch_bounds__(SPLIT ? 64 * kSplit : 64) __attribute__((amdgpu_wav
     }
 #pragma unroll 1
     while (w.e < n_lt) {
-      w.e = own_next(w.e);
+      w.e = list_next(w.e + 1);
       const bool more = w.e < n_lt;
       const int J_nxt = more ? list_block(w.e) : -1;
       f32x16 s = step(more, J_nxt);
@@ -476,42 +435,6 @@ __global__ __launch_bounds__(SPLIT ? 64 * kSplit : 64) __attribute__((amdgpu_wav
   };
   if (hp_st | hp_lt) walk(std::true_type{});
   else walk(std::false_type{});
-
-  if (SPLIT) {
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // (a wavefront without a tile: nothing may land in LDS after it)
-    if (wv > 0) {
-      float4 *to = part_s + (wv - 1) * 16 * 64 + lane;
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          to[64 * (4 * mb + g)] = make_float4(o_lt[mb][4 * g], o_lt[mb][4 * g + 1], o_lt[mb][4 * g + 2], o_lt[mb][4 * g + 3]);
-          to[64 * (8 + 4 * mb + g)] = make_float4(o_st[mb][4 * g], o_st[mb][4 * g + 1], o_st[mb][4 * g + 2], o_st[mb][4 * g + 3]);
-        }
-      part_l[(wv - 1) * 128 + lane] = l_lt;
-      part_l[(wv - 1) * 128 + 64 + lane] = l_st;
-    }
-    __syncthreads();
-    if (wv > 0) return;  // (no barrier follows)
-#pragma unroll 1
-    for (int g1 = 0; g1 < WAVES - 1; ++g1) {
-      const float4 *from = part_s + g1 * 16 * 64 + lane;
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const float4 a = from[64 * (4 * mb + g)], b = from[64 * (8 + 4 * mb + g)];
-          const float as[4] = {a.x, a.y, a.z, a.w}, bs[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            o_lt[mb][4 * g + e] += as[e];
-            o_st[mb][4 * g + e] += bs[e];
-          }
-        }
-      l_lt += part_l[g1 * 128 + lane];
-      l_st += part_l[g1 * 128 + 64 + lane];
-    }
-  }
 
   // ---- closing: normalised outputs, lse, gate (Eq. 18-19) ----
   float ref_lt = 0.0f, ref_st = 0.0f, lse_lt, lse_st, inv_lt, inv_st, z;
@@ -688,24 +611,21 @@ void launch_fwd_mfma(const KParams &p, const FwdArgs &a, hipStream_t st)
     launch_fwd_mfma4(p, a, st);
     return;
   }
+  // (The last block alone goes through the same walk as among all blocks: a history's served outputs are those of its full run, bit for bit,
+  // in a batch of any size.  Four wavefronts with every fourth tile each would take 51.4 instead of 59.1 us with the selection at B=16 H=8 L=8192
+  // k=16 w=128, but add in another order.)
   const unsigned grid = (unsigned)(p.B * p.H * p.nq);
   auto u16 = [](const void *x) { return reinterpret_cast<const uint16_t *>(x); };
-  const bool split = p.nq == 1 && p.NB > kSplitBlocks && grid <= 256u && (p.k < p.NB ? p.k : p.NB) >= kSplitList && !a.dense;
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(split ? 64 * kSplit : 64), 0, st, u16(a.Q), u16(a.K), u16(a.V), a.valid_len, a.sel,
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, st, u16(a.Q), u16(a.K), u16(a.V), a.valid_len, a.sel,
                        a.gate_w, a.gate_b, (uint16_t *)a.O, (float *)a.o_lt, (float *)a.o_st, a.lse_lt, a.lse_st,
                        a.dense, p);
   };
   const bool eq15 = p.sblk != 0 && !a.dense;
   const bool sub = eq15 && p.sblk < p.b;  // mask block smaller than the tile
-  auto pick = [&](auto shared) {
-    constexpr bool SPLIT = decltype(shared)::value;
-    if (sub) go(fwd_mfma_kernel<true, true, SPLIT>);
-    else if (eq15) go(fwd_mfma_kernel<true, false, SPLIT>);
-    else go(fwd_mfma_kernel<false, false, SPLIT>);
-  };
-  if (split) pick(std::true_type{});
-  else pick(std::false_type{});
+  if (sub) go(fwd_mfma_kernel<true, true>);
+  else if (eq15) go(fwd_mfma_kernel<true, false>);
+  else go(fwd_mfma_kernel<false, false>);
 }
 
 }  // namespace blossom
