@@ -40,20 +40,12 @@ constexpr float kRaise4 = 8.0f;        // log2 units by which the maximum must g
 constexpr int kFewKeys4 = 32;          // rows seeing fewer keys than this get two-term bf16 probabilities
 constexpr float kSumLimit4 = 4096.0f;  // a lane's 16 probabilities of a tile may sum to this (16 * 2^kRaise4)
 constexpr int BLK4 = 64;
-// Entries of a list from which it is shared out for the last block alone, where every workgroup has a CU to itself: selection + forward,
-// us, one group / three: B=1 L=8192 k=16 27.0 / 24.4, B=4 L=1500 k=8 21.5 / 20.2, B=16 H=8 L=3000 k=12 29.5 / 28.5, B=16 H=8 L=8192 k=8 44.7 /
-// 44.4.  (Shorter lists have hardly more tiles than the short-term branch, which is one group's.)
-constexpr int kSplitList = 8;
 
 
 }  // namespace
 
-// SPLIT: three such groups of four wavefronts, for the last query block alone, whose workgroups leave CUs idle and last as long as one
-// chain of tiles does: the first takes the short-term tiles, the others half of the list each, with buffers of their own; the second
-// merges and stores.  us of this kernel, one group / three: B=16 H=8 L=8192 k=16 w=128 18.2 / 16.4 (cold keys and values; the chain of a
-// tile's step, 0.7 us, and what stands before and after the walk remain).
-template <bool EQ15, bool SUB, bool SPLIT>
-__global__ __launch_bounds__(SPLIT ? 768 : 256) __attribute__((amdgpu_waves_per_eu(3, 3))) void fwd_mfma4_kernel(
+template <bool EQ15, bool SUB>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void fwd_mfma4_kernel(
     const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K, const uint16_t *__restrict__ V,
     const int *__restrict__ valid_len, const int *__restrict__ sel, const float *__restrict__ gate_w,
     const float *__restrict__ gate_b, uint16_t *__restrict__ O, float *__restrict__ o_lt_out,
@@ -63,24 +55,19 @@ __global__ __launch_bounds__(SPLIT ? 768 : 256) __attribute__((amdgpu_waves_per_
   constexpr int BLK = BLK4;
   constexpr int TILE = BLK * D;  // bf16 elements of one staged tile (rows of 128 bytes, swizzled)
   constexpr int HALF = 32 * D;   // elements of the 32 key rows one wavefront reads
-  constexpr int GROUPS = SPLIT ? 3 : 1;
-  __shared__ __attribute__((aligned(1024))) uint16_t Ks0_all[GROUPS * TILE];
-  __shared__ __attribute__((aligned(1024))) uint16_t Ks1_all[GROUPS * TILE];
-  __shared__ __attribute__((aligned(1024))) uint16_t Ks2_all[GROUPS * TILE];
-  __shared__ __attribute__((aligned(1024))) uint16_t Vs0_all[GROUPS * TILE];
-  __shared__ __attribute__((aligned(1024))) uint16_t Vs1_all[GROUPS * TILE];
-  __shared__ __attribute__((aligned(1024))) uint16_t Vs2_all[GROUPS * TILE];
+  __shared__ __attribute__((aligned(1024))) uint16_t Ks0[TILE];
+  __shared__ __attribute__((aligned(1024))) uint16_t Ks1[TILE];
+  __shared__ __attribute__((aligned(1024))) uint16_t Ks2[TILE];
+  __shared__ __attribute__((aligned(1024))) uint16_t Vs0[TILE];
+  __shared__ __attribute__((aligned(1024))) uint16_t Vs1[TILE];
+  __shared__ __attribute__((aligned(1024))) uint16_t Vs2[TILE];
   __shared__ float gate_s[2 * D];  // this head's gate weights
-  __shared__ float xch_s[4 * GROUPS][3][32];  // per wavefront: reference, row sum (branch merge), gate partial
+  __shared__ float xch_s[4][3][32];  // per wavefront: reference, row sum (branch merge), gate partial
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   // (uniform through readfirstlane: every branch on them is scalar, as matrix instructions need)
-  const int grp = SPLIT ? __builtin_amdgcn_readfirstlane(tid >> 8) : 0;
-  const int wv = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);  // of the group
-  uint16_t *const Ks0 = Ks0_all + grp * TILE, *const Ks1 = Ks1_all + grp * TILE, *const Ks2 = Ks2_all + grp * TILE;
-  uint16_t *const Vs0 = Vs0_all + grp * TILE, *const Vs1 = Vs1_all + grp * TILE, *const Vs2 = Vs2_all + grp * TILE;
-  float(*const xch)[3][32] = xch_s + 4 * grp;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qg = wv & 1;   // query group: rows 32*qg .. 32*qg+31 of the block
   const int kh = wv >> 1;  // key half: rows 32*kh .. 32*kh+31 of every tile; after a merge: channels 32*kh ..
   const int lq = lane & 31;
@@ -110,7 +97,6 @@ __global__ __launch_bounds__(SPLIT ? 768 : 256) __attribute__((amdgpu_waves_per_
   const bool q_ok = iq < p.L && iq >= p0;
 
   if (min((I + 1) * BLK, p.L) <= p0) {  // no valid query in the block: zero outputs (16 rows per wavefront)
-    if (SPLIT && grp > 0) return;
     const int zr = I * BLK + 16 * wv;
     zero_rows(O + head, zr, 16, p.L, lane);
     if (o_lt_out) {
@@ -177,10 +163,8 @@ __global__ __launch_bounds__(SPLIT ? 768 : 256) __attribute__((amdgpu_waves_per_
 
   // the first tile is on its way while the rest of the prologue runs
   const int first_J = dense ? J_first : J_lo;
-  if (!SPLIT || grp == 0) {
-    stage(Kh, k_lane, 64u, Ks0, first_J);
-    stage(Vh, v_lane, 0u, Vs0, first_J);
-  }
+  stage(Kh, k_lane, 64u, Ks0, first_J);
+  stage(Vh, v_lane, 0u, Vs0, first_J);
 
   // Q^T operand: lane (query lq, half lh) holds c*Q[iq][16*kk + 8*lh .. +7], c = scale*log2(e), in bf16
   const float c2 = p.scale * kLog2e;
@@ -214,18 +198,11 @@ __global__ __launch_bounds__(SPLIT ? 768 : 256) __attribute__((amdgpu_waves_per_
     }
     n_all = n_st + n_lt;
   }
-  // the tiles of this group: n_mine of the list from t_off on
-  int t_off = 0, n_mine = n_all;
-  if (SPLIT) {
-    const int half = (n_all - n_st + 1) / 2;
-    t_off = grp == 0 ? 0 : grp == 1 ? n_st : n_st + half;
-    n_mine = grp == 0 ? n_st : grp == 1 ? half : n_all - n_st - half;
-  }
   // The tile list, 64 entries at a time in one register (lane l: entry 64*c + l): window blocks by
   // arithmetic, then the selection row; entries outside [0, NB) and entries past the end are -1 (a tile
   // whose keys are all masked).  A step takes its block id with one v_readlane.
   auto list_chunk = [&](int c) __attribute__((always_inline)) -> int {
-    const int t = 64 * c + lane + t_off;
+    const int t = 64 * c + lane;
     int J;
     if (dense) {
       J = J_first + t;
@@ -236,7 +213,7 @@ __global__ __launch_bounds__(SPLIT ? 768 : 256) __attribute__((amdgpu_waves_per_
       J = e < p.k ? (e < 64 && n_st == 0 ? sel0 : my_sel[e]) : -1;
       J = (unsigned)J < (unsigned)p.NB ? J : -1;
     }
-    return t < t_off + n_mine ? J : -1;
+    return t < n_all ? J : -1;
   };
   int tl = list_chunk(0);
   auto list_at = [&](int t) __attribute__((always_inline)) -> int {
@@ -435,10 +412,8 @@ __global__ __launch_bounds__(SPLIT ? 768 : 256) __attribute__((amdgpu_waves_per_
   // triples over disjoint key halves.  Each hands the channel block it does not keep (32*(1-kh) ..)
   // to its partner through the staging rows just consumed (4 KB per wavefront) and merges the
   // partner's part of the block it keeps.  Leaves the normalised 32 rows x 32 channels (block kh) in
-  // `fin` and returns the lse (natural log; log2_sum: the same in log2 units, minus infinity without a key).  kx, vx: the tile buffers
-  // free at this point.
+  // `fin` and returns the lse (natural log).  kx, vx: the tile buffers free at this point.
   f32x16 fin;
-  float log2_sum = kNegInf;
   auto close_branch = [&](uint16_t *kx, uint16_t *vx) __attribute__((always_inline)) -> float {
     __syncthreads();  // every wavefront is past its operand reads of kx, vx: they become exchange space
     float4 *mine = reinterpret_cast<float4 *>(wv < 2 ? kx : vx) + (wv & 1) * 256 + lane;  // [4][64]: 2 wavefronts x 4 KB per buffer
@@ -457,12 +432,12 @@ __global__ __launch_bounds__(SPLIT ? 768 : 256) __attribute__((amdgpu_waves_per_
       fin = oacc[1];
     }
     if (lh == 0) {
-      xch[wv][0][lq] = fresh ? kNegInf : m_ref;
-      xch[wv][1][lq] = l_mine;
+      xch_s[wv][0][lq] = fresh ? kNegInf : m_ref;
+      xch_s[wv][1][lq] = l_mine;
     }
     __syncthreads();
-    const float m_b = xch[pw][0][lq];
-    const float l_b = xch[pw][1][lq];
+    const float m_b = xch_s[pw][0][lq];
+    const float l_b = xch_s[pw][1][lq];
     const float m_a = fresh ? kNegInf : m_ref;
     const float m = fmaxf(m_a, m_b);
     const float fa = m_a == kNegInf ? 0.0f : __builtin_amdgcn_exp2f(m_a - m);
@@ -480,7 +455,6 @@ __global__ __launch_bounds__(SPLIT ? 768 : 256) __attribute__((amdgpu_waves_per_
       fin[4 * g + 3] = fin[4 * g + 3] * ga + t.w * gb;
     }
     __syncthreads();  // the partner has read this wavefront's rows: they may be refilled
-    if (SPLIT) log2_sum = ok ? m + __log2f(l_tot) : kNegInf;
     return ok ? (m + __log2f(l_tot)) * kLn2 : 0.0f;
   };
 
@@ -496,14 +470,7 @@ __global__ __launch_bounds__(SPLIT ? 768 : 256) __attribute__((amdgpu_waves_per_
   int J_cur = first_J;
   int J_n1 = list_at(1);
   int J_n2 = list_at(2);
-  if (SPLIT && grp > 0) {
-    J_cur = list_at(0);
-    if (n_mine > 0) {
-      stage(Kh, k_lane, 64u, Ks0, J_cur);
-      stage(Vh, v_lane, 0u, Vs0, J_cur);
-    }
-  }
-  if (n_mine > 1) {
+  if (n_all > 1) {
     stage(Kh, k_lane, 64u, Ks1, J_n1);
     stage(Vh, v_lane, 0u, Vs1, J_n1);
     arrived_all<4>();  // tile 0 and the gate weights are in LDS
@@ -511,21 +478,17 @@ __global__ __launch_bounds__(SPLIT ? 768 : 256) __attribute__((amdgpu_waves_per_
     arrived_all<0>();
   }
   auto step = [&](int t, uint16_t *k_cur, uint16_t *v_cur, uint16_t *k_fill, uint16_t *v_fill) __attribute__((always_inline)) {
-    const bool more = t + 2 < n_mine;
+    const bool more = t + 2 < n_all;
     if (more) {
       stage(Kh, k_lane, 64u, k_fill, J_n2);
       stage(Vh, v_lane, 0u, v_fill, J_n2);
     }
-    if (SPLIT) {
-      if (t < n_mine) tile(k_cur, v_cur, J_cur, grp == 0);
-    } else {
-      tile(k_cur, v_cur, J_cur, t < n_st);
-    }
+    tile(k_cur, v_cur, J_cur, t < n_st);
     J_cur = J_n1;
     J_n1 = J_n2;
-    if (((t + 3) & 63) == 0 && t + 3 < n_mine) tl = list_chunk((t + 3) >> 6);  // (once per 64 tiles)
+    if (((t + 3) & 63) == 0 && t + 3 < n_all) tl = list_chunk((t + 3) >> 6);  // (once per 64 tiles)
     J_n2 = list_at(t + 3);
-    if (!SPLIT && t + 1 == n_st) {  // the short-term tiles are done (the merge has its own barriers)
+    if (t + 1 == n_st) {  // the short-term tiles are done (the merge has its own barriers)
       lse_st = close_branch(k_cur, v_cur);
       ost = fin;
       reset();
@@ -534,45 +497,12 @@ __global__ __launch_bounds__(SPLIT ? 768 : 256) __attribute__((amdgpu_waves_per_
     if (more) arrived_all<4>();
     else arrived_all<0>();
   };
-  // (a barrier a step: the groups take as many as the longest list has)
-  const int steps = SPLIT ? max(n_st, (n_all - n_st + 1) / 2) : n_all;
-  for (int t = 0; t < steps; t += 3) {
+  for (int t = 0; t < n_all; t += 3) {
     step(t, Ks0, Vs0, Ks2, Vs2);
-    if (t + 1 < steps) step(t + 1, Ks1, Vs1, Ks0, Vs0);
-    if (t + 2 < steps) step(t + 2, Ks2, Vs2, Ks1, Vs1);
+    if (t + 1 < n_all) step(t + 1, Ks1, Vs1, Ks0, Vs0);
+    if (t + 2 < n_all) step(t + 2, Ks2, Vs2, Ks1, Vs1);
   }
-  float lse_lt = close_branch(Ks0, Vs0);
-  if (SPLIT) {
-    // the first and the third group leave their rows and sums to the second (fin[i] of lane l: 4 KB a wavefront, as in close_branch)
-    float4 *rows = reinterpret_cast<float4 *>((wv < 2 ? Ks0_all : Vs0_all)) + (wv & 1) * 256 + lane;
-    constexpr int kPitch = TILE * 2 / 16;  // of a group's buffer, in float4
-    if (grp != 1) {
-#pragma unroll
-      for (int g = 0; g < 4; ++g) rows[grp * kPitch + 64 * g] = make_float4(fin[4 * g], fin[4 * g + 1], fin[4 * g + 2], fin[4 * g + 3]);
-      if (lh == 0) {
-        xch[wv][0][lq] = log2_sum;
-        xch[wv][1][lq] = lse_lt;
-      }
-    }
-    __syncthreads();
-    if (grp != 1) return;
-    const float other = xch_s[8 + wv][0][lq], top = fmaxf(log2_sum, other);
-    const float a = log2_sum == kNegInf ? 0.0f : __builtin_amdgcn_exp2f(log2_sum - top);
-    const float b = other == kNegInf ? 0.0f : __builtin_amdgcn_exp2f(other - top);
-    const float sum = a + b, inv = sum > 0.0f ? 1.0f / sum : 0.0f;
-    lse_lt = sum > 0.0f ? (top + __log2f(sum)) * kLn2 : 0.0f;
-    lse_st = xch_s[wv][1][lq];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const float4 x = rows[2 * kPitch + 64 * g], y = rows[64 * g];
-      const float xs[4] = {x.x, x.y, x.z, x.w}, ys[4] = {y.x, y.y, y.z, y.w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        fin[4 * g + e] = (fin[4 * g + e] * a + xs[e] * b) * inv;
-        ost[4 * g + e] = ys[e];
-      }
-    }
-  }
+  const float lse_lt = close_branch(Ks0, Vs0);
 
   // ---- epilogue: gate (Eq. 18-19) and stores of this wavefront's 32 rows x 32 channels ----
   // fin[4*g + e] (and ost): channel 32*kh + 8*g + 4*lh + e of row qbase + lq.  The tiles leave through
@@ -642,10 +572,10 @@ __global__ __launch_bounds__(SPLIT ? 768 : 256) __attribute__((amdgpu_waves_per_
     z = fmaf(b.w, ost[4 * g + 3], z);
   }
   z += __shfl_xor(z, 32);
-  if (lh == 0) xch[wv][2][lq] = z;
-  __syncthreads();  // (SPLIT: of the one group that is left)
+  if (lh == 0) xch_s[wv][2][lq] = z;
+  __syncthreads();
   // both wavefronts of the pair add the two partial sums in the same order: the same alpha bit for bit
-  z = xch[qg][2][lq] + xch[qg + 2][2][lq];
+  z = xch_s[qg][2][lq] + xch_s[qg + 2][2][lq];
   z += gate_b ? gate_b[h] : 0.0f;
   const float alpha = q_ok ? 1.0f / (1.0f + __expf(-z)) : 0.0f;
   if (o_lt_out) {
@@ -661,25 +591,21 @@ __global__ __launch_bounds__(SPLIT ? 768 : 256) __attribute__((amdgpu_waves_per_
 
 void launch_fwd_mfma4(const KParams &p, const FwdArgs &a, hipStream_t st)
 {
+  // (The last block alone: the walk of all blocks, as at block size 32.  Three groups of wavefronts, one with the short-term tiles and two with
+  // half of the list each, would take 46.9 instead of 48.8 us with the selection at B=16 H=8 L=8192 k=16 w=128, but each list rounds its
+  // probabilities to bf16 against a reference of its own: outputs up to a step of bf16 off those of the full run.)
   const unsigned grid = (unsigned)(p.B * p.H * p.nq);
   auto u16 = [](const void *x) { return reinterpret_cast<const uint16_t *>(x); };
-  // the last query block alone, one workgroup to a CU at most, and a list that is worth two halves
-  const bool split = p.nq == 1 && p.NB > 1 && grid <= 256u && (p.k < p.NB ? p.k : p.NB) >= kSplitList && !a.dense;
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(split ? 768 : 256), 0, st, u16(a.Q), u16(a.K), u16(a.V), a.valid_len, a.sel,
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, st, u16(a.Q), u16(a.K), u16(a.V), a.valid_len, a.sel,
                        a.gate_w, a.gate_b, (uint16_t *)a.O, (float *)a.o_lt, (float *)a.o_st, a.lse_lt, a.lse_st,
                        a.dense, p);
   };
   const bool eq15 = p.sblk != 0 && !a.dense;
   const bool sub = eq15 && p.sblk < p.b;  // mask block smaller than the tile
-  auto pick = [&](auto three) {
-    constexpr bool SPLIT = decltype(three)::value;
-    if (sub) go(fwd_mfma4_kernel<true, true, SPLIT>);
-    else if (eq15) go(fwd_mfma4_kernel<true, false, SPLIT>);
-    else go(fwd_mfma4_kernel<false, false, SPLIT>);
-  };
-  if (split) pick(std::true_type{});
-  else pick(std::false_type{});
+  if (sub) go(fwd_mfma4_kernel<true, true>);
+  else if (eq15) go(fwd_mfma4_kernel<true, false>);
+  else go(fwd_mfma4_kernel<false, false>);
 }
 
 }  // namespace blossom

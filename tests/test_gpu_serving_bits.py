@@ -46,3 +46,24 @@ def _last_block_alone(rows, H, L, d, b, topk, window, sblk, dtype, amp=1.0):
 ])
 def test_serving_at_block_32(rows, H, L, topk, window, sblk, amp):
     _last_block_alone(rows, H, L, 64, 32, topk, window, sblk, torch.bfloat16, amp)
+
+
+@pytest.mark.parametrize("rows,H", [(64, 4), (257, 1)])
+@pytest.mark.parametrize("L,topk,window,sblk,amp", [
+    (64 * 8, 8, 64, 0, 1.0),
+    (64 * 20 + 5, 16, 128, 0, 1.0),
+    (64 * 70 + 9, 66, 4400, 0, 1.0),
+    (64 * 11 + 60, 10, 100, 64, 1.0),   # all of Eq. 15
+    (64 * 12 + 28, 9, 100, 1, 64.0),
+])
+def test_serving_at_block_64(rows, H, L, topk, window, sblk, amp):
+    _last_block_alone(rows, H, L, 64, 64, topk, window, sblk, torch.bfloat16, amp)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("d,b,L,sblk", [
+    (8, 16, 200, 1), (8, 8, 1100, 1), (16, 16, 200, 0), (16, 16, 1100, 1), (32, 8, 203, 1), (32, 16, 700, 0),
+    (16, 16, 200, 16), (32, 8, 700, 2),
+])
+def test_serving_of_small_heads(d, b, L, sblk, dtype):
+    _last_block_alone(257, 1, L, d, b, 4, 9, sblk, dtype)
