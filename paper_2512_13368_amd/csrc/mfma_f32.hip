@@ -1934,7 +1934,7 @@ namespace {
 // LDS of bwd_res_kernel, in floats: K and V, per head Q and dO (overlay: in the place of K and V), row constants, tile words and
 // selection bits, the wavefronts' selection words
 struct ResLayout {
-  int pitch, qg, rowc, words, waves, gates, red, total;
+  int pitch, qg, rowc, words, waves, held, gates, red, total;
   // row: floats of a staged row
   __host__ __device__ ResLayout(const KParams &p, int row, bool perpos, int hpg, int overlay, int W)
   {
@@ -1945,10 +1945,11 @@ struct ResLayout {
     words = rowc + hpg * 6 * rows;
     waves = words + NT * ((NT + 31) / 32) + (perpos ? 2 * rows : p.b < kTile ? 2 * NT * ((p.NB + 31) / 32) : 0);
     waves = (waves + 3) / 4 * 4;
+    held = waves + W * lt_words(p, perpos);
     // (the near form: the heads' gate rows, and every wavefront's gate sums of every head)
-    gates = waves + (W * lt_words(p, perpos) + 3) / 4 * 4;
+    gates = (held + 3) / 4 * 4;
     red = gates + hpg * 2 * p.d;
-    total = near_form(p) ? red + hpg * W * (2 * p.d + 1) : waves + W * lt_words(p, perpos);
+    total = near_form(p) ? red + hpg * W * (2 * p.d + 1) : held;
   }
 };
 
@@ -3882,19 +3883,20 @@ SmallPlan bwd_plan(const KParams &p, int dtype, bool perpos, int hpg)
   // with many heads four small workgroups per CU beat two that hold everything (B=2048 H=8 L=200 d=16: 672 against 917 us); with so
   // few that no CU has more than two to hold, everything fits beside a second one (gradients at B=82 H=4 L=174 d=16: 50.8 us with
   // everything in LDS, 52.3 with Q and dO read again; B=40 H=8 L=170 d=16, a whole step 47.5 and 48.4)
-  auto bytes = [&](const SmallPlan &s) {
-    return (size_t)ResLayout(p, lds_row(dtype == 1, p.d), perpos, hpg, s.overlay, s.waves).total * sizeof(float);
+  // A limit is about what both forms hold; the near form's gate rows and sums, 1 to 9 KB, come on top as long as the same number of
+  // workgroups fits a CU.  (Counted in, they sent the longest heads the other way: a training step, us, in LDS / streamed, fp32 at L=240 with
+  // B=64 H=8 d=16 52.6 / 62.7, B=125 H=8 d=16 87.1 / 95.5, per position with B=64 H=4 d=32 101 / 112, bf16 at B=600 H=4 L=416 d=32 404 / 466;
+  // per position with 256 key/value heads at d=8 L=464 and d=16 L=400 120 / 117 and 105 / 102.)
+  auto fits = [&](SmallPlan &s, size_t limit) {
+    const ResLayout lay(p, lds_row(dtype == 1, p.d), perpos, hpg, s.overlay, s.waves);
+    s.lds = (size_t)lay.total * sizeof(float);
+    return (size_t)lay.held * sizeof(float) <= limit && s.lds <= (limit == kTwoPerCU ? 79 * 1024 : 52 * 1024);
   };
   for (int overlay = many_heads(units) ? 1 : 0; overlay < 2; ++overlay) {
     SmallPlan s{true, overlay != 0, res_waves(units), 1, 0};
-    s.lds = bytes(s);
-    if (s.lds > small_lds_limit(p)) continue;
-    const SmallPlan all{true, false, s.waves, 1, 0};
-    if (s.overlay && units <= 2 * kCUs && bytes(all) <= kTwoPerCU) {
-      s = all;
-      s.lds = bytes(all);
-    }
-    return s;
+    if (!fits(s, small_lds_limit(p))) continue;
+    SmallPlan all{true, false, s.waves, 1, 0};
+    return s.overlay && units <= 2 * kCUs && fits(all, kTwoPerCU) ? all : s;
   }
   return stream_plan(p, p.B * p.H, lt_words(p, perpos), near_form(p) ? (p.d == 8 ? 5 : 4) : 0);
 }
