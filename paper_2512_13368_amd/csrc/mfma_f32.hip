@@ -73,6 +73,8 @@ struct Geo {
   static constexpr int NACC = kQuads ? 2 : NMB;  // their accumulators
 };
 
+// both halves, the lower one first; at: 8-byte aligned
+__device__ __forceinline__ void store_pair(unsigned *at, unsigned long long x) { *reinterpret_cast<uint2 *>(at) = make_uint2((unsigned)x, (unsigned)(x >> 32)); }
 // CPL consecutive elements as floats
 template <int N>
 __device__ __forceinline__ void load_n(const float *p, float (&o)[N])
@@ -87,6 +89,14 @@ __device__ __forceinline__ void load_n(const float *p, float (&o)[N])
       o[i] = v.x; o[i + 1] = v.y; o[i + 2] = v.z; o[i + 3] = v.w;
     }
   }
+}
+// Waits for what these registers are loaded with.  (Each goes to the assembly in its own type: through a pointer to another one the
+// compiler need not see that they are read and written here.)
+template <typename X, int N>
+__device__ __forceinline__ void arrive(X (&x)[N])
+{
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(x[i]));
 }
 template <int N>
 __device__ __forceinline__ void zero_n(float (&o)[N])
@@ -177,6 +187,11 @@ struct Operands {
       if constexpr (kBf) o[i] = __uint_as_float((i & 1) ? a.w[i / 2] & 0xFFFF0000u : a.w[i / 2] << 16);
       else o[i] = a.v[i];
     }
+  }
+  static __device__ __forceinline__ void arrived(Row &a)
+  {
+    if constexpr (kBf) arrive(a.w);
+    else arrive(a.v);
   }
   static __device__ __forceinline__ void clean(Row &a)  // elements that are not finite become zeros
   {
@@ -1584,9 +1599,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     int sel[Sel::kFirst];
     __device__ __forceinline__ void arrived()
     {
-      unsigned *w = reinterpret_cast<unsigned *>(this);
-#pragma unroll
-      for (unsigned i = 0; i < sizeof(Request) / 4; ++i) asm volatile("" : "+v"(w[i]));
+      Ops::arrived(q);
+      arrive(sel);
     }
   };
   const int *sel_unit = sel + (PERPOS ? (size_t)kvh * p.L : (size_t)bh0 * p.NB) * p.k;
@@ -2651,9 +2665,12 @@ struct QueryIn {
   // Waits for them: before a tile's stores go out, for behind those a wait for them would be one for the stores.
   __device__ __forceinline__ void arrived()
   {
-    unsigned *w = reinterpret_cast<unsigned *>(this);
-#pragma unroll
-    for (unsigned i = 0; i < sizeof(QueryIn) / 4; ++i) asm volatile("" : "+v"(w[i]));
+    Ops::arrived(q);
+    Ops::arrived(g);
+    arrive(ol);
+    arrive(os);
+    arrive(lse);
+    arrive(sel);
   }
 };
 
@@ -3214,7 +3231,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     if (PERPOS && bh % hpg != 0) return;
     for (int i = el; i < NWt; i += 64) ws.tile_words[((size_t)kvh * NT + I) * NWt + i] = ls.tiles[i];
     if constexpr (PERPOS) {
-      if (eg == 0) *reinterpret_cast<unsigned long long *>(ws.sel_bits + ((size_t)kvh * NT * kTile + I * kTile + eq) * 2) = ls.row;
+      if (eg == 0) store_pair(ws.sel_bits + ((size_t)kvh * NT * kTile + I * kTile + eq) * 2, ls.row);
     } else if constexpr (BK < kTile) {
       for (int i = el; i < 2 * ls.NWb; i += 64) ws.sel_bits[((size_t)kvh * NT + I) * 2 * ls.NWb + i] = ls.bits[i];
     }
@@ -3359,7 +3376,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
       if (hl > 0) return;
       for (int i = lane; i < NWt; i += 64) words[I * NWt + i] = ls.tiles[i];
       if constexpr (PERPOS) {
-        if (g == 0) *reinterpret_cast<unsigned long long *>(bits + (I * kTile + q) * 2) = ls.row;
+        if (g == 0) store_pair(bits + (I * kTile + q) * 2, ls.row);
       } else if constexpr (BK < kTile) {
         for (int i = lane; i < 2 * NWb; i += 64) bits[I * 2 * NWb + i] = ls.bits[i];
       }
@@ -3502,7 +3519,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
       const Word all = tiles_of(0);
       if (lane < NWt) words[I * NWt + lane] = lane == 0 ? (unsigned)all : (unsigned)(all >> 32);
       if constexpr (PERPOS) {
-        if (g == 0) *reinterpret_cast<unsigned long long *>(bits + (I * kTile + q) * 2) = ls.row;
+        if (g == 0) store_pair(bits + (I * kTile + q) * 2, ls.row);
       } else if constexpr (BK < kTile) {
         for (int i = lane; i < 2 * NWb; i += 64) bits[I * 2 * NWb + i] = ls.bits[i];
       }
@@ -3574,9 +3591,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
       good &= near_key_tile<T, D, BK, PERPOS, true>(
           p, J, T0, NT, p0, lane, kf, vf, hpg, src, nm_k, dK + head_kv, dV + head_kv, [&]() __attribute__((always_inline)) { fetch(u); },
           [&]() __attribute__((always_inline)) {
-            unsigned *a = reinterpret_cast<unsigned *>(&kn), *b = reinterpret_cast<unsigned *>(&vn);
-#pragma unroll
-            for (unsigned i = 0; i < sizeof(kn) / 4; ++i) asm volatile("" : "+v"(a[i]), "+v"(b[i]));
+            Operands<T, D>::arrived(kn);
+            Operands<T, D>::arrived(vn);
           });
     }
     if (__builtin_expect(!good, 0)) {
@@ -3673,7 +3689,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
       if (el < min(2, NWt - 2 * w)) words[2 * w + el] = el == 0 ? (unsigned)m : (unsigned)(m >> 32);
     }
     if constexpr (PERPOS) {
-      if (eg == 0) *reinterpret_cast<unsigned long long *>(ws.sel_bits + ((size_t)kvh * NT * kTile + I * kTile + eq) * 2) = ls.row;
+      if (eg == 0) store_pair(ws.sel_bits + ((size_t)kvh * NT * kTile + I * kTile + eq) * 2, ls.row);
     } else if constexpr (BK < kTile) {
       for (int i = el; i < 2 * ls.NWb; i += 64) ws.sel_bits[((size_t)kvh * NT + I) * 2 * ls.NWb + i] = ls.bits[i];
     }
@@ -3774,9 +3790,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
       good &= near_key_tile<T, D, BK, PERPOS, PERPOS>(
           p, now, T0, NT, p0, lane, kf, vf, hpg, src, nm, dK + head_kv, dV + head_kv, [&]() __attribute__((always_inline)) { fetch(J); },
           [&]() __attribute__((always_inline)) {
-            unsigned *a = reinterpret_cast<unsigned *>(&kn), *b = reinterpret_cast<unsigned *>(&vn);
-#pragma unroll
-            for (unsigned i = 0; i < sizeof(kn) / 4; ++i) asm volatile("" : "+v"(a[i]), "+v"(b[i]));
+            Operands<T, D>::arrived(kn);
+            Operands<T, D>::arrived(vn);
           },
           turn_s[wv]);
     }
