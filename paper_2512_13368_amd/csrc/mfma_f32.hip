@@ -50,6 +50,7 @@
 
 #include "launch.h"
 #include "mfma_common.h"
+#include "near_host.h"
 
 namespace blossom {
 
@@ -519,21 +520,7 @@ __device__ __forceinline__ Word elements_from(int x, int r)
   const int n = 16 * ((x - r + 3) >> 2);
   return n >= 64 ? 0ull : ~0ull << n;
 }
-struct NearMasks {  // (made on the host)
-  Word own[4], next[4];  // short-term: the row's (key's) own tile, the tile before (after) it
-  NearMasks(const KParams &p, bool key_side)
-  {
-    for (int r = 0; r < 4; ++r) {
-      own[r] = next[r] = 0;
-      for (int l = 0; l < 64; ++l) {
-        const int x = 4 * (l >> 4) + r - (l & 15), d = key_side ? x : -x;  // distance between the lane's row and its element
-        auto sees = [&](int d) { return d >= 0 && (d < p.w || (p.sblk == 1 && is_pow2(d))); };
-        own[r] |= (Word)sees(d) << l;
-        next[r] |= (Word)sees(d + kTile) << l;
-      }
-    }
-  }
-};
+inline NearMasks near_masks(const KParams &p, bool key_side) { return NearMasks(p.w, p.sblk == 1, key_side); }
 
 // may any query of tile I see any key of tile J in the short-term branch (J <= I in the causal form)?
 __device__ __forceinline__ bool st_reaches(const KParams &p, int I, int J)
@@ -3865,15 +3852,7 @@ SmallPlan stream_plan(const KParams &p, int units, size_t words_per_wave, int pe
   const int NT = (p.L + kTile - 1) / kTile;
   SmallPlan s{false, false, kStreamWaves, 1, kStreamWaves * words_per_wave * sizeof(float)};
   if (per_simd > 0) {
-    int best = 0;
-    for (int parts = 1; parts <= (NT + s.waves - 1) / s.waves; ++parts) {
-      const int rounds = (units * parts + kCUs * per_simd - 1) / (kCUs * per_simd), tiles = (NT + s.waves * parts - 1) / (s.waves * parts);
-      const int cost = rounds * (2 * tiles + 1);
-      if (best == 0 || cost < best) {
-        best = cost;
-        s.parts = parts;
-      }
-    }
+    s.parts = parts_that_end_together(units, NT, s.waves, kCUs * per_simd);
     return s;
   }
   // enough workgroups for about two rounds of the chip's wavefronts (20 per CU), at most one tile per wavefront
@@ -3965,7 +3944,7 @@ static void launch_fwd_small_t(const KParams &p, const FwdArgs &a, hipStream_t s
     };
     const bool ordered = pl.res && order_by_length(p, grid, perpos) && (perpos || (grid <= 2 * kCUs && p.L >= 128));
     if (near_form(p) && !a.dense) {
-      const NearMasks nm(p, false);
+      const NearMasks nm = near_masks(p, false);
       auto go = [&](auto kernel) {
         want_lds(kernel, pl.lds);
         hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * pl.waves), pl.lds, st, (const T *)a.Q, (const T *)a.K,
@@ -4002,7 +3981,7 @@ static void launch_bwd_small_t(const KParams &p, const BwdArgs &a, const SmallWs
                            hpg, (int)pl.overlay, stages, p);
       };
       if (near_form(p)) {
-        const NearMasks nm_q(p, false), nm_k(p, true);
+        const NearMasks nm_q = near_masks(p, false), nm_k = near_masks(p, true);
         auto go = [&](auto kernel) {
           want_lds(kernel, pl.lds);
           hipLaunchKernelGGL(kernel, dim3((unsigned)(p.B * p.H / hpg)), dim3(64 * pl.waves), pl.lds, st, (const T *)a.Q,
@@ -4024,7 +4003,7 @@ static void launch_bwd_small_t(const KParams &p, const BwdArgs &a, const SmallWs
           hipLaunchKernelGGL(kernel, dim3((unsigned)(p.B * p.H * pl.parts)), dim3(64 * pl.waves), pl.lds, st, (const T *)a.Q,
                              (const T *)a.K, (const T *)a.V, a.valid_len, a.sel, a.gate_w, a.gate_b, (const float *)a.o_lt,
                              (const float *)a.o_st, a.lse_lt, a.lse_st, (const T *)a.dO, (T *)a.dQ, w, hpg, pl.parts, stages,
-                             NearMasks(p, false), p);
+                             near_masks(p, false), p);
         };
         perpos ? go(bwd_dq_near_kernel<T, D, BK, true>) : go(bwd_dq_near_kernel<T, D, BK, false>);
         if (launch_failed()) return;
@@ -4034,7 +4013,7 @@ static void launch_bwd_small_t(const KParams &p, const BwdArgs &a, const SmallWs
         auto go = [&](auto kernel) {
           hipLaunchKernelGGL(kernel, dim3((unsigned)(p.B * p.H / hpg * pk.parts)), dim3(64 * pk.waves), 0, st, (const T *)a.Q,
                              (const T *)a.K, (const T *)a.V, a.valid_len, a.gate_w, (const T *)a.dO, w, (T *)a.dK, (T *)a.dV, hpg,
-                             pk.parts, NearMasks(p, true), p);
+                             pk.parts, near_masks(p, true), p);
         };
         perpos ? go(bwd_dkv_near_kernel<T, D, BK, true>) : go(bwd_dkv_near_kernel<T, D, BK, false>);
       }
