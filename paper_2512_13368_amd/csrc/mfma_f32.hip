@@ -3813,18 +3813,35 @@ struct SmallPlan {
 };
 // LDS up to which a workgroup holds whole heads: two of them per CU at d = 32, three below, whose lighter walks want the wavefronts
 // (a training step, us, by limit 76 / 50 / 40 KB: B=300 H=8 d=16 L=300 296 / 280 / 277, L=450 446 / 422 / 421, d=8 L=450 289 / 288 / 297,
-// L=600 455 / 414 / 416; B=32 d=8 L=1000 110 / 98 / -; B=1024 H=2 d=32 L=200 339 / 410 / 411)
+// L=600 455 / 414 / 416; B=32 d=8 L=1000 110 / 98 / -; B=1024 H=2 d=32 L=200 339 / 410 / 411; in the near form 226 / 209 / 207, 348 / 336 /
+// 336, 238 / 237 / 227, 339 / 287 / 287, 85 / 76 / 76, 231 / 300 / 299)
 constexpr size_t kTwoPerCU = 76 * 1024;
 size_t small_lds_limit(const KParams &p) { return p.d == 32 ? kTwoPerCU : 44 * 1024; }
 // Few heads: eight wavefronts each, a head's latency counts.  Many: four, whose shares are longer and better balanced (always a
-// multiple of the four SIMDs: with five or six wavefronts the backward took 1.4 times as long).
+// multiple of the four SIMDs: with five or six wavefronts the backward took 1.4 times as long).  The near form's lighter walks are
+// many earlier, from more than two heads to a CU on, the longer the head (at d = 32, where fewer fit a CU, short ones alone): a training
+// step, fp32, lengths U[L/10,L], eight wavefronts / four, us:
+//   heads               400                 600                1000                1600
+//   d = 8          L=60   22.9 / 22.3   L=100  35.2 / 32.5  L=200  59.4 / 54.2  L=300 118.5 / 104.6
+//                 L=150   31.1 / 34.8   L=300  55.9 / 62.5  L=300  78.8 / 76.9
+//   d = 16        L=100   30.2 / 30.3   L=100  38.6 / 35.5  L=150  59.6 / 54.1  L=200 105.4 /  93.0
+//                 L=200   38.7 / 44.5   L=200  53.1 / 52.9  L=200  70.7 / 64.9
+//   d = 32         L=60   30.8 / 30.2    L=60  43.6 / 33.9   L=60  51.3 / 40.0   L=60  78.7 /  57.3
+//                 L=200   58.4 / 67.0   L=100  54.3 / 57.7  L=200   107 /  115  L=200   165 /   176
+//   per position  L=100   40.5 / 44.1   L=100  55.1 / 49.6  L=150  88.5 / 80.6  L=200   173 /   150
+//                 L=200   62.8 / 80.5   L=150  61.3 / 65.0  L=200   111 /  107
 bool many_heads(int units) { return units >= 2048; }
-int res_waves(int units) { return many_heads(units) ? 4 : 8; }
+int res_waves(const KParams &p, int units, bool near)
+{
+  return many_heads(units) || (near && units > 2 * kCUs && (p.d == 32 ? p.L <= 64 : 5 * p.L <= units)) ? 4 : 8;
+}
 // More than one head to a CU (with one the order is of no account), and not so many that they average out.  The forward, a third of
-// the backward's time, only where the order pays for itself: two heads to a CU of at least 128 positions, or several query heads a
-// workgroup (B=250 H=8 L=200 d=16 44.2 us in turn, 47.9 by length; B=128 H=4 L=60 d=32 9.9 and 11.3; per position B=500 80.0 and 73.6).
+// the backward's time, only where the order pays for itself: two heads to a CU of at least 128 positions (in the near form 150, or 112 at
+// d = 32), or several query heads a workgroup (B=250 H=8 L=200 d=16 44.2 us in turn, 47.9 by length; B=128 H=4 L=60 d=32 9.9 and 11.3; per
+// position B=500 80.0 and 73.6.  In the near form 31.7 and 32.9, 8.3 and 9.1; B=128 H=4 d=16 L=128 9.0 and 9.3, L=150 10.5 and 10.2, d=32 L=100
+// 12.1 and 12.2, L=128 13.2 and 12.9; per position B=250 38.4 and 31.9).
 // Short heads end before the order is found, and the more heads a CU takes one after another the more often it is found and the less
-// it gives, so both of them bound the length from which it is used (a training step, fp32, lengths U[L/10,L], in order / in turn, us):
+// it gives, so both of them bound the length from which it is used (a training step, fp32, lengths U[L/10,L], by length / in turn, us):
 //   units          300                    600                    1200                   1800
 //   d = 8   L=60   26.6 / 26.6   L=100   41.8 / 41.0   L=100   61.7 / 61.2   L=130   92.6 / 90.8
 //          L=100   31.6 / 32.2   L=130   46.8 / 48.3   L=130   67.9 / 69.3   L=200  110.9 / 113.7
@@ -3835,13 +3852,33 @@ int res_waves(int units) { return many_heads(units) ? 4 : 8; }
 //   per position, in both passes
 //           L=40   41.6 / 42.5    L=40   56.0 / 55.3    L=70  103.9 / 101.7  L=100  161 / 158
 //           L=70   49.8 / 53.3    L=70   70.1 / 72.1   L=100  118.3 / 120.7  L=130  189 / 191
-int shortest_ordered(const KParams &p, int units, bool perpos)
+// The near form with eight wavefronts:
+//           400 heads              600                   1000                  1600
+//   d = 8   L=60   22.9 / 22.1   L=150   37.8 / 39.0   L=300   78.8 / 88.8
+//          L=100   27.8 / 28.5
+//   d = 16  L=60   24.2 / 23.9   L=150   43.0 / 45.7
+//          L=100   30.2 / 31.6
+//   d = 32  L=60   30.8 / 31.8   L=100   54.3 / 57.5   L=100   70.4 / 73.0   L=100   108 / 105
+//          L=200   58.4 / 71.2   L=200   78.4 / 86.9   L=200    107 / 121    L=150   136 / 142
+//   per position
+//           L=60   32.5 / 32.2   L=150   61.3 / 68.7
+//          L=100   40.5 / 48.6
+// and with four:
+//   d = 8                         L=60   24.6 / 24.3    L=60   27.6 / 27.6    L=60  38.2 / 37.2
+//                                L=100   32.5 / 35.1   L=100   38.8 / 40.5   L=100  53.7 / 55.5
+//   d = 16                        L=60   25.8 / 26.3    L=60   29.4 / 29.7    L=60  41.1 / 40.7
+//                                L=100   35.5 / 39.0   L=100   43.6 / 45.8   L=100  60.0 / 62.0
+//   d = 32                        L=60   33.9 / 35.3    L=60   40.0 / 41.6    L=60  57.3 / 60.3
+//   per position                  L=60   35.1 / 37.8    L=60   42.9 / 44.2    L=60  60.0 / 61.6
+int shortest_ordered(const KParams &p, int units, bool perpos, bool near)
 {
+  if (near && res_waves(p, units, true) == 4) return perpos ? 50 : p.d == 32 ? 45 : 50 + units / 40;
+  if (near && p.d == 32 && !perpos) return 25 + units / 16;
   return perpos ? 30 + units / 18 : p.d == 32 ? 30 + units / 25 : (p.d == 16 ? 60 : 80) + units / 20;
 }
-bool order_by_length(const KParams &p, int units, bool perpos)
+bool order_by_length(const KParams &p, int units, bool perpos, bool near)
 {
-  return units > kCUs && !many_heads(units) && p.B <= kOrderRows && p.L >= shortest_ordered(p, units, perpos);
+  return units > kCUs && !many_heads(units) && p.B <= kOrderRows && p.L >= shortest_ordered(p, units, perpos, near);
 }
 // per_simd: wavefronts a SIMD holds of a kernel whose tiles cost about the same (dQ of the near form).  Its workgroups then come in
 // the number that ends together: rounds of the chip times a wavefront's tiles and its start, half a tile.  (us, by the first rule / so:
@@ -3860,11 +3897,11 @@ SmallPlan stream_plan(const KParams &p, int units, size_t words_per_wave, int pe
   s.parts = std::max(1, std::min((NT + s.waves - 1) / s.waves, want));
   return s;
 }
-SmallPlan fwd_plan(const KParams &p, int dtype, bool perpos, int hpg)
+SmallPlan fwd_plan(const KParams &p, int dtype, bool perpos, int hpg, bool near)
 {
   const size_t rows = (size_t)(p.L + kTile - 1) / kTile * kTile;
   const int units = p.B * p.H / hpg;
-  SmallPlan s{true, false, res_waves(units), 1, 0};
+  SmallPlan s{true, false, res_waves(p, units, near), 1, 0};
   s.lds = (2 * rows * lds_row(dtype == 1, p.d) + (size_t)s.waves * lt_words(p, perpos)) * sizeof(float);
   if (p.nq == p.NB && s.lds <= small_lds_limit(p)) return s;
   s = stream_plan(p, p.B * p.H, lt_words(p, perpos));
@@ -3876,7 +3913,8 @@ SmallPlan bwd_plan(const KParams &p, int dtype, bool perpos, int hpg)
   const int units = p.B * p.H / hpg;
   // with many heads four small workgroups per CU beat two that hold everything (B=2048 H=8 L=200 d=16: 672 against 917 us); with so
   // few that no CU has more than two to hold, everything fits beside a second one (gradients at B=82 H=4 L=174 d=16: 50.8 us with
-  // everything in LDS, 52.3 with Q and dO read again; B=40 H=8 L=170 d=16, a whole step 47.5 and 48.4)
+  // everything in LDS, 52.3 with Q and dO read again; B=40 H=8 L=170 d=16, a whole step 47.5 and 48.4.  Whole steps in the near form: 749 against
+  // 946, 34.6 and 35.4, 35.2 and 35.8; B=128 H=4 d=8 L=350 48.3 and 49.0)
   // A limit is about what both forms hold; the near form's gate rows and sums, 1 to 9 KB, come on top as long as the same number of
   // workgroups fits a CU.  (Counted in, they sent the longest heads the other way: a training step, us, in LDS / streamed, fp32 at L=240 with
   // B=64 H=8 d=16 52.6 / 62.7, B=125 H=8 d=16 87.1 / 95.5, per position with B=64 H=4 d=32 101 / 112, bf16 at B=600 H=4 L=416 d=32 404 / 466;
@@ -3887,7 +3925,7 @@ SmallPlan bwd_plan(const KParams &p, int dtype, bool perpos, int hpg)
     return (size_t)lay.held * sizeof(float) <= limit && s.lds <= (limit == kTwoPerCU ? 79 * 1024 : 52 * 1024);
   };
   for (int overlay = many_heads(units) ? 1 : 0; overlay < 2; ++overlay) {
-    SmallPlan s{true, overlay != 0, res_waves(units), 1, 0};
+    SmallPlan s{true, overlay != 0, res_waves(p, units, near_form(p)), 1, 0};
     if (!fits(s, small_lds_limit(p))) continue;
     SmallPlan all{true, false, s.waves, 1, 0};
     return s.overlay && units <= 2 * kCUs && fits(all, kTwoPerCU) ? all : s;
@@ -3932,7 +3970,8 @@ static void launch_fwd_small_t(const KParams &p, const FwdArgs &a, hipStream_t s
 {
   const bool perpos = a.kv_groups > 0;
   const int hpg = perpos ? p.H / a.kv_groups : 1;
-  const SmallPlan pl = fwd_plan(p, std::is_same<T, float>::value ? 0 : 1, perpos, hpg);
+  const bool near = near_form(p) && !a.dense;
+  const SmallPlan pl = fwd_plan(p, std::is_same<T, float>::value ? 0 : 1, perpos, hpg, near);
   const int grid = p.B * p.H / (pl.res ? hpg : 1) * pl.parts;
   with_small_dims(p, [&](auto dim, auto bk) {
     constexpr int D = decltype(dim)::value, BK = decltype(bk)::value;
@@ -3942,8 +3981,9 @@ static void launch_fwd_small_t(const KParams &p, const FwdArgs &a, hipStream_t s
                          (const T *)a.V, a.valid_len, a.dense ? nullptr : a.sel, a.gate_w, a.gate_b, (T *)a.O,
                          (float *)a.o_lt, (float *)a.o_st, a.lse_lt, a.lse_st, hpg, pl.parts, p);
     };
-    const bool ordered = pl.res && order_by_length(p, grid, perpos) && (perpos || (grid <= 2 * kCUs && p.L >= 128));
-    if (near_form(p) && !a.dense) {
+    const int shortest = !near ? 128 : p.d == 32 ? 112 : 150;
+    const bool ordered = pl.res && order_by_length(p, grid, perpos, near) && (perpos || (grid <= 2 * kCUs && p.L >= shortest));
+    if (near) {
       const NearMasks nm = near_masks(p, false);
       auto go = [&](auto kernel) {
         want_lds(kernel, pl.lds);
@@ -3989,11 +4029,11 @@ static void launch_bwd_small_t(const KParams &p, const BwdArgs &a, const SmallWs
                              (const float *)a.o_st, a.lse_lt, a.lse_st, (const T *)a.dO, (T *)a.dQ, (T *)a.dK, (T *)a.dV, w.partial,
                              hpg, (int)pl.overlay, stages, nm_q, nm_k, p);
         };
-        if (order_by_length(p, p.B * p.H / hpg, perpos)) perpos ? go(bwd_near_kernel<T, D, BK, true, true>) : go(bwd_near_kernel<T, D, BK, false, true>);
+        if (order_by_length(p, p.B * p.H / hpg, perpos, true)) perpos ? go(bwd_near_kernel<T, D, BK, true, true>) : go(bwd_near_kernel<T, D, BK, false, true>);
         else perpos ? go(bwd_near_kernel<T, D, BK, true, false>) : go(bwd_near_kernel<T, D, BK, false, false>);
         return;
       }
-      if (order_by_length(p, p.B * p.H / hpg, perpos)) perpos ? go(bwd_res_kernel<T, D, BK, true, true>) : go(bwd_res_kernel<T, D, BK, false, true>);
+      if (order_by_length(p, p.B * p.H / hpg, perpos, false)) perpos ? go(bwd_res_kernel<T, D, BK, true, true>) : go(bwd_res_kernel<T, D, BK, false, true>);
       else perpos ? go(bwd_res_kernel<T, D, BK, true, false>) : go(bwd_res_kernel<T, D, BK, false, false>);
       return;
     }
