@@ -1804,10 +1804,18 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
       float x_lt = kNegInfF, x_st = kNegInfF;
       auto each = [&](auto f) __attribute__((always_inline)) {
         for (int w = T0 >> 6; w <= I >> 6; ++w) {
-          const Word m = tiles_of(w);
-          for (int t = max(T0, 64 * w); t <= min(I, 64 * w + 63); ++t) {
-            const bool in_lt = (m >> (t & 63)) & 1ull;
-            if (!in_lt && t < I - 1 && !(p.sblk == 1 && __popc(I - t) == 1)) continue;
+          const Word lt = tiles_of(w);
+          // the tiles of either branch, from T0 to I: of the short-term one those at distances 0 and 1 and, with all of Eq. 15, 2^r
+          Word m = lt;
+          for (int d = 0; I - d >= T0; d = d ? 2 * d : 1) {
+            if ((I - d) >> 6 == w) m |= 1ull << ((I - d) & 63);
+            if (d == 1 && p.sblk != 1) break;
+          }
+          if (w == T0 >> 6) m &= ~0ull << (T0 & 63);
+          if (w == I >> 6) m &= ~0ull >> (63 - (I & 63));
+          for (; m; m &= m - 1) {
+            const int t = 64 * w + __builtin_ctzll(m);
+            const bool in_lt = (lt >> (t & 63)) & 1ull;
             Kr.op(t, kf);
             const f32x4 s = logits() * kc;
             const int key0 = t * kTile + 4 * g;
