@@ -1064,20 +1064,28 @@ struct LtSel {
     else return true;
   }
 };
+// the OR over the wavefront
+__device__ __forceinline__ unsigned or_all(unsigned x)
+{
+  x = LtSel<kTile, true>::or_row(x);
+  u32x2_t a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  const unsigned y = a[0] | a[1];
+  a = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+  return __builtin_amdgcn_readfirstlane(a[0] | a[1]);
+}
 // the same of a tile of the near form with one block to a tile: the entries stay in registers, 64 at a time, lane e holding entry e
 struct PickedTiles {
   const int *rows;
   int k, J;
-  // tiles 64w .. 64w + 63, whatever else the entries name
+  // tiles 64w .. 64w + 63, whatever else the entries name: every lane's bit, and their OR over the wavefront.  (Entry by entry, six scalar
+  // instructions each, a step at B=2 H=2 L=600 d=16 took 40.6 us with lists of 9 and 60.0 with lists of 35; 39.7 and 57.7 so, of 4 the same.)
   __device__ __forceinline__ Word word(int w, int lane) const
   {
     Word m = 0;
-    auto add = [&](int x, int count) __attribute__((always_inline)) {
-      for (Word b = __ballot((x >> 6) == w && lane < count); b; b &= b - 1) m |= 1ull << (__builtin_amdgcn_readlane(x, __builtin_ctzll(b)) & 63);
-    };
+    auto add = [&](int x, int count) __attribute__((always_inline)) { m |= (x >> 6) == w && lane < count ? 1ull << (x & 63) : 0ull; };
     add(J, k);  // (apart from the others: a load in the loop, though never issued, would have this wait for all that are on their way)
     for (int e0 = 64; e0 < k; e0 += 64) add(rows[min(e0 + lane, k - 1)], k - e0);
-    return m;
+    return (Word)or_all((unsigned)(m >> 32)) << 32 | or_all((unsigned)m);
   }
 };
 __host__ __device__ inline int lt_words(const KParams &p, bool perpos)
