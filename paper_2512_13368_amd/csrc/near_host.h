@@ -30,10 +30,14 @@ struct NearMasks {
 // Workgroups per unit of a launch whose tiles cost about the same: the number whose rounds of the chip (`slots` workgroups at a time)
 // times a wavefront's tiles and its start, half a tile, are least, the smallest of several.  For a given number of tiles a wavefront
 // the smallest number of workgroups is the one to look at.  (L = 16384: 0.6 us with every number of workgroups, so 0.3.)
+// No more than kMostTiles a wavefront: rows of different lengths, which the host does not know, end together only where the workgroups are
+// many.  (Backward at H=8, us, without that bound / with it, full rows and lengths U[L/10,L]: B=32 d=32 L=1600 503 / 505 and 372 / 339, d=32
+// L=2200 690 / 698 and 390 / 343, d=16 L=2000 187 / 186 and 139 / 133, d=8 L=2000 128 / 130 and 94 / 95.)
+constexpr int kMostTiles = 5;
 inline int parts_that_end_together(int units, int tiles, int waves, int slots)
 {
   int best = 0, parts = 1;
-  for (int p = 1;;) {
+  for (int p = (tiles + waves * kMostTiles - 1) / (waves * kMostTiles);;) {
     const int each = (tiles + waves * p - 1) / (waves * p);
     const int cost = (units * p + slots - 1) / slots * (2 * each + 1);
     if (best == 0 || cost < best) {

@@ -19,6 +19,7 @@ static int parts_by_trial(int units, int tiles, int waves, int slots)
   int best = 0, parts = 0;
   for (int p = 1; p <= (tiles + waves - 1) / waves; ++p) {
     const int rounds = (units * p + slots - 1) / slots, each = (tiles + waves * p - 1) / (waves * p);
+    if (each > kMostTiles) continue;
     if (best == 0 || rounds * (2 * each + 1) < best) best = rounds * (2 * each + 1), parts = p;
   }
   return parts;
