@@ -102,7 +102,8 @@ typedef struct {
   int32_t last_block_only; /* 1: serving mode (Appendix C: only the representation of the last
                              position is scored).  blossom_select_blocks writes only the
                              selection row of the last query block, blossom_attn_fwd only the
-                             rows of that block (O, and the saved tensors if asked for);
+                             rows of that block (O, and the saved tensors if asked for), with
+                             the same bits as a call over all query blocks, whatever the batch;
                              everything else in those buffers is left untouched.  Backward
                              calls return BLOSSOM_ERR_UNSUPPORTED.  0: all query blocks.          */
 } blossom_params;

@@ -453,8 +453,8 @@ __global__ __launch_bounds__(64 * kInvWaves) void inverse_list_kernel(const int 
 // next rows are requested before the current ones are worked on.  B=128 H=4 L=1024 d=64, lengths U[100,1024]: 77 -> 71 us, 59 with the
 // heads to the XCDs in turn; B=16 H=8 L=8192: 183 -> 175 us (5.7 TB/s).  Since it writes no gradients of the branches for the
 // matrix-core kernels, 52 and 148 us; with chunks of 64 rows, whose last ones leave fewer CUs idle than those of 128, and the lists'
-// rows eight at a time, 48 and 142; with a chunk's two steps written out 45 and 124 (47 and 131 in the same run; 6.6 TB/s).  What a short
-// batch loses is its padding: workgroups that find no valid row, and the last ones of each head.
+// rows eight at a time, 48 and 142; with a chunk's two steps written out 45 and 124 (47 and 131 in the same run; 5.9 TB/s of
+// the 738 MB that it moves there).  What a short batch loses is its padding: workgroups that find no valid row, and the last ones of each head.
 // The gate-weight partials accumulate in registers and meet in LDS in a fixed order.
 // =============================================================================================
 // The first `lists` workgroups make the inverse selection lists instead: a chain of latencies (8 us at B=128 H=4 L=1024, 26 at B=16
@@ -591,8 +591,8 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(const float *__restrict__
 #pragma unroll
   for (int e = 0; e < CPL; ++e) acc_l[e] = acc_s[e] = 0.0f;
 
-  // (both steps written out: 86 instead of 105 registers at d = 64, where the copies of a loop keep two sets of rows alive to its end:
-  // five wavefronts a SIMD instead of four)
+  // (both steps written out, at d = 32 and 64; below, a chunk is one step: 86 instead of 105 registers at d = 64 in bf16, 90 instead of 109 in
+  // fp32, where the copies of a loop keep two sets of rows alive to its end: five wavefronts a SIMD instead of four)
 #pragma unroll
   for (int base = 0; base < ROWS; base += RPS) {
     const int i = row0 + base;

@@ -30,8 +30,9 @@
 // EXPONENTIALS WITHOUT A RUNNING MAXIMUM.  A walk takes exp2 of the logits themselves, one exponential for both
 // branches, and keeps the largest |logit| it met (of masked keys too): up to 60 (log2 units) nothing overflows or loses
 // accuracy in fp32.  Beyond that (or if an output left fp32's range) the walk is repeated with the two row maxima,
-// found by a walk of their own, as references.  With every tile beyond it the forward takes 46 us instead of 22 at B=256
-// H=2 L=200 d=32, 560 instead of 292 at B=2048 H=8 L=200 d=16, 192 instead of 56 at B=32 H=8 L=2000 d=8.
+// found by a walk of their own, as references.  With every tile beyond it the forward of the near form (see there) takes 29 us instead of 16
+// at B=256 H=2 L=200 d=32, 493 instead of 185 at B=2048 H=8 L=200 d=16, 184 instead of 43 at B=32 H=8 L=2000 d=8; the general one there 30
+// and 17, 529 and 243, 191 and 51.
 //
 // VALUES THAT ARE NOT FINITE.  A walk multiplies whole tiles, so a masked element adds zero times whatever the tile holds: a NaN
 // or an infinity, in a row of the padding too, would reach every row of its tile.  Such a result is not finite itself,
@@ -75,7 +76,10 @@ struct Geo {
 };
 
 // both halves, the lower one first; at: 8-byte aligned
-__device__ __forceinline__ void store_pair(unsigned *at, unsigned long long x) { *reinterpret_cast<uint2 *>(at) = make_uint2((unsigned)x, (unsigned)(x >> 32)); }
+__device__ __forceinline__ void store_pair(unsigned *at, unsigned long long x)
+{
+  *reinterpret_cast<uint2 *>(at) = make_uint2((unsigned)x, (unsigned)(x >> 32));
+}
 // CPL consecutive elements as floats
 template <int N>
 __device__ __forceinline__ void load_n(const float *p, float (&o)[N])
@@ -1544,14 +1548,15 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
 // =============================================================================================
 // A query tile walks the tile before, itself, its long-term tiles below (the first valid one, which may hold padding, first) and the
 // diagonals.  (The tile before first: its terms are the smaller ones, and what is added after a large sum is rounded at that sum's size.  The
-// other way round o_st of bf16 at d = 32 under mask block 1 errs 1.03 times as much.)  Bound by the latency of a wavefront's own chain at three to four wavefronts a SIMD (half of their time went on waits,
-// 566 vector and 420 scalar instructions a tile) rather than by a pipe, so:
+// other way round o_st of bf16 at d = 32 under mask block 1 errs 1.03 times as much.)
+// Bound by the latency of a wavefront's own chain at three to four wavefronts a SIMD (half of their time went on waits, 566 vector and
+// 420 scalar instructions a tile) rather than by a pipe, so:
 //  - What a tile needs from memory is requested a tile ahead and has arrived before the stores go out: loads and stores finish in
 //    order, and a wait for loads issued behind a tile's stores was a wait for those stores.
 //  - The selection is read from registers, entry by entry, where LDS words were cleared, set by atomics and read back.
 //  - Masks are scalars, the walk is three straight pieces, row sums and the lse of both branches are closed together.
-// us, with fwd_small_kernel / with this: B=256 H=2 L=200 d=32 19.6 / 17.8, B=2048 H=8 L=200 d=16 284 / 210, per position at d=8 240 /
-// 199, B=32 H=8 L=2000 d=8 (streamed) 60.5 / 53.5; selection + forward at B=4 H=2 L=50 d=32 10.2 / 9.3.
+// us, with fwd_small_kernel / with this: B=256 H=2 L=200 d=32 19.5 / 18.1, B=2048 H=8 L=200 d=16 283 / 219, per position at d=8 238 /
+// 194, B=32 H=8 L=2000 d=8 (streamed) 58.8 / 52.9; selection + forward at B=4 H=2 L=50 d=32 10.1 / 9.3.
 template <typename T, int D, int BK, bool PERPOS, bool RES, bool ORDER>
 __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(D == 32 || (RES && PERPOS) ? 4 : 5))) void fwd_near_kernel(
     const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V, const int *__restrict__ valid_len,
@@ -2579,7 +2584,7 @@ __device__ __forceinline__ void query_tiles_carefully(const KParams &p, int firs
 
 // The gate gradient sums of a head's rows that a wavefront takes, in registers until leave().  d = 32: the walk needs the seventeen
 // registers, so every tile's sums over its rows go to LDS at once (mine[2D + 1], cleared by the caller): spilled registers in bf16 18 -> 1,
-// with two blocks to a tile in fp32 53 -> 24, a whole training step at B=180 H=4 L=150 d=32 b=8 fp32 98.5 us with them in registers, 89.2 so.
+// with two blocks to a tile in fp32 53 -> 20, a whole training step at B=180 H=4 L=150 d=32 b=8 fp32 98.5 us with them in registers, 89.2 so.
 template <int D>
 struct NearGateSums {
   static constexpr int CPL = Geo<D>::CPL;
@@ -3455,8 +3460,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
 // As bwd_res_kernel, and as in fwd_near_kernel: what the next tile needs is on its way during the walk and has arrived before the stores
 // go out, masks are scalars, the selection stays in registers.  The (tile, head) pairs of a group are dealt out over all of its heads
 // without a barrier between them, there and back; Q and dO are requested before the barrier that closes K and V; the gate row lies
-// in LDS.  us, with bwd_res_kernel / with this: B=2048 H=8 L=200 d=16 605 / 550 (vector instructions 1390 a pair of tiles before),
-// per position at d=8 561 / 507, B=256 H=2 L=200 d=32 44.4 / 40.0.
+// in LDS.  us, with bwd_res_kernel / with this: B=2048 H=8 L=200 d=16 603 / 550 (vector instructions 1390 a pair of tiles before),
+// per position at d=8 560 / 502, B=256 H=2 L=200 d=32 43.8 / 39.4.
 template <typename T, int D, int BK, bool PERPOS, bool ORDER>
 __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(4))) void bwd_near_kernel(
     const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V, const int *__restrict__ valid_len,
@@ -3637,8 +3642,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
 // backward, heads streamed from memory, THE NEAR FORM
 // =============================================================================================
 // As bwd_dq_small_kernel and bwd_dkv_small_kernel, and as bwd_near_kernel.  Tiles are turned in LDS (turn_floats): dK/dV issued sixteen
-// vector-memory instructions a tile and waited for the address unit, five now.  us, before / now, B=32 H=8 L=2000 d=8: dQ 70 / 64, dK/dV
-// 104 / 83; a whole step 240 / 202, at B=16 H=8 L=1500 d=16 150 / 132.  (The forward's values turned the same way: 53.3 / 52.5 and, at
+// vector-memory instructions a tile and waited for the address unit, five now.  us, with those / with these, B=32 H=8 L=2000 d=8: dQ 69 / 63, dK/dV
+// 101 / 82; a whole step 241 / 200.  (The forward's values turned the same way: 53.3 / 52.5 and, at
 // d=16, slower: its five instructions a tile stay.)
 template <typename T, int D, int BK, bool PERPOS>
 __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(D == 8 ? 5 : 4))) void bwd_dq_near_kernel(
